@@ -21,8 +21,6 @@
 //     operand (8 keys of one head-dim column per lane) comes from the LDS transposing read.
 //   * O and l are rescaled lazily: only when a row max has outgrown the exponent reference.
 //   * exp is taken in base 2 with scale * log2(e) folded into one FMA.
-#include <atomic>
-
 #include "usp_common.h"
 #include "prefetch_copy.h"
 
@@ -1258,20 +1256,6 @@ usp_status launch_attn_arrive_reset(int* arrive, hipStream_t st) {
 }
 
 namespace {
-// More than 64 KB of dynamic LDS has to be allowed per kernel, and the setting belongs to the device
-// that is current when it is made: once per (kernel, device ordinal below 64), every launch beyond.
-template <void (*kKernel)(AttnStep)>
-hipError_t allow_large_lds(int bytes) {
-  static std::atomic<uint64_t> done{0};
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e != hipSuccess) return e;
-  const bool tracked = dev >= 0 && dev < 64;
-  if (tracked && ((done.load(std::memory_order_acquire) >> dev) & 1u) != 0) return hipSuccess;
-  e = hipFuncSetAttribute(reinterpret_cast<const void*>(kKernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-  if (e == hipSuccess && tracked) done.fetch_or((uint64_t)1 << dev, std::memory_order_release);
-  return e;
-}
 template <bool kSplit, bool kExt, bool kMulti = false, bool kNoDead = false, bool kHalfD = false>
 usp_status launch_pp_d(const AttnStep& s, unsigned wgs, hipStream_t st) {
   static_assert(kLdsBytes >= (int)sizeof(SmemPPExt) && kLdsBytes <= 160 * 1024, "LDS plan");

@@ -1,0 +1,460 @@
+// Attention for every shape the bf16 d = 128 / 64 kernels do not take: fp32 inputs, other head
+// dimensions (multiples of 8 up to 256), FP8 K/V with those.  fp32 arithmetic throughout, on the
+// matrix cores.  For one KV chunk (FastUSP section 2.2 and 2.2.2),
+//   O_r = softmax(q K^T * scale) V,   lse_r = log sum_j exp(q.k_j * scale),
+// and over several chunks in one launch, each folded into the carried (O, lse) by the merge equations
+// of section 3.4 with the operations a launch per chunk would perform (same bits).
+//
+//   * A wave owns 16 queries.  Scores are computed transposed, S^T = K Q^T, so that a lane owns one
+//     query (column r = lane % 16) and four consecutive keys per 16-key block, and P^T in accumulator
+//     layout is the B operand of O^T += V^T P^T as it stands.
+//   * bf16 Q (engine Bf16Q): v_mfma_f32_16x16x32_bf16.  Products of bf16 values (and of E4M3 codes, which
+//     are bf16 values) are exact in fp32; P is not rounded but split into three bf16 parts that add up
+//     to its 24 bits, so P.V is three exact products instead of one.  fp32 Q (engine F32Q):
+//     v_mfma_f32_16x16x4_f32.
+//   * Per-key factors: FP8 scales of K multiply the fp32 scores, those of V multiply P.
+//   * 64-key tiles are staged in LDS by the whole work-group, the next tile's global loads being in
+//     flight while the current one is computed on.  Pitches are odd multiples of 16 bytes (K) and of 32
+//     bytes (V of Bf16Q, read transposed), or d + 4 words (F32Q): no bank conflicts by construction.
+//   * kKW waves share the 16 queries and take 64 / kKW keys of every tile each, their partial results
+//     being combined through LDS at the end of a chunk: for calls with few query blocks.
+//
+// What bounds it: a work-group's serial chain per tile (stage, barrier, scores, softmax, P.V: 1.8 us at bf16
+// d = 72, of which the matrix cores are busy 0.3), hidden in part by a second work-group on the CU; fp32 is
+// bound by the fp32 matrix rate from about 256 work-groups on.  B=2 H=16 S=1024 d=72 bf16: 39 us = 249 TFLOP/s;
+// one wave per query row with scalar products, which this replaced, took 855 us.  Two chunks of 128 keys,
+// H=2 Sq=128 d=64 fp32: one launch of 9.4 us for two of 12.
+#pragma once
+#include <type_traits>
+
+#include "usp_common.h"
+#include "prefetch_copy.h"
+
+namespace usp {
+namespace tile {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int kThreads = 256;
+constexpr int kTile = 64;          // keys per tile
+
+// maximum / sum over the four lanes r, r + 16, r + 32, r + 48 that hold one query
+__device__ __forceinline__ float group_max(float x) {
+  auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+__device__ __forceinline__ float group_sum(float x) {
+  auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+  auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+
+// Eight consecutive elements of a K / V row in flight from global memory, and their form in LDS.
+struct UnitBf16 {
+  typedef bf16_t elt;
+  u32x4 w;
+  __device__ __forceinline__ void zero() { w = u32x4{0u, 0u, 0u, 0u}; }
+  __device__ __forceinline__ void load(const elt* p) { w = *reinterpret_cast<const u32x4*>(p); }
+  __device__ __forceinline__ u32x4 as_bf16() const { return w; }
+};
+struct UnitF8 {
+  typedef uint8_t elt;
+  u32x2 w;
+  __device__ __forceinline__ void zero() { w = u32x2{0u, 0u}; }
+  __device__ __forceinline__ void load(const elt* p) { w = *reinterpret_cast<const u32x2*>(p); }   // rows are 8-byte aligned
+  __device__ __forceinline__ void as_f32(f32x4& a, f32x4& b) const {
+    const f32x2 c0 = __builtin_amdgcn_cvt_pk_f32_fp8((int)w[0], false), c1 = __builtin_amdgcn_cvt_pk_f32_fp8((int)w[0], true);
+    const f32x2 c2 = __builtin_amdgcn_cvt_pk_f32_fp8((int)w[1], false), c3 = __builtin_amdgcn_cvt_pk_f32_fp8((int)w[1], true);
+    a = f32x4{c0[0], c0[1], c1[0], c1[1]};
+    b = f32x4{c2[0], c2[1], c3[0], c3[1]};
+  }
+  __device__ __forceinline__ u32x4 as_bf16() const {   // exact: every E4M3 value is a bf16 value
+    f32x4 a, b;
+    as_f32(a, b);
+    return u32x4{pack_bf16x2(a[0], a[1]), pack_bf16x2(a[2], a[3]), pack_bf16x2(b[0], b[1]), pack_bf16x2(b[2], b[3])};
+  }
+};
+struct UnitF32 {
+  typedef float elt;
+  f32x4 a, b;
+  __device__ __forceinline__ void zero() { a = b = f32x4{0.0f, 0.0f, 0.0f, 0.0f}; }
+  __device__ __forceinline__ void load(const elt* p) {
+    a = *reinterpret_cast<const f32x4*>(p);
+    b = *reinterpret_cast<const f32x4*>(p + 4);
+  }
+  __device__ __forceinline__ void as_f32(f32x4& x, f32x4& y) const { x = a; y = b; }
+};
+
+// p0, p1 as three bf16 pairs whose sums are p0 and p1 exactly (8 + 8 + 8 significant bits)
+__device__ __forceinline__ void split3(float p0, float p1, uint32_t& hi, uint32_t& mid, uint32_t& lo) {
+  hi = pack_bf16x2(p0, p1);
+  const float a0 = p0 - __uint_as_float(hi << 16), a1 = p1 - __uint_as_float(hi & 0xffff0000u);
+  mid = pack_bf16x2(a0, a1);
+  lo = pack_bf16x2(a0 - __uint_as_float(mid << 16), a1 - __uint_as_float(mid & 0xffff0000u));
+}
+
+// kD: head dimension rounded up to the kernel's size (columns past s.d are zero); kMB: 16-key blocks per wave
+template <int kD, int kMB>
+struct Bf16Q {
+  typedef bf16_t qo_elt;
+  static constexpr int kSK = kD / 32, kDB = kD / 16;
+  static constexpr int kPitchK = kD * 2 + 16, kPitchV = kD * 2 + 32;   // bytes
+  static_assert(kD % 32 == 0 && kMB % 2 == 0, "32-wide contraction steps");
+  bf16x8 q[kSK];
+  __device__ __forceinline__ void load_q(const bf16_t* row, int d, int g) {
+#pragma unroll
+    for (int ks = 0; ks < kSK; ++ks) {
+      const int c = 32 * ks + 8 * g;
+      u32x4 w = {0u, 0u, 0u, 0u};
+      if (c < d) w = *reinterpret_cast<const u32x4*>(row + c);
+      q[ks] = __builtin_bit_cast(bf16x8, w);
+    }
+  }
+  template <class U> static __device__ __forceinline__ void put(unsigned char* kv, int pitch, int row, int unit, const U& u) {
+    *reinterpret_cast<u32x4*>(kv + row * pitch + unit * 16) = u.as_bf16();
+  }
+  // scores of the wave's keys: block mb holds keys 16 * mb + 4 * g + i of query r
+  __device__ __forceinline__ void scores(const unsigned char* k, int r, int g, f32x4 (&s)[kMB]) const {
+#pragma unroll
+    for (int mb = 0; mb < kMB; ++mb) s[mb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int ks = 0; ks < kSK; ++ks)
+#pragma unroll
+      for (int mb = 0; mb < kMB; ++mb) {
+        const bf16x8 a = *reinterpret_cast<const bf16x8*>(k + (16 * mb + r) * kPitchK + (4 * ks + g) * 16);
+        s[mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, q[ks], s[mb], 0, 0, 0);
+      }
+  }
+  static __device__ __forceinline__ bf16x8 v_operand(const unsigned char* v, int kk, int db, int r, int g) {
+    typedef short s16x4 __attribute__((ext_vector_type(4)));
+    typedef __attribute__((address_space(3))) s16x4* lds_p;
+    const unsigned char* p = v + (32 * kk + 4 * g + (r >> 2)) * kPitchV + db * 32 + 8 * (r & 3);
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_p)p);
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_p)(p + 16 * kPitchV));
+    const u32x2 a = __builtin_bit_cast(u32x2, lo), b = __builtin_bit_cast(u32x2, hi);
+    return __builtin_bit_cast(bf16x8, u32x4{a[0], a[1], b[0], b[1]});
+  }
+  // O^T += V^T P^T
+  __device__ __forceinline__ void pv(const unsigned char* v, int d, int r, int g, const float (&p)[kMB][4], f32x4 (&o)[kDB]) const {
+    constexpr int kGrp = 4;   // head-dim blocks whose MFMAs alternate, so that none waits for its predecessor
+#pragma unroll
+    for (int kk = 0; kk < kMB / 2; ++kk) {
+      u32x4 part[3];
+#pragma unroll
+      for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          uint32_t hi, mid, lo;
+          split3(p[2 * kk + a][2 * j], p[2 * kk + a][2 * j + 1], hi, mid, lo);
+          part[0][2 * a + j] = hi; part[1][2 * a + j] = mid; part[2][2 * a + j] = lo;
+        }
+#pragma unroll
+      for (int d0 = 0; d0 < kDB; d0 += kGrp) {
+        if (16 * d0 >= d) break;   // (uniform) columns past the head dimension
+        bf16x8 a[kGrp];
+#pragma unroll
+        for (int x = 0; x < kGrp; ++x)
+          if (d0 + x < kDB) a[x] = v_operand(v, kk, d0 + x, r, g);
+#pragma unroll
+        for (int t = 2; t >= 0; --t)   // small parts first
+#pragma unroll
+          for (int x = 0; x < kGrp; ++x)
+            if (d0 + x < kDB) o[d0 + x] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[x], __builtin_bit_cast(bf16x8, part[t]), o[d0 + x], 0, 0, 0);
+      }
+    }
+  }
+  static __device__ __forceinline__ void store4(bf16_t* p, const float (&o)[4]) {
+    *reinterpret_cast<u32x2*>(p) = u32x2{pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3])};
+  }
+};
+
+template <int kD, int kMB>
+struct F32Q {
+  typedef float qo_elt;
+  static constexpr int kSK = kD / 16, kDB = kD / 16;
+  static constexpr int kPitchK = (kD + 4) * 4, kPitchV = (kD + 4) * 4;
+  f32x4 q[kSK];   // head dims 16 * s + 4 * g + j: the contraction visits the head dimensions in that order on both sides
+  __device__ __forceinline__ void load_q(const float* row, int d, int g) {
+#pragma unroll
+    for (int s = 0; s < kSK; ++s) {
+      const int c = 16 * s + 4 * g;
+      q[s] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+      if (c < d) q[s] = *reinterpret_cast<const f32x4*>(row + c);
+    }
+  }
+  template <class U> static __device__ __forceinline__ void put(unsigned char* kv, int pitch, int row, int unit, const U& u) {
+    f32x4 a, b;
+    u.as_f32(a, b);
+    *reinterpret_cast<f32x4*>(kv + row * pitch + unit * 32) = a;
+    *reinterpret_cast<f32x4*>(kv + row * pitch + unit * 32 + 16) = b;
+  }
+  __device__ __forceinline__ void scores(const unsigned char* k, int r, int g, f32x4 (&s)[kMB]) const {
+#pragma unroll
+    for (int mb = 0; mb < kMB; ++mb) s[mb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int c = 0; c < kSK; ++c) {
+      f32x4 a[kMB];
+#pragma unroll
+      for (int mb = 0; mb < kMB; ++mb) a[mb] = *reinterpret_cast<const f32x4*>(k + (16 * mb + r) * kPitchK + (16 * c + 4 * g) * 4);
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int mb = 0; mb < kMB; ++mb) s[mb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[mb][j], q[c][j], s[mb], 0, 0, 0);
+    }
+  }
+  __device__ __forceinline__ void pv(const unsigned char* v, int d, int r, int g, const float (&p)[kMB][4], f32x4 (&o)[kDB]) const {
+#pragma unroll
+    for (int mb = 0; mb < kMB; ++mb)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)   // contraction index g of the MFMA is key 16 * mb + 4 * g + i
+#pragma unroll
+        for (int d0 = 0; d0 < kDB; d0 += 4) {
+          if (16 * d0 >= d) break;
+#pragma unroll
+          for (int x = d0; x < d0 + 4 && x < kDB; ++x) {
+            const float a = *reinterpret_cast<const float*>(v + (16 * mb + 4 * g + i) * kPitchV + (16 * x + r) * 4);
+            o[x] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, p[mb][i], o[x], 0, 0, 0);
+          }
+        }
+  }
+  static __device__ __forceinline__ void store4(float* p, const float (&o)[4]) {
+    *reinterpret_cast<float4*>(p) = make_float4(o[0], o[1], o[2], o[3]);
+  }
+};
+
+// LDS of a work-group: K tile | V tile | per-key factor of the exponent, bias (0 / -inf), V scale; the
+// exchange of the kKW partial results reuses the tiles
+template <class E, int kD, int kKW>
+constexpr int lds_bytes() {
+  constexpr int tiles = kTile * (E::kPitchK + E::kPitchV);
+  constexpr int xch = 4 * 64 * (kD / 4 + 2) * 4;
+  return (kKW > 1 && xch > tiles ? xch : tiles) + 3 * kTile * 4;
+}
+
+template <template <int, int> class Engine, class Unit, int kD, int kKW>
+__global__ __launch_bounds__(kThreads, kD > 160 ? 1 : 2)   // waves per SIMD the registers allow
+void attn_tile_kernel(AttnStep s) {
+  constexpr int kMB = 4 / kKW, kDB = kD / 16;
+  typedef Engine<kD, kMB> E;
+  typedef typename Unit::elt KT;
+  typedef typename E::qo_elt QT;
+  constexpr bool fp8 = std::is_same<Unit, UnitF8>::value;
+  extern __shared__ __align__(16) unsigned char smem[];
+  if (s.copy_wgs > 0 && blockIdx.x >= gridDim.x - s.copy_wgs) {   // prefetch work-groups end the x axis
+    if (blockIdx.y == 0 && blockIdx.z == 0) prefetch_copy(s, blockIdx.x - (gridDim.x - s.copy_wgs), threadIdx.x, kThreads);
+    return;
+  }
+  unsigned char* k_lds = smem;
+  unsigned char* v_lds = smem + kTile * E::kPitchK;
+  float* fac = reinterpret_cast<float*>(smem + lds_bytes<E, kD, kKW>() - 3 * kTile * 4);   // factor | bias | V scale
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int r = lane & 15, g = lane >> 4;
+  const int part = wave % kKW;                                  // which keys of a tile this wave takes
+  const int h = blockIdx.y, b = blockIdx.z, d = s.d;
+  const int qi = (blockIdx.x * (4 / kKW) + wave / kKW) * 16 + r;
+  const int qc = min(qi, s.Sq - 1);                             // surplus lanes recompute the last row, store nothing
+  const float scale2 = s.scale * 1.44269504088896340736f;
+
+  E e;
+  e.load_q((const QT*)s.q + b * s.qs[0] + h * s.qs[1] + (int64_t)qc * s.qs[2], d, g);
+
+  // ---- staging: unit u of a tile (8 elements of one row) goes through thread u % 256
+  constexpr int kUPR = kD / 8, kNU = kTile * kUPR / kThreads;   // units per row; units per thread and tensor
+  Unit ku[kNU], vu[kNU];
+  float f_c = 0.0f, f_b = 0.0f, f_v = 0.0f;                     // threads 0..63: the tile's per-key values
+  auto fetch = [&](int c, int t) {
+    const AttnStep::Chunk& ch = s.chunk[c];
+    const int left = ch.Sc - t * kTile;                         // valid rows of this tile
+    const KT* kb = (const KT*)ch.k + b * ch.ks0 + h * ch.ks1 + (int64_t)t * kTile * s.ks[2];
+    const KT* vb = (const KT*)ch.v + b * ch.ks0 + h * ch.ks1 + (int64_t)t * kTile * s.ks[2];
+#pragma unroll
+    for (int i = 0; i < kNU; ++i) {
+      const int u = tid + i * kThreads, row = u / kUPR, col = (u % kUPR) * 8;
+      ku[i].zero();
+      vu[i].zero();
+      if (row < left && col < d) {
+        ku[i].load(kb + row * s.ks[2] + col);
+        vu[i].load(vb + row * s.ks[2] + col);
+      }
+    }
+    if (tid < kTile) {
+      const int key = t * kTile + tid;
+      const bool keep = tid < left && (ch.mask_src == nullptr || ch.mask_src[(int64_t)b * ch.Sc + key] != 0);
+      f_c = scale2; f_b = keep ? 0.0f : -INFINITY; f_v = 1.0f;
+      if (fp8 && tid < left) {
+        const int64_t row = ((int64_t)b * s.H + h) * ch.Sc + key;
+        f_c = ch.k_scale_src[row] * scale2;
+        f_v = ch.v_scale_src[row];
+      }
+    }
+  };
+  auto stage = [&]() {
+#pragma unroll
+    for (int i = 0; i < kNU; ++i) {
+      const int u = tid + i * kThreads, row = u / kUPR, unit = u % kUPR;
+      E::put(k_lds, E::kPitchK, row, unit, ku[i]);
+      E::put(v_lds, E::kPitchV, row, unit, vu[i]);
+    }
+    if (tid < kTile) { fac[tid] = f_c; fac[kTile + tid] = f_b; fac[2 * kTile + tid] = f_v; }
+  };
+
+  // carried (O, lse) of earlier chunks
+  f32x4 oc[kDB];
+  float lse_c = -INFINITY;
+  bool carried = s.mode >= 2;
+  const int64_t row = ((int64_t)b * s.H + h) * s.Sq + qc;
+  float* accp = s.acc ? s.acc + row * d : nullptr;
+  if (carried && part == 0) {
+    lse_c = s.lse[row];
+#pragma unroll
+    for (int db = 0; db < kDB; ++db) {
+      oc[db] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+      if (16 * db + 4 * g < d) oc[db] = *reinterpret_cast<const f32x4*>(accp + 16 * db + 4 * g);
+    }
+  }
+
+  int pc = 0, pt = 0;   // next tile to fetch
+  auto skip_empty = [&]() { while (pc < s.n_multi && pt * kTile >= s.chunk[pc].Sc) { ++pc; pt = 0; } };
+  skip_empty();
+  if (pc < s.n_multi) { fetch(pc, pt); ++pt; skip_empty(); }
+
+  for (int c = 0; c < s.n_multi; ++c) {
+    float m = -INFINITY, l = 0.0f;
+    f32x4 o[kDB];
+#pragma unroll
+    for (int db = 0; db < kDB; ++db) o[db] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    for (int t = 0; t * kTile < s.chunk[c].Sc; ++t) {
+      __syncthreads();              // the previous tile (or the exchange) has been read
+      stage();
+      if (pc < s.n_multi) { fetch(pc, pt); ++pt; skip_empty(); }
+      __syncthreads();
+      const int k0 = part * 16 * kMB;                            // first key of this wave
+      f32x4 sc[kMB];
+      e.scores(k_lds + k0 * E::kPitchK, r, g, sc);
+      float p[kMB][4], tm = -INFINITY;
+#pragma unroll
+      for (int mb = 0; mb < kMB; ++mb) {
+        const f32x4 fc = *reinterpret_cast<const f32x4*>(fac + k0 + 16 * mb + 4 * g);
+        const f32x4 fb = *reinterpret_cast<const f32x4*>(fac + kTile + k0 + 16 * mb + 4 * g);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          p[mb][i] = fmaf(sc[mb][i], fc[i], fb[i]);
+          tm = fmaxf(tm, p[mb][i]);
+        }
+      }
+      const float m_new = fmaxf(m, group_max(tm));
+      // no live key so far: every exponent is -inf and P = 0 against any finite reference
+      const float ref = m_new == -INFINITY ? 0.0f : m_new;
+      const float alpha = __builtin_amdgcn_exp2f(m - ref);       // m = -inf gives 0
+      float ps = 0.0f;
+#pragma unroll
+      for (int mb = 0; mb < kMB; ++mb)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) { p[mb][i] = __builtin_amdgcn_exp2f(p[mb][i] - ref); ps += p[mb][i]; }
+      if (__builtin_amdgcn_ballot_w64(m_new != m) != 0ull) {
+#pragma unroll
+        for (int db = 0; db < kDB; ++db) o[db] *= alpha;
+      }
+      l = l * alpha + ps;
+      m = m_new;
+      if (fp8) {
+#pragma unroll
+        for (int mb = 0; mb < kMB; ++mb) {
+          const f32x4 fv = *reinterpret_cast<const f32x4*>(fac + 2 * kTile + k0 + 16 * mb + 4 * g);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) p[mb][i] *= fv[i];
+        }
+      }
+      e.pv(v_lds + k0 * E::kPitchV, d, r, g, p, o);
+    }
+    l = group_sum(l);
+
+    if (kKW > 1) {   // combine the waves that share these queries: [wave][slot][lane] in the tiles' place
+      constexpr int kSlots = kD / 4 + 2;
+      float* x = reinterpret_cast<float*>(smem) + wave * kSlots * 64 + lane;
+      __syncthreads();
+      if (part > 0) {
+#pragma unroll
+        for (int db = 0; db < kDB; ++db)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) x[(4 * db + i) * 64] = o[db][i];
+        x[(kD / 4) * 64] = m;
+        x[(kD / 4 + 1) * 64] = l;
+      }
+      __syncthreads();
+      if (part == 0) {
+#pragma unroll
+        for (int w = 1; w < kKW; ++w) {
+          const float* y = x + w * kSlots * 64;
+          const float mw = y[(kD / 4) * 64], lw = y[(kD / 4 + 1) * 64];
+          const float mm = fmaxf(m, mw), ref = mm == -INFINITY ? 0.0f : mm;
+          const float wa = __builtin_amdgcn_exp2f(m - ref), wb = __builtin_amdgcn_exp2f(mw - ref);
+#pragma unroll
+          for (int db = 0; db < kDB; ++db)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) o[db][i] = wa * o[db][i] + wb * y[(4 * db + i) * 64];
+          l = wa * l + wb * lw;
+          m = mm;
+        }
+      }
+    }
+    // the chunk's result and the merge of section 3.4
+    float lse_r = -INFINITY, c_cur = 0.0f, w_prev = 0.0f;
+    if (l > 0.0f) { lse_r = (m + log2f(l)) * 0.69314718055994530942f; c_cur = 1.0f / l; }
+    float lse_new = lse_r;
+    if (carried) {
+      const float mm = fmaxf(lse_c, lse_r);
+      if (mm == -INFINITY) { c_cur = 0.0f; lse_new = -INFINITY; }
+      else {
+        lse_new = mm + logf(expf(lse_c - mm) + expf(lse_r - mm));
+        w_prev = expf(lse_c - lse_new);
+        c_cur *= expf(lse_r - lse_new);
+      }
+    }
+#pragma unroll
+    for (int db = 0; db < kDB; ++db)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float x = o[db][i] * c_cur;
+        oc[db][i] = carried ? fmaf(w_prev, oc[db][i], x) : x;
+      }
+    lse_c = lse_new;
+    carried = true;
+  }
+
+  if (part != 0 || qi >= s.Sq) return;
+  QT* outp = (QT*)s.out + b * s.os[0] + h * s.os[1] + (int64_t)qi * s.os[2];
+#pragma unroll
+  for (int db = 0; db < kDB; ++db) {
+    const int col = 16 * db + 4 * g;
+    if (col >= d) continue;
+    if (s.mode == 1 || s.mode == 2) *reinterpret_cast<f32x4*>(accp + col) = oc[db];
+    else {
+      const float x[4] = {oc[db][0], oc[db][1], oc[db][2], oc[db][3]};
+      E::store4(outp + col, x);
+    }
+  }
+  if (g == 0) s.lse[row] = lse_c;
+}
+
+template <template <int, int> class Engine, class Unit, int kD, int kKW>
+usp_status launch_tile(const AttnStep& s, hipStream_t st) {
+  typedef Engine<kD, 4 / kKW> E;
+  constexpr int lds = lds_bytes<E, kD, kKW>();
+  constexpr int qpw = 64 / kKW;   // queries per work-group
+  if (lds > 64 * 1024) USP_CHECK_HIP((allow_large_lds<attn_tile_kernel<Engine, Unit, kD, kKW>>(lds)));
+  const dim3 grid((unsigned)((s.Sq + qpw - 1) / qpw + s.copy_wgs), (unsigned)s.H, (unsigned)s.B);
+  hipLaunchKernelGGL((attn_tile_kernel<Engine, Unit, kD, kKW>), grid, dim3(kThreads), lds, st, s);
+  USP_CHECK_HIP(hipGetLastError());
+  return USP_OK;
+}
+
+}  // namespace tile
+}  // namespace usp

@@ -552,6 +552,29 @@ usp_status usp::ring_attn_fwd_impl(const usp_attn_desc* desc, const void* q, con
     }
   }
 
+  // Shapes of the general kernel, every chunk at hand: one launch, the chunks merged one after another in
+  // registers with the operations of a launch per chunk (same bits): one launch gap and one round trip of the carried state less per chunk
+  if (!p.mfma && p.W > 1 && p.W <= AttnStep::kMaxMulti && !p.dbuf && !p.unfused && !(desc->flags & USP_ATTN_STEPWISE)) {
+    AttnStep a;
+    memset(&a, 0, sizeof(a));
+    a.B = desc->B; a.H = desc->H; a.d = d; a.Sq = desc->Sq;
+    a.qo_dtype = desc->qo_dtype; a.kv_dtype = desc->kv_dtype;
+    a.q = q; a.out = out; a.lse = lse; a.scale = scale; a.mode = 0;
+    const bool dense = p.fp8 || kv_auto(desc);
+    for (int i = 0; i < 3; ++i) { a.qs[i] = desc->q_stride[i]; a.os[i] = desc->o_stride[i]; }
+    a.ks[2] = dense ? d : desc->kv_stride[2];
+    for (int r = 0; r < p.W; ++r) {
+      const int len = desc->chunk_len[r];
+      AttnStep::Chunk& c = a.chunk[a.n_multi++];
+      c.k = k_chunks[r]; c.v = v_chunks[r]; c.Sc = len;
+      c.ks0 = dense ? (int64_t)desc->H * len * d : desc->kv_stride[0];
+      c.ks1 = dense ? (int64_t)len * d : desc->kv_stride[1];
+      if (p.fp8) { c.k_scale_src = k_scales[r]; c.v_scale_src = v_scales[r]; }
+      c.mask_src = key_mask ? key_mask[r] : nullptr;
+    }
+    return launch_attn_generic(a, cs);
+  }
+
   // FP8 chunks: one launch over the ring that decodes them as it goes
   if (p.ring8 && short_steps) {
     bool ok = true;

@@ -4,6 +4,7 @@
 #include <stdint.h>
 #include <stdio.h>
 #include <stdarg.h>
+#include <atomic>
 #include "usp.h"
 
 namespace usp {
@@ -174,6 +175,20 @@ usp_status launch_attn_fp8_chunk_prepare(const AttnStep& s, int c, bool reset_ar
 // and V, the per-tile records and n_live[B] in one launch
 usp_status launch_attn_fp8_step_prepare(const AttnStep& s, int* n_live, hipStream_t st);
 
+// More than 64 KB of dynamic LDS has to be allowed per kernel, and the setting belongs to the device
+// that is current when it is made: once per (kernel, device ordinal below 64), every launch beyond.
+template <void (*kKernel)(AttnStep)>
+static hipError_t allow_large_lds(int bytes) {
+  static std::atomic<uint64_t> done{0};
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  const bool tracked = dev >= 0 && dev < 64;
+  if (tracked && ((done.load(std::memory_order_acquire) >> dev) & 1u) != 0) return hipSuccess;
+  e = hipFuncSetAttribute(reinterpret_cast<const void*>(kKernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  if (e == hipSuccess && tracked) done.fetch_or((uint64_t)1 << dev, std::memory_order_release);
+  return e;
+}
 
 // What usp_ring_attn_fwd does, with the knobs the ABI does not carry.
 struct CallOptions {

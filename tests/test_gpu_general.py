@@ -1,0 +1,71 @@
+"""Attention outside the bf16 d = 128 / 64 kernels (attn_tile.h) against the fp64 oracle: both engines, every
+size class of the head dimension and its edges, waves that share queries and waves that do not, ragged,
+empty and masked chunks, FP8 K/V.  Bars: fp32 results 2e-5 / 5e-6 / 2e-5 as elsewhere; bf16 results carry
+the rounding of the output plus the fp32 bar, because nothing inside is rounded to bf16: with 8 significant
+bits a value in [2^e, 2^(e+1)) has neighbours 2^(e-7) apart, so rounding to nearest moves it by at most
+2^(e-8), which is at most 2^-8 of the value."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import usp_oracle as orc
+from paper_2602_10940_amd import workloads as W
+from tests.gpu_util import DEV, attn_errors, dev_bf16, dev_f32, host_f64
+
+pytestmark = pytest.mark.gpu
+
+# B, H, d, Sq, chunks, masked keys, FP8 K/V
+SHAPES = [
+    (1, 1, 8, 1, (1,), (0, 0), False),                  # smallest
+    (2, 3, 40, 77, (100, 0, 65), (90, 165), False),     # empty middle chunk, last chunk and a tail masked
+    (1, 2, 64, 63, (64, 63), (0, 0), False),            # (bf16: the other kernels)
+    (1, 3, 72, 130, (65, 128), (0, 64), False),         # first tile all dead
+    (1, 2, 96, 64, (200,), (0, 0), False),
+    (2, 2, 104, 33, (64, 64, 1), (0, 0), False),
+    (1, 40, 80, 450, (129,), (0, 0), False),            # 64-query work-groups (waves do not share queries)
+    (1, 40, 136, 450, (70,), (3, 9), False),
+    (1, 2, 160, 50, (90,), (0, 0), False),
+    (1, 3, 168, 20, (64, 10), (0, 0), False),
+    (1, 2, 256, 65, (130,), (0, 0), False),
+    (1, 40, 256, 260, (66,), (0, 0), False),
+    (1, 3, 72, 40, (96, 33), (100, 129), True),         # rows of codes 8-byte aligned only
+    (2, 20, 96, 300, (64, 65), (0, 0), True),
+    (1, 2, 248, 17, (70,), (0, 0), True),
+]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("B,H,d,Sq,lens,masked,fp8", SHAPES)
+def test_general_shapes(dtype, B, H, d, Sq, lens, masked, fp8):
+    import paper_2602_10940_amd as P
+    wl = W.Workload("general", 500 + d, B, H, d, Sq, lens, dtype, masked_keys=masked)
+    inp = W.make_attention_inputs(wl)
+    up = dev_f32 if dtype == "f32" else dev_bf16
+    kw = dict(key_mask=None if inp.key_mask is None else [torch.from_numpy(m).to(DEV) for m in inp.key_mask],
+              softmax_scale=float(inp.softmax_scale))
+    ks, vs, kx, vx = [up(k) for k in inp.k], [up(v) for v in inp.v], inp.k, inp.v
+    if fp8:
+        def pack(ts):
+            qs = [P.usp_fp8_quant(t.reshape(-1, d)) for t in ts]
+            return ([q.reshape(t.shape) for (q, _), t in zip(qs, ts)], [s.reshape(t.shape[:3]) for (_, s), t in zip(qs, ts)])
+        (ks, ksc), (vs, vsc) = pack(ks), pack(vs)
+        kw.update(k_scales=ksc, v_scales=vsc)
+        kx = [orc.dequant_exact_f64(q.cpu().numpy(), s.cpu().numpy()) for q, s in zip(ks, ksc)]
+        vx = [orc.dequant_exact_f64(q.cpu().numpy(), s.cpu().numpy()) for q, s in zip(vs, vsc)]
+    o, l = P.usp_ring_attn_fwd(up(inp.q), ks, vs, **kw)
+    torch.cuda.synchronize()
+    ro, rl = orc.ring_attention(inp.q, kx, vx, float(inp.softmax_scale), inp.key_mask)
+    got_o, got_l = host_f64(o), host_f64(l)
+    mx, rel = attn_errors(got_o, ro)
+    assert np.array_equal(np.isneginf(got_l), np.isneginf(rl))
+    fin = np.isfinite(rl)
+    if dtype == "bf16" and d == 64:
+        assert mx <= 2e-2 and rel <= 5e-3 and np.max(np.abs(got_l - rl)[fin]) <= 1e-3
+        return
+    size = max(1.0, float(np.max(np.abs(ro))))
+    out_max, out_rel = (0.0, 0.0) if dtype == "f32" else (2.0 ** -8 * size, 2.0 ** -8)
+    assert mx <= 2e-5 * size + out_max and rel <= 5e-6 + out_rel and np.max(np.abs(got_l - rl)[fin], initial=0.0) <= 2e-5, (mx, rel)
+    # one launch over the chunks and a launch per chunk: the same operations, the same bits
+    o2, l2 = P.usp_ring_attn_fwd(up(inp.q), ks, vs, flags=P.USP_ATTN_STEPWISE, **kw)
+    torch.cuda.synchronize()
+    assert torch.equal(o, o2) and torch.equal(l, l2)
