@@ -229,35 +229,36 @@ __device__ __forceinline__ void finish_and_store(const AttnStep& s, f32x4 (&oacc
 // K and V tiles go through three LDS stages each, written by direct global->LDS loads issued
 // from the softmax phases (whose critical resource, the VALU, is not the matrix core's).
 //
-// Template parameter kExt adds what the plain kernels exclude: per-key scales of FP8 K/V
-// (Algorithm 1, line 4, applied to the fp32 scores and to P instead of to K and V), a key mask,
-// and a chunk length that is not a multiple of 64.  A small kernel run before the attention
-// kernel turns scales, mask and length into four vectors of 64 floats per (batch, head, tile):
-//   c    = k_scale * softmax_scale * log2(e)   (0 for a masked or out-of-range key)
-//   bias = 0, or -inf for a masked or out-of-range key
-//   flag = (flag[0] != 0) iff the tile has any such key
-//   (a fourth, unused, vector keeps one 256-byte load per wave of the loading group)
-// and the tile's record follows its K tile through the LDS stages.  The scales of FP8 V are not
-// applied here: V is widened to bf16 as round(code * v_scale) before the kernel runs (the dequantise
-// step of Algorithm 1 in the working precision), because a multiply per P element would make the
-// softmax phase, which issues from a single wave per SIMD, the longer of the two phases.  K keeps
-// its exact codes: its scale costs nothing inside the exponent's FMA, and rounding K would move
+// Template parameter kExt: per-key scales of FP8 K (Algorithm 1, line 4, applied to the fp32 scores instead
+// of to K).  The launch that decodes a chunk writes, per (batch, head, tile), a record of 64 factors
+// c = k_scale * softmax_scale * log2(e), and the record follows its K tile through the LDS stages.  The
+// scales of FP8 V are not applied here: V is widened to bf16 as round(code * v_scale) before the kernel
+// runs (the dequantise step of Algorithm 1 in the working precision), because a multiply per P element
+// would make the softmax phase, which issues from a single wave per SIMD, the longer of the two phases.
+// K keeps its exact codes: its scale costs nothing inside the exponent's FMA, and rounding K would move
 // the scores themselves.
 //
+// Template parameter kDead: some keys take no part (a key mask, a chunk length that is not a multiple of
+// 64).  A work-group starts by turning masks and lengths into one 64-bit word per tile in LDS (bit = key
+// lives; a mask is a byte per key, so that is one load per tile, all in flight together), from which it
+// knows where the live keys end and, one scan of 64 words at a time, which tile is the next with a dead
+// key.  A softmax phase compares its tile index with that one and nothing else; only a tile with dead keys
+// reads its word and overwrites their scores with -inf.  The per-tile records of factor, bias and flag
+// this replaced (1 KB a tile, written by a launch in front) cost that launch and its gap, 4 to 5 us a
+// chunk, an LDS read per block of exponentials and 5 to 10 % of the kernel.  More tiles than the words'
+// room (kMaxWords): every tile looks its keys up in global memory.
+//
 // Template parameter kMulti lets one launch cover a whole ring (Algorithm 2): the 64-key tiles of up
-// to 16 chunks (whole tiles only) form one stream in ring order, a cursor maps a tile index to
+// to 16 chunks (a ragged one ends in a tile with dead keys) form one stream in ring order, a cursor maps a tile index to
 // its chunk's pointer, and the running (O~, m, l) stays in registers from the first tile to the
 // last, which is the merge of section 3.4 applied tile by tile.  With AttnStep::arrive set the
 // launch also plays the ring's transfers: its first work-groups copy the chunks into staging
 // buffers and count themselves on a per-chunk arrival counter (prefetch_copy.h), and an attention
 // work-group waits for a chunk's count before it loads the chunk's first tile (wait_arrival).
 // FP8 chunks (AttnStep::multi_fp8) are decoded by those work-groups on the way (Algorithm 1 line 4:
-// K widened, V dequantised, the records above written, masks included) and attended by the
-// record-reading form; there the tiles of a chunk that came with a mask read their dead-key flag
-// from the record in LDS (it cannot be fetched ahead from memory the launch is still writing).
+// K widened, V dequantised, the records above written) and attended by the record-reading form.
 //
-// kNoDead: records that carry only per-key factors (no mask, whole tiles): flag and bias are never
-// read.  kHalfD: head dimension 64 (see attn_pp_body).
+// kHalfD: head dimension 64 (see attn_pp_body).
 // =============================================================================================
 __device__ __forceinline__ void lds_dma16(const void* gbase, uint32_t lane_off, uint32_t lds_base) {
   // 64 lanes x 16 bytes from gbase (wave-uniform) + lane_off (per lane): lane i's 16 bytes land at
@@ -267,26 +268,29 @@ __device__ __forceinline__ void lds_dma16(const void* gbase, uint32_t lane_off, 
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                :: "s"(lds_base), "v"(lane_off), "s"(gbase) : "memory", "m0");
 }
+// The same through a buffer descriptor (base, 0, bytes, flags) with a uniform offset on top of the lanes':
+// lanes that fall outside the descriptor's bytes load zeros.
+__device__ __forceinline__ void lds_dma16_bounded(u32x4 desc, uint32_t lane_off, uint32_t offset, uint32_t lds_base) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+               :: "s"(lds_base), "v"(lane_off), "s"(desc), "s"(offset) : "memory", "m0");
+}
 __device__ __forceinline__ void lds_dma4(const void* gbase, uint32_t lane_off, uint32_t lds_base) {
   // the same with 4 bytes per lane: lane i's dword lands at lds_base + 4*i
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2"
                :: "s"(lds_base), "v"(lane_off), "s"(gbase) : "memory", "m0");
 }
-constexpr int kStages = 3;       // LDS tile buffers per tensor
-constexpr int kExtTileB = 1024;  // bytes of one tile's record of the extended path: c | bias | flag | unused
+constexpr int kStagesWide = 3, kStagesSplit = 4;   // LDS tile buffers per tensor
+constexpr int kExtTileB = kTile * 4;   // bytes of one tile's record: the factors of its 64 keys
 
-struct SmemPP {
-  unsigned char k[kStages][kTileB];
-  unsigned char v[kStages][kTileB];
-};
-// The wide work-groups' epilogue stages each wave's O tile through LDS (eight regions from offset 0,
-// over the tile stages, which are dead by then).
-constexpr int kLdsBytes = 8 * kEpiWaveB;
-struct SmemPPExt {
-  unsigned char k[kStages][kTileB];
-  unsigned char v[kStages][kTileB];
-  unsigned char ext[4][kExtTileB];   // the 256-query kernel rotates its records over four stages
-};
+// LDS of a work-group: K stages | V stages | eight records | the words of kDead launches (245 000 keys).  The
+// wide work-groups' epilogue stages each wave's O tile (eight regions from offset 0, over everything else,
+// which is dead by then).
+constexpr int kRecStages = 8;
+constexpr int kExtOff = 2 * kStagesSplit * kTileB;
+constexpr int kWordsOff = kExtOff + kRecStages * kExtTileB;
+constexpr int kLdsBytes = 159 * 1024;   // (__syncthreads_or of the one-launch form takes some LDS of its own)
+constexpr int kMaxWords = (kLdsBytes - kWordsOff) / 8;
+static_assert(kStagesSplit >= kStagesWide && kWordsOff % 8 == 0 && 8 * kEpiWaveB <= kLdsBytes, "LDS plan");
 
 // LDS transposing read: the 16 lanes of a group each name 8 bytes; seen as a 4 x 16 matrix of
 // bf16 (row i = the data of lanes 4i..4i+3), lane j of the group receives column j.
@@ -296,60 +300,6 @@ __device__ __forceinline__ u32x2 lds_read_tr3(const __attribute__((address_space
   return __builtin_bit_cast(u32x2, r);
 }
 
-
-// One work-group of 64 threads per (tile, batch*head): the record described above.  Blocks of tile 0
-// with h == 0 also count the tiles up to the last one that has a live key (n_live[b]); the
-// attention kernel stops there.
-__global__ __launch_bounds__(64) void attn_ext_prepare_kernel(AttnStep s, float* ext, int* n_live) {
-  const int tile = blockIdx.x, bh = blockIdx.y, t = threadIdx.x;
-  const int b = bh / s.H;
-  const int nt_all = (s.Sc + kTile - 1) / kTile;   // the grid has max(nt_all, 1) tiles
-  const uint8_t* mask = s.key_mask ? s.key_mask + (int64_t)b * s.Sc : nullptr;
-  if (tile < nt_all) {
-    const int key = tile * kTile + t;
-    const bool keep = key < s.Sc && (!mask || mask[key] != 0);
-    const int64_t srow = (int64_t)bh * s.Sc + key;
-    float* rec = ext + ((int64_t)bh * nt_all + tile) * (kExtTileB / 4);
-    const float scale2 = s.scale * 1.44269504088896340736f;
-    rec[t] = keep ? (s.k_scale ? s.k_scale[srow] : 1.0f) * scale2 : 0.0f;
-    rec[64 + t] = keep ? 0.0f : -INFINITY;
-    rec[128 + t] = __builtin_amdgcn_ballot_w64(!keep) != 0ull ? 1.0f : 0.0f;
-    rec[192 + t] = 0.0f;
-  }
-  if (tile == 0 && bh % s.H == 0) {
-    int last = -1;   // last live key of this batch entry
-    if (!mask) last = s.Sc - 1;
-    else {
-#pragma unroll 8
-      for (int k0 = t; k0 < s.Sc; k0 += 64)
-        if (mask[k0] != 0) last = k0;
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) last = max(last, __shfl_xor(last, o, 64));
-    if (t == 0) n_live[b] = last < 0 ? 0 : last / kTile + 1;
-  }
-}
-
-// Records of a launch over several bf16 chunks of which some have a key mask: one work-group of 64
-// threads per (tile of the ring's tile stream, batch*head), laid out [B*H][tiles in ring order] like
-// the records the FP8 form writes while it decodes.  Masks are inputs of the call, not part of what
-// the ring transfers, so the records of every chunk can be written before the attention launch.
-__global__ __launch_bounds__(64) void attn_multi_records_kernel(AttnStep s) {
-  int tile = blockIdx.x;
-  const int bh = blockIdx.y, t = threadIdx.x;
-  int nt_total = 0;
-  for (int c = 0; c < s.n_multi; ++c) nt_total += s.chunk[c].Sc / kTile;
-  int c = 0;
-  while (tile >= s.chunk[c].Sc / kTile) { tile -= s.chunk[c].Sc / kTile; ++c; }   // (the grid has nt_total tiles)
-  const AttnStep::Chunk& ch = s.chunk[c];
-  const int key = tile * kTile + t;
-  const bool keep = ch.mask_src == nullptr || ch.mask_src[(int64_t)(bh / s.H) * ch.Sc + key] != 0;
-  float* rec = s.ext + ((int64_t)bh * nt_total + blockIdx.x) * (kExtTileB / 4);
-  rec[t] = keep ? s.scale * 1.44269504088896340736f : 0.0f;
-  rec[64 + t] = keep ? 0.0f : -INFINITY;
-  rec[128 + t] = __builtin_amdgcn_ballot_w64(!keep) != 0ull ? 1.0f : 0.0f;
-  rec[192 + t] = 0.0f;
-}
 
 // Wait of an attention work-group for a chunk that the copy work-groups of the same launch are still
 // writing: polls the chunk's counter with device-scope loads until it reaches `need`.  The copy
@@ -371,44 +321,26 @@ __device__ __forceinline__ bool wait_arrival(const int* counter, int need, int p
 __global__ __launch_bounds__(64) void attn_arrive_reset_kernel(int* arrive) {
   if (threadIdx.x < AttnStep::kMaxMulti) arrive[threadIdx.x] = 0;
 }
-// Chunk c of a launch over several FP8 chunks, decoded by a launch of its own (the first chunk,
-// which no attention work-group could overlap with anything).
+// Chunk c of a launch over FP8 chunks, decoded by a launch of its own (the first chunk, which no attention
+// work-group could overlap with anything; the chunk of a launch-per-chunk step).
 __global__ __launch_bounds__(256) void attn_fp8_chunk_prepare_kernel(AttnStep s, int c, int reset_arrive) {
   if (reset_arrive && blockIdx.x == 0 && threadIdx.x < AttnStep::kMaxMulti) s.arrive[threadIdx.x] = 0;
   fp8_chunk_prepare<false>(s, c, (int64_t)blockIdx.x * 256 + threadIdx.x, (int64_t)gridDim.x * 256);
 }
 
-// The same for a step of the launch-per-chunk form (the chunk is s.chunk[0] of a one-chunk description):
-// codes -> bf16 K and V and the per-tile records in one launch instead of three, plus the count of tiles up
-// to the last live key of every batch entry, which the attention kernel of a single chunk stops at.
-__global__ __launch_bounds__(256) void attn_fp8_step_prepare_kernel(AttnStep s, int* n_live) {
-  fp8_chunk_prepare<false>(s, 0, (int64_t)blockIdx.x * 256 + threadIdx.x, (int64_t)gridDim.x * 256);
-  if (blockIdx.x == 0 && threadIdx.x < 64) {
-    const AttnStep::Chunk& ch = s.chunk[0];
-    const int t = threadIdx.x;
-    for (int b = 0; b < s.B; ++b) {
-      int last = ch.Sc - 1;
-      if (ch.mask_src != nullptr) {
-        last = -1;
-        const uint8_t* mask = ch.mask_src + (int64_t)b * ch.Sc;
-#pragma unroll 8
-        for (int k0 = t; k0 < ch.Sc; k0 += 64)
-          if (mask[k0] != 0) last = k0;
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) last = max(last, __shfl_xor(last, o, 64));
-      }
-      if (t == 0) n_live[b] = last < 0 ? 0 : last / kTile + 1;
-    }
-  }
+// The live keys of tile t (of a launch's tile stream) as a word, by the lanes of a wave: bit = key takes part.
+__device__ __forceinline__ uint64_t live_keys(const uint8_t* mask, int Sc, int t, int lane) {
+  const int key = t * kTile + lane;
+  bool live = key < Sc;
+  if (live && mask != nullptr) live = mask[key] != 0;
+  return __builtin_amdgcn_ballot_w64(live);
 }
 
 // One work-group's share: the queries q_base .. q_base + 255 (wide) or + 127 (split) of (batch, head) bh_.
-// kNoDead (with kExt): the records carry per-key factors only, no key of the launch is dead (FP8
-// scales on unmasked chunks of whole tiles): the per-tile flag is not read at all.
 // kHalfD: head dimension 64: rows of Q, K, V and O are 128 bytes (K and V are read in place, their LDS
 // tiles have 128-byte rows with swizzles of their own), the scores contract over two 32-wide slices
 // of the head dimension and P.V produces four 16-wide blocks.
-template <bool kSplit, bool kExt, bool kMulti = false, bool kNoDead = false, bool kHalfD = false>
+template <bool kSplit, bool kExt, bool kMulti, bool kDead, bool kHalfD>
 __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* smem_raw, int bh_, int q_base) {
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -417,6 +349,7 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
   constexpr int kKS = kHalfD ? 2 : 4;        // 32-wide slices of the head dimension (contraction of the scores)
   constexpr int kNV = kHalfD ? 2 : 4;        // operands of either kind per block of the matrix phase
   constexpr int kDB = kHalfD ? 4 : 8;        // 16-wide blocks of the head dimension that P.V produces
+  constexpr int kStages = kSplit ? kStagesSplit : kStagesWide;
   constexpr int kBurst = 1;                  // operands whose MFMAs are issued back to back before the next reads (1, 2, 4: no difference measured)
   const int h = bh_ % s.H, b = bh_ / s.H;
   // split: waves w and w+4 share their 32 queries
@@ -427,17 +360,86 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
   const unsigned char* kb = (const unsigned char*)((const bf16_t*)s.k + b * s.ks[0] + h * s.ks[1]);
   const unsigned char* vb = (const unsigned char*)((const bf16_t*)s.v + b * s.ks[0] + h * s.ks[1]);
   const float scale2 = s.scale * 1.44269504088896340736f;
-  // plain: the host guarantees Sc % 64 == 0 and Sc > 0.  extended: tiles up to the last live key;
-  // the last tile of the chunk may be ragged (tail_tile), none may be left (nt == 0).
-  // several chunks per launch: full tiles only; with records (kExt) these follow the tile stream
-  int nt_multi = 0;
-  if (kMulti)
-    for (int c = 0; c < s.n_multi; ++c) nt_multi += s.chunk[c].Sc / kTile;
-  const int nt_all = kMulti ? nt_multi : (s.Sc + kTile - 1) / kTile;
-  const int nt = kMulti ? nt_multi
-                        : kExt ? min(nt_all, __builtin_amdgcn_readfirstlane(s.n_live[b])) : s.Sc / kTile;
-  const int tail_tile = (kExt && !kMulti && (s.Sc % kTile) != 0) ? nt_all - 1 : -1;
-  const int tail_last_row = s.Sc - (nt_all - 1) * kTile - 1;   // last valid row of the ragged tile
+  // without kDead the host guarantees whole tiles and at least one; with it, the tiles up to the last live
+  // key are visited, and none may be left (nt == 0)
+  auto tiles_of = [](int len) { return (len + kTile - 1) / kTile; };
+  int nt_all = 0;
+  bool masked = false;
+  if (kMulti) {
+    for (int c = 0; c < s.n_multi; ++c) {
+      nt_all += tiles_of(s.chunk[c].Sc);
+      masked |= s.chunk[c].mask_src != nullptr;
+    }
+  } else {
+    nt_all = tiles_of(s.Sc);
+    masked = s.key_mask != nullptr;
+  }
+  int nt = nt_all;
+  typedef const __attribute__((address_space(3))) uint64_t* lds_words;
+  const lds_words words = (lds_words)(uintptr_t)((uint32_t)(uintptr_t)smem_raw + kWordsOff);
+  const bool in_lds = kMulti || nt_all <= kMaxWords;   // (the host keeps several chunks below that)
+  // the word of tile t where the words have no room in LDS
+  auto word_from_memory = [&](int t) -> uint64_t {
+    return live_keys(s.key_mask ? s.key_mask + (int64_t)b * s.Sc : nullptr, s.Sc, t, lane);
+  };
+  auto dead_word = [&](int t) -> uint64_t {
+    if (!in_lds) return word_from_memory(t);
+    const uint64_t w = words[t];
+    return (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)w) |
+           (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(w >> 32)) << 32;
+  };
+  // first tile >= t of the launch's stream that has a dead key (nt_all or more: none)
+  auto find_dead = [&](int t) -> int {
+    if (!in_lds) return t;
+    for (; t < nt_all; t += 64) {
+      const bool dead = t + lane < nt_all && words[t + lane] != ~0ull;
+      const uint64_t any = __builtin_amdgcn_ballot_w64(dead);
+      if (any != 0ull) return t + __builtin_ctzll(any);
+    }
+    return t;
+  };
+  if (kDead) {
+    if (in_lds) {
+      int first = 0;
+      for (int c = 0; c < (kMulti ? s.n_multi : 1); ++c) {
+        const int len = kMulti ? s.chunk[c].Sc : s.Sc, ntc = tiles_of(len);
+        const uint8_t* mask = kMulti ? s.chunk[c].mask_src : s.key_mask;
+        if (mask != nullptr) mask += (int64_t)b * len;
+        for (int t0 = wave; t0 < ntc; t0 += 8 * kWaves) {   // the loads of eight tiles in flight
+          uint32_t live[8];
+#pragma unroll
+          for (int u = 0; u < 8; ++u) {
+            const int key = (t0 + u * kWaves) * kTile + lane;
+            live[u] = key < len ? 1u : 0u;
+            if (mask != nullptr && key < len) live[u] = mask[key];
+          }
+#pragma unroll
+          for (int u = 0; u < 8; ++u) {
+            const uint64_t w = __builtin_amdgcn_ballot_w64(live[u] != 0u);
+            if (lane == 0 && t0 + u * kWaves < ntc)
+              *(__attribute__((address_space(3))) uint64_t*)(words + first + t0 + u * kWaves) = w;
+          }
+        }
+        first += ntc;
+      }
+    }
+    if (masked) {   // where the live keys end (without a mask every tile has one); the first barrier below publishes the words otherwise
+      __syncthreads();
+      nt = 0;
+      if (in_lds) {
+        for (int t0 = (nt_all - 1) / 64 * 64; t0 >= 0 && nt_all > 0; t0 -= 64) {
+          const bool any_live = t0 + lane < nt_all && words[t0 + lane] != 0ull;
+          const uint64_t any = __builtin_amdgcn_ballot_w64(any_live);
+          if (any != 0ull) { nt = t0 + 64 - __builtin_clzll(any); break; }
+        }
+      } else {
+        for (int t = nt_all; t > 0; --t)
+          if (word_from_memory(t - 1) != 0ull) { nt = t; break; }
+      }
+      nt = __builtin_amdgcn_readfirstlane(nt);
+    }
+  }
+  if (kDead && masked && nt == 0) __syncthreads();   // no barrier of the tile loop stands between the words and the epilogue that reuses their place
 
   f32x4 oacc[8][2];   // O~^T: [16-wide head-dim block db][16-query block nb]: head dims 16*db + 4*g + i of query 16*nb + r
 #pragma unroll
@@ -449,7 +451,7 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
   int arrived_upto = 0, probe_c = 0, probe_val = 0;   // chunks known to have arrived; the count read ahead for chunk probe_c
   constexpr int kProbeAheadTiles = 4;
 
-  if (!kExt || nt > 0) {   // (uniform over the work-group)
+  if (!kDead || nt > 0) {   // (uniform over the work-group)
   // ---- direct global->LDS tile loads, 4 rows (16 lanes each) per instruction.  wide: wave w moves
   // rows 8w..8w+7 of every tile.  split: only the group in its softmax phase loads, wave w its own
   // rows 8w..8w+7 and those of its partner w^4, 32 rows away (same swizzle: 32 is a multiple of
@@ -468,42 +470,40 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
   // V: the 32-byte chunk c of key r sits at chunk c ^ (r & 7) (kHalfD: c ^ ((r >> 1) & 3)): in 16-byte pieces
   const uint32_t vsw0 = kHalfD ? (uint32_t)((dma_p ^ (((dma_r0 >> 1) & 3) << 1)) << 4) : (uint32_t)((dma_p ^ ((dma_r0 & 7) << 1)) << 4);
   const uint32_t vsw1 = (dma_p ^ ((dma_r1 & 7) << 1)) << 4;
-  const uint32_t kg0 = dma_r0 * rowB + ksw0, kg1 = dma_r1 * rowB + ksw1;
-  const uint32_t vg0 = dma_r0 * rowB + vsw0, vg1 = dma_r1 * rowB + vsw1;
+  // kDead: a tile is loaded through a descriptor that ends with its chunk, so that the rows past the end of a
+  // ragged one arrive as zeros (finite data; their P is 0); a wave's rows of the tile's lower or upper half
+  // (split) are then told apart by the uniform offset
+  const int pair_rows = kSplit ? (grpA ? 32 : -32) : 0;
+  const int own_half = kDead && kSplit && !grpA ? 32 : 0;
+  const uint32_t kg0 = (dma_r0 - own_half) * rowB + ksw0, kg1 = (dma_r1 - own_half) * rowB + ksw1;
+  const uint32_t vg0 = (dma_r0 - own_half) * rowB + vsw0, vg1 = (dma_r1 - own_half) * rowB + vsw1;
   const uint32_t lds_base = (uint32_t)(uintptr_t)smem_raw;
   const uint32_t lds_k = __builtin_amdgcn_readfirstlane(lds_base + 8 * wave * RB);
   const uint32_t lds_v = __builtin_amdgcn_readfirstlane(lds_base + kStages * kTileB + 8 * wave * RB);
-  const int pair_rows = kSplit ? (grpA ? 32 : -32) : 0;
-  // rows past the end of a ragged last tile re-read its last valid row (finite data; their P is 0)
-  auto row_off = [&](int r, int tile_idx) -> uint32_t {
-    if (kExt && tile_idx == tail_tile) r = min(r, tail_last_row);
-    return (uint32_t)r * rowB;
+  // a tile of K or V: where it starts, and how many rows its chunk has from there on
+  struct TileRef { const unsigned char* p; int left; };
+  auto tile_desc = [&](TileRef t) -> u32x4 {
+    const uint64_t p = (uint64_t)(uintptr_t)t.p;
+    return u32x4{(uint32_t)p, (uint32_t)(p >> 32) & 0xffffu, (uint32_t)min(t.left, kTile) * rowB, 0x00020000u};
   };
-  auto issue_k_half = [&](const unsigned char* tile, int tile_idx, int stage, int half, bool pair) {
+  auto issue_half = [&](const TileRef& t, uint32_t off, uint32_t lds, int half, bool pair) {
     if (kHalfD && half) return;               // one load covers the wave's 8 rows
     const int dr = pair ? pair_rows : 0;
-    uint32_t off = half ? kg1 : kg0;
-    if (kExt && tile_idx == tail_tile) { off = row_off((half ? dma_r1 : dma_r0) + dr, tile_idx) + (half ? ksw1 : ksw0); }
-    else tile += (int64_t)dr * rowB;
-    lds_dma16(tile, off, lds_k + dr * RB + stage * kTileB + half * 4 * RB);
+    lds += dr * RB + half * 4 * RB;
+    if (kDead) lds_dma16_bounded(tile_desc(t), off, (uint32_t)(own_half + dr) * rowB, lds);
+    else lds_dma16(t.p + (int64_t)dr * rowB, off, lds);
   };
-  auto issue_v_half = [&](const unsigned char* tile, int tile_idx, int stage, int half, bool pair) {
-    if (kHalfD && half) return;
-    const int dr = pair ? pair_rows : 0;
-    uint32_t off = half ? vg1 : vg0;
-    if (kExt && tile_idx == tail_tile) { off = row_off((half ? dma_r1 : dma_r0) + dr, tile_idx) + (half ? vsw1 : vsw0); }
-    else tile += (int64_t)dr * rowB;
-    lds_dma16(tile, off, lds_v + dr * RB + stage * kTileB + half * 4 * RB);
-  };
-  // extended path: the four 64-float vectors of a tile's record, one per wave of the loading group
-  const unsigned char* extb = kExt ? (const unsigned char*)(s.ext + (int64_t)bh_ * nt_all * (kExtTileB / 4)) : nullptr;
-  const uint32_t lds_ext = lds_base + 2 * kStages * kTileB;
+  auto issue_k_half = [&](const TileRef& t, int stage, int half, bool pair) { issue_half(t, half ? kg1 : kg0, lds_k + stage * kTileB, half, pair); };
+  auto issue_v_half = [&](const TileRef& t, int stage, int half, bool pair) { issue_half(t, half ? vg1 : vg0, lds_v + stage * kTileB, half, pair); };
+  // kExt: the record of a tile, one load by the first wave of the loading group
+  const unsigned char* extb = kExt ? (const unsigned char*)s.ext + (int64_t)bh_ * nt_all * kExtTileB : nullptr;
+  const uint32_t lds_ext = lds_base + kExtOff;
   // kMulti: the record of a tile is written by the copy work-groups together with its chunk
-  int xcur_c = 0, xcur_first = 0;
+  int xcur_c = 0, xcur_end = kMulti ? tiles_of(s.chunk[0].Sc) : 0;
   auto await_record = [&](int idx) {
-    while (idx >= xcur_first + s.chunk[xcur_c].Sc / kTile) {
-      xcur_first += s.chunk[xcur_c].Sc / kTile;
+    while (idx >= xcur_end) {
       ++xcur_c;
+      xcur_end += tiles_of(s.chunk[xcur_c].Sc);
       if (s.arrive != nullptr && xcur_c > arrived_upto) {
         if (!wait_arrival(s.arrive + xcur_c, s.arrive_need, s.arrive_polls)) late = true;
         arrived_upto = xcur_c;
@@ -511,27 +511,39 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
     }
   };
   auto issue_ext = [&](int tile_idx, int stage) {
+    if ((wave & 3) != 0) return;
     if (kMulti) await_record(tile_idx);
-    lds_dma4(extb + (int64_t)tile_idx * kExtTileB + (wave & 3) * 256, lane * 4,
-             lds_ext + stage * kExtTileB + (wave & 3) * 256);
+    lds_dma4(extb + (int64_t)(tile_idx) * kExtTileB, lane * 4, lds_ext + stage * kExtTileB);
   };
-  auto issue_k_tile = [&](const unsigned char* tile, int tile_idx, int stage) {   // this wave's share
-    issue_k_half(tile, tile_idx, stage, 0, false); issue_k_half(tile, tile_idx, stage, 1, false);
-    if (kSplit) { issue_k_half(tile, tile_idx, stage, 0, true); issue_k_half(tile, tile_idx, stage, 1, true); }
+  auto issue_k_tile = [&](TileRef t, int stage) {   // this wave's share
+    issue_k_half(t, stage, 0, false); issue_k_half(t, stage, 1, false);
+    if (kSplit) { issue_k_half(t, stage, 0, true); issue_k_half(t, stage, 1, true); }
   };
-  auto issue_v_tile = [&](const unsigned char* tile, int tile_idx, int stage) {
-    issue_v_half(tile, tile_idx, stage, 0, false); issue_v_half(tile, tile_idx, stage, 1, false);
-    if (kSplit) { issue_v_half(tile, tile_idx, stage, 0, true); issue_v_half(tile, tile_idx, stage, 1, true); }
+  auto issue_v_tile = [&](TileRef t, int stage) {
+    issue_v_half(t, stage, 0, false); issue_v_half(t, stage, 1, false);
+    if (kSplit) { issue_v_half(t, stage, 0, true); issue_v_half(t, stage, 1, true); }
   };
 
-  // Where tile idx of the K (or V) stream starts.  kMulti: the tiles of the chunks follow one another;
-  // a cursor (chunk, index of its first tile) moves forward with the indices asked for.
-  struct TileCursor { int c, first; };
-  auto tile_at = [&](TileCursor& cur, int idx, bool is_v) -> const unsigned char* {
-    if (!kMulti) return (is_v ? vb : kb) + idx * tileB;
-    while (idx >= cur.first + s.chunk[cur.c].Sc / kTile) {
-      cur.first += s.chunk[cur.c].Sc / kTile;
+  // A place in the K or V stream, moved on by whole tiles.  kMulti: the chunks follow one another; a place
+  // that has run past its chunk (left <= 0) is carried into the next one when its tile is asked for.  Kept
+  // in scalar registers: a lone wave issues one instruction of any kind per 5 cycles or so, and looking the chunk up
+  // for every tile cost the softmax phase some hundred scalar instructions and the latency of their loads.
+  struct TileCursor { TileRef t; int c; };
+  auto chunk_base = [&](int c, bool is_v) -> const unsigned char* {
+    if (!kMulti) return is_v ? vb : kb;
+    const AttnStep::Chunk& ch = s.chunk[c];
+    return (const unsigned char*)((const bf16_t*)(is_v ? ch.v : ch.k) + b * ch.ks0 + h * ch.ks1);
+  };
+  auto place = [&](int idx, bool is_v) -> TileCursor {   // tile idx of the stream
+    return TileCursor{TileRef{chunk_base(0, is_v) + idx * tileB, (kMulti ? s.chunk[0].Sc : s.Sc) - idx * kTile}, 0};
+  };
+  auto settle = [&](TileCursor& cur, bool is_v) {
+    if (!kMulti) return;
+    while (cur.t.left <= 0) {
+      const int over = (-cur.t.left) / kTile;   // whole tiles of the next chunk
       ++cur.c;
+      cur.t.p = chunk_base(cur.c, is_v) + over * tileB;
+      cur.t.left = s.chunk[cur.c].Sc - over * kTile;
       if (s.arrive != nullptr && cur.c > arrived_upto) {
         // the count read a few tiles ago usually settles it; otherwise poll
         const bool seen = probe_c == cur.c && __builtin_amdgcn_readfirstlane(probe_val) >= s.arrive_need;
@@ -541,29 +553,30 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
     }
     // a few tiles before the K stream leaves a chunk, read the next chunk's count without waiting
     // for the answer: a blocking poll at the boundary costs a round trip to memory on the critical path
-    if (s.arrive != nullptr && !is_v && cur.c + 1 < s.n_multi && cur.c + 1 > arrived_upto && probe_c <= cur.c &&
-        idx + kProbeAheadTiles >= cur.first + s.chunk[cur.c].Sc / kTile) {
+    if (!is_v && cur.t.left <= kProbeAheadTiles * kTile && s.arrive != nullptr && cur.c + 1 < s.n_multi &&
+        cur.c + 1 > arrived_upto && probe_c <= cur.c) {
       probe_c = cur.c + 1;
       probe_val = __hip_atomic_load(s.arrive + probe_c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    const AttnStep::Chunk& ch = s.chunk[cur.c];
-    const bf16_t* base = (const bf16_t*)(is_v ? ch.v : ch.k) + b * ch.ks0 + h * ch.ks1;
-    return (const unsigned char*)base + (idx - cur.first) * tileB;
   };
-  TileCursor kcur{0, 0}, vcur{0, 0};
+  auto tile_at = [&](int idx, bool is_v) -> TileRef {
+    TileCursor cur = place(idx, is_v);
+    settle(cur, is_v);
+    return cur.t;
+  };
 
   // Tiles needed before the first loads of the softmax phases land are fetched here.
   //   wide : A's SM(j) prefetches K(j+2) (with its record) and V(j+1); B's SM(j), one phase later,
   //          K(j+3) and V(j+2).
-  //   split: the softmax phase p prefetches K(p+3), V(p+1) and the record of tile p+2.
+  //   split: the softmax phase p prefetches K(p+4), V(p+2) and the record of tile p+4.
   int kpre_idx, vpre_idx;   // next K / V tile this wave prefetches
   if (!kSplit) {
-    { const unsigned char* t = tile_at(kcur, 0, false); issue_k_half(t, 0, 0, 0, false); issue_k_half(t, 0, 0, 1, false); }
-    { const unsigned char* t = tile_at(vcur, 0, true); issue_v_half(t, 0, 0, 0, false); issue_v_half(t, 0, 0, 1, false); }
-    if (nt > 1) { const unsigned char* t = tile_at(kcur, 1, false); issue_k_half(t, 1, 1, 0, false); issue_k_half(t, 1, 1, 1, false); }
+    issue_k_tile(tile_at(0, false), 0);
+    issue_v_tile(tile_at(0, true), 0);
+    if (nt > 1) issue_k_tile(tile_at(1, false), 1);
     if (!grpA) {
-      if (nt > 1) { const unsigned char* t = tile_at(vcur, 1, true); issue_v_half(t, 1, 1, 0, false); issue_v_half(t, 1, 1, 1, false); }
-      if (nt > 2) { const unsigned char* t = tile_at(kcur, 2, false); issue_k_half(t, 2, 2, 0, false); issue_k_half(t, 2, 2, 1, false); }
+      if (nt > 1) issue_v_tile(tile_at(1, true), 1);
+      if (nt > 2) issue_k_tile(tile_at(2, false), 2);
     } else if (kExt) {
       issue_ext(0, 0);
       if (nt > 1) issue_ext(1, 1);
@@ -571,21 +584,21 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
     kpre_idx = grpA ? 2 : 3;
     vpre_idx = grpA ? 1 : 2;
   } else {
-    if (grpA) {   // the loading lambdas of the split kernel move a wave pair's rows: one group suffices
-      issue_k_tile(tile_at(kcur, 0, false), 0, 0);
-      issue_v_tile(tile_at(vcur, 0, true), 0, 0);
-      if (nt > 1) issue_k_tile(tile_at(kcur, 1, false), 1, 1);
-      if (nt > 2) issue_k_tile(tile_at(kcur, 2, false), 2, 2);
-      if (kExt) {
-        issue_ext(0, 0);
-        if (nt > 1) issue_ext(1, 1);
-      }
+    // (a group moves whole tiles, its own rows and its partner waves'.)  What phases 0 and 1 read; group B
+    // loads the rest, V(1) and K(3), in phase 0, where it has nothing else to do
+    if (grpA) {
+      issue_k_tile(tile_at(0, false), 0);
+      if (nt > 1) issue_k_tile(tile_at(1, false), 1);
+      issue_v_tile(tile_at(0, true), 0);
+      if (kExt)
+        for (int i = 0; i < 4 && i < nt; ++i) issue_ext(i, i);
+    } else {
+      if (nt > 2) issue_k_tile(tile_at(2, false), 2);
     }
-    kpre_idx = grpA ? 3 : 4;   // K(p+3) / V(p+1) of this group's first softmax phase, p = 0 (A) or 1 (B)
-    vpre_idx = grpA ? 1 : 2;
+    kpre_idx = grpA ? 4 : 5;   // K(p+4) / V(p+2) of this group's first softmax phase, p = 0 (A) or 1 (B)
+    vpre_idx = grpA ? 2 : 3;
   }
-  const unsigned char* kpre = kMulti ? nullptr : kb + kpre_idx * tileB;   // kMulti: looked up when the load is issued
-  const unsigned char* vpre = kMulti ? nullptr : vb + vpre_idx * tileB;
+  TileCursor kpre = place(kpre_idx, false), vpre = place(vpre_idx, true);
   constexpr int kPreStep = kSplit ? 2 : 1;   // tiles between two softmax phases of a wave
 
   // Q^T operand (B of S^T = K Q^T): lane (r, g) holds Q[q0 + 16*nb + r][32*ks + 8*g .. +7]
@@ -630,7 +643,7 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
         v_rd[db] = (lds_cptr)(uintptr_t)(lds_base + kStages * kTileB + vrow * RB + (((db & 3) ^ ((vrow >> 1) & 3)) << 5) + 8 * (r & 3));
     }
   }
-  // extended path: this lane's keys of a tile are rows 16*mb + 4*g + (0..3), mb = 0..3
+  // kExt: this lane's keys of a tile are rows 16*mb + 4*g + (0..3), mb = 0..3
   const lds_cptr x_rd = (lds_cptr)(uintptr_t)(lds_ext + 16 * g);
 
   // LDS operands.  K: keys 16*mb .. +15 (MFMA rows), head dims 32*ks + 8*g .. +7: one 16-byte read.
@@ -726,20 +739,18 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
   // does the wave find the true maximum, move m, rescale O and l, and redo the exponentials.
   // While it runs, the wave also issues its tile loads, spread between the exponential blocks so
   // that the waves do not hit the load path at once.
-  // Extended path: the per-key factor c replaces the uniform scale, and in a tile with dead keys
-  // their bias (-inf) is added to the exponent.
-  auto x_vec = [&](int stage, int which, int mb) -> f32x4 {   // which: 0 c, 1 bias; keys 16*mb + 4*g + (0..3)
-    return *reinterpret_cast<const __attribute__((address_space(3))) f32x4*>(
-        x_rd + stage * kExtTileB + which * 256 + 64 * mb);
+  // kExt: the per-key factor c replaces the uniform scale.
+  auto x_vec = [&](int stage, int mb) -> f32x4 {   // c of keys 16*mb + 4*g + (0..3)
+    return *reinterpret_cast<const __attribute__((address_space(3))) f32x4*>(x_rd + stage * kExtTileB + 64 * mb);
   };
   // c of the second key step is fetched while the first is computed
   f32x4 xc[2][2];
   auto x_load = [&](int kk, int xs) {
 #pragma unroll
-    for (int a = 0; a < 2; ++a) xc[kk][a] = x_vec(xs, 0, 2 * kk + a);
+    for (int a = 0; a < 2; ++a) xc[kk][a] = x_vec(xs, 2 * kk + a);
   };
   // one block: the 8 scores of query block nb over key step kk -> pk[kk][nb]
-  auto exp_block = [&](int kk, int nb, float& psum, int xs, bool dead_keys, bool fetch_ahead) {
+  auto exp_block = [&](int kk, int nb, float& psum, int xs, bool fetch_ahead) {
     float p[8];
     if (!kExt) {
 #pragma unroll
@@ -753,17 +764,9 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
       if (fetch_ahead && kk == 0 && nb == 1) x_load(1, xs);   // blocks run in the order (0,0) (0,1) (1,0) (1,1)
 #pragma unroll
       for (int a = 0; a < 2; ++a) {
-        f32x4 t;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) t[e] = fmaf(sacc[2 * kk + a][nb][e], xc[kk][a][e], -m[nb]);
-        if (dead_keys) {
-          const f32x4 bias = x_vec(xs, 1, 2 * kk + a);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) t[e] += bias[e];
-        }
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          p[4 * a + e] = __builtin_amdgcn_exp2f(t[e]);
+          p[4 * a + e] = __builtin_amdgcn_exp2f(fmaf(sacc[2 * kk + a][nb][e], xc[kk][a][e], -m[nb]));
           psum += p[4 * a + e];
         }
       }
@@ -789,11 +792,11 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
     }
 #pragma unroll
     for (int mb = 0; mb < 4; ++mb) {
-      const f32x4 c = x_vec(xs, 0, mb), bias = x_vec(xs, 1, mb);
+      const f32x4 c = x_vec(xs, mb);
 #pragma unroll
       for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) tmax[nb] = fmaxf(tmax[nb], fmaf(sacc[mb][nb][e], c[e], bias[e]));
+        for (int e = 0; e < 4; ++e) tmax[nb] = fmaxf(tmax[nb], sacc[mb][nb][e] * c[e]);
     }
     tmax[0] = xgroup_max(tmax[0]);
     tmax[1] = xgroup_max(tmax[1]);
@@ -819,48 +822,32 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
   constexpr float kRefMargin = 32.0f;
   constexpr int kMaxFirstTiles = 8;
   int max_first = 0;
-  // "some key of the tile is dead", read from the tile's record in global memory through the scalar
-  // path (uniform address, written by an earlier launch) one softmax phase ahead of its use, so that
-  // no softmax phase starts by waiting for it
-  auto tile_flag = [&](int tile) -> float {
-    typedef const __attribute__((address_space(4))) float* const_fptr;
-    const float* p = s.ext + ((int64_t)bh_ * nt_all + min(tile, nt_all - 1)) * (kExtTileB / 4) + 128;
-    return *(const_fptr)(uintptr_t)p;
-  };
-  // several chunks per launch: the records are written while the launch runs, so a tile's flag cannot
-  // be fetched ahead from global memory; tiles of chunks that came with a key mask read it from their
-  // record in LDS when the softmax phase starts (a short wait), tiles of other chunks skip it
-  int sm_c = 0, sm_first = 0;   // chunk of sm_tile and the index of its first tile
-  auto chunk_masked = [&](int tile) -> bool {
-    while (sm_c + 1 < s.n_multi && tile >= sm_first + s.chunk[sm_c].Sc / kTile) {
-      sm_first += s.chunk[sm_c].Sc / kTile;
-      ++sm_c;
-    }
-    return s.chunk[sm_c].mask_src != nullptr;
-  };
-  int sm_tile = (kSplit && !grpA) ? 1 : 0;   // tile of this wave's next softmax phase
-  float flag_next = 0.0f;
+  int sm_tile = kSplit && !grpA ? 1 : 0;   // kDead: tile of this wave's next softmax phase
+  int next_dead = 0;                         // kDead: the next tile with a dead key, as far as it has been looked up
   // SM of the tile whose record sits in stage xs; loads K tile kpre_idx into stage sk (if do_k, with
   // the record of tile xpre_idx into stage xst if do_x) and V tile vpre_idx into stage sv (if do_v)
   auto SM = [&](int xs, int sk, int sv, bool do_k, bool do_v, bool do_x, int xpre_idx, int xst) {
     float psum[2] = {0.0f, 0.0f};
-    bool dead_keys = false;
     if (kExt) x_load(0, xs);
-    if (kExt && !kNoDead) {
-      // this tile's flag was fetched during the wave's previous softmax phase; fetch the next one
-      if (kMulti) {
-        // a tile of a chunk that came with a mask: its flag, from the record in LDS
-        if (chunk_masked(sm_tile)) {
-          const float f = *reinterpret_cast<const __attribute__((address_space(3))) float*>(
-              (lds_cptr)(uintptr_t)(lds_ext + xs * kExtTileB + 512));
-          dead_keys = __builtin_amdgcn_readfirstlane(__float_as_uint(f)) != 0u;
+    if (kDead) {
+      if (next_dead < sm_tile) next_dead = find_dead(sm_tile);
+      if (next_dead == sm_tile) {
+        // (any positive finite factor keeps -inf, and exp2 makes it 0)
+        const uint64_t live = dead_word(sm_tile) >> (4 * g);
+#pragma unroll
+        for (int mb = 0; mb < 4; ++mb) {
+          const uint32_t bits = (uint32_t)(live >> (16 * mb));   // bit e: key 16*mb + 4*g + e
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const bool keep = (bits & (1u << e)) != 0u;
+            sacc[mb][0][e] = keep ? sacc[mb][0][e] : -INFINITY;
+            sacc[mb][1][e] = keep ? sacc[mb][1][e] : -INFINITY;
+          }
+          __builtin_amdgcn_sched_barrier(0);   // one block's lane masks at a time: sixteen pairs of scalar registers are not to be had
         }
-        sm_tile += kPreStep;
-      } else {
-        dead_keys = flag_next != 0.0f;
-        sm_tile += kPreStep;
-        flag_next = tile_flag(sm_tile);
+        next_dead = find_dead(sm_tile + 1);
       }
+      sm_tile += kPreStep;
     }
     if (max_first > 0) {
       --max_first;
@@ -880,44 +867,41 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
       }
       __builtin_amdgcn_sched_barrier(0);
     }
-    if (kMulti) {
-      if (do_k) kpre = tile_at(kcur, kpre_idx, false);
-      if (do_v) vpre = tile_at(vcur, vpre_idx, true);
-    }
+    if (do_k) settle(kpre, false);
+    if (do_v) settle(vpre, true);
     // sched_barrier: keep each load between two blocks of arithmetic (the scheduler would
     // otherwise hoist all of them to the top, where they queue behind one another)
     if (!kSplit) {
-      if (do_k) issue_k_half(kpre, kpre_idx, sk, 0, false);
-      exp_block(0, 0, psum[0], xs, dead_keys, true);
+      if (do_k) issue_k_half(kpre.t, sk, 0, false);
+      exp_block(0, 0, psum[0], xs, true);
       __builtin_amdgcn_sched_barrier(0);
-      if (do_k) issue_k_half(kpre, kpre_idx, sk, 1, false);
-      exp_block(0, 1, psum[1], xs, dead_keys, true);
+      if (do_k) issue_k_half(kpre.t, sk, 1, false);
+      exp_block(0, 1, psum[1], xs, true);
       __builtin_amdgcn_sched_barrier(0);
-      if (do_v) issue_v_half(vpre, vpre_idx, sv, 0, false);
-      exp_block(1, 0, psum[0], xs, dead_keys, true);
+      if (do_v) issue_v_half(vpre.t, sv, 0, false);
+      exp_block(1, 0, psum[0], xs, true);
       __builtin_amdgcn_sched_barrier(0);
-      if (do_v) issue_v_half(vpre, vpre_idx, sv, 1, false);
+      if (do_v) issue_v_half(vpre.t, sv, 1, false);
       if (kExt && do_x) issue_ext(xpre_idx, xst);
-      exp_block(1, 1, psum[1], xs, dead_keys, true);
+      exp_block(1, 1, psum[1], xs, true);
       __builtin_amdgcn_sched_barrier(0);
     } else {
-      if (do_v) { issue_v_half(vpre, vpre_idx, sv, 0, false); issue_v_half(vpre, vpre_idx, sv, 0, true); }
-      exp_block(0, 0, psum[0], xs, dead_keys, true);
+      if (do_v) { issue_v_half(vpre.t, sv, 0, false); issue_v_half(vpre.t, sv, 0, true); }
+      exp_block(0, 0, psum[0], xs, true);
       __builtin_amdgcn_sched_barrier(0);
-      if (do_v) { issue_v_half(vpre, vpre_idx, sv, 1, false); issue_v_half(vpre, vpre_idx, sv, 1, true); }
-      exp_block(0, 1, psum[1], xs, dead_keys, true);
+      if (do_v) { issue_v_half(vpre.t, sv, 1, false); issue_v_half(vpre.t, sv, 1, true); }
+      exp_block(0, 1, psum[1], xs, true);
       __builtin_amdgcn_sched_barrier(0);
-      if (do_k) { issue_k_half(kpre, kpre_idx, sk, 0, false); issue_k_half(kpre, kpre_idx, sk, 0, true); }
-      exp_block(1, 0, psum[0], xs, dead_keys, true);
+      if (do_k) { issue_k_half(kpre.t, sk, 0, false); issue_k_half(kpre.t, sk, 0, true); }
+      exp_block(1, 0, psum[0], xs, true);
       __builtin_amdgcn_sched_barrier(0);
-      if (do_k) { issue_k_half(kpre, kpre_idx, sk, 1, false); issue_k_half(kpre, kpre_idx, sk, 1, true); }
+      if (do_k) { issue_k_half(kpre.t, sk, 1, false); issue_k_half(kpre.t, sk, 1, true); }
       if (kExt && do_x) issue_ext(xpre_idx, xst);
-      exp_block(1, 1, psum[1], xs, dead_keys, true);
+      exp_block(1, 1, psum[1], xs, true);
       __builtin_amdgcn_sched_barrier(0);
     }
-    if (!kMulti) { kpre += kPreStep * tileB; vpre += kPreStep * tileB; }
-    kpre_idx += kPreStep;
-    vpre_idx += kPreStep;
+    kpre.t.p += kPreStep * tileB; kpre.t.left -= kPreStep * kTile;
+    vpre.t.p += kPreStep * tileB; vpre.t.left -= kPreStep * kTile;
     // (per query block: a block all of whose lanes passed keeps its exponentials and its reference)
     const bool redo0 = __builtin_amdgcn_ballot_w64(!(psum[0] <= kCertifiedSum)) != 0ull;
     const bool redo1 = __builtin_amdgcn_ballot_w64(!(psum[1] <= kCertifiedSum)) != 0ull;
@@ -937,12 +921,12 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
         m[nb] = m_new;
         rescale(nb, alpha);
         psum[nb] = 0.0f;
-        if (kExt && m_new == -INFINITY) {
+        if ((kExt || kDead) && m_new == -INFINITY) {
           pk[0][nb] = u32x4{0u, 0u, 0u, 0u};
           pk[1][nb] = u32x4{0u, 0u, 0u, 0u};
         } else {
-          exp_block(0, nb, psum[nb], xs, dead_keys, false);
-          exp_block(1, nb, psum[nb], xs, dead_keys, false);
+          exp_block(0, nb, psum[nb], xs, false);
+          exp_block(1, nb, psum[nb], xs, false);
         }
       }
     }
@@ -957,7 +941,6 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
     asm volatile("" : "+v"(lsum[0]), "+v"(lsum[1]));
   };
   auto nxt = [](int x) { return x == 2 ? 0 : x + 1; };
-  if (kExt && !kNoDead && !kMulti) flag_next = tile_flag(sm_tile);
   auto first_scores = [&](int stage) {
 #pragma unroll
     for (int mb = 0; mb < 4; ++mb) {
@@ -974,7 +957,12 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
 
   // prologue: the first tiles have landed
   __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
-  __builtin_amdgcn_s_barrier();
+  if (kDead) {
+    __syncthreads();                      // (orders the words too)
+    next_dead = find_dead(0);
+  } else {
+    __builtin_amdgcn_s_barrier();
+  }
 
   if (!kSplit) {
     first_scores(0);   // scores of tile 0 in both groups
@@ -996,8 +984,8 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
     auto phase_barrier = [&](int wait_mode, bool needed = true) {   // 0: no wait, 1: all but the last full batch, 2: vmcnt(0)
       __builtin_amdgcn_sched_barrier(0);
       if (wait_mode == 1) {
-        // a full batch is 4 loads (2 with 128-byte rows), plus the record's in the group that loads it
-        if (kExt && grpA) __builtin_amdgcn_s_waitcnt(kHalfD ? 0x0F73 : 0x0F75);   // vmcnt(3) / vmcnt(5)
+        // a full batch is 4 loads (2 with 128-byte rows), plus the record's in the wave that loads it
+        if (kExt && wave == 0) __builtin_amdgcn_s_waitcnt(kHalfD ? 0x0F73 : 0x0F75);   // vmcnt(3) / vmcnt(5)
         else __builtin_amdgcn_s_waitcnt(kHalfD ? 0x0F72 : 0x0F74);                // vmcnt(2) / vmcnt(4)
       } else if (wait_mode == 2) __builtin_amdgcn_s_waitcnt(0x0F70);
       if (needed) __builtin_amdgcn_s_barrier();
@@ -1043,40 +1031,54 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
     // scores of tile 0 (group A) / tile 1 (group B)
     if (grpA || nt > 1) first_scores(grpA ? 0 : 1);
     // Phases p = 0..nt, one work-group barrier each; both groups execute nt + 1 of them.
-    //   reads in phase p : V(p-1) from stage (p-1)%3, K(p+1) from stage (p+1)%3, record p from p%3
-    //   batch of phase p : K(p+3) -> stage p%3 (last read, as K(p), in phase p-1),
-    //                      V(p+1) -> stage (p+1)%3 (last read, as V(p-2), in phase p-1),
-    //                      record p+2 -> stage (p+2)%3 (last read, as record p-1, in phase p-1)
-    //   end of phase p   : the batch of phase p-1 must have landed (first read in phase p+1); its
-    //                      issuers are the group now ending a matrix phase, which waits for all of
-    //                      its loads; the other group has only this phase's batch in flight
-    auto end_phase = [&](bool wait_loads) {
+    //   reads in phase p : V(p-1) and K(p+1) (stages mod 4), record p (mod 8)
+    //   batch of phase p : K(p+4) into the stage of K(p), last read in phase p-1,
+    //                      V(p+2) into the stage of V(p-2), last read in phase p-1,
+    //                      record p+4 into the stage of record p-4, last read in phase p-4
+    //   first read of it : phase p+3 (record: p+4).  Its issuers, in their softmax phase again in phase p+2,
+    //                      wait for it at that phase's end, with that phase's own batch still in flight.
+    // Three stages and a wait one phase earlier, as this kernel began, gave a load one to two phases of
+    // 0.75 us, less than the memory behind the L2 takes when the chip is full: a ring of four chunks of 1152 on
+    // 24 heads (216 work-groups) 78.8 -> 72 us, of eight chunks of 2112 on 12 heads (204) 269 -> 247 us.
+    auto end_phase = [&]() {
       __builtin_amdgcn_sched_barrier(0);
-      if (wait_loads) __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
       __builtin_amdgcn_s_barrier();
       __builtin_amdgcn_sched_barrier(0);
     };
+    auto wait_but = [&](bool do_k, bool do_v, bool do_x) {   // all loads but those of the batch just issued
+      __builtin_amdgcn_sched_barrier(0);
+      if (do_k) {   // (and then V too)
+        if (kExt && do_x && (wave & 3) == 0) __builtin_amdgcn_s_waitcnt(kHalfD ? 0x0F75 : 0x0F79);   // vmcnt(5) / vmcnt(9)
+        else __builtin_amdgcn_s_waitcnt(kHalfD ? 0x0F74 : 0x0F78);                                   // vmcnt(4) / vmcnt(8)
+      } else if (do_v) __builtin_amdgcn_s_waitcnt(kHalfD ? 0x0F72 : 0x0F74);                         // vmcnt(2) / vmcnt(4)
+      else __builtin_amdgcn_s_waitcnt(0x0F70);
+    };
+    end_phase();                           // K(0) has been read by every wave before phase 0 loads over it
     int t = grpA ? 0 : 1;                  // this group's current tile; SM(t) runs in phase t
-    int st = t;                            // t % 3
-    if (!grpA) end_phase(false);           // phase 0: group B has no scores yet
-    while (t + 2 < nt) {
-      const int s1 = nxt(st), s2 = nxt(s1);                // (t + 1) % 3, (t + 2) % 3
-      SM(st, st, s1, t + 3 < nt, true, true, t + 2, s2);   // phase t (t + 1 < nt holds here)
-      end_phase(false);
-      MM_full(st, s2);                                     // phase t + 1
-      end_phase(true);
-      t += 2;
-      st = s2;
+    if (!grpA) {                           // phase 0: group B has no scores yet
+      if (nt > 1) issue_v_tile(tile_at(1, true), 1);
+      if (nt > 3) issue_k_tile(tile_at(3, false), 3);
+      end_phase();
     }
-    if (t < nt) {                                          // this group's last tile
-      SM(st, st, nxt(st), false, t + 1 < nt, false, 0, 0);
-      end_phase(false);
-      MM_last(st);
-      end_phase(true);
+    while (t + 2 < nt) {
+      const bool do_k = t + 4 < nt;
+      SM(t & 7, t & 3, (t + 2) & 3, do_k, true, do_k, t + 4, (t + 4) & 7);   // phase t
+      wait_but(do_k, true, do_k);
+      end_phase();
+      MM_full(t & 3, (t + 2) & 3);                                           // phase t + 1
+      end_phase();
+      t += 2;
+    }
+    if (t < nt) {                                                            // this group's last tile
+      SM(t & 7, 0, 0, false, false, false, 0, 0);
+      wait_but(false, false, false);
+      end_phase();
+      MM_last(t & 3);
+      end_phase();
       t += 2;
     }
     // the group whose last matrix phase was phase nt-1 sits out phase nt
-    if ((grpA && (nt % 2 == 0)) || (!grpA && (nt % 2 == 1))) end_phase(false);
+    if ((grpA && (nt % 2 == 0)) || (!grpA && (nt % 2 == 1))) end_phase();
   }
   }  // nt > 0
   // A wave that gave up waiting for a chunk loaded its rows of the tiles too early, and every wave of
@@ -1125,7 +1127,7 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
   else finish_and_store<kHalfD>(s, oacc, m, lsum, b, h, q0, r, g, smem_raw + wave * kEpiWaveB, kMulti && late);
 }
 
-template <bool kSplit, bool kExt, bool kMulti = false, bool kNoDead = false, bool kHalfD = false>
+template <bool kSplit, bool kExt, bool kMulti, bool kDead, bool kHalfD>
 __global__ __launch_bounds__(kThreads, 2) void attn_pp_kernel(AttnStep s) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   if (!kMulti && s.copy_wgs > 0 && blockIdx.x >= gridDim.x - s.copy_wgs) {   // prefetch work-group: copy and leave
@@ -1138,13 +1140,13 @@ __global__ __launch_bounds__(kThreads, 2) void attn_pp_kernel(AttnStep s) {
   if (kMulti && s.arrive != nullptr) {   // the whole ring's transfers ride in this launch, in its first work-groups
     if ((int)blockIdx.x < s.copy_wgs) {
       if (kExt && s.multi_fp8) stream_chunks_fp8(s, blockIdx.x, threadIdx.x, kThreads);
-      else stream_chunks(s, blockIdx.x, threadIdx.x, kThreads);   // bf16 chunks (their records, if any, were written before the launch)
+      else stream_chunks(s, blockIdx.x, threadIdx.x, kThreads);
       return;
     }
     lead = s.copy_wgs;
   }
   if (!wg_to_tile(s.copy_wgs, (s.Sq + kQBlock - 1) / kQBlock, s.B * s.H, bh_, qb_, lead)) return;   // whole work-group
-  attn_pp_body<kSplit, kExt, kMulti, kNoDead, kHalfD>(s, smem_raw, bh_, qb_ * kQBlock);
+  attn_pp_body<kSplit, kExt, kMulti, kDead, kHalfD>(s, smem_raw, bh_, qb_ * kQBlock);
 }
 
 // Mixed launch: when the 256-query blocks do not fill the last round of work-groups on the 256 CUs
@@ -1152,7 +1154,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_pp_kernel(AttnStep s) {
 // of 128 queries each, which take about 0.55 of a wide work-group's time.  Per XCD (ids go round
 // robin) the contiguous, head-major range of blocks is dispatched wide blocks first, then the
 // halves of its last s.mix_halves blocks.
-template <bool kExt>
+template <bool kExt, bool kDead>
 __global__ __launch_bounds__(kThreads, 2) void attn_pp_mixed_kernel(AttnStep s) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   if (s.copy_wgs > 0 && blockIdx.x >= gridDim.x - s.copy_wgs) {
@@ -1170,7 +1172,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_pp_mixed_kernel(AttnStep s) 
   if (slot < wide) {
     const int item = first + slot;
     const int bh_ = item / nqb;
-    attn_pp_body<false, kExt>(s, smem_raw, bh_, (item - bh_ * nqb) * kQPerWG);
+    attn_pp_body<false, kExt, false, kDead, false>(s, smem_raw, bh_, (item - bh_ * nqb) * kQPerWG);
   } else {
     const int hs = slot - wide;
     if (hs >= 2 * halves) return;
@@ -1178,7 +1180,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_pp_mixed_kernel(AttnStep s) 
     const int bh_ = item / nqb;
     const int q_base = (item - bh_ * nqb) * kQPerWG + (hs & 1) * kQPerWGSplit;
     if (q_base >= s.Sq) return;                        // second half of a ragged last block
-    attn_pp_body<true, kExt>(s, smem_raw, bh_, q_base);
+    attn_pp_body<true, kExt, false, kDead, false>(s, smem_raw, bh_, q_base);
   }
 }
 
@@ -1188,63 +1190,15 @@ bool attn_mfma_supported(const AttnStep& s) {
   return s.qo_dtype == USP_BF16 && s.kv_dtype == USP_BF16 && (s.d == kD || (s.d == 64 && s.half_d)) && s.Sq > 0;
 }
 
-size_t attn_mfma_ext_bytes(int B, int H, int Sc) {
-  const size_t nt_all = (size_t)(Sc + kTile - 1) / kTile;
-  return (size_t)B * H * nt_all * kExtTileB;
-}
-
-bool attn_mfma_needs_ext(const AttnStep& s) {
-  return !(s.Sc > 0 && s.Sc % kTile == 0 && !s.key_mask && !s.k_scale);
-}
-
-usp_status launch_attn_ext_prepare(const AttnStep& s, hipStream_t st) {
-  const unsigned nt_all = (unsigned)((s.Sc + kTile - 1) / kTile);
-  hipLaunchKernelGGL(attn_ext_prepare_kernel, dim3(nt_all > 0 ? nt_all : 1, (unsigned)(s.B * s.H)), dim3(64), 0, st,
-                     s, s.ext, s.n_live);
-  USP_CHECK_HIP(hipGetLastError());
-  return USP_OK;
-}
-
 usp_status launch_attn_fp8_chunk_prepare(const AttnStep& s, int c, bool reset_arrive, hipStream_t st) {
   if (!s.multi_fp8 || c < 0 || c >= s.n_multi || !s.ext || (reset_arrive && !s.arrive)) {
-    set_error("FP8 chunk preparation needs a step over several FP8 chunks with its records");
+    set_error("FP8 chunk preparation needs a step over FP8 chunks with its records");
     return USP_ERR_INVALID_ARG;
   }
   const int64_t units = (int64_t)s.B * s.H * s.chunk[c].Sc * (s.d / 16);   // 16 codes each
   const int64_t blocks = (units + 255) / 256;                          // one unit per thread while the chunk is small
   hipLaunchKernelGGL(attn_fp8_chunk_prepare_kernel, dim3((unsigned)(blocks < 1 ? 1 : blocks > 8192 ? 8192 : blocks)), dim3(256),
                      0, st, s, c, reset_arrive ? 1 : 0);
-  USP_CHECK_HIP(hipGetLastError());
-  return USP_OK;
-}
-
-usp_status launch_attn_fp8_step_prepare(const AttnStep& s, int* n_live, hipStream_t st) {
-  if (!s.multi_fp8 || s.n_multi != 1 || !s.ext || !n_live || s.chunk[0].Sc <= 0 || s.chunk[0].Sc % kTile != 0) {
-    set_error("FP8 step preparation needs one FP8 chunk of whole tiles with room for its records");
-    return USP_ERR_INVALID_ARG;
-  }
-  const int64_t units = (int64_t)s.B * s.H * s.chunk[0].Sc * (s.d / 16);   // 16 codes each
-  const int64_t blocks = (units + 255) / 256;
-  hipLaunchKernelGGL(attn_fp8_step_prepare_kernel, dim3((unsigned)(blocks < 1 ? 1 : blocks > 8192 ? 8192 : blocks)), dim3(256),
-                     0, st, s, n_live);
-  USP_CHECK_HIP(hipGetLastError());
-  return USP_OK;
-}
-
-usp_status launch_attn_multi_records(const AttnStep& s, hipStream_t st) {
-  int nt_total = 0;
-  for (int c = 0; c < s.n_multi; ++c) {
-    if (s.chunk[c].Sc <= 0 || s.chunk[c].Sc % kTile != 0) {
-      set_error("records of a launch over several chunks need chunk lengths that are positive multiples of %d", kTile);
-      return USP_ERR_INVALID_ARG;
-    }
-    nt_total += s.chunk[c].Sc / kTile;
-  }
-  if (s.n_multi <= 0 || s.n_multi > AttnStep::kMaxMulti || !s.ext || s.multi_fp8) {
-    set_error("records of a launch over several bf16 chunks need the chunks and room for the records");
-    return USP_ERR_INVALID_ARG;
-  }
-  hipLaunchKernelGGL(attn_multi_records_kernel, dim3((unsigned)nt_total, (unsigned)(s.B * s.H)), dim3(64), 0, st, s);
   USP_CHECK_HIP(hipGetLastError());
   return USP_OK;
 }
@@ -1256,43 +1210,56 @@ usp_status launch_attn_arrive_reset(int* arrive, hipStream_t st) {
 }
 
 namespace {
-template <bool kSplit, bool kExt, bool kMulti = false, bool kNoDead = false, bool kHalfD = false>
-usp_status launch_pp_d(const AttnStep& s, unsigned wgs, hipStream_t st) {
-  static_assert(kLdsBytes >= (int)sizeof(SmemPPExt) && kLdsBytes <= 160 * 1024, "LDS plan");
+template <bool kSplit, bool kExt, bool kMulti, bool kDead, bool kHalfD>
+usp_status launch_pp(const AttnStep& s, unsigned wgs, hipStream_t st) {
   constexpr int lds = kLdsBytes;
-  USP_CHECK_HIP((allow_large_lds<attn_pp_kernel<kSplit, kExt, kMulti, kNoDead, kHalfD>>(lds)));
-  hipLaunchKernelGGL((attn_pp_kernel<kSplit, kExt, kMulti, kNoDead, kHalfD>), dim3(wgs + s.copy_wgs), dim3(kThreads), lds, st, s);
+  USP_CHECK_HIP((allow_large_lds<attn_pp_kernel<kSplit, kExt, kMulti, kDead, kHalfD>>(lds)));
+  hipLaunchKernelGGL((attn_pp_kernel<kSplit, kExt, kMulti, kDead, kHalfD>), dim3(wgs + s.copy_wgs), dim3(kThreads), lds, st, s);
   USP_CHECK_HIP(hipGetLastError());
   return USP_OK;
 }
-template <bool kSplit, bool kExt, bool kMulti = false, bool kNoDead = false>
-usp_status launch_pp(const AttnStep& s, unsigned wgs, hipStream_t st) {
-  return s.half_d ? launch_pp_d<kSplit, kExt, kMulti, kNoDead, true>(s, wgs, st)
-                  : launch_pp_d<kSplit, kExt, kMulti, kNoDead, false>(s, wgs, st);
+template <bool kExt, bool kMulti, bool kDead>
+usp_status launch_pp_form(const AttnStep& s, bool split, unsigned wgs, hipStream_t st) {
+  if (s.half_d) return split ? launch_pp<true, kExt, kMulti, kDead, true>(s, wgs, st) : launch_pp<false, kExt, kMulti, kDead, true>(s, wgs, st);
+  return split ? launch_pp<true, kExt, kMulti, kDead, false>(s, wgs, st) : launch_pp<false, kExt, kMulti, kDead, false>(s, wgs, st);
+}
+template <bool kMulti>
+usp_status launch_pp_any(const AttnStep& s, bool ext, bool dead, bool split, unsigned wgs, hipStream_t st) {
+  if (ext) return dead ? launch_pp_form<true, kMulti, true>(s, split, wgs, st) : launch_pp_form<true, kMulti, false>(s, split, wgs, st);
+  return dead ? launch_pp_form<false, kMulti, true>(s, split, wgs, st) : launch_pp_form<false, kMulti, false>(s, split, wgs, st);
+}
+template <bool kExt, bool kDead>
+usp_status launch_mixed(const AttnStep& s, unsigned wgs, hipStream_t st) {
+  constexpr int lds = kLdsBytes;
+  USP_CHECK_HIP((allow_large_lds<attn_pp_mixed_kernel<kExt, kDead>>(lds)));
+  hipLaunchKernelGGL((attn_pp_mixed_kernel<kExt, kDead>), dim3(wgs + s.copy_wgs), dim3(kThreads), lds, st, s);
+  USP_CHECK_HIP(hipGetLastError());
+  return USP_OK;
 }
 }  // namespace
+
+int64_t attn_mfma_max_dead_tiles() { return kMaxWords; }
 
 usp_status launch_attn_mfma(const AttnStep& step, hipStream_t st) {
   AttnStep s = step;
   if (s.n_multi > 0) {
     // several resident chunks, one launch: the same two work decompositions, by the same rule
     if (s.n_multi > AttnStep::kMaxMulti || s.mode != 0 || s.n_copy != 0 || s.key_mask || s.k_scale || s.v_scale) {   // (n_copy: the per-step form of the transfers)
-      set_error("a launch over several chunks takes at most %d unmasked chunks and finishes the result", AttnStep::kMaxMulti);
+      set_error("a launch over several chunks takes at most %d chunks and finishes the result", AttnStep::kMaxMulti);
       return USP_ERR_INVALID_ARG;
     }
     if (s.multi_fp8 && (!s.arrive || !s.ext)) {
       set_error("a launch over several FP8 chunks needs arrival counters and per-tile records");
       return USP_ERR_INVALID_ARG;
     }
-    if (!s.multi_fp8 && s.multi_masked && !s.ext) {
-      set_error("a launch over several chunks with key masks needs their per-tile records");
-      return USP_ERR_INVALID_ARG;
-    }
-    for (int c = 0; c < s.n_multi; ++c)
-      if (s.chunk[c].Sc <= 0 || s.chunk[c].Sc % kTile != 0 || !s.chunk[c].k || !s.chunk[c].v) {
-        set_error("a launch over several chunks needs chunk lengths that are positive multiples of %d", kTile);
+    bool dead = false;
+    for (int c = 0; c < s.n_multi; ++c) {
+      if (s.chunk[c].Sc <= 0 || !s.chunk[c].k || !s.chunk[c].v) {
+        set_error("a launch over several chunks needs chunks that hold keys");
         return USP_ERR_INVALID_ARG;
       }
+      dead |= s.chunk[c].mask_src != nullptr || s.chunk[c].Sc % kTile != 0;
+    }
     const unsigned w256 = wg_grid_size((s.Sq + kQPerWG - 1) / kQPerWG, s.B * s.H);
     const unsigned w128 = wg_grid_size((s.Sq + kQPerWGSplit - 1) / kQPerWGSplit, s.B * s.H);
     // There is no mixed form of this launch: between the two decompositions, take the one whose
@@ -1306,8 +1273,7 @@ usp_status launch_attn_mfma(const AttnStep& step, hipStream_t st) {
       for (int c = s.multi_fp8 ? 0 : 1; c < s.n_multi; ++c)
         if (!s.chunk[c].k_src || !s.chunk[c].v_src || s.chunk[c].bytes <= 0 || s.chunk[c].bytes % 16 != 0 ||
             !aligned16(s.chunk[c].k_src) || !aligned16(s.chunk[c].v_src) || !aligned16(s.chunk[c].k) || !aligned16(s.chunk[c].v) ||
-            (s.multi_fp8 && (!s.chunk[c].k_scale_src || !s.chunk[c].v_scale_src || !aligned16(s.chunk[c].k_scale_src) ||
-                             ((uintptr_t)s.chunk[c].mask_src & 3u) != 0))) {
+            (s.multi_fp8 && (!s.chunk[c].k_scale_src || !s.chunk[c].v_scale_src))) {
           set_error("transfers inside a launch over several chunks need 16-byte aligned sources and buffers");
           return USP_ERR_INVALID_ARG;
         }
@@ -1317,21 +1283,16 @@ usp_status launch_attn_mfma(const AttnStep& step, hipStream_t st) {
       s.arrive_need = s.copy_wgs + (s.arrive_need_extra > 0 ? s.arrive_need_extra : 0);
       if (s.arrive_polls <= 0 || s.arrive_polls > kArrivePolls) s.arrive_polls = kArrivePolls;
     }
-    if (s.multi_fp8 && s.multi_masked)
-      return split ? launch_pp<true, true, true, false>(s, wgs, st) : launch_pp<false, true, true, false>(s, wgs, st);
-    if (s.multi_fp8) return split ? launch_pp<true, true, true, true>(s, wgs, st) : launch_pp<false, true, true, true>(s, wgs, st);
-    if (s.multi_masked)   // bf16 chunks, records written by launch_attn_multi_records
-      return split ? launch_pp<true, true, true, false>(s, wgs, st) : launch_pp<false, true, true, false>(s, wgs, st);
-    if (split) return launch_pp<true, false, true>(s, wgs, st);
-    return launch_pp<false, false, true>(s, wgs, st);
+    return launch_pp_any<true>(s, s.multi_fp8 != 0, dead, split, wgs, st);
   }
-  const bool ext = attn_mfma_needs_ext(s);
+  const bool ext = s.k_scale != nullptr;
+  const bool dead = s.key_mask != nullptr || s.Sc % kTile != 0 || s.Sc == 0;
   // Few query blocks (a small Q shard of a ring step): 256-query work-groups would leave CUs idle;
   // 128-query work-groups whose two wave groups split the keys fill twice as many.
   const unsigned wgs256 = wg_grid_size((s.Sq + kQPerWG - 1) / kQPerWG, s.B * s.H);
   const bool split = s.variant == 2 || (s.variant == 0 && (int)wgs256 <= kSplitBelowWGs);
-  if (ext && (s.ext == nullptr || s.n_live == nullptr)) {
-    set_error("attention step with a key mask, FP8 scales or a ragged chunk needs its per-tile records");
+  if (ext && s.ext == nullptr) {
+    set_error("attention step with FP8 scales needs its per-tile records");
     return USP_ERR_INVALID_ARG;
   }
   if (s.v_scale != nullptr) {
@@ -1350,24 +1311,12 @@ usp_status launch_attn_mfma(const AttnStep& step, hipStream_t st) {
     const int per = (items + kXcds - 1) / kXcds;
     const unsigned wgs_mixed = (unsigned)(kXcds * (per + s.mix_halves));
     s.copy_wgs = prefetch_wg_count(s, (int)wgs_mixed, 1);
-    constexpr int lds = kLdsBytes;
-    if (ext) {
-      USP_CHECK_HIP(allow_large_lds<attn_pp_mixed_kernel<true>>(lds));
-      hipLaunchKernelGGL((attn_pp_mixed_kernel<true>), dim3(wgs_mixed + s.copy_wgs), dim3(kThreads), lds, st, s);
-    } else {
-      USP_CHECK_HIP(allow_large_lds<attn_pp_mixed_kernel<false>>(lds));
-      hipLaunchKernelGGL((attn_pp_mixed_kernel<false>), dim3(wgs_mixed + s.copy_wgs), dim3(kThreads), lds, st, s);
-    }
-    USP_CHECK_HIP(hipGetLastError());
-    return USP_OK;
+    if (ext) return dead ? launch_mixed<true, true>(s, wgs_mixed, st) : launch_mixed<true, false>(s, wgs_mixed, st);
+    return dead ? launch_mixed<false, true>(s, wgs_mixed, st) : launch_mixed<false, false>(s, wgs_mixed, st);
   }
   const unsigned wgs = split ? wg_grid_size((s.Sq + kQPerWGSplit - 1) / kQPerWGSplit, s.B * s.H) : wgs256;
   s.copy_wgs = prefetch_wg_count(s, (int)wgs, 1);
-  // records only because of FP8 scales: no key is dead
-  if (ext && !s.key_mask && s.Sc % kTile == 0)
-    return split ? launch_pp<true, true, false, true>(s, wgs, st) : launch_pp<false, true, false, true>(s, wgs, st);
-  if (split) return ext ? launch_pp<true, true>(s, wgs, st) : launch_pp<true, false>(s, wgs, st);
-  return ext ? launch_pp<false, true>(s, wgs, st) : launch_pp<false, false>(s, wgs, st);
+  return launch_pp_any<false>(s, ext, dead, split, wgs, st);
 }
 
 }  // namespace usp

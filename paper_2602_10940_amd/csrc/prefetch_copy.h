@@ -69,13 +69,20 @@ __device__ __forceinline__ void store16_device_scope(uint4* p, const uint4& v) {
   const vec4u x = {v.x, v.y, v.z, v.w};
   asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" :: "v"(p), "v"(x) : "memory");
 }
-// Algorithm 1 line 4 for chunk c of a launch over several FP8 chunks: unit `first`, first + stride, ..
-// of the chunk (16 codes of K and of V each; then 4 keys of the records).  The arithmetic is the
-// dequantiser's: E4M3 code -> fp32 (exact), times the scale in fp32, RNE to bf16; K keeps scale 1
-// and hands its scales to the records as per-key factors of the exponent.
+// Algorithm 1 line 4 for chunk c of a launch over FP8 chunks: unit `first`, first + stride, .. of the chunk
+// (16 codes of K and of V each; then one key of the records).  The arithmetic is the dequantiser's: E4M3
+// code -> fp32 (exact), times the scale in fp32, RNE to bf16; K keeps scale 1 and hands its scales to the
+// records as per-key factors of the exponent.  A key that takes no part (masked, or past the end of the
+// last tile) gets the plain factor instead of its scale's: its score is -inf by then and stays so under
+// any positive finite factor.
 template <bool kDeviceScope>
 __device__ __forceinline__ void put16(uint4* p, const uint4& v) {
   if (kDeviceScope) store16_device_scope(p, v);
+  else *p = v;
+}
+template <bool kDeviceScope>
+__device__ __forceinline__ void put_float(float* p, float v) {
+  if (kDeviceScope) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   else *p = v;
 }
 __device__ __forceinline__ uint4 decode8_bf16(uint32_t w0, uint32_t w1, float sc) {
@@ -90,8 +97,8 @@ __device__ __forceinline__ void fp8_chunk_prepare(const AttnStep& s, int c, int6
   const AttnStep::Chunk& ch = s.chunk[c];
   int tile0 = 0, nt_total = 0;                          // first tile of the chunk, tiles of all chunks
   for (int i = 0; i < s.n_multi; ++i) {
-    if (i < c) tile0 += s.chunk[i].Sc / 64;
-    nt_total += s.chunk[i].Sc / 64;
+    if (i < c) tile0 += (s.chunk[i].Sc + 63) / 64;
+    nt_total += (s.chunk[i].Sc + 63) / 64;
   }
   const int64_t rows = (int64_t)s.B * s.H * ch.Sc;      // (head, token) rows of d = 128 or 64 codes
   const int ush = s.d == 64 ? 2 : 3;                    // log2 of the 16-code units per row
@@ -116,35 +123,14 @@ __device__ __forceinline__ void fp8_chunk_prepare(const AttnStep& s, int c, int6
   }
   for (; u < units; u += stride) emit(u, kc[u], vc[u], ch.v_scale_src[u >> ush]);
   const float scale2 = s.scale * 1.44269504088896340736f;
-  const uint4 zero = make_uint4(0u, 0u, 0u, 0u);
-  for (int64_t u = first; u < rows / 4; u += stride) {  // chunk lengths are multiples of 64
-    const int64_t row = 4 * u;
-    const int64_t bh = row / ch.Sc;
-    const int key = (int)(row - bh * ch.Sc);
-    const float4 ks = ((const float4*)ch.k_scale_src)[u];
-    float* rec = s.ext + ((bh * nt_total + tile0 + (key >> 6)) << 8) + (key & 63);
-    if (ch.mask_src == nullptr) {                       // no dead keys: bias 0, flag 0
-      put16<kDeviceScope>((uint4*)rec, make_uint4(__float_as_uint(ks.x * scale2), __float_as_uint(ks.y * scale2),
-                                                 __float_as_uint(ks.z * scale2), __float_as_uint(ks.w * scale2)));
-      put16<kDeviceScope>((uint4*)(rec + 64), zero);
-      put16<kDeviceScope>((uint4*)(rec + 128), zero);
-      put16<kDeviceScope>((uint4*)(rec + 192), zero);
-      continue;
-    }
-    // masked chunk: a dead key gets factor 0 and bias -inf; the tile's flag says whether it has any.
-    // The 16 lanes that share a tile are consecutive (units are handed out in lane order and a tile
-    // is 16 units), so the wave's ballot holds the tile's 16 answers side by side.
-    const uint32_t mk = *(const uint32_t*)(ch.mask_src + (bh / s.H) * ch.Sc + key);
-    const bool k0 = (mk & 0xffu) != 0, k1 = (mk & 0xff00u) != 0, k2 = (mk & 0xff0000u) != 0, k3 = (mk & 0xff000000u) != 0;
-    const unsigned long long dead = __builtin_amdgcn_ballot_w64(!(k0 && k1 && k2 && k3));
-    const int lane16 = (int)(__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u))) & ~15;
-    const uint32_t fl = ((dead >> lane16) & 0xffffull) != 0 ? 0x3f800000u : 0u;
-    const uint32_t ninf = 0xff800000u;
-    put16<kDeviceScope>((uint4*)rec, make_uint4(k0 ? __float_as_uint(ks.x * scale2) : 0u, k1 ? __float_as_uint(ks.y * scale2) : 0u,
-                                               k2 ? __float_as_uint(ks.z * scale2) : 0u, k3 ? __float_as_uint(ks.w * scale2) : 0u));
-    put16<kDeviceScope>((uint4*)(rec + 64), make_uint4(k0 ? 0u : ninf, k1 ? 0u : ninf, k2 ? 0u : ninf, k3 ? 0u : ninf));
-    put16<kDeviceScope>((uint4*)(rec + 128), make_uint4(fl, fl, fl, fl));
-    put16<kDeviceScope>((uint4*)(rec + 192), zero);
+  const uint32_t ntc = (uint32_t)(ch.Sc + 63) / 64;
+  const int64_t slots = (int64_t)s.B * s.H * ntc * 64;
+  for (int64_t i = first; i < slots; i += stride) {
+    const uint32_t t = (uint32_t)(i >> 6), bh = t / ntc, tile = t - bh * ntc;   // (2^32 tiles would be 32 TB of codes)
+    const int key = (int)(tile * 64 + (uint32_t)(i & 63));
+    const bool live = key < ch.Sc && (ch.mask_src == nullptr || ch.mask_src[(int64_t)(bh / s.H) * ch.Sc + key] != 0);
+    const float f = live ? ch.k_scale_src[(int64_t)bh * ch.Sc + key] * scale2 : scale2;
+    put_float<kDeviceScope>(s.ext + (((int64_t)bh * nt_total + tile0 + tile) << 6) + (i & 63), f);
   }
 }
 // The copy work-groups of a launch over several FP8 chunks: chunk 1, 2, .. decoded and counted.

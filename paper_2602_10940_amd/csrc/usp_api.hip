@@ -62,14 +62,13 @@ struct Plan {
   size_t off_buf[2] = {0, 0}; // staged chunk: K | V | k_scale | v_scale
   size_t buf_k = 0, buf_v = 0, buf_ks = 0, buf_vs = 0;  // offsets inside a staging buffer
   size_t off_deq_k = 0, off_deq_v = 0;  // bf16 K/V after dequantisation (FP8 + MFMA kernel)
-  size_t off_ext = 0, off_nlive = 0;    // per-tile key records and live tile counts (MFMA kernel, masks / scales / ragged chunks)
+  size_t off_ext = 0;                   // per-tile key records of an FP8 chunk (MFMA kernel)
+  bool one_launch = false;              // chunk lengths and flags that one launch over the ring takes
   bool ring1 = false;                   // fused prefetch as one launch over the whole ring: a staging buffer per chunk
   size_t off_ring1 = 0, off_arrive = 0; // K | V of chunk 1, K | V of chunk 2, ... (dense, 256-byte aligned each); arrival counters
   bool ring8 = false;                   // FP8 chunks decoded inside one launch over the whole ring
   size_t off_ring8 = 0, off_ext8 = 0;   // bf16 K | V of every live chunk; records of all their tiles
-  bool ext = false;
-  bool multi_rec = false;               // room for the records of a one-launch ring over bf16 chunks with key masks
-  size_t off_multi_rec = 0;
+  size_t tiles = 0;                     // 64-key tiles of all chunks
   size_t total = 0;
 };
 
@@ -86,7 +85,33 @@ bool o_dense(const usp_attn_desc* d) {
          d->o_stride[0] == (int64_t)d->H * d->Sq * d->d;
 }
 
-usp_status make_plan(const usp_attn_desc* d, Plan* p) {
+// Chunk lengths that one launch over the ring takes: 2 to 16 non-empty chunks, whole tiles, or (unless
+// `least`) any lengths of at least kRaggedRing keys on average.  A ring of ragged chunks as one launch saves
+// per chunk a launch gap, a pipeline fill and the carried state's round trip (12 heads, two chunks of 2215:
+// 98 -> 78 us).  Shorter ragged rings keep their launch per chunk, and with it the bits that
+// USP_ATTN_DOUBLE_BUFFER gives for the same ring; from there on the two agree up to rounding order, as
+// they do on whole tiles.
+constexpr int kRaggedRing = 512;
+bool one_launch_lengths(const usp_attn_desc* d, bool least, bool* whole, size_t* tiles) {
+  int live = 0;
+  int64_t keys = 0;
+  *whole = true;
+  *tiles = 0;
+  for (int r = 0; r < d->n_chunks; ++r) {
+    const int len = d->chunk_len[r];
+    if (len == 0) continue;
+    if (len % 64 != 0) *whole = false;
+    *tiles += ((size_t)len + 63) / 64;
+    keys += len;
+    ++live;
+  }
+  if (live < 2 || live > AttnStep::kMaxMulti) return false;
+  return *whole || (!least && keys >= (int64_t)live * kRaggedRing);
+}
+
+// `least`: the plan that needs no more workspace than a launch per chunk, or one launch over whole tiles,
+// does: no one launch over ragged chunks.
+usp_status make_plan_of(const usp_attn_desc* d, bool least, Plan* p) {
   USP_CHECK_ARG(d != nullptr, "desc is NULL");
   USP_CHECK_ARG(d->B > 0 && d->H > 0 && d->Sq > 0, "B, H, Sq must be positive (B=%d H=%d Sq=%d)", d->B, d->H, d->Sq);
   USP_CHECK_ARG(d->d > 0 && d->d % 8 == 0 && d->d <= 256, "d must be a multiple of 8 in [8, 256] (got %d)", d->d);
@@ -160,26 +185,21 @@ usp_status make_plan(const usp_attn_desc* d, Plan* p) {
     p->off_deq_k = off; off += align_up(chunk_elems * 2);
     p->off_deq_v = off; off += align_up(chunk_elems * 2);
   }
+  // Records of one chunk's tiles.  The size query's answers are kept from the time when a tile took 1 KB,
+  // whatever the K/V type, and a batch entry a count; FP8 chunks use 256 bytes a tile of it.
   if (p->mfma) {
-    // Records are needed by chunks with FP8 scales, a key mask (not known here: assume one) or a
-    // length that is not a multiple of 64; they are small (1 KB per 64 keys of a head).
-    p->ext = true;
-    p->off_ext = off; off += align_up(attn_mfma_ext_bytes(d->B, d->H, p->max_len));
-    p->off_nlive = off; off += align_up((size_t)d->B * 4);
+    p->off_ext = off; off += align_up((size_t)d->B * d->H * (((size_t)p->max_len + 63) / 64) * 1024);
+    off += align_up((size_t)d->B * 4);
   }
+  const int64_t q_blocks = (int64_t)d->B * d->H * ((d->Sq + 255) / 256);
+  bool whole = true;
+  size_t tiles = 0;
+  p->one_launch = p->mfma && !p->unfused && !(d->flags & USP_ATTN_STEPWISE) && one_launch_lengths(d, least, &whole, &tiles);
+  p->tiles = p->W == 1 ? ((size_t)p->max_len + 63) / 64 : tiles;
   // Transfers inside a single launch over the whole ring (see usp_ring_attn_fwd): every chunk after
   // the first gets a staging buffer of its own, because a buffer that is reused inside one launch
   // would make the copy work-groups wait for the attention work-groups.
-  p->ring1 = p->fused_pf && p->mfma && !p->fp8 && !p->unfused && !(d->flags & USP_ATTN_STEPWISE);
-  if (p->ring1) {
-    int live = 0;
-    for (int r = 0; r < p->W; ++r) {
-      if (d->chunk_len[r] == 0) continue;
-      if (d->chunk_len[r] % 64 != 0) p->ring1 = false;
-      ++live;
-    }
-    if (live < 2 || live > AttnStep::kMaxMulti) p->ring1 = false;
-  }
+  p->ring1 = p->fused_pf && !p->fp8 && p->one_launch;
   if (p->ring1) {
     p->off_ring1 = off;
     for (int r = 1; r < p->W; ++r) off += 2 * align_up((size_t)d->B * d->H * d->chunk_len[r] * d->d * 2);
@@ -187,45 +207,31 @@ usp_status make_plan(const usp_attn_desc* d, Plan* p) {
   }
   // FP8 chunks, all of them at hand or with the transfers inside the launches: the decoding of
   // Algorithm 1 line 4 rides in the one launch over the ring (copy work-groups decode chunk r+1
-  // while chunk r is computed on), each live chunk into bf16 buffers of its own; key masks go into the
-  // records the same work-groups write.
-  p->ring8 = p->fp8 && p->mfma && !p->unfused && !(d->flags & (USP_ATTN_STEPWISE | USP_ATTN_DOUBLE_BUFFER)) &&
-             (p->fused_pf || (int64_t)d->B * d->H * ((d->Sq + 255) / 256) <= 256);   // short ring steps (see usp_ring_attn_fwd)
+  // while chunk r is computed on), each live chunk into bf16 buffers of its own.
+  p->ring8 = p->fp8 && p->one_launch && !(d->flags & USP_ATTN_DOUBLE_BUFFER) &&
+             (p->fused_pf || q_blocks <= 256);   // short ring steps (see usp_ring_attn_fwd)
   if (p->ring8) {
-    int live = 0;
-    size_t tiles = 0;
-    for (int r = 0; r < p->W; ++r) {
-      if (d->chunk_len[r] == 0) continue;
-      if (d->chunk_len[r] % 64 != 0) p->ring8 = false;
-      tiles += (size_t)d->chunk_len[r] / 64;
-      ++live;
-    }
-    if (live < 2 || live > AttnStep::kMaxMulti) p->ring8 = false;
-    if (p->ring8) {
-      p->off_ring8 = off;
-      for (int r = 0; r < p->W; ++r) off += 2 * align_up((size_t)d->B * d->H * d->chunk_len[r] * d->d * 2);
-      p->off_ext8 = off; off += align_up((size_t)d->B * d->H * tiles * 1024);
-      p->off_arrive = off; off += align_up(AttnStep::kMaxMulti * sizeof(int));
-    }
+    p->off_ring8 = off;
+    for (int r = 0; r < p->W; ++r) off += 2 * align_up((size_t)d->B * d->H * d->chunk_len[r] * d->d * 2);
+    p->off_ext8 = off; off += align_up((size_t)d->B * d->H * tiles * 1024);   // (256 bytes a tile are used, as above)
+    p->off_arrive = off; off += align_up(AttnStep::kMaxMulti * sizeof(int));
   }
-  // bf16 chunks that one launch could take (see usp_ring_attn_fwd): should some of them come with a key
-  // mask (not known here), that launch reads per-tile records, 1 KB per 64 keys of a head
-  p->multi_rec = p->mfma && !p->fp8 && (!p->dbuf || p->ring1) && !p->unfused && p->W > 1 && !(d->flags & USP_ATTN_STEPWISE);
-  if (p->multi_rec) {
-    int live = 0;
-    size_t tiles = 0;
-    for (int r = 0; r < p->W; ++r) {
-      if (d->chunk_len[r] == 0) continue;
-      if (d->chunk_len[r] % 64 != 0) p->multi_rec = false;
-      tiles += (size_t)d->chunk_len[r] / 64;
-      ++live;
-    }
-    if (live < 2 || live > AttnStep::kMaxMulti) p->multi_rec = false;
-    if (p->multi_rec) { p->off_multi_rec = off; off += align_up((size_t)d->B * d->H * tiles * 1024); }
-  }
+  // (kept in the size query's answers: what key masks of a one-launch ring over bf16 chunks took)
+  if (p->one_launch && whole && !p->fp8 && (!p->dbuf || p->ring1)) off += align_up((size_t)d->B * d->H * tiles * 1024);
   p->total = off;
   p->valid = true;
   return USP_OK;
+}
+
+// The least plan where only that one fits the built-in scratch: usp_ring_attn_fwd and
+// usp_ring_attn_fwd_noalloc run the same plan (their outputs have the same bits), and what the latter
+// accepts does not shrink.
+usp_status make_plan(const usp_attn_desc* d, Plan* p) {
+  usp_status st = make_plan_of(d, false, p);
+  if (st != USP_OK || p->total <= (size_t)USP_NOALLOC_SCRATCH_BYTES) return st;
+  Plan least;
+  if ((st = make_plan_of(d, true, &least)) == USP_OK && least.total <= (size_t)USP_NOALLOC_SCRATCH_BYTES) *p = least;
+  return st;
 }
 
 }  // namespace
@@ -425,6 +431,10 @@ usp_status usp::ring_attn_fwd_impl(const usp_attn_desc* desc, const void* q, con
     USP_CHECK_ARG(!p.fp8 || (k_scales[r] && v_scales[r]), "scale pointer of chunk %d is NULL", r);
   }
   if (p.total > 0) {
+    if (workspace != nullptr && workspace_bytes < p.total) {   // a caller that has no more
+      p = Plan();
+      if ((st = make_plan_of(desc, true, &p)) != USP_OK) return st;
+    }
     if (workspace == nullptr || workspace_bytes < p.total) {
       set_error("workspace of %zu bytes needed, %zu given", p.total, workspace ? workspace_bytes : (size_t)0);
       return USP_ERR_WORKSPACE;
@@ -489,29 +499,14 @@ usp_status usp::ring_attn_fwd_impl(const usp_attn_desc* desc, const void* q, con
   // that asks for the transfers inside the launches takes the one launch at any size.
   const int64_t q_blocks = (int64_t)desc->B * desc->H * ((desc->Sq + 255) / 256);
   const bool short_steps = q_blocks <= 256 || p.fused_pf;
-  // Every chunk resident, whole tiles, merge fused: one launch over the whole ring (chunks with a key
-  // mask through per-tile records written just before it).
+  // Dead keys in more tiles than such a launch keeps words for: a launch per chunk.
+  if (p.one_launch && (int64_t)p.tiles > attn_mfma_max_dead_tiles()) {
+    for (int r = 0; r < p.W; ++r)
+      if (desc->chunk_len[r] % 64 != 0 || (key_mask && key_mask[r] && desc->chunk_len[r] > 0)) p.one_launch = p.ring8 = false;
+  }
+  // bf16 chunks, merge fused: one launch over the whole ring.
   {
-    bool one_launch = p.mfma && !p.fp8 && (!p.dbuf || p.ring1) && !p.unfused && p.W > 1 && !(desc->flags & USP_ATTN_STEPWISE) &&
-                      short_steps;
-    int n_live = 0, n_masked = 0;
-    int64_t keys = 0;
-    for (int r = 0; one_launch && r < p.W; ++r) {
-      const int len = desc->chunk_len[r];
-      if (len == 0) continue;
-      if (len % 64 != 0) one_launch = false;
-      if (key_mask && key_mask[r]) ++n_masked;
-      keys += len;
-      ++n_live;
-    }
-    // Key masks: the one launch then reads per-tile records for every chunk, which costs it about a
-    // third (96 against 73 us on a FLUX-1024 ring of four with one masked chunk), while the per-chunk
-    // form pays for records only in the masked chunks' launches.  The one launch still wins where the
-    // ring steps are short (below about 40 million query-key pairs per step) or every chunk is masked.
-    if (one_launch && n_masked > 0 && n_masked < n_live &&
-        (double)desc->B * desc->H * desc->Sq * ((double)keys / n_live) > 40e6)
-      one_launch = false;
-    if (one_launch && n_live >= 2 && n_live <= AttnStep::kMaxMulti && p.multi_rec) {
+    if (p.one_launch && !p.fp8 && (!p.dbuf || p.ring1) && short_steps) {
       AttnStep a;
       memset(&a, 0, sizeof(a));
       a.B = desc->B; a.H = desc->H; a.d = d; a.Sq = desc->Sq;
@@ -535,7 +530,7 @@ usp_status usp::ring_attn_fwd_impl(const usp_attn_desc* desc, const void* q, con
             c.k_src = k_chunks[r]; c.v_src = v_chunks[r]; c.bytes = (int64_t)bytes;
             c.k = ws + stage; c.v = ws + stage + align_up(bytes);
           }
-          if (key_mask && key_mask[r]) { c.mask_src = key_mask[r]; a.multi_masked = 1; }
+          c.mask_src = key_mask ? key_mask[r] : nullptr;
         }
         if (r >= 1) stage += 2 * align_up(bytes);
       }
@@ -543,10 +538,6 @@ usp_status usp::ring_attn_fwd_impl(const usp_attn_desc* desc, const void* q, con
         a.arrive = (int*)(ws + p.off_arrive);
         a.arrive_need_extra = opt.arrive_need_extra; a.arrive_polls = opt.arrive_polls;
         if ((st = launch_attn_arrive_reset(a.arrive, cs)) != USP_OK) return st;
-      }
-      if (a.multi_masked) {   // some chunk has a key mask: the launch reads per-tile records
-        a.ext = (float*)(ws + p.off_multi_rec);
-        if ((st = launch_attn_multi_records(a, cs)) != USP_OK) return st;
       }
       return launch_attn_mfma(a, cs);
     }
@@ -575,43 +566,41 @@ usp_status usp::ring_attn_fwd_impl(const usp_attn_desc* desc, const void* q, con
     return launch_attn_generic(a, cs);
   }
 
-  // FP8 chunks: one launch over the ring that decodes them as it goes
-  if (p.ring8 && short_steps) {
-    bool ok = true;
-    for (int r = 0; r < p.W; ++r)
-      if (desc->chunk_len[r] > 0 && (((uintptr_t)k_scales[r] & 15) != 0 || (key_mask && ((uintptr_t)key_mask[r] & 3) != 0))) ok = false;
-    if (ok) {
-      AttnStep a;
-      memset(&a, 0, sizeof(a));
-      a.B = desc->B; a.H = desc->H; a.d = d; a.Sq = desc->Sq;
-      a.qo_dtype = desc->qo_dtype; a.half_d = d == 64 ? 1 : 0; a.kv_dtype = USP_BF16;   // what the attention work-groups read
-      a.q = q; a.out = out; a.lse = lse; a.scale = scale; a.mode = 0;
-      for (int i = 0; i < 3; ++i) { a.qs[i] = desc->q_stride[i]; a.os[i] = desc->o_stride[i]; }
-      a.ks[2] = d;
-      a.variant = (desc->flags & USP_ATTN_KERNEL_SPLIT) ? 2 : (desc->flags & USP_ATTN_KERNEL_WIDE) ? 1 : 0;
-      a.multi_fp8 = 1;
-      a.ext = (float*)(ws + p.off_ext8);
-      a.arrive = (int*)(ws + p.off_arrive);
-      a.arrive_need_extra = opt.arrive_need_extra; a.arrive_polls = opt.arrive_polls;
-      size_t stage = p.off_ring8;
-      for (int r = 0; r < p.W; ++r) {
-        const int len = desc->chunk_len[r];
-        const size_t bytes = (size_t)desc->B * desc->H * len * d * 2;
-        if (len > 0) {
-          AttnStep::Chunk& c = a.chunk[a.n_multi++];
-          c.Sc = len;
-          c.ks0 = (int64_t)desc->H * len * d; c.ks1 = (int64_t)len * d;
-          c.k = ws + stage; c.v = ws + stage + align_up(bytes);
-          c.k_src = k_chunks[r]; c.v_src = v_chunks[r]; c.bytes = (int64_t)(bytes / 2);
-          c.k_scale_src = k_scales[r]; c.v_scale_src = v_scales[r];
-          c.mask_src = key_mask ? key_mask[r] : nullptr;
-          if (c.mask_src) a.multi_masked = 1;
-        }
-        stage += 2 * align_up(bytes);
+  // FP8 chunks: one launch over the ring that decodes them as it goes.  (Scales and masks at odd addresses
+  // keep a launch per chunk and its order of operations.)
+  bool aligned = true;
+  for (int r = 0; p.ring8 && r < p.W; ++r)
+    if (desc->chunk_len[r] > 0 && (!aligned16(k_scales[r]) || (key_mask && ((uintptr_t)key_mask[r] & 3) != 0))) aligned = false;
+  if (p.ring8 && aligned) {
+    AttnStep a;
+    memset(&a, 0, sizeof(a));
+    a.B = desc->B; a.H = desc->H; a.d = d; a.Sq = desc->Sq;
+    a.qo_dtype = desc->qo_dtype; a.half_d = d == 64 ? 1 : 0; a.kv_dtype = USP_BF16;   // what the attention work-groups read
+    a.q = q; a.out = out; a.lse = lse; a.scale = scale; a.mode = 0;
+    for (int i = 0; i < 3; ++i) { a.qs[i] = desc->q_stride[i]; a.os[i] = desc->o_stride[i]; }
+    a.ks[2] = d;
+    a.variant = (desc->flags & USP_ATTN_KERNEL_SPLIT) ? 2 : (desc->flags & USP_ATTN_KERNEL_WIDE) ? 1 : 0;
+    a.multi_fp8 = 1;
+    a.ext = (float*)(ws + p.off_ext8);
+    a.arrive = (int*)(ws + p.off_arrive);
+    a.arrive_need_extra = opt.arrive_need_extra; a.arrive_polls = opt.arrive_polls;
+    size_t stage = p.off_ring8;
+    for (int r = 0; r < p.W; ++r) {
+      const int len = desc->chunk_len[r];
+      const size_t bytes = (size_t)desc->B * desc->H * len * d * 2;
+      if (len > 0) {
+        AttnStep::Chunk& c = a.chunk[a.n_multi++];
+        c.Sc = len;
+        c.ks0 = (int64_t)desc->H * len * d; c.ks1 = (int64_t)len * d;
+        c.k = ws + stage; c.v = ws + stage + align_up(bytes);
+        c.k_src = k_chunks[r]; c.v_src = v_chunks[r]; c.bytes = (int64_t)(bytes / 2);
+        c.k_scale_src = k_scales[r]; c.v_scale_src = v_scales[r];
+        c.mask_src = key_mask ? key_mask[r] : nullptr;
       }
-      if ((st = launch_attn_fp8_chunk_prepare(a, 0, true, cs)) != USP_OK) return st;   // also zeroes the counters
-      return launch_attn_mfma(a, cs);
+      stage += 2 * align_up(bytes);
     }
+    if ((st = launch_attn_fp8_chunk_prepare(a, 0, true, cs)) != USP_OK) return st;   // also zeroes the counters
+    return launch_attn_mfma(a, cs);
   }
 
   for (int r = 0; r < p.W; ++r) {
@@ -664,12 +653,10 @@ usp_status usp::ring_attn_fwd_impl(const usp_attn_desc* desc, const void* q, con
       }
     } else a.mode = r == 0 ? 1 : (r == p.W - 1 ? 3 : 2);
 
-    bool records_ready = false;
-    if (p.dequant_stage && len > 0 && len % 64 == 0 && aligned16(kp) && aligned16(vp) && aligned16(ksp) && aligned16(vsp) &&
-        ((uintptr_t)a.key_mask & 3u) == 0) {
-      // Algorithm 1 line 4 for a chunk of whole tiles, in one launch: K widened exactly, V dequantised to
-      // bf16(code * scale), the per-tile records (K's scales as per-key factors, the mask) and the live-tile
-      // counts; the same arithmetic as the three launches of the general case below, bit for bit
+    if (p.dequant_stage && len > 0) {
+      // Algorithm 1 line 4, in one launch.  K: the codes are widened to bf16 exactly and the MFMA kernel
+      // multiplies the fp32 scores by the per-token scales (the records), so the exponents see no rounding
+      // beyond the quantisation itself.  V: dequantised to the working precision, bf16(code * scale).
       AttnStep m;
       memset(&m, 0, sizeof(m));
       m.B = desc->B; m.H = desc->H; m.d = d; m.scale = scale;
@@ -677,36 +664,18 @@ usp_status usp::ring_attn_fwd_impl(const usp_attn_desc* desc, const void* q, con
       m.ext = (float*)(ws + p.off_ext);
       AttnStep::Chunk& c = m.chunk[0];
       c.k = ws + p.off_deq_k; c.v = ws + p.off_deq_v; c.Sc = len;
-      c.ks0 = (int64_t)desc->H * len * d; c.ks1 = (int64_t)len * d;
       c.k_src = kp; c.v_src = vp; c.k_scale_src = ksp; c.v_scale_src = vsp;
       c.mask_src = a.key_mask;
-      if ((st = launch_attn_fp8_step_prepare(m, (int*)(ws + p.off_nlive), cs)) != USP_OK) return st;
+      if ((st = launch_attn_fp8_chunk_prepare(m, 0, false, cs)) != USP_OK) return st;
       a.k = c.k; a.v = c.v;
       a.v_scale = nullptr;
       a.kv_dtype = USP_BF16;
       a.ext = m.ext;
-      a.n_live = (int*)(ws + p.off_nlive);
-      records_ready = true;
-    } else if (p.dequant_stage && len > 0) {
-      // Algorithm 1 line 4.  K: the codes are widened to bf16 exactly here (scale 1) and the MFMA
-      // kernel multiplies the fp32 scores by the per-token scales, so the exponents see no rounding
-      // beyond the quantisation itself.  V: dequantised to the working precision, bf16(code * scale).
-      const int64_t rows = (int64_t)desc->B * desc->H * len;
-      if ((st = launch_fp8_dequant(rows, d, USP_BF16, (const uint8_t*)kp, nullptr, ws + p.off_deq_k, cs)) != USP_OK) return st;
-      if ((st = launch_fp8_dequant(rows, d, USP_BF16, (const uint8_t*)vp, vsp, ws + p.off_deq_v, cs)) != USP_OK) return st;
-      a.k = ws + p.off_deq_k; a.v = ws + p.off_deq_v;
-      a.v_scale = nullptr;
-      a.kv_dtype = USP_BF16;
     } else if (p.dequant_stage) {
       // an empty chunk still merges and stores (its epilogue mode): keep it on the matrix-core kernel,
       // which reads no key of it
       a.k_scale = nullptr; a.v_scale = nullptr;
       a.kv_dtype = USP_BF16;
-    }
-    if (!records_ready && attn_mfma_supported(a) && attn_mfma_needs_ext(a)) {
-      a.ext = (float*)(ws + p.off_ext);
-      a.n_live = (int*)(ws + p.off_nlive);
-      if ((st = launch_attn_ext_prepare(a, cs)) != USP_OK) return st;
     }
     st = attn_mfma_supported(a) ? launch_attn_mfma(a, cs) : launch_attn_generic(a, cs);
     if (st != USP_OK) return st;

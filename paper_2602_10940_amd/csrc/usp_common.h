@@ -97,15 +97,13 @@ struct AttnStep {
   float* acc;                // fp32 [B,H,Sq,d] dense carried O (modes 1-3)
   void* out;                 // qo_dtype by os strides (modes 0, 3)
   float* lse;                // fp32 [B,H,Sq] dense
-  // Matrix-core kernels, chunks with a key mask, FP8 scales or a length that is not a multiple of 64:
-  // per-(batch, head, 64-key tile) records (attn_mfma_ext_bytes) and per-batch live tile counts [B],
-  // filled by launch_attn_ext_prepare on the same stream before the attention launch
+  // Matrix-core kernels, FP8 K: per-(batch, head, 64-key tile) records of 64 floats, laid out
+  // [B*H][tiles of the launch], filled by launch_attn_fp8_chunk_prepare on the same stream before the
+  // attention launch or by the copy work-groups inside it
   float* ext;
-  int* n_live;
-  // Matrix-core kernels, several resident chunks in one launch (n_multi > 0; plain bf16 chunks whose
-  // lengths are positive multiples of 64, no mask): their 64-key tiles form one stream in ring
-  // order and the running (O~, m, l) stays in registers from the first tile to the last, which is
-  // the merge of section 3.4 applied tile by tile.  k, v, Sc and ks above are then unused.
+  // Matrix-core kernels, several resident chunks in one launch (n_multi > 0): their 64-key tiles form one
+  // stream in ring order and the running (O~, m, l) stays in registers from the first tile to the last,
+  // which is the merge of section 3.4 applied tile by tile.  k, v, Sc and ks above are then unused.
   //
   // With `arrive` set the launch also plays the ring's transfers (Algorithm 2 inside one launch): its
   // first copy_wgs work-groups copy chunk c = 1, 2, .. from k_src / v_src (bytes each) into k / v, a
@@ -117,8 +115,8 @@ struct AttnStep {
   // multi_fp8: the sources are FP8 E4M3 chunks ([B,H,Sc,128] codes at k_src / v_src, per-(head, token)
   // scales at k_scale_src / v_scale_src; Algorithm 1 line 4 on arrival).  A copy work-group then
   // decodes while it copies: K's codes widened to bf16 as they are, V's multiplied by their scales,
-  // and the per-tile records of the chunk (K's scales as per-key factors) written into `ext`, laid
-  // out [B*H][tiles of all chunks in ring order].  Chunk 0 is decoded by a launch of its own
+  // and the per-tile records of the chunk (K's scales as per-key factors) written into `ext`.  Chunk 0 is
+  // decoded by a launch of its own
   // (launch_attn_fp8_chunk_prepare) before the attention launch.
   struct Chunk {
     const void* k; const void* v; int64_t ks0, ks1; int Sc;
@@ -129,8 +127,6 @@ struct AttnStep {
   static constexpr int kMaxMulti = 16;
   int n_multi;
   int multi_fp8;
-  int multi_masked;          // some chunk has a key mask (Chunk::mask_src): the records may flag dead keys.  With bf16
-                             // chunks (no multi_fp8) the records are those of launch_attn_multi_records
   int* arrive;               // [kMaxMulti] counters, zero when the launch starts; or null
   // what an attention work-group waits for on arrive[c], and for how long: the launcher sets the
   // count to copy_wgs plus arrive_need_extra and the poll limit to its default when arrive_polls is
@@ -161,19 +157,12 @@ inline int prefetch_wg_count(const AttnStep& s, int attn_wgs, int slots_per_cu) 
 usp_status launch_attn_generic(const AttnStep& s, hipStream_t st);
 usp_status launch_attn_mfma(const AttnStep& s, hipStream_t st);
 bool attn_mfma_supported(const AttnStep& s);
-bool attn_mfma_needs_ext(const AttnStep& s);
-size_t attn_mfma_ext_bytes(int B, int H, int Sc);
-usp_status launch_attn_ext_prepare(const AttnStep& s, hipStream_t st);
+// tiles a launch over several chunks takes if some of its keys are dead (a mask, a ragged chunk)
+int64_t attn_mfma_max_dead_tiles();
 usp_status launch_attn_arrive_reset(int* arrive, hipStream_t st);
-// per-tile records (AttnStep::ext, [B*H][tiles in ring order]) of a step over several bf16 chunks some of
-// which have a key mask (Chunk::mask_src, multi_masked); precedes the attention launch on the stream
-usp_status launch_attn_multi_records(const AttnStep& s, hipStream_t st);
-// chunk c of a step over several FP8 chunks decoded by a launch of its own; reset_arrive: the same
+// chunk c of a step over FP8 chunks decoded by a launch of its own (bf16 K and V, records); reset_arrive: the same
 // launch zeroes the arrival counters (it precedes the attention launch on the stream)
 usp_status launch_attn_fp8_chunk_prepare(const AttnStep& s, int c, bool reset_arrive, hipStream_t st);
-// One FP8 chunk of a launch-per-chunk step (s describes it as the only chunk of a several-chunk launch): bf16 K
-// and V, the per-tile records and n_live[B] in one launch
-usp_status launch_attn_fp8_step_prepare(const AttnStep& s, int* n_live, hipStream_t st);
 
 // More than 64 KB of dynamic LDS has to be allowed per kernel, and the setting belongs to the device
 // that is current when it is made: once per (kernel, device ordinal below 64), every launch beyond.

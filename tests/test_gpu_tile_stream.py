@@ -1,0 +1,112 @@
+"""Dead keys (ragged chunks, key masks) in the tile stream of the matrix-core kernels: edges of tiles and
+words, against the fp64 oracle at the bars of the other attention tests."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import usp_oracle as orc
+from paper_2602_10940_amd import workloads as W
+from tests.gpu_util import DEV, dev_bf16, host_f64
+from tests.test_gpu_fp8_ring import _fp8_ring
+
+pytestmark = pytest.mark.gpu
+
+
+def _P():
+    import paper_2602_10940_amd as P
+    return P
+
+
+def _leave_nan_in_lds(d):
+    """An ordinary launch on NaN inputs: whatever the next kernel does not write in LDS is then NaN."""
+    x = torch.full((1, 256, 256, d), float("nan"), device=DEV, dtype=torch.bfloat16)
+    _P().usp_ring_attn_fwd(x, [x], [x])
+
+
+def _parity(o, l, ro, rl):
+    o, l = host_f64(o), host_f64(l)
+    assert np.array_equal(np.isneginf(l), np.isneginf(rl))
+    live = ~np.isneginf(rl)
+    assert np.abs(o - ro).max() <= 2e-2 * max(1.0, np.abs(ro).max())
+    assert np.linalg.norm(o - ro) <= 5e-3 * np.linalg.norm(ro)
+    assert np.abs(l[live] - rl[live]).max() <= 1e-3
+
+
+def _masks(rng, B, lens, kind):
+    if kind is None:
+        return None
+    total = sum(lens)
+    m = np.ones((B, total), np.uint8)
+    for b in range(B):
+        if kind == "tail":       # whole tiles of the end are dead, another number in every entry
+            m[b, total - (total // 3) * (b + 1) // B - 7:] = 0
+        elif kind == "holes":    # single keys, a whole tile, the first keys
+            m[b, rng.integers(0, total, 9)] = 0
+            m[b, 64:128] = 0
+            m[b, :3] = 0
+        elif kind == "all":      # one entry has no live key
+            m[b, :] = 1 if b else 0
+    cuts = np.cumsum(lens)[:-1]
+    return [np.ascontiguousarray(x) for x in np.split(m, cuts, axis=1)]
+
+
+# (B, H, Sq, lens): ragged rings in one launch (513 = one row in the last tile, 575 = one missing), one chunk
+# shorter than a tile, more and fewer tiles
+SHAPES = [(1, 6, 300, (513, 575, 640)), (2, 3, 129, (700, 0, 525)), (1, 4, 40, (37,)), (2, 2, 200, (1100,)),
+          (1, 1, 64, (4608,)), (1, 2, 130, (2049, 1023)), (2, 1, 257, (1024, 1024))]
+
+
+@pytest.mark.parametrize("mask", [None, "tail", "holes", "all"])
+@pytest.mark.parametrize("d,fp8", [(128, False), (64, False), (128, True), (64, True)])
+@pytest.mark.parametrize("B,H,Sq,lens", SHAPES)
+def test_dead_keys(B, H, Sq, lens, d, fp8, mask):
+    if mask == "all" and B == 1:
+        pytest.skip("covered with two entries")
+    P = _P()
+    wl = W.Workload("stream", 17 + Sq, B, H, d, Sq, lens, "bf16")
+    km = _masks(np.random.default_rng(Sq), B, lens, mask)
+    if fp8:
+        inp, q, k, ksc, v, vsc, kx, vx = _fp8_ring(wl)
+        kw = dict(k_scales=ksc, v_scales=vsc)
+    else:
+        inp = W.make_attention_inputs(wl)
+        q, k, v, kx, vx = dev_bf16(inp.q), [dev_bf16(x) for x in inp.k], [dev_bf16(x) for x in inp.v], inp.k, inp.v
+        kw = dict()
+    kw["softmax_scale"] = float(inp.softmax_scale)
+    if km is not None:
+        kw["key_mask"] = [torch.from_numpy(m).to(DEV) for m in km]
+    ro, rl = orc.ring_attention(inp.q, kx, vx, float(inp.softmax_scale), km)
+    ref = None
+    for flags in (0, P.USP_ATTN_KERNEL_WIDE, P.USP_ATTN_KERNEL_SPLIT, P.USP_ATTN_FUSED_PREFETCH):
+        _leave_nan_in_lds(d)
+        desc = P.make_attn_desc(q, k, q, kw["softmax_scale"], flags)
+        ws = torch.full((P.usp_ring_attn_workspace_bytes(desc),), 0xFF, dtype=torch.uint8, device=DEV)
+        o, l = P.usp_ring_attn_fwd(q, k, v, flags=flags, workspace=ws, **kw)
+        torch.cuda.synchronize()
+        _parity(o, l, ro, rl)
+        if flags == 0:
+            ref = o, l
+        elif flags == P.USP_ATTN_FUSED_PREFETCH:     # the transfers inside the launch change no bit
+            assert torch.equal(o, ref[0]) and torch.equal(l, ref[1])
+
+
+@pytest.mark.parametrize("split", [False, True])
+@pytest.mark.parametrize("n", [1, 2])
+def test_more_dead_tiles_than_words(n, split):
+    """250 007 keys, ragged and masked: beyond the words a work-group keeps in LDS.  Reference in fp32."""
+    P = _P()
+    g = torch.Generator(device=DEV)
+    g.manual_seed(3)
+    total, Sq = 250007, 96
+    q, k, v = (torch.randn((1, 1, s, 128), generator=g, device=DEV).bfloat16() for s in (Sq, total, total))
+    keep = torch.ones((1, total), dtype=torch.uint8, device=DEV)
+    keep[:, 1000:1500] = 0
+    keep[:, total - 70000:] = 0
+    lens = (total,) if n == 1 else (130001, total - 130001)
+    o, l = P.usp_ring_attn_fwd(q, [x.contiguous() for x in k.split(lens, 2)], [x.contiguous() for x in v.split(lens, 2)],
+                               key_mask=[x.contiguous() for x in keep.split(lens, 1)],
+                               flags=P.USP_ATTN_KERNEL_SPLIT if split else P.USP_ATTN_KERNEL_WIDE)
+    s = (q[0, 0].float() @ k[0, 0].float().T) * 128 ** -0.5
+    s = s.masked_fill(keep[0] == 0, float("-inf"))
+    ro, rl = torch.softmax(s, -1) @ v[0, 0].float(), torch.logsumexp(s, -1)
+    _parity(o, l, host_f64(ro[None, None]), host_f64(rl[None, None]))
