@@ -116,7 +116,7 @@ typedef struct usp_attn_desc {
 /*
  * Bytes of device workspace usp_ring_attn_fwd needs for this descriptor
  * (0 is possible, e.g. one f32 chunk; bf16 with d = 128 or 64 always asks for a little, 1 KB per
- * 64 keys of a head).  Returns (size_t)-1 if the descriptor is invalid.
+ * 64 keys of a head, and more where few queries meet many keys).  Returns (size_t)-1 if the descriptor is invalid.
  */
 size_t usp_ring_attn_workspace_bytes(const usp_attn_desc* desc);
 

@@ -116,18 +116,21 @@ __device__ __forceinline__ RowFinish finish_row(const AttnStep& s, float m, floa
 // kHalfD: head dimension 64: only the first four 16-wide blocks exist, rows are 64 wide everywhere.
 template <bool kHalfD>
 __device__ __forceinline__ void finish_and_store_direct(const AttnStep& s, f32x4 (&oacc)[8][2], const float (&m)[2],
-                                                        const float (&lsum)[2], int b, int h, int q0, int r, int g, bool invalid) {
+                                                        const float (&lsum)[2], int b, int h, int q0, int r, int g, bool invalid,
+                                                        int part) {
   constexpr int kDB = kHalfD ? 4 : 8;
   constexpr int kAccP = kHalfD ? 64 : kD;   // floats per row of the carried O
+  const int64_t rows = (int64_t)s.B * s.H * s.Sq;
 #pragma unroll
   for (int nb = 0; nb < 2; ++nb) {
     const float l = xgroup_sum(lsum[nb]);
     const int qi = q0 + 16 * nb + r;
     const bool valid = qi < s.Sq;
     const int64_t row = ((int64_t)b * s.H + h) * s.Sq + (valid ? qi : s.Sq - 1);
-    const RowFinish f = finish_row(s, m[nb], l, row, invalid);
+    RowFinish f = finish_row(s, m[nb], l, row, invalid);
+    if (s.parts > 1 && !invalid) f.c_cur = 1.0f;   // a part's O~, m and l are kept as they are (attn_combine_kernel)
     if (!valid) continue;
-    float* accp = s.acc ? s.acc + row * kAccP : nullptr;
+    float* accp = s.parts > 1 ? s.part_o + (part * rows + row) * kAccP : s.acc ? s.acc + row * kAccP : nullptr;
     bf16_t* outp = (bf16_t*)s.out + b * s.os[0] + h * s.os[1] + (int64_t)qi * s.os[2];
 #pragma unroll
     for (int db = 0; db < kDB; ++db) {
@@ -140,12 +143,15 @@ __device__ __forceinline__ void finish_and_store_direct(const AttnStep& s, f32x4
         o[0] = fmaf(f.w_prev, p.x, o[0]); o[1] = fmaf(f.w_prev, p.y, o[1]);
         o[2] = fmaf(f.w_prev, p.z, o[2]); o[3] = fmaf(f.w_prev, p.w, o[3]);
       }
-      if (s.mode == 1 || s.mode == 2)
+      if (s.mode == 1 || s.mode == 2 || s.parts > 1)
         *reinterpret_cast<float4*>(accp + dcol) = make_float4(o[0], o[1], o[2], o[3]);
       else
         *reinterpret_cast<uint2*>(outp + dcol) = make_uint2(pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3]));
     }
-    if (g == 0) s.lse[row] = f.lse_new;
+    if (g == 0) {
+      if (s.parts > 1) *reinterpret_cast<float2*>(s.part_ml + 2 * (part * rows + row)) = make_float2(m[nb], invalid ? f.c_cur : l);
+      else s.lse[row] = f.lse_new;
+    }
   }
 }
 
@@ -341,7 +347,7 @@ __device__ __forceinline__ uint64_t live_keys(const uint8_t* mask, int Sc, int t
 // tiles have 128-byte rows with swizzles of their own), the scores contract over two 32-wide slices
 // of the head dimension and P.V produces four 16-wide blocks.
 template <bool kSplit, bool kExt, bool kMulti, bool kDead, bool kHalfD>
-__device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* smem_raw, int bh_, int q_base) {
+__device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* smem_raw, int bh_, int q_base, int part) {
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: keep it in an SGPR
@@ -439,6 +445,11 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
       nt = __builtin_amdgcn_readfirstlane(nt);
     }
   }
+  // this work-group's part of the tiles, t_beg .. nt - 1; tile indices below count from t_beg
+  const int nt_live = nt;
+  const bool parted = kSplit && s.parts > 1;
+  const int t_beg = parted ? (int)((int64_t)nt_live * part / s.parts) : 0;
+  if (parted) nt = (int)((int64_t)nt_live * (part + 1) / s.parts) - t_beg;
   if (kDead && masked && nt == 0) __syncthreads();   // no barrier of the tile loop stands between the words and the epilogue that reuses their place
 
   f32x4 oacc[8][2];   // O~^T: [16-wide head-dim block db][16-query block nb]: head dims 16*db + 4*g + i of query 16*nb + r
@@ -512,8 +523,8 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
   };
   auto issue_ext = [&](int tile_idx, int stage) {
     if ((wave & 3) != 0) return;
-    if (kMulti) await_record(tile_idx);
-    lds_dma4(extb + (int64_t)(tile_idx) * kExtTileB, lane * 4, lds_ext + stage * kExtTileB);
+    if (kMulti) await_record(t_beg + tile_idx);
+    lds_dma4(extb + (int64_t)(t_beg + tile_idx) * kExtTileB, lane * 4, lds_ext + stage * kExtTileB);
   };
   auto issue_k_tile = [&](TileRef t, int stage) {   // this wave's share
     issue_k_half(t, stage, 0, false); issue_k_half(t, stage, 1, false);
@@ -534,7 +545,8 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
     const AttnStep::Chunk& ch = s.chunk[c];
     return (const unsigned char*)((const bf16_t*)(is_v ? ch.v : ch.k) + b * ch.ks0 + h * ch.ks1);
   };
-  auto place = [&](int idx, bool is_v) -> TileCursor {   // tile idx of the stream
+  auto place = [&](int idx, bool is_v) -> TileCursor {   // idx tiles behind this work-group's first one
+    idx += t_beg;
     return TileCursor{TileRef{chunk_base(0, is_v) + idx * tileB, (kMulti ? s.chunk[0].Sc : s.Sc) - idx * kTile}, 0};
   };
   auto settle = [&](TileCursor& cur, bool is_v) {
@@ -822,7 +834,7 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
   constexpr float kRefMargin = 32.0f;
   constexpr int kMaxFirstTiles = 8;
   int max_first = 0;
-  int sm_tile = kSplit && !grpA ? 1 : 0;   // kDead: tile of this wave's next softmax phase
+  int sm_tile = t_beg + (kSplit && !grpA ? 1 : 0);   // kDead: tile of this wave's next softmax phase
   int next_dead = 0;                         // kDead: the next tile with a dead key, as far as it has been looked up
   // SM of the tile whose record sits in stage xs; loads K tile kpre_idx into stage sk (if do_k, with
   // the record of tile xpre_idx into stage xst if do_x) and V tile vpre_idx into stage sv (if do_v)
@@ -959,7 +971,7 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
   __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
   if (kDead) {
     __syncthreads();                      // (orders the words too)
-    next_dead = find_dead(0);
+    next_dead = find_dead(t_beg);
   } else {
     __builtin_amdgcn_s_barrier();
   }
@@ -1123,7 +1135,7 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
   }
 
   // every tile read of the work-group is behind a barrier here (the one after the last matrix phase)
-  if (kSplit) finish_and_store_direct<kHalfD>(s, oacc, m, lsum, b, h, q0, r, g, kMulti && late);
+  if (kSplit) finish_and_store_direct<kHalfD>(s, oacc, m, lsum, b, h, q0, r, g, kMulti && late, part);
   else finish_and_store<kHalfD>(s, oacc, m, lsum, b, h, q0, r, g, smem_raw + wave * kEpiWaveB, kMulti && late);
 }
 
@@ -1145,8 +1157,46 @@ __global__ __launch_bounds__(kThreads, 2) void attn_pp_kernel(AttnStep s) {
     }
     lead = s.copy_wgs;
   }
-  if (!wg_to_tile(s.copy_wgs, (s.Sq + kQBlock - 1) / kQBlock, s.B * s.H, bh_, qb_, lead)) return;   // whole work-group
-  attn_pp_body<kSplit, kExt, kMulti, kDead, kHalfD>(s, smem_raw, bh_, qb_ * kQBlock);
+  // (batch, head, part of the keys), each with its query blocks: whoever shares K and V follows one another
+  const int parts = kSplit ? s.parts : 1;   // (only key-split work-groups come in parts)
+  if (!wg_to_tile(s.copy_wgs, (s.Sq + kQBlock - 1) / kQBlock, s.B * s.H * parts, bh_, qb_, lead)) return;   // whole work-group
+  int part = 0;
+  if (parts > 1) {
+    part = bh_ % parts;
+    bh_ /= parts;
+  }
+  attn_pp_body<kSplit, kExt, kMulti, kDead, kHalfD>(s, smem_raw, bh_, qb_ * kQBlock, part);
+}
+
+// The parts of a launch whose work-groups shared the keys of a query block (AttnStep::parts): per query,
+// O = sum_i 2^(m_i - m) O~_i / l, l = sum_i 2^(m_i - m) l_i, m = max_i m_i, and lse = (m + log2 l) ln 2.
+// One thread per four head dims; bound by the reading of the parts, which lie in the caches.
+template <int kRowD>
+__global__ __launch_bounds__(256) void attn_combine_kernel(const float* __restrict__ part_o, const float* __restrict__ part_ml,
+                                                           bf16_t* __restrict__ out, float* __restrict__ lse, int parts,
+                                                           uint32_t rows, uint32_t Sq, uint32_t H, int64_t os0, int64_t os1, int64_t os2) {
+  constexpr uint32_t kLanes = kRowD / 4;
+  const uint32_t row = blockIdx.x * (256 / kLanes) + threadIdx.x / kLanes, c = threadIdx.x % kLanes;
+  if (row >= rows) return;
+  float m = -INFINITY;
+  for (int i = 0; i < parts; ++i) m = fmaxf(m, part_ml[2 * ((int64_t)i * rows + row)]);
+  const float ref = m == -INFINITY ? 0.0f : m;   // (no live key: every weight and every l is 0)
+  float l = 0.0f;
+  f32x4 o = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 4
+  for (int i = 0; i < parts; ++i) {
+    const float2 ml = *reinterpret_cast<const float2*>(part_ml + 2 * ((int64_t)i * rows + row));
+    const f32x4 x = *reinterpret_cast<const f32x4*>(part_o + ((int64_t)i * rows + row) * kRowD + 4 * c);
+    const float w = __builtin_amdgcn_exp2f(ml.x - ref);
+    l = fmaf(w, ml.y, l);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o[e] = fmaf(w, x[e], o[e]);
+  }
+  const float inv = l == 0.0f ? 0.0f : 1.0f / l;   // (a part that gave up left NaN in l and O~)
+  const uint32_t bh = row / Sq, qi = row - bh * Sq, b = bh / H, h = bh - b * H;
+  const u32x2 v = {pack_bf16x2(o[0] * inv, o[1] * inv), pack_bf16x2(o[2] * inv, o[3] * inv)};
+  __builtin_nontemporal_store(v, reinterpret_cast<u32x2*>(out + b * os0 + h * os1 + (int64_t)qi * os2 + 4 * c));
+  if (c == 0) lse[row] = l == 0.0f ? -INFINITY : (m + log2f(l)) * 0.69314718055994530942f;
 }
 
 // Mixed launch: when the 256-query blocks do not fill the last round of work-groups on the 256 CUs
@@ -1172,7 +1222,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_pp_mixed_kernel(AttnStep s) 
   if (slot < wide) {
     const int item = first + slot;
     const int bh_ = item / nqb;
-    attn_pp_body<false, kExt, false, kDead, false>(s, smem_raw, bh_, (item - bh_ * nqb) * kQPerWG);
+    attn_pp_body<false, kExt, false, kDead, false>(s, smem_raw, bh_, (item - bh_ * nqb) * kQPerWG, 0);
   } else {
     const int hs = slot - wide;
     if (hs >= 2 * halves) return;
@@ -1180,7 +1230,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_pp_mixed_kernel(AttnStep s) 
     const int bh_ = item / nqb;
     const int q_base = (item - bh_ * nqb) * kQPerWG + (hs & 1) * kQPerWGSplit;
     if (q_base >= s.Sq) return;                        // second half of a ragged last block
-    attn_pp_body<true, kExt, false, kDead, false>(s, smem_raw, bh_, q_base);
+    attn_pp_body<true, kExt, false, kDead, false>(s, smem_raw, bh_, q_base, 0);
   }
 }
 
@@ -1228,6 +1278,19 @@ usp_status launch_pp_any(const AttnStep& s, bool ext, bool dead, bool split, uns
   if (ext) return dead ? launch_pp_form<true, kMulti, true>(s, split, wgs, st) : launch_pp_form<true, kMulti, false>(s, split, wgs, st);
   return dead ? launch_pp_form<false, kMulti, true>(s, split, wgs, st) : launch_pp_form<false, kMulti, false>(s, split, wgs, st);
 }
+usp_status launch_combine(const AttnStep& s, hipStream_t st) {
+  const uint32_t rows = (uint32_t)((int64_t)s.B * s.H * s.Sq), per = 1024 / (uint32_t)s.d;
+  const dim3 grid((rows + per - 1) / per);
+  bf16_t* out = (bf16_t*)s.out;
+  if (s.half_d)
+    hipLaunchKernelGGL((attn_combine_kernel<64>), grid, dim3(256), 0, st, s.part_o, s.part_ml, out, s.lse, s.parts, rows,
+                       (uint32_t)s.Sq, (uint32_t)s.H, s.os[0], s.os[1], s.os[2]);
+  else
+    hipLaunchKernelGGL((attn_combine_kernel<128>), grid, dim3(256), 0, st, s.part_o, s.part_ml, out, s.lse, s.parts, rows,
+                       (uint32_t)s.Sq, (uint32_t)s.H, s.os[0], s.os[1], s.os[2]);
+  USP_CHECK_HIP(hipGetLastError());
+  return USP_OK;
+}
 template <bool kExt, bool kDead>
 usp_status launch_mixed(const AttnStep& s, unsigned wgs, hipStream_t st) {
   constexpr int lds = kLdsBytes;
@@ -1240,8 +1303,37 @@ usp_status launch_mixed(const AttnStep& s, unsigned wgs, hipStream_t st) {
 
 int64_t attn_mfma_max_dead_tiles() { return kMaxWords; }
 
+// Keys shared between work-groups: for Q shards whose key-split work-groups leave most of the chip idle.  In
+// microseconds, a launch takes about 7.5 + tiles * t, t = 0.75 up to 128 work-groups and 0.92 at 216 and
+// more; parts add 6 for the second launch and what the parts' bytes, written and read, take at 5.5 TB/s.
+// Taken when that comes out at least 3 us lower.  Measured, 1 against the chosen number of parts: H = 3, Sq = 4608,
+// 4608 keys 57 -> 43 us; H = 1, Sq = 256, 4608 keys 57 -> 21 us; H = 4, Sq = 1024, 1024 keys 20.6 us with 1, 2 or 4.
+// At most 240 work-groups, so that the copy work-groups of the same launch (16 at least) find a CU.
+AttnForm attn_mfma_form(int B, int H, int Sq, int d, int64_t tiles) {
+  const int64_t wgs = 8 * (((int64_t)B * H * ((Sq + kQPerWGSplit - 1) / kQPerWGSplit) + 7) / 8);
+  AttnForm best = {0, 1};
+  if (wgs > 120) return best;
+  auto cost = [&](int parts) {
+    const double n = (double)wgs * parts;
+    const double t = 0.75 + 0.17 * (n <= 128 ? 0.0 : n >= 216 ? 1.0 : (n - 128) / 88);
+    const double bytes = parts > 1 ? 2.0 * 4 * d * parts * B * H * Sq : 0.0;
+    return 7.5 + (double)((tiles + parts - 1) / parts) * t + (parts > 1 ? 6.0 + bytes / 5.5e6 : 0.0);
+  };
+  double least = cost(1) - 3.0;
+  for (int parts = 2; parts <= 16 && parts * wgs <= 240 && parts <= tiles; ++parts) {
+    const double c = cost(parts);
+    if (c < least) { least = c; best = {2, parts}; }
+  }
+  return best;
+}
+
 usp_status launch_attn_mfma(const AttnStep& step, hipStream_t st) {
   AttnStep s = step;
+  if (s.parts < 1) s.parts = 1;
+  if (s.parts > 1 && (s.mode != 0 || s.variant != 2 || !s.part_o || !s.part_ml || s.n_copy != 0)) {
+    set_error("a launch that shares keys between work-groups finishes the result and needs room for the parts (key-split form)");
+    return USP_ERR_INVALID_ARG;
+  }
   if (s.n_multi > 0) {
     // several resident chunks, one launch: the same two work decompositions, by the same rule
     if (s.n_multi > AttnStep::kMaxMulti || s.mode != 0 || s.n_copy != 0 || s.key_mask || s.k_scale || s.v_scale) {   // (n_copy: the per-step form of the transfers)
@@ -1261,7 +1353,7 @@ usp_status launch_attn_mfma(const AttnStep& step, hipStream_t st) {
       dead |= s.chunk[c].mask_src != nullptr || s.chunk[c].Sc % kTile != 0;
     }
     const unsigned w256 = wg_grid_size((s.Sq + kQPerWG - 1) / kQPerWG, s.B * s.H);
-    const unsigned w128 = wg_grid_size((s.Sq + kQPerWGSplit - 1) / kQPerWGSplit, s.B * s.H);
+    const unsigned w128 = wg_grid_size((s.Sq + kQPerWGSplit - 1) / kQPerWGSplit, s.B * s.H * s.parts);
     // There is no mixed form of this launch: between the two decompositions, take the one whose
     // rounds of work-groups over the 256 CUs cost less (a key-split work-group takes about 0.55 of a
     // 256-query one)
@@ -1283,7 +1375,8 @@ usp_status launch_attn_mfma(const AttnStep& step, hipStream_t st) {
       s.arrive_need = s.copy_wgs + (s.arrive_need_extra > 0 ? s.arrive_need_extra : 0);
       if (s.arrive_polls <= 0 || s.arrive_polls > kArrivePolls) s.arrive_polls = kArrivePolls;
     }
-    return launch_pp_any<true>(s, s.multi_fp8 != 0, dead, split, wgs, st);
+    const usp_status r = launch_pp_any<true>(s, s.multi_fp8 != 0, dead, split, wgs, st);
+    return r == USP_OK && s.parts > 1 ? launch_combine(s, st) : r;
   }
   const bool ext = s.k_scale != nullptr;
   const bool dead = s.key_mask != nullptr || s.Sc % kTile != 0 || s.Sc == 0;
@@ -1303,7 +1396,7 @@ usp_status launch_attn_mfma(const AttnStep& step, hipStream_t st) {
   const int items = (int)((s.Sq + kQPerWG - 1) / kQPerWG) * s.B * s.H;
   const int rem = items % 256;
   int mix_blocks = 0;
-  if (s.half_d) mix_blocks = 0;                                           // (the mixed kernel has no half-head-dimension form)
+  if (s.half_d || s.parts > 1) mix_blocks = 0;                                           // (the mixed kernel has no half-head-dimension form)
   else if (s.variant == 4) mix_blocks = (items + 1) / 2;                  // forced: the second half of the blocks
   else if (s.variant == 0 && !split && rem > 0 && rem <= 128) mix_blocks = rem;
   if (mix_blocks > 0) {
@@ -1314,9 +1407,10 @@ usp_status launch_attn_mfma(const AttnStep& step, hipStream_t st) {
     if (ext) return dead ? launch_mixed<true, true>(s, wgs_mixed, st) : launch_mixed<true, false>(s, wgs_mixed, st);
     return dead ? launch_mixed<false, true>(s, wgs_mixed, st) : launch_mixed<false, false>(s, wgs_mixed, st);
   }
-  const unsigned wgs = split ? wg_grid_size((s.Sq + kQPerWGSplit - 1) / kQPerWGSplit, s.B * s.H) : wgs256;
+  const unsigned wgs = split ? wg_grid_size((s.Sq + kQPerWGSplit - 1) / kQPerWGSplit, s.B * s.H * s.parts) : wgs256;
   s.copy_wgs = prefetch_wg_count(s, (int)wgs, 1);
-  return launch_pp_any<false>(s, ext, dead, split, wgs, st);
+  const usp_status r = launch_pp_any<false>(s, ext, dead, split, wgs, st);
+  return r == USP_OK && s.parts > 1 ? launch_combine(s, st) : r;
 }
 
 }  // namespace usp

@@ -67,7 +67,10 @@ struct Plan {
   bool ring1 = false;                   // fused prefetch as one launch over the whole ring: a staging buffer per chunk
   size_t off_ring1 = 0, off_arrive = 0; // K | V of chunk 1, K | V of chunk 2, ... (dense, 256-byte aligned each); arrival counters
   bool ring8 = false;                   // FP8 chunks decoded inside one launch over the whole ring
+  size_t off_stepwise_end = 0;          // end of what the launch-per-chunk forms use
   size_t off_ring8 = 0, off_ext8 = 0;   // bf16 K | V of every live chunk; records of all their tiles
+  AttnForm form = {0, 1};               // work decomposition of a launch that finishes the result (one launch, or one chunk)
+  size_t off_parts = 0;                 // its parts: fp32 O~, then (m, l)
   size_t tiles = 0;                     // 64-key tiles of all chunks
   size_t total = 0;
 };
@@ -110,7 +113,7 @@ bool one_launch_lengths(const usp_attn_desc* d, bool least, bool* whole, size_t*
 }
 
 // `least`: the plan that needs no more workspace than a launch per chunk, or one launch over whole tiles,
-// does: no one launch over ragged chunks.
+// does: no one launch over ragged chunks, no parts.
 usp_status make_plan_of(const usp_attn_desc* d, bool least, Plan* p) {
   USP_CHECK_ARG(d != nullptr, "desc is NULL");
   USP_CHECK_ARG(d->B > 0 && d->H > 0 && d->Sq > 0, "B, H, Sq must be positive (B=%d H=%d Sq=%d)", d->B, d->H, d->Sq);
@@ -191,6 +194,7 @@ usp_status make_plan_of(const usp_attn_desc* d, bool least, Plan* p) {
     p->off_ext = off; off += align_up((size_t)d->B * d->H * (((size_t)p->max_len + 63) / 64) * 1024);
     off += align_up((size_t)d->B * 4);
   }
+  p->off_stepwise_end = off;
   const int64_t q_blocks = (int64_t)d->B * d->H * ((d->Sq + 255) / 256);
   bool whole = true;
   size_t tiles = 0;
@@ -218,6 +222,21 @@ usp_status make_plan_of(const usp_attn_desc* d, bool least, Plan* p) {
   }
   // (kept in the size query's answers: what key masks of a one-launch ring over bf16 chunks took)
   if (p->one_launch && whole && !p->fp8 && (!p->dbuf || p->ring1)) off += align_up((size_t)d->B * d->H * tiles * 1024);
+  const size_t stepwise = p->off_stepwise_end;
+  if (p->mfma && !least && !(d->flags & (USP_ATTN_KERNEL_WIDE | USP_ATTN_KERNEL_SPLIT | USP_ATTN_KERNEL_MIXED)) &&
+      (p->W == 1 || (p->one_launch && (p->fp8 ? p->ring8 : (!p->dbuf || p->ring1) && (p->fused_pf || q_blocks <= 256))))) {
+    p->form = attn_mfma_form(d->B, d->H, d->Sq, d->d, (int64_t)p->tiles);
+    if (p->form.parts > 1) {
+      // in the place of what only a launch per chunk uses, where that is enough or nothing else lies behind it
+      const size_t need = align_up((size_t)p->form.parts * p->rows_q * d->d * 4) + align_up((size_t)p->form.parts * p->rows_q * 8);
+      if (p->W > 1 && (need <= stepwise || (!p->ring1 && !p->ring8))) {
+        if (off < need) off = need;
+      } else {
+        p->off_parts = off;
+        off += need;
+      }
+    }
+  }
   p->total = off;
   p->valid = true;
   return USP_OK;
@@ -450,6 +469,15 @@ usp_status usp::ring_attn_fwd_impl(const usp_attn_desc* desc, const void* q, con
   const float scale = desc->softmax_scale > 0.0f ? desc->softmax_scale : 1.0f / sqrtf((float)d);
   const size_t kv_es = elt_size(desc->kv_dtype);
 
+  // a launch that finishes the result: its work decomposition, and room for the parts if the keys are shared
+  auto set_form = [&](AttnStep* a) {
+    if (p.form.parts <= 1) return;
+    a->variant = p.form.variant;
+    a->parts = p.form.parts;
+    a->part_o = (float*)(ws + p.off_parts);
+    a->part_ml = (float*)(ws + p.off_parts + align_up((size_t)p.form.parts * p.rows_q * d * 4));
+  };
+
   // ---- Algorithm 2, lines 1-3: the first prefetch is issued before the local chunk is computed
   std::vector<hipEvent_t> copied(p.W, nullptr), computed(p.W, nullptr);
   auto stage_chunk = [&](int r) -> usp_status {  // "recv" chunk r (r >= 1) into buffer (r-1)%2 on xs
@@ -539,6 +567,7 @@ usp_status usp::ring_attn_fwd_impl(const usp_attn_desc* desc, const void* q, con
         a.arrive_need_extra = opt.arrive_need_extra; a.arrive_polls = opt.arrive_polls;
         if ((st = launch_attn_arrive_reset(a.arrive, cs)) != USP_OK) return st;
       }
+      set_form(&a);
       return launch_attn_mfma(a, cs);
     }
   }
@@ -599,6 +628,7 @@ usp_status usp::ring_attn_fwd_impl(const usp_attn_desc* desc, const void* q, con
       }
       stage += 2 * align_up(bytes);
     }
+    set_form(&a);
     if ((st = launch_attn_fp8_chunk_prepare(a, 0, true, cs)) != USP_OK) return st;   // also zeroes the counters
     return launch_attn_mfma(a, cs);
   }
@@ -643,7 +673,10 @@ usp_status usp::ring_attn_fwd_impl(const usp_attn_desc* desc, const void* q, con
     a.lse = lse;
     a.out = out;
     a.acc = p.W > 1 && !p.unfused ? (float*)(ws + p.off_acc) : nullptr;
-    if (p.W == 1) a.mode = 0;
+    if (p.W == 1) {
+      a.mode = 0;
+      if (p.mfma) set_form(&a);
+    }
     else if (p.unfused) {
       a.mode = 0;
       if (r > 0) {

@@ -95,6 +95,11 @@ struct AttnStep {
   int half_d;                // matrix-core kernels: d = 64: the rows of Q, K, V, `out` and acc are 64 wide (128 bytes), the kernels
                              // run their head-dimension loops over half the slices
   float* acc;                // fp32 [B,H,Sq,d] dense carried O (modes 1-3)
+  // matrix-core kernels, mode 0: the keys of a query block are shared by `parts` work-groups (0 counts as 1), each
+  // with its own range of tiles; their unnormalised O~ and (m in log2 units, l) per query are put together by a second launch
+  int parts;
+  float* part_o;             // fp32 [parts][B,H,Sq,d]
+  float* part_ml;            // fp32 [parts][B,H,Sq][2]
   void* out;                 // qo_dtype by os strides (modes 0, 3)
   float* lse;                // fp32 [B,H,Sq] dense
   // Matrix-core kernels, FP8 K: per-(batch, head, 64-key tile) records of 64 floats, laid out
@@ -157,6 +162,9 @@ inline int prefetch_wg_count(const AttnStep& s, int attn_wgs, int slots_per_cu) 
 usp_status launch_attn_generic(const AttnStep& s, hipStream_t st);
 usp_status launch_attn_mfma(const AttnStep& s, hipStream_t st);
 bool attn_mfma_supported(const AttnStep& s);
+// How the matrix-core kernels run a launch that finishes its result: variant as AttnStep::variant, and parts
+struct AttnForm { int variant, parts; };
+AttnForm attn_mfma_form(int B, int H, int Sq, int d, int64_t tiles);
 // tiles a launch over several chunks takes if some of its keys are dead (a mask, a ragged chunk)
 int64_t attn_mfma_max_dead_tiles();
 usp_status launch_attn_arrive_reset(int* arrive, hipStream_t st);

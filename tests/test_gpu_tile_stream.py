@@ -1,5 +1,5 @@
-"""Dead keys (ragged chunks, key masks) in the tile stream of the matrix-core kernels: edges of tiles and
-words, against the fp64 oracle at the bars of the other attention tests."""
+"""Dead keys (ragged chunks, key masks) and shared keys in the tile stream of the matrix-core kernels: edges
+of tiles, words and parts, against the fp64 oracle at the bars of the other attention tests."""
 import numpy as np
 import pytest
 import torch
@@ -51,7 +51,7 @@ def _masks(rng, B, lens, kind):
 
 
 # (B, H, Sq, lens): ragged rings in one launch (513 = one row in the last tile, 575 = one missing), one chunk
-# shorter than a tile, more and fewer tiles
+# shorter than a tile, keys shared by 2 and more work-groups, more parts than live tiles
 SHAPES = [(1, 6, 300, (513, 575, 640)), (2, 3, 129, (700, 0, 525)), (1, 4, 40, (37,)), (2, 2, 200, (1100,)),
           (1, 1, 64, (4608,)), (1, 2, 130, (2049, 1023)), (2, 1, 257, (1024, 1024))]
 
@@ -59,7 +59,7 @@ SHAPES = [(1, 6, 300, (513, 575, 640)), (2, 3, 129, (700, 0, 525)), (1, 4, 40, (
 @pytest.mark.parametrize("mask", [None, "tail", "holes", "all"])
 @pytest.mark.parametrize("d,fp8", [(128, False), (64, False), (128, True), (64, True)])
 @pytest.mark.parametrize("B,H,Sq,lens", SHAPES)
-def test_dead_keys(B, H, Sq, lens, d, fp8, mask):
+def test_dead_keys_and_parts(B, H, Sq, lens, d, fp8, mask):
     if mask == "all" and B == 1:
         pytest.skip("covered with two entries")
     P = _P()
@@ -88,6 +88,22 @@ def test_dead_keys(B, H, Sq, lens, d, fp8, mask):
             ref = o, l
         elif flags == P.USP_ATTN_FUSED_PREFETCH:     # the transfers inside the launch change no bit
             assert torch.equal(o, ref[0]) and torch.equal(l, ref[1])
+
+
+def test_parts_need_no_more_workspace_than_there_is():
+    """A workspace that holds a launch per chunk but not the parts is enough; one byte less is refused."""
+    P = _P()
+    inp = W.make_attention_inputs(W.Workload("least", 5, 1, 1, 128, 128, (4608,), "bf16"))
+    q, k, v = dev_bf16(inp.q), [dev_bf16(x) for x in inp.k], [dev_bf16(x) for x in inp.v]
+    least = 72 * 1024 + 256                          # 1 KB per tile of the head, one count
+    assert P.usp_ring_attn_workspace_bytes(P.make_attn_desc(q, k, q)) > least
+    ro, rl = orc.ring_attention(inp.q, inp.k, inp.v, float(inp.softmax_scale))
+    o, l = P.usp_ring_attn_fwd(q, k, v, softmax_scale=float(inp.softmax_scale),
+                               workspace=torch.empty((least,), dtype=torch.uint8, device=DEV))
+    torch.cuda.synchronize()
+    _parity(o, l, ro, rl)
+    with pytest.raises(P.UspError):
+        P.usp_ring_attn_fwd(q, k, v, workspace=torch.empty((least - 1,), dtype=torch.uint8, device=DEV))
 
 
 @pytest.mark.parametrize("split", [False, True])
