@@ -1,6 +1,6 @@
 """MI355X (gfx950) hot path of Unified Sequence Parallel attention: ring attention with
 log-sum-exp merging and FP8 (E4M3) payload pack/unpack, as a C-ABI HIP library
-(include/usp.h, built into libusp.so) with a thin ctypes binding.
+(include/usp.h, built into libusp.so) with a thin binding.
 
     from paper_2602_10940_amd import usp_ring_attn_fwd, usp_lse_merge, usp_fp8_quant, usp_fp8_dequant
 
@@ -17,5 +17,6 @@ _BINDING_NAMES = (
 def __getattr__(name):
     if name in _BINDING_NAMES:
         from . import binding
-        return getattr(binding, name)
+        value = globals()[name] = getattr(binding, name)   # found directly from now on
+        return value
     raise AttributeError(name)

@@ -1,8 +1,9 @@
-"""ctypes binding of libusp.so: same names as the C ABI in include/usp.h.
+"""Binding of libusp.so: same names as the C ABI in include/usp.h.
 
-Marshalling only: every step of the path runs in the library's HIP kernels.  torch is
-used for device memory and stream handles, nothing else.  There is no CPU fallback:
-if the library is missing or a call fails, a UspError is raised.
+The calls that launch kernels go through _usp_calls.so (csrc/py_calls.cpp), which reads the tensors in
+native code; descriptors, sizes and errors go through ctypes.  Marshalling only: every step of the path
+runs in the library's HIP kernels.  torch is used for device memory and stream handles, nothing else.
+There is no CPU fallback: if a library is missing or a call fails, a UspError is raised.
 """
 from __future__ import annotations
 
@@ -14,6 +15,7 @@ import torch
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "libusp.so")
+CALLS_PATH = os.path.join(_PKG, "_usp_calls.so")
 
 USP_OK, USP_ERR_INVALID_ARG, USP_ERR_UNSUPPORTED, USP_ERR_WORKSPACE, USP_ERR_HIP = 0, -1, -2, -3, -4
 USP_F32, USP_BF16, USP_FP8_E4M3FN = 0, 1, 2
@@ -60,16 +62,20 @@ class AttnDesc(ctypes.Structure):
 
 
 _lib = None
+_calls = None   # the extension module _usp_calls
 
 
 def load_library() -> ctypes.CDLL:
-    """Load libusp.so (built in-tree by paper_2602_10940_amd.build). Fails loudly if absent."""
-    global _lib
+    """Load libusp.so and _usp_calls.so (built in-tree by paper_2602_10940_amd.build). Fails loudly if absent."""
+    global _lib, _calls
     if _lib is not None:
         return _lib
     if not os.path.exists(LIB_PATH):
         raise UspError(USP_ERR_HIP, "%s not found: run `python -m paper_2602_10940_amd.build` "
                        "(or __graft_entry__.build()) first; there is no fallback path" % LIB_PATH)
+    if not os.path.exists(CALLS_PATH):
+        raise UspError(USP_ERR_HIP, "%s not found: run `python -m paper_2602_10940_amd.build` first; there is no "
+                       "fallback path" % CALLS_PATH)
     lib = ctypes.CDLL(LIB_PATH)
     vp, i64, i32, sz = ctypes.c_void_p, ctypes.c_int64, ctypes.c_int32, ctypes.c_size_t
     lib.usp_last_error.restype = ctypes.c_char_p
@@ -93,8 +99,24 @@ def load_library() -> ctypes.CDLL:
     lib.usp_fp8_quant_mapped.argtypes = [ctypes.POINTER(RowMap), i64, i32, vp, vp, vp, vp]
     lib.usp_fp8_dequant_mapped.restype = i32
     lib.usp_fp8_dequant_mapped.argtypes = [ctypes.POINTER(RowMap), i64, i32, vp, vp, vp, vp]
+    from . import _usp_calls
+    _calls = _usp_calls
     _lib = lib
     return lib
+
+
+def _native():
+    """The extension module, loaded with the library."""
+    if _lib is None:
+        load_library()
+    return _calls
+
+
+def _raise(status: int, *tensors: torch.Tensor) -> None:
+    """Raise for a status of the extension module; what it cannot name is a dtype of one of the tensors."""
+    for t in tensors:
+        _dt(t.dtype)
+    _check(status)
 
 
 def _check(status: int) -> None:
@@ -139,25 +161,27 @@ def usp_fp8_quant(x: torch.Tensor, q: Optional[torch.Tensor] = None,
                   scales: Optional[torch.Tensor] = None, stream=None
                   ) -> Tuple[torch.Tensor, torch.Tensor]:
     """x [rows, cols] (bf16 or f32, dense) -> (codes uint8 [rows, cols], scales f32 [rows])."""
-    lib = load_library()
+    calls = _native()
     assert x.dim() == 2 and x.is_contiguous() and x.is_cuda
-    rows, cols = x.shape
     if q is None:
-        q = torch.empty((rows, cols), dtype=torch.uint8, device=x.device)
+        q = torch.empty(x.shape, dtype=torch.uint8, device=x.device)
     if scales is None:
-        scales = torch.empty((rows,), dtype=torch.float32, device=x.device)
-    _check(lib.usp_fp8_quant(rows, cols, _dt(x.dtype), _ptr(x), _ptr(q), _ptr(scales), _stream_handle(stream)))
+        scales = torch.empty((x.shape[0],), dtype=torch.float32, device=x.device)
+    st = calls.fp8_quant(x, q, scales, stream)
+    if st:
+        _raise(st, x)
     return q, scales
 
 
 def usp_fp8_dequant(q: torch.Tensor, scales: torch.Tensor, out_dtype: torch.dtype = torch.bfloat16,
                     y: Optional[torch.Tensor] = None, stream=None) -> torch.Tensor:
-    lib = load_library()
+    calls = _native()
     assert q.dim() == 2 and q.is_contiguous() and q.dtype == torch.uint8 and q.is_cuda
-    rows, cols = q.shape
     if y is None:
-        y = torch.empty((rows, cols), dtype=out_dtype, device=q.device)
-    _check(lib.usp_fp8_dequant(rows, cols, _dt(y.dtype), _ptr(q), _ptr(scales), _ptr(y), _stream_handle(stream)))
+        y = torch.empty(q.shape, dtype=out_dtype, device=q.device)
+    st = calls.fp8_dequant(q, scales, y, stream)
+    if st:
+        _raise(st, y)
     return y
 
 
@@ -166,16 +190,17 @@ def usp_fp8_quant_mapped(x: torch.Tensor, n, src_stride, dst_stride, cols: int,
                          stream=None) -> Tuple[torch.Tensor, torch.Tensor]:
     """x: any contiguous tensor (flat element offsets); returns q uint8 [rows, cols], scales f32 [rows]
     with rows = prod(n).  src_stride in elements of x, dst_stride in rows of q."""
-    lib = load_library()
+    calls = _native()
     assert x.is_contiguous() and x.is_cuda
-    rows = int(n[0]) * int(n[1]) * int(n[2]) * int(n[3])
-    if q is None:
-        q = torch.empty((rows, cols), dtype=torch.uint8, device=x.device)
-    if scales is None:
-        scales = torch.empty((rows,), dtype=torch.float32, device=x.device)
-    m = make_row_map(n, src_stride, dst_stride)
-    _check(lib.usp_fp8_quant_mapped(ctypes.byref(m), cols, _dt(x.dtype), _ptr(x), _ptr(q), _ptr(scales),
-                                    _stream_handle(stream)))
+    if q is None or scales is None:
+        rows = int(n[0]) * int(n[1]) * int(n[2]) * int(n[3])
+        if q is None:
+            q = torch.empty((rows, cols), dtype=torch.uint8, device=x.device)
+        if scales is None:
+            scales = torch.empty((rows,), dtype=torch.float32, device=x.device)
+    st = calls.fp8_quant_mapped(x, n, src_stride, dst_stride, cols, q, scales, stream)
+    if st:
+        _raise(st, x)
     return q, scales
 
 
@@ -183,11 +208,11 @@ def usp_fp8_dequant_mapped(q: torch.Tensor, scales: torch.Tensor, n, src_stride,
                            stream=None) -> torch.Tensor:
     """q uint8 [rows, cols] and scales read by row (src_stride in rows); rows written into the contiguous
     tensor y (bf16 or f32) at element offsets sum i_k * dst_stride[k]."""
-    lib = load_library()
+    calls = _native()
     assert q.dim() == 2 and q.is_contiguous() and q.dtype == torch.uint8 and y.is_contiguous()
-    m = make_row_map(n, src_stride, dst_stride)
-    _check(lib.usp_fp8_dequant_mapped(ctypes.byref(m), q.shape[1], _dt(y.dtype), _ptr(q), _ptr(scales), _ptr(y),
-                                      _stream_handle(stream)))
+    st = calls.fp8_dequant_mapped(q, scales, n, src_stride, dst_stride, y, stream)
+    if st:
+        _raise(st, y)
     return y
 
 
@@ -195,16 +220,15 @@ def usp_lse_merge(o1: torch.Tensor, lse1: torch.Tensor, o2: torch.Tensor, lse2: 
                   o_out: Optional[torch.Tensor] = None, lse_out: Optional[torch.Tensor] = None,
                   stream=None) -> Tuple[torch.Tensor, torch.Tensor]:
     """o* [..., d] dense, lse* [...] f32.  Outputs may alias inputs."""
-    lib = load_library()
+    calls = _native()
     assert o1.is_contiguous() and o2.is_contiguous() and o1.shape == o2.shape and o1.dtype == o2.dtype
-    d = o1.shape[-1]
-    rows = o1.numel() // d if d else 0
     if o_out is None:
         o_out = torch.empty_like(o1)
     if lse_out is None:
         lse_out = torch.empty_like(lse1)
-    _check(lib.usp_lse_merge(rows, d, _dt(o1.dtype), _ptr(o1), _ptr(lse1), _ptr(o2), _ptr(lse2),
-                             _ptr(o_out), _ptr(lse_out), _stream_handle(stream)))
+    st = calls.lse_merge(o1, lse1, o2, lse2, o_out, lse_out, stream)
+    if st:
+        _raise(st, o1)
     return o_out, lse_out
 
 
@@ -251,22 +275,17 @@ def usp_ring_attn_fwd(q: torch.Tensor, k_chunks: Sequence[torch.Tensor], v_chunk
                       workspace: Optional[torch.Tensor] = None,
                       compute_stream=None, copy_stream=None) -> Tuple[torch.Tensor, torch.Tensor]:
     """Ring attention of q [B,H,Sq,d] over KV chunks [B,H,Sc_r,d]; returns (out, lse [B,H,Sq])."""
-    lib = load_library()
-    B, H, Sq, d = q.shape
+    calls = _native()
     if out is None:
-        out = torch.empty((B, H, Sq, d), dtype=q.dtype, device=q.device)
+        out = torch.empty(q.shape, dtype=q.dtype, device=q.device)
     if lse is None:
-        lse = torch.empty((B, H, Sq), dtype=torch.float32, device=q.device)
-    desc = make_attn_desc(q, k_chunks, out, softmax_scale, flags)
-    need = usp_ring_attn_workspace_bytes(desc)
-    if workspace is None and need > 0:
-        workspace = torch.empty((need,), dtype=torch.uint8, device=q.device)
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    cs = _stream_handle(compute_stream)
-    xs = None if copy_stream is None else _stream_handle(copy_stream)
-    _check(lib.usp_ring_attn_fwd(ctypes.byref(desc), _ptr(q), _ptr_array(k_chunks), _ptr_array(v_chunks),
-                                 _ptr_array(k_scales), _ptr_array(v_scales), _ptr_array(key_mask),
-                                 _ptr(out), _ptr(lse), _ptr(workspace), ws_bytes, cs, xs))
+        lse = torch.empty(q.shape[:3], dtype=torch.float32, device=q.device)
+    st = calls.ring_attn_fwd(q, k_chunks, v_chunks, k_scales, v_scales, key_mask, softmax_scale, flags, out, lse, workspace,
+                             compute_stream, copy_stream)
+    if st.__class__ is not int:
+        workspace = st              # allocated for the call
+    elif st:
+        _raise(st, q, k_chunks[0])
     out._usp_workspace = workspace  # keep the workspace alive as long as the result
     return out, lse
 
@@ -280,9 +299,8 @@ def usp_ring_attn_fwd_noalloc(q: torch.Tensor, k_chunks: Sequence[torch.Tensor],
                               ) -> Tuple[torch.Tensor, torch.Tensor]:
     """usp_ring_attn_fwd on the library's built-in scratch: the caller passes every input and output
     (out [B,H,Sq,d], lse [B,H,Sq]); nothing is allocated, here or in the library."""
-    lib = load_library()
-    desc = make_attn_desc(q, k_chunks, out, softmax_scale, flags)
-    _check(lib.usp_ring_attn_fwd_noalloc(ctypes.byref(desc), _ptr(q), _ptr_array(k_chunks), _ptr_array(v_chunks),
-                                         _ptr_array(k_scales), _ptr_array(v_scales), _ptr_array(key_mask),
-                                         _ptr(out), _ptr(lse), _stream_handle(compute_stream)))
+    st = _native().ring_attn_fwd_noalloc(q, k_chunks, v_chunks, k_scales, v_scales, key_mask, softmax_scale, flags, out, lse,
+                                         compute_stream)
+    if st:
+        _raise(st, q, k_chunks[0])
     return out, lse

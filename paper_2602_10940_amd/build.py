@@ -1,4 +1,4 @@
-"""Build the C-ABI library (libusp.so) for gfx950 with hipcc, in-tree.
+"""Build the C-ABI library (libusp.so) for gfx950 with hipcc, and the binding's calls with g++, in-tree.
 
     python -m paper_2602_10940_amd.build          # rebuild
 """
@@ -7,6 +7,7 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
@@ -22,6 +23,9 @@ DIAG_SOURCES = [os.path.join("diag", "usp_diag.hip")]
 
 # -packed-fp32-ops off: keep the compiler from forming packed fp32 VALU ops.
 # IEEE fp32 division / denormals are required by the FP8 scale arithmetic (no fast-math).
+# _usp_calls.so: the binding's calls on torch tensors, a CPython extension (host code) linked against libusp.so
+CALLS_LIB = os.path.join(PKG, "_usp_calls.so")
+CALLS_SOURCE = "py_calls.cpp"
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -48,11 +52,36 @@ def _compile(src: str, extra) -> str:
     return obj
 
 
+def _compile_calls() -> str:
+    import torch
+    from torch.utils.cpp_extension import include_paths
+    obj = os.path.join(OBJ_DIR, "py_calls.o")
+    incs = [sysconfig.get_path("include"), *include_paths(), os.path.join(ROOT, "include")]
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-fvisibility=hidden", "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
+           *[x for i in incs for x in ("-isystem", i)], "-c", os.path.join(CSRC, CALLS_SOURCE), "-o", obj]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed for %s:\n%s\n%s" % (CALLS_SOURCE, " ".join(cmd), r.stderr[-8000:]))
+    return obj
+
+
+def _link_calls(obj: str) -> None:
+    import torch
+    lib_dir = os.path.join(os.path.dirname(torch.__file__), "lib")
+    cmd = ["g++", "-shared", "-fPIC", "-o", CALLS_LIB, obj, "-L", PKG, "-lusp", "-Wl,-rpath,$ORIGIN",
+           "-L", lib_dir, "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("link failed:\n%s" % r.stderr[-8000:])
+
+
 def build(verbose: bool = False, extra_flags=()) -> str:
     os.makedirs(OBJ_DIR, exist_ok=True)
     srcs = SOURCES + DIAG_SOURCES
-    with ThreadPoolExecutor(max_workers=min(8, len(srcs))) as ex:
+    with ThreadPoolExecutor(max_workers=min(8, len(srcs) + 1)) as ex:
+        calls = ex.submit(_compile_calls)
         objs = list(ex.map(lambda s: _compile(s, list(extra_flags)), srcs))
+        calls_obj = calls.result()
     n = len(SOURCES)
     for lib, lib_objs, extra in ((LIB, objs[:n], []),
                                  (DIAG_LIB, objs[n:], ["-L", PKG, "-lusp", "-Wl,-rpath,$ORIGIN"])):
@@ -62,6 +91,9 @@ def build(verbose: bool = False, extra_flags=()) -> str:
             raise RuntimeError("link failed:\n%s" % r.stderr[-8000:])
         if verbose:
             print("built", lib)
+    _link_calls(calls_obj)
+    if verbose:
+        print("built", CALLS_LIB)
     return LIB
 
 
