@@ -7,17 +7,21 @@ namespace usp {
 usp_status launch_attn_generic_f32(const AttnStep& s, bool few, hipStream_t st);   // attn_generic_f32.hip
 
 namespace {
-template <class Unit, int kD>
+template <class Unit, int kD, int kDB>
 usp_status run_bf16(const AttnStep& s, bool few, hipStream_t st) {
-  return few ? tile::launch_tile<tile::Bf16Q, Unit, kD, 2>(s, st) : tile::launch_tile<tile::Bf16Q, Unit, kD, 1>(s, st);
+  return few ? tile::launch_tile<tile::Bf16Q, Unit, kD, kDB, 2>(s, st) : tile::launch_tile<tile::Bf16Q, Unit, kD, kDB, 1>(s, st);
 }
+// 32-wide steps of the head dimension in the scores, 16-wide blocks of it in the output
 template <class Unit>
 usp_status run_bf16_d(const AttnStep& s, bool few, hipStream_t st) {
-  if (s.d <= 64) return run_bf16<Unit, 64>(s, few, st);
-  if (s.d <= 96) return run_bf16<Unit, 96>(s, few, st);
-  if (s.d <= 128) return run_bf16<Unit, 128>(s, few, st);
-  if (s.d <= 160) return run_bf16<Unit, 160>(s, few, st);
-  return run_bf16<Unit, 256>(s, few, st);
+  if (s.d <= 48) return run_bf16<Unit, 64, 3>(s, few, st);
+  if (s.d <= 64) return run_bf16<Unit, 64, 4>(s, few, st);
+  if (s.d <= 80) return run_bf16<Unit, 96, 5>(s, few, st);
+  if (s.d <= 96) return run_bf16<Unit, 96, 6>(s, few, st);
+  if (s.d <= 112) return run_bf16<Unit, 128, 7>(s, few, st);
+  if (s.d <= 128) return run_bf16<Unit, 128, 8>(s, few, st);
+  if (s.d <= 160) return run_bf16<Unit, 160, 10>(s, few, st);
+  return run_bf16<Unit, 256, 16>(s, few, st);
 }
 }  // namespace
 

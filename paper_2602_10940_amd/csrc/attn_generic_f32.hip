@@ -5,7 +5,7 @@ namespace usp {
 namespace {
 template <class Unit, int kD>
 usp_status run_f32(const AttnStep& s, bool few, hipStream_t st) {
-  return few ? tile::launch_tile<tile::F32Q, Unit, kD, 4>(s, st) : tile::launch_tile<tile::F32Q, Unit, kD, 1>(s, st);
+  return few ? tile::launch_tile<tile::F32Q, Unit, kD, kD / 16, 4>(s, st) : tile::launch_tile<tile::F32Q, Unit, kD, kD / 16, 1>(s, st);
 }
 template <class Unit>
 usp_status run_f32_d(const AttnStep& s, bool few, hipStream_t st) {

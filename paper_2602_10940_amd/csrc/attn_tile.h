@@ -13,17 +13,20 @@
 //     to its 24 bits, so P.V is three exact products instead of one.  fp32 Q (engine F32Q):
 //     v_mfma_f32_16x16x4_f32.
 //   * Per-key factors: FP8 scales of K multiply the fp32 scores, those of V multiply P.
-//   * 64-key tiles are staged in LDS by the whole work-group, the next tile's global loads being in
-//     flight while the current one is computed on.  Pitches are odd multiples of 16 bytes (K) and of 32
+//   * 64-key tiles are staged in LDS by the whole work-group through registers, a tile's global loads being in
+//     flight while the one before it is computed on.  Pitches are odd multiples of 16 bytes (K) and of 32
 //     bytes (V of Bf16Q, read transposed), or d + 4 words (F32Q): no bank conflicts by construction.
 //   * kKW waves share the 16 queries and take 64 / kKW keys of every tile each, their partial results
 //     being combined through LDS at the end of a chunk: for calls with few query blocks.
 //
-// What bounds it: a work-group's serial chain per tile (stage, barrier, scores, softmax, P.V: 1.8 us at bf16
-// d = 72, of which the matrix cores are busy 0.3), hidden in part by a second work-group on the CU; fp32 is
-// bound by the fp32 matrix rate from about 256 work-groups on.  B=2 H=16 S=1024 d=72 bf16: 39 us = 249 TFLOP/s;
-// one wave per query row with scalar products, which this replaced, took 855 us.  Two chunks of 128 keys,
-// H=2 Sq=128 d=64 fp32: one launch of 9.4 us for two of 12.
+// What bounds it (bf16, d = 72, two work-groups per CU): the instructions its two waves per SIMD issue, 43 % of the
+// cycles on the VALU (a third of that the split of P) and 29 % on the matrix cores, with waits between the phases of a
+// tile in the rest.  So: one barrier per tile where two buffers fit, tiles fetched through descriptors at places
+// fixed per thread, no test of a key outside masked and ragged tiles, no work for 16-wide blocks past the head
+// dimension, O rescaled only when a maximum has grown by more than 2^8.  B=2 H=16 S=1024 d=72 bf16: 32.7 us =
+// 295 TFLOP/s (38.6 before those; one wave per query row with scalar products, the first form, 856).
+// fp32 is bound by the fp32 matrix rate from about 256 work-groups on (d = 64, same sizes: 85 us, 100 TFLOP/s).
+// Two chunks of 128 keys, H=2 Sq=128 d=64 fp32: one launch of 9.8 us for two of 12.
 #pragma once
 #include <type_traits>
 
@@ -56,12 +59,20 @@ __device__ __forceinline__ float group_sum(float x) {
   return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
+// A tile of K or V as a buffer: what lies past its valid rows, or is asked for at kNowhere, loads as zeros.
+typedef __amdgpu_buffer_rsrc_t Buf;
+constexpr uint32_t kNowhere = 0xf0000000u;
+__device__ __forceinline__ Buf tile_buffer(const void* p, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
+}
+
 // Eight consecutive elements of a K / V row in flight from global memory, and their form in LDS.
 struct UnitBf16 {
   typedef bf16_t elt;
   u32x4 w;
   __device__ __forceinline__ void zero() { w = u32x4{0u, 0u, 0u, 0u}; }
   __device__ __forceinline__ void load(const elt* p) { w = *reinterpret_cast<const u32x4*>(p); }
+  __device__ __forceinline__ void load(Buf b, uint32_t off) { w = __builtin_amdgcn_raw_buffer_load_b128(b, off, 0, 0); }
   __device__ __forceinline__ u32x4 as_bf16() const { return w; }
 };
 struct UnitF8 {
@@ -69,6 +80,7 @@ struct UnitF8 {
   u32x2 w;
   __device__ __forceinline__ void zero() { w = u32x2{0u, 0u}; }
   __device__ __forceinline__ void load(const elt* p) { w = *reinterpret_cast<const u32x2*>(p); }   // rows are 8-byte aligned
+  __device__ __forceinline__ void load(Buf b, uint32_t off) { w = __builtin_amdgcn_raw_buffer_load_b64(b, off, 0, 0); }
   __device__ __forceinline__ void as_f32(f32x4& a, f32x4& b) const {
     const f32x2 c0 = __builtin_amdgcn_cvt_pk_f32_fp8((int)w[0], false), c1 = __builtin_amdgcn_cvt_pk_f32_fp8((int)w[0], true);
     const f32x2 c2 = __builtin_amdgcn_cvt_pk_f32_fp8((int)w[1], false), c3 = __builtin_amdgcn_cvt_pk_f32_fp8((int)w[1], true);
@@ -89,6 +101,10 @@ struct UnitF32 {
     a = *reinterpret_cast<const f32x4*>(p);
     b = *reinterpret_cast<const f32x4*>(p + 4);
   }
+  __device__ __forceinline__ void load(Buf buf, uint32_t off) {
+    a = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(buf, off, 0, 0));
+    b = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(buf, off + 16, 0, 0));
+  }
   __device__ __forceinline__ void as_f32(f32x4& x, f32x4& y) const { x = a; y = b; }
 };
 
@@ -100,11 +116,12 @@ __device__ __forceinline__ void split3(float p0, float p1, uint32_t& hi, uint32_
   lo = pack_bf16x2(a0 - __uint_as_float(mid << 16), a1 - __uint_as_float(mid & 0xffff0000u));
 }
 
-// kD: head dimension rounded up to the kernel's size (columns past s.d are zero); kMB: 16-key blocks per wave
-template <int kD, int kMB>
+// kD: head dimension rounded up to the kernel's size (columns past s.d are zero); kDB: 16-wide blocks of it that
+// the output has; kMB: 16-key blocks per wave
+template <int kD, int kDB, int kMB>
 struct Bf16Q {
   typedef bf16_t qo_elt;
-  static constexpr int kSK = kD / 32, kDB = kD / 16;
+  static constexpr int kSK = kD / 32;
   static constexpr int kPitchK = kD * 2 + 16, kPitchV = kD * 2 + 32;   // bytes
   static_assert(kD % 32 == 0 && kMB % 2 == 0, "32-wide contraction steps");
   bf16x8 q[kSK];
@@ -142,7 +159,7 @@ struct Bf16Q {
     return __builtin_bit_cast(bf16x8, u32x4{a[0], a[1], b[0], b[1]});
   }
   // O^T += V^T P^T
-  __device__ __forceinline__ void pv(const unsigned char* v, int d, int r, int g, const float (&p)[kMB][4], f32x4 (&o)[kDB]) const {
+  __device__ __forceinline__ void pv(const unsigned char* v, int r, int g, const float (&p)[kMB][4], f32x4 (&o)[kDB]) const {
     constexpr int kGrp = 4;   // head-dim blocks whose MFMAs alternate, so that none waits for its predecessor
 #pragma unroll
     for (int kk = 0; kk < kMB / 2; ++kk) {
@@ -157,7 +174,6 @@ struct Bf16Q {
         }
 #pragma unroll
       for (int d0 = 0; d0 < kDB; d0 += kGrp) {
-        if (16 * d0 >= d) break;   // (uniform) columns past the head dimension
         bf16x8 a[kGrp];
 #pragma unroll
         for (int x = 0; x < kGrp; ++x)
@@ -175,10 +191,10 @@ struct Bf16Q {
   }
 };
 
-template <int kD, int kMB>
+template <int kD, int kDB, int kMB>
 struct F32Q {
   typedef float qo_elt;
-  static constexpr int kSK = kD / 16, kDB = kD / 16;
+  static constexpr int kSK = kD / 16;
   static constexpr int kPitchK = (kD + 4) * 4, kPitchV = (kD + 4) * 4;
   f32x4 q[kSK];   // head dims 16 * s + 4 * g + j: the contraction visits the head dimensions in that order on both sides
   __device__ __forceinline__ void load_q(const float* row, int d, int g) {
@@ -195,9 +211,14 @@ struct F32Q {
     *reinterpret_cast<f32x4*>(kv + row * pitch + unit * 32) = a;
     *reinterpret_cast<f32x4*>(kv + row * pitch + unit * 32 + 16) = b;
   }
+  // kAcc sums per block, so that an MFMA does not wait for the one before it where a wave has one block
   __device__ __forceinline__ void scores(const unsigned char* k, int r, int g, f32x4 (&s)[kMB]) const {
+    constexpr int kAcc = kMB >= 4 ? 1 : 4 / kMB;
+    f32x4 acc[kAcc][kMB];
 #pragma unroll
-    for (int mb = 0; mb < kMB; ++mb) s[mb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    for (int x = 0; x < kAcc; ++x)
+#pragma unroll
+      for (int mb = 0; mb < kMB; ++mb) acc[x][mb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
     for (int c = 0; c < kSK; ++c) {
       f32x4 a[kMB];
@@ -206,22 +227,25 @@ struct F32Q {
 #pragma unroll
       for (int j = 0; j < 4; ++j)
 #pragma unroll
-        for (int mb = 0; mb < kMB; ++mb) s[mb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[mb][j], q[c][j], s[mb], 0, 0, 0);
+        for (int mb = 0; mb < kMB; ++mb)
+          acc[j % kAcc][mb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[mb][j], q[c][j], acc[j % kAcc][mb], 0, 0, 0);
+    }
+#pragma unroll
+    for (int mb = 0; mb < kMB; ++mb) {
+      s[mb] = acc[0][mb];
+#pragma unroll
+      for (int x = 1; x < kAcc; ++x) s[mb] += acc[x][mb];
     }
   }
-  __device__ __forceinline__ void pv(const unsigned char* v, int d, int r, int g, const float (&p)[kMB][4], f32x4 (&o)[kDB]) const {
+  __device__ __forceinline__ void pv(const unsigned char* v, int r, int g, const float (&p)[kMB][4], f32x4 (&o)[kDB]) const {
 #pragma unroll
     for (int mb = 0; mb < kMB; ++mb)
 #pragma unroll
       for (int i = 0; i < 4; ++i)   // contraction index g of the MFMA is key 16 * mb + 4 * g + i
 #pragma unroll
-        for (int d0 = 0; d0 < kDB; d0 += 4) {
-          if (16 * d0 >= d) break;
-#pragma unroll
-          for (int x = d0; x < d0 + 4 && x < kDB; ++x) {
-            const float a = *reinterpret_cast<const float*>(v + (16 * mb + 4 * g + i) * kPitchV + (16 * x + r) * 4);
-            o[x] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, p[mb][i], o[x], 0, 0, 0);
-          }
+        for (int x = 0; x < kDB; ++x) {
+          const float a = *reinterpret_cast<const float*>(v + (16 * mb + 4 * g + i) * kPitchV + (16 * x + r) * 4);
+          o[x] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, p[mb][i], o[x], 0, 0, 0);
         }
   }
   static __device__ __forceinline__ void store4(float* p, const float (&o)[4]) {
@@ -229,20 +253,24 @@ struct F32Q {
   }
 };
 
-// LDS of a work-group: K tile | V tile | per-key factor of the exponent, bias (0 / -inf), V scale; the
-// exchange of the kKW partial results reuses the tiles
+// LDS of a work-group: one or two buffers of K tile | V tile | per-key factor of the exponent, bias (0 / -inf),
+// V scale.  Two where two work-groups still fit a CU: a tile is then staged while the one before it is
+// computed on, with one barrier per tile.  The exchange of the kKW partial results reuses a buffer's tiles.
 template <class E, int kD, int kKW>
-constexpr int lds_bytes() {
-  constexpr int tiles = kTile * (E::kPitchK + E::kPitchV);
-  constexpr int xch = 4 * 64 * (kD / 4 + 2) * 4;
-  return (kKW > 1 && xch > tiles ? xch : tiles) + 3 * kTile * 4;
-}
+struct Plan {
+  static constexpr int tiles = kTile * (E::kPitchK + E::kPitchV);
+  static constexpr int xch = kKW > 1 ? 4 * 64 * (kD / 4 + 2) * 4 : 0;
+  static constexpr int fac = xch > tiles ? xch : tiles;          // offset of the per-key values
+  static constexpr int one = fac + 3 * kTile * 4;
+  static constexpr int buffers = 2 * one <= 80 * 1024 ? 2 : 1;
+};
 
-template <template <int, int> class Engine, class Unit, int kD, int kKW>
+template <template <int, int, int> class Engine, class Unit, int kD, int kDB, int kKW>
 __global__ __launch_bounds__(kThreads, kD > 160 ? 1 : 2)   // waves per SIMD the registers allow
 void attn_tile_kernel(AttnStep s) {
-  constexpr int kMB = 4 / kKW, kDB = kD / 16;
-  typedef Engine<kD, kMB> E;
+  constexpr int kMB = 4 / kKW;
+  typedef Engine<kD, kDB, kMB> E;
+  typedef Plan<E, kD, kKW> L;
   typedef typename Unit::elt KT;
   typedef typename E::qo_elt QT;
   constexpr bool fp8 = std::is_same<Unit, UnitF8>::value;
@@ -251,9 +279,6 @@ void attn_tile_kernel(AttnStep s) {
     if (blockIdx.y == 0 && blockIdx.z == 0) prefetch_copy(s, blockIdx.x - (gridDim.x - s.copy_wgs), threadIdx.x, kThreads);
     return;
   }
-  unsigned char* k_lds = smem;
-  unsigned char* v_lds = smem + kTile * E::kPitchK;
-  float* fac = reinterpret_cast<float*>(smem + lds_bytes<E, kD, kKW>() - 3 * kTile * 4);   // factor | bias | V scale
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r = lane & 15, g = lane >> 4;
   const int part = wave % kKW;                                  // which keys of a tile this wave takes
@@ -269,23 +294,42 @@ void attn_tile_kernel(AttnStep s) {
   constexpr int kUPR = kD / 8, kNU = kTile * kUPR / kThreads;   // units per row; units per thread and tensor
   Unit ku[kNU], vu[kNU];
   float f_c = 0.0f, f_b = 0.0f, f_v = 0.0f;                     // threads 0..63: the tile's per-key values
-  auto fetch = [&](int c, int t) {
-    const AttnStep::Chunk& ch = s.chunk[c];
-    const int left = ch.Sc - t * kTile;                         // valid rows of this tile
-    const KT* kb = (const KT*)ch.k + b * ch.ks0 + h * ch.ks1 + (int64_t)t * kTile * s.ks[2];
-    const KT* vb = (const KT*)ch.v + b * ch.ks0 + h * ch.ks1 + (int64_t)t * kTile * s.ks[2];
+  // A thread's places in a tile are the same in every tile, so that a tile costs the scalar unit a descriptor and
+  // nothing else: with a 64-bit address, a row and a column test per unit, fetching took 140 of the 500
+  // instructions a wave issued per tile, and the issue of instructions is what bounds the kernel.
+  const uint32_t rowB = (uint32_t)(s.ks[2] * sizeof(KT));
+  const bool near_rows = s.ks[2] * (int64_t)sizeof(KT) * kTile < (int64_t)kNowhere;   // else: addresses of 64 bits
+  uint32_t place[kNU];
 #pragma unroll
-    for (int i = 0; i < kNU; ++i) {
-      const int u = tid + i * kThreads, row = u / kUPR, col = (u % kUPR) * 8;
-      ku[i].zero();
-      vu[i].zero();
-      if (row < left && col < d) {
-        ku[i].load(kb + row * s.ks[2] + col);
-        vu[i].load(vb + row * s.ks[2] + col);
+  for (int i = 0; i < kNU; ++i) {
+    const int u = tid + i * kThreads, row = u / kUPR, col = (u % kUPR) * 8;
+    place[i] = col < d ? row * rowB + col * (uint32_t)sizeof(KT) : kNowhere;
+  }
+  int pc = -1, first_key = 0, left = 0;                         // next tile to fetch: its chunk, first key, rows from there on
+  const KT *kb = nullptr, *vb = nullptr;
+  auto fetch = [&]() {
+    if (near_rows) {
+      const uint32_t bytes = (uint32_t)min(left, kTile) * rowB;
+      const Buf kbuf = tile_buffer(kb, bytes), vbuf = tile_buffer(vb, bytes);
+#pragma unroll
+      for (int i = 0; i < kNU; ++i) ku[i].load(kbuf, place[i]);
+#pragma unroll
+      for (int i = 0; i < kNU; ++i) vu[i].load(vbuf, place[i]);
+    } else {
+#pragma unroll
+      for (int i = 0; i < kNU; ++i) {
+        const int u = tid + i * kThreads, row = u / kUPR, col = (u % kUPR) * 8;
+        ku[i].zero();
+        vu[i].zero();
+        if (row < left && col < d) {
+          ku[i].load(kb + row * s.ks[2] + col);
+          vu[i].load(vb + row * s.ks[2] + col);
+        }
       }
     }
     if (tid < kTile) {
-      const int key = t * kTile + tid;
+      const AttnStep::Chunk& ch = s.chunk[pc];
+      const int key = first_key + tid;
       const bool keep = tid < left && (ch.mask_src == nullptr || ch.mask_src[(int64_t)b * ch.Sc + key] != 0);
       f_c = scale2; f_b = keep ? 0.0f : -INFINITY; f_v = 1.0f;
       if (fp8 && tid < left) {
@@ -295,11 +339,13 @@ void attn_tile_kernel(AttnStep s) {
       }
     }
   };
-  auto stage = [&]() {
+  auto stage = [&](unsigned char* buf) {
+    unsigned char* v_lds = buf + kTile * E::kPitchK;
+    float* fac = reinterpret_cast<float*>(buf + L::fac);         // factor | bias | V scale
 #pragma unroll
     for (int i = 0; i < kNU; ++i) {
       const int u = tid + i * kThreads, row = u / kUPR, unit = u % kUPR;
-      E::put(k_lds, E::kPitchK, row, unit, ku[i]);
+      E::put(buf, E::kPitchK, row, unit, ku[i]);
       E::put(v_lds, E::kPitchV, row, unit, vu[i]);
     }
     if (tid < kTile) { fac[tid] = f_c; fac[kTile + tid] = f_b; fac[2 * kTile + tid] = f_v; }
@@ -320,50 +366,88 @@ void attn_tile_kernel(AttnStep s) {
     }
   }
 
-  int pc = 0, pt = 0;   // next tile to fetch
-  auto skip_empty = [&]() { while (pc < s.n_multi && pt * kTile >= s.chunk[pc].Sc) { ++pc; pt = 0; } };
-  skip_empty();
-  if (pc < s.n_multi) { fetch(pc, pt); ++pt; skip_empty(); }
+  bool fetched = false;                                         // a tile waits in registers
+  auto fetch_next = [&]() {
+    while (left <= 0 && pc < s.n_multi) {                       // into the next chunk that holds keys
+      if (++pc == s.n_multi) break;
+      const AttnStep::Chunk& ch = s.chunk[pc];
+      left = ch.Sc;
+      first_key = 0;
+      kb = (const KT*)ch.k + b * ch.ks0 + h * ch.ks1;
+      vb = (const KT*)ch.v + b * ch.ks0 + h * ch.ks1;
+    }
+    fetched = left > 0;
+    if (!fetched) return;
+    fetch();
+    left -= kTile;
+    first_key += kTile;
+    kb += kTile * s.ks[2];
+    vb += kTile * s.ks[2];
+  };
+  unsigned char* cur = smem;                                    // the tile computed on
+  unsigned char* oth = smem + (L::buffers - 1) * L::one;        // the other buffer, if there is one
+  fetch_next();
+  if (L::buffers == 2 && fetched) {
+    stage(cur);
+    fetch_next();
+    __syncthreads();
+  }
 
   for (int c = 0; c < s.n_multi; ++c) {
-    float m = -INFINITY, l = 0.0f;
+    float m = -INFINITY, l = 0.0f;                              // m: a reference that lags the maximum by at most 2^8
     f32x4 o[kDB];
 #pragma unroll
     for (int db = 0; db < kDB; ++db) o[db] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    for (int t = 0; t * kTile < s.chunk[c].Sc; ++t) {
-      __syncthreads();              // the previous tile (or the exchange) has been read
-      stage();
-      if (pc < s.n_multi) { fetch(pc, pt); ++pt; skip_empty(); }
-      __syncthreads();
+    const int len = s.chunk[c].Sc;
+    for (int t = 0; t * kTile < len; ++t) {
+      if (L::buffers == 1) {
+        __syncthreads();              // the previous tile (or the exchange) has been read
+        stage(cur);
+        fetch_next();
+        __syncthreads();
+      }
+      const float* fac = reinterpret_cast<const float*>(cur + L::fac);
       const int k0 = part * 16 * kMB;                            // first key of this wave
       f32x4 sc[kMB];
-      e.scores(k_lds + k0 * E::kPitchK, r, g, sc);
-      float p[kMB][4], tm = -INFINITY;
+      e.scores(cur + k0 * E::kPitchK, r, g, sc);
+      // exponents in log2 units are sc * f with f the uniform scale, or with FP8 K sc itself, scaled by key here
+      float tm = -INFINITY;
+      if (fp8) {
 #pragma unroll
-      for (int mb = 0; mb < kMB; ++mb) {
-        const f32x4 fc = *reinterpret_cast<const f32x4*>(fac + k0 + 16 * mb + 4 * g);
-        const f32x4 fb = *reinterpret_cast<const f32x4*>(fac + kTile + k0 + 16 * mb + 4 * g);
+        for (int mb = 0; mb < kMB; ++mb) sc[mb] *= *reinterpret_cast<const f32x4*>(fac + k0 + 16 * mb + 4 * g);
+      }
+      if (s.chunk[c].mask_src != nullptr || len - t * kTile < kTile) {   // (uniform) the tile may hold dead keys
+        asm volatile("" ::: "memory");                           // (kept a branch)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          p[mb][i] = fmaf(sc[mb][i], fc[i], fb[i]);
-          tm = fmaxf(tm, p[mb][i]);
+        for (int mb = 0; mb < kMB; ++mb) {
+          const f32x4 fb = *reinterpret_cast<const f32x4*>(fac + kTile + k0 + 16 * mb + 4 * g);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) sc[mb][i] = fb[i] == 0.0f ? sc[mb][i] : -INFINITY;
         }
       }
-      const float m_new = fmaxf(m, group_max(tm));
-      // no live key so far: every exponent is -inf and P = 0 against any finite reference
-      const float ref = m_new == -INFINITY ? 0.0f : m_new;
-      const float alpha = __builtin_amdgcn_exp2f(m - ref);       // m = -inf gives 0
-      float ps = 0.0f;
 #pragma unroll
       for (int mb = 0; mb < kMB; ++mb)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) { p[mb][i] = __builtin_amdgcn_exp2f(p[mb][i] - ref); ps += p[mb][i]; }
-      if (__builtin_amdgcn_ballot_w64(m_new != m) != 0ull) {
+        for (int i = 0; i < 4; ++i) tm = fmaxf(tm, sc[mb][i]);
+      tm = group_max(tm);
+      const float f = fp8 ? 1.0f : scale2;
+      if (!fp8) tm *= scale2;
+      const bool jump = tm > m + 8.0f;                           // m = -inf: the first live key
+      if (__builtin_amdgcn_ballot_w64(jump) != 0ull) {
+        const float alpha = jump ? __builtin_amdgcn_exp2f(m - tm) : 1.0f;
+        m = jump ? tm : m;
+        l *= alpha;
 #pragma unroll
         for (int db = 0; db < kDB; ++db) o[db] *= alpha;
       }
-      l = l * alpha + ps;
-      m = m_new;
+      // no live key so far: every exponent is -inf and P = 0 against any finite reference
+      const float ref = m == -INFINITY ? 0.0f : m;
+      float p[kMB][4], ps = 0.0f;
+#pragma unroll
+      for (int mb = 0; mb < kMB; ++mb)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) { p[mb][i] = __builtin_amdgcn_exp2f(fmaf(sc[mb][i], f, -ref)); ps += p[mb][i]; }
+      l += ps;
       if (fp8) {
 #pragma unroll
         for (int mb = 0; mb < kMB; ++mb) {
@@ -372,14 +456,22 @@ void attn_tile_kernel(AttnStep s) {
           for (int i = 0; i < 4; ++i) p[mb][i] *= fv[i];
         }
       }
-      e.pv(v_lds + k0 * E::kPitchV, d, r, g, p, o);
+      e.pv(cur + kTile * E::kPitchK + k0 * E::kPitchV, r, g, p, o);
+      if (L::buffers == 2) {
+        if (fetched) {
+          stage(oth);
+          fetch_next();
+        }
+        __syncthreads();
+        unsigned char* x = cur; cur = oth; oth = x;              // oth: the tile just computed on
+      }
     }
     l = group_sum(l);
 
     if (kKW > 1) {   // combine the waves that share these queries: [wave][slot][lane] in the tiles' place
       constexpr int kSlots = kD / 4 + 2;
-      float* x = reinterpret_cast<float*>(smem) + wave * kSlots * 64 + lane;
-      __syncthreads();
+      float* x = reinterpret_cast<float*>(oth) + wave * kSlots * 64 + lane;
+      if (L::buffers == 1) __syncthreads();
       if (part > 0) {
 #pragma unroll
         for (int db = 0; db < kDB; ++db)
@@ -404,6 +496,7 @@ void attn_tile_kernel(AttnStep s) {
           m = mm;
         }
       }
+      if (L::buffers == 2 && c + 1 < s.n_multi) __syncthreads();   // before the next chunk's tiles are staged over it
     }
     // the chunk's result and the merge of section 3.4
     float lse_r = -INFINITY, c_cur = 0.0f, w_prev = 0.0f;
@@ -444,14 +537,14 @@ void attn_tile_kernel(AttnStep s) {
   if (g == 0) s.lse[row] = lse_c;
 }
 
-template <template <int, int> class Engine, class Unit, int kD, int kKW>
+template <template <int, int, int> class Engine, class Unit, int kD, int kDB, int kKW>
 usp_status launch_tile(const AttnStep& s, hipStream_t st) {
-  typedef Engine<kD, 4 / kKW> E;
-  constexpr int lds = lds_bytes<E, kD, kKW>();
+  typedef Plan<Engine<kD, kDB, 4 / kKW>, kD, kKW> L;
+  constexpr int lds = L::buffers * L::one;
   constexpr int qpw = 64 / kKW;   // queries per work-group
-  if (lds > 64 * 1024) USP_CHECK_HIP((allow_large_lds<attn_tile_kernel<Engine, Unit, kD, kKW>>(lds)));
+  if (lds > 64 * 1024) USP_CHECK_HIP((allow_large_lds<attn_tile_kernel<Engine, Unit, kD, kDB, kKW>>(lds)));
   const dim3 grid((unsigned)((s.Sq + qpw - 1) / qpw + s.copy_wgs), (unsigned)s.H, (unsigned)s.B);
-  hipLaunchKernelGGL((attn_tile_kernel<Engine, Unit, kD, kKW>), grid, dim3(kThreads), lds, st, s);
+  hipLaunchKernelGGL((attn_tile_kernel<Engine, Unit, kD, kDB, kKW>), grid, dim3(kThreads), lds, st, s);
   USP_CHECK_HIP(hipGetLastError());
   return USP_OK;
 }
