@@ -285,18 +285,17 @@ __device__ __forceinline__ void lds_dma4(const void* gbase, uint32_t lane_off, u
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2"
                :: "s"(lds_base), "v"(lane_off), "s"(gbase) : "memory", "m0");
 }
-constexpr int kStagesWide = 3, kStagesSplit = 4;   // LDS tile buffers per tensor
+constexpr int kStages = 3, kStagesSplitK = 4;   // LDS tile buffers per tensor; of K in the key-split form
 constexpr int kExtTileB = kTile * 4;   // bytes of one tile's record: the factors of its 64 keys
 
-// LDS of a work-group: K stages | V stages | eight records | the words of kDead launches (245 000 keys).  The
+// LDS of a work-group: K stages | V stages | four records | the words of kDead launches (188 000 keys).  The
 // wide work-groups' epilogue stages each wave's O tile (eight regions from offset 0, over everything else,
 // which is dead by then).
-constexpr int kRecStages = 8;
-constexpr int kExtOff = 2 * kStagesSplit * kTileB;
-constexpr int kWordsOff = kExtOff + kRecStages * kExtTileB;
-constexpr int kLdsBytes = 159 * 1024;   // (__syncthreads_or of the one-launch form takes some LDS of its own)
+constexpr int kExtOff = (kStagesSplitK + kStages) * kTileB;
+constexpr int kWordsOff = kExtOff + 4 * kExtTileB;
+constexpr int kLdsBytes = 8 * kEpiWaveB;
 constexpr int kMaxWords = (kLdsBytes - kWordsOff) / 8;
-static_assert(kStagesSplit >= kStagesWide && kWordsOff % 8 == 0 && 8 * kEpiWaveB <= kLdsBytes, "LDS plan");
+static_assert(kWordsOff % 8 == 0 && kWordsOff < kLdsBytes && kLdsBytes <= 159 * 1024, "LDS plan");   // (some is left to __syncthreads_or)
 
 // LDS transposing read: the 16 lanes of a group each name 8 bytes; seen as a 4 x 16 matrix of
 // bf16 (row i = the data of lanes 4i..4i+3), lane j of the group receives column j.
@@ -355,7 +354,7 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
   constexpr int kKS = kHalfD ? 2 : 4;        // 32-wide slices of the head dimension (contraction of the scores)
   constexpr int kNV = kHalfD ? 2 : 4;        // operands of either kind per block of the matrix phase
   constexpr int kDB = kHalfD ? 4 : 8;        // 16-wide blocks of the head dimension that P.V produces
-  constexpr int kStages = kSplit ? kStagesSplit : kStagesWide;
+  constexpr int kStagesK = kSplit ? kStagesSplitK : kStages;
   constexpr int kBurst = 1;                  // operands whose MFMAs are issued back to back before the next reads (1, 2, 4: no difference measured)
   const int h = bh_ % s.H, b = bh_ / s.H;
   // split: waves w and w+4 share their 32 queries
@@ -490,7 +489,7 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
   const uint32_t vg0 = (dma_r0 - own_half) * rowB + vsw0, vg1 = (dma_r1 - own_half) * rowB + vsw1;
   const uint32_t lds_base = (uint32_t)(uintptr_t)smem_raw;
   const uint32_t lds_k = __builtin_amdgcn_readfirstlane(lds_base + 8 * wave * RB);
-  const uint32_t lds_v = __builtin_amdgcn_readfirstlane(lds_base + kStages * kTileB + 8 * wave * RB);
+  const uint32_t lds_v = __builtin_amdgcn_readfirstlane(lds_base + kStagesK * kTileB + 8 * wave * RB);
   // a tile of K or V: where it starts, and how many rows its chunk has from there on
   struct TileRef { const unsigned char* p; int left; };
   auto tile_desc = [&](TileRef t) -> u32x4 {
@@ -580,7 +579,7 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
   // Tiles needed before the first loads of the softmax phases land are fetched here.
   //   wide : A's SM(j) prefetches K(j+2) (with its record) and V(j+1); B's SM(j), one phase later,
   //          K(j+3) and V(j+2).
-  //   split: the softmax phase p prefetches K(p+4), V(p+2) and the record of tile p+4.
+  //   split: the softmax phase p prefetches K(p+3), V(p+1) and the record of tile p+2.
   int kpre_idx, vpre_idx;   // next K / V tile this wave prefetches
   if (!kSplit) {
     issue_k_tile(tile_at(0, false), 0);
@@ -596,19 +595,18 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
     kpre_idx = grpA ? 2 : 3;
     vpre_idx = grpA ? 1 : 2;
   } else {
-    // (a group moves whole tiles, its own rows and its partner waves'.)  What phases 0 and 1 read; group B
-    // loads the rest, V(1) and K(3), in phase 0, where it has nothing else to do
-    if (grpA) {
+    if (grpA) {   // (a group moves whole tiles, its own rows and its partner waves': one group suffices)
       issue_k_tile(tile_at(0, false), 0);
-      if (nt > 1) issue_k_tile(tile_at(1, false), 1);
       issue_v_tile(tile_at(0, true), 0);
-      if (kExt)
-        for (int i = 0; i < 4 && i < nt; ++i) issue_ext(i, i);
-    } else {
+      if (nt > 1) issue_k_tile(tile_at(1, false), 1);
       if (nt > 2) issue_k_tile(tile_at(2, false), 2);
+      if (kExt) {
+        issue_ext(0, 0);
+        if (nt > 1) issue_ext(1, 1);
+      }
     }
-    kpre_idx = grpA ? 4 : 5;   // K(p+4) / V(p+2) of this group's first softmax phase, p = 0 (A) or 1 (B)
-    vpre_idx = grpA ? 2 : 3;
+    kpre_idx = grpA ? 3 : 4;   // K(p+3) / V(p+1) of this group's first softmax phase, p = 0 (A) or 1 (B)
+    vpre_idx = grpA ? 1 : 2;
   }
   TileCursor kpre = place(kpre_idx, false), vpre = place(vpre_idx, true);
   constexpr int kPreStep = kSplit ? 2 : 1;   // tiles between two softmax phases of a wave
@@ -645,14 +643,14 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
         k_rd[ks] = (lds_cptr)(uintptr_t)(lds_base + r * RB + (((4 * ks + g) ^ r) << 4));
 #pragma unroll
       for (int db = 0; db < 8; ++db)
-        v_rd[db] = (lds_cptr)(uintptr_t)(lds_base + kStages * kTileB + vrow * RB + ((db ^ (vrow & 7)) << 5) + 8 * (r & 3));
+        v_rd[db] = (lds_cptr)(uintptr_t)(lds_base + kStagesK * kTileB + vrow * RB + ((db ^ (vrow & 7)) << 5) + 8 * (r & 3));
     } else {
 #pragma unroll
       for (int ks = 0; ks < 4; ++ks)
         k_rd[ks] = (lds_cptr)(uintptr_t)(lds_base + r * RB + ((((4 * ks + g) & 7) ^ ((r >> 1) & 7)) << 4));
 #pragma unroll
       for (int db = 0; db < 8; ++db)
-        v_rd[db] = (lds_cptr)(uintptr_t)(lds_base + kStages * kTileB + vrow * RB + (((db & 3) ^ ((vrow >> 1) & 3)) << 5) + 8 * (r & 3));
+        v_rd[db] = (lds_cptr)(uintptr_t)(lds_base + kStagesK * kTileB + vrow * RB + (((db & 3) ^ ((vrow >> 1) & 3)) << 5) + 8 * (r & 3));
     }
   }
   // kExt: this lane's keys of a tile are rows 16*mb + 4*g + (0..3), mb = 0..3
@@ -1043,54 +1041,44 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
     // scores of tile 0 (group A) / tile 1 (group B)
     if (grpA || nt > 1) first_scores(grpA ? 0 : 1);
     // Phases p = 0..nt, one work-group barrier each; both groups execute nt + 1 of them.
-    //   reads in phase p : V(p-1) and K(p+1) (stages mod 4), record p (mod 8)
-    //   batch of phase p : K(p+4) into the stage of K(p), last read in phase p-1,
-    //                      V(p+2) into the stage of V(p-2), last read in phase p-1,
-    //                      record p+4 into the stage of record p-4, last read in phase p-4
-    //   first read of it : phase p+3 (record: p+4).  Its issuers, in their softmax phase again in phase p+2,
-    //                      wait for it at that phase's end, with that phase's own batch still in flight.
-    // Three stages and a wait one phase earlier, as this kernel began, gave a load one to two phases of
-    // 0.75 us, less than the memory behind the L2 takes when the chip is full: a ring of four chunks of 1152 on
-    // 24 heads (216 work-groups) 78.8 -> 72 us, of eight chunks of 2112 on 12 heads (204) 269 -> 247 us.
-    auto end_phase = [&]() {
+    //   reads in phase p : V(p-1) from stage (p-1)%3, K(p+1) from stage (p+1)%4, record p from p%3
+    //   batch of phase p : K(p+3) -> stage (p+3)%4 (last read, as K(p-1), in phase p-2; a stage less, and the
+    //                      batch of phase 0 would land on K(0), which the first scores read without a
+    //                      barrier in between),
+    //                      V(p+1) -> stage (p+1)%3 (last read, as V(p-2), in phase p-1),
+    //                      record p+2 -> stage (p+2)%3 (last read, as record p-1, in phase p-1)
+    //   end of phase p   : the batch of phase p-1 must have landed (first read in phase p+1); its
+    //                      issuers are the group now ending a matrix phase, which waits for all of
+    //                      its loads; the other group has only this phase's batch in flight
+    // (A stage more for each tensor and loads a phase further ahead gained nothing and cost every launch 0.5 us:
+    // 4 heads of 768 17.8 -> 18.2 us, a ring of four chunks of 1152 on 24 heads 67.9 -> 68.2.)
+    auto end_phase = [&](bool wait_loads) {
       __builtin_amdgcn_sched_barrier(0);
+      if (wait_loads) __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
       __builtin_amdgcn_s_barrier();
       __builtin_amdgcn_sched_barrier(0);
     };
-    auto wait_but = [&](bool do_k, bool do_v, bool do_x) {   // all loads but those of the batch just issued
-      __builtin_amdgcn_sched_barrier(0);
-      if (do_k) {   // (and then V too)
-        if (kExt && do_x && (wave & 3) == 0) __builtin_amdgcn_s_waitcnt(kHalfD ? 0x0F75 : 0x0F79);   // vmcnt(5) / vmcnt(9)
-        else __builtin_amdgcn_s_waitcnt(kHalfD ? 0x0F74 : 0x0F78);                                   // vmcnt(4) / vmcnt(8)
-      } else if (do_v) __builtin_amdgcn_s_waitcnt(kHalfD ? 0x0F72 : 0x0F74);                         // vmcnt(2) / vmcnt(4)
-      else __builtin_amdgcn_s_waitcnt(0x0F70);
-    };
-    end_phase();                           // K(0) has been read by every wave before phase 0 loads over it
     int t = grpA ? 0 : 1;                  // this group's current tile; SM(t) runs in phase t
-    if (!grpA) {                           // phase 0: group B has no scores yet
-      if (nt > 1) issue_v_tile(tile_at(1, true), 1);
-      if (nt > 3) issue_k_tile(tile_at(3, false), 3);
-      end_phase();
-    }
+    int st = t;                            // t % 3
+    if (!grpA) end_phase(false);           // phase 0: group B has no scores yet
     while (t + 2 < nt) {
-      const bool do_k = t + 4 < nt;
-      SM(t & 7, t & 3, (t + 2) & 3, do_k, true, do_k, t + 4, (t + 4) & 7);   // phase t
-      wait_but(do_k, true, do_k);
-      end_phase();
-      MM_full(t & 3, (t + 2) & 3);                                           // phase t + 1
-      end_phase();
+      const int s1 = nxt(st), s2 = nxt(s1);                // (t + 1) % 3, (t + 2) % 3
+      SM(st, (t + 3) & 3, s1, t + 3 < nt, true, true, t + 2, s2);   // phase t (t + 1 < nt holds here)
+      end_phase(false);
+      MM_full(st, (t + 2) & 3);                            // phase t + 1
+      end_phase(true);
       t += 2;
+      st = s2;
     }
-    if (t < nt) {                                                            // this group's last tile
-      SM(t & 7, 0, 0, false, false, false, 0, 0);
-      wait_but(false, false, false);
-      end_phase();
-      MM_last(t & 3);
-      end_phase();
+    if (t < nt) {                                          // this group's last tile
+      SM(st, 0, nxt(st), false, t + 1 < nt, false, 0, 0);
+      end_phase(false);
+      MM_last(st);
+      end_phase(true);
       t += 2;
     }
     // the group whose last matrix phase was phase nt-1 sits out phase nt
-    if ((grpA && (nt % 2 == 0)) || (!grpA && (nt % 2 == 1))) end_phase();
+    if ((grpA && (nt % 2 == 0)) || (!grpA && (nt % 2 == 1))) end_phase(false);
   }
   }  // nt > 0
   // A wave that gave up waiting for a chunk loaded its rows of the tiles too early, and every wave of
