@@ -78,9 +78,10 @@ typedef enum {
                                      whole ring: without USP_ATTN_DOUBLE_BUFFER and USP_ATTN_UNFUSED_MERGE,
                                      bf16 or FP8 chunks (bf16 Q, d = 128 or 64), with or without key masks,
                                      whose lengths are multiples of 64 or 512 and more on average (2 to 16
-                                     of them non-empty) are otherwise taken as one stream of key tiles by a single launch (when the Q
-                                     shard's 256-query blocks fit one round of work-groups on the chip,
-                                     or the transfers are asked to ride inside the launch), the running
+                                     of them non-empty) are otherwise taken as one stream of key tiles by a
+                                     single launch (when the Q shard's 256-query blocks fit one round of
+                                     work-groups on the chip, or the chunks are bf16 and short, or the
+                                     transfers are asked to ride inside the launch), the running
                                      softmax state staying in registers from the first chunk to the last
                                      (no carried state in the workspace); FP8 chunks are decoded by
                                      work-groups of that launch as described under

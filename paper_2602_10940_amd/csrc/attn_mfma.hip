@@ -1315,6 +1315,26 @@ AttnForm attn_mfma_form(int B, int H, int Sq, int d, int64_t tiles) {
   return best;
 }
 
+// One launch over a ring of bf16 chunks, or one per chunk, where the Q shard's 256-query blocks need more than
+// one round of work-groups (up to one round the one launch is always the better).  In microseconds, a launch
+// per chunk takes 9 + 1.5 per tile and round, the last round counting 0.6 where the mixed launch can halve its
+// blocks, and the carried fp32 O goes out and back at 4.5 TB/s between two chunks; the one launch takes
+// 7 + tiles * t per round, t = 1.5 for 256-query work-groups, and for key-split ones 0.68 + 0.29 * the share of
+// the rounds that they fill (idle CUs let the others clock higher).  Measured, per chunk against one launch:
+// H = 24, Sq = 2816, four chunks of 1024 244 -> 183 us; H = 20, Sq = 3500, three of 2048 287 -> 259;
+// H = 24, two of 3000 265 and 265, two of 4096 358 against 386 (left per chunk).
+bool attn_mfma_ring_pays(int B, int H, int Sq, int d, int64_t tiles, int chunks) {
+  const int64_t items = (int64_t)B * H * ((Sq + kQPerWG - 1) / kQPerWG), halves = (int64_t)B * H * ((Sq + kQPerWGSplit - 1) / kQPerWGSplit);
+  if (items <= 256) return true;
+  const int64_t rem = items % 256, rounds128 = (halves + 255) / 256;
+  const double rounds = (double)(items / 256) + (rem == 0 ? 0.0 : d == kD && rem <= 128 ? 0.6 : 1.0);
+  const double carry = 2.0 * 4 * d * B * H * Sq / 4.5e6;
+  const double stepwise = chunks * 9.0 + rounds * tiles * 1.5 + (chunks - 1) * carry;
+  const double wide = (double)((items + 255) / 256) * (7.0 + tiles * 1.5);
+  const double split = rounds128 * (7.0 + tiles * (0.68 + 0.29 * halves / (256.0 * rounds128)));
+  return (wide < split ? wide : split) < 0.97 * stepwise;
+}
+
 usp_status launch_attn_mfma(const AttnStep& step, hipStream_t st) {
   AttnStep s = step;
   if (s.parts < 1) s.parts = 1;

@@ -72,6 +72,7 @@ struct Plan {
   AttnForm form = {0, 1};               // work decomposition of a launch that finishes the result (one launch, or one chunk)
   size_t off_parts = 0;                 // its parts: fp32 O~, then (m, l)
   size_t tiles = 0;                     // 64-key tiles of all chunks
+  int live = 0;                         // chunks that hold keys
   size_t total = 0;
 };
 
@@ -199,6 +200,7 @@ usp_status make_plan_of(const usp_attn_desc* d, bool least, Plan* p) {
   bool whole = true;
   size_t tiles = 0;
   p->one_launch = p->mfma && !p->unfused && !(d->flags & USP_ATTN_STEPWISE) && one_launch_lengths(d, least, &whole, &tiles);
+  for (int r = 0; r < p->W; ++r) p->live += d->chunk_len[r] > 0;
   p->tiles = p->W == 1 ? ((size_t)p->max_len + 63) / 64 : tiles;
   // Transfers inside a single launch over the whole ring (see usp_ring_attn_fwd): every chunk after
   // the first gets a staging buffer of its own, because a buffer that is reused inside one launch
@@ -522,11 +524,10 @@ usp_status usp::ring_attn_fwd_impl(const usp_attn_desc* desc, const void* q, con
 
   // One launch over the ring pays when a ring step is short (launch, pipeline fill and the carried
   // state's round trip weigh on it).  Where the Q shard's 256-query blocks need more than one round of
-  // work-groups on the 256 CUs, a step is long, its per-chunk launch can mix the two work
-  // decompositions to fill its last round, and the plain call keeps one launch per chunk; a call
-  // that asks for the transfers inside the launches takes the one launch at any size.
-  const int64_t q_blocks = (int64_t)desc->B * desc->H * ((desc->Sq + 255) / 256);
-  const bool short_steps = q_blocks <= 256 || p.fused_pf;
+  // work-groups on the 256 CUs, a launch per chunk can mix the two work decompositions to fill its last
+  // round, and bf16 chunks take the form that is expected to be faster; FP8 chunks keep one launch per chunk there
+  // (H = 24, Sq = 4096, two of 4096: 404 against 432 us).  A call that asks for the transfers inside the
+  // launches takes the one launch at any size.
   // Dead keys in more tiles than such a launch keeps words for: a launch per chunk.
   if (p.one_launch && (int64_t)p.tiles > attn_mfma_max_dead_tiles()) {
     for (int r = 0; r < p.W; ++r)
@@ -534,7 +535,8 @@ usp_status usp::ring_attn_fwd_impl(const usp_attn_desc* desc, const void* q, con
   }
   // bf16 chunks, merge fused: one launch over the whole ring.
   {
-    if (p.one_launch && !p.fp8 && (!p.dbuf || p.ring1) && short_steps) {
+    if (p.one_launch && !p.fp8 && (!p.dbuf || p.ring1) &&
+        (p.fused_pf || attn_mfma_ring_pays(desc->B, desc->H, desc->Sq, d, (int64_t)p.tiles, p.live))) {
       AttnStep a;
       memset(&a, 0, sizeof(a));
       a.B = desc->B; a.H = desc->H; a.d = d; a.Sq = desc->Sq;

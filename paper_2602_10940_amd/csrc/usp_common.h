@@ -165,6 +165,8 @@ bool attn_mfma_supported(const AttnStep& s);
 // How the matrix-core kernels run a launch that finishes its result: variant as AttnStep::variant, and parts
 struct AttnForm { int variant, parts; };
 AttnForm attn_mfma_form(int B, int H, int Sq, int d, int64_t tiles);
+// whether one launch over a ring of bf16 chunks is expected to beat one per chunk
+bool attn_mfma_ring_pays(int B, int H, int Sq, int d, int64_t tiles, int chunks);
 // tiles a launch over several chunks takes if some of its keys are dead (a mask, a ragged chunk)
 int64_t attn_mfma_max_dead_tiles();
 usp_status launch_attn_arrive_reset(int* arrive, hipStream_t st);

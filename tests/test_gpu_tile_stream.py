@@ -90,6 +90,17 @@ def test_dead_keys_and_parts(B, H, Sq, lens, d, fp8, mask):
             assert torch.equal(o, ref[0]) and torch.equal(l, ref[1])
 
 
+@pytest.mark.parametrize("d,Sq,lens", [(128, 1800, (64, 128, 64)), (128, 1700, (600, 500)), (64, 1800, (128, 64, 192))])
+def test_short_chunks_under_more_than_one_round_of_query_blocks(d, Sq, lens):
+    """40 heads with seven or eight 256-query blocks each: the plain call takes these rings as one launch."""
+    inp = W.make_attention_inputs(W.Workload("rounds", 3 + Sq, 1, 40, d, Sq, lens, "bf16"))
+    ro, rl = orc.ring_attention(inp.q, inp.k, inp.v, float(inp.softmax_scale))
+    o, l = _P().usp_ring_attn_fwd(dev_bf16(inp.q), [dev_bf16(x) for x in inp.k], [dev_bf16(x) for x in inp.v],
+                                  softmax_scale=float(inp.softmax_scale))
+    torch.cuda.synchronize()
+    _parity(o, l, ro, rl)
+
+
 def test_parts_need_no_more_workspace_than_there_is():
     """A workspace that holds a launch per chunk but not the parts is enough; one byte less is refused."""
     P = _P()
