@@ -52,7 +52,7 @@ typedef enum {
                                       work-groups of the attention launches on compute_stream;
                                       copy_stream is ignored.  Excludes USP_ATTN_DOUBLE_BUFFER.  Two forms:
                                       - one launch per chunk (always with USP_ATTN_STEPWISE or chunk lengths
-                                        that are no multiples of 64 and below 512 on average): step
+                                        that are no multiples of 64 and, bf16, below 320 on average): step
                                         r's launch carries the transfer of chunk r+1 into the idle one
                                         of two internal buffers, in work-groups that occupy the CUs the
                                         attention grid leaves free.  Same buffers and results as
@@ -76,8 +76,8 @@ typedef enum {
                                      64-key tiles and combine their partial results at the end */
 #define USP_ATTN_STEPWISE 64u     /* one attention launch per chunk even where one launch could cover the
                                      whole ring: without USP_ATTN_DOUBLE_BUFFER and USP_ATTN_UNFUSED_MERGE,
-                                     bf16 or FP8 chunks (bf16 Q, d = 128 or 64), with or without key masks,
-                                     whose lengths are multiples of 64 or 512 and more on average (2 to 16
+                                     bf16 or FP8 chunks (bf16 Q, d = 128 or 64), with or without key masks
+                                     (bf16: of lengths that are multiples of 64 or average 320 and more; 2 to 16
                                      of them non-empty) are otherwise taken as one stream of key tiles by a
                                      single launch (when the Q shard's 256-query blocks fit one round of
                                      work-groups on the chip, or the chunks are bf16 and short, or the

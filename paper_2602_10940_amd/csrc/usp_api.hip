@@ -90,12 +90,12 @@ bool o_dense(const usp_attn_desc* d) {
 }
 
 // Chunk lengths that one launch over the ring takes: 2 to 16 non-empty chunks, whole tiles, or (unless
-// `least`) any lengths of at least kRaggedRing keys on average.  A ring of ragged chunks as one launch saves
-// per chunk a launch gap, a pipeline fill and the carried state's round trip (12 heads, two chunks of 2215:
-// 98 -> 78 us).  Shorter ragged rings keep their launch per chunk, and with it the bits that
-// USP_ATTN_DOUBLE_BUFFER gives for the same ring; from there on the two agree up to rounding order, as
-// they do on whole tiles.
-constexpr int kRaggedRing = 512;
+// `least`) ragged ones: FP8 chunks of any lengths, bf16 chunks of at least kRaggedRing keys on average.  A ring
+// of ragged chunks as one launch saves per chunk a launch gap, a pipeline fill and the carried state's round
+// trip (12 heads, two chunks of 2215 98 -> 70 us; FP8, 8 heads with 70 queries, two of 70 33.9 -> 21.3).
+// Shorter ragged bf16 rings keep their launch per chunk, and with it the bits that USP_ATTN_DOUBLE_BUFFER
+// gives for the same ring; from there on the two agree up to rounding order, as they do on whole tiles.
+constexpr int kRaggedRing = 320;
 bool one_launch_lengths(const usp_attn_desc* d, bool least, bool* whole, size_t* tiles) {
   int live = 0;
   int64_t keys = 0;
@@ -110,7 +110,7 @@ bool one_launch_lengths(const usp_attn_desc* d, bool least, bool* whole, size_t*
     ++live;
   }
   if (live < 2 || live > AttnStep::kMaxMulti) return false;
-  return *whole || (!least && keys >= (int64_t)live * kRaggedRing);
+  return *whole || (!least && (d->kv_dtype == USP_FP8_E4M3FN || keys >= (int64_t)live * kRaggedRing));
 }
 
 // `least`: the plan that needs no more workspace than a launch per chunk, or one launch over whole tiles,

@@ -52,7 +52,7 @@ def _masks(rng, B, lens, kind):
 
 # (B, H, Sq, lens): ragged rings in one launch (513 = one row in the last tile, 575 = one missing), one chunk
 # shorter than a tile, keys shared by 2 and more work-groups, more parts than live tiles
-SHAPES = [(1, 6, 300, (513, 575, 640)), (2, 3, 129, (700, 0, 525)), (1, 4, 40, (37,)), (2, 2, 200, (1100,)),
+SHAPES = [(1, 6, 300, (513, 575, 640)), (2, 2, 70, (70, 0, 69, 5)), (2, 3, 129, (700, 0, 525)), (1, 4, 40, (37,)), (2, 2, 200, (1100,)),
           (1, 1, 64, (4608,)), (1, 2, 130, (2049, 1023)), (2, 1, 257, (1024, 1024))]
 
 
