@@ -232,7 +232,7 @@ __device__ __forceinline__ void finish_and_store(const AttnStep& s, f32x4 (&oacc
 //           LDS at the end.  Twice the work-groups for half the time each: for Q shards too
 //           small to fill the chip with 256-query work-groups.
 //             phase p : the owner of tile p does SM(p), the other group MM(p-1)
-// K and V tiles go through three LDS stages each, written by direct global->LDS loads issued
+// K and V tiles go through three LDS stages each (K four in the split form), written by direct global->LDS loads issued
 // from the softmax phases (whose critical resource, the VALU, is not the matrix core's).
 //
 // Template parameter kExt: per-key scales of FP8 K (Algorithm 1, line 4, applied to the fp32 scores instead
