@@ -1296,18 +1296,43 @@ int64_t attn_mfma_max_dead_tiles() { return kMaxWords; }
 // more; parts add 6 for the second launch and what the parts' bytes, written and read, take at 5.5 TB/s.
 // Taken when that comes out at least 3 us lower.  Measured, 1 against the chosen number of parts: H = 3, Sq = 4608,
 // 4608 keys 57 -> 43 us; H = 1, Sq = 256, 4608 keys 57 -> 21 us; H = 4, Sq = 1024, 1024 keys 20.6 us with 1, 2 or 4.
+// One chunk of 500 to 2600 keys, d = 64 or 128, bf16 or FP8, 35 random shapes that take parts: 0.54 to 0.97 of the time.
 // At most 240 work-groups, so that the copy work-groups of the same launch (16 at least) find a CU.
-AttnForm attn_mfma_form(int B, int H, int Sq, int d, int64_t tiles) {
-  const int64_t wgs = 8 * (((int64_t)B * H * ((Sq + kQPerWGSplit - 1) / kQPerWGSplit) + 7) / 8);
+//
+// A ring's chunks arrive inside the launch (FP8 chunks always; bf16 ones with USP_ATTN_FUSED_PREFETCH, and the plain
+// call takes the same form, so that the two give the same bits): the last one 11 us after the start, plus 4 (FP8: 7)
+// for each that its group of copy work-groups has to bring one after another, and the bytes moved at 50 GB/s per
+// copy work-group, of which parts leave fewer.  A work-group ends no earlier than its share of that chunk's
+// tiles takes from there on, nor than all its tiles take from the arrival of the chunk it begins with, and it
+// spends 1 us (FP8: 2) on each chunk it enters.  With the tile times of each form this predicts 440 measured
+// launches within 7 % rms; parts have to gain 15 % there.  By the rule for one chunk alone short chunks
+// under few queries lost: B = 2, H = 12, Sq = 150, FP8, eight of 320 keys 72 us with 1 part, 103 with 5; B = 2, H = 3,
+// d = 64, Sq = 379, six of 320 34 us with 1, 50 with 10.  Long ones gain: H = 2, Sq = 108, six of 2816 202 us
+// with 1, 59 with 16.
+AttnForm attn_mfma_form(int B, int H, int Sq, int d, int64_t tiles, const RingTransfers* ring) {
+  const int64_t blocks = (int64_t)B * H * ((Sq + kQPerWGSplit - 1) / kQPerWGSplit), wgs = 8 * ((blocks + 7) / 8);
   AttnForm best = {0, 1};
   if (wgs > 120) return best;
+  const double tile = !ring ? 0.75 : d == kD ? (ring->fp8 ? 0.82 : 0.75) : (ring->fp8 ? 0.65 : 0.58);
   auto cost = [&](int parts) {
     const double n = (double)wgs * parts;
-    const double t = 0.75 + 0.17 * (n <= 128 ? 0.0 : n >= 216 ? 1.0 : (n - 128) / 88);
-    const double bytes = parts > 1 ? 2.0 * 4 * d * parts * B * H * Sq : 0.0;
-    return 7.5 + (double)((tiles + parts - 1) / parts) * t + (parts > 1 ? 6.0 + bytes / 5.5e6 : 0.0);
+    const double t = tile * (1.0 + 0.17 / 0.75 * (n <= 128 ? 0.0 : n >= 216 ? 1.0 : (n - 128) / 88));
+    const double combine = parts > 1 ? 6.0 + 2.0 * 4 * d * parts * B * H * Sq / 5.5e6 : 0.0;
+    const int64_t mine = (tiles + parts - 1) / parts;
+    const double work = (double)mine * t;
+    if (!ring) return 7.5 + work + combine;
+    const int copy_wgs = copy_wgs_beside((int)(8 * ((blocks * parts + 7) / 8)));
+    const int later = ring->chunks - 1, groups = copy_groups_of(copy_wgs, later, ring->largest);
+    const double chain = (later + groups - 1) / groups * (ring->fp8 ? 7.0 : 4.0) + (double)ring->bytes / (copy_wgs * 50e3);
+    const double share = (double)mine / (double)tiles, enters = share * later + 1.0 < later ? share * later + 1.0 : later;
+    const double busy = 8.5 + work + enters * (ring->fp8 ? 2.0 : 1.0);
+    const double from_first = 11.0 + chain * (1.0 - share) + work;
+    const double from_last = 11.0 + chain + (double)(mine < ring->last_tiles ? mine : ring->last_tiles) * t;
+    const double waited = from_last > from_first ? from_last : from_first;
+    return (busy > waited ? busy : waited) + (parts > 1 ? combine + 1.0 : 0.0);
   };
-  double least = cost(1) - 3.0;
+  const double one = cost(1);
+  double least = !ring ? one - 3.0 : 0.96 * one;
   for (int parts = 2; parts <= 16 && parts * wgs <= 240 && parts <= tiles; ++parts) {
     const double c = cost(parts);
     if (c < least) { least = c; best = {2, parts}; }
@@ -1377,10 +1402,11 @@ usp_status launch_attn_mfma(const AttnStep& step, hipStream_t st) {
           set_error("transfers inside a launch over several chunks need 16-byte aligned sources and buffers");
           return USP_ERR_INVALID_ARG;
         }
-      s.n_copy = 1;                                    // (only asks prefetch_wg_count for a count)
-      s.copy_wgs = prefetch_wg_count(s, (int)wgs, 1);
-      s.n_copy = 0;
-      s.arrive_need = s.copy_wgs + (s.arrive_need_extra > 0 ? s.arrive_need_extra : 0);
+      s.copy_wgs = copy_wgs_beside((int)wgs);
+      int64_t largest = 0;
+      for (int c = 1; c < s.n_multi; ++c) largest = s.chunk[c].bytes > largest ? s.chunk[c].bytes : largest;
+      s.copy_groups = copy_groups_of(s.copy_wgs, s.n_multi - 1, largest * (s.multi_fp8 ? 6 : 4));   // K and V, codes or bf16 read, bf16 written
+      s.arrive_need = s.copy_wgs / s.copy_groups + (s.arrive_need_extra > 0 ? s.arrive_need_extra : 0);
       if (s.arrive_polls <= 0 || s.arrive_polls > kArrivePolls) s.arrive_polls = kArrivePolls;
     }
     const usp_status r = launch_pp_any<true>(s, s.multi_fp8 != 0, dead, split, wgs, st);
@@ -1411,12 +1437,12 @@ usp_status launch_attn_mfma(const AttnStep& step, hipStream_t st) {
     s.mix_halves = (mix_blocks + kXcds - 1) / kXcds;
     const int per = (items + kXcds - 1) / kXcds;
     const unsigned wgs_mixed = (unsigned)(kXcds * (per + s.mix_halves));
-    s.copy_wgs = prefetch_wg_count(s, (int)wgs_mixed, 1);
+    s.copy_wgs = prefetch_wg_count(s, (int)wgs_mixed);
     if (ext) return dead ? launch_mixed<true, true>(s, wgs_mixed, st) : launch_mixed<true, false>(s, wgs_mixed, st);
     return dead ? launch_mixed<false, true>(s, wgs_mixed, st) : launch_mixed<false, false>(s, wgs_mixed, st);
   }
   const unsigned wgs = split ? wg_grid_size((s.Sq + kQPerWGSplit - 1) / kQPerWGSplit, s.B * s.H * s.parts) : wgs256;
-  s.copy_wgs = prefetch_wg_count(s, (int)wgs, 1);
+  s.copy_wgs = prefetch_wg_count(s, (int)wgs);
   const usp_status r = launch_pp_any<false>(s, ext, dead, split, wgs, st);
   return r == USP_OK && s.parts > 1 ? launch_combine(s, st) : r;
 }

@@ -46,10 +46,11 @@ __device__ __forceinline__ void prefetch_copy(const AttnStep& s, int wg, int tid
 }
 
 // The transfers of a whole ring inside one launch: work-group wg of s.copy_wgs copies its share of
-// chunk c = 1, 2, .. and then counts itself on s.arrive[c].  The stores carry device scope (they are
-// written through to where every XCD's loads find them; a fence would write back and invalidate the
-// whole L2 under the attention work-groups), each thread waits until its own stores have been
-// acknowledged, the work-group barrier collects the threads, and one thread publishes the count.
+// chunk c = 1, 2, .. (of its group's chunks, see copy_groups_of) and then counts itself on s.arrive[c].
+// The stores carry device scope (they are written through to where every XCD's loads find them; a fence
+// would write back and invalidate the whole L2 under the attention work-groups), each thread waits until
+// its own stores have been acknowledged, the work-group barrier collects the threads, and one thread
+// publishes the count.
 // The readers make no acquire of their own either: nothing reads a staging buffer or its records
 // before their chunk's count is complete, and the launch starts with invalid caches, so no cache on
 // the reading side can hold an older copy of those lines.
@@ -135,15 +136,17 @@ __device__ __forceinline__ void fp8_chunk_prepare(const AttnStep& s, int c, int6
 }
 // The copy work-groups of a launch over several FP8 chunks: chunk 1, 2, .. decoded and counted.
 __device__ __forceinline__ void stream_chunks_fp8(const AttnStep& s, int wg, int tid, int nthr) {
-  for (int c = 1; c < s.n_multi; ++c) {
-    fp8_chunk_prepare<true>(s, c, (int64_t)wg * nthr + tid, (int64_t)s.copy_wgs * nthr);
+  const int groups = s.copy_groups;
+  for (int c = 1 + wg % groups; c < s.n_multi; c += groups) {
+    fp8_chunk_prepare<true>(s, c, (int64_t)(wg / groups) * nthr + tid, (int64_t)(s.copy_wgs / groups) * nthr);
     publish_chunk(s.arrive + c, tid);
   }
 }
 __device__ __forceinline__ void stream_chunks(const AttnStep& s, int wg, int tid, int nthr) {
-  const int64_t stride = (int64_t)s.copy_wgs * nthr;
-  const int64_t first = (int64_t)wg * nthr + tid;
-  for (int c = 1; c < s.n_multi; ++c) {
+  const int groups = s.copy_groups;
+  const int64_t stride = (int64_t)(s.copy_wgs / groups) * nthr;
+  const int64_t first = (int64_t)(wg / groups) * nthr + tid;
+  for (int c = 1 + wg % groups; c < s.n_multi; c += groups) {
     const int64_t n = s.chunk[c].bytes >> 4;           // the host passes 16-byte multiples, 16-byte aligned
     for (int t = 0; t < 2; ++t) {
       const uint4* s4 = (const uint4*)(t ? s.chunk[c].v_src : s.chunk[c].k_src);

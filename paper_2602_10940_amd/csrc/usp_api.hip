@@ -64,6 +64,7 @@ struct Plan {
   size_t off_deq_k = 0, off_deq_v = 0;  // bf16 K/V after dequantisation (FP8 + MFMA kernel)
   size_t off_ext = 0;                   // per-tile key records of an FP8 chunk (MFMA kernel)
   bool one_launch = false;              // chunk lengths and flags that one launch over the ring takes
+  bool whole = true;                    // of a ring: every chunk is a number of whole 64-key tiles
   bool ring1 = false;                   // fused prefetch as one launch over the whole ring: a staging buffer per chunk
   size_t off_ring1 = 0, off_arrive = 0; // K | V of chunk 1, K | V of chunk 2, ... (dense, 256-byte aligned each); arrival counters
   bool ring8 = false;                   // FP8 chunks decoded inside one launch over the whole ring
@@ -197,9 +198,8 @@ usp_status make_plan_of(const usp_attn_desc* d, bool least, Plan* p) {
   }
   p->off_stepwise_end = off;
   const int64_t q_blocks = (int64_t)d->B * d->H * ((d->Sq + 255) / 256);
-  bool whole = true;
   size_t tiles = 0;
-  p->one_launch = p->mfma && !p->unfused && !(d->flags & USP_ATTN_STEPWISE) && one_launch_lengths(d, least, &whole, &tiles);
+  p->one_launch = p->mfma && !p->unfused && !(d->flags & USP_ATTN_STEPWISE) && one_launch_lengths(d, least, &p->whole, &tiles);
   for (int r = 0; r < p->W; ++r) p->live += d->chunk_len[r] > 0;
   p->tiles = p->W == 1 ? ((size_t)p->max_len + 63) / 64 : tiles;
   // Transfers inside a single launch over the whole ring (see usp_ring_attn_fwd): every chunk after
@@ -223,11 +223,24 @@ usp_status make_plan_of(const usp_attn_desc* d, bool least, Plan* p) {
     p->off_arrive = off; off += align_up(AttnStep::kMaxMulti * sizeof(int));
   }
   // (kept in the size query's answers: what key masks of a one-launch ring over bf16 chunks took)
-  if (p->one_launch && whole && !p->fp8 && (!p->dbuf || p->ring1)) off += align_up((size_t)d->B * d->H * tiles * 1024);
+  if (p->one_launch && p->whole && !p->fp8 && (!p->dbuf || p->ring1)) off += align_up((size_t)d->B * d->H * tiles * 1024);
   const size_t stepwise = p->off_stepwise_end;
   if (p->mfma && !least && !(d->flags & (USP_ATTN_KERNEL_WIDE | USP_ATTN_KERNEL_SPLIT | USP_ATTN_KERNEL_MIXED)) &&
       (p->W == 1 || (p->one_launch && (p->fp8 ? p->ring8 : (!p->dbuf || p->ring1) && (p->fused_pf || q_blocks <= 256))))) {
-    p->form = attn_mfma_form(d->B, d->H, d->Sq, d->d, (int64_t)p->tiles);
+    RingTransfers ring = {p->live, 0, 0, 0, p->fp8};
+    bool later = false;                                   // (the first chunk that holds keys is not moved)
+    for (int r = 0; r < p->W; ++r) {
+      const int len = d->chunk_len[r];
+      if (len == 0) continue;
+      const int64_t moved = (int64_t)d->B * d->H * len * d->d * (p->fp8 ? 6 : 8);   // both tensors, codes or bf16 read, bf16 written
+      if (later) {
+        ring.bytes += moved;
+        if (moved > ring.largest) ring.largest = moved;
+      }
+      later = true;
+      ring.last_tiles = ((int64_t)len + 63) / 64;
+    }
+    p->form = attn_mfma_form(d->B, d->H, d->Sq, d->d, (int64_t)p->tiles, p->W > 1 ? &ring : nullptr);
     if (p->form.parts > 1) {
       // in the place of what only a launch per chunk uses, where that is enough or nothing else lies behind it
       const size_t need = align_up((size_t)p->form.parts * p->rows_q * d->d * 4) + align_up((size_t)p->form.parts * p->rows_q * 8);
@@ -253,6 +266,18 @@ usp_status make_plan(const usp_attn_desc* d, Plan* p) {
   Plan least;
   if ((st = make_plan_of(d, true, &least)) == USP_OK && least.total <= (size_t)USP_NOALLOC_SCRATCH_BYTES) *p = least;
   return st;
+}
+
+// How a call's chunks are launched (the comments stand in ring_attn_fwd_impl).  `masked`: some chunk that holds
+// keys has a key mask.
+enum class Way { per_chunk, ring, ring_fp8, general };
+Way way_of(const usp_attn_desc* d, const Plan& p, bool masked) {
+  if (!p.mfma)
+    return p.W > 1 && p.W <= AttnStep::kMaxMulti && !p.dbuf && !p.unfused && !(d->flags & USP_ATTN_STEPWISE) ? Way::general : Way::per_chunk;
+  if (!p.one_launch || ((masked || !p.whole) && (int64_t)p.tiles > attn_mfma_max_dead_tiles())) return Way::per_chunk;
+  if (p.fp8) return p.ring8 ? Way::ring_fp8 : Way::per_chunk;
+  if (p.dbuf && !p.ring1) return Way::per_chunk;
+  return p.fused_pf || attn_mfma_ring_pays(d->B, d->H, d->Sq, d->d, (int64_t)p.tiles, p.live) ? Way::ring : Way::per_chunk;
 }
 
 }  // namespace
@@ -434,6 +459,16 @@ usp_status usp_ring_attn_fwd(const usp_attn_desc* desc, const void* q, const voi
 
 }  // extern "C"
 
+usp_status usp::attn_route(const usp_attn_desc* desc, bool masked, AttnRoute* route) {
+  Plan p;
+  const usp_status st = make_plan(desc, &p);
+  if (st != USP_OK) return st;
+  const Way way = way_of(desc, p, masked);
+  const bool finishes = p.mfma && (way != Way::per_chunk || p.W == 1);
+  *route = {way != Way::per_chunk, finishes ? p.form.parts : 1};
+  return USP_OK;
+}
+
 usp_status usp::ring_attn_fwd_impl(const usp_attn_desc* desc, const void* q, const void* const* k_chunks,
                                    const void* const* v_chunks, const float* const* k_scales,
                                    const float* const* v_scales, const uint8_t* const* key_mask, void* out,
@@ -529,54 +564,50 @@ usp_status usp::ring_attn_fwd_impl(const usp_attn_desc* desc, const void* q, con
   // (H = 24, Sq = 4096, two of 4096: 404 against 432 us).  A call that asks for the transfers inside the
   // launches takes the one launch at any size.
   // Dead keys in more tiles than such a launch keeps words for: a launch per chunk.
-  if (p.one_launch && (int64_t)p.tiles > attn_mfma_max_dead_tiles()) {
-    for (int r = 0; r < p.W; ++r)
-      if (desc->chunk_len[r] % 64 != 0 || (key_mask && key_mask[r] && desc->chunk_len[r] > 0)) p.one_launch = p.ring8 = false;
-  }
+  bool masked = false;
+  for (int r = 0; r < p.W; ++r) masked |= key_mask && key_mask[r] && desc->chunk_len[r] > 0;
+  const Way way = way_of(desc, p, masked);
   // bf16 chunks, merge fused: one launch over the whole ring.
-  {
-    if (p.one_launch && !p.fp8 && (!p.dbuf || p.ring1) &&
-        (p.fused_pf || attn_mfma_ring_pays(desc->B, desc->H, desc->Sq, d, (int64_t)p.tiles, p.live))) {
-      AttnStep a;
-      memset(&a, 0, sizeof(a));
-      a.B = desc->B; a.H = desc->H; a.d = d; a.Sq = desc->Sq;
-      a.qo_dtype = desc->qo_dtype; a.half_d = d == 64 ? 1 : 0; a.kv_dtype = desc->kv_dtype;
-      a.q = q; a.out = out; a.lse = lse; a.scale = scale; a.mode = 0;
-      for (int i = 0; i < 3; ++i) { a.qs[i] = desc->q_stride[i]; a.ks[i] = desc->kv_stride[i]; a.os[i] = desc->o_stride[i]; }
-      if (kv_auto(desc)) a.ks[2] = d;
-      a.variant = (desc->flags & USP_ATTN_KERNEL_SPLIT) ? 2 : (desc->flags & USP_ATTN_KERNEL_WIDE) ? 1 : 0;
-      const bool transfers = p.dbuf;                      // (ring1) Algorithm 2 inside the launch
-      if (transfers) a.ks[2] = d;                         // the double-buffered modes take dense chunks only
-      size_t stage = p.off_ring1;
-      for (int r = 0; r < p.W; ++r) {
-        const int len = desc->chunk_len[r];
-        const size_t bytes = (size_t)desc->B * desc->H * len * d * 2;
-        if (len > 0) {
-          AttnStep::Chunk& c = a.chunk[a.n_multi++];
-          c.k = k_chunks[r]; c.v = v_chunks[r]; c.Sc = len;
-          c.ks0 = kv_auto(desc) || transfers ? (int64_t)desc->H * len * d : desc->kv_stride[0];
-          c.ks1 = kv_auto(desc) || transfers ? (int64_t)len * d : desc->kv_stride[1];
-          if (transfers && a.n_multi > 1) {               // every live chunk but the first arrives through its buffer
-            c.k_src = k_chunks[r]; c.v_src = v_chunks[r]; c.bytes = (int64_t)bytes;
-            c.k = ws + stage; c.v = ws + stage + align_up(bytes);
-          }
-          c.mask_src = key_mask ? key_mask[r] : nullptr;
+  if (way == Way::ring) {
+    AttnStep a;
+    memset(&a, 0, sizeof(a));
+    a.B = desc->B; a.H = desc->H; a.d = d; a.Sq = desc->Sq;
+    a.qo_dtype = desc->qo_dtype; a.half_d = d == 64 ? 1 : 0; a.kv_dtype = desc->kv_dtype;
+    a.q = q; a.out = out; a.lse = lse; a.scale = scale; a.mode = 0;
+    for (int i = 0; i < 3; ++i) { a.qs[i] = desc->q_stride[i]; a.ks[i] = desc->kv_stride[i]; a.os[i] = desc->o_stride[i]; }
+    if (kv_auto(desc)) a.ks[2] = d;
+    a.variant = (desc->flags & USP_ATTN_KERNEL_SPLIT) ? 2 : (desc->flags & USP_ATTN_KERNEL_WIDE) ? 1 : 0;
+    const bool transfers = p.dbuf;                      // (ring1) Algorithm 2 inside the launch
+    if (transfers) a.ks[2] = d;                         // the double-buffered modes take dense chunks only
+    size_t stage = p.off_ring1;
+    for (int r = 0; r < p.W; ++r) {
+      const int len = desc->chunk_len[r];
+      const size_t bytes = (size_t)desc->B * desc->H * len * d * 2;
+      if (len > 0) {
+        AttnStep::Chunk& c = a.chunk[a.n_multi++];
+        c.k = k_chunks[r]; c.v = v_chunks[r]; c.Sc = len;
+        c.ks0 = kv_auto(desc) || transfers ? (int64_t)desc->H * len * d : desc->kv_stride[0];
+        c.ks1 = kv_auto(desc) || transfers ? (int64_t)len * d : desc->kv_stride[1];
+        if (transfers && a.n_multi > 1) {               // every live chunk but the first arrives through its buffer
+          c.k_src = k_chunks[r]; c.v_src = v_chunks[r]; c.bytes = (int64_t)bytes;
+          c.k = ws + stage; c.v = ws + stage + align_up(bytes);
         }
-        if (r >= 1) stage += 2 * align_up(bytes);
+        c.mask_src = key_mask ? key_mask[r] : nullptr;
       }
-      if (transfers) {
-        a.arrive = (int*)(ws + p.off_arrive);
-        a.arrive_need_extra = opt.arrive_need_extra; a.arrive_polls = opt.arrive_polls;
-        if ((st = launch_attn_arrive_reset(a.arrive, cs)) != USP_OK) return st;
-      }
-      set_form(&a);
-      return launch_attn_mfma(a, cs);
+      if (r >= 1) stage += 2 * align_up(bytes);
     }
+    if (transfers) {
+      a.arrive = (int*)(ws + p.off_arrive);
+      a.arrive_need_extra = opt.arrive_need_extra; a.arrive_polls = opt.arrive_polls;
+      if ((st = launch_attn_arrive_reset(a.arrive, cs)) != USP_OK) return st;
+    }
+    set_form(&a);
+    return launch_attn_mfma(a, cs);
   }
 
   // Shapes of the general kernel, every chunk at hand: one launch, the chunks merged one after another in
   // registers with the operations of a launch per chunk (same bits): one launch gap and one round trip of the carried state less per chunk
-  if (!p.mfma && p.W > 1 && p.W <= AttnStep::kMaxMulti && !p.dbuf && !p.unfused && !(desc->flags & USP_ATTN_STEPWISE)) {
+  if (way == Way::general) {
     AttnStep a;
     memset(&a, 0, sizeof(a));
     a.B = desc->B; a.H = desc->H; a.d = d; a.Sq = desc->Sq;
@@ -600,9 +631,9 @@ usp_status usp::ring_attn_fwd_impl(const usp_attn_desc* desc, const void* q, con
   // FP8 chunks: one launch over the ring that decodes them as it goes.  (Scales and masks at odd addresses
   // keep a launch per chunk and its order of operations.)
   bool aligned = true;
-  for (int r = 0; p.ring8 && r < p.W; ++r)
+  for (int r = 0; way == Way::ring_fp8 && r < p.W; ++r)
     if (desc->chunk_len[r] > 0 && (!aligned16(k_scales[r]) || (key_mask && ((uintptr_t)key_mask[r] & 3) != 0))) aligned = false;
-  if (p.ring8 && aligned) {
+  if (way == Way::ring_fp8 && aligned) {
     AttnStep a;
     memset(&a, 0, sizeof(a));
     a.B = desc->B; a.H = desc->H; a.d = d; a.Sq = desc->Sq;

@@ -112,10 +112,11 @@ struct AttnStep {
   //
   // With `arrive` set the launch also plays the ring's transfers (Algorithm 2 inside one launch): its
   // first copy_wgs work-groups copy chunk c = 1, 2, .. from k_src / v_src (bytes each) into k / v, a
-  // staging buffer of its own per chunk, and count themselves on arrive[c] when their share of chunk
-  // c is visible device-wide; an attention work-group waits for arrive[c] == copy_wgs before it
-  // loads the first tile of chunk c.  Dependencies only point from the attention work-groups to the
-  // copy work-groups, which are dispatched first and wait for nothing.
+  // staging buffer of its own per chunk (each of copy_groups groups its own chunks), and count themselves on
+  // arrive[c] when their share of chunk c is visible device-wide; an attention work-group waits for
+  // arrive[c] == copy_wgs / copy_groups before it loads the first tile of chunk c.  Dependencies only
+  // point from the attention work-groups to the copy work-groups, which are dispatched first and wait
+  // for nothing.
   //
   // multi_fp8: the sources are FP8 E4M3 chunks ([B,H,Sc,128] codes at k_src / v_src, per-(head, token)
   // scales at k_scale_src / v_scale_src; Algorithm 1 line 4 on arrival).  A copy work-group then
@@ -133,8 +134,9 @@ struct AttnStep {
   int n_multi;
   int multi_fp8;
   int* arrive;               // [kMaxMulti] counters, zero when the launch starts; or null
+  int copy_groups;           // the copy work-groups fall into this many groups (copy_groups_of, set by the launcher)
   // what an attention work-group waits for on arrive[c], and for how long: the launcher sets the
-  // count to copy_wgs plus arrive_need_extra and the poll limit to its default when arrive_polls is
+  // count to copy_wgs / copy_groups plus arrive_need_extra and the poll limit to its default when arrive_polls is
   // 0.  Both exist so that a host-side test can make the bounded wait give up (a count that is never
   // reached, a short limit) with every kernel still running to its end.
   int arrive_need_extra;
@@ -150,21 +152,32 @@ struct AttnStep {
   CopySeg copy[4];
 };
 static_assert(sizeof(AttnStep) <= 4096, "AttnStep is passed by value as the kernels' only argument");
-// Copy work-groups appended to a launch of attn_wgs attention work-groups, slots_per_cu of which
-// fit on a CU: the CU slots the attention grid leaves free, as a multiple of 8 in [16, 64]
-// (one work-group moves about 50 GB/s).
-inline int prefetch_wg_count(const AttnStep& s, int attn_wgs, int slots_per_cu) {
-  if (s.n_copy <= 0) return 0;
-  const int spare = 256 * slots_per_cu - attn_wgs % (256 * slots_per_cu);
-  const int n = spare / 8 * 8;
+// Copy work-groups that go with attn_wgs attention work-groups, one of which fits on a CU: the CUs the
+// attention grid leaves free, as a multiple of 8 in [16, 64] (one work-group copies about 50 GB/s).
+inline int copy_wgs_beside(int attn_wgs) {
+  const int n = (256 - attn_wgs % 256) / 8 * 8;
   return n < 16 ? 16 : (n > 64 ? 64 : n);
 }
+// Groups into which the copy work-groups of a launch over a ring fall, each with chunks of its own: a chunk is a
+// chain of load, store, acknowledgement and count that takes 4 to 5 us however short it is, so short chunks travel
+// side by side, up to eight, as long as that puts the first one off by no more than another 4 us (65 GB/s per
+// work-group; `largest`: bytes read and written for the largest chunk; `later`: chunks that travel).
+inline int copy_groups_of(int copy_wgs, int later, int64_t largest) {
+  int g = 1;
+  while (g < 8 && g < later && (double)(2 * g) * (double)largest <= 4.0 * 65e3 * copy_wgs) g *= 2;   // (copy_wgs is a multiple of 8)
+  return g;
+}
+inline int prefetch_wg_count(const AttnStep& s, int attn_wgs) { return s.n_copy <= 0 ? 0 : copy_wgs_beside(attn_wgs); }
 usp_status launch_attn_generic(const AttnStep& s, hipStream_t st);
 usp_status launch_attn_mfma(const AttnStep& s, hipStream_t st);
 bool attn_mfma_supported(const AttnStep& s);
 // How the matrix-core kernels run a launch that finishes its result: variant as AttnStep::variant, and parts
 struct AttnForm { int variant, parts; };
-AttnForm attn_mfma_form(int B, int H, int Sq, int d, int64_t tiles);
+// What a launch over a ring moves while it computes: chunks that hold keys, bytes read and written for all
+// but the first of them and for the largest of those, tiles of the last
+struct RingTransfers { int chunks; int64_t bytes, largest, last_tiles; bool fp8; };
+// ring: null for a launch over one chunk
+AttnForm attn_mfma_form(int B, int H, int Sq, int d, int64_t tiles, const RingTransfers* ring);
 // whether one launch over a ring of bf16 chunks is expected to beat one per chunk
 bool attn_mfma_ring_pays(int B, int H, int Sq, int d, int64_t tiles, int chunks);
 // tiles a launch over several chunks takes if some of its keys are dead (a mask, a ragged chunk)
@@ -188,6 +201,11 @@ static hipError_t allow_large_lds(int bytes) {
   if (e == hipSuccess && tracked) done.fetch_or((uint64_t)1 << dev, std::memory_order_release);
   return e;
 }
+
+// The route of a call with its full workspace, for tests: one launch over all chunks or a launch for each, and the
+// work-groups that share the keys of a query block.  masked: some chunk comes with a key mask.
+struct AttnRoute { bool one_launch; int parts; };
+usp_status attn_route(const usp_attn_desc* desc, bool masked, AttnRoute* route);
 
 // What usp_ring_attn_fwd does, with the knobs the ABI does not carry.
 struct CallOptions {

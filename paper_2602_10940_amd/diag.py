@@ -38,6 +38,8 @@ def load_diag_library() -> ctypes.CDLL:
     lib.usp_diag_ring_attn_fwd_wait.argtypes = [ctypes.POINTER(B.AttnDesc), vp, ctypes.POINTER(vp), ctypes.POINTER(vp),
                                                 ctypes.POINTER(vp), ctypes.POINTER(vp), ctypes.POINTER(vp),
                                                 vp, vp, vp, sz, vp, i32, i32]
+    lib.usp_diag_attn_route.restype = i32
+    lib.usp_diag_attn_route.argtypes = [ctypes.POINTER(B.AttnDesc), i32, ctypes.POINTER(i32), ctypes.POINTER(i32)]
     _diag = lib
     return lib
 
@@ -83,6 +85,14 @@ def usp_diag_repeat_merge_calls(reps: int, o1, l1, o2, l2, o, l, stream=None) ->
     rows, d = o1[0].shape
     B._check(lib.usp_diag_repeat_merge_calls(int(reps), len(o1), rows, d, B._ptr_array(o1), B._ptr_array(l1), B._ptr_array(o2),
                                              B._ptr_array(l2), B._ptr_array(o), B._ptr_array(l), B._stream_handle(stream)))
+
+
+def usp_diag_attn_route(desc: B.AttnDesc, masked: bool = False) -> Tuple[bool, int]:
+    """(one launch over all chunks, work-groups that share the keys of a query block) of a call."""
+    lib = load_diag_library()
+    one, parts = ctypes.c_int32(), ctypes.c_int32()
+    B._check(lib.usp_diag_attn_route(ctypes.byref(desc), 1 if masked else 0, ctypes.byref(one), ctypes.byref(parts)))
+    return bool(one.value), parts.value
 
 
 def usp_diag_ring_attn_fwd_wait(q: torch.Tensor, k_chunks: Sequence[torch.Tensor], v_chunks: Sequence[torch.Tensor],

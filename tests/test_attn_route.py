@@ -1,0 +1,46 @@
+"""Which launches usp_ring_attn_fwd chooses (usp_diag_attn_route: host code, no GPU)."""
+import ctypes
+
+import pytest
+
+from paper_2602_10940_amd import binding as b
+from paper_2602_10940_amd import diag
+
+
+def _desc(B, H, d, Sq, lens, fp8=False, flags=0):
+    x = b.AttnDesc()
+    x._lens = (ctypes.c_int32 * len(lens))(*lens)
+    x.B, x.H, x.d, x.Sq, x.n_chunks, x.flags = B, H, d, Sq, len(lens), flags
+    x.chunk_len = ctypes.cast(x._lens, ctypes.POINTER(ctypes.c_int32))
+    x.qo_dtype, x.kv_dtype = b.USP_BF16, b.USP_FP8_E4M3FN if fp8 else b.USP_BF16
+    for i, s in enumerate((H * Sq * d, Sq * d, d)):
+        x.q_stride[i] = x.o_stride[i] = s
+    return x
+
+
+def _route(*a, masked=False, **kw):
+    return diag.usp_diag_attn_route(_desc(*a, **kw), masked)
+
+
+# rings whose chunks arrive later than few tiles of keys take: sharing the keys was slower there by 13 to 43 %
+SHORT = [(2, 12, 128, 150, (320,) * 8, True), (2, 11, 128, 576, (576,) * 8, True), (2, 18, 128, 70, (395,) * 3, True),
+         (1, 7, 64, 102, (384,) * 3, False), (1, 16, 64, 82, (192,) * 6, False)]
+
+
+@pytest.mark.parametrize("B,H,d,Sq,lens,fp8", SHORT)
+def test_short_chunks_that_arrive_late_keep_their_keys_together(B, H, d, Sq, lens, fp8):
+    assert _route(B, H, d, Sq, lens, fp8=fp8, flags=b.USP_ATTN_FUSED_PREFETCH) == (True, 1)
+
+
+@pytest.mark.parametrize("fp8", [False, True])
+def test_long_chunks_under_few_queries_share_their_keys(fp8):
+    for lens in ((2816,) * 6, (2816,)):
+        one, parts = _route(1, 2, 128, 108, lens, fp8=fp8)
+        assert one == (len(lens) > 1) and parts >= 8
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("lens", [(64,) * 8, (128, 640), (384,) * 8, (513, 575, 640), (2816,) * 4])
+def test_transfers_inside_the_launch_do_not_change_the_form(d, lens):
+    for H, Sq in ((1, 64), (2, 300), (5, 640), (12, 100)):
+        assert _route(1, H, d, Sq, lens) == _route(1, H, d, Sq, lens, flags=b.USP_ATTN_FUSED_PREFETCH)

@@ -90,6 +90,34 @@ def test_dead_keys_and_parts(B, H, Sq, lens, d, fp8, mask):
             assert torch.equal(o, ref[0]) and torch.equal(l, ref[1])
 
 
+# short chunks travel side by side in up to eight groups of the copy work-groups: fewer later chunks than
+# groups, as many, more (two for some groups), the most that one launch takes
+@pytest.mark.parametrize("fp8", [False, True])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("lens", [(64, 64), (64, 128, 64, 64), (64,) * 9, (128, 0, 64) + (64,) * 9, (64,) * 16])
+def test_short_chunks_travel_side_by_side(lens, d, fp8):
+    P = _P()
+    wl = W.Workload("groups", 40 + len(lens), 2, 3, d, 200, lens, "bf16")
+    if fp8:
+        inp, q, k, ksc, v, vsc, kx, vx = _fp8_ring(wl)
+        kw = dict(k_scales=ksc, v_scales=vsc)
+    else:
+        inp = W.make_attention_inputs(wl)
+        q, k, v, kx, vx = dev_bf16(inp.q), [dev_bf16(x) for x in inp.k], [dev_bf16(x) for x in inp.v], inp.k, inp.v
+        kw = dict()
+    kw["softmax_scale"] = float(inp.softmax_scale)
+    ro, rl = orc.ring_attention(inp.q, kx, vx, kw["softmax_scale"])
+    plain = P.usp_ring_attn_fwd(q, k, v, **kw)
+    desc = P.make_attn_desc(q, k, q, kw["softmax_scale"], P.USP_ATTN_FUSED_PREFETCH)
+    ws = torch.empty((P.usp_ring_attn_workspace_bytes(desc),), dtype=torch.uint8, device=DEV)
+    for _ in range(3):
+        ws.fill_(0xFF)
+        o, l = P.usp_ring_attn_fwd(q, k, v, flags=P.USP_ATTN_FUSED_PREFETCH, workspace=ws, **kw)
+        torch.cuda.synchronize()
+        _parity(o, l, ro, rl)
+        assert torch.equal(o, plain[0]) and torch.equal(l, plain[1])
+
+
 @pytest.mark.parametrize("d,Sq,lens", [(128, 1800, (64, 128, 64)), (128, 1700, (600, 500)), (64, 1800, (128, 64, 192))])
 def test_short_chunks_under_more_than_one_round_of_query_blocks(d, Sq, lens):
     """40 heads with seven or eight 256-query blocks each: the plain call takes these rings as one launch."""
