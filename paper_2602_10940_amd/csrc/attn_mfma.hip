@@ -1340,24 +1340,37 @@ AttnForm attn_mfma_form(int B, int H, int Sq, int d, int64_t tiles, const RingTr
   return best;
 }
 
-// One launch over a ring of bf16 chunks, or one per chunk, where the Q shard's 256-query blocks need more than
-// one round of work-groups (up to one round the one launch is always the better).  In microseconds, a launch
-// per chunk takes 9 + 1.5 per tile and round, the last round counting 0.6 where the mixed launch can halve its
-// blocks, and the carried fp32 O goes out and back at 4.5 TB/s between two chunks; the one launch takes
-// 7 + tiles * t per round, t = 1.5 for 256-query work-groups, and for key-split ones 0.68 + 0.29 * the share of
-// the rounds that they fill (idle CUs let the others clock higher).  Measured, per chunk against one launch:
-// H = 24, Sq = 2816, four chunks of 1024 244 -> 183 us; H = 20, Sq = 3500, three of 2048 287 -> 259;
-// H = 24, two of 3000 265 and 265, two of 4096 358 against 386 (left per chunk).
-bool attn_mfma_ring_pays(int B, int H, int Sq, int d, int64_t tiles, int chunks) {
-  const int64_t items = (int64_t)B * H * ((Sq + kQPerWG - 1) / kQPerWG), halves = (int64_t)B * H * ((Sq + kQPerWGSplit - 1) / kQPerWGSplit);
-  if (items <= 256) return true;
-  const int64_t rem = items % 256, rounds128 = (halves + 255) / 256;
-  const double rounds = (double)(items / 256) + (rem == 0 ? 0.0 : d == kD && rem <= 128 ? 0.6 : 1.0);
-  const double carry = 2.0 * 4 * d * B * H * Sq / 4.5e6;
-  const double stepwise = chunks * 9.0 + rounds * tiles * 1.5 + (chunks - 1) * carry;
-  const double wide = (double)((items + 255) / 256) * (7.0 + tiles * 1.5);
-  const double split = rounds128 * (7.0 + tiles * (0.68 + 0.29 * halves / (256.0 * rounds128)));
-  return (wide < split ? wide : split) < 0.97 * stepwise;
+// How one launch over a ring is decomposed, and whether it is expected to beat a launch per chunk (bf16 chunks,
+// all of them at hand).  variant: as AttnStep::variant, 1 and 2 force a form and are judged by that one.
+// Up to one round of 256-query blocks on the 256 CUs the one launch is always the better; key-split there where
+// the blocks number at most kSplitBelowWGs or their halves, which take about 0.55 of a block's time, fit a round.
+// Beyond, in microseconds, with `rounds` of the work-groups over the CUs: 256-query work-groups
+// rounds * (10.8 + 1.46 * tiles), d = 64 (8.0 + 1.13 * tiles); key-split ones rounds * (9.6 + 0.73 * tiles) and 0.116
+// per tile and 256 work-groups (idle CUs let the others clock higher), d = 64 (7.1 + 0.47 * tiles) and 0.16; a launch
+// per chunk 10.5 (d = 64: 1.1) each, 5.3 (6.5) per chunk and round, 1.48 (1.12) per tile and round, the last round counting
+// 0.6 where the mixed launch can halve its blocks (d = 128), and 0.115 (0.22) per MB of the carried fp32 O, out and
+// back between two chunks.  70 rings of 260 to 864 blocks, two to eight chunks of 64 to 4096 keys, all three timed:
+// each estimate within 12 % (d = 128: 9 %).  Per chunk, 256-query, key-split: B = 2, H = 24, Sq = 4608, two of 1536
+// 370, 331, 363 us; B = 2, H = 22, d = 64, Sq = 4416, two of 128 92, 47, 62; H = 24, Sq = 2816, four of 1024 245,
+// 208, 184; B = 2, H = 18, Sq = 3629, two of 3008 430, 456, 432 (left per chunk).
+RingForm attn_mfma_ring_form(int B, int H, int Sq, int d, int64_t tiles, int chunks, int variant) {
+  const int64_t blocks = (int64_t)B * H * ((Sq + kQPerWG - 1) / kQPerWG), halves = (int64_t)B * H * ((Sq + kQPerWGSplit - 1) / kQPerWGSplit);
+  if (blocks <= 256) {
+    const int64_t w256 = (blocks + 7) / 8 * 8, w128 = (halves + 7) / 8 * 8;   // (as the grid rounds them)
+    return {variant == 2 || (variant != 1 && (w256 <= kSplitBelowWGs || w128 <= 256)), true};
+  }
+  const bool narrow = d != kD;
+  const int64_t r256 = (blocks + 255) / 256, r128 = (halves + 255) / 256, rem = blocks % 256;
+  const double n = (double)tiles;
+  const double wide = (double)r256 * (narrow ? 8.0 + 1.13 * n : 10.8 + 1.46 * n);
+  const double split = narrow ? (double)r128 * (7.1 + 0.47 * n) + 0.16 * n * (double)halves / 256.0
+                              : (double)r128 * (9.6 + 0.73 * n) + 0.116 * n * (double)halves / 256.0;
+  const double rounds = (double)(blocks / 256) + (rem == 0 ? 0.0 : !narrow && rem <= 128 ? 0.6 : 1.0);
+  const double carry = 2.0 * 4 * d * B * H * Sq / 1e6;
+  const double stepwise = chunks * (narrow ? 1.1 + 6.5 * rounds : 10.5 + 5.3 * rounds) + rounds * n * (narrow ? 1.12 : 1.48) +
+                          (chunks - 1) * carry * (narrow ? 0.22 : 0.115);
+  const bool take_split = variant == 2 || (variant != 1 && split < wide);
+  return {take_split, (take_split ? split : wide) < 0.97 * stepwise};
 }
 
 usp_status launch_attn_mfma(const AttnStep& step, hipStream_t st) {
@@ -1368,7 +1381,6 @@ usp_status launch_attn_mfma(const AttnStep& step, hipStream_t st) {
     return USP_ERR_INVALID_ARG;
   }
   if (s.n_multi > 0) {
-    // several resident chunks, one launch: the same two work decompositions, by the same rule
     if (s.n_multi > AttnStep::kMaxMulti || s.mode != 0 || s.n_copy != 0 || s.key_mask || s.k_scale || s.v_scale) {   // (n_copy: the per-step form of the transfers)
       set_error("a launch over several chunks takes at most %d chunks and finishes the result", AttnStep::kMaxMulti);
       return USP_ERR_INVALID_ARG;
@@ -1387,11 +1399,10 @@ usp_status launch_attn_mfma(const AttnStep& step, hipStream_t st) {
     }
     const unsigned w256 = wg_grid_size((s.Sq + kQPerWG - 1) / kQPerWG, s.B * s.H);
     const unsigned w128 = wg_grid_size((s.Sq + kQPerWGSplit - 1) / kQPerWGSplit, s.B * s.H * s.parts);
-    // There is no mixed form of this launch: between the two decompositions, take the one whose
-    // rounds of work-groups over the 256 CUs cost less (a key-split work-group takes about 0.55 of a
-    // 256-query one)
-    const double cost256 = (double)((w256 + 255) / 256), cost128 = 0.55 * (double)((w128 + 255) / 256);
-    const bool split = s.variant == 2 || (s.variant != 1 && ((int)w256 <= kSplitBelowWGs || cost128 < cost256));
+    // (there is no mixed form of this launch)
+    int64_t tiles = 0;
+    for (int c = 0; c < s.n_multi; ++c) tiles += (s.chunk[c].Sc + kTile - 1) / kTile;
+    const bool split = attn_mfma_ring_form(s.B, s.H, s.Sq, s.d, tiles, s.n_multi, s.variant).split;
     const unsigned wgs = split ? w128 : w256;
     s.copy_wgs = 0;
     if (s.arrive != nullptr) {

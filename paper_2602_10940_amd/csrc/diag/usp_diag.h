@@ -72,8 +72,10 @@ usp_status usp_diag_ring_attn_fwd_wait(const usp_attn_desc* desc, const void* q,
 /* How usp_ring_attn_fwd would launch this call with a full workspace; host only.
  *   masked     : nonzero if some chunk comes with a key mask
  *   one_launch : receives 1 for one launch over all chunks, 0 for a launch per chunk (or a single chunk)
+ *   split      : receives 1 if that one launch over a ring is key-split
  *   parts      : receives the number of work-groups that share the keys of a query block */
-usp_status usp_diag_attn_route(const usp_attn_desc* desc, int32_t masked, int32_t* one_launch, int32_t* parts);
+usp_status usp_diag_attn_route(const usp_attn_desc* desc, int32_t masked, int32_t* one_launch, int32_t* split,
+                               int32_t* parts);
 
 #ifdef __cplusplus
 }

@@ -230,13 +230,14 @@ usp_status usp_diag_ring_attn_fwd_wait(const usp_attn_desc* desc, const void* q,
                             workspace_bytes, compute_stream, nullptr, opt);
 }
 
-usp_status usp_diag_attn_route(const usp_attn_desc* desc, int32_t masked, int32_t* one_launch, int32_t* parts) {
+usp_status usp_diag_attn_route(const usp_attn_desc* desc, int32_t masked, int32_t* one_launch, int32_t* split, int32_t* parts) {
   clear_error();
-  USP_CHECK_ARG(one_launch != nullptr && parts != nullptr, "an output is NULL");
+  USP_CHECK_ARG(one_launch && split && parts, "an output is NULL");
   AttnRoute r;
   const usp_status st = attn_route(desc, masked != 0, &r);
   if (st != USP_OK) return st;
   *one_launch = r.one_launch ? 1 : 0;
+  *split = r.split ? 1 : 0;
   *parts = r.parts;
   return USP_OK;
 }

@@ -271,13 +271,16 @@ usp_status make_plan(const usp_attn_desc* d, Plan* p) {
 // How a call's chunks are launched (the comments stand in ring_attn_fwd_impl).  `masked`: some chunk that holds
 // keys has a key mask.
 enum class Way { per_chunk, ring, ring_fp8, general };
+int forced_variant(const usp_attn_desc* d) {   // of a launch over a ring
+  return (d->flags & USP_ATTN_KERNEL_SPLIT) ? 2 : (d->flags & USP_ATTN_KERNEL_WIDE) ? 1 : 0;
+}
 Way way_of(const usp_attn_desc* d, const Plan& p, bool masked) {
   if (!p.mfma)
     return p.W > 1 && p.W <= AttnStep::kMaxMulti && !p.dbuf && !p.unfused && !(d->flags & USP_ATTN_STEPWISE) ? Way::general : Way::per_chunk;
   if (!p.one_launch || ((masked || !p.whole) && (int64_t)p.tiles > attn_mfma_max_dead_tiles())) return Way::per_chunk;
   if (p.fp8) return p.ring8 ? Way::ring_fp8 : Way::per_chunk;
   if (p.dbuf && !p.ring1) return Way::per_chunk;
-  return p.fused_pf || attn_mfma_ring_pays(d->B, d->H, d->Sq, d->d, (int64_t)p.tiles, p.live) ? Way::ring : Way::per_chunk;
+  return p.fused_pf || attn_mfma_ring_form(d->B, d->H, d->Sq, d->d, (int64_t)p.tiles, p.live, forced_variant(d)).pays ? Way::ring : Way::per_chunk;
 }
 
 }  // namespace
@@ -465,7 +468,11 @@ usp_status usp::attn_route(const usp_attn_desc* desc, bool masked, AttnRoute* ro
   if (st != USP_OK) return st;
   const Way way = way_of(desc, p, masked);
   const bool finishes = p.mfma && (way != Way::per_chunk || p.W == 1);
-  *route = {way != Way::per_chunk, finishes ? p.form.parts : 1};
+  const int variant = finishes && p.form.parts > 1 ? p.form.variant : forced_variant(desc);
+  const bool ring = way == Way::ring || way == Way::ring_fp8;
+  *route = {way != Way::per_chunk,
+            ring && attn_mfma_ring_form(desc->B, desc->H, desc->Sq, desc->d, (int64_t)p.tiles, p.live, variant).split,
+            finishes ? p.form.parts : 1};
   return USP_OK;
 }
 
@@ -576,7 +583,7 @@ usp_status usp::ring_attn_fwd_impl(const usp_attn_desc* desc, const void* q, con
     a.q = q; a.out = out; a.lse = lse; a.scale = scale; a.mode = 0;
     for (int i = 0; i < 3; ++i) { a.qs[i] = desc->q_stride[i]; a.ks[i] = desc->kv_stride[i]; a.os[i] = desc->o_stride[i]; }
     if (kv_auto(desc)) a.ks[2] = d;
-    a.variant = (desc->flags & USP_ATTN_KERNEL_SPLIT) ? 2 : (desc->flags & USP_ATTN_KERNEL_WIDE) ? 1 : 0;
+    a.variant = forced_variant(desc);
     const bool transfers = p.dbuf;                      // (ring1) Algorithm 2 inside the launch
     if (transfers) a.ks[2] = d;                         // the double-buffered modes take dense chunks only
     size_t stage = p.off_ring1;
@@ -641,7 +648,7 @@ usp_status usp::ring_attn_fwd_impl(const usp_attn_desc* desc, const void* q, con
     a.q = q; a.out = out; a.lse = lse; a.scale = scale; a.mode = 0;
     for (int i = 0; i < 3; ++i) { a.qs[i] = desc->q_stride[i]; a.os[i] = desc->o_stride[i]; }
     a.ks[2] = d;
-    a.variant = (desc->flags & USP_ATTN_KERNEL_SPLIT) ? 2 : (desc->flags & USP_ATTN_KERNEL_WIDE) ? 1 : 0;
+    a.variant = forced_variant(desc);
     a.multi_fp8 = 1;
     a.ext = (float*)(ws + p.off_ext8);
     a.arrive = (int*)(ws + p.off_arrive);

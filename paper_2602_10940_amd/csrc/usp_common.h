@@ -178,8 +178,9 @@ struct AttnForm { int variant, parts; };
 struct RingTransfers { int chunks; int64_t bytes, largest, last_tiles; bool fp8; };
 // ring: null for a launch over one chunk
 AttnForm attn_mfma_form(int B, int H, int Sq, int d, int64_t tiles, const RingTransfers* ring);
-// whether one launch over a ring of bf16 chunks is expected to beat one per chunk
-bool attn_mfma_ring_pays(int B, int H, int Sq, int d, int64_t tiles, int chunks);
+// One launch over a ring: key-split or 256-query work-groups, and whether it is expected to beat a launch per chunk
+struct RingForm { bool split, pays; };
+RingForm attn_mfma_ring_form(int B, int H, int Sq, int d, int64_t tiles, int chunks, int variant);
 // tiles a launch over several chunks takes if some of its keys are dead (a mask, a ragged chunk)
 int64_t attn_mfma_max_dead_tiles();
 usp_status launch_attn_arrive_reset(int* arrive, hipStream_t st);
@@ -202,9 +203,10 @@ static hipError_t allow_large_lds(int bytes) {
   return e;
 }
 
-// The route of a call with its full workspace, for tests: one launch over all chunks or a launch for each, and the
-// work-groups that share the keys of a query block.  masked: some chunk comes with a key mask.
-struct AttnRoute { bool one_launch; int parts; };
+// The route of a call with its full workspace, for tests: one launch over all chunks or a launch for each, whether
+// that launch is key-split, and the work-groups that share the keys of a query block.  masked: some chunk comes
+// with a key mask.
+struct AttnRoute { bool one_launch, split; int parts; };
 usp_status attn_route(const usp_attn_desc* desc, bool masked, AttnRoute* route);
 
 // What usp_ring_attn_fwd does, with the knobs the ABI does not carry.

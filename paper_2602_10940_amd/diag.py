@@ -4,7 +4,7 @@ from __future__ import annotations
 
 import ctypes
 import os
-from typing import Optional, Sequence, Tuple
+from typing import NamedTuple, Optional, Sequence, Tuple
 
 import torch
 
@@ -39,7 +39,7 @@ def load_diag_library() -> ctypes.CDLL:
                                                 ctypes.POINTER(vp), ctypes.POINTER(vp), ctypes.POINTER(vp),
                                                 vp, vp, vp, sz, vp, i32, i32]
     lib.usp_diag_attn_route.restype = i32
-    lib.usp_diag_attn_route.argtypes = [ctypes.POINTER(B.AttnDesc), i32, ctypes.POINTER(i32), ctypes.POINTER(i32)]
+    lib.usp_diag_attn_route.argtypes = [ctypes.POINTER(B.AttnDesc), i32] + [ctypes.POINTER(i32)] * 3
     _diag = lib
     return lib
 
@@ -87,12 +87,18 @@ def usp_diag_repeat_merge_calls(reps: int, o1, l1, o2, l2, o, l, stream=None) ->
                                              B._ptr_array(l2), B._ptr_array(o), B._ptr_array(l), B._stream_handle(stream)))
 
 
-def usp_diag_attn_route(desc: B.AttnDesc, masked: bool = False) -> Tuple[bool, int]:
-    """(one launch over all chunks, work-groups that share the keys of a query block) of a call."""
+class AttnRoute(NamedTuple):
+    one_launch: bool   # one launch over all chunks
+    split: bool        # that launch is key-split
+    parts: int         # work-groups that share the keys of a query block
+
+
+def usp_diag_attn_route(desc: B.AttnDesc, masked: bool = False) -> AttnRoute:
     lib = load_diag_library()
-    one, parts = ctypes.c_int32(), ctypes.c_int32()
-    B._check(lib.usp_diag_attn_route(ctypes.byref(desc), 1 if masked else 0, ctypes.byref(one), ctypes.byref(parts)))
-    return bool(one.value), parts.value
+    one, split, parts = ctypes.c_int32(), ctypes.c_int32(), ctypes.c_int32()
+    B._check(lib.usp_diag_attn_route(ctypes.byref(desc), 1 if masked else 0, ctypes.byref(one), ctypes.byref(split),
+                                     ctypes.byref(parts)))
+    return AttnRoute(bool(one.value), bool(split.value), parts.value)
 
 
 def usp_diag_ring_attn_fwd_wait(q: torch.Tensor, k_chunks: Sequence[torch.Tensor], v_chunks: Sequence[torch.Tensor],

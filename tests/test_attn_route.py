@@ -29,13 +29,13 @@ SHORT = [(2, 12, 128, 150, (320,) * 8, True), (2, 11, 128, 576, (576,) * 8, True
 
 @pytest.mark.parametrize("B,H,d,Sq,lens,fp8", SHORT)
 def test_short_chunks_that_arrive_late_keep_their_keys_together(B, H, d, Sq, lens, fp8):
-    assert _route(B, H, d, Sq, lens, fp8=fp8, flags=b.USP_ATTN_FUSED_PREFETCH) == (True, 1)
+    assert _route(B, H, d, Sq, lens, fp8=fp8, flags=b.USP_ATTN_FUSED_PREFETCH)[::2] == (True, 1)
 
 
 @pytest.mark.parametrize("fp8", [False, True])
 def test_long_chunks_under_few_queries_share_their_keys(fp8):
     for lens in ((2816,) * 6, (2816,)):
-        one, parts = _route(1, 2, 128, 108, lens, fp8=fp8)
+        one, _, parts = _route(1, 2, 128, 108, lens, fp8=fp8)
         assert one == (len(lens) > 1) and parts >= 8
 
 
@@ -44,3 +44,25 @@ def test_long_chunks_under_few_queries_share_their_keys(fp8):
 def test_transfers_inside_the_launch_do_not_change_the_form(d, lens):
     for H, Sq in ((1, 64), (2, 300), (5, 640), (12, 100)):
         assert _route(1, H, d, Sq, lens) == _route(1, H, d, Sq, lens, flags=b.USP_ATTN_FUSED_PREFETCH)
+
+
+# us of a launch per chunk, one launch of 256-query work-groups, one key-split launch (all chunks at hand)
+MEASURED = [(2, 24, 128, 4608, 2, 1536, 370, 331, 363), (2, 22, 64, 4416, 2, 128, 92, 47, 62), (2, 19, 64, 3621, 2, 128, 71, 37, 46),
+            (1, 22, 128, 3112, 2, 128, 57, 32, 39), (1, 24, 128, 2816, 4, 1024, 245, 208, 184), (1, 20, 128, 3500, 3, 2048, 302, 302, 261),
+            (2, 15, 64, 2149, 6, 384, 189, 99, 63), (2, 13, 128, 2384, 6, 256, 214, 92, 64), (2, 22, 64, 1725, 6, 3328, 810, 701, 544),
+            (2, 21, 128, 1865, 8, 1216, 563, 470, 410), (2, 18, 128, 3629, 2, 3008, 430, 456, 432), (2, 14, 64, 4544, 2, 960, 114, 84, 96)]
+
+
+@pytest.mark.parametrize("B,H,d,Sq,n,chunk,stepwise,wide,split", MEASURED)
+def test_more_than_one_round_of_query_blocks_runs_the_form_that_was_judged(B, H, d, Sq, n, chunk, stepwise, wide, split):
+    r = _route(B, H, d, Sq, (chunk,) * n)
+    took = stepwise if not r.one_launch else split if r.split else wide
+    assert took <= 1.05 * min(stepwise, wide, split)
+    # the transfers inside the launch: the same form
+    pre = _route(B, H, d, Sq, (chunk,) * n, flags=b.USP_ATTN_FUSED_PREFETCH)
+    assert pre.one_launch and (not r.one_launch or pre.split == r.split)
+    # a forced form is judged by what it costs itself
+    for flag, us in ((b.USP_ATTN_KERNEL_WIDE, wide), (b.USP_ATTN_KERNEL_SPLIT, split)):
+        f = _route(B, H, d, Sq, (chunk,) * n, flags=flag)
+        assert (us if f.one_launch else stepwise) <= 1.05 * min(us, stepwise)
+        assert not f.one_launch or f.split == (flag == b.USP_ATTN_KERNEL_SPLIT)
