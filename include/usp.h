@@ -146,7 +146,9 @@ size_t usp_ring_attn_workspace_bytes(const usp_attn_desc* desc);
  *              are all masked gets O = 0, lse = -inf.
  *   out        [B,H,Sq,d] by o_stride, dtype qo_dtype
  *   lse        float [B,H,Sq] dense, natural log
- *   workspace  device memory, >= usp_ring_attn_workspace_bytes(desc), 256-byte aligned
+ *   workspace  device memory, >= usp_ring_attn_workspace_bytes(desc), 256-byte aligned.  (With less,
+ *              ragged chunks get a launch each and keys are not shared between work-groups, if that
+ *              fits; else USP_ERR_WORKSPACE.)
  *   compute_stream   all kernels run here
  *   copy_stream      used only with USP_ATTN_DOUBLE_BUFFER: chunk r+1 is copied into an
  *              internal buffer here while chunk r is computed (the one-GPU stand-in for
@@ -164,13 +166,16 @@ usp_status usp_ring_attn_fwd(const usp_attn_desc* desc, const void* q,
 /*
  * usp_ring_attn_fwd for callers that cannot allocate device memory or hand over a workspace: code
  * under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments
- * and results as usp_ring_attn_fwd (same kernels, same order: bit-identical outputs), minus the
- * workspace and the copy stream: the workspace is an array of USP_NOALLOC_SCRATCH_BYTES that the
- * library holds in device memory on every GPU it runs on, from the first such call on that GPU until
- * the process ends.  The call allocates and frees nothing (no hipMalloc, no events).
- *   - A descriptor whose usp_ring_attn_workspace_bytes() exceeds USP_NOALLOC_SCRATCH_BYTES is refused
- *     with USP_ERR_WORKSPACE and nothing is enqueued (e.g. the FLUX-1024 ring shard needs 17 MB, the
- *     Qwen-Image-like FP8 shard 0.5 GB: the latter has to bring its own workspace).
+ * and results as usp_ring_attn_fwd, minus the workspace and the copy stream: the workspace is an array
+ * of USP_NOALLOC_SCRATCH_BYTES that the library holds in device memory on every GPU it runs on, from the
+ * first such call on that GPU until the process ends.  The call allocates and frees nothing (no
+ * hipMalloc, no events).
+ *   - Where usp_ring_attn_workspace_bytes() is at most USP_NOALLOC_SCRATCH_BYTES: the same kernels in
+ *     the same order, bit-identical outputs.  A descriptor that asks for more, but whose ragged chunks
+ *     taken by a launch each and keys not shared between work-groups would fit, runs that way: the same
+ *     result up to rounding order, as usp_ring_attn_fwd gives with that much workspace.
+ *   - Any other is refused with USP_ERR_WORKSPACE and nothing is enqueued (e.g. the FLUX-1024 ring shard
+ *     needs 17 MB, the Qwen-Image-like FP8 shard 0.5 GB: the latter has to bring its own workspace).
  *   - USP_ATTN_DOUBLE_BUFFER (side stream and events) is refused with USP_ERR_UNSUPPORTED; the
  *     transfers inside the launches (USP_ATTN_FUSED_PREFETCH) are available.
  *   - Every call on one GPU uses that GPU's one array: calls that overlap in time on one GPU (two

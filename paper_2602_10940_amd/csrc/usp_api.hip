@@ -116,7 +116,7 @@ bool one_launch_lengths(const usp_attn_desc* d, bool least, bool* whole, size_t*
 
 // `least`: the plan that needs no more workspace than a launch per chunk, or one launch over whole tiles,
 // does: no one launch over ragged chunks, no parts.
-usp_status make_plan_of(const usp_attn_desc* d, bool least, Plan* p) {
+usp_status make_plan(const usp_attn_desc* d, bool least, Plan* p) {
   USP_CHECK_ARG(d != nullptr, "desc is NULL");
   USP_CHECK_ARG(d->B > 0 && d->H > 0 && d->Sq > 0, "B, H, Sq must be positive (B=%d H=%d Sq=%d)", d->B, d->H, d->Sq);
   USP_CHECK_ARG(d->d > 0 && d->d % 8 == 0 && d->d <= 256, "d must be a multiple of 8 in [8, 256] (got %d)", d->d);
@@ -257,17 +257,6 @@ usp_status make_plan_of(const usp_attn_desc* d, bool least, Plan* p) {
   return USP_OK;
 }
 
-// The least plan where only that one fits the built-in scratch: usp_ring_attn_fwd and
-// usp_ring_attn_fwd_noalloc run the same plan (their outputs have the same bits), and what the latter
-// accepts does not shrink.
-usp_status make_plan(const usp_attn_desc* d, Plan* p) {
-  usp_status st = make_plan_of(d, false, p);
-  if (st != USP_OK || p->total <= (size_t)USP_NOALLOC_SCRATCH_BYTES) return st;
-  Plan least;
-  if ((st = make_plan_of(d, true, &least)) == USP_OK && least.total <= (size_t)USP_NOALLOC_SCRATCH_BYTES) *p = least;
-  return st;
-}
-
 // How a call's chunks are launched (the comments stand in ring_attn_fwd_impl).  `masked`: some chunk that holds
 // keys has a key mask.
 enum class Way { per_chunk, ring, ring_fp8, general };
@@ -328,12 +317,16 @@ usp_status usp_ring_attn_fwd_noalloc(const usp_attn_desc* desc, const void* q, c
                                      float* lse, void* compute_stream) {
   clear_error();
   Plan p;
-  usp_status st = make_plan(desc, &p);
+  usp_status st = make_plan(desc, false, &p);
   if (st != USP_OK) return st;
   if ((desc->flags & USP_ATTN_DOUBLE_BUFFER) != 0) {
     set_error("usp_ring_attn_fwd_noalloc has no copy stream: USP_ATTN_DOUBLE_BUFFER is not available "
               "(USP_ATTN_FUSED_PREFETCH is)");
     return USP_ERR_UNSUPPORTED;
+  }
+  if (p.total > (size_t)USP_NOALLOC_SCRATCH_BYTES) {   // (ring_attn_fwd_impl makes the same choice)
+    p = Plan();
+    if ((st = make_plan(desc, true, &p)) != USP_OK) return st;
   }
   if (p.total > (size_t)USP_NOALLOC_SCRATCH_BYTES) {
     set_error("this call needs %zu bytes of workspace, the built-in scratch holds %zu: use usp_ring_attn_fwd "
@@ -351,7 +344,7 @@ const char* usp_version(void) { return "usp-gfx950 0.1"; }
 
 size_t usp_ring_attn_workspace_bytes(const usp_attn_desc* desc) {
   Plan p;
-  if (make_plan(desc, &p) != USP_OK) return (size_t)-1;
+  if (make_plan(desc, false, &p) != USP_OK) return (size_t)-1;
   return p.total;
 }
 
@@ -464,7 +457,7 @@ usp_status usp_ring_attn_fwd(const usp_attn_desc* desc, const void* q, const voi
 
 usp_status usp::attn_route(const usp_attn_desc* desc, bool masked, AttnRoute* route) {
   Plan p;
-  const usp_status st = make_plan(desc, &p);
+  const usp_status st = make_plan(desc, false, &p);
   if (st != USP_OK) return st;
   const Way way = way_of(desc, p, masked);
   const bool finishes = p.mfma && (way != Way::per_chunk || p.W == 1);
@@ -482,7 +475,7 @@ usp_status usp::ring_attn_fwd_impl(const usp_attn_desc* desc, const void* q, con
                                    float* lse, void* workspace, size_t workspace_bytes, void* compute_stream,
                                    void* copy_stream, const CallOptions& opt) {
   Plan p;
-  usp_status st = make_plan(desc, &p);
+  usp_status st = make_plan(desc, false, &p);
   if (st != USP_OK) return st;
   USP_CHECK_ARG(q && out && lse && k_chunks && v_chunks, "q, out, lse, k_chunks or v_chunks is NULL");
   USP_CHECK_ARG(aligned16(q) && aligned16(out), "q and out must be 16-byte aligned");
@@ -496,7 +489,7 @@ usp_status usp::ring_attn_fwd_impl(const usp_attn_desc* desc, const void* q, con
   if (p.total > 0) {
     if (workspace != nullptr && workspace_bytes < p.total) {   // a caller that has no more
       p = Plan();
-      if ((st = make_plan_of(desc, true, &p)) != USP_OK) return st;
+      if ((st = make_plan(desc, true, &p)) != USP_OK) return st;
     }
     if (workspace == nullptr || workspace_bytes < p.total) {
       set_error("workspace of %zu bytes needed, %zu given", p.total, workspace ? workspace_bytes : (size_t)0);

@@ -66,3 +66,20 @@ def test_more_than_one_round_of_query_blocks_runs_the_form_that_was_judged(B, H,
         f = _route(B, H, d, Sq, (chunk,) * n, flags=flag)
         assert (us if f.one_launch else stepwise) <= 1.05 * min(us, stepwise)
         assert not f.one_launch or f.split == (flag == b.USP_ATTN_KERNEL_SPLIT)
+
+
+@pytest.mark.parametrize("H,n,fp8", [(12, 3, False), (12, 8, False), (8, 8, False), (20, 3, False), (12, 2, True)])
+def test_the_route_does_not_depend_on_the_scratch_of_another_entry_point(H, n, fp8):
+    """Ragged rings whose one launch needs more workspace than the library's own scratch holds: the caller
+    brings it, so they take the one launch, as the plain call does (whose bits they promise)."""
+    lens, pre = (2215,) * n, b.USP_ATTN_FUSED_PREFETCH
+    plain, inside = _route(1, H, 128, 2215, lens, fp8=fp8), _route(1, H, 128, 2215, lens, fp8=fp8, flags=pre)
+    assert inside.one_launch and (fp8 or plain == inside)
+    full = b.usp_ring_attn_workspace_bytes(_desc(1, H, 128, 2215, lens, fp8, pre))
+    assert full > b.usp_ring_attn_workspace_bytes(_desc(1, H, 128, 2215, lens, fp8, pre | b.USP_ATTN_STEPWISE))
+    if full <= b.USP_NOALLOC_SCRATCH_BYTES:
+        return
+    # what fits the scratch with a launch per chunk is not refused there for want of workspace
+    least = b.usp_ring_attn_workspace_bytes(_desc(1, H, 128, 2215, lens, fp8, pre | b.USP_ATTN_STEPWISE))
+    st = b.load_library().usp_ring_attn_fwd_noalloc(ctypes.byref(_desc(1, H, 128, 2215, lens, fp8, pre)), *[None] * 9)
+    assert (st == b.USP_ERR_WORKSPACE) == (least > b.USP_NOALLOC_SCRATCH_BYTES) and st != b.USP_OK

@@ -121,3 +121,25 @@ def test_replays_from_a_hip_graph(flags):
         g.replay()
         torch.cuda.synchronize()
         assert torch.equal(out, ref_o) and torch.equal(lse, ref_l)
+
+
+def test_a_ring_whose_one_launch_outgrows_the_scratch():
+    """12 heads, three chunks of 2215 keys with the transfers inside: 68 MB for one launch, 41 MB for one per
+    chunk.  With the caller's workspace it gives the plain call's bits; on the scratch it runs per chunk."""
+    import paper_2602_10940_amd as P
+    g = torch.Generator(device=DEV)
+    g.manual_seed(5)
+    q, *kv = [torch.randn((1, 12, 2215, 128), generator=g, device=DEV).bfloat16() for _ in range(7)]
+    k, v = kv[:3], kv[3:]
+    plain_o, plain_l = P.usp_ring_attn_fwd(q, k, v)
+    o, l = P.usp_ring_attn_fwd(q, k, v, flags=FUSED)
+    step_o, step_l = P.usp_ring_attn_fwd(q, k, v, flags=FUSED | STEPWISE)
+    out, lse = torch.empty_like(q), torch.empty(q.shape[:3], device=DEV)
+    P.usp_ring_attn_fwd_noalloc(q, k, v, out, lse, flags=FUSED)
+    torch.cuda.synchronize()
+    assert torch.equal(o, plain_o) and torch.equal(l, plain_l)
+    assert torch.equal(out, step_o) and torch.equal(lse, step_l)
+    z = (q[0].float() @ torch.cat(k, 2)[0].float().transpose(1, 2).contiguous()) * 128 ** -0.5
+    ref = (torch.softmax(z, -1) @ torch.cat(v, 2)[0].float())[None]
+    for x, y in ((o, l), (out, lse)):
+        _assert_parity(host_f64(x), host_f64(y), host_f64(ref), host_f64(torch.logsumexp(z, -1)[None]))
