@@ -68,9 +68,10 @@ typedef enum {
                                         times scales) and K's scales as per-key factors of the exponent;
                                         the first chunk is decoded by a launch of its own in front;
                                         key masks go into the records as well. */
-/* Work decomposition of the bf16 d=128 matrix-core kernel on unmasked chunks whose length is a
- * multiple of 64.  Default (neither bit): chosen from the number of work-groups the Q shard gives.
- * All variants meet the same accuracy bar; the bits exist for tuning and for tests. */
+/* Work decomposition of the matrix-core launches (bf16 Q, d = 128 or 64), masked and ragged chunks
+ * included.  Default (none of the bits): chosen from the number of work-groups the Q shard gives and, with
+ * several chunks, from their tiles.  A forced form does not share keys between work-groups.  All variants
+ * meet the same accuracy bar; the bits exist for tuning and for tests. */
 #define USP_ATTN_KERNEL_WIDE 4u   /* 256 queries per work-group, every wave visits every key */
 #define USP_ATTN_KERNEL_SPLIT 8u  /* 128 queries per work-group, the two wave groups take alternate
                                      64-key tiles and combine their partial results at the end */
@@ -89,7 +90,11 @@ typedef enum {
                                      result up to rounding order. */
 #define USP_ATTN_KERNEL_MIXED 32u /* one launch of both: 256-query work-groups, and the blocks of the
                                      last, partly filled round as pairs of key-split work-groups
-                                     (forced: the second half of all blocks) */
+                                     (forced: the second half of all blocks).  d = 128 only, and not in a
+                                     launch over a ring: a launch per chunk is taken for this bit where
+                                     chunks are ragged, where bf16 ones come with key masks, and, without
+                                     USP_ATTN_FUSED_PREFETCH, where the query blocks exceed one round;
+                                     other rings that one launch covers ignore it */
 
 /*
  * Shape of one ring-attention call (paper section 2.2: Q, K, V are [B, H, S, D]).

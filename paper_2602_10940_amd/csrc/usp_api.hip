@@ -267,7 +267,12 @@ Way way_of(const usp_attn_desc* d, const Plan& p, bool masked) {
   if (!p.mfma)
     return p.W > 1 && p.W <= AttnStep::kMaxMulti && !p.dbuf && !p.unfused && !(d->flags & USP_ATTN_STEPWISE) ? Way::general : Way::per_chunk;
   if (!p.one_launch || ((masked || !p.whole) && (int64_t)p.tiles > attn_mfma_max_dead_tiles())) return Way::per_chunk;
-  if (p.fp8) return p.ring8 ? Way::ring_fp8 : Way::per_chunk;
+  // USP_ATTN_KERNEL_MIXED asks for a form that no launch over a ring has.  (Rings of whole, unmasked tiles within one
+  // round of query blocks, or with the transfers inside, take the one launch whatever that bit says.)
+  const bool mixed = (d->flags & USP_ATTN_KERNEL_MIXED) && d->d == 128;
+  if (p.fp8) return p.ring8 && !(mixed && !p.whole) ? Way::ring_fp8 : Way::per_chunk;
+  const int64_t q_blocks = (int64_t)d->B * d->H * ((d->Sq + 255) / 256);
+  if (mixed && (masked || !p.whole || (!p.fused_pf && q_blocks > 256))) return Way::per_chunk;
   if (p.dbuf && !p.ring1) return Way::per_chunk;
   return p.fused_pf || attn_mfma_ring_form(d->B, d->H, d->Sq, d->d, (int64_t)p.tiles, p.live, forced_variant(d)).pays ? Way::ring : Way::per_chunk;
 }

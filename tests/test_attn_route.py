@@ -83,3 +83,18 @@ def test_the_route_does_not_depend_on_the_scratch_of_another_entry_point(H, n, f
     least = b.usp_ring_attn_workspace_bytes(_desc(1, H, 128, 2215, lens, fp8, pre | b.USP_ATTN_STEPWISE))
     st = b.load_library().usp_ring_attn_fwd_noalloc(ctypes.byref(_desc(1, H, 128, 2215, lens, fp8, pre)), *[None] * 9)
     assert (st == b.USP_ERR_WORKSPACE) == (least > b.USP_NOALLOC_SCRATCH_BYTES) and st != b.USP_OK
+
+
+@pytest.mark.parametrize("lens,fp8,pre,masked", [((64, 128, 64), False, 0, False), ((513, 640), False, 0, False),
+                                                 ((513, 640), False, b.USP_ATTN_FUSED_PREFETCH, False),
+                                                 ((513, 640), True, 0, False), ((512, 640), False, 0, True)])
+def test_the_mixed_form_is_honoured_by_a_launch_per_chunk(lens, fp8, pre, masked):
+    H, Sq = (40, 1800) if not pre and not fp8 and lens[0] == 64 else (6, 300)     # more than one round of query blocks, or ragged
+    assert _route(1, H, 128, Sq, lens, fp8=fp8, flags=pre, masked=masked).one_launch
+    assert not _route(1, H, 128, Sq, lens, fp8=fp8, flags=pre | b.USP_ATTN_KERNEL_MIXED, masked=masked).one_launch
+
+
+def test_the_mixed_form_is_ignored_where_it_always_was():
+    assert _route(1, 6, 128, 300, (512, 640), flags=b.USP_ATTN_KERNEL_MIXED).one_launch
+    assert _route(1, 40, 128, 1800, (64, 128), flags=b.USP_ATTN_KERNEL_MIXED | b.USP_ATTN_FUSED_PREFETCH).one_launch
+    assert _route(1, 6, 64, 300, (513, 640), flags=b.USP_ATTN_KERNEL_MIXED).one_launch      # (d = 64 has no such form)

@@ -129,6 +129,16 @@ def test_short_chunks_under_more_than_one_round_of_query_blocks(d, Sq, lens):
     _parity(o, l, ro, rl)
 
 
+def test_the_mixed_form_of_a_ring_is_a_launch_per_chunk():
+    P = _P()
+    inp = W.make_attention_inputs(W.Workload("mixed", 8, 1, 40, 128, 1800, (64, 128, 64), "bf16"))
+    q, k, v = dev_bf16(inp.q), [dev_bf16(x) for x in inp.k], [dev_bf16(x) for x in inp.v]
+    o, l = P.usp_ring_attn_fwd(q, k, v, flags=P.USP_ATTN_KERNEL_MIXED)
+    o2, l2 = P.usp_ring_attn_fwd(q, k, v, flags=P.USP_ATTN_KERNEL_MIXED | P.USP_ATTN_STEPWISE)
+    torch.cuda.synchronize()
+    assert torch.equal(o, o2) and torch.equal(l, l2)
+
+
 def test_parts_need_no_more_workspace_than_there_is():
     """A workspace that holds a launch per chunk but not the parts is enough; one byte less is refused."""
     P = _P()
