@@ -23,7 +23,7 @@
 // cycles on the VALU (a third of that the split of P) and 29 % on the matrix cores, with waits between the phases of a
 // tile in the rest.  So: one barrier per tile where two buffers fit, tiles fetched through descriptors at places
 // fixed per thread, no test of a key outside masked and ragged tiles, no work for 16-wide blocks past the head
-// dimension, O rescaled only when a maximum has grown by more than 2^8.  B=2 H=16 S=1024 d=72 bf16: 32.7 us =
+// dimension, O rescaled only when a maximum has outgrown a reference that was set 2^8 above it.  B=2 H=16 S=1024 d=72 bf16: 32.7 us =
 // 295 TFLOP/s (38.6 before those; one wave per query row with scalar products, the first form, 856).
 // fp32 is bound by the fp32 matrix rate from about 256 work-groups on (d = 64, same sizes: 85 us, 100 TFLOP/s).
 // Two chunks of 128 keys, H=2 Sq=128 d=64 fp32: one launch of 9.8 us for two of 12.
@@ -394,7 +394,11 @@ void attn_tile_kernel(AttnStep s) {
   }
 
   for (int c = 0; c < s.n_multi; ++c) {
-    float m = -INFINITY, l = 0.0f;                              // m: a reference that lags the maximum by at most 2^8
+    // m: a reference that is never below the maximum (so that P <= 1, as V times a larger P could leave the fp32 range)
+    // and was set kAbove above the one that moved it last, so that it moves seldom.  fp32: less, because the exponents
+    // are rounded at their own size (d = 32, 1000 keys: O off by 6.3e-7 with 8)
+    constexpr float kAbove = std::is_same<QT, float>::value ? 2.0f : 8.0f;
+    float m = -INFINITY, l = 0.0f;
     f32x4 o[kDB];
 #pragma unroll
     for (int db = 0; db < kDB; ++db) o[db] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
@@ -432,10 +436,10 @@ void attn_tile_kernel(AttnStep s) {
       tm = group_max(tm);
       const float f = fp8 ? 1.0f : scale2;
       if (!fp8) tm *= scale2;
-      const bool jump = tm > m + 8.0f;                           // m = -inf: the first live key
+      const bool jump = tm > m;                                  // m = -inf: the first live key
       if (__builtin_amdgcn_ballot_w64(jump) != 0ull) {
-        const float alpha = jump ? __builtin_amdgcn_exp2f(m - tm) : 1.0f;
-        m = jump ? tm : m;
+        const float m_new = tm + kAbove, alpha = jump ? __builtin_amdgcn_exp2f(m - m_new) : 1.0f;
+        m = jump ? m_new : m;
         l *= alpha;
 #pragma unroll
         for (int db = 0; db < kDB; ++db) o[db] *= alpha;

@@ -69,3 +69,22 @@ def test_general_shapes(dtype, B, H, d, Sq, lens, masked, fp8):
     o2, l2 = P.usp_ring_attn_fwd(up(inp.q), ks, vs, flags=P.USP_ATTN_STEPWISE, **kw)
     torch.cuda.synchronize()
     assert torch.equal(o, o2) and torch.equal(l, l2)
+
+
+@pytest.mark.parametrize("dtype,d,Sq,H", [("bf16", 72, 20, 2), ("bf16", 72, 300, 60), ("f32", 64, 20, 2), ("f32", 64, 300, 60)])
+def test_values_near_the_end_of_the_fp32_range(dtype, d, Sq, H):
+    """|V| = 2e36 and scores that grow by less than 2^8 after the first tile: weights above 1 would take the sums
+    (64 keys of up to 180 times 2e36) out of the fp32 range.  Every key has the same V, so that O is V."""
+    import paper_2602_10940_amd as P
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    q = torch.zeros((1, H, Sq, d), dtype=dt, device=DEV)
+    q[..., 0] = 1.0
+    k = torch.zeros((1, H, 128, d), dtype=dt, device=DEV)
+    k[:, :, 64:, 0] = 5.1875                                   # 2^7.48 with a scale of 1
+    v = torch.full((1, H, 128, d), 2e36, dtype=dt, device=DEV)
+    o, l = P.usp_ring_attn_fwd(q, [k], [v], softmax_scale=1.0)
+    torch.cuda.synchronize()
+    # 128 roundings of a sum at most; bf16: one rounding of the output on top
+    tol = 128 * 2.0 ** -24 + (2.0 ** -8 if dtype == "bf16" else 0.0)
+    assert float((o.double() / v[:, :, :1].double() - 1.0).abs().max()) <= tol
+    assert float((l.double() - np.log(64.0 + 64.0 * np.exp(5.1875))).abs().max()) <= 2e-5
