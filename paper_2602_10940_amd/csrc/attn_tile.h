@@ -504,7 +504,8 @@ void attn_tile_kernel(AttnStep s) {
     }
     // the chunk's result and the merge of section 3.4
     float lse_r = -INFINITY, c_cur = 0.0f, w_prev = 0.0f;
-    if (l > 0.0f) { lse_r = (m + log2f(l)) * 0.69314718055994530942f; c_cur = 1.0f / l; }
+    // (log l apart from m ln 2, so that what is rounded is no larger than the result: in log2 units it would be by half)
+    if (l > 0.0f) { lse_r = fmaf(m, 0.69314718055994530942f, logf(l)); c_cur = 1.0f / l; }
     float lse_new = lse_r;
     if (carried) {
       const float mm = fmaxf(lse_c, lse_r);

@@ -88,3 +88,24 @@ def test_values_near_the_end_of_the_fp32_range(dtype, d, Sq, H):
     tol = 128 * 2.0 ** -24 + (2.0 ** -8 if dtype == "bf16" else 0.0)
     assert float((o.double() / v[:, :, :1].double() - 1.0).abs().max()) <= tol
     assert float((l.double() - np.log(64.0 + 64.0 * np.exp(5.1875))).abs().max()) <= 2e-5
+
+
+@pytest.mark.parametrize("dtype,B,H,d,Sq,lens", [("bf16", 2, 16, 72, 1024, (1024,)), ("bf16", 1, 4, 160, 300, (2000,)), ("f32", 2, 16, 32, 1000, (1000,)),
+                                                 ("f32", 1, 8, 96, 700, (513, 513))])
+def test_lse_is_as_exact_as_its_own_size_allows(dtype, B, H, d, Sq, lens):
+    """lse = m ln 2 + log l with |lse| in [4, 16): the logarithm and the sum are rounded once each at the result's
+    size or below (ulp 2^-21 to 8, 2^-20 beyond), and the scores, whose scale times log2 e is rounded once, move the
+    result by 2^-24 of their weighted mean, here below 4: two units of the last place in all, per chunk."""
+    import paper_2602_10940_amd as P
+    g = torch.Generator(device=DEV)
+    g.manual_seed(7)
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    q = torch.randn((B, H, Sq, d), generator=g, device=DEV).to(dt)
+    ks = [torch.randn((B, H, n, d), generator=g, device=DEV).to(dt) for n in lens]
+    scale = float(np.float32(1.0 / np.sqrt(d)))
+    _, l = P.usp_ring_attn_fwd(q, ks, ks, softmax_scale=scale)
+    z = torch.matmul(q.double(), torch.cat(ks, 2).double().transpose(2, 3).contiguous()) * scale
+    ref = torch.logsumexp(z, -1)
+    ulp = torch.where(ref < 8.0, 2.0 ** -21, 2.0 ** -20)
+    assert float(ref.min()) > 4.0 and float(ref.max()) < 16.0
+    assert float(((l.double() - ref).abs() / ulp).max()) <= 2.0 * len(lens)
