@@ -492,9 +492,10 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
   const uint32_t lds_v = __builtin_amdgcn_readfirstlane(lds_base + kStagesK * kTileB + 8 * wave * RB);
   // a tile of K or V: where it starts, and how many rows its chunk has from there on
   struct TileRef { const unsigned char* p; int left; };
+  // (the descriptor ends with the last row, not with the step to the one after it: 64 steps of 64 MB are 2^32)
   auto tile_desc = [&](TileRef t) -> u32x4 {
     const uint64_t p = (uint64_t)(uintptr_t)t.p;
-    return u32x4{(uint32_t)p, (uint32_t)(p >> 32) & 0xffffu, (uint32_t)min(t.left, kTile) * rowB, 0x00020000u};
+    return u32x4{(uint32_t)p, (uint32_t)(p >> 32) & 0xffffu, (uint32_t)min(t.left, kTile) * rowB - (rowB - RB), 0x00020000u};
   };
   auto issue_half = [&](const TileRef& t, uint32_t off, uint32_t lds, int half, bool pair) {
     if (kHalfD && half) return;               // one load covers the wave's 8 rows

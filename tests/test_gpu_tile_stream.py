@@ -129,6 +129,28 @@ def test_short_chunks_under_more_than_one_round_of_query_blocks(d, Sq, lens):
     _parity(o, l, ro, rl)
 
 
+@pytest.mark.parametrize("d,Sc,masked,flags", [(128, 64, True, 4), (128, 64, True, 8), (128, 100, False, 4), (128, 100, False, 8),
+                                               (64, 100, True, 0), (72, 100, True, 0), (72, 64, False, 0)])
+def test_token_strides_at_the_end_of_32_bits(d, Sc, masked, flags):
+    """Keys 64 MB apart: a tile's 64 steps are 2^32 bytes (d = 72: past what the general kernel reaches with 32 bits)."""
+    P = _P()
+    step = 1 << 25                                    # elements
+    store = torch.empty(((Sc - 1) * step + 2048,), dtype=torch.bfloat16, device=DEV)
+    k, v = (store.as_strided((1, 2, Sc, d), (step, 512, step, 1), off) for off in (0, 1024))
+    g = torch.Generator(device=DEV)
+    g.manual_seed(d + Sc)
+    for t in (k, v):
+        t.copy_(torch.randn((1, 2, Sc, d), generator=g, device=DEV))
+    q = torch.randn((1, 2, 50, d), generator=g, device=DEV).bfloat16()
+    keep = torch.ones((1, Sc), dtype=torch.uint8, device=DEV)
+    if masked:
+        keep[0, 3], keep[0, 60:63] = 0, 0
+    o, l = P.usp_ring_attn_fwd(q, [k], [v], key_mask=[keep] if masked else None, flags=flags)
+    z = torch.matmul(q.float(), k.float().transpose(2, 3).contiguous()) * d ** -0.5
+    z = z.masked_fill(keep[0] == 0, float("-inf"))
+    _parity(o, l, host_f64(torch.softmax(z, -1) @ v.float()), host_f64(torch.logsumexp(z, -1)))
+
+
 def test_the_mixed_form_of_a_ring_is_a_launch_per_chunk():
     P = _P()
     inp = W.make_attention_inputs(W.Workload("mixed", 8, 1, 40, 128, 1800, (64, 128, 64), "bf16"))
