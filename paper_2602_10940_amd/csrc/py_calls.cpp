@@ -11,6 +11,7 @@
 #include <Python.h>
 
 #include <ATen/ops/empty.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <exception>
@@ -120,11 +121,8 @@ PyObject* guarded(Py_ssize_t given, Py_ssize_t want, F body) {
     return body();
   } catch (const PyFailure&) {
     return nullptr;
-  } catch (const std::exception& e) {
-    PyErr_SetString(PyExc_RuntimeError, e.what());
-    return nullptr;
-  } catch (...) {
-    PyErr_SetString(PyExc_RuntimeError, "unknown C++ exception");
+  } catch (...) {   // torch's exceptions as torch's own functions raise them: OutOfMemoryError, IndexError, ..
+    torch::translate_exception_to_python(std::current_exception());
     return nullptr;
   }
 }

@@ -199,6 +199,15 @@ def test_missing_library_is_an_error_not_a_fallback(monkeypatch, tmp_path):
         b.usp_version()
 
 
+def test_the_extension_raises_torchs_own_exceptions():
+    """An error inside torch keeps its type on the way through _usp_calls.so (here: a tensor without a dimension)."""
+    import torch
+    from paper_2602_10940_amd import binding as b
+    x = torch.zeros(())
+    with pytest.raises(IndexError):
+        b.usp_lse_merge(x, x, x, x)
+
+
 def test_product_code_does_not_import_the_oracle():
     """oracle/ is test infrastructure: nothing under the package (Python or HIP sources) names it."""
     import glob

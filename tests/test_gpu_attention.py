@@ -677,3 +677,25 @@ def test_one_launch_masked_ring_with_every_key_of_an_entry_dead():
     o, l = _run(inp)
     _assert_parity(o, l, ro, rl)
     assert np.all(np.isneginf(l[1])) and np.all(o[1] == 0.0) and np.all(np.isfinite(l[0]))
+
+
+def test_a_workspace_that_cannot_be_allocated_is_torchs_out_of_memory_error():
+    """Programs catch torch.OutOfMemoryError and go on with smaller batches.  The allocator's own limit stands in
+    for a full device."""
+    P = _P()
+    q = torch.zeros((1, 24, 2048, 128), dtype=torch.bfloat16, device=DEV)
+    codes = [torch.zeros((1, 24, 2048, 128), dtype=torch.uint8, device=DEV) for _ in range(4)]
+    sc = [torch.ones((1, 24, 2048), device=DEV) for _ in range(4)]
+    out, lse = torch.empty_like(q), torch.empty((1, 24, 2048), device=DEV)
+    assert P.usp_ring_attn_workspace_bytes(P.make_attn_desc(q, codes, out)) > 64 << 20
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    torch.cuda.set_per_process_memory_fraction(1e-6)
+    try:
+        with pytest.raises(torch.OutOfMemoryError):
+            P.usp_ring_attn_fwd(q, codes, codes, k_scales=sc, v_scales=sc, out=out, lse=lse)
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    P.usp_ring_attn_fwd(q, codes, codes, k_scales=sc, v_scales=sc, out=out, lse=lse)
+    torch.cuda.synchronize()
+    assert torch.isfinite(lse).all()
