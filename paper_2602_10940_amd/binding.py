@@ -66,16 +66,13 @@ _calls = None   # the extension module _usp_calls
 
 
 def load_library() -> ctypes.CDLL:
-    """Load libusp.so and _usp_calls.so (built in-tree by paper_2602_10940_amd.build). Fails loudly if absent."""
-    global _lib, _calls
+    """Load libusp.so (built in-tree by paper_2602_10940_amd.build). Fails loudly if absent."""
+    global _lib
     if _lib is not None:
         return _lib
     if not os.path.exists(LIB_PATH):
         raise UspError(USP_ERR_HIP, "%s not found: run `python -m paper_2602_10940_amd.build` "
                        "(or __graft_entry__.build()) first; there is no fallback path" % LIB_PATH)
-    if not os.path.exists(CALLS_PATH):
-        raise UspError(USP_ERR_HIP, "%s not found: run `python -m paper_2602_10940_amd.build` first; there is no "
-                       "fallback path" % CALLS_PATH)
     lib = ctypes.CDLL(LIB_PATH)
     vp, i64, i32, sz = ctypes.c_void_p, ctypes.c_int64, ctypes.c_int32, ctypes.c_size_t
     lib.usp_last_error.restype = ctypes.c_char_p
@@ -99,16 +96,23 @@ def load_library() -> ctypes.CDLL:
     lib.usp_fp8_quant_mapped.argtypes = [ctypes.POINTER(RowMap), i64, i32, vp, vp, vp, vp]
     lib.usp_fp8_dequant_mapped.restype = i32
     lib.usp_fp8_dequant_mapped.argtypes = [ctypes.POINTER(RowMap), i64, i32, vp, vp, vp, vp]
-    from . import _usp_calls
-    _calls = _usp_calls
     _lib = lib
     return lib
 
 
 def _native():
-    """The extension module, loaded with the library."""
-    if _lib is None:
-        load_library()
+    """The extension module _usp_calls.so, which the calls that launch kernels go through.  The descriptors, the
+    size query and the error texts do without it."""
+    global _calls
+    if _calls is not None:
+        return _calls
+    load_library()
+    try:
+        from . import _usp_calls
+    except ImportError as e:   # not built, or built against another torch
+        raise UspError(USP_ERR_HIP, "%s cannot be loaded (%s): run `python -m paper_2602_10940_amd.build` with the installed "
+                       "torch; there is no fallback path" % (CALLS_PATH, e)) from e
+    _calls = _usp_calls
     return _calls
 
 

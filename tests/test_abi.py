@@ -199,6 +199,26 @@ def test_missing_library_is_an_error_not_a_fallback(monkeypatch, tmp_path):
         b.usp_version()
 
 
+def test_an_extension_that_does_not_load_is_a_usp_error(monkeypatch):
+    """_usp_calls.so built against another torch (or not at all): the calls raise UspError, and what needs no call
+    still works: the version, the size query and its error texts."""
+    import sys
+    import torch
+    import paper_2602_10940_amd as pkg
+    from paper_2602_10940_amd import binding as b
+    monkeypatch.setattr(b, "_calls", None)
+    monkeypatch.setattr(b, "_lib", None)
+    monkeypatch.delattr(pkg, "_usp_calls", raising=False)
+    monkeypatch.setitem(sys.modules, "paper_2602_10940_amd._usp_calls", None)      # import fails
+    q = torch.zeros((1, 2, 64, 128), dtype=torch.bfloat16)
+    assert b.usp_version().startswith("usp-")
+    assert b.usp_ring_attn_workspace_bytes(b.make_attn_desc(q, [q], q)) > 0
+    with pytest.raises(b.UspError, match="exclude"):
+        b.usp_ring_attn_workspace_bytes(b.make_attn_desc(q, [q], q, flags=b.USP_ATTN_KERNEL_WIDE | b.USP_ATTN_KERNEL_SPLIT))
+    with pytest.raises(b.UspError, match="no fallback"):
+        b.usp_lse_merge(q, q[..., 0].float(), q, q[..., 0].float())
+
+
 def test_the_extension_raises_torchs_own_exceptions():
     """An error inside torch keeps its type on the way through _usp_calls.so (here: a tensor without a dimension)."""
     import torch
