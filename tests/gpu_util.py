@@ -29,6 +29,21 @@ def host_bits_bf16(t: torch.Tensor) -> np.ndarray:
     return t.contiguous().view(torch.int16).cpu().numpy().view(np.uint16)
 
 
+def bf16_ulps(bits: np.ndarray, ref: np.ndarray) -> np.ndarray:
+    """Distance of bf16 values (as bits) from a float64 reference rounded to bf16, in units of the last place."""
+    def ordered(b):
+        b = b.astype(np.int32)
+        return np.where(b & 0x8000, -(b & 0x7fff), b)
+    return np.abs(ordered(bits) - ordered(W.f32_to_bf16_bits(ref.astype(np.float32))))
+
+
+# Where everything up to the rounding of a bf16 output is held in fp32, an entry differs from the rounded reference
+# only if that reference lies within the fp32 error (about 5e-7 of the output's size) of a rounding boundary; the
+# boundaries lie 2^-8 of the entry apart, which makes some hundredths of a per cent.  Weights rounded to bf16 are off by
+# 2^-9 each and move every third entry or so (test_oracle_attention.py shows both).
+BF16_MOVED = 0.01
+
+
 def attn_errors(got: np.ndarray, ref: np.ndarray):
     """(max-abs error, relative L2 error) of an attention output against the oracle."""
     diff = got - ref

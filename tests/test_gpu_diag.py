@@ -129,6 +129,28 @@ def test_arrival_wait_that_gives_up_returns_nan_rows(kind, flags):
     assert torch.equal(o, ref_o) and torch.equal(l, ref_l)
 
 
+@pytest.mark.parametrize("kind,flags", [("bf16", FUSED), ("fp8", 0)])
+def test_arrival_wait_that_gives_up_returns_nan_rows_through_shared_keys(kind, flags):
+    """The same where several work-groups share a query block's keys: those whose part lies in the first chunk wait
+    for nothing and finish theirs, and the launch that puts the parts together must still return NaN."""
+    import paper_2602_10940_amd as U
+    from paper_2602_10940_amd import diag
+    r = _ring(kind, shape=(1, 2, 128, 140, (1408, 1408, 1408)))
+    desc = U.make_attn_desc(r["q"], r["k_chunks"], torch.empty_like(r["q"]), r["softmax_scale"], flags)
+    route = diag.usp_diag_attn_route(desc)
+    assert route.one_launch and route.parts > 3                    # more parts than chunks
+    ws = torch.full((U.usp_ring_attn_workspace_bytes(desc),), 0xFF, dtype=torch.uint8, device=DEV)
+    ref_o, ref_l = U.usp_ring_attn_fwd(flags=flags, workspace=ws, **r)
+    torch.cuda.synchronize()
+    assert torch.isfinite(ref_o.float()).all() and torch.isfinite(ref_l).all()
+    o, l = diag.usp_diag_ring_attn_fwd_wait(arrive_need_extra=1, arrive_polls=200, flags=flags, workspace=ws, **r)
+    torch.cuda.synchronize()
+    assert torch.isnan(o.float()).all() and torch.isnan(l).all()
+    o, l = U.usp_ring_attn_fwd(flags=flags, workspace=ws, **r)
+    torch.cuda.synchronize()
+    assert torch.equal(o, ref_o) and torch.equal(l, ref_l)
+
+
 def test_arrival_wait_knobs_are_ignored_by_other_forms_and_checked():
     import paper_2602_10940_amd as U
     from paper_2602_10940_amd import diag

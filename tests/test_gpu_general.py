@@ -3,14 +3,15 @@ size class of the head dimension and its edges, waves that share queries and wav
 empty and masked chunks, FP8 K/V.  Bars: fp32 results 2e-5 / 5e-6 / 2e-5 as elsewhere; bf16 results carry
 the rounding of the output plus the fp32 bar, because nothing inside is rounded to bf16: with 8 significant
 bits a value in [2^e, 2^(e+1)) has neighbours 2^(e-7) apart, so rounding to nearest moves it by at most
-2^(e-8), which is at most 2^-8 of the value."""
+2^(e-8), which is at most 2^-8 of the value.  That alone would let weights in bf16 pass, so the entries that
+differ from the rounded oracle are counted too (BF16_MOVED)."""
 import numpy as np
 import pytest
 import torch
 
 from oracle import usp_oracle as orc
 from paper_2602_10940_amd import workloads as W
-from tests.gpu_util import DEV, attn_errors, dev_bf16, dev_f32, host_f64
+from tests.gpu_util import BF16_MOVED, DEV, attn_errors, bf16_ulps, dev_bf16, dev_f32, host_bits_bf16, host_f64
 
 pytestmark = pytest.mark.gpu
 
@@ -65,10 +66,37 @@ def test_general_shapes(dtype, B, H, d, Sq, lens, masked, fp8):
     size = max(1.0, float(np.max(np.abs(ro))))
     out_max, out_rel = (0.0, 0.0) if dtype == "f32" else (2.0 ** -8 * size, 2.0 ** -8)
     assert mx <= 2e-5 * size + out_max and rel <= 5e-6 + out_rel and np.max(np.abs(got_l - rl)[fin], initial=0.0) <= 2e-5, (mx, rel)
+    if dtype == "bf16":
+        moved = np.count_nonzero(bf16_ulps(host_bits_bf16(o), ro))
+        assert moved <= max(1, BF16_MOVED * ro.size), (moved, ro.size)
     # one launch over the chunks and a launch per chunk: the same operations, the same bits
     o2, l2 = P.usp_ring_attn_fwd(up(inp.q), ks, vs, flags=P.USP_ATTN_STEPWISE, **kw)
     torch.cuda.synchronize()
     assert torch.equal(o, o2) and torch.equal(l, l2)
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 72), ("f32", 64), ("bf16", 160)])
+@pytest.mark.parametrize("lens", [(100, 65), (64, 64, 30)])
+def test_strided_chunks_with_nothing_readable_behind_them(dtype, d, lens):
+    """[B, S, H, d] storage of several chunks in one launch; the tokens behind each chunk's last one are NaN."""
+    import paper_2602_10940_amd as P
+    B, H, Sq, room = 2, 3, 70, 160
+    inp = W.make_attention_inputs(W.Workload("strided", 90 + d, B, H, d, Sq, lens, dtype))
+    up = dev_f32 if dtype == "f32" else dev_bf16
+
+    def view(x):
+        t = up(x)
+        store = torch.full((B, room, H, d), float("nan"), dtype=t.dtype, device=DEV)
+        store[:, :x.shape[2]] = t.transpose(1, 2)
+        return store[:, :x.shape[2]].transpose(1, 2)
+    q, scale = up(inp.q), float(inp.softmax_scale)
+    o, l = P.usp_ring_attn_fwd(q, [view(k) for k in inp.k], [view(v) for v in inp.v], softmax_scale=scale)
+    o2, l2 = P.usp_ring_attn_fwd(q, [up(k) for k in inp.k], [up(v) for v in inp.v], softmax_scale=scale)
+    torch.cuda.synchronize()
+    assert torch.equal(o, o2) and torch.equal(l, l2)
+    ro, rl = orc.ring_attention(inp.q, inp.k, inp.v, scale)
+    mx, rel = attn_errors(host_f64(o), ro)
+    assert rel <= (5e-6 if dtype == "f32" else 2.0 ** -8) and np.max(np.abs(host_f64(l) - rl)) <= 2e-5
 
 
 @pytest.mark.parametrize("dtype,d,Sq,H", [("bf16", 72, 20, 2), ("bf16", 72, 300, 60), ("f32", 64, 20, 2), ("f32", 64, 300, 60)])

@@ -5,6 +5,7 @@ import pytest
 import torch
 
 from oracle import usp_oracle as orc
+from paper_2602_10940_amd import diag
 from paper_2602_10940_amd import workloads as W
 from tests.gpu_util import DEV, dev_bf16, host_f64
 from tests.test_gpu_fp8_ring import _fp8_ring
@@ -177,10 +178,11 @@ def test_parts_need_no_more_workspace_than_there_is():
         P.usp_ring_attn_fwd(q, k, v, workspace=torch.empty((least - 1,), dtype=torch.uint8, device=DEV))
 
 
-@pytest.mark.parametrize("split", [False, True])
+@pytest.mark.parametrize("split", [False, True, None])
 @pytest.mark.parametrize("n", [1, 2])
 def test_more_dead_tiles_than_words(n, split):
-    """250 007 keys, ragged and masked: beyond the words a work-group keeps in LDS.  Reference in fp32."""
+    """250 007 keys, ragged and masked: beyond the words a work-group keeps in LDS.  None: the plain call, which
+    shares the keys of the one chunk between work-groups.  Reference in fp32."""
     P = _P()
     g = torch.Generator(device=DEV)
     g.manual_seed(3)
@@ -190,10 +192,32 @@ def test_more_dead_tiles_than_words(n, split):
     keep[:, 1000:1500] = 0
     keep[:, total - 70000:] = 0
     lens = (total,) if n == 1 else (130001, total - 130001)
-    o, l = P.usp_ring_attn_fwd(q, [x.contiguous() for x in k.split(lens, 2)], [x.contiguous() for x in v.split(lens, 2)],
-                               key_mask=[x.contiguous() for x in keep.split(lens, 1)],
-                               flags=P.USP_ATTN_KERNEL_SPLIT if split else P.USP_ATTN_KERNEL_WIDE)
+    flags = 0 if split is None else P.USP_ATTN_KERNEL_SPLIT if split else P.USP_ATTN_KERNEL_WIDE
+    ks, vs = [x.contiguous() for x in k.split(lens, 2)], [x.contiguous() for x in v.split(lens, 2)]
+    route = diag.usp_diag_attn_route(P.make_attn_desc(q, ks, q, flags=flags), masked=True)
+    assert not route.one_launch and (route.parts > 1) == (split is None and n == 1)
+    o, l = P.usp_ring_attn_fwd(q, ks, vs, key_mask=[x.contiguous() for x in keep.split(lens, 1)], flags=flags)
     s = (q[0, 0].float() @ k[0, 0].float().T) * 128 ** -0.5
     s = s.masked_fill(keep[0] == 0, float("-inf"))
     ro, rl = torch.softmax(s, -1) @ v[0, 0].float(), torch.logsumexp(s, -1)
     _parity(o, l, host_f64(ro[None, None]), host_f64(rl[None, None]))
+
+
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("flags", [0, 4, 8])
+@pytest.mark.parametrize("Sc,n", [(37, 1), (97, 1), (1000, 1), (545, 2)])
+def test_nothing_behind_a_ragged_chunk_is_read(d, flags, Sc, n):
+    """The rows behind each head's last key are NaN: they load as zeros, in the lower and the upper half of a tile."""
+    P = _P()
+    B, H, Sq = 2, 2, 140
+    inp = W.make_attention_inputs(W.Workload("behind", 60 + Sc, B, H, d, Sq, (Sc,) * n, "bf16"))
+
+    def view(x):
+        store = torch.full((B, H, Sc + 64, d), float("nan"), dtype=torch.bfloat16, device=DEV)
+        store[:, :, :Sc] = dev_bf16(x)
+        return store[:, :, :Sc]
+    o, l = P.usp_ring_attn_fwd(dev_bf16(inp.q), [view(k) for k in inp.k], [view(v) for v in inp.v],
+                               softmax_scale=float(inp.softmax_scale), flags=flags)
+    torch.cuda.synchronize()
+    ro, rl = orc.ring_attention(inp.q, inp.k, inp.v, float(inp.softmax_scale))
+    _parity(o, l, ro, rl)

@@ -14,6 +14,7 @@ import pytest
 import torch
 
 from oracle import usp_oracle as orc
+from paper_2602_10940_amd import workloads as W
 
 
 def _rand(seed, *shape):
@@ -282,3 +283,22 @@ def test_merge_infinities_and_large_lse():
     assert abs(l[3] - (700.0 + math.log1p(math.exp(-1.0)))) < 1e-12
     w = 1.0 / (1.0 + math.exp(-1.0))
     np.testing.assert_allclose(o[3], w * o1[3] + (1 - w) * o2[3], atol=1e-13)
+
+
+def test_counting_moved_entries_tells_bf16_weights_from_fp32_ones():
+    """The count that the GPU tests of bf16 outputs use (gpu_util.BF16_MOVED): weights held in fp32 pass it with room to
+    spare, weights rounded to bf16 fail it by far."""
+    from tests.gpu_util import BF16_MOVED, bf16_ulps
+    rng = np.random.default_rng(11)
+    for d, n in ((40, 77), (72, 130), (160, 50)):
+        q, k, v = (W.bf16_bits_to_f32(W.f32_to_bf16_bits(rng.standard_normal((1, 3, n, d)).astype(np.float32))).reshape(1, 3, n, d) for _ in range(3))
+        ro, _ = orc.ring_attention(q, [k], [v], d ** -0.5)
+        s = np.einsum("bhqd,bhkd->bhqk", q.astype(np.float64), k.astype(np.float64)) * d ** -0.5
+        p = np.exp(s - s.max(-1, keepdims=True))
+        for cast, moved_much in ((lambda x: x.astype(np.float32), False),
+                                 (lambda x: W.bf16_bits_to_f32(W.f32_to_bf16_bits(x.astype(np.float32))).reshape(x.shape), True)):
+            w = cast(p).astype(np.float32)
+            o = np.einsum("bhqk,bhkd->bhqd", w, v.astype(np.float32)) / p.sum(-1, keepdims=True).astype(np.float32)
+            bits = W.f32_to_bf16_bits(o.astype(np.float32))
+            share = np.count_nonzero(bf16_ulps(bits, ro)) / ro.size
+            assert (share > 10 * BF16_MOVED) if moved_much else (share < 0.5 * BF16_MOVED), (d, moved_much, share)
