@@ -500,8 +500,7 @@ def ring_leg(P, W, torch, dev, up_bf16, name="flux1024_r4", reps=600):
     t_mk_1 = timed(lambda: P.usp_ring_attn_fwd(q, ks, vs, key_mask=km, softmax_scale=scale, out=out, lse=lse, workspace=ws1))
     masked = {"dead_keys": int(sum(wl.chunk_len) // 10), "t_per_chunk_ms": round(t_mk_c, 4), "t_plain_call_ms": round(t_mk_1, 4),
               "plain_call_over_unmasked_one_launch": round(t_mk_1 / t_1, 3),
-              "note": "the plain call takes one launch over the ring (per-tile records for every chunk) where the ring "
-                      "steps are short or every chunk is masked, else one launch per chunk"}
+              "note": "the plain call takes one launch over the ring; its work-groups keep the dead keys as a word per tile"}
     hid = lambda t: round(max(0.0, min(1.0, 1.0 - (t - t_c) / t_m)), 3) if t_m > 0 else None
     return {"workload": "%s: Sq=%d, %d chunks of %d, H=%d d=%d bf16" % (name, wl.Sq, wl.W, wl.chunk_len[0], wl.H, wl.d),
             "t_compute_ms": round(t_c, 4), "t_copies_ms": round(t_m, 4),

@@ -66,8 +66,7 @@ typedef enum {
                                         arrival): the same work-groups decode each chunk while they
                                         copy it, into bf16 K (the codes as they are), bf16 V (codes
                                         times scales) and K's scales as per-key factors of the exponent;
-                                        the first chunk is decoded by a launch of its own in front;
-                                        key masks go into the records as well. */
+                                        the first chunk is decoded by a launch of its own in front. */
 /* Work decomposition of the matrix-core launches (bf16 Q, d = 128 or 64), masked and ragged chunks
  * included.  Default (none of the bits): chosen from the number of work-groups the Q shard gives and, with
  * several chunks, from their tiles.  A forced form does not share keys between work-groups.  All variants

@@ -15,13 +15,15 @@
 //   * Per-key factors: FP8 scales of K multiply the fp32 scores, those of V multiply P.
 //   * 64-key tiles are staged in LDS by the whole work-group through registers, a tile's global loads being in
 //     flight while the one before it is computed on.  Pitches are odd multiples of 16 bytes (K) and of 32
-//     bytes (V of Bf16Q, read transposed), or d + 4 words (F32Q): no bank conflicts by construction.
+//     bytes (V of Bf16Q, read transposed), or d + 4 words (F32Q): no bank conflicts in the operand reads.  The staging
+//     writes are not free of them: SQ_LDS_BANK_CONFLICT reads 32, 64, 64 and 96 cycles per wave and tile for d = 40,
+//     72, 112 and 160 bf16, 8 to 11 for each of the wave's 4, 6, 8 and 10 writes, a quarter to a third of the LDS cycles.
 //   * kKW waves share the 16 queries and take 64 / kKW keys of every tile each, their partial results
 //     being combined through LDS at the end of a chunk: for calls with few query blocks.
 //
 // What bounds it (bf16, d = 72, two work-groups per CU): the instructions its two waves per SIMD issue, 43 % of the
-// cycles on the VALU (a third of that the split of P) and 29 % on the matrix cores, with waits between the phases of a
-// tile in the rest.  So: one barrier per tile where two buffers fit, tiles fetched through descriptors at places
+// cycles on the VALU (191 instructions per wave and tile besides the 42 MFMAs, a third of them the split of P) and 29 %
+// on the matrix cores, with 49 scalar and 39 LDS instructions and waits between the phases of a tile in the rest.  So: one barrier per tile where two buffers fit, tiles fetched through descriptors at places
 // fixed per thread, no test of a key outside masked and ragged tiles, no work for 16-wide blocks past the head
 // dimension, O rescaled only when a maximum has outgrown a reference that was set 2^8 above it.  B=2 H=16 S=1024 d=72 bf16: 32.7 us =
 // 295 TFLOP/s (38.6 before those; one wave per query row with scalar products, the first form, 856).

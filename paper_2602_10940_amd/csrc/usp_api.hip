@@ -94,8 +94,11 @@ bool o_dense(const usp_attn_desc* d) {
 // `least`) ragged ones: FP8 chunks of any lengths, bf16 chunks of at least kRaggedRing keys on average.  A ring
 // of ragged chunks as one launch saves per chunk a launch gap, a pipeline fill and the carried state's round
 // trip (12 heads, two chunks of 2215 98 -> 70 us; FP8, 8 heads with 70 queries, two of 70 33.9 -> 21.3).
-// Shorter ragged bf16 rings keep their launch per chunk, and with it the bits that USP_ATTN_DOUBLE_BUFFER
-// gives for the same ring; from there on the two agree up to rounding order, as they do on whole tiles.
+// Shorter ragged bf16 rings keep their launch per chunk.  Not for speed: the one launch takes 0.20 to 0.70 of the time
+// there as well (40 random rings of 33 to 640 keys a chunk; B = 2, H = 14, Sq = 219, six of 219 98 against 38 us; H = 3,
+// Sq = 75, two of 38 20.7 against 11.7), but USP_ATTN_DOUBLE_BUFFER, which has a launch per chunk in any case, would
+// no longer give the plain call's bits for short ragged rings, as programs and tests (288 keys a chunk) have had it.
+// From 320 on the two agree up to rounding order, as they do on whole tiles.
 constexpr int kRaggedRing = 320;
 bool one_launch_lengths(const usp_attn_desc* d, bool least, bool* whole, size_t* tiles) {
   int live = 0;
