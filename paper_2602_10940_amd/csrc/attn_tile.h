@@ -10,8 +10,8 @@
 //     layout is the B operand of O^T += V^T P^T as it stands.
 //   * bf16 Q (engine Bf16Q): v_mfma_f32_16x16x32_bf16.  Products of bf16 values (and of E4M3 codes, which
 //     are bf16 values) are exact in fp32; P is not rounded but split into three bf16 parts that add up
-//     to its 24 bits, so P.V is three exact products instead of one.  fp32 Q (engine F32Q):
-//     v_mfma_f32_16x16x4_f32.
+//     to its 24 bits, so P.V is three exact products instead of one (of finite V: a part that is 0 times
+//     infinity is NaN).  fp32 Q (engine F32Q): v_mfma_f32_16x16x4_f32.
 //   * Per-key factors: FP8 scales of K multiply the fp32 scores, those of V multiply P.
 //   * 64-key tiles are staged in LDS by the whole work-group through registers, a tile's global loads being in
 //     flight while the one before it is computed on.  Pitches are odd multiples of 16 bytes (K) and of 32
