@@ -222,7 +222,7 @@ struct RingCall {
   usp_attn_desc desc;
   std::vector<int32_t> lens;
   std::vector<const void*> k, v, ks, vs, mask;
-  bool has_ks = false, has_vs = false, has_mask = false;
+  bool has_v = false, has_ks = false, has_vs = false, has_mask = false;
   const void* q;
   void* out;
   float* lse;
@@ -277,12 +277,12 @@ int describe(PyObject* const* a, RingCall* c) {
   d.flags = (uint32_t)whole(a[7]);
   c->q = q.data_ptr();
   addresses(a[1], &c->k);
-  addresses(a[2], &c->v);
+  c->has_v = addresses(a[2], &c->v);
   c->has_ks = addresses(a[3], &c->ks);
   c->has_vs = addresses(a[4], &c->vs);
   c->has_mask = addresses(a[5], &c->mask);
   // (the library reads n_chunks entries of each)
-  require(c->v.size() >= c->k.size() && (!c->has_ks || c->ks.size() >= c->k.size()) && (!c->has_vs || c->vs.size() >= c->k.size()) &&
+  require((!c->has_v || c->v.size() >= c->k.size()) && (!c->has_ks || c->ks.size() >= c->k.size()) && (!c->has_vs || c->vs.size() >= c->k.size()) &&
               (!c->has_mask || c->mask.size() >= c->k.size()),
           "one entry per chunk is needed in v_chunks, k_scales, v_scales and key_mask");
   c->out = out.data_ptr();
@@ -314,7 +314,7 @@ PyObject* ring_attn_fwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
     void* cs = stream_handle(a[11]);
     void* xs = a[12] == Py_None ? nullptr : stream_handle(a[12]);
     const int status = unlocked([&] {
-      return usp_ring_attn_fwd(&c.desc, c.q, c.k.data(), c.v.data(), c.has_ks ? (const float* const*)c.ks.data() : nullptr,
+      return usp_ring_attn_fwd(&c.desc, c.q, c.k.data(), c.has_v ? c.v.data() : nullptr, c.has_ks ? (const float* const*)c.ks.data() : nullptr,
                                c.has_vs ? (const float* const*)c.vs.data() : nullptr,
                                c.has_mask ? (const uint8_t* const*)c.mask.data() : nullptr, c.out, c.lse, ws, ws_bytes, cs, xs);
     });
@@ -331,7 +331,7 @@ PyObject* ring_attn_fwd_noalloc(PyObject*, PyObject* const* a, Py_ssize_t n) {
     if (st != USP_OK) return PyLong_FromLong(st);
     void* cs = stream_handle(a[10]);
     return PyLong_FromLong(unlocked([&] {
-      return usp_ring_attn_fwd_noalloc(&c.desc, c.q, c.k.data(), c.v.data(), c.has_ks ? (const float* const*)c.ks.data() : nullptr,
+      return usp_ring_attn_fwd_noalloc(&c.desc, c.q, c.k.data(), c.has_v ? c.v.data() : nullptr, c.has_ks ? (const float* const*)c.ks.data() : nullptr,
                                        c.has_vs ? (const float* const*)c.vs.data() : nullptr,
                                        c.has_mask ? (const uint8_t* const*)c.mask.data() : nullptr, c.out, c.lse, cs);
     }));

@@ -219,6 +219,22 @@ def test_an_extension_that_does_not_load_is_a_usp_error(monkeypatch):
         b.usp_lse_merge(q, q[..., 0].float(), q, q[..., 0].float())
 
 
+def test_missing_inputs_are_the_librarys_errors():
+    """No V, or a chunk without one: refused by the library with its text, before anything is launched."""
+    import torch
+    from paper_2602_10940_amd import binding as b
+    q, s = torch.zeros((1, 2, 64, 128), dtype=torch.bfloat16), 1     # (a stream handle: nothing asks the driver for one)
+    for v in (None, [None]):
+        with pytest.raises(b.UspError, match="NULL") as e:
+            b.usp_ring_attn_fwd(q, [q], v, compute_stream=s)
+        assert e.value.status == b.USP_ERR_INVALID_ARG
+    codes = q.to(torch.uint8)
+    with pytest.raises(b.UspError, match="needs k_scales and v_scales"):
+        b.usp_ring_attn_fwd(q, [codes], [codes], compute_stream=s)
+    with pytest.raises(AssertionError, match="one entry per chunk"):
+        b.usp_ring_attn_fwd(q, [q, q], [q], compute_stream=s)
+
+
 def test_the_extension_raises_torchs_own_exceptions():
     """An error inside torch keeps its type on the way through _usp_calls.so (here: a tensor without a dimension)."""
     import torch
