@@ -23,12 +23,13 @@
 //
 // What bounds it (bf16, d = 72, two work-groups per CU): the instructions its two waves per SIMD issue, 43 % of the
 // cycles on the VALU (191 instructions per wave and tile besides the 42 MFMAs, a third of them the split of P) and 29 %
-// on the matrix cores, with 49 scalar and 39 LDS instructions and waits between the phases of a tile in the rest.  So: one barrier per tile where two buffers fit, tiles fetched through descriptors at places
-// fixed per thread, no test of a key outside masked and ragged tiles, no work for 16-wide blocks past the head
-// dimension, O rescaled only when a maximum has outgrown a reference that was set 2^8 above it.  B=2 H=16 S=1024 d=72 bf16: 32.7 us =
-// 295 TFLOP/s (38.6 before those; one wave per query row with scalar products, the first form, 856).
-// fp32 is bound by the fp32 matrix rate from about 256 work-groups on (d = 64, same sizes: 85 us, 100 TFLOP/s).
-// Two chunks of 128 keys, H=2 Sq=128 d=64 fp32: one launch of 9.8 us for two of 12.
+// on the matrix cores, with 49 scalar and 39 LDS instructions and waits between the phases of a tile in the rest. So:
+// one barrier per tile where two buffers fit, tiles fetched through descriptors at places fixed per thread, no test of
+// a key outside masked and ragged tiles, no work for 16-wide blocks past the head dimension, O rescaled only when a
+// maximum has outgrown a reference that was set 2^8 above it. B=2 H=16 S=1024 d=72 bf16: 32.7 us = 295 TFLOP/s (38.6
+// before those; one wave per query row with scalar products, the first form, 856). fp32 is bound by the fp32 matrix
+// rate from about 256 work-groups on (d = 64, same sizes: 85 us, 100 TFLOP/s). Two chunks of 128 keys, H=2 Sq=128 d=64
+// fp32: one launch of 9.8 us for two of 12.
 #pragma once
 #include <type_traits>
 
