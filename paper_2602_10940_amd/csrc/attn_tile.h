@@ -28,7 +28,7 @@
 // a key outside masked and ragged tiles, no work for 16-wide blocks past the head dimension, O rescaled only when a
 // maximum has outgrown a reference that was set 2^8 above it. B=2 H=16 S=1024 d=72 bf16: 32.7 us = 295 TFLOP/s (38.6
 // before those; one wave per query row with scalar products, the first form, 856). fp32 is bound by the fp32 matrix
-// rate from about 256 work-groups on (d = 64, same sizes: 85 us, 100 TFLOP/s). Two chunks of 128 keys, H=2 Sq=128 d=64
+// rate from about 256 work-groups on (d = 64, same sizes: 81 us, 106 TFLOP/s). Two chunks of 128 keys, H=2 Sq=128 d=64
 // fp32: one launch of 9.8 us for two of 12.
 #pragma once
 #include <type_traits>
