@@ -56,9 +56,9 @@ constexpr int kTileB = kTile * kRowB;          // 16 KB
 // last item return false.
 constexpr int kXcds = 8;
 constexpr int kSplitBelowWGs = 128;   // use the key-split kernel when 256-query work-groups number at most this
-__device__ __forceinline__ bool wg_to_tile(int copy_wgs, int nqb, int bh_total, int& bh, int& qb, int lead = 0) {
+__device__ __forceinline__ bool wg_to_tile(int attn_wgs, int nqb, int bh_total, int& bh, int& qb, int lead = 0) {
   const int id = blockIdx.x - lead;                   // the copy work-groups are the last ids of the grid, or the first `lead` (a multiple of 8)
-  const int per_xcd = ((int)gridDim.x - copy_wgs) / kXcds;
+  const int per_xcd = attn_wgs / kXcds;
   const int item = (id % kXcds) * per_xcd + id / kXcds;
   bh = item / nqb;
   qb = item - bh * nqb;
@@ -110,107 +110,139 @@ __device__ __forceinline__ RowFinish finish_row(const AttnStep& s, float m, floa
   return f;
 }
 
-// Chunk result, merge and store straight from the accumulator layout (a lane holds four consecutive head
-// dims of a query: 8 bytes of bf16 or 16 bytes of the fp32 carry per store): what the key-split
-// work-groups use, whose epilogue is too short for the detour through LDS to pay.
+// Chunk result, merge and store.  In the accumulator layout a store would touch 16 rows with 16 or 32 bytes each, and the
+// CU's one address unit takes a cycle per line and quad of lanes: the key-split work-groups, which once stored so, spent
+// 6400 cycles there (and as many branches on the mode as stores).  So a wave turns its O~ tile through its own LDS
+// region (a row pitch 16 bytes past a multiple of 128, so that rows do not all start in the same bank) and moves whole
+// rows: 16 lanes (kHalfD: 8) x 32 bytes of fp32 or 16 bytes of bf16 per row.
+//   wide : a wave has its own 32 queries; only it touches its region, and the LDS operations of one wave complete in
+//          order, so no barrier is needed.
+//   split: waves w and w + 4 hold the same 32 queries over different keys.  Both stage, and behind a barrier wave w puts the
+//          two together for the first 16 queries, wave w + 4 for the others.
 // kHalfD: head dimension 64: only the first four 16-wide blocks exist, rows are 64 wide everywhere.
-template <bool kHalfD>
-__device__ __forceinline__ void finish_and_store_direct(const AttnStep& s, f32x4 (&oacc)[8][2], const float (&m)[2],
-                                                        const float (&lsum)[2], int b, int h, int q0, int r, int g, bool invalid,
-                                                        int part) {
-  constexpr int kDB = kHalfD ? 4 : 8;
-  constexpr int kAccP = kHalfD ? 64 : kD;   // floats per row of the carried O
-  const int64_t rows = (int64_t)s.B * s.H * s.Sq;
+constexpr int kEpiPitch = kD * 4 + 16;                    // bytes per staged row
+constexpr int kEpiInfoB = kQPerWave * 32 + 16 * 16;       // per row: m, four partial sums l (split) or scale of O~, weight of the carry (wide); split: the 16 rows' weights
+constexpr int kEpiWaveB = kQPerWave * kEpiPitch + kEpiInfoB;
+
+// Rows 0 .. rows - 1 of the wave's share, of them `valid` (may be <= 0) exist.  a, b: the staged rows (b of the other half of
+// the keys, split only); info: per row {weight of a, weight of b, scale, weight of the carry}.  kCarry: fold the carried O
+// in; kF32: the result is the fp32 carry (or a part), dst32, else bf16.  row0: first row in the dense fp32 tensors.
+template <bool kSplit, bool kHalfD, bool kCarry, bool kF32>
+__device__ __forceinline__ void store_rows(const unsigned char* a, const unsigned char* b, const f32x4* info, int lane, int valid,
+                                           const float* carry, float* dst32, bf16_t* dst16, int64_t stride16) {
+  constexpr int kLPR = kHalfD ? 8 : 16, kRPI = 64 / kLPR;           // lanes per row, rows per instruction
+  constexpr int kRows = kSplit ? 16 : kQPerWave, kRowF = kHalfD ? 64 : kD;
+  const int sub = lane / kLPR, c = lane % kLPR;
 #pragma unroll
-  for (int nb = 0; nb < 2; ++nb) {
-    const float l = xgroup_sum(lsum[nb]);
-    const int qi = q0 + 16 * nb + r;
-    const bool valid = qi < s.Sq;
-    const int64_t row = ((int64_t)b * s.H + h) * s.Sq + (valid ? qi : s.Sq - 1);
-    RowFinish f = finish_row(s, m[nb], l, row, invalid);
-    if (s.parts > 1 && !invalid) f.c_cur = 1.0f;   // a part's O~, m and l are kept as they are (attn_combine_kernel)
-    if (!valid) continue;
-    float* accp = s.parts > 1 ? s.part_o + (part * rows + row) * kAccP : s.acc ? s.acc + row * kAccP : nullptr;
-    bf16_t* outp = (bf16_t*)s.out + b * s.os[0] + h * s.os[1] + (int64_t)qi * s.os[2];
+  for (int it = 0; it < kRows / kRPI; ++it) {
+    const int rr = it * kRPI + sub;
+    if (rr >= valid) continue;
+    const f32x4 w = info[rr];
+    f32x4 o[2];
 #pragma unroll
-    for (int db = 0; db < kDB; ++db) {
-      const int dcol = 16 * db + 4 * g;
-      float o[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) o[e] = oacc[db][nb][e] * f.c_cur;
-      if (s.mode >= 2) {
-        const float4 p = *reinterpret_cast<const float4*>(accp + dcol);
-        o[0] = fmaf(f.w_prev, p.x, o[0]); o[1] = fmaf(f.w_prev, p.y, o[1]);
-        o[2] = fmaf(f.w_prev, p.z, o[2]); o[3] = fmaf(f.w_prev, p.w, o[3]);
+    for (int u = 0; u < 2; ++u) {
+      o[u] = *reinterpret_cast<const f32x4*>(a + rr * kEpiPitch + c * 32 + u * 16);
+      if (kSplit) {
+        const f32x4 p = *reinterpret_cast<const f32x4*>(b + rr * kEpiPitch + c * 32 + u * 16);
+        o[u] = w[0] * o[u] + w[1] * p;
       }
-      if (s.mode == 1 || s.mode == 2 || s.parts > 1)
-        *reinterpret_cast<float4*>(accp + dcol) = make_float4(o[0], o[1], o[2], o[3]);
-      else
-        *reinterpret_cast<uint2*>(outp + dcol) = make_uint2(pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3]));
+      o[u] = o[u] * w[2];
     }
-    if (g == 0) {
-      if (s.parts > 1) *reinterpret_cast<float2*>(s.part_ml + 2 * (part * rows + row)) = make_float2(m[nb], invalid ? f.c_cur : l);
-      else s.lse[row] = f.lse_new;
+    if (kCarry) {
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const f32x4 p = *reinterpret_cast<const f32x4*>(carry + (int64_t)rr * kRowF + 8 * c + 4 * u);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[u][e] = fmaf(w[3], p[e], o[u][e]);
+      }
+    }
+    if (kF32) {
+#pragma unroll
+      for (int u = 0; u < 2; ++u) *reinterpret_cast<f32x4*>(dst32 + (int64_t)rr * kRowF + 8 * c + 4 * u) = o[u];
+    } else {
+      // the final output is not read again here: a streaming store leaves no dirty line for the end of the kernel to
+      // write back (the fp32 carry above is re-read by the next step and stays cached)
+      const u32x4 v = {pack_bf16x2(o[0][0], o[0][1]), pack_bf16x2(o[0][2], o[0][3]), pack_bf16x2(o[1][0], o[1][1]), pack_bf16x2(o[1][2], o[1][3])};
+      __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(dst16 + rr * stride16 + 8 * c));
     }
   }
 }
 
-// The same for the 256-query work-groups.  In the accumulator layout direct stores would touch 16 rows
-// with 32 bytes each per instruction.  The wave therefore turns its 32 x 128 tile through its own LDS
-// region (row pitch 528 bytes, so that rows do not all start in the same bank) and then moves
-// whole rows: 32 lanes x 16 bytes (fp32 carry, read and write) or x 8 bytes (bf16 output) per row,
-// two rows per instruction.  Only this wave touches the region; LDS operations of one wave complete
-// in order, so no barrier is needed.
-constexpr int kEpiPitch = kD * 4 + 16;                    // bytes per staged row
-constexpr int kEpiWaveB = kQPerWave * kEpiPitch + 512;    // + per-row (scale of O~, weight of the carry, lse, unused)
-template <bool kHalfD>
-__device__ __forceinline__ void finish_and_store(const AttnStep& s, f32x4 (&oacc)[8][2], const float (&m)[2],
-                                                 const float (&lsum)[2], int b, int h, int q0, int r, int g,
-                                                 unsigned char* epi, bool invalid) {
-  constexpr int kDB = kHalfD ? 4 : 8;
-  constexpr int kAccP = kHalfD ? 64 : kD;                 // floats per row of the carried O
-  const int lane = r + 16 * g;
+// q0: the wave's first query (its pair's, in the split form).  Every tile read of the work-group is behind a barrier.
+template <bool kSplit, bool kHalfD>
+__device__ __forceinline__ void finish_and_store(const AttnStep& s, f32x4 (&oacc)[8][2], const float (&m)[2], const float (&lsum)[2],
+                                                 int b, int h, int q0, int wave, int lane, unsigned char* smem, bool invalid, int part) {
+  constexpr int kDB = kHalfD ? 4 : 8, kRowF = kHalfD ? 64 : kD;
+  const int r = lane & 15, g = lane >> 4;
   const int64_t row0 = ((int64_t)b * s.H + h) * s.Sq;     // first row of this (batch, head) in lse / acc
+  unsigned char* epi = smem + wave * kEpiWaveB;
   float* info = reinterpret_cast<float*>(epi + kQPerWave * kEpiPitch);
 #pragma unroll
-  for (int nb = 0; nb < 2; ++nb) {
-    const float l = xgroup_sum(lsum[nb]);
-    const int qr = 16 * nb + r;                           // row of the wave's tile
-    const int qi = q0 + qr;
-    const RowFinish f = finish_row(s, m[nb], l, row0 + min(qi, s.Sq - 1), invalid);
-    if (g == 0 && qi < s.Sq) s.lse[row0 + qi] = f.lse_new;
-    if (g == 0) { info[2 * qr] = f.c_cur; info[2 * qr + 1] = f.w_prev; }
-    // stage: row qr, head dims 16*db + 4*g .. +3
+  for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
-    for (int db = 0; db < kDB; ++db)
-      *reinterpret_cast<f32x4*>(epi + qr * kEpiPitch + (16 * db + 4 * g) * 4) = oacc[db][nb];
-  }
-  // rows: lane (r2, c) handles head dims 4c .. 4c+3 of rows 2*it + r2
-  const int r2 = lane >> 5, c = lane & 31;
-  const int rows_valid = min(kQPerWave, s.Sq - q0);       // <= 0: nothing to store
-#pragma unroll 4
-  for (int it = 0; it < kQPerWave / 2; ++it) {
-    const int rr = 2 * it + r2;
-    if (rr >= rows_valid || (kHalfD && c >= 16)) continue;   // kHalfD: rows are 64 wide
-    const f32x4 v = *reinterpret_cast<const f32x4*>(epi + rr * kEpiPitch + c * 16);
-    const float cc = info[2 * rr], wp = info[2 * rr + 1];
-    float o[4] = {v[0] * cc, v[1] * cc, v[2] * cc, v[3] * cc};
-    const int64_t row = row0 + q0 + rr;
-    if (s.mode >= 2) {
-      const float4 p = *reinterpret_cast<const float4*>(s.acc + row * kAccP + 4 * c);
-      o[0] = fmaf(wp, p.x, o[0]); o[1] = fmaf(wp, p.y, o[1]);
-      o[2] = fmaf(wp, p.z, o[2]); o[3] = fmaf(wp, p.w, o[3]);
+    for (int db = 0; db < kDB; ++db)                       // row 16*nb + r, head dims 16*db + 4*g .. +3
+      *reinterpret_cast<f32x4*>(epi + (16 * nb + r) * kEpiPitch + (16 * db + 4 * g) * 4) = oacc[db][nb];
+  const unsigned char* other = epi;
+  f32x4* weights;                                          // of the rows this wave stores
+  int first = q0;                                          // the first of them
+  if (kSplit) {
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb) {
+      if (g == 0) info[8 * (16 * nb + r)] = m[nb];
+      info[8 * (16 * nb + r) + 1 + g] = lsum[nb];
     }
-    if (s.mode == 1 || s.mode == 2)
-      *reinterpret_cast<float4*>(s.acc + row * kAccP + 4 * c) = make_float4(o[0], o[1], o[2], o[3]);
-    else {
-      bf16_t* outp = (bf16_t*)s.out + b * s.os[0] + h * s.os[1] + (int64_t)(q0 + rr) * s.os[2];
-      // the final output is not read again here: a streaming store leaves no dirty line for the
-      // end of the kernel to write back (the fp32 carry above is re-read by the next step and stays cached)
-      const u32x2 v2 = {pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3])};
-      __builtin_nontemporal_store(v2, reinterpret_cast<u32x2*>(outp + 4 * c));
+    __syncthreads();
+    const int half = wave >> 2;                            // which 16 of the 32 queries
+    first += 16 * half;
+    const unsigned char* mine = smem + (wave & 3) * kEpiWaveB;   // the even tiles' half of the keys; then the odd ones'
+    const unsigned char* theirs = mine + 4 * kEpiWaveB;
+    const float* ia = reinterpret_cast<const float*>(mine + kQPerWave * kEpiPitch) + 8 * (16 * half + r);
+    const float* ib = reinterpret_cast<const float*>(theirs + kQPerWave * kEpiPitch) + 8 * (16 * half + r);
+    const float mA = ia[0], mB = ib[0], mm = fmaxf(mA, mB);
+    const float wa = (mm == -INFINITY) ? 0.0f : __builtin_amdgcn_exp2f(mA - mm);
+    const float wb = (mm == -INFINITY) ? 0.0f : __builtin_amdgcn_exp2f(mB - mm);
+    float l4[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) l4[e] = wa * ia[1 + e] + wb * ib[1 + e];
+    const float l = (l4[0] + l4[1]) + (l4[2] + l4[3]);
+    const int qi = first + r;
+    RowFinish f = finish_row(s, mm, l, row0 + min(qi, s.Sq - 1), invalid);
+    if (s.parts > 1 && !invalid) f.c_cur = 1.0f;   // a part's O~, m and l are kept as they are (attn_combine_kernel)
+    weights = reinterpret_cast<f32x4*>(epi + kQPerWave * (kEpiPitch + 32));
+    if (g == 0) {
+      weights[r] = f32x4{wa, wb, f.c_cur, f.w_prev};
+      if (qi < s.Sq) {
+        if (s.parts > 1) *reinterpret_cast<float2*>(s.part_ml + 2 * (part * (int64_t)s.B * s.H * s.Sq + row0 + qi)) = make_float2(mm, invalid ? f.c_cur : l);
+        else s.lse[row0 + qi] = f.lse_new;
+      }
+    }
+    epi = smem + (wave & 3) * kEpiWaveB + 16 * half * kEpiPitch;
+    other = epi + 4 * kEpiWaveB;
+  } else {
+    weights = reinterpret_cast<f32x4*>(info);
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb) {
+      const float l = xgroup_sum(lsum[nb]);
+      const int qi = q0 + 16 * nb + r;
+      const RowFinish f = finish_row(s, m[nb], l, row0 + min(qi, s.Sq - 1), invalid);
+      if (g == 0) {
+        weights[16 * nb + r] = f32x4{1.0f, 0.0f, f.c_cur, f.w_prev};
+        if (qi < s.Sq) s.lse[row0 + qi] = f.lse_new;
+      }
     }
   }
+  const int valid = s.Sq - first;
+  bf16_t* dst16 = (bf16_t*)s.out + b * s.os[0] + h * s.os[1] + (int64_t)first * s.os[2];
+  if (kSplit && s.parts > 1) {
+    float* dst = s.part_o + ((int64_t)part * s.B * s.H * s.Sq + row0 + first) * kRowF;
+    store_rows<kSplit, kHalfD, false, true>(epi, other, weights, lane, valid, nullptr, dst, nullptr, 0);
+    return;
+  }
+  float* acc = s.acc + (row0 + first) * kRowF;             // (null, and not touched, in mode 0)
+  if (s.mode == 0) store_rows<kSplit, kHalfD, false, false>(epi, other, weights, lane, valid, nullptr, nullptr, dst16, s.os[2]);
+  else if (s.mode == 1) store_rows<kSplit, kHalfD, false, true>(epi, other, weights, lane, valid, nullptr, acc, nullptr, 0);
+  else if (s.mode == 2) store_rows<kSplit, kHalfD, true, true>(epi, other, weights, lane, valid, acc, acc, nullptr, 0);
+  else store_rows<kSplit, kHalfD, true, false>(epi, other, weights, lane, valid, acc, nullptr, dst16, s.os[2]);
 }
 
 // =============================================================================================
@@ -274,6 +306,10 @@ __device__ __forceinline__ void lds_dma16(const void* gbase, uint32_t lane_off, 
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                :: "s"(lds_base), "v"(lane_off), "s"(gbase) : "memory", "m0");
 }
+// The same from an address per lane.
+__device__ __forceinline__ void lds_dma16_lanes(const void* p, uint32_t lds_base) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(lds_base), "v"(p) : "memory", "m0");
+}
 // The same through a buffer descriptor (base, 0, bytes, flags) with a uniform offset on top of the lanes':
 // lanes that fall outside the descriptor's bytes load zeros.
 __device__ __forceinline__ void lds_dma16_bounded(u32x4 desc, uint32_t lane_off, uint32_t offset, uint32_t lds_base) {
@@ -285,6 +321,12 @@ __device__ __forceinline__ void lds_dma4(const void* gbase, uint32_t lane_off, u
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2"
                :: "s"(lds_base), "v"(lane_off), "s"(gbase) : "memory", "m0");
 }
+// Waits until at most kLoads of this wave's loads are in flight (and, if lgkm, none of its LDS operations)
+template <int kLoads, bool kLds = false>
+__device__ __forceinline__ void wait_loads() {
+  if (kLds) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(kLoads) : "memory");
+  else asm volatile("s_waitcnt vmcnt(%0)" :: "n"(kLoads) : "memory");
+}
 constexpr int kStages = 3, kStagesSplitK = 4;   // LDS tile buffers per tensor; of K in the key-split form
 constexpr int kExtTileB = kTile * 4;   // bytes of one tile's record: the factors of its 64 keys
 
@@ -294,8 +336,8 @@ constexpr int kExtTileB = kTile * 4;   // bytes of one tile's record: the factor
 constexpr int kExtOff = (kStagesSplitK + kStages) * kTileB;
 constexpr int kWordsOff = kExtOff + 4 * kExtTileB;
 constexpr int kLdsBytes = 8 * kEpiWaveB;
-constexpr int kMaxWords = (kLdsBytes - kWordsOff) / 8;
-static_assert(kWordsOff % 8 == 0 && kWordsOff < kLdsBytes && kLdsBytes <= 159 * 1024, "LDS plan");   // (some is left to __syncthreads_or)
+constexpr int kMaxWords = 2944;
+static_assert(kWordsOff % 8 == 0 && kWordsOff + kMaxWords * 8 <= kLdsBytes && kLdsBytes <= 159 * 1024, "LDS plan");   // (some is left to __syncthreads_or)
 
 // LDS transposing read: the 16 lanes of a group each name 8 bytes; seen as a 4 x 16 matrix of
 // bf16 (row i = the data of lanes 4i..4i+3), lane j of the group receives column j.
@@ -315,7 +357,8 @@ __device__ __forceinline__ u32x2 lds_read_tr3(const __attribute__((address_space
 constexpr int kArrivePolls = 1 << 21;
 __device__ __forceinline__ bool wait_arrival(const int* counter, int need, int polls) {
   for (int i = 0; i < polls; ++i) {
-    if (__hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= need) {
+    // (readfirstlane: the loop ends for the whole wave at once, so that what lives across it may stay in scalar registers)
+    if (__builtin_amdgcn_readfirstlane(__hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) >= need) {
       asm volatile("" ::: "memory");
       return true;
     }
@@ -341,6 +384,24 @@ __device__ __forceinline__ uint64_t live_keys(const uint8_t* mask, int Sc, int t
   return __builtin_amdgcn_ballot_w64(live);
 }
 
+// The kernel's argument lies in memory that a scalar load takes some 700 cycles to reach the first time: a word of each of
+// its 64-byte lines up to the chunk table, all in flight together, so that no later use of a field waits for memory
+// (they came one after another, line by line, and made a good part of the 4500 cycles in front of the first tile).
+__device__ __forceinline__ void touch_step() {
+  typedef const __attribute__((address_space(4))) uint32_t* words;
+  const words p = (words)__builtin_amdgcn_kernarg_segment_ptr();
+  static_assert(offsetof(AttnStep, chunk) > 4 * 64 && offsetof(AttnStep, chunk) <= 6 * 64, "lines of the step");
+  asm volatile("" :: "s"(p[0]), "s"(p[16]), "s"(p[32]), "s"(p[48]), "s"(p[64]), "s"(p[80]));
+}
+// The chunk table, likewise
+__device__ __forceinline__ void touch_chunks() {
+  typedef const __attribute__((address_space(4))) uint32_t* words;
+  const words p = (words)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(AttnStep, chunk) / 4;
+  static_assert(sizeof(AttnStep::Chunk) * AttnStep::kMaxMulti == 22 * 64, "lines of the table");
+  asm volatile("" :: "s"(p[0]), "s"(p[16]), "s"(p[32]), "s"(p[48]), "s"(p[64]), "s"(p[80]), "s"(p[96]), "s"(p[112]), "s"(p[128]), "s"(p[144]), "s"(p[160]));
+  asm volatile("" :: "s"(p[176]), "s"(p[192]), "s"(p[208]), "s"(p[224]), "s"(p[240]), "s"(p[256]), "s"(p[272]), "s"(p[288]), "s"(p[304]), "s"(p[320]), "s"(p[336]));
+}
+
 // One work-group's share: the queries q_base .. q_base + 255 (wide) or + 127 (split) of (batch, head) bh_.
 // kHalfD: head dimension 64: rows of Q, K, V and O are 128 bytes (K and V are read in place, their LDS
 // tiles have 128-byte rows with swizzles of their own), the scores contract over two 32-wide slices
@@ -361,24 +422,35 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
   const int q0 = q_base + (kSplit ? (wave & 3) : wave) * kQPerWave;
   const bool grpA = wave < 4;
 
-  const bf16_t* qb = (const bf16_t*)s.q + b * s.qs[0] + h * s.qs[1];
+  constexpr int RB = kHalfD ? 128 : kRowB;   // bytes per row of Q, K and V, in LDS too
+  const uint32_t lds_base = (uint32_t)(uintptr_t)smem_raw;
+  // ---- Q first, the longest way to the first score.  Its operand layout (16 rows x 64 bytes an instruction) would take the
+  // CU's one address unit 64 cycles a load, 4000 for a work-group, so whole rows are moved to LDS, swizzled as K's are, and
+  // the operands read from there.  It lands in tile buffers that no load in front of the second barrier uses: split, the
+  // 32 rows of a pair of waves, half by each, in V stages 1 and 2; wide, a wave's own 32 rows in K stage 2, V stages 1
+  // and 2 and the room behind them.
+  const uint32_t q_lds = lds_base + (kSplit ? (kStagesK + 1) * kTileB + (wave & 3) * kQPerWave * RB
+                                            : wave < 2 ? 2 * kTileB + wave * kQPerWave * RB : 4 * kTileB + (wave - 2) * kQPerWave * RB);
+  {
+    const bf16_t* qb = (const bf16_t*)s.q + b * s.qs[0] + h * s.qs[1];
+    constexpr int kRPI = kHalfD ? 8 : 4, kLPR = 64 / kRPI;   // rows per instruction, lanes per row
+    const int first = kSplit && !grpA ? kQPerWave / 2 : 0;
+#pragma unroll
+    for (int t = 0; t < (kSplit ? kQPerWave / 2 : kQPerWave) / kRPI; ++t) {
+      const int row = first + t * kRPI + lane / kLPR;
+      const int piece = kHalfD ? (lane % kLPR) ^ ((row >> 1) & 7) : (lane % kLPR) ^ (row & 15);
+      lds_dma16_lanes(qb + (int64_t)min(q0 + row, s.Sq - 1) * s.qs[2] + 8 * piece,
+                      __builtin_amdgcn_readfirstlane(q_lds + (first + t * kRPI) * RB));
+    }
+  }
   const unsigned char* kb = (const unsigned char*)((const bf16_t*)s.k + b * s.ks[0] + h * s.ks[1]);
   const unsigned char* vb = (const unsigned char*)((const bf16_t*)s.v + b * s.ks[0] + h * s.ks[1]);
   const float scale2 = s.scale * 1.44269504088896340736f;
   // without kDead the host guarantees whole tiles and at least one; with it, the tiles up to the last live
   // key are visited, and none may be left (nt == 0)
   auto tiles_of = [](int len) { return (len + kTile - 1) / kTile; };
-  int nt_all = 0;
-  bool masked = false;
-  if (kMulti) {
-    for (int c = 0; c < s.n_multi; ++c) {
-      nt_all += tiles_of(s.chunk[c].Sc);
-      masked |= s.chunk[c].mask_src != nullptr;
-    }
-  } else {
-    nt_all = tiles_of(s.Sc);
-    masked = s.key_mask != nullptr;
-  }
+  const int nt_all = s.tiles;
+  const bool masked = s.any_mask != 0;
   int nt = nt_all;
   typedef const __attribute__((address_space(3))) uint64_t* lds_words;
   const lds_words words = (lds_words)(uintptr_t)((uint32_t)(uintptr_t)smem_raw + kWordsOff);
@@ -447,9 +519,8 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
   // this work-group's part of the tiles, t_beg .. nt - 1; tile indices below count from t_beg
   const int nt_live = nt;
   const bool parted = kSplit && s.parts > 1;
-  const int t_beg = parted ? (int)((int64_t)nt_live * part / s.parts) : 0;
-  if (parted) nt = (int)((int64_t)nt_live * (part + 1) / s.parts) - t_beg;
-  if (kDead && masked && nt == 0) __syncthreads();   // no barrier of the tile loop stands between the words and the epilogue that reuses their place
+  const int t_beg = parted ? (int)((uint32_t)nt_live * (uint32_t)part / (uint32_t)s.parts) : 0;   // (at most 2^25 tiles and 16 parts)
+  if (parted) nt = (int)((uint32_t)nt_live * (uint32_t)(part + 1) / (uint32_t)s.parts) - t_beg;
 
   f32x4 oacc[8][2];   // O~^T: [16-wide head-dim block db][16-query block nb]: head dims 16*db + 4*g + i of query 16*nb + r
 #pragma unroll
@@ -470,7 +541,6 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
   // 8 rows (8 lanes each) and a wave's share of a tile is a single load per tensor; the swizzles are
   //   K: piece c (of 8) of key r sits at piece c ^ ((r >> 1) & 7)   (two rows share a sweep of the banks)
   //   V: the 64-byte half h of key r sits at half h ^ ((r >> 1) & 1)
-  constexpr int RB = kHalfD ? 128 : kRowB;   // bytes per K / V row in LDS
   const int dma_r0 = 8 * wave + (kHalfD ? (lane >> 3) : (lane >> 4)), dma_r1 = dma_r0 + 4;
   const int dma_p = kHalfD ? (lane & 7) : (lane & 15);
   const uint32_t rowB = (uint32_t)(s.ks[2] * 2);   // bytes between keys in global memory
@@ -487,7 +557,6 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
   const int own_half = kDead && kSplit && !grpA ? 32 : 0;
   const uint32_t kg0 = (dma_r0 - own_half) * rowB + ksw0, kg1 = (dma_r1 - own_half) * rowB + ksw1;
   const uint32_t vg0 = (dma_r0 - own_half) * rowB + vsw0, vg1 = (dma_r1 - own_half) * rowB + vsw1;
-  const uint32_t lds_base = (uint32_t)(uintptr_t)smem_raw;
   const uint32_t lds_k = __builtin_amdgcn_readfirstlane(lds_base + 8 * wave * RB);
   const uint32_t lds_v = __builtin_amdgcn_readfirstlane(lds_base + kStagesK * kTileB + 8 * wave * RB);
   // a tile of K or V: where it starts, and how many rows its chunk has from there on
@@ -581,53 +650,31 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
   //   wide : A's SM(j) prefetches K(j+2) (with its record) and V(j+1); B's SM(j), one phase later,
   //          K(j+3) and V(j+2).
   //   split: the softmax phase p prefetches K(p+3), V(p+1) and the record of tile p+2.
-  int kpre_idx, vpre_idx;   // next K / V tile this wave prefetches
+  // next K / V tile this wave prefetches; split: K(p+3) / V(p+1) of its group's first softmax phase, p = 0 (A) or 1 (B)
+  const int kpre_idx = (kSplit ? 3 : 2) + (wave >> 2), vpre_idx = 1 + (wave >> 2);
+  if (kMulti) touch_chunks();
+  if (kExt && grpA) {
+    issue_ext(0, 0);
+    if (nt > 1) issue_ext(1, 1);
+  }
   if (!kSplit) {
     issue_k_tile(tile_at(0, false), 0);
     issue_v_tile(tile_at(0, true), 0);
-    if (nt > 1) issue_k_tile(tile_at(1, false), 1);
-    if (!grpA) {
-      if (nt > 1) issue_v_tile(tile_at(1, true), 1);
-      if (nt > 2) issue_k_tile(tile_at(2, false), 2);
-    } else if (kExt) {
-      issue_ext(0, 0);
-      if (nt > 1) issue_ext(1, 1);
-    }
-    kpre_idx = grpA ? 2 : 3;
-    vpre_idx = grpA ? 1 : 2;
+    if (nt > 1) issue_k_tile(tile_at(1, false), 1);   // (V(1) and K(2): group B, once Q has left their place)
   } else {
-    if (grpA) {   // (a group moves whole tiles, its own rows and its partner waves': one group suffices)
+    // a group moves whole tiles, its own rows and its partner waves': each group two of them
+    if (grpA) {
       issue_k_tile(tile_at(0, false), 0);
       issue_v_tile(tile_at(0, true), 0);
+    } else {
       if (nt > 1) issue_k_tile(tile_at(1, false), 1);
       if (nt > 2) issue_k_tile(tile_at(2, false), 2);
-      if (kExt) {
-        issue_ext(0, 0);
-        if (nt > 1) issue_ext(1, 1);
-      }
     }
-    kpre_idx = grpA ? 3 : 4;   // K(p+3) / V(p+1) of this group's first softmax phase, p = 0 (A) or 1 (B)
-    vpre_idx = grpA ? 1 : 2;
   }
   TileCursor kpre = place(kpre_idx, false), vpre = place(vpre_idx, true);
   constexpr int kPreStep = kSplit ? 2 : 1;   // tiles between two softmax phases of a wave
 
-  // Q^T operand (B of S^T = K Q^T): lane (r, g) holds Q[q0 + 16*nb + r][32*ks + 8*g .. +7]
-  bf16x8 qreg[2][4];
-  {
-#pragma unroll
-    for (int nb = 0; nb < 2; ++nb) {
-      const int qi = min(q0 + 16 * nb + r, s.Sq - 1);
-      const bf16_t* qr = qb + (int64_t)qi * s.qs[2] + 8 * g;
-#pragma unroll
-      for (int ks = 0; ks < kKS; ++ks) qreg[nb][ks] = *reinterpret_cast<const bf16x8*>(qr + 32 * ks);
-    }
-#pragma unroll
-    for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-      for (int ks = 0; ks < kKS; ++ks) asm volatile("" : "+v"(qreg[nb][ks]));
-  }
-
+  bf16x8 qreg[2][4];   // Q^T operand (B of S^T = K Q^T): lane (r, g) holds Q[q0 + 16*nb + r][32*ks + 8*g .. +7]
   f32x4 sacc[4][2];   // scores: [16-key block mb][16-query block nb]: keys 16*mb + 4*g + i of query 16*nb + r
   u32x4 pk[2][2];     // bf16 P as the B operand of P.V: [32-key step kk][nb]: keys 32*kk + 16*(j >> 2) + 4*g + (j & 3), j = 0..7
 
@@ -966,17 +1013,56 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
     }
   };
 
-  // prologue: the first tiles have landed
-  __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
+  // prologue: Q has landed and is read, then the tiles of the first scores
+  {
+    constexpr int kTL = (kSplit ? 2 : 1) * (kHalfD ? 1 : 2);   // a wave's loads per tile
+    if (kSplit) {
+      if (grpA || nt > 2) wait_loads<2 * kTL>();
+      else wait_loads<0>();
+      __builtin_amdgcn_s_barrier();                  // (each wave of a pair has moved half of their rows)
+      asm volatile("" ::: "memory");
+    } else if (nt > 1) wait_loads<3 * kTL>();
+    else wait_loads<2 * kTL>();
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+      for (int ks = 0; ks < kKS; ++ks)
+        qreg[nb][ks] = *reinterpret_cast<const __attribute__((address_space(3))) bf16x8*>(k_rd[ks] + (q_lds - lds_base) + 16 * nb * RB);
+    if (kSplit) {
+      if (grpA || nt > 2) wait_loads<kTL, true>();
+      else wait_loads<0, true>();
+    } else if (nt > 1) wait_loads<2 * kTL, true>();
+    else wait_loads<kTL, true>();
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+      for (int ks = 0; ks < kKS; ++ks) asm volatile("" : "+v"(qreg[nb][ks]));
+  }
   if (kDead) {
     __syncthreads();                      // (orders the words too)
     next_dead = find_dead(t_beg);
   } else {
     __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
   }
+  // The reference of the first tile, unless it has dead keys (its softmax phase then finds the maximum, after the
+  // exponentials against the reference -inf have failed the certification).  sm_tile: that tile.
+  auto first_reference = [&](int xs) {
+    if (kDead && next_dead <= sm_tile) return;
+    float tmax[2];
+    tile_max(xs, tmax);
+    m[0] = tmax[0] + kRefMargin;
+    m[1] = tmax[1] + kRefMargin;
+  };
 
   if (!kSplit) {
     first_scores(0);   // scores of tile 0 in both groups
+    first_reference(0);
+    wait_loads<0>();   // V(0), K(1): published by the barrier in front of A's matrix phase
+    if (!grpA) {
+      if (nt > 1) issue_v_tile(tile_at(1, true), 1);
+      if (nt > 2) issue_k_tile(tile_at(2, false), 2);
+    }
     // Both groups execute the same barrier sequence (two per tile index j = 0..nt); the steady-state
     // bodies are straight-line code so the accumulators stay in place.
     // sched_barrier(0): nothing may be moved across a phase boundary (the compiler would otherwise
@@ -1040,7 +1126,11 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
     }
   } else {
     // scores of tile 0 (group A) / tile 1 (group B)
-    if (grpA || nt > 1) first_scores(grpA ? 0 : 1);
+    if (grpA || nt > 1) {
+      first_scores(grpA ? 0 : 1);
+      first_reference(grpA ? 0 : 1);
+    }
+    wait_loads<0>();   // V(0), K(2): published by the barrier that ends phase 0
     // Phases p = 0..nt, one work-group barrier each; both groups execute nt + 1 of them.
     //   reads in phase p : V(p-1) from stage (p-1)%3, K(p+1) from stage (p+1)%4, record p from p%3
     //   batch of phase p : K(p+3) -> stage (p+3)%4 (last read, as K(p-1), in phase p-2; a stage less, and the
@@ -1081,58 +1171,26 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
     // the group whose last matrix phase was phase nt-1 sits out phase nt
     if ((grpA && (nt % 2 == 0)) || (!grpA && (nt % 2 == 1))) end_phase(false);
   }
-  }  // nt > 0
+  } else {               // no live key: the loads of Q and the words' last readers are through before the epilogue reuses their place
+    wait_loads<0>();
+    __syncthreads();
+  }
   // A wave that gave up waiting for a chunk loaded its rows of the tiles too early, and every wave of
   // the work-group has read those rows: the flag belongs to the work-group.
   if (kMulti) {
     if (s.arrive != nullptr) late = __syncthreads_or(late ? 1 : 0) != 0;
   }
 
-  if (kSplit) {
-    // ---- fold group B's partial state into group A's (same queries, disjoint keys) --------------
-    // all tile reads are behind the last barrier, so the tile buffers are reused for the exchange:
-    // float slot i of wave w, lane l sits at x[(w * 66 + i) * 64 + l]
-    float* xch = reinterpret_cast<float*>(smem_raw);
-    constexpr int kSlots = 8 * 2 * 4 + 4;   // O~, the two references, the two sums
-    if (!grpA) {
-      float* dst = xch + ((wave - 4) * kSlots) * 64 + lane;
-#pragma unroll
-      for (int db = 0; db < kDB; ++db)
-#pragma unroll
-        for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) dst[((db * 2 + nb) * 4 + e) * 64] = oacc[db][nb][e];
-      dst[64 * 64] = m[0]; dst[65 * 64] = m[1];
-      dst[66 * 64] = lsum[0]; dst[67 * 64] = lsum[1];
-    }
-    __syncthreads();
-    if (!grpA) return;
-    const float* src = xch + (wave * kSlots) * 64 + lane;
-#pragma unroll
-    for (int nb = 0; nb < 2; ++nb) {
-      const float mB = src[(64 + nb) * 64], lB = src[(66 + nb) * 64];
-      const float mm = fmaxf(m[nb], mB);
-      const float wa = (mm == -INFINITY) ? 0.0f : __builtin_amdgcn_exp2f(m[nb] - mm);
-      const float wb = (mm == -INFINITY) ? 0.0f : __builtin_amdgcn_exp2f(mB - mm);
-#pragma unroll
-      for (int db = 0; db < kDB; ++db)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) oacc[db][nb][e] = wa * oacc[db][nb][e] + wb * src[((db * 2 + nb) * 4 + e) * 64];
-      lsum[nb] = wa * lsum[nb] + wb * lB;
-      m[nb] = mm;
-    }
-  }
-
   // every tile read of the work-group is behind a barrier here (the one after the last matrix phase)
-  if (kSplit) finish_and_store_direct<kHalfD>(s, oacc, m, lsum, b, h, q0, r, g, kMulti && late, part);
-  else finish_and_store<kHalfD>(s, oacc, m, lsum, b, h, q0, r, g, smem_raw + wave * kEpiWaveB, kMulti && late);
+  finish_and_store<kSplit, kHalfD>(s, oacc, m, lsum, b, h, q0, wave, lane, smem_raw, kMulti && late, part);
 }
 
 template <bool kSplit, bool kExt, bool kMulti, bool kDead, bool kHalfD>
 __global__ __launch_bounds__(kThreads, 2) void attn_pp_kernel(AttnStep s) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  if (!kMulti && s.copy_wgs > 0 && blockIdx.x >= gridDim.x - s.copy_wgs) {   // prefetch work-group: copy and leave
-    prefetch_copy(s, blockIdx.x - (gridDim.x - s.copy_wgs), threadIdx.x, kThreads);
+  touch_step();
+  if (!kMulti && (int)blockIdx.x >= s.grid_wgs) {   // prefetch work-group: copy and leave
+    prefetch_copy(s, blockIdx.x - s.grid_wgs, threadIdx.x, kThreads);
     return;
   }
   constexpr int kQBlock = kSplit ? kQPerWGSplit : kQPerWG;
@@ -1148,7 +1206,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_pp_kernel(AttnStep s) {
   }
   // (batch, head, part of the keys), each with its query blocks: whoever shares K and V follows one another
   const int parts = kSplit ? s.parts : 1;   // (only key-split work-groups come in parts)
-  if (!wg_to_tile(s.copy_wgs, (s.Sq + kQBlock - 1) / kQBlock, s.B * s.H * parts, bh_, qb_, lead)) return;   // whole work-group
+  if (!wg_to_tile(s.grid_wgs, (s.Sq + kQBlock - 1) / kQBlock, s.B * s.H * parts, bh_, qb_, lead)) return;   // whole work-group
   int part = 0;
   if (parts > 1) {
     part = bh_ % parts;
@@ -1196,8 +1254,9 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(const float* __restri
 template <bool kExt, bool kDead>
 __global__ __launch_bounds__(kThreads, 2) void attn_pp_mixed_kernel(AttnStep s) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  if (s.copy_wgs > 0 && blockIdx.x >= gridDim.x - s.copy_wgs) {
-    prefetch_copy(s, blockIdx.x - (gridDim.x - s.copy_wgs), threadIdx.x, kThreads);
+  touch_step();
+  if ((int)blockIdx.x >= s.grid_wgs) {
+    prefetch_copy(s, blockIdx.x - s.grid_wgs, threadIdx.x, kThreads);
     return;
   }
   const int nqb = (s.Sq + kQPerWG - 1) / kQPerWG;
@@ -1390,13 +1449,14 @@ usp_status launch_attn_mfma(const AttnStep& step, hipStream_t st) {
       set_error("a launch over several FP8 chunks needs arrival counters and per-tile records");
       return USP_ERR_INVALID_ARG;
     }
-    bool dead = false;
+    bool dead = false, masked = false;
     for (int c = 0; c < s.n_multi; ++c) {
       if (s.chunk[c].Sc <= 0 || !s.chunk[c].k || !s.chunk[c].v) {
         set_error("a launch over several chunks needs chunks that hold keys");
         return USP_ERR_INVALID_ARG;
       }
-      dead |= s.chunk[c].mask_src != nullptr || s.chunk[c].Sc % kTile != 0;
+      masked |= s.chunk[c].mask_src != nullptr;
+      dead |= masked || s.chunk[c].Sc % kTile != 0;
     }
     const unsigned w256 = wg_grid_size((s.Sq + kQPerWG - 1) / kQPerWG, s.B * s.H);
     const unsigned w128 = wg_grid_size((s.Sq + kQPerWGSplit - 1) / kQPerWGSplit, s.B * s.H * s.parts);
@@ -1405,6 +1465,9 @@ usp_status launch_attn_mfma(const AttnStep& step, hipStream_t st) {
     for (int c = 0; c < s.n_multi; ++c) tiles += (s.chunk[c].Sc + kTile - 1) / kTile;
     const bool split = attn_mfma_ring_form(s.B, s.H, s.Sq, s.d, tiles, s.n_multi, s.variant).split;
     const unsigned wgs = split ? w128 : w256;
+    s.grid_wgs = (int)wgs;
+    s.tiles = (int)tiles;
+    s.any_mask = masked;
     s.copy_wgs = 0;
     if (s.arrive != nullptr) {
       for (int c = s.multi_fp8 ? 0 : 1; c < s.n_multi; ++c)
@@ -1424,6 +1487,8 @@ usp_status launch_attn_mfma(const AttnStep& step, hipStream_t st) {
     const usp_status r = launch_pp_any<true>(s, s.multi_fp8 != 0, dead, split, wgs, st);
     return r == USP_OK && s.parts > 1 ? launch_combine(s, st) : r;
   }
+  s.tiles = (s.Sc + kTile - 1) / kTile;
+  s.any_mask = s.key_mask != nullptr;
   const bool ext = s.k_scale != nullptr;
   const bool dead = s.key_mask != nullptr || s.Sc % kTile != 0 || s.Sc == 0;
   // Few query blocks (a small Q shard of a ring step): 256-query work-groups would leave CUs idle;
@@ -1449,11 +1514,13 @@ usp_status launch_attn_mfma(const AttnStep& step, hipStream_t st) {
     s.mix_halves = (mix_blocks + kXcds - 1) / kXcds;
     const int per = (items + kXcds - 1) / kXcds;
     const unsigned wgs_mixed = (unsigned)(kXcds * (per + s.mix_halves));
+    s.grid_wgs = (int)wgs_mixed;
     s.copy_wgs = prefetch_wg_count(s, (int)wgs_mixed);
     if (ext) return dead ? launch_mixed<true, true>(s, wgs_mixed, st) : launch_mixed<true, false>(s, wgs_mixed, st);
     return dead ? launch_mixed<false, true>(s, wgs_mixed, st) : launch_mixed<false, false>(s, wgs_mixed, st);
   }
   const unsigned wgs = split ? wg_grid_size((s.Sq + kQPerWGSplit - 1) / kQPerWGSplit, s.B * s.H * s.parts) : wgs256;
+  s.grid_wgs = (int)wgs;
   s.copy_wgs = prefetch_wg_count(s, (int)wgs);
   const usp_status r = launch_pp_any<false>(s, ext, dead, split, wgs, st);
   return r == USP_OK && s.parts > 1 ? launch_combine(s, st) : r;

@@ -142,13 +142,18 @@ struct AttnStep {
   int arrive_need_extra;
   int arrive_need;
   int arrive_polls;
-  Chunk chunk[kMaxMulti];
   // Prefetch carried by this launch (Algorithm 2, the transfer of the next chunk): the last
   // copy_wgs work-groups of the grid copy the n_copy segments and exit; they are dispatched after
   // the attention work-groups, onto the CU slots those leave free.  The launcher fills copy_wgs (0 when n_copy == 0).
   struct CopySeg { const void* src; void* dst; int64_t bytes; };
   int n_copy;
   int copy_wgs;
+  // set by the launcher, so that a work-group need not walk the chunk table first: work-groups of the grid, tiles of
+  // the launch's stream, and whether some chunk has a key mask
+  int grid_wgs;
+  int tiles;
+  int any_mask;
+  Chunk chunk[kMaxMulti];
   CopySeg copy[4];
 };
 static_assert(sizeof(AttnStep) <= 4096, "AttnStep is passed by value as the kernels' only argument");
