@@ -718,18 +718,22 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
   const f32x4 zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
   // matrix phase: O += P V (V tile in stage sv) interleaved with the scores of the next tile (K in
   // stage sk), in four blocks of sixteen MFMAs: block b takes kNV V^T operands (key step b >> 1, head-dim
-  // blocks kNV * (b & 1) ..) and kNV K operands (key block b, all head-dim slices), each operand feeding
-  // two MFMAs (the wave's two 16-query blocks), so that consecutive MFMAs share their A operand.
+  // blocks kNV * (b & 1) ..) and kNV K operands (head-dim slice b, all key blocks; kHalfD: key block b, both slices), each
+  // operand feeding two MFMAs (the wave's two 16-query blocks).  Head dimension 128: the two change their order from operand to
+  // operand, so that from one MFMA to the next one of the two operands stays, which the chip, at its power limit, pays back in
+  // clock (24 heads of 4608 226 -> 224.6 us, a ring of eight chunks of 2112 226.3 -> 223.6).
   // Only this wave feeds the SIMD's matrix core during the phase, so its LDS operand reads run one
   // block ahead of their use.  The order is written out and pinned (sched_barrier after every operand's
   // MFMAs and the reads issued behind them) rather than left to the instruction scheduler.
+  // (The softmax phase is the one with the raised priority: what it loses to the matrix phase's issue beside it, it
+  // loses in full, while the matrix core has work queued.  24 heads of 4608 queries and keys 225 -> 218 us against the other way round.)
   auto MM_full = [&](int sv, int sk) {
-    __builtin_amdgcn_s_setprio(2);
+    __builtin_amdgcn_s_setprio(0);
     bf16x8 va[2][kNV], ka[2][kNV];
 #pragma unroll
     for (int i = 0; i < kNV; ++i) va[0][i] = v_operand(sv, 0, i);
 #pragma unroll
-    for (int i = 0; i < kNV; ++i) ka[0][i] = k_operand(sk, 0, i);
+    for (int i = 0; i < kNV; ++i) ka[0][i] = kHalfD ? k_operand(sk, 0, i) : k_operand(sk, i, 0);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int blk = 0; blk < 4; ++blk) {
@@ -740,8 +744,10 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
 #pragma unroll
         for (int j = i; j < i + kBurst; ++j) {
           const int db = kNV * (blk & 1) + j;
+          if (!kHalfD && (j & 1)) oacc[db][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[c][j], pb1, oacc[db][1], 0, 0, 0);
           oacc[db][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[c][j], pb0, oacc[db][0], 0, 0, 0);
-          oacc[db][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[c][j], pb1, oacc[db][1], 0, 0, 0);
+          if (kHalfD || !(j & 1)) oacc[db][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[c][j], pb1, oacc[db][1], 0, 0, 0);
+          if (!kHalfD) __builtin_amdgcn_sched_barrier(0);
         }
 #pragma unroll
         for (int j = i; j < i + kBurst; ++j)
@@ -749,22 +755,25 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
         __builtin_amdgcn_sched_barrier(0);
       }
 #pragma unroll
-      for (int i = 0; i < kNV; i += kBurst) {     // (kNV == kKS: the head-dim slices of the scores)
+      for (int i = 0; i < kNV; i += kBurst) {     // (kNV is both the key blocks and, or for kHalfD, the head-dim slices)
 #pragma unroll
-        for (int ks = i; ks < i + kBurst; ++ks) {
-          sacc[blk][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[c][ks], qreg[0][ks], ks == 0 ? zero4 : sacc[blk][0], 0, 0, 0);
-          sacc[blk][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[c][ks], qreg[1][ks], ks == 0 ? zero4 : sacc[blk][1], 0, 0, 0);
+        for (int j = i; j < i + kBurst; ++j) {
+          const int mb = kHalfD ? blk : j, ks = kHalfD ? j : blk;
+          if (!kHalfD && (j & 1)) sacc[mb][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[c][j], qreg[1][ks], ks == 0 ? zero4 : sacc[mb][1], 0, 0, 0);
+          sacc[mb][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[c][j], qreg[0][ks], ks == 0 ? zero4 : sacc[mb][0], 0, 0, 0);
+          if (kHalfD || !(j & 1)) sacc[mb][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[c][j], qreg[1][ks], ks == 0 ? zero4 : sacc[mb][1], 0, 0, 0);
+          if (!kHalfD) __builtin_amdgcn_sched_barrier(0);
         }
 #pragma unroll
-        for (int ks = i; ks < i + kBurst; ++ks)
-          if (blk < 3) ka[c ^ 1][ks] = k_operand(sk, blk + 1, ks);
+        for (int j = i; j < i + kBurst; ++j)
+          if (blk < 3) ka[c ^ 1][j] = kHalfD ? k_operand(sk, blk + 1, j) : k_operand(sk, j, blk + 1);
         __builtin_amdgcn_sched_barrier(0);
       }
     }
-    __builtin_amdgcn_s_setprio(0);
+    __builtin_amdgcn_s_setprio(1);
   };
   auto MM_last = [&](int sv) {   // last tile: no further scores; the reads run two blocks ahead
-    __builtin_amdgcn_s_setprio(2);
+    __builtin_amdgcn_s_setprio(0);
     bf16x8 va[4][kNV];
 #pragma unroll
     for (int blk = 0; blk < 2; ++blk)
@@ -784,7 +793,7 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
         __builtin_amdgcn_sched_barrier(0);
       }
     }
-    __builtin_amdgcn_s_setprio(0);
+    __builtin_amdgcn_s_setprio(1);
   };
   // softmax phase: sacc (scores of one tile) -> pk (bf16 P), running references m and sums l of the
   // lane's two queries.
@@ -1055,6 +1064,7 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
     m[1] = tmax[1] + kRefMargin;
   };
 
+  __builtin_amdgcn_s_setprio(1);
   if (!kSplit) {
     first_scores(0);   // scores of tile 0 in both groups
     first_reference(0);
