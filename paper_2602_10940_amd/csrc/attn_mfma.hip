@@ -198,13 +198,13 @@ __device__ __forceinline__ void finish_and_store(const AttnStep& s, f32x4 (&oacc
     const unsigned char* theirs = mine + 4 * kEpiWaveB;
     const float* ia = reinterpret_cast<const float*>(mine + kQPerWave * kEpiPitch) + 8 * (16 * half + r);
     const float* ib = reinterpret_cast<const float*>(theirs + kQPerWave * kEpiPitch) + 8 * (16 * half + r);
-    const float mA = ia[0], mB = ib[0], mm = fmaxf(mA, mB);
-    const float wa = (mm == -INFINITY) ? 0.0f : __builtin_amdgcn_exp2f(mA - mm);
-    const float wb = (mm == -INFINITY) ? 0.0f : __builtin_amdgcn_exp2f(mB - mm);
-    float l4[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) l4[e] = wa * ia[1 + e] + wb * ib[1 + e];
-    const float l = (l4[0] + l4[1]) + (l4[2] + l4[3]);
+    // Both under one reference, the larger of what the two have summed to (in log2 units) and not of their references,
+    // which say little about it: one may lag its sum by 2^60 and more, the other lie 2^64 above.
+    const float mA = ia[0], mB = ib[0], lA = (ia[1] + ia[2]) + (ia[3] + ia[4]), lB = (ib[1] + ib[2]) + (ib[3] + ib[4]);
+    const float mm = fmaxf(mA + __builtin_amdgcn_logf(lA), mB + __builtin_amdgcn_logf(lB));
+    const float wa = (lA == 0.0f) ? 0.0f : __builtin_amdgcn_exp2f(mA - mm);
+    const float wb = (lB == 0.0f) ? 0.0f : __builtin_amdgcn_exp2f(mB - mm);
+    const float l = wa * lA + wb * lB;
     const int qi = first + r;
     RowFinish f = finish_row(s, mm, l, row0 + min(qi, s.Sq - 1), invalid);
     if (s.parts > 1 && !invalid) f.c_cur = 1.0f;   // a part's O~, m and l are kept as they are (attn_combine_kernel)
@@ -868,27 +868,26 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
     tmax[0] = xgroup_max(tmax[0]);
     tmax[1] = xgroup_max(tmax[1]);
   };
-  auto rescale = [&](int nb, float alpha) {   // O~ and l of query block nb
-    lsum[nb] *= alpha;
+  // O~ and l of query block nb, for a reference that moves on by `down` (>= 0, or infinity: there is nothing yet).  In two
+  // steps: what was summed under a reference that lagged by 2^60 and now counts 2^64 and more below the new one is still
+  // part of the result, and one factor 2^-down may be no normal number.
+  auto rescale = [&](int nb, float down) {
+    const float a = __builtin_amdgcn_exp2f(-0.5f * down);
+    lsum[nb] = lsum[nb] * a * a;
 #pragma unroll
     for (int db = 0; db < 8; ++db)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) oacc[db][nb][e] *= alpha;
+      for (int e = 0; e < 4; ++e) oacc[db][nb][e] = oacc[db][nb][e] * a * a;
   };
-  // Tiles still to be handled maximum-first (wave-uniform).  After a failed certification with a
-  // reference already in place, the next kMaxFirstTiles softmax phases of the wave find the tile's
-  // maximum before the exponentials and move the reference if it is outgrown by more than 2^8; every
-  // such move re-arms the counter.  Scores with heavy tails then cost one maximum pass per tile
-  // instead of a second round of exponentials on most tiles; ordinary scores never arm it.
   constexpr float kCertifiedSum = 1152921504606846976.0f;   // 2^60
-  // A reference that moves is set this far ABOVE the maximum that moved it: the largest P is then 2^-32
+  // A reference is set this far ABOVE the maximum that moved it: the largest P is then 2^-32
   // instead of 1, which fp32 sums and bf16 P carry as well (every P, l and O~ is scaled by the same
   // power of two), and a later score has to exceed the maximum seen so far by 2^92, not 2^60, before
-  // the reference has to move again.  With heavy-tailed scores (x20 outliers in Q and K) that is the
-  // difference between a second round of exponentials on many tiles and on few.
-  constexpr float kRefMargin = 32.0f;
-  constexpr int kMaxFirstTiles = 8;
-  int max_first = 0;
+  // the reference has to move again.  Where it does, the scores have heavy tails (x20 outliers in Q and K), and the
+  // next one is set 2^64 above, so that a third is rare: weights down to 2^-62 of the largest stay normal numbers.
+  // 24 heads of 4096 queries, FP8 ring of two with such outliers: 460 us with 2^32 throughout and, after a failure, eight
+  // tiles handled maximum-first; 441 with 2^72 and two such tiles, 424 with 2^72 or 425 with 2^64 and none.
+  constexpr float kRefMargin = 32.0f, kFarMargin = 64.0f;
   int sm_tile = t_beg + (kSplit && !grpA ? 1 : 0);   // kDead: tile of this wave's next softmax phase
   int next_dead = 0;                         // kDead: the next tile with a dead key, as far as it has been looked up
   // SM of the tile whose record sits in stage xs; loads K tile kpre_idx into stage sk (if do_k, with
@@ -915,24 +914,6 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
         next_dead = find_dead(sm_tile + 1);
       }
       sm_tile += kPreStep;
-    }
-    if (max_first > 0) {
-      --max_first;
-      float tmax[2];
-      tile_max(xs, tmax);
-      const bool jump0 = tmax[0] > m[0] + 8.0f, jump1 = tmax[1] > m[1] + 8.0f;
-      if (__builtin_amdgcn_ballot_w64(jump0 || jump1) != 0ull) {
-#pragma unroll
-        for (int nb = 0; nb < 2; ++nb) {
-          const bool jump = nb ? jump1 : jump0;
-          const float m_new = tmax[nb] + kRefMargin;
-          const float alpha = jump ? __builtin_amdgcn_exp2f(m[nb] - m_new) : 1.0f;   // m = -inf gives 0
-          m[nb] = jump ? m_new : m[nb];
-          rescale(nb, alpha);
-        }
-        max_first = kMaxFirstTiles;
-      }
-      __builtin_amdgcn_sched_barrier(0);
     }
     if (do_k) settle(kpre, false);
     if (do_v) settle(vpre, true);
@@ -973,20 +954,16 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
     const bool redo0 = __builtin_amdgcn_ballot_w64(!(psum[0] <= kCertifiedSum)) != 0ull;
     const bool redo1 = __builtin_amdgcn_ballot_w64(!(psum[1] <= kCertifiedSum)) != 0ull;
     if (redo0 || redo1) {
-      // a reference that was already set and still failed: scores with heavy tails; look for the
-      // maximum first on the next tiles instead of paying for the exponentials twice
-      if (__builtin_amdgcn_ballot_w64(m[0] != -INFINITY || m[1] != -INFINITY) != 0ull) max_first = kMaxFirstTiles;
       float tmax[2];
       tile_max(xs, tmax);
       if (kExt) { x_load(0, xs); x_load(1, xs); }
 #pragma unroll
       for (int nb = 0; nb < 2; ++nb) {
         if (!(nb ? redo1 : redo0)) continue;
-        const float m_new = tmax[nb] > m[nb] ? tmax[nb] + kRefMargin : m[nb];
-        // m = -inf (first live tile) gives alpha 0; no live key so far: nothing to rescale, P = 0
-        const float alpha = m_new == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f(m[nb] - m_new);
+        const float m_new = tmax[nb] > m[nb] ? tmax[nb] + (m[nb] == -INFINITY ? kRefMargin : kFarMargin) : m[nb];
+        // m = -inf (first live tile) gives the factor 0; no live key so far: nothing to rescale, P = 0
+        rescale(nb, m_new == -INFINITY ? 0.0f : m_new - m[nb]);
         m[nb] = m_new;
-        rescale(nb, alpha);
         psum[nb] = 0.0f;
         if ((kExt || kDead) && m_new == -INFINITY) {
           pk[0][nb] = u32x4{0u, 0u, 0u, 0u};

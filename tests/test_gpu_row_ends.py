@@ -1,0 +1,60 @@
+"""The ends of a matrix-core attention launch: rows that do not fill a wave, a work-group or a store instruction, in every
+form that finishes or carries rows, and references of the exponent that lag the scores or stand far above them when the
+halves of a work-group's keys are put together.  Parity against the fp64 oracle."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import usp_oracle as orc
+from paper_2602_10940_amd import workloads as W
+from tests.gpu_util import DEV, dev_bf16, host_f64
+from tests.test_gpu_attention import _assert_parity, _oracle
+
+pytestmark = pytest.mark.gpu
+
+WIDE, SPLIT, STEPWISE = 4, 8, 64
+
+
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("flags,lens", [
+    (WIDE, (128,)), (SPLIT, (192,)),                              # a launch that writes the result
+    (WIDE | STEPWISE, (64, 128, 64)), (SPLIT | STEPWISE, (64, 128, 64)),   # the carried state: first, middle, last chunk
+    (0, (1088,)),                                                 # few work-groups: keys shared between them
+])
+@pytest.mark.parametrize("Sq", [1, 15, 17, 33, 129, 257])
+def test_rows_at_the_ends(Sq, flags, lens, d):
+    import paper_2602_10940_amd as P
+    wl = W.Workload("ends", 17, 1, 3, d, Sq, lens, "bf16")
+    inp = W.make_attention_inputs(wl)
+    room = torch.full((1, 3, Sq + 5, d), 7.0, dtype=torch.bfloat16, device=DEV)   # rows behind the last stay what they are
+    out, lse = P.usp_ring_attn_fwd(dev_bf16(inp.q), [dev_bf16(k) for k in inp.k], [dev_bf16(v) for v in inp.v],
+                                   softmax_scale=float(inp.softmax_scale), flags=flags, out=room[:, :, :Sq])
+    torch.cuda.synchronize()
+    ro, rl = _oracle(inp)
+    _assert_parity(host_f64(out), host_f64(lse), ro, rl)
+    assert bool((room[:, :, Sq:] == 7.0).all())
+
+
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("flags", [WIDE, SPLIT, 0])
+@pytest.mark.parametrize("levels", [
+    (0, 62, 64, 66), (66, 64, 62, 0),               # 2^90 above the first maximum without a new reference, then past it
+    (0, 62, 66, 66, 120, 62, 130, 131, 100),        # a second and a third move
+    (0, 100, 62, 100, 0, 101, 62, 0),               # the two halves of the keys apart: one lags, the other has moved
+    (40, 0, 39, 130, 41, 131, 127, 128, 129, 60),
+])
+def test_references_that_lag(levels, flags, d):
+    """Scores that climb from tile to tile: what was summed before a reference moved may be all but the whole result."""
+    import paper_2602_10940_amd as P
+    rng = np.random.default_rng(5)
+    n = 64 * len(levels)
+    q = np.zeros((1, 2, 40, d), np.float32)
+    q[..., 0] = rng.choice([1.0, 0.75, 0.5], size=(1, 2, 40))
+    k = np.zeros((1, 2, n, d), np.float32)
+    k[..., 0] = np.repeat(np.asarray(levels, np.float32), 64) - rng.integers(0, 8, size=(1, 2, n)) * 0.5   # bf16 holds these
+    v = W.bf16_bits_to_f32(W.f32_to_bf16_bits(rng.standard_normal((1, 2, n, d)).astype(np.float32))).reshape(1, 2, n, d)
+    kb = W.bf16_bits_to_f32(W.f32_to_bf16_bits(k)).reshape(k.shape)
+    out, lse = P.usp_ring_attn_fwd(dev_bf16(q), [dev_bf16(kb)], [dev_bf16(v)], softmax_scale=1.0, flags=flags)
+    torch.cuda.synchronize()
+    ro, rl = orc.ring_attention(q, [kb], [v], 1.0, None)
+    _assert_parity(host_f64(out), host_f64(lse), ro, rl)
