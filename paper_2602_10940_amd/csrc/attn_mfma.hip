@@ -373,7 +373,7 @@ __global__ __launch_bounds__(64) void attn_arrive_reset_kernel(int* arrive) {
 // work-group could overlap with anything; the chunk of a launch-per-chunk step).
 __global__ __launch_bounds__(256) void attn_fp8_chunk_prepare_kernel(AttnStep s, int c, int reset_arrive) {
   if (reset_arrive && blockIdx.x == 0 && threadIdx.x < AttnStep::kMaxMulti) s.arrive[threadIdx.x] = 0;
-  fp8_chunk_prepare<false>(s, c, (int64_t)blockIdx.x * 256 + threadIdx.x, (int64_t)gridDim.x * 256);
+  fp8_chunk_prepare(s, c, (int64_t)blockIdx.x * 256 + threadIdx.x, (int64_t)gridDim.x * 256);
 }
 
 // The live keys of tile t (of a launch's tile stream) as a word, by the lanes of a wave: bit = key takes part.
@@ -1185,8 +1185,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_pp_kernel(AttnStep s) {
   int lead = 0;
   if (kMulti && s.arrive != nullptr) {   // the whole ring's transfers ride in this launch, in its first work-groups
     if ((int)blockIdx.x < s.copy_wgs) {
-      if (kExt && s.multi_fp8) stream_chunks_fp8(s, blockIdx.x, threadIdx.x, kThreads);
-      else stream_chunks(s, blockIdx.x, threadIdx.x, kThreads);
+      stream_chunks<kExt>(s, blockIdx.x, threadIdx.x, kThreads);   // (several FP8 chunks: kExt, and the other way round)
       return;
     }
     lead = s.copy_wgs;
@@ -1280,7 +1279,7 @@ usp_status launch_attn_fp8_chunk_prepare(const AttnStep& s, int c, bool reset_ar
     set_error("FP8 chunk preparation needs a step over FP8 chunks with its records");
     return USP_ERR_INVALID_ARG;
   }
-  const int64_t units = (int64_t)s.B * s.H * s.chunk[c].Sc * (s.d / 16);   // 16 codes each
+  const int64_t units = (int64_t)s.B * s.H * s.chunk[c].Sc * (s.d / 8);   // 8 codes each
   const int64_t blocks = (units + 255) / 256;                          // one unit per thread while the chunk is small
   hipLaunchKernelGGL(attn_fp8_chunk_prepare_kernel, dim3((unsigned)(blocks < 1 ? 1 : blocks > 8192 ? 8192 : blocks)), dim3(256),
                      0, st, s, c, reset_arrive ? 1 : 0);

@@ -55,32 +55,16 @@ __device__ __forceinline__ void prefetch_copy(const AttnStep& s, int wg, int tid
 // before their chunk's count is complete, and the launch starts with invalid caches, so no cache on
 // the reading side can hold an older copy of those lines.
 __device__ __forceinline__ void publish_chunk(int* counter, int tid) {
-  __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this thread's stores have been acknowledged
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this thread's stores have been acknowledged (and none is moved past this)
   __syncthreads();
   if (tid == 0) __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// A 16-byte store with device scope.  The instruction sits in inline asm (no builtin sets the scope
-// bits of a plain store), where the compiler's hazard recogniser cannot see that it is a store: on
-// gfx9 a store of more than 8 bytes reads its data registers late, and a VALU instruction that
-// overwrites them within the next two wait states can change what is stored (seen as rare wrong
-// words in some lanes when the next store's data was computed into the same registers).  The two
-// wait states therefore ride inside the asm statement.
-__device__ __forceinline__ void store16_device_scope(uint4* p, const uint4& v) {
-  typedef unsigned int vec4u __attribute__((ext_vector_type(4)));
-  const vec4u x = {v.x, v.y, v.z, v.w};
-  asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" :: "v"(p), "v"(x) : "memory");
-}
 // Algorithm 1 line 4 for chunk c of a launch over FP8 chunks: unit `first`, first + stride, .. of the chunk
-// (16 codes of K and of V each; then one key of the records).  The arithmetic is the dequantiser's: E4M3
+// (8 codes of K and of V each; then one key of the records).  The arithmetic is the dequantiser's: E4M3
 // code -> fp32 (exact), times the scale in fp32, RNE to bf16; K keeps scale 1 and hands its scales to the
 // records as per-key factors of the exponent.  A key that takes no part (masked, or past the end of the
 // last tile) gets the plain factor instead of its scale's: its score is -inf by then and stays so under
 // any positive finite factor.
-template <bool kDeviceScope>
-__device__ __forceinline__ void put16(uint4* p, const uint4& v) {
-  if (kDeviceScope) store16_device_scope(p, v);
-  else *p = v;
-}
 template <bool kDeviceScope>
 __device__ __forceinline__ void put_float(float* p, float v) {
   if (kDeviceScope) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -94,35 +78,13 @@ __device__ __forceinline__ uint4 decode8_bf16(uint32_t w0, uint32_t w1, float sc
                     pack_bf16x2(c.x * sc, c.y * sc), pack_bf16x2(e.x * sc, e.y * sc));
 }
 template <bool kDeviceScope>
-__device__ __forceinline__ void fp8_chunk_prepare(const AttnStep& s, int c, int64_t first, int64_t stride) {
+__device__ __forceinline__ void fp8_chunk_records(const AttnStep& s, int c, int64_t first, int64_t stride) {
   const AttnStep::Chunk& ch = s.chunk[c];
   int tile0 = 0, nt_total = 0;                          // first tile of the chunk, tiles of all chunks
   for (int i = 0; i < s.n_multi; ++i) {
     if (i < c) tile0 += (s.chunk[i].Sc + 63) / 64;
     nt_total += (s.chunk[i].Sc + 63) / 64;
   }
-  const int64_t rows = (int64_t)s.B * s.H * ch.Sc;      // (head, token) rows of d = 128 or 64 codes
-  const int ush = s.d == 64 ? 2 : 3;                    // log2 of the 16-code units per row
-  const uint4* kc = (const uint4*)ch.k_src;
-  const uint4* vc = (const uint4*)ch.v_src;
-  uint4* kd = (uint4*)ch.k;
-  uint4* vd = (uint4*)ch.v;
-  auto emit = [&](int64_t u, const uint4& a, const uint4& b, float vs) {
-    put16<kDeviceScope>(kd + 2 * u, decode8_bf16(a.x, a.y, 1.0f));
-    put16<kDeviceScope>(kd + 2 * u + 1, decode8_bf16(a.z, a.w, 1.0f));
-    put16<kDeviceScope>(vd + 2 * u, decode8_bf16(b.x, b.y, vs));
-    put16<kDeviceScope>(vd + 2 * u + 1, decode8_bf16(b.z, b.w, vs));
-  };
-  const int64_t units = rows << ush;
-  int64_t u = first;
-  for (; u + 3 * stride < units; u += 4 * stride) {     // the loads of four units in flight per lane
-    const uint4 a0 = kc[u], b0 = vc[u], a1 = kc[u + stride], b1 = vc[u + stride];
-    const uint4 a2 = kc[u + 2 * stride], b2 = vc[u + 2 * stride], a3 = kc[u + 3 * stride], b3 = vc[u + 3 * stride];
-    const float s0 = ch.v_scale_src[u >> ush], s1 = ch.v_scale_src[(u + stride) >> ush];
-    const float s2 = ch.v_scale_src[(u + 2 * stride) >> ush], s3 = ch.v_scale_src[(u + 3 * stride) >> ush];
-    emit(u, a0, b0, s0); emit(u + stride, a1, b1, s1); emit(u + 2 * stride, a2, b2, s2); emit(u + 3 * stride, a3, b3, s3);
-  }
-  for (; u < units; u += stride) emit(u, kc[u], vc[u], ch.v_scale_src[u >> ush]);
   const float scale2 = s.scale * 1.44269504088896340736f;
   const uint32_t ntc = (uint32_t)(ch.Sc + 63) / 64;
   const int64_t slots = (int64_t)s.B * s.H * ntc * 64;
@@ -134,31 +96,134 @@ __device__ __forceinline__ void fp8_chunk_prepare(const AttnStep& s, int c, int6
     put_float<kDeviceScope>(s.ext + (((int64_t)bh * nt_total + tile0 + tile) << 6) + (i & 63), f);
   }
 }
-// The copy work-groups of a launch over several FP8 chunks: chunk 1, 2, .. decoded and counted.
-__device__ __forceinline__ void stream_chunks_fp8(const AttnStep& s, int wg, int tid, int nthr) {
-  const int groups = s.copy_groups;
-  for (int c = 1 + wg % groups; c < s.n_multi; c += groups) {
-    fp8_chunk_prepare<true>(s, c, (int64_t)(wg / groups) * nthr + tid, (int64_t)(s.copy_wgs / groups) * nthr);
-    publish_chunk(s.arrive + c, tid);
+// A chunk decoded by a launch of its own.  A thread takes 8 codes at a time, so that a store instruction writes 1024
+// consecutive bytes: with 16 codes and two stores each wrote every other 16 bytes.
+__device__ __forceinline__ void fp8_chunk_prepare(const AttnStep& s, int c, int64_t first, int64_t stride) {
+  const AttnStep::Chunk& ch = s.chunk[c];
+  const int ush = s.d == 64 ? 3 : 4;                    // log2 of the 8-code units per row
+  const uint2* kc = (const uint2*)ch.k_src;
+  const uint2* vc = (const uint2*)ch.v_src;
+  uint4* kd = (uint4*)ch.k;
+  uint4* vd = (uint4*)ch.v;
+  const int64_t units = ((int64_t)s.B * s.H * ch.Sc) << ush;
+  int64_t u = first;
+  for (; u + 3 * stride < units; u += 4 * stride) {     // the loads of four units in flight per lane
+    uint2 a[4], b[4];
+    float sc[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { a[i] = kc[u + i * stride]; b[i] = vc[u + i * stride]; sc[i] = ch.v_scale_src[(u + i * stride) >> ush]; }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { kd[u + i * stride] = decode8_bf16(a[i].x, a[i].y, 1.0f); vd[u + i * stride] = decode8_bf16(b[i].x, b[i].y, sc[i]); }
+  }
+  for (; u < units; u += stride) {
+    const uint2 a = kc[u], b = vc[u];
+    const float sc = ch.v_scale_src[u >> ush];
+    kd[u] = decode8_bf16(a.x, a.y, 1.0f);
+    vd[u] = decode8_bf16(b.x, b.y, sc);
+  }
+  fp8_chunk_records<false>(s, c, first, stride);
+}
+// ---- the copy work-groups of a launch over a ring ----
+// They are few (the CUs that the attention leaves free) and the ring waits for them: a chunk of 24 heads x 1152 keys took
+// 40 of them 21 us in bf16 and 24 in FP8, where the attention needs 15 for it.  So loads run two batches ahead of the
+// stores, through registers, bounded by descriptors, so that no test and no tail stand between them; the stores are
+// builtins, whose count the compiler knows (behind stores in inline asm it waited for their acknowledgement before the
+// next batch could be used); and an FP8 thread takes 8 codes at a time, so that a store instruction writes whole lines
+// (with 16 codes and two stores each wrote every other 16 bytes, straight through to memory).  That ring's calls
+// with the transfers inside, inputs changing: bf16 84.5 -> 73 us, FP8 104 -> 82; B = 2, H = 12, Sq = 150, FP8, eight of 320
+// keys 56 -> 50.
+typedef uint32_t copy_u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t copy_u32x4 __attribute__((ext_vector_type(4)));
+typedef __amdgpu_buffer_rsrc_t CopyBuf;
+constexpr int kCopyBatch = 2;          // units per thread and batch: 2, 3, 4 and 8 bring long chunks equally fast, and what a batch has past the end costs the address unit too
+constexpr int kCopyDeviceScope = 16;   // cache policy of a buffer store: sc1
+__device__ __forceinline__ CopyBuf copy_buffer(const void* p, int64_t bytes) {   // (what lies past the bytes loads as zeros, and is not stored)
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)(bytes < 0 ? 0 : bytes < 0x7fffffff ? bytes : 0x7fffffff), 0x00020000);
+}
+// Batches 0 .. n - 1 through `load(batch, buffer)` and `store(batch, buffer)`, buffer a constant 0, 1 or 2.  Loads of batches
+// past the last are empty (their descriptors hold nothing): a branch around them would cost the others their distance, as
+// the wait in front of a store has to be right for both ways.
+template <class Load, class Store>
+__device__ __forceinline__ void copy_pipeline(int n, Load load, Store store) {
+  load(0, 0);
+  load(1, 1);
+  for (int i = 0; i < n; i += 3) {
+    load(i + 2, 2);
+    store(i, 0);
+    if (i + 1 >= n) break;
+    load(i + 3, 0);
+    store(i + 1, 1);
+    if (i + 2 >= n) break;
+    load(i + 4, 1);
+    store(i + 2, 2);
   }
 }
+// Chunk c of a launch over several FP8 chunks, decoded (fp8_chunk_prepare's arithmetic)
+__device__ __forceinline__ void stream_chunk_fp8(const AttnStep& s, int c, int first, int stride) {
+  constexpr int kU = kCopyBatch;                          // units of 8 codes of K and of V
+  const AttnStep::Chunk& ch = s.chunk[c];
+  const int ush = s.d == 64 ? 3 : 4;                      // log2 of the units per row
+  const int64_t rows = (int64_t)s.B * s.H * ch.Sc, units = rows << ush;
+  const int64_t span = (int64_t)stride * kU;              // (stride is a multiple of 512: a batch begins with a row)
+  copy_u32x2 k[3][kU], v[3][kU];
+  float sc[3][kU];
+  copy_pipeline((int)((units + span - 1) / span),
+      [&](int i, int buf) __attribute__((always_inline)) {
+        const int64_t u0 = i * span;
+        const CopyBuf kb = copy_buffer((const uint2*)ch.k_src + u0, (units - u0) * 8), vb = copy_buffer((const uint2*)ch.v_src + u0, (units - u0) * 8);
+        const CopyBuf sb = copy_buffer(ch.v_scale_src + (u0 >> ush), (rows - (u0 >> ush)) * 4);
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+          const int at = first + u * stride;
+          k[buf][u] = __builtin_amdgcn_raw_buffer_load_b64(kb, at * 8, 0, 0);
+          v[buf][u] = __builtin_amdgcn_raw_buffer_load_b64(vb, at * 8, 0, 0);
+          sc[buf][u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(sb, (at >> ush) * 4, 0, 0));
+        }
+      },
+      [&](int i, int buf) __attribute__((always_inline)) {
+        const int64_t u0 = i * span;
+        const CopyBuf kd = copy_buffer((const uint4*)ch.k + u0, (units - u0) * 16), vd = copy_buffer((const uint4*)ch.v + u0, (units - u0) * 16);
+        auto put = [](CopyBuf b, int off, const uint4& x) { __builtin_amdgcn_raw_buffer_store_b128(copy_u32x4{x.x, x.y, x.z, x.w}, b, off, 0, kCopyDeviceScope); };
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+          const int off = (first + u * stride) * 16;
+          put(kd, off, decode8_bf16(k[buf][u][0], k[buf][u][1], 1.0f));
+          put(vd, off, decode8_bf16(v[buf][u][0], v[buf][u][1], sc[buf][u]));
+        }
+      });
+}
+// Chunk c of a launch over several bf16 chunks
+__device__ __forceinline__ void stream_chunk(const AttnStep& s, int c, int first, int stride) {
+  constexpr int kU = kCopyBatch;                          // 16-byte units
+  const int64_t bytes = s.chunk[c].bytes;                 // (the host passes 16-byte multiples, 16-byte aligned)
+  const int64_t span = (int64_t)stride * kU * 16;
+  const int per = (int)((bytes + span - 1) / span);       // batches of K, then of V
+  copy_u32x4 r[3][kU];
+  copy_pipeline(2 * per,
+      [&](int i, int buf) __attribute__((always_inline)) {
+        const int64_t at = (i < per ? i : i - per) * span;
+        const CopyBuf b = copy_buffer((const char*)(i < per ? s.chunk[c].k_src : s.chunk[c].v_src) + at, bytes - at);
+#pragma unroll
+        for (int u = 0; u < kU; ++u) r[buf][u] = __builtin_amdgcn_raw_buffer_load_b128(b, (first + u * stride) * 16, 0, 0);
+      },
+      [&](int i, int buf) __attribute__((always_inline)) {
+        const int64_t at = (i < per ? i : i - per) * span;
+        const CopyBuf b = copy_buffer((const char*)(i < per ? s.chunk[c].k : s.chunk[c].v) + at, bytes - at);
+#pragma unroll
+        for (int u = 0; u < kU; ++u) __builtin_amdgcn_raw_buffer_store_b128(r[buf][u], b, (first + u * stride) * 16, 0, kCopyDeviceScope);
+      });
+}
+// Copy work-group wg: its group's chunks, each counted when its stores have been acknowledged
+template <bool kFp8>
 __device__ __forceinline__ void stream_chunks(const AttnStep& s, int wg, int tid, int nthr) {
   const int groups = s.copy_groups;
-  const int64_t stride = (int64_t)(s.copy_wgs / groups) * nthr;
-  const int64_t first = (int64_t)(wg / groups) * nthr + tid;
+  const int stride = s.copy_wgs / groups * nthr;
+  const int first = wg / groups * nthr + tid;
   for (int c = 1 + wg % groups; c < s.n_multi; c += groups) {
-    const int64_t n = s.chunk[c].bytes >> 4;           // the host passes 16-byte multiples, 16-byte aligned
-    for (int t = 0; t < 2; ++t) {
-      const uint4* s4 = (const uint4*)(t ? s.chunk[c].v_src : s.chunk[c].k_src);
-      uint4* d4 = (uint4*)(t ? s.chunk[c].v : s.chunk[c].k);
-      int64_t i = first;
-      for (; i + 3 * stride < n; i += 4 * stride) {   // four loads in flight per lane
-        const uint4 a = s4[i], b = s4[i + stride], e = s4[i + 2 * stride], f = s4[i + 3 * stride];
-        store16_device_scope(d4 + i, a); store16_device_scope(d4 + i + stride, b);
-        store16_device_scope(d4 + i + 2 * stride, e); store16_device_scope(d4 + i + 3 * stride, f);
-      }
-      for (; i < n; i += stride) store16_device_scope(d4 + i, s4[i]);
-    }
+    if (kFp8) {
+      stream_chunk_fp8(s, c, first, stride);
+      fp8_chunk_records<true>(s, c, first, stride);
+    } else stream_chunk(s, c, first, stride);
     publish_chunk(s.arrive + c, tid);
   }
 }

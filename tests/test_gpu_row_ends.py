@@ -58,3 +58,28 @@ def test_references_that_lag(levels, flags, d):
     torch.cuda.synchronize()
     ro, rl = orc.ring_attention(q, [kb], [v], 1.0, None)
     _assert_parity(host_f64(out), host_f64(lse), ro, rl)
+
+
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("fp8", [False, True])
+@pytest.mark.parametrize("H,lens", [(1, (64, 64)), (1, (640, 1)), (3, (321, 319, 322)), (5, (128, 192, 64, 640)), (2, (2048, 2111))])
+def test_transfers_of_any_length(H, lens, fp8, d):
+    """The ring's transfers inside the launch: batches that a chunk does not fill, chunks of less than one."""
+    import paper_2602_10940_amd as P
+    wl = W.Workload("moved", 23, 1, H, d, 70, lens, "bf16")
+    inp = W.make_attention_inputs(wl)
+    q, k, v = dev_bf16(inp.q), [dev_bf16(x) for x in inp.k], [dev_bf16(x) for x in inp.v]
+    ref_k, ref_v, kw = inp.k, inp.v, {}
+    if fp8:
+        packed = [[P.usp_fp8_quant(x.reshape(-1, d)) for x in t] for t in (k, v)]
+        k, v = ([p[0].reshape(1, H, -1, d) for p in t] for t in packed)
+        kw = {n: [p[1].reshape(1, H, -1) for p in t] for n, t in zip(("k_scales", "v_scales"), packed)}
+        ref_k, ref_v = ([orc.fp8_dequant(p[0].cpu().numpy(), p[1].cpu().numpy()).reshape(1, H, -1, d) for p in t] for t in packed)
+    out, lse = P.usp_ring_attn_fwd(q, k, v, softmax_scale=float(inp.softmax_scale), flags=16, **kw)
+    torch.cuda.synchronize()
+    ro, rl = orc.ring_attention(inp.q, ref_k, ref_v, float(inp.softmax_scale), None)
+    _assert_parity(host_f64(out), host_f64(lse), ro, rl)
+    if not fp8:
+        plain, plse = P.usp_ring_attn_fwd(q, k, v, softmax_scale=float(inp.softmax_scale))
+        torch.cuda.synchronize()
+        assert torch.equal(out, plain) and torch.equal(lse, plse)
