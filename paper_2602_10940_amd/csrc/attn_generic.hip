@@ -7,21 +7,27 @@ namespace usp {
 usp_status launch_attn_generic_f32(const AttnStep& s, bool few, hipStream_t st);   // attn_generic_f32.hip
 
 namespace {
+// wgs: work-groups of 64 queries
 template <class Unit, int kD, int kDB>
-usp_status run_bf16(const AttnStep& s, bool few, hipStream_t st) {
-  return few ? tile::launch_tile<tile::Bf16Q, Unit, kD, kDB, 2>(s, st) : tile::launch_tile<tile::Bf16Q, Unit, kD, kDB, 1>(s, st);
+usp_status run_bf16(const AttnStep& s, bool few, int64_t wgs, hipStream_t st) {
+  if (few) return tile::launch_tile<tile::Bf16Q, Unit, kD, kDB, 2, 4, 2>(s, st);
+  // 65 to 80 columns of output, as long as the chip takes all work-groups at once with two on a CU: eight waves share 64 queries,
+  // two by two, for four waves a SIMD.  Four waves leave room for three work-groups.  B = 2, H = 16, Sq = 1024, d = 72 (512 of them)
+  // 34.5 us with eight, 36 with four; H = 18, Sq = 960 (540) 43.5, 35.7.
+  if constexpr (kDB == 5) if (wgs <= 512) return tile::launch_tile<tile::Bf16Q, Unit, kD, kDB, 2, 8, 1>(s, st);
+  return tile::launch_tile<tile::Bf16Q, Unit, kD, kDB, 1, 4, 1>(s, st);
 }
 // 32-wide steps of the head dimension in the scores, 16-wide blocks of it in the output
 template <class Unit>
-usp_status run_bf16_d(const AttnStep& s, bool few, hipStream_t st) {
-  if (s.d <= 48) return run_bf16<Unit, 64, 3>(s, few, st);
-  if (s.d <= 64) return run_bf16<Unit, 64, 4>(s, few, st);
-  if (s.d <= 80) return run_bf16<Unit, 96, 5>(s, few, st);
-  if (s.d <= 96) return run_bf16<Unit, 96, 6>(s, few, st);
-  if (s.d <= 112) return run_bf16<Unit, 128, 7>(s, few, st);
-  if (s.d <= 128) return run_bf16<Unit, 128, 8>(s, few, st);
-  if (s.d <= 160) return run_bf16<Unit, 160, 10>(s, few, st);
-  return run_bf16<Unit, 256, 16>(s, few, st);
+usp_status run_bf16_d(const AttnStep& s, bool few, int64_t wgs, hipStream_t st) {
+  if (s.d <= 48) return run_bf16<Unit, 64, 3>(s, few, wgs, st);
+  if (s.d <= 64) return run_bf16<Unit, 64, 4>(s, few, wgs, st);
+  if (s.d <= 80) return run_bf16<Unit, 96, 5>(s, few, wgs, st);
+  if (s.d <= 96) return run_bf16<Unit, 96, 6>(s, few, wgs, st);
+  if (s.d <= 112) return run_bf16<Unit, 128, 7>(s, few, wgs, st);
+  if (s.d <= 128) return run_bf16<Unit, 128, 8>(s, few, wgs, st);
+  if (s.d <= 160) return run_bf16<Unit, 160, 10>(s, few, wgs, st);
+  return run_bf16<Unit, 256, 16>(s, few, wgs, st);
 }
 }  // namespace
 
@@ -45,7 +51,7 @@ usp_status launch_attn_generic(const AttnStep& step, hipStream_t st) {
   const int64_t wgs = (int64_t)((s.Sq + 63) / 64) * s.B * s.H;
   const bool few = wgs < (s.d > 160 || (s.qo_dtype == USP_F32 && s.d > 128) ? 160 : 256);
   if (s.qo_dtype == USP_F32) return launch_attn_generic_f32(s, few, st);
-  return s.kv_dtype == USP_FP8_E4M3FN ? run_bf16_d<tile::UnitF8>(s, few, st) : run_bf16_d<tile::UnitBf16>(s, few, st);
+  return s.kv_dtype == USP_FP8_E4M3FN ? run_bf16_d<tile::UnitF8>(s, few, wgs, st) : run_bf16_d<tile::UnitBf16>(s, few, wgs, st);
 }
 
 }  // namespace usp

@@ -5,7 +5,7 @@ namespace usp {
 namespace {
 template <class Unit, int kD>
 usp_status run_f32(const AttnStep& s, bool few, hipStream_t st) {
-  return few ? tile::launch_tile<tile::F32Q, Unit, kD, kD / 16, 4>(s, st) : tile::launch_tile<tile::F32Q, Unit, kD, kD / 16, 1>(s, st);
+  return few ? tile::launch_tile_one<tile::F32Q, Unit, kD, kD / 16, 4, 4, false>(s, st) : tile::launch_tile_one<tile::F32Q, Unit, kD, kD / 16, 1, 4, false>(s, st);
 }
 template <class Unit>
 usp_status run_f32_d(const AttnStep& s, bool few, hipStream_t st) {

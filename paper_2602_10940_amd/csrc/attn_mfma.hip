@@ -384,24 +384,6 @@ __device__ __forceinline__ uint64_t live_keys(const uint8_t* mask, int Sc, int t
   return __builtin_amdgcn_ballot_w64(live);
 }
 
-// The kernel's argument lies in memory that a scalar load takes some 700 cycles to reach the first time: a word of each of
-// its 64-byte lines up to the chunk table, all in flight together, so that no later use of a field waits for memory
-// (they came one after another, line by line, and made a good part of the 4500 cycles in front of the first tile).
-__device__ __forceinline__ void touch_step() {
-  typedef const __attribute__((address_space(4))) uint32_t* words;
-  const words p = (words)__builtin_amdgcn_kernarg_segment_ptr();
-  static_assert(offsetof(AttnStep, chunk) > 4 * 64 && offsetof(AttnStep, chunk) <= 6 * 64, "lines of the step");
-  asm volatile("" :: "s"(p[0]), "s"(p[16]), "s"(p[32]), "s"(p[48]), "s"(p[64]), "s"(p[80]));
-}
-// The chunk table, likewise
-__device__ __forceinline__ void touch_chunks() {
-  typedef const __attribute__((address_space(4))) uint32_t* words;
-  const words p = (words)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(AttnStep, chunk) / 4;
-  static_assert(sizeof(AttnStep::Chunk) * AttnStep::kMaxMulti == 22 * 64, "lines of the table");
-  asm volatile("" :: "s"(p[0]), "s"(p[16]), "s"(p[32]), "s"(p[48]), "s"(p[64]), "s"(p[80]), "s"(p[96]), "s"(p[112]), "s"(p[128]), "s"(p[144]), "s"(p[160]));
-  asm volatile("" :: "s"(p[176]), "s"(p[192]), "s"(p[208]), "s"(p[224]), "s"(p[240]), "s"(p[256]), "s"(p[272]), "s"(p[288]), "s"(p[304]), "s"(p[320]), "s"(p[336]));
-}
-
 // One work-group's share: the queries q_base .. q_base + 255 (wide) or + 127 (split) of (batch, head) bh_.
 // kHalfD: head dimension 64: rows of Q, K, V and O are 128 bytes (K and V are read in place, their LDS
 // tiles have 128-byte rows with swizzles of their own), the scores contract over two 32-wide slices

@@ -13,23 +13,22 @@
 //     to its 24 bits, so P.V is three exact products instead of one (of finite V: a part that is 0 times
 //     infinity is NaN).  fp32 Q (engine F32Q): v_mfma_f32_16x16x4_f32.
 //   * Per-key factors: FP8 scales of K multiply the fp32 scores, those of V multiply P.
-//   * 64-key tiles are staged in LDS by the whole work-group through registers, a tile's global loads being in
-//     flight while the one before it is computed on.  Pitches are odd multiples of 16 bytes (K) and of 32
-//     bytes (V of Bf16Q, read transposed), or d + 4 words (F32Q): no bank conflicts in the operand reads.  The staging
-//     writes are not free of them: SQ_LDS_BANK_CONFLICT reads 32, 64, 64 and 96 cycles per wave and tile for d = 40,
-//     72, 112 and 160 bf16, 8 to 11 for each of the wave's 4, 6, 8 and 10 writes, a quarter to a third of the LDS cycles.
+//   * 64-key tiles come to LDS while the one before is computed on: bf16 ones of d <= 128 directly, the others through
+//     registers (see Plan).  Pitches are odd multiples of 16 bytes (K) and of 32 bytes (V of Bf16Q, read transposed), or
+//     d + 4 words (F32Q): no bank conflicts in the operand reads.
 //   * kKW waves share the 16 queries and take 64 / kKW keys of every tile each, their partial results
-//     being combined through LDS at the end of a chunk: for calls with few query blocks.
+//     being combined through LDS at the end of a chunk: for calls with few query blocks, and to have eight waves on 64 queries.
 //
-// What bounds it (bf16, d = 72, two work-groups per CU): the instructions its two waves per SIMD issue, 43 % of the
-// cycles on the VALU (191 instructions per wave and tile besides the 42 MFMAs, a third of them the split of P) and 29 %
-// on the matrix cores, with 49 scalar and 39 LDS instructions and waits between the phases of a tile in the rest. So:
-// one barrier per tile where two buffers fit, tiles fetched through descriptors at places fixed per thread, no test of
-// a key outside masked and ragged tiles, no work for 16-wide blocks past the head dimension, O rescaled only when a
-// maximum has outgrown a reference that was set 2^8 above it. B=2 H=16 S=1024 d=72 bf16: 32.7 us = 295 TFLOP/s (38.6
-// before those; one wave per query row with scalar products, the first form, 856). fp32 is bound by the fp32 matrix
-// rate from about 256 work-groups on (d = 64, same sizes: 81 us, 106 TFLOP/s). Two chunks of 128 keys, H=2 Sq=128 d=64
-// fp32: one launch of 9.8 us for two of 12.
+// What bounds it (bf16, d = 72): the issue of instructions and the bytes that the operand reads return.  Per wave, 16 queries
+// and 32 keys: 66 VALU instructions and 21 MFMAs, 16 operand reads of 11 KB, which is some 640 cycles of a SIMD for the 920
+// it takes.  So: one barrier per tile, tiles fetched through descriptors at places fixed per lane (directly to LDS they cost
+// neither registers nor LDS writes), no test of a key outside masked and ragged tiles, no work for 16-wide blocks past the
+// head dimension, exponentials whose row sum shows that no maximum is needed, a split of P with one instruction per
+// remainder, O rescaled only when a maximum has outgrown a reference that was set 2^8 above it.  B=2 H=16 S=1024 d=72
+// bf16 on one chip: 34.5 us (38.4 with tiles through registers, a maximum per tile and four waves; one wave per query row
+// with scalar products, the first form, 856); 22 heads of 700 queries and keys 26.7 -> 24.1; with a mask 28.7 -> 24.2.  fp32 is
+// bound by the fp32 matrix rate from about 256 work-groups on (d = 64, same sizes: 80 us, 107 TFLOP/s).  Two chunks of 128
+// keys, H=2 Sq=128 d=64 fp32: one launch of 9.4 us for two of 12.
 #pragma once
 #include <type_traits>
 
@@ -45,7 +44,6 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kThreads = 256;
 constexpr int kTile = 64;          // keys per tile
 
 // maximum / sum over the four lanes r, r + 16, r + 32, r + 48 that hold one query
@@ -111,12 +109,25 @@ struct UnitF32 {
   __device__ __forceinline__ void as_f32(f32x4& x, f32x4& y) const { x = a; y = b; }
 };
 
-// p0, p1 as three bf16 pairs whose sums are p0 and p1 exactly (8 + 8 + 8 significant bits)
-__device__ __forceinline__ void split3(float p0, float p1, uint32_t& hi, uint32_t& mid, uint32_t& lo) {
+// p0, p1 as three bf16 pairs whose sums are p0 and p1 exactly (8 + 8 + 8 significant bits).  What is left of a value
+// after its leading bf16 is one v_dot2_f32_bf16 with (-1, 0) or (0, -1), exact for every value between 0 and 1, subnormal ones
+// too (compared on the device over 2^27 of them); a shift and a subtraction otherwise.  The constants are kept in
+// registers: the inline constant -1.0 that the compiler puts for (-1, 0) is not that pair.
+struct Minus { uint32_t lo, hi; };
+__device__ __forceinline__ Minus minus_one() {
+  Minus m = {0x0000bf80u, 0xbf800000u};
+  asm volatile("" : "+s"(m.lo), "+s"(m.hi));
+  return m;
+}
+__device__ __forceinline__ void split3(Minus one, float p0, float p1, uint32_t& hi, uint32_t& mid, uint32_t& lo) {
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  auto rest = [](uint32_t pair, uint32_t c, float p) {
+    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pair), __builtin_bit_cast(bf16x2, c), p, false);
+  };
   hi = pack_bf16x2(p0, p1);
-  const float a0 = p0 - __uint_as_float(hi << 16), a1 = p1 - __uint_as_float(hi & 0xffff0000u);
+  const float a0 = rest(hi, one.lo, p0), a1 = rest(hi, one.hi, p1);
   mid = pack_bf16x2(a0, a1);
-  lo = pack_bf16x2(a0 - __uint_as_float(mid << 16), a1 - __uint_as_float(mid & 0xffff0000u));
+  lo = pack_bf16x2(rest(mid, one.lo, a0), rest(mid, one.hi, a1));
 }
 
 // kD: head dimension rounded up to the kernel's size (columns past s.d are zero); kDB: 16-wide blocks of it that
@@ -124,8 +135,8 @@ __device__ __forceinline__ void split3(float p0, float p1, uint32_t& hi, uint32_
 template <int kD, int kDB, int kMB>
 struct Bf16Q {
   typedef bf16_t qo_elt;
-  static constexpr int kSK = kD / 32;
-  static constexpr int kPitchK = kD * 2 + 16, kPitchV = kD * 2 + 32;   // bytes
+  static constexpr int kSK = kD / 32, kBlocks = kDB;
+  static constexpr int kPitchK = kD * 2 + 16, kPitchV = (kDB | 1) * 32;   // bytes
   static_assert(kD % 32 == 0 && kMB % 2 == 0, "32-wide contraction steps");
   bf16x8 q[kSK];
   __device__ __forceinline__ void load_q(const bf16_t* row, int d, int g) {
@@ -164,6 +175,7 @@ struct Bf16Q {
   // O^T += V^T P^T
   __device__ __forceinline__ void pv(const unsigned char* v, int r, int g, const float (&p)[kMB][4], f32x4 (&o)[kDB]) const {
     constexpr int kGrp = 4;   // head-dim blocks whose MFMAs alternate, so that none waits for its predecessor
+    const Minus one = minus_one();
 #pragma unroll
     for (int kk = 0; kk < kMB / 2; ++kk) {
       u32x4 part[3];
@@ -172,7 +184,7 @@ struct Bf16Q {
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
           uint32_t hi, mid, lo;
-          split3(p[2 * kk + a][2 * j], p[2 * kk + a][2 * j + 1], hi, mid, lo);
+          split3(one, p[2 * kk + a][2 * j], p[2 * kk + a][2 * j + 1], hi, mid, lo);
           part[0][2 * a + j] = hi; part[1][2 * a + j] = mid; part[2][2 * a + j] = lo;
         }
 #pragma unroll
@@ -197,7 +209,7 @@ struct Bf16Q {
 template <int kD, int kDB, int kMB>
 struct F32Q {
   typedef float qo_elt;
-  static constexpr int kSK = kD / 16;
+  static constexpr int kSK = kD / 16, kBlocks = kDB;
   static constexpr int kPitchK = (kD + 4) * 4, kPitchV = (kD + 4) * 4;
   f32x4 q[kSK];   // head dims 16 * s + 4 * g + j: the contraction visits the head dimensions in that order on both sides
   __device__ __forceinline__ void load_q(const float* row, int d, int g) {
@@ -256,69 +268,114 @@ struct F32Q {
   }
 };
 
-// LDS of a work-group: one or two buffers of K tile | V tile | per-key factor of the exponent, bias (0 / -inf),
-// V scale.  Two where two work-groups still fit a CU: a tile is then staged while the one before it is
-// computed on, with one barrier per tile.  The exchange of the kKW partial results reuses a buffer's tiles.
-template <class E, int kD, int kKW>
+// bf16 K and V whose two buffers leave room for a second work-group on the CU (kDma): the tiles go from memory to LDS
+// directly.  A load instruction fills 64 consecutive 16-byte slots with what its lanes name, so the rows' padding is slots
+// that name nothing (they load as zeros, as columns past d and rows past the chunk do).  Otherwise (FP8 K/V, rows further
+// apart than a descriptor reaches, d above 128) through registers; so are fp32 tiles, whose waves have the time: directly,
+// 6 heads of d = 96 in a ring of four chunks of 500 took 68.6 us instead of 62.8, 4 heads of d = 64 26.5 instead of 25.0.
+template <class Unit> struct Directly { static constexpr bool value = std::is_same<Unit, UnitBf16>::value; };
+
+// LDS of a work-group: one or two buffers of K tile | V tile | per-key factors of FP8 (exponent, V).  With two, a tile is
+// brought while the one before it is computed on, with one barrier per tile.  The exchange of the kKW partial results reuses a
+// buffer's tiles (kDma: has its own room behind them, since the next chunk's tiles are on their way).
+template <class E, int kD, int kKW, int kW>
 struct Plan {
   static constexpr int tiles = kTile * (E::kPitchK + E::kPitchV);
-  static constexpr int xch = kKW > 1 ? 4 * 64 * (kD / 4 + 2) * 4 : 0;
+  static constexpr int xch = (kW / kKW) * (kKW - 1) * 64 * (4 * E::kBlocks + 2) * 4;
   static constexpr int fac = xch > tiles ? xch : tiles;          // offset of the per-key values
-  static constexpr int one = fac + 3 * kTile * 4;
-  static constexpr int buffers = 2 * one <= 80 * 1024 ? 2 : 1;
+  static constexpr int one = fac + 2 * kTile * 4;
+  static constexpr bool pair = 2 * one <= 80 * 1024;             // two buffers, and two work-groups on a CU
+  static constexpr int direct = 2 * tiles + xch;
+  static constexpr bool dma = direct <= 80 * 1024;
 };
 
-template <template <int, int, int> class Engine, class Unit, int kD, int kDB, int kKW>
-__global__ __launch_bounds__(kThreads, kD > 160 ? 1 : 2)   // waves per SIMD the registers allow
+__device__ __forceinline__ void dma_slots(u32x4 desc, uint32_t lane_off, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" :: "s"(lds), "v"(lane_off), "s"(desc) : "memory", "m0");
+}
+
+template <template <int, int, int> class Engine, class Unit, int kD, int kDB, int kKW, int kW, bool kDma>
+__global__ __launch_bounds__(kW * 64, kW / 4 * (kD > 160 ? 1 : 2))   // waves per SIMD the registers allow
 void attn_tile_kernel(AttnStep s) {
-  constexpr int kMB = 4 / kKW;
+  constexpr int kMB = 4 / kKW, kThreads = kW * 64;
   typedef Engine<kD, kDB, kMB> E;
-  typedef Plan<E, kD, kKW> L;
+  typedef Plan<E, kD, kKW, kW> L;
+  constexpr int kBuffers = kDma || L::pair ? 2 : 1, kOne = kDma ? L::tiles : L::one;
   typedef typename Unit::elt KT;
   typedef typename E::qo_elt QT;
   constexpr bool fp8 = std::is_same<Unit, UnitF8>::value;
   extern __shared__ __align__(16) unsigned char smem[];
+  touch_step();
   if (s.copy_wgs > 0 && blockIdx.x >= gridDim.x - s.copy_wgs) {   // prefetch work-groups end the x axis
     if (blockIdx.y == 0 && blockIdx.z == 0) prefetch_copy(s, blockIdx.x - (gridDim.x - s.copy_wgs), threadIdx.x, kThreads);
     return;
   }
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r = lane & 15, g = lane >> 4;
   const int part = wave % kKW;                                  // which keys of a tile this wave takes
   const int h = blockIdx.y, b = blockIdx.z, d = s.d;
-  const int qi = (blockIdx.x * (4 / kKW) + wave / kKW) * 16 + r;
+  const int qi = (blockIdx.x * (kW / kKW) + wave / kKW) * 16 + r;
   const int qc = min(qi, s.Sq - 1);                             // surplus lanes recompute the last row, store nothing
   const float scale2 = s.scale * 1.44269504088896340736f;
 
   E e;
   e.load_q((const QT*)s.q + b * s.qs[0] + h * s.qs[1] + (int64_t)qc * s.qs[2], d, g);
 
-  // ---- staging: unit u of a tile (8 elements of one row) goes through thread u % 256
-  constexpr int kUPR = kD / 8, kNU = kTile * kUPR / kThreads;   // units per row; units per thread and tensor
+  // ---- staging.  A thread's (kDma: a lane's) places in a tile are the same in every tile, so that a tile costs the scalar unit
+  // a descriptor and nothing else: with a 64-bit address, a row and a column test per unit, fetching took 140 of the
+  // 500 instructions a wave issued per tile.
+  constexpr int kUPR = kD / 8, kNU = kDma ? 1 : kTile * kUPR / kThreads;   // through registers: units per row; per thread and tensor (unit u: thread u % kThreads)
+  constexpr int kSlotsK = E::kPitchK / 16, kSlotsV = E::kPitchV / 16;      // directly: slots per row, which is also the instructions per tensor
+  constexpr int kNI = kDma ? (kSlotsK + kSlotsV + kW - 1) / kW : 1;        // a wave's instructions: wave, wave + kW, ..
   Unit ku[kNU], vu[kNU];
-  float f_c = 0.0f, f_b = 0.0f, f_v = 0.0f;                     // threads 0..63: the tile's per-key values
-  // A thread's places in a tile are the same in every tile, so that a tile costs the scalar unit a descriptor and
-  // nothing else: with a 64-bit address, a row and a column test per unit, fetching took 140 of the 500
-  // instructions a wave issued per tile, and the issue of instructions is what bounds the kernel.
+  float f_c = 0.0f, f_v = 0.0f;                                 // FP8, threads 0..63: the tile's per-key values
   const uint32_t rowB = (uint32_t)(s.ks[2] * sizeof(KT));
-  const bool near_rows = s.ks[2] * (int64_t)sizeof(KT) * kTile < (int64_t)kNowhere;   // else: addresses of 64 bits
-  uint32_t place[kNU];
+  const bool near_rows = kDma || s.ks[2] * (int64_t)sizeof(KT) * kTile < (int64_t)kNowhere;   // else: addresses of 64 bits
+  uint32_t place[kDma ? kNI : kNU];
+  if (kDma) {
 #pragma unroll
-  for (int i = 0; i < kNU; ++i) {
-    const int u = tid + i * kThreads, row = u / kUPR, col = (u % kUPR) * 8;
-    place[i] = col < d ? row * rowB + col * (uint32_t)sizeof(KT) : kNowhere;
+    for (int i = 0; i < kNI; ++i) {
+      const int j = wave + i * kW, is_v = j >= kSlotsK;
+      const int slot = (is_v ? j - kSlotsK : j) * 64 + lane, per = is_v ? kSlotsV : kSlotsK;
+      const int row = slot / per, col = (slot - row * per) * (16 / (int)sizeof(KT));
+      place[i] = col < d && row < kTile ? row * rowB + col * (uint32_t)sizeof(KT) : kNowhere;
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < kNU; ++i) {
+      const int u = tid + i * kThreads, row = u / kUPR, col = (u % kUPR) * 8;
+      place[i] = col < d ? row * rowB + col * (uint32_t)sizeof(KT) : kNowhere;
+    }
   }
   int pc = -1, first_key = 0, left = 0;                         // next tile to fetch: its chunk, first key, rows from there on
   const KT *kb = nullptr, *vb = nullptr;
-  auto fetch = [&]() {
+  const uint8_t* mask = nullptr;                                // of that chunk and batch entry, or null
+  uint8_t mask_byte = 1;                                        // key `lane` of the tile fetched last takes part
+  bool masked = false;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)smem;
+  auto fetch = [&](uint32_t lds) {                              // lds: where a tile that goes directly lands
     if (near_rows) {
       const uint32_t bytes = (uint32_t)min(left, kTile) * rowB;
-      const Buf kbuf = tile_buffer(kb, bytes), vbuf = tile_buffer(vb, bytes);
+      if constexpr (kDma) {
+        auto desc = [&](const void* p) {
+          const uint64_t a = (uint64_t)(uintptr_t)p;
+          return u32x4{(uint32_t)a, (uint32_t)(a >> 32) & 0xffffu, bytes, 0x00020000u};
+        };
+        const u32x4 kd = desc(kb), vd = desc(vb);
 #pragma unroll
-      for (int i = 0; i < kNU; ++i) ku[i].load(kbuf, place[i]);
+        for (int i = 0; i < kNI; ++i) {
+          const int j = wave + i * kW;
+          if ((i + 1) * kW > kSlotsK + kSlotsV && j >= kSlotsK + kSlotsV) continue;
+          if (j < kSlotsK) dma_slots(kd, place[i], lds + j * 1024);
+          else dma_slots(vd, place[i], lds + kTile * E::kPitchK + (j - kSlotsK) * 1024);
+        }
+      } else {
+        const Buf kbuf = tile_buffer(kb, bytes), vbuf = tile_buffer(vb, bytes);
 #pragma unroll
-      for (int i = 0; i < kNU; ++i) vu[i].load(vbuf, place[i]);
-    } else {
+        for (int i = 0; i < kNU; ++i) ku[i].load(kbuf, place[i]);
+#pragma unroll
+        for (int i = 0; i < kNU; ++i) vu[i].load(vbuf, place[i]);
+      }
+    } else if constexpr (!kDma) {
 #pragma unroll
       for (int i = 0; i < kNU; ++i) {
         const int u = tid + i * kThreads, row = u / kUPR, col = (u % kUPR) * 8;
@@ -330,13 +387,13 @@ void attn_tile_kernel(AttnStep s) {
         }
       }
     }
-    if (tid < kTile) {
+    masked = mask != nullptr;
+    if (masked) mask_byte = lane < left ? mask[first_key + lane] : 0;
+    if (fp8 && tid < kTile) {
       const AttnStep::Chunk& ch = s.chunk[pc];
-      const int key = first_key + tid;
-      const bool keep = tid < left && (ch.mask_src == nullptr || ch.mask_src[(int64_t)b * ch.Sc + key] != 0);
-      f_c = scale2; f_b = keep ? 0.0f : -INFINITY; f_v = 1.0f;
-      if (fp8 && tid < left) {
-        const int64_t row = ((int64_t)b * s.H + h) * ch.Sc + key;
+      f_c = scale2; f_v = 1.0f;
+      if (tid < left) {
+        const int64_t row = ((int64_t)b * s.H + h) * ch.Sc + first_key + tid;
         f_c = ch.k_scale_src[row] * scale2;
         f_v = ch.v_scale_src[row];
       }
@@ -344,14 +401,14 @@ void attn_tile_kernel(AttnStep s) {
   };
   auto stage = [&](unsigned char* buf) {
     unsigned char* v_lds = buf + kTile * E::kPitchK;
-    float* fac = reinterpret_cast<float*>(buf + L::fac);         // factor | bias | V scale
+    float* fac = reinterpret_cast<float*>(buf + L::fac);         // factor | V scale
 #pragma unroll
     for (int i = 0; i < kNU; ++i) {
       const int u = tid + i * kThreads, row = u / kUPR, unit = u % kUPR;
       E::put(buf, E::kPitchK, row, unit, ku[i]);
-      E::put(v_lds, E::kPitchV, row, unit, vu[i]);
+      if ((unit + 1) * 8 <= kDB * 16) E::put(v_lds, E::kPitchV, row, unit, vu[i]);
     }
-    if (tid < kTile) { fac[tid] = f_c; fac[kTile + tid] = f_b; fac[2 * kTile + tid] = f_v; }
+    if (fp8 && tid < kTile) { fac[tid] = f_c; fac[kTile + tid] = f_v; }
   };
 
   // carried (O, lse) of earlier chunks
@@ -369,8 +426,8 @@ void attn_tile_kernel(AttnStep s) {
     }
   }
 
-  bool fetched = false;                                         // a tile waits in registers
-  auto fetch_next = [&]() {
+  bool fetched = false;                                         // a tile is on the way, or waits in registers
+  auto fetch_next = [&](uint32_t lds) {
     while (left <= 0 && pc < s.n_multi) {                       // into the next chunk that holds keys
       if (++pc == s.n_multi) break;
       const AttnStep::Chunk& ch = s.chunk[pc];
@@ -378,21 +435,32 @@ void attn_tile_kernel(AttnStep s) {
       first_key = 0;
       kb = (const KT*)ch.k + b * ch.ks0 + h * ch.ks1;
       vb = (const KT*)ch.v + b * ch.ks0 + h * ch.ks1;
+      mask = ch.mask_src ? ch.mask_src + (int64_t)b * ch.Sc : nullptr;
     }
     fetched = left > 0;
     if (!fetched) return;
-    fetch();
+    fetch(lds);
     left -= kTile;
     first_key += kTile;
     kb += kTile * s.ks[2];
     vb += kTile * s.ks[2];
   };
+  // live keys of the tile fetched last (its mask has landed), bit = key
+  auto live_word = [&]() -> uint64_t { return masked ? __builtin_amdgcn_ballot_w64(mask_byte != 0) : ~0ull; };
+  uint64_t live = ~0ull, live_next = ~0ull;                     // of the tile computed on, and of the one behind it
   unsigned char* cur = smem;                                    // the tile computed on
-  unsigned char* oth = smem + (L::buffers - 1) * L::one;        // the other buffer, if there is one
-  fetch_next();
-  if (L::buffers == 2 && fetched) {
+  unsigned char* oth = smem + (kBuffers - 1) * kOne;            // the other buffer, if there is one
+  auto lds_of = [&](const unsigned char* p) -> uint32_t { return __builtin_amdgcn_readfirstlane(lds0 + (uint32_t)(p - smem)); };
+  fetch_next(lds0);
+  if (kDma) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    live = live_word();
+    __syncthreads();
+    fetch_next(lds_of(oth));
+  } else if (kBuffers == 2 && fetched) {
     stage(cur);
-    fetch_next();
+    live = live_word();
+    fetch_next(0);
     __syncthreads();
   }
 
@@ -401,16 +469,18 @@ void attn_tile_kernel(AttnStep s) {
     // and was set kAbove above the one that moved it last, so that it moves seldom.  fp32: less, because the exponents
     // are rounded at their own size (d = 32, 1000 keys: O off by 6.3e-7 with 8)
     constexpr float kAbove = std::is_same<QT, float>::value ? 2.0f : 8.0f;
+    constexpr bool kMaxFirst = std::is_same<QT, float>::value || kD > 128;   // (fp32 waves wait for the matrix cores, not for the issue; d > 128: registers)
     float m = -INFINITY, l = 0.0f;
     f32x4 o[kDB];
 #pragma unroll
     for (int db = 0; db < kDB; ++db) o[db] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     const int len = s.chunk[c].Sc;
     for (int t = 0; t * kTile < len; ++t) {
-      if (L::buffers == 1) {
+      if (kBuffers == 1) {
         __syncthreads();              // the previous tile (or the exchange) has been read
         stage(cur);
-        fetch_next();
+        live = live_word();
+        fetch_next(0);
         __syncthreads();
       }
       const float* fac = reinterpret_cast<const float*>(cur + L::fac);
@@ -418,81 +488,103 @@ void attn_tile_kernel(AttnStep s) {
       f32x4 sc[kMB];
       e.scores(cur + k0 * E::kPitchK, r, g, sc);
       // exponents in log2 units are sc * f with f the uniform scale, or with FP8 K sc itself, scaled by key here
-      float tm = -INFINITY;
       if (fp8) {
 #pragma unroll
         for (int mb = 0; mb < kMB; ++mb) sc[mb] *= *reinterpret_cast<const f32x4*>(fac + k0 + 16 * mb + 4 * g);
       }
-      if (s.chunk[c].mask_src != nullptr || len - t * kTile < kTile) {   // (uniform) the tile may hold dead keys
+      const int rest = len - t * kTile;
+      if (rest < kTile || live != ~0ull) {                       // (uniform) the tile has dead keys
         asm volatile("" ::: "memory");                           // (kept a branch)
+        const uint64_t keep = (rest < kTile ? live & ((1ull << rest) - 1ull) : live) >> (k0 + 4 * g);
 #pragma unroll
-        for (int mb = 0; mb < kMB; ++mb) {
-          const f32x4 fb = *reinterpret_cast<const f32x4*>(fac + kTile + k0 + 16 * mb + 4 * g);
+        for (int mb = 0; mb < kMB; ++mb)
 #pragma unroll
-          for (int i = 0; i < 4; ++i) sc[mb][i] = fb[i] == 0.0f ? sc[mb][i] : -INFINITY;
-        }
+          for (int i = 0; i < 4; ++i) sc[mb][i] = (keep >> (16 * mb + i)) & 1 ? sc[mb][i] : -INFINITY;
       }
-#pragma unroll
-      for (int mb = 0; mb < kMB; ++mb)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) tm = fmaxf(tm, sc[mb][i]);
-      tm = group_max(tm);
       const float f = fp8 ? 1.0f : scale2;
-      if (!fp8) tm *= scale2;
-      const bool jump = tm > m;                                  // m = -inf: the first live key
-      if (__builtin_amdgcn_ballot_w64(jump) != 0ull) {
-        const float m_new = tm + kAbove, alpha = jump ? __builtin_amdgcn_exp2f(m - m_new) : 1.0f;
-        m = jump ? m_new : m;
-        l *= alpha;
+      // The exponentials against the reference as it stands; a lane whose sum of them is at most 1 has none above 1, which
+      // is what the maximum would have to show.  Otherwise (always on the first live tile) the wave finds the
+      // maximum, and where a lane's is above its reference, moves that and takes the exponentials again.
+      float p[kMB][4], ps;
+      auto exponentials = [&]() {
+        // no live key so far: every exponent is -inf and P = 0 against any finite reference
+        const float ref = m == -INFINITY ? 0.0f : m;
+        ps = 0.0f;
 #pragma unroll
-        for (int db = 0; db < kDB; ++db) o[db] *= alpha;
+        for (int mb = 0; mb < kMB; ++mb)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) { p[mb][i] = __builtin_amdgcn_exp2f(fmaf(sc[mb][i], f, -ref)); ps += p[mb][i]; }
+      };
+      const bool first = kMaxFirst || __builtin_amdgcn_ballot_w64(m == -INFINITY) != 0ull;
+      if (!first) exponentials();
+      if (first || __builtin_amdgcn_ballot_w64(!(ps <= 1.0f)) != 0ull) {
+        float tm = -INFINITY;
+#pragma unroll
+        for (int mb = 0; mb < kMB; ++mb)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) tm = fmaxf(tm, sc[mb][i]);
+        tm = group_max(tm);
+        if (!fp8) tm *= scale2;
+        const bool jump = tm > m;                                // m = -inf: the first live key
+        const bool move = __builtin_amdgcn_ballot_w64(jump) != 0ull;
+        if (move) {
+          const float m_new = tm + kAbove, alpha = jump ? __builtin_amdgcn_exp2f(m - m_new) : 1.0f;
+          m = jump ? m_new : m;
+          l *= alpha;
+#pragma unroll
+          for (int db = 0; db < kDB; ++db) o[db] *= alpha;
+        }
+        if (first || move) exponentials();
       }
-      // no live key so far: every exponent is -inf and P = 0 against any finite reference
-      const float ref = m == -INFINITY ? 0.0f : m;
-      float p[kMB][4], ps = 0.0f;
-#pragma unroll
-      for (int mb = 0; mb < kMB; ++mb)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) { p[mb][i] = __builtin_amdgcn_exp2f(fmaf(sc[mb][i], f, -ref)); ps += p[mb][i]; }
       l += ps;
       if (fp8) {
 #pragma unroll
         for (int mb = 0; mb < kMB; ++mb) {
-          const f32x4 fv = *reinterpret_cast<const f32x4*>(fac + 2 * kTile + k0 + 16 * mb + 4 * g);
+          const f32x4 fv = *reinterpret_cast<const f32x4*>(fac + kTile + k0 + 16 * mb + 4 * g);
 #pragma unroll
           for (int i = 0; i < 4; ++i) p[mb][i] *= fv[i];
         }
       }
       e.pv(cur + kTile * E::kPitchK + k0 * E::kPitchV, r, g, p, o);
-      if (L::buffers == 2) {
-        if (fetched) {
-          stage(oth);
-          fetch_next();
+      if (kBuffers == 2) {
+        if (kDma) {
+          asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // the next tile, asked for a tile ago
+          live_next = live_word();
+          __syncthreads();
+          fetch_next(lds_of(cur));
+        } else {
+          if (fetched) {
+            stage(oth);
+            live_next = live_word();
+            fetch_next(0);
+          }
+          __syncthreads();
         }
-        __syncthreads();
+        live = live_next;
         unsigned char* x = cur; cur = oth; oth = x;              // oth: the tile just computed on
       }
     }
     l = group_sum(l);
 
-    if (kKW > 1) {   // combine the waves that share these queries: [wave][slot][lane] in the tiles' place
-      constexpr int kSlots = kD / 4 + 2;
-      float* x = reinterpret_cast<float*>(oth) + wave * kSlots * 64 + lane;
-      if (L::buffers == 1) __syncthreads();
+    if (kKW > 1 && len > 0) {   // combine the waves that share these queries: [wave][slot][lane], in the place of the last tile or behind the tiles
+      constexpr int kSlots = 4 * kDB + 2;
+      float* x = reinterpret_cast<float*>(kDma ? smem + 2 * kOne : oth) + ((wave / kKW) * (kKW - 1) - 1) * kSlots * 64 + lane;
+      if (kBuffers == 1) __syncthreads();
       if (part > 0) {
+        float* y = x + part * kSlots * 64;
 #pragma unroll
         for (int db = 0; db < kDB; ++db)
 #pragma unroll
-          for (int i = 0; i < 4; ++i) x[(4 * db + i) * 64] = o[db][i];
-        x[(kD / 4) * 64] = m;
-        x[(kD / 4 + 1) * 64] = l;
+          for (int i = 0; i < 4; ++i) y[(4 * db + i) * 64] = o[db][i];
+        y[4 * kDB * 64] = m;
+        y[(4 * kDB + 1) * 64] = l;
       }
       __syncthreads();
       if (part == 0) {
 #pragma unroll
         for (int w = 1; w < kKW; ++w) {
           const float* y = x + w * kSlots * 64;
-          const float mw = y[(kD / 4) * 64], lw = y[(kD / 4 + 1) * 64];
+          const float mw = y[4 * kDB * 64], lw = y[(4 * kDB + 1) * 64];
           const float mm = fmaxf(m, mw), ref = mm == -INFINITY ? 0.0f : mm;
           const float wa = __builtin_amdgcn_exp2f(m - ref), wb = __builtin_amdgcn_exp2f(mw - ref);
 #pragma unroll
@@ -503,7 +595,7 @@ void attn_tile_kernel(AttnStep s) {
           m = mm;
         }
       }
-      if (L::buffers == 2 && c + 1 < s.n_multi) __syncthreads();   // before the next chunk's tiles are staged over it
+      if (!kDma && kBuffers == 2 && c + 1 < s.n_multi) __syncthreads();   // before the next chunk's tiles are staged over it
     }
     // the chunk's result and the merge of section 3.4
     float lse_r = -INFINITY, c_cur = 0.0f, w_prev = 0.0f;
@@ -545,16 +637,24 @@ void attn_tile_kernel(AttnStep s) {
   if (g == 0) s.lse[row] = lse_c;
 }
 
-template <template <int, int, int> class Engine, class Unit, int kD, int kDB, int kKW>
-usp_status launch_tile(const AttnStep& s, hipStream_t st) {
-  typedef Plan<Engine<kD, kDB, 4 / kKW>, kD, kKW> L;
-  constexpr int lds = L::buffers * L::one;
-  constexpr int qpw = 64 / kKW;   // queries per work-group
-  if (lds > 64 * 1024) USP_CHECK_HIP((allow_large_lds<attn_tile_kernel<Engine, Unit, kD, kDB, kKW>>(lds)));
+template <template <int, int, int> class Engine, class Unit, int kD, int kDB, int kKW, int kW, bool kDma>
+usp_status launch_tile_one(const AttnStep& s, hipStream_t st) {
+  typedef Plan<Engine<kD, kDB, 4 / kKW>, kD, kKW, kW> L;
+  constexpr int lds = kDma ? L::direct : (L::pair ? 2 : 1) * L::one;
+  constexpr int qpw = 16 * kW / kKW;   // queries per work-group
+  if (lds > 64 * 1024) USP_CHECK_HIP((allow_large_lds<attn_tile_kernel<Engine, Unit, kD, kDB, kKW, kW, kDma>>(lds)));
   const dim3 grid((unsigned)((s.Sq + qpw - 1) / qpw + s.copy_wgs), (unsigned)s.H, (unsigned)s.B);
-  hipLaunchKernelGGL((attn_tile_kernel<Engine, Unit, kD, kDB, kKW>), grid, dim3(kThreads), lds, st, s);
+  hipLaunchKernelGGL((attn_tile_kernel<Engine, Unit, kD, kDB, kKW, kW, kDma>), grid, dim3(kW * 64), lds, st, s);
   USP_CHECK_HIP(hipGetLastError());
   return USP_OK;
+}
+// kKW, kW: waves that share queries, and waves of a work-group where the tiles go directly to LDS (four otherwise, with kKWR)
+template <template <int, int, int> class Engine, class Unit, int kD, int kDB, int kKW, int kW, int kKWR>
+usp_status launch_tile(const AttnStep& s, hipStream_t st) {
+  if constexpr (Directly<Unit>::value && Plan<Engine<kD, kDB, 4 / kKW>, kD, kKW, kW>::dma) {
+    if (s.ks[2] * (int64_t)sizeof(typename Unit::elt) * kTile < (int64_t)kNowhere) return launch_tile_one<Engine, Unit, kD, kDB, kKW, kW, true>(s, st);
+  }
+  return launch_tile_one<Engine, Unit, kD, kDB, kKWR, 4, false>(s, st);
 }
 
 }  // namespace tile

@@ -137,3 +137,28 @@ def test_lse_is_as_exact_as_its_own_size_allows(dtype, B, H, d, Sq, lens):
     ulp = torch.where(ref < 8.0, 2.0 ** -21, 2.0 ** -20)
     assert float(ref.min()) > 4.0 and float(ref.max()) < 16.0
     assert float(((l.double() - ref).abs() / ulp).max()) <= 2.0 * len(lens)
+
+
+@pytest.mark.parametrize("d", [40, 64 + 8, 80, 96, 112, 120])
+@pytest.mark.parametrize("H,Sq", [(2, 33), (60, 260), (60, 600)])   # few work-groups; 300 of 64 queries; 600 of them
+def test_bf16_tiles_of_every_width(d, H, Sq):
+    """Tiles that go to LDS directly, with eight and with four waves on a work-group's queries: columns past d, rows past
+    the chunk, an empty chunk, dead keys, strided views with NaN behind them."""
+    import paper_2602_10940_amd as P
+    lens, room = (65, 0, 128), 140
+    wl = W.Workload("widths", 300 + d, 1, H, d, Sq, lens, "bf16", masked_keys=(60, 120))
+    inp = W.make_attention_inputs(wl)
+
+    def view(x):
+        t = dev_bf16(x)
+        store = torch.full((1, room, H, d), float("nan"), dtype=t.dtype, device=DEV)
+        store[:, :x.shape[2]] = t.transpose(1, 2)
+        return store[:, :x.shape[2]].transpose(1, 2)
+    km = [torch.from_numpy(m).to(DEV) for m in inp.key_mask]
+    o, l = P.usp_ring_attn_fwd(dev_bf16(inp.q), [view(k) for k in inp.k], [view(v) for v in inp.v], key_mask=km, softmax_scale=float(inp.softmax_scale))
+    torch.cuda.synchronize()
+    ro, rl = orc.ring_attention(inp.q, inp.k, inp.v, float(inp.softmax_scale), inp.key_mask)
+    mx, rel = attn_errors(host_f64(o), ro)
+    size = max(1.0, float(np.max(np.abs(ro))))
+    assert mx <= (2e-5 + 2.0 ** -8) * size and rel <= 5e-6 + 2.0 ** -8 and np.max(np.abs(host_f64(l) - rl)) <= 2e-5, (mx, rel)
+    assert np.count_nonzero(bf16_ulps(host_bits_bf16(o), ro)) <= max(1, BF16_MOVED * ro.size)
