@@ -121,7 +121,7 @@ __device__ __forceinline__ RowFinish finish_row(const AttnStep& s, float m, floa
 //          two together for the first 16 queries, wave w + 4 for the others.
 // kHalfD: head dimension 64: only the first four 16-wide blocks exist, rows are 64 wide everywhere.
 constexpr int kEpiPitch = kD * 4 + 16;                    // bytes per staged row
-constexpr int kEpiInfoB = kQPerWave * 32 + 16 * 16;       // per row: m, four partial sums l (split) or scale of O~, weight of the carry (wide); split: the 16 rows' weights
+constexpr int kEpiInfoB = kQPerWave * 32 + 16 * 16;       // per row: m, four partial sums l, factor of O~ (split) or the row's weights (wide); split: the 16 rows' weights
 constexpr int kEpiWaveB = kQPerWave * kEpiPitch + kEpiInfoB;
 
 // Rows 0 .. rows - 1 of the wave's share, of them `valid` (may be <= 0) exist.  a, b: the staged rows (b of the other half of
@@ -168,9 +168,9 @@ __device__ __forceinline__ void store_rows(const unsigned char* a, const unsigne
   }
 }
 
-// q0: the wave's first query (its pair's, in the split form).  Every tile read of the work-group is behind a barrier.
+// q0: the wave's first query (its pair's, in the split form).  lratio: factor of O~ beside 1 / l.  Every tile read of the work-group is behind a barrier.
 template <bool kSplit, bool kHalfD>
-__device__ __forceinline__ void finish_and_store(const AttnStep& s, f32x4 (&oacc)[8][2], const float (&m)[2], const float (&lsum)[2],
+__device__ __forceinline__ void finish_and_store(const AttnStep& s, f32x4 (&oacc)[8][2], const float (&m)[2], const float (&lsum)[2], const float (&lratio)[2],
                                                  int b, int h, int q0, int wave, int lane, unsigned char* smem, bool invalid, int part) {
   constexpr int kDB = kHalfD ? 4 : 8, kRowF = kHalfD ? 64 : kD;
   const int r = lane & 15, g = lane >> 4;
@@ -188,7 +188,10 @@ __device__ __forceinline__ void finish_and_store(const AttnStep& s, f32x4 (&oacc
   if (kSplit) {
 #pragma unroll
     for (int nb = 0; nb < 2; ++nb) {
-      if (g == 0) info[8 * (16 * nb + r)] = m[nb];
+      if (g == 0) {
+        info[8 * (16 * nb + r)] = m[nb];
+        info[8 * (16 * nb + r) + 5] = lratio[nb];
+      }
       info[8 * (16 * nb + r) + 1 + g] = lsum[nb];
     }
     __syncthreads();
@@ -210,7 +213,7 @@ __device__ __forceinline__ void finish_and_store(const AttnStep& s, f32x4 (&oacc
     if (s.parts > 1 && !invalid) f.c_cur = 1.0f;   // a part's O~, m and l are kept as they are (attn_combine_kernel)
     weights = reinterpret_cast<f32x4*>(epi + kQPerWave * (kEpiPitch + 32));
     if (g == 0) {
-      weights[r] = f32x4{wa, wb, f.c_cur, f.w_prev};
+      weights[r] = f32x4{wa * ia[5], wb * ib[5], f.c_cur, f.w_prev};
       if (qi < s.Sq) {
         if (s.parts > 1) *reinterpret_cast<float2*>(s.part_ml + 2 * (part * (int64_t)s.B * s.H * s.Sq + row0 + qi)) = make_float2(mm, invalid ? f.c_cur : l);
         else s.lse[row0 + qi] = f.lse_new;
@@ -226,7 +229,7 @@ __device__ __forceinline__ void finish_and_store(const AttnStep& s, f32x4 (&oacc
       const int qi = q0 + 16 * nb + r;
       const RowFinish f = finish_row(s, m[nb], l, row0 + min(qi, s.Sq - 1), invalid);
       if (g == 0) {
-        weights[16 * nb + r] = f32x4{1.0f, 0.0f, f.c_cur, f.w_prev};
+        weights[16 * nb + r] = f32x4{1.0f, 0.0f, f.c_cur * lratio[nb], f.w_prev};
         if (qi < s.Sq) s.lse[row0 + qi] = f.lse_new;
       }
     }
@@ -510,6 +513,8 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
 #pragma unroll
     for (int nb = 0; nb < 2; ++nb) oacc[db][nb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
   float m[2] = {-INFINITY, -INFINITY}, lsum[2] = {0.0f, 0.0f};   // per query block
+  float lhat[2] = {0.0f, 0.0f};   // heavy: sums of the weights as bf16 has them (see kFarMargin)
+  bool heavy = false;             // a reference has been outgrown (wave-uniform)
   bool late = false;   // an awaited chunk never arrived (see wait_arrival): the results are replaced by NaN
   int arrived_upto = 0, probe_c = 0, probe_val = 0;   // chunks known to have arrived; the count read ahead for chunk probe_c
   constexpr int kProbeAheadTiles = 4;
@@ -856,6 +861,7 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
   auto rescale = [&](int nb, float down) {
     const float a = __builtin_amdgcn_exp2f(-0.5f * down);
     lsum[nb] = lsum[nb] * a * a;
+    lhat[nb] = lhat[nb] * a * a;
 #pragma unroll
     for (int db = 0; db < 8; ++db)
 #pragma unroll
@@ -869,9 +875,15 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
   // next one is set 2^64 above, so that a third is rare: weights down to 2^-62 of the largest stay normal numbers.
   // 24 heads of 4096 queries, FP8 ring of two with such outliers: 460 us with 2^32 throughout and, after a failure, eight
   // tiles handled maximum-first; 441 with 2^72 and two such tiles, 424 with 2^72 or 425 with 2^64 and none.
+  // Heavy tails also make a row mostly one key, whose weight, far from the reference, is no power of two: what it loses
+  // to bf16 would be the row's error.  So O is divided by the sum of the weights as they multiply V, lhat, and lse alone
+  // comes from their sum in fp32: against 64 bits 1.25e-3 of O instead of 1.81e-3 (1.68e-3 with the maximum first), for
+  // 18 of the 425 us.  Summed here, where registers are free: in the matrix phase it spills, and sums on the matrix cores
+  // take as long.
   constexpr float kRefMargin = 32.0f, kFarMargin = 64.0f;
   int sm_tile = t_beg + (kSplit && !grpA ? 1 : 0);   // kDead: tile of this wave's next softmax phase
   int next_dead = 0;                         // kDead: the next tile with a dead key, as far as it has been looked up
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
   // SM of the tile whose record sits in stage xs; loads K tile kpre_idx into stage sk (if do_k, with
   // the record of tile xpre_idx into stage xst if do_x) and V tile vpre_idx into stage sv (if do_v)
   auto SM = [&](int xs, int sk, int sv, bool do_k, bool do_v, bool do_x, int xpre_idx, int xst) {
@@ -936,6 +948,11 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
     const bool redo0 = __builtin_amdgcn_ballot_w64(!(psum[0] <= kCertifiedSum)) != 0ull;
     const bool redo1 = __builtin_amdgcn_ballot_w64(!(psum[1] <= kCertifiedSum)) != 0ull;
     if (redo0 || redo1) {
+      if (!heavy && __builtin_amdgcn_ballot_w64(m[0] != -INFINITY || m[1] != -INFINITY) != 0ull) {
+        heavy = true;
+        lhat[0] = lsum[0];
+        lhat[1] = lsum[1];
+      }
       float tmax[2];
       tile_max(xs, tmax);
       if (kExt) { x_load(0, xs); x_load(1, xs); }
@@ -958,13 +975,24 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
     }
     lsum[0] += psum[0];
     lsum[1] += psum[1];
+    if (heavy) {
+      bf16x2 ones = __builtin_bit_cast(bf16x2, 0x3f803f80u);
+      asm volatile("" : "+v"(ones));   // (as an inline constant it would not be that pair)
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb) {
+          const uint32_t w = pk[i >> 2][nb][i & 3];
+          lhat[nb] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w), ones, lhat[nb], false);
+        }
+    }
     // pin the results here: without a use in this phase the optimiser sinks the exponentials past
     // the barrier, next to their first use in the matrix phase
 #pragma unroll
     for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
       for (int nb = 0; nb < 2; ++nb) asm volatile("" : "+v"(pk[kk][nb]));
-    asm volatile("" : "+v"(lsum[0]), "+v"(lsum[1]));
+    asm volatile("" : "+v"(lsum[0]), "+v"(lsum[1]), "+v"(lhat[0]), "+v"(lhat[1]));
   };
   auto nxt = [](int x) { return x == 2 ? 0 : x + 1; };
   auto first_scores = [&](int stage) {
@@ -1150,8 +1178,16 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
     if (s.arrive != nullptr) late = __syncthreads_or(late ? 1 : 0) != 0;
   }
 
+  float lratio[2] = {1.0f, 1.0f};
+  if (heavy) {
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb) {
+      const float lh = xgroup_sum(lhat[nb]);
+      if (lh > 0.0f) lratio[nb] = xgroup_sum(lsum[nb]) / lh;
+    }
+  }
   // every tile read of the work-group is behind a barrier here (the one after the last matrix phase)
-  finish_and_store<kSplit, kHalfD>(s, oacc, m, lsum, b, h, q0, wave, lane, smem_raw, kMulti && late, part);
+  finish_and_store<kSplit, kHalfD>(s, oacc, m, lsum, lratio, b, h, q0, wave, lane, smem_raw, kMulti && late, part);
 }
 
 template <bool kSplit, bool kExt, bool kMulti, bool kDead, bool kHalfD>

@@ -61,6 +61,31 @@ def test_references_that_lag(levels, flags, d):
 
 
 @pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("flags", [WIDE, SPLIT, 0, WIDE | STEPWISE])
+@pytest.mark.parametrize("at", [0, 1, 70, 130, 199, 256])
+def test_one_key_is_the_row(at, flags, d):
+    """Once a reference has been outgrown, a row that is one key's (all others count less than e^-25 together) is that key's
+    V to the bit: weight over sum of weights is 1 to fp32 rounding, however the weight itself was rounded."""
+    import paper_2602_10940_amd as P
+    rng = np.random.default_rng(at)
+    n = 257
+    q = np.zeros((1, 2, 40, d), np.float32)
+    q[..., 0] = rng.choice([1.0, 0.984375, 0.96875, 0.953125], size=(1, 2, 40))
+    k = np.zeros((1, 2, n, d), np.float32)
+    k[:, :, 64:, 0] = 100.0     # e^95 and more above the first tile
+    k[:, :, 0, 0] = -50.0
+    k[:, :, at, 0] = 135.0
+    v = W.bf16_bits_to_f32(W.f32_to_bf16_bits(rng.standard_normal((1, 2, n, d)).astype(np.float32))).reshape(1, 2, n, d)
+    lens = (128, 129) if flags & STEPWISE else (n,)
+    cut = np.cumsum((0,) + lens)
+    kd, vd = ([dev_bf16(np.ascontiguousarray(x[:, :, a:b])) for a, b in zip(cut, cut[1:])] for x in (k, v))
+    out, lse = P.usp_ring_attn_fwd(dev_bf16(q), kd, vd, softmax_scale=1.0, flags=flags)
+    torch.cuda.synchronize()
+    assert np.array_equal(host_f64(out), np.broadcast_to(v[:, :, at:at + 1], q.shape).astype(np.float64))
+    _assert_parity(host_f64(out), host_f64(lse), *orc.ring_attention(q, [k], [v], 1.0, None))
+
+
+@pytest.mark.parametrize("d", [128, 64])
 @pytest.mark.parametrize("fp8", [False, True])
 @pytest.mark.parametrize("H,lens", [(1, (64, 64)), (1, (640, 1)), (3, (321, 319, 322)), (5, (128, 192, 64, 640)), (2, (2048, 2111))])
 def test_transfers_of_any_length(H, lens, fp8, d):
