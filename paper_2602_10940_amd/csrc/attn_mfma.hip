@@ -202,7 +202,7 @@ __device__ __forceinline__ void finish_and_store(const AttnStep& s, f32x4 (&oacc
     const float* ia = reinterpret_cast<const float*>(mine + kQPerWave * kEpiPitch) + 8 * (16 * half + r);
     const float* ib = reinterpret_cast<const float*>(theirs + kQPerWave * kEpiPitch) + 8 * (16 * half + r);
     // Both under one reference, the larger of what the two have summed to (in log2 units) and not of their references,
-    // which say little about it: one may lag its sum by 2^60 and more, the other lie 2^64 above.
+    // which say little about it: one may lag its sum by 2^60 and more, the other lie 2^32 above.
     const float mA = ia[0], mB = ib[0], lA = (ia[1] + ia[2]) + (ia[3] + ia[4]), lB = (ib[1] + ib[2]) + (ib[3] + ib[4]);
     const float mm = fmaxf(mA + __builtin_amdgcn_logf(lA), mB + __builtin_amdgcn_logf(lB));
     const float wa = (lA == 0.0f) ? 0.0f : __builtin_amdgcn_exp2f(mA - mm);
@@ -513,7 +513,7 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
 #pragma unroll
     for (int nb = 0; nb < 2; ++nb) oacc[db][nb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
   float m[2] = {-INFINITY, -INFINITY}, lsum[2] = {0.0f, 0.0f};   // per query block
-  float lhat[2] = {0.0f, 0.0f};   // heavy: sums of the weights as bf16 has them (see kFarMargin)
+  float lhat[2] = {0.0f, 0.0f};   // heavy: sums of the weights as bf16 has them (see kRefMargin)
   bool heavy = false;             // a reference has been outgrown (wave-uniform)
   bool late = false;   // an awaited chunk never arrived (see wait_arrival): the results are replaced by NaN
   int arrived_upto = 0, probe_c = 0, probe_val = 0;   // chunks known to have arrived; the count read ahead for chunk probe_c
@@ -856,8 +856,8 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
     tmax[1] = xgroup_max(tmax[1]);
   };
   // O~ and l of query block nb, for a reference that moves on by `down` (>= 0, or infinity: there is nothing yet).  In two
-  // steps: what was summed under a reference that lagged by 2^60 and now counts 2^64 and more below the new one is still
-  // part of the result, and one factor 2^-down may be no normal number.
+  // steps: what was summed under a reference that lagged by 2^60 may still be part of the result, and one factor 2^-down may
+  // be no normal number.
   auto rescale = [&](int nb, float down) {
     const float a = __builtin_amdgcn_exp2f(-0.5f * down);
     lsum[nb] = lsum[nb] * a * a;
@@ -870,17 +870,16 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
   constexpr float kCertifiedSum = 1152921504606846976.0f;   // 2^60
   // A reference is set this far ABOVE the maximum that moved it: the largest P is then 2^-32
   // instead of 1, which fp32 sums and bf16 P carry as well (every P, l and O~ is scaled by the same
-  // power of two), and a later score has to exceed the maximum seen so far by 2^92, not 2^60, before
-  // the reference has to move again.  Where it does, the scores have heavy tails (x20 outliers in Q and K), and the
-  // next one is set 2^64 above, so that a third is rare: weights down to 2^-62 of the largest stay normal numbers.
-  // 24 heads of 4096 queries, FP8 ring of two with such outliers: 460 us with 2^32 throughout and, after a failure, eight
-  // tiles handled maximum-first; 441 with 2^72 and two such tiles, 424 with 2^72 or 425 with 2^64 and none.
+  // power of two; P V stays a normal number for |V| down to 2^-94), and a later score has to exceed the maximum seen so far
+  // by 2^92, not 2^60, before the reference has to move again.  No tile looks for its maximum first, not even after a move.
+  // 2^64 for the references that replace an outgrown one, as scores with heavy tails (x20 outliers in Q and K) have them,
+  // would make a third one rare, for V of 2^-90 it would leave nothing of O.
   // Heavy tails also make a row mostly one key, whose weight, far from the reference, is no power of two: what it loses
   // to bf16 would be the row's error.  So O is divided by the sum of the weights as they multiply V, lhat, and lse alone
   // comes from their sum in fp32: against 64 bits 1.25e-3 of O instead of 1.81e-3 (1.68e-3 with the maximum first), for
   // 18 of the 425 us.  Summed here, where registers are free: in the matrix phase it spills, and sums on the matrix cores
   // take as long.
-  constexpr float kRefMargin = 32.0f, kFarMargin = 64.0f;
+  constexpr float kRefMargin = 32.0f;
   int sm_tile = t_beg + (kSplit && !grpA ? 1 : 0);   // kDead: tile of this wave's next softmax phase
   int next_dead = 0;                         // kDead: the next tile with a dead key, as far as it has been looked up
   typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -959,7 +958,7 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
 #pragma unroll
       for (int nb = 0; nb < 2; ++nb) {
         if (!(nb ? redo1 : redo0)) continue;
-        const float m_new = tmax[nb] > m[nb] ? tmax[nb] + (m[nb] == -INFINITY ? kRefMargin : kFarMargin) : m[nb];
+        const float m_new = tmax[nb] > m[nb] ? tmax[nb] + kRefMargin : m[nb];
         // m = -inf (first live tile) gives the factor 0; no live key so far: nothing to rescale, P = 0
         rescale(nb, m_new == -INFINITY ? 0.0f : m_new - m[nb]);
         m[nb] = m_new;

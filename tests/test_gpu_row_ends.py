@@ -62,6 +62,30 @@ def test_references_that_lag(levels, flags, d):
 
 @pytest.mark.parametrize("d", [128, 64])
 @pytest.mark.parametrize("flags", [WIDE, SPLIT, 0, WIDE | STEPWISE])
+@pytest.mark.parametrize("size", [0, -60, -76, -84, -92])
+def test_small_values_under_outgrown_references(size, flags, d):
+    """V of 2^size beside scores whose references have been outgrown: a weight is at least 2^-32 of one where it counts, so
+    that the smallest of these products, 2^-124, is a normal number of fp32 and O as exact as for V of order one."""
+    import paper_2602_10940_amd as P
+    rng = np.random.default_rng(6)
+    levels = (0, 0, 100, 100, 62, 62, 99, 99, 20, 20)          # in pairs of tiles: both halves of the keys outgrow theirs
+    n = 64 * len(levels)
+    q = np.zeros((1, 2, 40, d), np.float32)
+    q[..., 0] = rng.choice([1.0, 0.984375, 0.96875], size=q.shape[:3])
+    k = np.zeros((1, 2, n, d), np.float32)
+    k[..., 0] = np.repeat(np.asarray(levels, np.float32), 64) - rng.integers(0, 8, size=(1, 2, n)) * 0.5   # bf16 holds these
+    v = W.bf16_bits_to_f32(W.f32_to_bf16_bits(rng.standard_normal((1, 2, n, d)).astype(np.float32))).reshape(k.shape)
+    small = np.ldexp(v, size).astype(np.float32)              # (exact: bf16 holds them)
+    lens = (192, 256, 192) if flags & STEPWISE else (n,)
+    cut = np.cumsum((0,) + lens)
+    kd, vd = ([dev_bf16(np.ascontiguousarray(x[:, :, a:b])) for a, b in zip(cut, cut[1:])] for x in (k, small))
+    out, lse = P.usp_ring_attn_fwd(dev_bf16(q), kd, vd, softmax_scale=1.0, flags=flags)
+    torch.cuda.synchronize()
+    _assert_parity(np.ldexp(host_f64(out), -size), host_f64(lse), *orc.ring_attention(q, [k], [v], 1.0, None))
+
+
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("flags", [WIDE, SPLIT, 0, WIDE | STEPWISE])
 @pytest.mark.parametrize("at", [0, 1, 70, 130, 199, 256])
 def test_one_key_is_the_row(at, flags, d):
     """Once a reference has been outgrown, a row that is one key's (all others count less than e^-25 together) is that key's
