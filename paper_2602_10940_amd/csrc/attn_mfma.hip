@@ -855,30 +855,28 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
     tmax[0] = xgroup_max(tmax[0]);
     tmax[1] = xgroup_max(tmax[1]);
   };
-  // O~ and l of query block nb, for a reference that moves on by `down` (>= 0, or infinity: there is nothing yet).  In two
-  // steps: what was summed under a reference that lagged by 2^60 may still be part of the result, and one factor 2^-down may
-  // be no normal number.
-  auto rescale = [&](int nb, float down) {
-    const float a = __builtin_amdgcn_exp2f(-0.5f * down);
-    lsum[nb] = lsum[nb] * a * a;
-    lhat[nb] = lhat[nb] * a * a;
+  // O~ and l of query block nb, for a reference that moves on.  (2^-126, the least factor that is not 0, takes what was summed
+  // under a reference that lagged by 2^60 to 2^-34 of the 2^-32 that the new largest weight has.)
+  auto rescale = [&](int nb, float alpha) {
+    lsum[nb] *= alpha;
+    lhat[nb] *= alpha;
 #pragma unroll
     for (int db = 0; db < 8; ++db)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) oacc[db][nb][e] = oacc[db][nb][e] * a * a;
+      for (int e = 0; e < 4; ++e) oacc[db][nb][e] *= alpha;
   };
   constexpr float kCertifiedSum = 1152921504606846976.0f;   // 2^60
   // A reference is set this far ABOVE the maximum that moved it: the largest P is then 2^-32
   // instead of 1, which fp32 sums and bf16 P carry as well (every P, l and O~ is scaled by the same
   // power of two; P V stays a normal number for |V| down to 2^-94), and a later score has to exceed the maximum seen so far
   // by 2^92, not 2^60, before the reference has to move again.  No tile looks for its maximum first, not even after a move.
-  // 2^64 for the references that replace an outgrown one, as scores with heavy tails (x20 outliers in Q and K) have them,
-  // would make a third one rare, for V of 2^-90 it would leave nothing of O.
+  // (2^64 for the references that replace an outgrown one, as scores with heavy tails have them, x20 outliers in Q and K,
+  // makes a third one rarer, but leaves nothing of O for V of 2^-90.)
   // Heavy tails also make a row mostly one key, whose weight, far from the reference, is no power of two: what it loses
   // to bf16 would be the row's error.  So O is divided by the sum of the weights as they multiply V, lhat, and lse alone
-  // comes from their sum in fp32: against 64 bits 1.25e-3 of O instead of 1.81e-3 (1.68e-3 with the maximum first), for
-  // 18 of the 425 us.  Summed here, where registers are free: in the matrix phase it spills, and sums on the matrix cores
-  // take as long.
+  // comes from their sum in fp32: against 64 bits 1.26e-3 of O instead of 1.84e-3 (12 heads of 4096 queries and keys with
+  // such outliers; 24 heads, FP8 ring of two 1.55e-3 instead of 2.02e-3), for 8 of 113 and 18 of 436 us.  Summed here, where registers are
+  // free: in the matrix phase it spills, and sums on the matrix cores take as long.
   constexpr float kRefMargin = 32.0f;
   int sm_tile = t_beg + (kSplit && !grpA ? 1 : 0);   // kDead: tile of this wave's next softmax phase
   int next_dead = 0;                         // kDead: the next tile with a dead key, as far as it has been looked up
@@ -946,7 +944,11 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
     // (per query block: a block all of whose lanes passed keeps its exponentials and its reference)
     const bool redo0 = __builtin_amdgcn_ballot_w64(!(psum[0] <= kCertifiedSum)) != 0ull;
     const bool redo1 = __builtin_amdgcn_ballot_w64(!(psum[1] <= kCertifiedSum)) != 0ull;
-    if (redo0 || redo1) {
+    // (kFarOff: what ordinary scores never reach lies outside the loop over the tiles.  FP8 ring of three chunks of 1152 keys,
+    // 12 heads, d = 64, 45.8 -> 43.8 us; in the 256-query form, which has no register to spare, that spills, and the mixed
+    // launch, which holds both, takes 447 us instead of 435 on 24 heads of 4096 queries, FP8 ring of two with outliers.)
+    constexpr bool kFarOff = kSplit && kMulti;
+    if (kFarOff ? __builtin_expect(redo0 || redo1, 0) : (redo0 || redo1)) {
       if (!heavy && __builtin_amdgcn_ballot_w64(m[0] != -INFINITY || m[1] != -INFINITY) != 0ull) {
         heavy = true;
         lhat[0] = lsum[0];
@@ -960,7 +962,7 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
         if (!(nb ? redo1 : redo0)) continue;
         const float m_new = tmax[nb] > m[nb] ? tmax[nb] + kRefMargin : m[nb];
         // m = -inf (first live tile) gives the factor 0; no live key so far: nothing to rescale, P = 0
-        rescale(nb, m_new == -INFINITY ? 0.0f : m_new - m[nb]);
+        rescale(nb, m_new == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f(m[nb] - m_new));
         m[nb] = m_new;
         psum[nb] = 0.0f;
         if ((kExt || kDead) && m_new == -INFINITY) {
@@ -974,7 +976,7 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
     }
     lsum[0] += psum[0];
     lsum[1] += psum[1];
-    if (heavy) {
+    if (kFarOff ? __builtin_expect(heavy, 0) : heavy) {
       bf16x2 ones = __builtin_bit_cast(bf16x2, 0x3f803f80u);
       asm volatile("" : "+v"(ones));   // (as an inline constant it would not be that pair)
 #pragma unroll
