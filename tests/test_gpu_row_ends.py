@@ -84,28 +84,45 @@ def test_small_values_under_outgrown_references(size, flags, d):
     _assert_parity(np.ldexp(host_f64(out), -size), host_f64(lse), *orc.ring_attention(q, [k], [v], 1.0, None))
 
 
+def _bf16(x):
+    return W.bf16_bits_to_f32(W.f32_to_bf16_bits(np.asarray(x, np.float32))).reshape(np.shape(x))
+
+
 @pytest.mark.parametrize("d", [128, 64])
-@pytest.mark.parametrize("flags", [WIDE, SPLIT, 0, WIDE | STEPWISE])
-@pytest.mark.parametrize("at", [0, 1, 70, 130, 199, 256])
+@pytest.mark.parametrize("flags", [WIDE, SPLIT, 0, WIDE | STEPWISE, SPLIT | STEPWISE])
+@pytest.mark.parametrize("at", [320, 364, 384, 447])
 def test_one_key_is_the_row(at, flags, d):
     """Once a reference has been outgrown, a row that is one key's (all others count less than e^-25 together) is that key's
-    V to the bit: weight over sum of weights is 1 to fp32 rounding, however the weight itself was rounded."""
+    V to the bit: weight over sum of weights is 1 to fp32 rounding, however the weight itself was rounded.  The weight lies
+    just beside the middle between two bf16 values, so that O over the sum of the unrounded weights would be another bf16
+    value for most of V, which is checked here.  (Key-split: the key is in the sixth or the seventh tile, and its half of the
+    keys has outgrown a reference two tiles ahead of it.)"""
     import paper_2602_10940_amd as P
     rng = np.random.default_rng(at)
-    n = 257
+    tiles = (0, 0, 0, 100, 100, 100, 100)
+    n = 64 * len(tiles)
     q = np.zeros((1, 2, 40, d), np.float32)
-    q[..., 0] = rng.choice([1.0, 0.984375, 0.96875, 0.953125], size=(1, 2, 40))
     k = np.zeros((1, 2, n, d), np.float32)
-    k[:, :, 64:, 0] = 100.0     # e^95 and more above the first tile
-    k[:, :, 0, 0] = -50.0
-    k[:, :, at, 0] = 135.0
-    v = W.bf16_bits_to_f32(W.f32_to_bf16_bits(rng.standard_normal((1, 2, n, d)).astype(np.float32))).reshape(1, 2, n, d)
-    lens = (128, 129) if flags & STEPWISE else (n,)
+    k[..., 0] = np.repeat(np.asarray(tiles, np.float32), 64)
+    k[:, :, at, 0] = 140.0
+    k[:, :, at, 1:3] = 1.0
+    # the key's exponent above the others', (40 q0 + q1 + q2) log2 e, is a whole number and the log2 of the weight's mantissa
+    q[..., 0] = rng.choice([1.0, 0.984375, 0.96875, 0.953125], size=(1, 2, 40))
+    mantissa = rng.choice([1.0033, 1.0045], size=(1, 2, 40))                    # (1.00390625 lies between 1 and 1.0078125)
+    up = q[..., 0].astype(np.float64) * 40 * np.log2(np.e)
+    left = (np.floor(up) + 1 + np.log2(mantissa) - up) / np.log2(np.e)
+    q[..., 1] = _bf16(left)
+    q[..., 2] = _bf16(left - q[..., 1])
+    v = _bf16(rng.standard_normal((1, 2, n, d)))
+    p = np.exp2(((q[..., 0].astype(np.float64) * 40 + q[..., 1] + q[..., 2]) * np.log2(np.e)) % 1.0)[..., None]
+    row = v[:, :, at:at + 1].astype(np.float64)
+    assert np.abs(p[..., 0] - mantissa).max() < 1e-4 and np.mean(_bf16(_bf16(p) * row / p) != row) > 0.5
+    lens = (64, 384) if flags & STEPWISE else (n,)
     cut = np.cumsum((0,) + lens)
     kd, vd = ([dev_bf16(np.ascontiguousarray(x[:, :, a:b])) for a, b in zip(cut, cut[1:])] for x in (k, v))
     out, lse = P.usp_ring_attn_fwd(dev_bf16(q), kd, vd, softmax_scale=1.0, flags=flags)
     torch.cuda.synchronize()
-    assert np.array_equal(host_f64(out), np.broadcast_to(v[:, :, at:at + 1], q.shape).astype(np.float64))
+    assert np.array_equal(host_f64(out), np.broadcast_to(row, q.shape))
     _assert_parity(host_f64(out), host_f64(lse), *orc.ring_attention(q, [k], [v], 1.0, None))
 
 
