@@ -110,8 +110,9 @@ struct UnitF32 {
 };
 
 // p0, p1 as three bf16 pairs whose sums are p0 and p1 exactly (8 + 8 + 8 significant bits).  What is left of a value
-// after its leading bf16 is one v_dot2_f32_bf16 with (-1, 0) or (0, -1), exact for every value between 0 and 1, subnormal ones
-// too (compared on the device over 2^27 of them); a shift and a subtraction otherwise.  The constants are kept in
+// after its leading bf16 is one v_dot2_f32_bf16 with (-1, 0) or (0, -1), which gives what a shift and a subtraction would for every
+// value that rounds to a finite bf16, of either sign, subnormal ones too (usp_diag_check_split3 compares all of them; with FP8 K/V
+// a weight comes times its key's V scale, so that it may have any size).  The sums are exact from 2^-109 on.  The constants are kept in
 // registers: the inline constant -1.0 that the compiler puts for (-1, 0) is not that pair.
 struct Minus { uint32_t lo, hi; };
 __device__ __forceinline__ Minus minus_one() {

@@ -162,3 +162,24 @@ def test_bf16_tiles_of_every_width(d, H, Sq):
     size = max(1.0, float(np.max(np.abs(ro))))
     assert mx <= (2e-5 + 2.0 ** -8) * size and rel <= 5e-6 + 2.0 ** -8 and np.max(np.abs(host_f64(l) - rl)) <= 2e-5, (mx, rel)
     assert np.count_nonzero(bf16_ulps(host_bits_bf16(o), ro)) <= max(1, BF16_MOVED * ro.size)
+
+
+@pytest.mark.parametrize("d,H,Sq", [(72, 3, 40), (72, 60, 300), (160, 3, 40)])
+@pytest.mark.parametrize("size", [12, 60, 100])
+def test_fp8_values_with_scales_far_from_one(size, d, H, Sq):
+    """V of 2^size in FP8: the weights come times scales of some 2^(size - 7) into the second product, split into bf16 parts there."""
+    import paper_2602_10940_amd as P
+    inp = W.make_attention_inputs(W.Workload("scaled", 40 + d, 1, H, d, Sq, (100, 65), "bf16"))
+
+    def pack(ts):
+        qs = [P.usp_fp8_quant(dev_f32(t).reshape(-1, d)) for t in ts]
+        return [q.reshape(t.shape) for (q, _), t in zip(qs, ts)], [s.reshape(t.shape[:3]) for (_, s), t in zip(qs, ts)]
+    (ks, ksc), (vs, vsc) = pack(inp.k), pack([np.ldexp(v, size).astype(np.float32) for v in inp.v])
+    o, l = P.usp_ring_attn_fwd(dev_bf16(inp.q), ks, vs, k_scales=ksc, v_scales=vsc, softmax_scale=float(inp.softmax_scale))
+    torch.cuda.synchronize()
+    kx, vx = ([orc.dequant_exact_f64(q.cpu().numpy(), s.cpu().numpy()) for q, s in zip(a, b)] for a, b in ((ks, ksc), (vs, vsc)))
+    ro, rl = orc.ring_attention(inp.q, kx, [np.ldexp(v, -size) for v in vx], float(inp.softmax_scale))
+    got = np.ldexp(host_f64(o), -size)
+    mx, rel = attn_errors(got, ro)
+    assert mx <= (2e-5 + 2.0 ** -8) * max(1.0, float(np.max(np.abs(ro)))) and rel <= 5e-6 + 2.0 ** -8 and np.max(np.abs(host_f64(l) - rl)) <= 2e-5, (mx, rel)
+    assert np.count_nonzero(bf16_ulps(host_bits_bf16(o), np.ldexp(ro, size))) <= max(1, BF16_MOVED * ro.size)
