@@ -12,8 +12,10 @@ template <class Unit, int kD, int kDB>
 usp_status run_bf16(const AttnStep& s, bool few, int64_t wgs, hipStream_t st) {
   if (few) return tile::launch_tile<tile::Bf16Q, Unit, kD, kDB, 2, 4, 2>(s, st);
   // 65 to 80 columns of output, as long as the chip takes all work-groups at once with two on a CU: eight waves share 64 queries,
-  // two by two, for four waves a SIMD.  Four waves leave room for three work-groups.  B = 2, H = 16, Sq = 1024, d = 72 (512 of them)
-  // 34.5 us with eight, 36 with four; H = 18, Sq = 960 (540) 43.5, 35.7.
+  // two by two, for four waves a SIMD.  Four waves leave room for three work-groups.  d = 72, 1024 queries and keys, with eight and
+  // four: 256 work-groups 22.1 us, 24.2; 272 27.5, 27.7; 384 27.9, 28.3; 512 29.0, 29.2; from 513 on eight need a second round
+  // (960 queries and keys, 540: 43.5, 35.7).  The neighbours have no such line: eight waves take 2 % more for d <= 64, and for d
+  // = 81 to 96 (126 registers) 3 % less at 272 to 448 work-groups and as much at 512.
   if constexpr (kDB == 5) if (wgs <= 512) return tile::launch_tile<tile::Bf16Q, Unit, kD, kDB, 2, 8, 1>(s, st);
   return tile::launch_tile<tile::Bf16Q, Unit, kD, kDB, 1, 4, 1>(s, st);
 }

@@ -13,22 +13,25 @@
 //     to its 24 bits, so P.V is three exact products instead of one (of finite V: a part that is 0 times
 //     infinity is NaN).  fp32 Q (engine F32Q): v_mfma_f32_16x16x4_f32.
 //   * Per-key factors: FP8 scales of K multiply the fp32 scores, those of V multiply P.
-//   * 64-key tiles come to LDS while the one before is computed on: bf16 ones of d <= 128 directly, the others through
-//     registers (see Plan).  Pitches are odd multiples of 16 bytes (K) and of 32 bytes (V of Bf16Q, read transposed), or
+//   * 64-key tiles come to LDS while the one before is computed on: bf16 ones of d <= 128 directly where that leaves room for
+//     two work-groups on a CU (few work-groups: d <= 112), the others through registers (see Plan).  Pitches are odd multiples of 16 bytes (K) and of 32 bytes (V of Bf16Q, read transposed), or
 //     d + 4 words (F32Q): no bank conflicts in the operand reads.
 //   * kKW waves share the 16 queries and take 64 / kKW keys of every tile each, their partial results
 //     being combined through LDS at the end of a chunk: for calls with few query blocks, and to have eight waves on 64 queries.
 //
 // What bounds it (bf16, d = 72): the issue of instructions and the bytes that the operand reads return.  Per wave, 16 queries
-// and 32 keys: 66 VALU instructions and 21 MFMAs, 16 operand reads of 11 KB, which is some 640 cycles of a SIMD for the 920
-// it takes.  So: one barrier per tile, tiles fetched through descriptors at places fixed per lane (directly to LDS they cost
+// and 32 keys: 80 VALU instructions of 4 cycles and more, 21 MFMAs of 16, 16 operand reads of 11 KB, some 700 cycles of a SIMD.
+// So: one barrier per tile, tiles fetched through descriptors at places fixed per lane (directly to LDS they cost
 // neither registers nor LDS writes), no test of a key outside masked and ragged tiles, no work for 16-wide blocks past the
-// head dimension, exponentials whose row sum shows that no maximum is needed, a split of P with one instruction per
-// remainder, O rescaled only when a maximum has outgrown a reference that was set 2^8 above it.  B=2 H=16 S=1024 d=72
-// bf16 on one chip: 34.5 us (38.4 with tiles through registers, a maximum per tile and four waves; one wave per query row
-// with scalar products, the first form, 856); 22 heads of 700 queries and keys 26.7 -> 24.1; with a mask 28.7 -> 24.2.  fp32 is
-// bound by the fp32 matrix rate from about 256 work-groups on (d = 64, same sizes: 80 us, 107 TFLOP/s).  Two chunks of 128
-// keys, H=2 Sq=128 d=64 fp32: one launch of 9.4 us for two of 12.
+// head dimension, O rescaled only when a maximum has outgrown a reference that was set 2^8 above it.  B=2 H=16 S=1024 d=72
+// bf16, a call among others: 29.0 us (32.5 with tiles through registers and four waves; one wave per query row
+// with scalar products, the first form, 857); 22 heads of 700 queries and keys 17.8 -> 15.8, 12 with a mask 19.2 -> 15.6.
+// (The exponentials against the old reference first, the maximum only where their sum does not show that none exceeds it, and
+// the remainders of the split of P as dot products with -1 were no gain: one work-group on a CU waits for the longer chain
+// of every tile.  16 heads of 1024, FP8, d = 40 29.0 us against 25.5, d = 72 34.2 against 30.7, d = 96 31.5 against 32.7; bf16,
+// d = 40 20.4 against 19.7, d = 56 22.5 against 21.6, 24 heads 26.3 against 25.2.)  fp32 is bound by the fp32 matrix
+// rate from about 256 work-groups on (d = 64, 32 heads: 80 us, 107 TFLOP/s).  Two chunks of 128 keys, H=2 Sq=128 d=64
+// fp32: one launch, 9.9 us a call.
 #pragma once
 #include <type_traits>
 
@@ -109,26 +112,12 @@ struct UnitF32 {
   __device__ __forceinline__ void as_f32(f32x4& x, f32x4& y) const { x = a; y = b; }
 };
 
-// p0, p1 as three bf16 pairs whose sums are p0 and p1 exactly (8 + 8 + 8 significant bits).  What is left of a value
-// after its leading bf16 is one v_dot2_f32_bf16 with (-1, 0) or (0, -1), which gives what a shift and a subtraction would for every
-// value that rounds to a finite bf16, of either sign, subnormal ones too (usp_diag_check_split3 compares all of them; with FP8 K/V
-// a weight comes times its key's V scale, so that it may have any size).  The sums are exact from 2^-109 on.  The constants are kept in
-// registers: the inline constant -1.0 that the compiler puts for (-1, 0) is not that pair.
-struct Minus { uint32_t lo, hi; };
-__device__ __forceinline__ Minus minus_one() {
-  Minus m = {0x0000bf80u, 0xbf800000u};
-  asm volatile("" : "+s"(m.lo), "+s"(m.hi));
-  return m;
-}
-__device__ __forceinline__ void split3(Minus one, float p0, float p1, uint32_t& hi, uint32_t& mid, uint32_t& lo) {
-  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-  auto rest = [](uint32_t pair, uint32_t c, float p) {
-    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pair), __builtin_bit_cast(bf16x2, c), p, false);
-  };
+// p0, p1 as three bf16 pairs whose sums are p0 and p1 exactly (8 + 8 + 8 significant bits)
+__device__ __forceinline__ void split3(float p0, float p1, uint32_t& hi, uint32_t& mid, uint32_t& lo) {
   hi = pack_bf16x2(p0, p1);
-  const float a0 = rest(hi, one.lo, p0), a1 = rest(hi, one.hi, p1);
+  const float a0 = p0 - __uint_as_float(hi << 16), a1 = p1 - __uint_as_float(hi & 0xffff0000u);
   mid = pack_bf16x2(a0, a1);
-  lo = pack_bf16x2(rest(mid, one.lo, a0), rest(mid, one.hi, a1));
+  lo = pack_bf16x2(a0 - __uint_as_float(mid << 16), a1 - __uint_as_float(mid & 0xffff0000u));
 }
 
 // kD: head dimension rounded up to the kernel's size (columns past s.d are zero); kDB: 16-wide blocks of it that
@@ -176,7 +165,6 @@ struct Bf16Q {
   // O^T += V^T P^T
   __device__ __forceinline__ void pv(const unsigned char* v, int r, int g, const float (&p)[kMB][4], f32x4 (&o)[kDB]) const {
     constexpr int kGrp = 4;   // head-dim blocks whose MFMAs alternate, so that none waits for its predecessor
-    const Minus one = minus_one();
 #pragma unroll
     for (int kk = 0; kk < kMB / 2; ++kk) {
       u32x4 part[3];
@@ -185,7 +173,7 @@ struct Bf16Q {
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
           uint32_t hi, mid, lo;
-          split3(one, p[2 * kk + a][2 * j], p[2 * kk + a][2 * j + 1], hi, mid, lo);
+          split3(p[2 * kk + a][2 * j], p[2 * kk + a][2 * j + 1], hi, mid, lo);
           part[0][2 * a + j] = hi; part[1][2 * a + j] = mid; part[2][2 * a + j] = lo;
         }
 #pragma unroll
@@ -416,7 +404,9 @@ void attn_tile_kernel(AttnStep s) {
   f32x4 oc[kDB];
   float lse_c = -INFINITY;
   bool carried = s.mode >= 2;
-  const int64_t row = ((int64_t)b * s.H + h) * s.Sq + qc;
+  // (bf16 with d above 128 has no register for the row's address across the tiles and forms it again at the end)
+  constexpr bool kFewRegisters = std::is_same<QT, bf16_t>::value && kD > 128;
+  int64_t row = ((int64_t)b * s.H + h) * s.Sq + qc;
   float* accp = s.acc ? s.acc + row * d : nullptr;
   if (carried && part == 0) {
     lse_c = s.lse[row];
@@ -470,7 +460,6 @@ void attn_tile_kernel(AttnStep s) {
     // and was set kAbove above the one that moved it last, so that it moves seldom.  fp32: less, because the exponents
     // are rounded at their own size (d = 32, 1000 keys: O off by 6.3e-7 with 8)
     constexpr float kAbove = std::is_same<QT, float>::value ? 2.0f : 8.0f;
-    constexpr bool kMaxFirst = std::is_same<QT, float>::value || kD > 128;   // (fp32 waves wait for the matrix cores, not for the issue; d > 128: registers)
     float m = -INFINITY, l = 0.0f;
     f32x4 o[kDB];
 #pragma unroll
@@ -503,40 +492,28 @@ void attn_tile_kernel(AttnStep s) {
           for (int i = 0; i < 4; ++i) sc[mb][i] = (keep >> (16 * mb + i)) & 1 ? sc[mb][i] : -INFINITY;
       }
       const float f = fp8 ? 1.0f : scale2;
-      // The exponentials against the reference as it stands; a lane whose sum of them is at most 1 has none above 1, which
-      // is what the maximum would have to show.  Otherwise (always on the first live tile) the wave finds the
-      // maximum, and where a lane's is above its reference, moves that and takes the exponentials again.
-      float p[kMB][4], ps;
-      auto exponentials = [&]() {
-        // no live key so far: every exponent is -inf and P = 0 against any finite reference
-        const float ref = m == -INFINITY ? 0.0f : m;
-        ps = 0.0f;
+      float tm = -INFINITY;
 #pragma unroll
-        for (int mb = 0; mb < kMB; ++mb)
+      for (int mb = 0; mb < kMB; ++mb)
 #pragma unroll
-          for (int i = 0; i < 4; ++i) { p[mb][i] = __builtin_amdgcn_exp2f(fmaf(sc[mb][i], f, -ref)); ps += p[mb][i]; }
-      };
-      const bool first = kMaxFirst || __builtin_amdgcn_ballot_w64(m == -INFINITY) != 0ull;
-      if (!first) exponentials();
-      if (first || __builtin_amdgcn_ballot_w64(!(ps <= 1.0f)) != 0ull) {
-        float tm = -INFINITY;
+        for (int i = 0; i < 4; ++i) tm = fmaxf(tm, sc[mb][i]);
+      tm = group_max(tm);
+      if (!fp8) tm *= scale2;
+      const bool jump = tm > m;                                  // m = -inf: the first live key
+      if (__builtin_amdgcn_ballot_w64(jump) != 0ull) {
+        const float m_new = tm + kAbove, alpha = jump ? __builtin_amdgcn_exp2f(m - m_new) : 1.0f;
+        m = jump ? m_new : m;
+        l *= alpha;
 #pragma unroll
-        for (int mb = 0; mb < kMB; ++mb)
-#pragma unroll
-          for (int i = 0; i < 4; ++i) tm = fmaxf(tm, sc[mb][i]);
-        tm = group_max(tm);
-        if (!fp8) tm *= scale2;
-        const bool jump = tm > m;                                // m = -inf: the first live key
-        const bool move = __builtin_amdgcn_ballot_w64(jump) != 0ull;
-        if (move) {
-          const float m_new = tm + kAbove, alpha = jump ? __builtin_amdgcn_exp2f(m - m_new) : 1.0f;
-          m = jump ? m_new : m;
-          l *= alpha;
-#pragma unroll
-          for (int db = 0; db < kDB; ++db) o[db] *= alpha;
-        }
-        if (first || move) exponentials();
+        for (int db = 0; db < kDB; ++db) o[db] *= alpha;
       }
+      // no live key so far: every exponent is -inf and P = 0 against any finite reference
+      const float ref = m == -INFINITY ? 0.0f : m;
+      float p[kMB][4], ps = 0.0f;
+#pragma unroll
+      for (int mb = 0; mb < kMB; ++mb)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) { p[mb][i] = __builtin_amdgcn_exp2f(fmaf(sc[mb][i], f, -ref)); ps += p[mb][i]; }
       l += ps;
       if (fp8) {
 #pragma unroll
@@ -624,6 +601,10 @@ void attn_tile_kernel(AttnStep s) {
   }
 
   if (part != 0 || qi >= s.Sq) return;
+  if (kFewRegisters) {                                          // (qi is qc here)
+    row = ((int64_t)b * s.H + h) * s.Sq + qi;
+    accp = s.acc + row * d;
+  }
   QT* outp = (QT*)s.out + b * s.os[0] + h * s.os[1] + (int64_t)qi * s.os[2];
 #pragma unroll
   for (int db = 0; db < kDB; ++db) {
