@@ -263,8 +263,8 @@ __device__ __forceinline__ void finish_and_store(const AttnStep& s, f32x4 (&oacc
 //             phase 2j   : A does SM(j),  B does MM(j-1)
 //             phase 2j+1 : A does MM(j),  B does SM(j)
 //   split : 128 queries per work-group, waves w and w+4 share 32 queries; group A takes the even
-//           tiles, group B the odd ones, and B's partial (O~, m, l) is folded into A's through
-//           LDS at the end.  Twice the work-groups for half the time each: for Q shards too
+//           tiles, group B the odd ones, and the two partial (O~, m, l) are put together through
+//           LDS at the end, sixteen of the 32 queries by each wave.  Twice the work-groups for half the time each: for Q shards too
 //           small to fill the chip with 256-query work-groups.
 //             phase p : the owner of tile p does SM(p), the other group MM(p-1)
 // K and V tiles go through three LDS stages each (K four in the split form), written by direct global->LDS loads issued
@@ -401,7 +401,6 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
   constexpr int kNV = kHalfD ? 2 : 4;        // operands of either kind per block of the matrix phase
   constexpr int kDB = kHalfD ? 4 : 8;        // 16-wide blocks of the head dimension that P.V produces
   constexpr int kStagesK = kSplit ? kStagesSplitK : kStages;
-  constexpr int kBurst = 1;                  // operands whose MFMAs are issued back to back before the next reads (1, 2, 4: no difference measured)
   const int h = bh_ % s.H, b = bh_ / s.H;
   // split: waves w and w+4 share their 32 queries
   const int q0 = q_base + (kSplit ? (wave & 3) : wave) * kQPerWave;
@@ -727,33 +726,23 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
       const int c = blk & 1, kk = blk >> 1;
       const bf16x8 pb0 = __builtin_bit_cast(bf16x8, pk[kk][0]), pb1 = __builtin_bit_cast(bf16x8, pk[kk][1]);
 #pragma unroll
-      for (int i = 0; i < kNV; i += kBurst) {
-#pragma unroll
-        for (int j = i; j < i + kBurst; ++j) {
-          const int db = kNV * (blk & 1) + j;
-          if (!kHalfD && (j & 1)) oacc[db][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[c][j], pb1, oacc[db][1], 0, 0, 0);
-          oacc[db][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[c][j], pb0, oacc[db][0], 0, 0, 0);
-          if (kHalfD || !(j & 1)) oacc[db][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[c][j], pb1, oacc[db][1], 0, 0, 0);
-          if (!kHalfD) __builtin_amdgcn_sched_barrier(0);
-        }
-#pragma unroll
-        for (int j = i; j < i + kBurst; ++j)
-          if (blk < 3) va[c ^ 1][j] = v_operand(sv, (blk + 1) >> 1, kNV * ((blk + 1) & 1) + j);
+      for (int j = 0; j < kNV; ++j) {
+        const int db = kNV * (blk & 1) + j;
+        if (!kHalfD && (j & 1)) oacc[db][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[c][j], pb1, oacc[db][1], 0, 0, 0);
+        oacc[db][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[c][j], pb0, oacc[db][0], 0, 0, 0);
+        if (kHalfD || !(j & 1)) oacc[db][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[c][j], pb1, oacc[db][1], 0, 0, 0);
+        if (!kHalfD) __builtin_amdgcn_sched_barrier(0);
+        if (blk < 3) va[c ^ 1][j] = v_operand(sv, (blk + 1) >> 1, kNV * ((blk + 1) & 1) + j);
         __builtin_amdgcn_sched_barrier(0);
       }
 #pragma unroll
-      for (int i = 0; i < kNV; i += kBurst) {     // (kNV is both the key blocks and, or for kHalfD, the head-dim slices)
-#pragma unroll
-        for (int j = i; j < i + kBurst; ++j) {
-          const int mb = kHalfD ? blk : j, ks = kHalfD ? j : blk;
-          if (!kHalfD && (j & 1)) sacc[mb][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[c][j], qreg[1][ks], ks == 0 ? zero4 : sacc[mb][1], 0, 0, 0);
-          sacc[mb][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[c][j], qreg[0][ks], ks == 0 ? zero4 : sacc[mb][0], 0, 0, 0);
-          if (kHalfD || !(j & 1)) sacc[mb][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[c][j], qreg[1][ks], ks == 0 ? zero4 : sacc[mb][1], 0, 0, 0);
-          if (!kHalfD) __builtin_amdgcn_sched_barrier(0);
-        }
-#pragma unroll
-        for (int j = i; j < i + kBurst; ++j)
-          if (blk < 3) ka[c ^ 1][j] = kHalfD ? k_operand(sk, blk + 1, j) : k_operand(sk, j, blk + 1);
+      for (int j = 0; j < kNV; ++j) {             // (kNV is both the key blocks and, or for kHalfD, the head-dim slices)
+        const int mb = kHalfD ? blk : j, ks = kHalfD ? j : blk;
+        if (!kHalfD && (j & 1)) sacc[mb][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[c][j], qreg[1][ks], ks == 0 ? zero4 : sacc[mb][1], 0, 0, 0);
+        sacc[mb][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[c][j], qreg[0][ks], ks == 0 ? zero4 : sacc[mb][0], 0, 0, 0);
+        if (kHalfD || !(j & 1)) sacc[mb][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[c][j], qreg[1][ks], ks == 0 ? zero4 : sacc[mb][1], 0, 0, 0);
+        if (!kHalfD) __builtin_amdgcn_sched_barrier(0);
+        if (blk < 3) ka[c ^ 1][j] = kHalfD ? k_operand(sk, blk + 1, j) : k_operand(sk, j, blk + 1);
         __builtin_amdgcn_sched_barrier(0);
       }
     }
@@ -789,7 +778,7 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
   // 2^60, no P exceeded 2^60, and neither l (at most 2^60 per key) nor O~ (at most 2^60 |v| per key)
   // leaves the fp32 range (2^127) over 2^20 keys with |v| up to 2^40; a reference that lags the
   // maximum by D only scales P, l and O~ by 2^D, which floating point carries without loss.  Only
-  // when some lane fails that test (always on the first tile, where m = -inf makes every P inf)
+  // when some lane fails that test (always on a first tile with dead keys, where m = -inf makes every P inf or NaN)
   // does the wave find the true maximum, move m, rescale O and l, and redo the exponentials.
   // While it runs, the wave also issues its tile loads, spread between the exponential blocks so
   // that the waves do not hit the load path at once.
@@ -1363,7 +1352,8 @@ int64_t attn_mfma_max_dead_tiles() { return kMaxWords; }
 // 4608 keys 57 -> 43 us; H = 1, Sq = 256, 4608 keys 57 -> 21 us; H = 4, Sq = 1024, 1024 keys 20.6 us with 1, 2 or 4.
 // One chunk of 500 to 2600 keys, d = 64 or 128, bf16 or FP8, 35 random shapes that take parts: 0.54 to 0.97 of the time.
 // (The prologue and the transfers have become shorter since these figures were taken, by 2 to 3 us and by a third: on 1660
-// random launches the choice takes 4 to 5 % more than the best number of parts on average, one chunk 1.28 times as much at most.)
+// random launches the choice takes 4 to 5 % more than the best number of parts on average, one chunk 1.28 times as much at most,
+// a ring 1.5 times.  The figures here and below are those of the launches the constants were fitted to.)
 // At most 240 work-groups, so that the copy work-groups of the same launch (16 at least) find a CU.
 //
 // A ring's chunks arrive inside the launch (FP8 chunks always; bf16 ones with USP_ATTN_FUSED_PREFETCH, and the plain
@@ -1371,8 +1361,8 @@ int64_t attn_mfma_max_dead_tiles() { return kMaxWords; }
 // for each that its group of copy work-groups has to bring one after another, and the bytes moved at 50 GB/s per
 // copy work-group, of which parts leave fewer.  A work-group ends no earlier than its share of that chunk's
 // tiles takes from there on, nor than all its tiles take from the arrival of the chunk it begins with, and it
-// spends 1 us (FP8: 2) on each chunk it enters.  With the tile times of each form this predicts 440 measured
-// launches within 7 % rms; parts have to gain 15 % there.  By the rule for one chunk alone short chunks
+// spends 1 us (FP8: 2) on each chunk it enters.  With the tile times of each form this predicted 440 launches, measured
+// with the longer prologue and slower transfers, within 7 % rms; parts have to gain 15 % there.  By the rule for one chunk alone short chunks
 // under few queries lost: B = 2, H = 12, Sq = 150, FP8, eight of 320 keys 72 us with 1 part, 103 with 5; B = 2, H = 3,
 // d = 64, Sq = 379, six of 320 34 us with 1, 50 with 10.  Long ones gain: H = 2, Sq = 108, six of 2816 202 us
 // with 1, 59 with 16.
@@ -1416,8 +1406,8 @@ AttnForm attn_mfma_form(int B, int H, int Sq, int d, int64_t tiles, const RingTr
 // per tile and 256 work-groups (idle CUs let the others clock higher), d = 64 (7.1 + 0.47 * tiles) and 0.16; a launch
 // per chunk 10.5 (d = 64: 1.1) each, 5.3 (6.5) per chunk and round, 1.48 (1.12) per tile and round, the last round counting
 // 0.6 where the mixed launch can halve its blocks (d = 128), and 0.115 (0.22) per MB of the carried fp32 O, out and
-// back between two chunks.  70 rings of 260 to 864 blocks, two to eight chunks of 64 to 4096 keys, all three timed:
-// each estimate within 12 % (d = 128: 9 %).  Per chunk, 256-query, key-split: B = 2, H = 24, Sq = 4608, two of 1536
+// back between two chunks.  70 rings of 260 to 864 blocks, two to eight chunks of 64 to 4096 keys, all three timed, with the
+// prologue 2 to 3 us longer than it is now: each estimate within 12 % (d = 128: 9 %).  Per chunk, 256-query, key-split: B = 2, H = 24, Sq = 4608, two of 1536
 // 370, 331, 363 us; B = 2, H = 22, d = 64, Sq = 4416, two of 128 92, 47, 62; H = 24, Sq = 2816, four of 1024 245,
 // 208, 184; B = 2, H = 18, Sq = 3629, two of 3008 430, 456, 432 (left per chunk).
 RingForm attn_mfma_ring_form(int B, int H, int Sq, int d, int64_t tiles, int chunks, int variant) {

@@ -158,7 +158,8 @@ struct AttnStep {
 };
 static_assert(sizeof(AttnStep) <= 4096, "AttnStep is passed by value as the kernels' only argument");
 // Copy work-groups that go with attn_wgs attention work-groups, one of which fits on a CU: the CUs the
-// attention grid leaves free, as a multiple of 8 in [16, 64] (one work-group copies about 50 GB/s).
+// attention grid leaves free, as a multiple of 8 in [16, 64] (one work-group copied about 50 GB/s when this was chosen, with
+// one batch of loads in flight; it has two now).
 inline int copy_wgs_beside(int attn_wgs) {
   const int n = (256 - attn_wgs % 256) / 8 * 8;
   return n < 16 ? 16 : (n > 64 ? 64 : n);
@@ -166,7 +167,7 @@ inline int copy_wgs_beside(int attn_wgs) {
 // Groups into which the copy work-groups of a launch over a ring fall, each with chunks of its own: a chunk is a
 // chain of load, store, acknowledgement and count that takes 4 to 5 us however short it is, so short chunks travel
 // side by side, up to eight, as long as that puts the first one off by no more than another 4 us (65 GB/s per
-// work-group; `largest`: bytes read and written for the largest chunk; `later`: chunks that travel).
+// work-group, as the copies were when this was chosen; `largest`: bytes read and written for the largest chunk; `later`: chunks that travel).
 inline int copy_groups_of(int copy_wgs, int later, int64_t largest) {
   int g = 1;
   while (g < 8 && g < later && (double)(2 * g) * (double)largest <= 4.0 * 65e3 * copy_wgs) g *= 2;   // (copy_wgs is a multiple of 8)
