@@ -10,16 +10,25 @@ namespace {
 // wgs: work-groups of 64 queries
 template <class Unit, int kD, int kDB>
 usp_status run_bf16(const AttnStep& s, bool few, int64_t wgs, hipStream_t st) {
-  // (few work-groups leave one wave to a SIMD, which waits for a tile on its way to LDS longer than for one in its registers: 16
-  // heads of 153 queries, 1793 keys, d = 56 28.4 us with direct tiles, 26.1 without, d = 96 32.7, 30.2, d = 112 35.8, 35.3)
-  if (few) return tile::launch_tile_one<tile::Bf16Q, Unit, kD, kDB, 2, 4, false>(s, st);
+  if (few) {
+    // Few work-groups leave one wave to a SIMD.  The narrow widths then wait longer for a tile on its way to LDS than for one in
+    // their registers, and d = 81 to 96 do with half the CUs busy; bytes of a mask, and LDS writes of wider rows, turn that round
+    // (d = 49 to 64 excepted).  us with direct tiles, through registers: 16 heads of 153 queries, 1793 keys, d = 40 21.7, 21.3 (masked
+    // 23.0, 23.9), d = 56 27.8, 25.6 (29.8, 30.1), d = 72 30.0, 28.9 (32.4, 34.4), d = 96 32.3, 30.0 (34.3, 35.6), d = 112 35.4, 34.8
+    // (36.7, 39.0); 2 x 5 heads of 959 queries, 634 keys, d = 56 12.7, 12.7, d = 72 13.9, 15.0, d = 96 14.9, 15.5, d = 112 16.1, 18.1;
+    // 4 heads of 512 queries, 700 keys, d = 56 11.3, 10.7, d = 72 12.3, 12.4, d = 96 12.7, 12.6, d = 112 14.2, 15.1.
+    bool masked = false;
+    for (int c = 0; c < s.n_multi; ++c) masked = masked || s.chunk[c].mask_src != nullptr;
+    if (kDB == 4 || (!masked && (kDB == 3 || (kDB == 6 && wgs <= 128)))) return tile::launch_tile_one<tile::Bf16Q, Unit, kD, kDB, 2, 4, false>(s, st);
+    return tile::launch_tile<tile::Bf16Q, Unit, kD, kDB, 2, 4, 2>(s, st);
+  }
   // 65 to 80 columns of output, as long as the chip takes all work-groups at once with two on a CU: eight waves share 64 queries,
   // two by two, for four waves a SIMD.  Four waves leave room for three work-groups.  d = 72, 1024 queries and keys, with eight and
   // four: 256 work-groups 22.1 us, 24.2; 272 27.5, 27.7; 384 27.9, 28.3; 512 29.0, 29.2; from 513 on eight need a second round
   // (960 queries and keys, 540: 43.5, 35.7).  The neighbours have no such line: eight waves take 2 % more for d <= 64, and for d
   // = 81 to 96 (126 registers) 3 % less at 272 to 448 work-groups and as much at 512.
-  if constexpr (kDB == 5) if (wgs <= 512) return tile::launch_tile<tile::Bf16Q, Unit, kD, kDB, 2, 8>(s, st);
-  return tile::launch_tile<tile::Bf16Q, Unit, kD, kDB, 1, 4>(s, st);
+  if constexpr (kDB == 5) if (wgs <= 512) return tile::launch_tile<tile::Bf16Q, Unit, kD, kDB, 2, 8, 1>(s, st);
+  return tile::launch_tile<tile::Bf16Q, Unit, kD, kDB, 1, 4, 1>(s, st);
 }
 // 32-wide steps of the head dimension in the scores, 16-wide blocks of it in the output
 template <class Unit>

@@ -13,8 +13,8 @@
 //     to its 24 bits, so P.V is three exact products instead of one (of finite V: a part that is 0 times
 //     infinity is NaN).  fp32 Q (engine F32Q): v_mfma_f32_16x16x4_f32.
 //   * Per-key factors: FP8 scales of K multiply the fp32 scores, those of V multiply P.
-//   * 64-key tiles come to LDS while the one before is computed on: bf16 ones of d <= 128 directly unless the work-groups are
-//     few, the others through registers (see Plan).  Pitches are odd multiples of 16 bytes (K) and of 32 bytes (V of Bf16Q, read transposed), or
+//   * 64-key tiles come to LDS while the one before is computed on: bf16 ones of d <= 128 directly (work-groups being few: by
+//     width and mask, see attn_generic.hip), the others through registers (see Plan).  Pitches are odd multiples of 16 bytes (K) and of 32 bytes (V of Bf16Q, read transposed), or
 //     d + 4 words (F32Q): no bank conflicts in the operand reads.
 //   * kKW waves share the 16 queries and take 64 / kKW keys of every tile each, their partial results
 //     being combined through LDS at the end of a chunk: for calls with few query blocks, and to have eight waves on 64 queries.
@@ -631,13 +631,13 @@ usp_status launch_tile_one(const AttnStep& s, hipStream_t st) {
   USP_CHECK_HIP(hipGetLastError());
   return USP_OK;
 }
-// kKW, kW: waves that share queries, and waves of a work-group where the tiles go directly to LDS (otherwise four, each its own queries)
-template <template <int, int, int> class Engine, class Unit, int kD, int kDB, int kKW, int kW>
+// kKW, kW: waves that share queries, and waves of a work-group where the tiles go directly to LDS (otherwise four, with kKWR)
+template <template <int, int, int> class Engine, class Unit, int kD, int kDB, int kKW, int kW, int kKWR>
 usp_status launch_tile(const AttnStep& s, hipStream_t st) {
   if constexpr (Directly<Unit>::value && Plan<Engine<kD, kDB, 4 / kKW>, kD, kKW, kW>::dma) {
     if (s.ks[2] * (int64_t)sizeof(typename Unit::elt) * kTile < (int64_t)kNowhere) return launch_tile_one<Engine, Unit, kD, kDB, kKW, kW, true>(s, st);
   }
-  return launch_tile_one<Engine, Unit, kD, kDB, 1, 4, false>(s, st);
+  return launch_tile_one<Engine, Unit, kD, kDB, kKWR, 4, false>(s, st);
 }
 
 }  // namespace tile

@@ -164,6 +164,23 @@ def test_bf16_tiles_of_every_width(d, H, Sq):
     assert np.count_nonzero(bf16_ulps(host_bits_bf16(o), ro)) <= max(1, BF16_MOVED * ro.size)
 
 
+@pytest.mark.parametrize("d,H,Sq", [(40, 3, 65), (56, 3, 65), (56, 60, 200), (72, 3, 65), (96, 3, 65), (96, 64, 128), (96, 43, 192), (112, 3, 65), (112, 60, 200)])
+@pytest.mark.parametrize("masked", [None, (60, 120)])
+def test_few_work_groups_through_registers_and_directly(d, H, Sq, masked):
+    """Both ways a tile of few work-groups can come, at each width that has a rule, on both sides of d = 96's 128 work-groups."""
+    import paper_2602_10940_amd as P
+    wl = W.Workload("few", 500 + d, 1, H, d, Sq, (65, 0, 127), "bf16", **({"masked_keys": masked} if masked else {}))
+    inp = W.make_attention_inputs(wl)
+    km = None if masked is None else [torch.from_numpy(m).to(DEV) for m in inp.key_mask]
+    o, l = P.usp_ring_attn_fwd(dev_bf16(inp.q), [dev_bf16(k) for k in inp.k], [dev_bf16(v) for v in inp.v], key_mask=km,
+                               softmax_scale=float(inp.softmax_scale))
+    torch.cuda.synchronize()
+    ro, rl = orc.ring_attention(inp.q, inp.k, inp.v, float(inp.softmax_scale), inp.key_mask if masked else None)
+    mx, rel = attn_errors(host_f64(o), ro)
+    assert mx <= (2e-5 + 2.0 ** -8) * max(1.0, float(np.max(np.abs(ro)))) and rel <= 5e-6 + 2.0 ** -8 and np.max(np.abs(host_f64(l) - rl)) <= 2e-5, (mx, rel)
+    assert np.count_nonzero(bf16_ulps(host_bits_bf16(o), ro)) <= max(1, BF16_MOVED * ro.size)
+
+
 @pytest.mark.parametrize("d,H,Sq", [(72, 3, 40), (72, 60, 300), (160, 3, 40)])
 @pytest.mark.parametrize("size", [12, 60, 100])
 def test_fp8_values_with_scales_far_from_one(size, d, H, Sq):
