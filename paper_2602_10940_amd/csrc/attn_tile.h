@@ -28,7 +28,7 @@
 // bf16, a call among others: 29.0 us (32.5 with tiles through registers and four waves; one wave per query row
 // with scalar products, the first form, 857); 22 heads of 700 queries and keys 17.8 -> 15.8.
 // (The exponentials against the old reference first, the maximum only where their sum does not show that none exceeds it, and
-// the remainders of the split of P as dot products with -1 were no gain: one work-group on a CU waits for the longer chain
+// the remainders of the split of P as dot products with -1 were no gain up to d = 128: one work-group on a CU waits for the longer chain
 // of every tile.  16 heads of 1024, FP8, d = 40 29.0 us against 25.5, d = 72 34.2 against 30.7, d = 96 31.5 against 32.7; bf16,
 // d = 40 20.4 against 19.7, d = 56 22.5 against 21.6, 24 heads 26.3 against 25.2.)  fp32 is bound by the fp32 matrix
 // rate from about 256 work-groups on (d = 64, 32 heads: 80 us, 107 TFLOP/s).  Two chunks of 128 keys, H=2 Sq=128 d=64
@@ -113,7 +113,28 @@ struct UnitF32 {
   __device__ __forceinline__ void as_f32(f32x4& x, f32x4& y) const { x = a; y = b; }
 };
 
-// p0, p1 as three bf16 pairs whose sums are p0 and p1 exactly (8 + 8 + 8 significant bits)
+// p0, p1 as three bf16 pairs whose sums are p0 and p1 exactly (8 + 8 + 8 significant bits).  split3_dot: what is left of a value
+// after its leading bf16 is one v_dot2_f32_bf16 with (-1, 0) or (0, -1), the same bits (compared for every fp32 value in the
+// diagnostics), instead of a shift and a subtraction: two instructions less a value, a longer chain.  For d above 128, where the
+// wave has the most MFMAs to hide it behind (9 heads of 1220 queries, 608 keys, d = 160 20.4 us with dots, 21.0 without; FP8, 4
+// heads of 512 queries, 700 keys 20.1, 20.6; d = 256 within 1.5 %); narrower heads lose by it (see above).  The
+// constants are kept in registers: the inline constant -1.0 that the compiler puts for (-1, 0) is not that pair.
+struct Minus { uint32_t lo, hi; };
+__device__ __forceinline__ Minus minus_one() {
+  Minus m = {0x0000bf80u, 0xbf800000u};
+  asm volatile("" : "+s"(m.lo), "+s"(m.hi));
+  return m;
+}
+__device__ __forceinline__ void split3_dot(Minus one, float p0, float p1, uint32_t& hi, uint32_t& mid, uint32_t& lo) {
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  auto rest = [](uint32_t pair, uint32_t c, float p) {
+    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pair), __builtin_bit_cast(bf16x2, c), p, false);
+  };
+  hi = pack_bf16x2(p0, p1);
+  const float a0 = rest(hi, one.lo, p0), a1 = rest(hi, one.hi, p1);
+  mid = pack_bf16x2(a0, a1);
+  lo = pack_bf16x2(rest(mid, one.lo, a0), rest(mid, one.hi, a1));
+}
 __device__ __forceinline__ void split3(float p0, float p1, uint32_t& hi, uint32_t& mid, uint32_t& lo) {
   hi = pack_bf16x2(p0, p1);
   const float a0 = p0 - __uint_as_float(hi << 16), a1 = p1 - __uint_as_float(hi & 0xffff0000u);
@@ -165,6 +186,9 @@ struct Bf16Q {
   }
   // O^T += V^T P^T
   __device__ __forceinline__ void pv(const unsigned char* v, int r, int g, const float (&p)[kMB][4], f32x4 (&o)[kDB]) const {
+    constexpr bool kDot = kD > 128;
+    Minus one = {};
+    if constexpr (kDot) one = minus_one();
     constexpr int kGrp = 4;   // head-dim blocks whose MFMAs alternate, so that none waits for its predecessor
 #pragma unroll
     for (int kk = 0; kk < kMB / 2; ++kk) {
@@ -174,7 +198,8 @@ struct Bf16Q {
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
           uint32_t hi, mid, lo;
-          split3(p[2 * kk + a][2 * j], p[2 * kk + a][2 * j + 1], hi, mid, lo);
+          if constexpr (kDot) split3_dot(one, p[2 * kk + a][2 * j], p[2 * kk + a][2 * j + 1], hi, mid, lo);
+          else split3(p[2 * kk + a][2 * j], p[2 * kk + a][2 * j + 1], hi, mid, lo);
           part[0][2 * a + j] = hi; part[1][2 * a + j] = mid; part[2][2 * a + j] = lo;
         }
 #pragma unroll
@@ -405,9 +430,7 @@ void attn_tile_kernel(AttnStep s) {
   f32x4 oc[kDB];
   float lse_c = -INFINITY;
   bool carried = s.mode >= 2;
-  // (bf16 with d above 128 has no register for the row's address across the tiles and forms it again at the end)
-  constexpr bool kFewRegisters = std::is_same<QT, bf16_t>::value && kD > 128;
-  int64_t row = ((int64_t)b * s.H + h) * s.Sq + qc;
+  const int64_t row = ((int64_t)b * s.H + h) * s.Sq + qc;
   float* accp = s.acc ? s.acc + row * d : nullptr;
   if (carried && part == 0) {
     lse_c = s.lse[row];
@@ -602,10 +625,6 @@ void attn_tile_kernel(AttnStep s) {
   }
 
   if (part != 0 || qi >= s.Sq) return;
-  if (kFewRegisters) {                                          // (qi is qc here)
-    row = ((int64_t)b * s.H + h) * s.Sq + qi;
-    accp = s.acc + row * d;
-  }
   QT* outp = (QT*)s.out + b * s.os[0] + h * s.os[1] + (int64_t)qi * s.os[2];
 #pragma unroll
   for (int db = 0; db < kDB; ++db) {

@@ -34,6 +34,14 @@ usp_status usp_diag_mfma_rate(int32_t wgs, int32_t iters, int32_t random_data, i
  * counts: device, 4 x uint64, zeroed by the caller.  Asynchronous on stream. */
 usp_status usp_diag_check_bf16_division(uint64_t* counts, void* stream);
 
+/* The general attention kernel (bf16 Q, d above 128) splits a weight, with FP8 K/V times its key's V scale, into three bf16 parts.
+ * This takes every fp32 value that rounds to a finite bf16, both signs, in both places of a pair, and counts:
+ *   counts[0] pairs, counts[1] values one of whose parts differs from rounding and subtracting (must be 0),
+ *   counts[2] values of at least 2^-109 whose parts do not add up to them exactly (must be 0; below, the third
+ *   part can be less than the smallest bf16).
+ * counts: device, 3 x uint64, zeroed by the caller.  Asynchronous on stream. */
+usp_status usp_diag_check_split3(uint64_t* counts, void* stream);
+
 /* What a pack launch over a [rows, 3072] bf16 payload costs before any arithmetic, on the pack's own
  * grid (one wave per row): kind 0 = nothing at all (x, q, scales may be NULL), 1 = read every row
  * (its |x| maximum goes to scales[row]), 2 = write rows * 3072 bytes to q.  x: rows * 3072 bf16. */

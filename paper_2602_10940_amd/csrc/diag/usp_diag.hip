@@ -5,12 +5,15 @@
 //     against (the clock the chip holds under a full matrix-core load depends on the operand data).
 //   * usp_diag_check_bf16_division: the short division sequence of the bf16 pack against the IEEE division,
 //     over every (row absmax, element) pair of bf16 values.
+//   * usp_diag_check_split3: the three bf16 parts of a weight, with the dot-product remainder of the general
+//     attention kernel, against subtractions, over every fp32 value.
 //   * usp_diag_payload_floor: an empty launch, a read-only and a write-only pass over a pack payload, which
 //     show what bounds a single pack / unpack launch.
 //   * usp_diag_ring_attn_fwd_wait: usp_ring_attn_fwd with the knobs of the bounded arrival wait of the
 //     one-launch ring, so that a test can drive its give-up path from the host.
 #include "usp_common.h"
 #include "fp8_arith.h"
+#include "attn_tile.h"
 #include "usp_diag.h"
 
 namespace usp {
@@ -107,6 +110,38 @@ __global__ __launch_bounds__(256) void check_bf16_division_kernel(unsigned long 
   atomicAdd(&counts[0], n); atomicAdd(&counts[1], bad_code); atomicAdd(&counts[2], bad_quot);
 }
 
+// Every fp32 value p that rounds to a finite bf16, both signs, in either place of a pair whose other place holds another
+// such value: the parts of tile::split3_dot against rounding and subtracting.  counts: [0] pairs, [1] parts that differ (0 and -0
+// do not), [2] of the values from 2^-109 on, those whose parts do not add up to them.
+__global__ __launch_bounds__(256) void check_split3_kernel(unsigned long long* counts) {
+  constexpr uint32_t kEnd = 0x7f7f8000u;            // (from here on RNE gives infinity)
+  const tile::Minus one = tile::minus_one();
+  auto part = [](uint32_t w, int at) { return __uint_as_float(at ? w & 0xffff0000u : w << 16); };
+  unsigned long long n = 0, differ = 0, off = 0;
+  for (uint32_t u = blockIdx.x * 256 + threadIdx.x; u < kEnd; u += gridDim.x * 256) {
+    const uint32_t v = (u * 2654435761u + 12345u) % kEnd;
+    for (int form = 0; form < 4; ++form) {          // place of p, sign of p (of the other value: the other place's)
+      const int at = form & 1;
+      const float p = __uint_as_float(u | (form & 2 ? 0x80000000u : 0u)), other = __uint_as_float(v | (form & 1 ? 0x80000000u : 0u));
+      uint32_t w[3];
+      tile::split3_dot(one, at ? other : p, at ? p : other, w[0], w[1], w[2]);
+      float left = p;
+      double sum = 0.0;
+      bool bad = false;
+      for (int i = 0; i < 3; ++i) {
+        const float want = bf16_to_f32(f32_to_bf16(left)), got = part(w[i], at);
+        bad |= !(got == want);
+        sum += (double)got;
+        left -= want;
+      }
+      ++n;
+      differ += bad ? 1 : 0;
+      off += u >= 0x09000000u && sum != (double)p ? 1 : 0;   // 0x09000000: 2^-109
+    }
+  }
+  atomicAdd(&counts[0], n); atomicAdd(&counts[1], differ); atomicAdd(&counts[2], off);
+}
+
 // What a pack launch over a [rows, 3072] bf16 payload costs before any arithmetic: the same grid
 // (one wave per row, 4 rows per block) doing nothing, only reading the rows (their |x| maximum goes to
 // scales), or only writing codes.
@@ -164,6 +199,14 @@ usp_status usp_diag_check_bf16_division(uint64_t* counts, void* stream) {
   USP_CHECK_ARG(counts != nullptr, "counts is NULL");
   hipLaunchKernelGGL(check_bf16_division_kernel, dim3(0x7f7f), dim3(256), 0, (hipStream_t)stream,
                      reinterpret_cast<unsigned long long*>(counts));
+  USP_CHECK_HIP(hipGetLastError());
+  return USP_OK;
+}
+
+usp_status usp_diag_check_split3(uint64_t* counts, void* stream) {
+  clear_error();
+  USP_CHECK_ARG(counts != nullptr, "counts is NULL");
+  hipLaunchKernelGGL(check_split3_kernel, dim3(8192), dim3(256), 0, (hipStream_t)stream, reinterpret_cast<unsigned long long*>(counts));
   USP_CHECK_HIP(hipGetLastError());
   return USP_OK;
 }

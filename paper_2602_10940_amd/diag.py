@@ -27,6 +27,8 @@ def load_diag_library() -> ctypes.CDLL:
     lib.usp_diag_mfma_rate.argtypes = [i32, i32, i32, i32, vp, vp, vp]
     lib.usp_diag_check_bf16_division.restype = i32
     lib.usp_diag_check_bf16_division.argtypes = [vp, vp]
+    lib.usp_diag_check_split3.restype = i32
+    lib.usp_diag_check_split3.argtypes = [vp, vp]
     lib.usp_diag_payload_floor.restype = i32
     lib.usp_diag_payload_floor.argtypes = [i32, i32, vp, vp, vp, vp]
     lib.usp_diag_repeat_payload_calls.restype = i32
@@ -59,6 +61,14 @@ def usp_diag_check_bf16_division(stream=None):
     lib = load_diag_library()
     counts = torch.zeros((4,), dtype=torch.int64, device="cuda")
     B._check(lib.usp_diag_check_bf16_division(B._ptr(counts), B._stream_handle(stream)))
+    return tuple(int(v) for v in counts.cpu())
+
+
+def usp_diag_check_split3(stream=None):
+    """(pairs checked, values with a part that differs, values of at least 2^-109 whose parts do not add up)."""
+    lib = load_diag_library()
+    counts = torch.zeros((3,), dtype=torch.int64, device="cuda")
+    B._check(lib.usp_diag_check_split3(B._ptr(counts), B._stream_handle(stream)))
     return tuple(int(v) for v in counts.cpu())
 
 

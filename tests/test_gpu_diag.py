@@ -46,6 +46,15 @@ def test_probe_rejects_bad_arguments():
         P.usp_diag_mfma_rate(1, 0, True, out, clocks)
 
 
+def test_three_bf16_parts_of_every_fp32_value():
+    """The weights of the general attention kernel: parts by dot product against parts by subtraction (the arithmetic of the
+    definition), and their sum against the value."""
+    from paper_2602_10940_amd import diag
+    pairs, differ, off = diag.usp_diag_check_split3()
+    assert pairs == 4 * 0x7f7f8000
+    assert differ == 0 and off == 0, (differ, off)
+
+
 def test_short_bf16_division_gives_the_codes_of_the_ieee_division_for_every_pair():
     """Algorithm 1 line 2 with bf16 inputs: the pack's short sequence against the true division, over
     every (row absmax a, element x) pair of bf16 values with |x| <= a (both signs, packed in both byte
