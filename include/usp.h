@@ -45,15 +45,14 @@ typedef enum {
 } usp_dtype;
 
 /* usp_attn_desc.flags */
-#define USP_ATTN_DOUBLE_BUFFER 1u /* stage chunks 1..W-1 through two internal buffers on copy_stream (ragged bf16
-                                     chunks of less than 320 keys on average: all of them, each into a buffer of its
-                                     own, in front of the one launch that the plain call is) */
+#define USP_ATTN_DOUBLE_BUFFER 1u /* stage chunks 1..W-1 through two internal buffers on copy_stream */
 #define USP_ATTN_UNFUSED_MERGE 2u /* per-chunk (O_i, lse_i) then usp_lse_merge, as Algorithm 2 is written;
                                      default folds the merge into the attention kernel's epilogue */
 #define USP_ATTN_FUSED_PREFETCH 16u /* Algorithm 2 without a second stream: the transfers are done by extra
                                       work-groups of the attention launches on compute_stream;
                                       copy_stream is ignored.  Excludes USP_ATTN_DOUBLE_BUFFER.  Two forms:
-                                      - one launch per chunk (always with USP_ATTN_STEPWISE): step
+                                      - one launch per chunk (always with USP_ATTN_STEPWISE or chunk lengths
+                                        that are no multiples of 64 and, bf16, below 320 on average): step
                                         r's launch carries the transfer of chunk r+1 into the idle one
                                         of two internal buffers, in work-groups that occupy the CUs the
                                         attention grid leaves free.  Same buffers and results as
@@ -78,7 +77,8 @@ typedef enum {
 #define USP_ATTN_STEPWISE 64u     /* one attention launch per chunk even where one launch could cover the
                                      whole ring: without USP_ATTN_DOUBLE_BUFFER and USP_ATTN_UNFUSED_MERGE,
                                      bf16 or FP8 chunks (bf16 Q, d = 128 or 64), with or without key masks
-                                     (2 to 16 of them non-empty) are otherwise taken as one stream of key tiles by a
+                                     (bf16: of lengths that are multiples of 64 or average 320 and more; 2 to 16
+                                     of them non-empty) are otherwise taken as one stream of key tiles by a
                                      single launch (when the Q shard's 256-query blocks fit one round of
                                      work-groups on the chip, or the chunks are short, or the
                                      transfers are asked to ride inside the launch), the running

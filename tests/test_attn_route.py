@@ -113,9 +113,13 @@ def test_fp8_rings_above_one_round_go_by_keys_per_chunk(B, H, d, Sq, lens, one):
         assert not _route(B, H, d, Sq, lens, fp8=True, flags=form).one_launch
 
 
-@pytest.mark.parametrize("lens", [(38, 38), (219, 1, 0, 63, 65), (33,) * 16, (288,) * 4])
+@pytest.mark.parametrize("lens", [(38, 38), (219, 1, 0, 63, 65), (33,) * 16, (288,) * 4, (300, 318)])
 @pytest.mark.parametrize("H,Sq", [(2, 75), (40, 1800)])
-def test_short_ragged_rings_run_the_plain_calls_launch_in_the_side_stream_mode(lens, H, Sq):
-    plain = _route(1, H, 128, Sq, lens)
-    assert plain.one_launch and _route(1, H, 128, Sq, lens, flags=b.USP_ATTN_DOUBLE_BUFFER) == plain
-    assert not _route(1, H, 128, Sq, (384, 385), flags=b.USP_ATTN_DOUBLE_BUFFER).one_launch
+@pytest.mark.parametrize("flags", [0, b.USP_ATTN_FUSED_PREFETCH, b.USP_ATTN_DOUBLE_BUFFER])
+def test_short_ragged_bf16_rings_are_a_launch_per_chunk(lens, H, Sq, flags):
+    for d in (64, 128):
+        assert not _route(1, H, d, Sq, lens, flags=flags).one_launch
+        assert b.usp_ring_attn_workspace_bytes(_desc(1, H, d, Sq, lens, flags=flags)) == \
+            b.usp_ring_attn_workspace_bytes(_desc(1, H, d, Sq, lens, flags=flags | b.USP_ATTN_STEPWISE))
+    if flags != b.USP_ATTN_DOUBLE_BUFFER:
+        assert _route(1, 2, 128, 75, (320, 321), flags=flags).one_launch and _route(1, 2, 128, 75, (64, 64), flags=flags).one_launch

@@ -738,36 +738,30 @@ def test_a_workspace_that_cannot_be_allocated_is_torchs_out_of_memory_error():
     assert torch.isfinite(lse).all()
 
 
-@pytest.mark.parametrize("H,d,Sq,lens,masked", [
-    (2, 128, 75, (38, 38), (0, 0)),                        # the smallest: a part of a tile each
-    (3, 128, 219, (219, 1, 0, 63, 65), (5, 230)),          # chunks of one key, an empty one; the first almost all dead
-    (2, 64, 130, (33,) * 16, (0, 0)),                      # the most chunks one launch takes
-    (1, 64, 1, (300, 318), (300, 618)),                    # a chunk without a live key; the longest such ring
-    (129, 128, 257, (70, 70, 70), (0, 0)),                 # more than one round of query blocks
+@pytest.mark.parametrize("B,H,d,Sq,lens,masked", [
+    (1, 2, 128, 75, (38, 38), (0, 0)),                        # the smallest: a part of a tile each
+    (1, 3, 128, 219, (219, 1, 0, 63, 65), (5, 230)),          # chunks of one key, an empty one; the first almost all dead
+    (2, 3, 64, 87, (87,) * 7 + (81,), (0, 0)),
+    (1, 1, 64, 130, (33,) * 16, (0, 0)),                      # the most chunks one launch takes
+    (1, 1, 64, 1, (300, 318), (300, 618)),                    # a chunk without a live key; the longest such ring
+    (1, 129, 128, 257, (70, 70, 70), (0, 0)),                 # more than one round of query blocks
 ])
-def test_short_ragged_rings_are_one_launch_in_every_transfer_mode(H, d, Sq, lens, masked):
-    """The plain call, the side-stream schedule (all chunks staged in front) and the transfers inside the launch: the same bits; against the
-    oracle; a launch per chunk with the workspace that one needs."""
+def test_short_ragged_rings_are_a_launch_per_chunk_in_every_mode(B, H, d, Sq, lens, masked):
+    """One weight per query and launch, the one at the reference, escapes its rounding to bf16: rings of short chunks taken as
+    one launch are 5 to 20 % further off.  So the plain call, both transfer modes and STEPWISE have the same bits, with
+    the workspace of any of them."""
     P = _P()
-    inp = W.make_attention_inputs(W.Workload("brief", 40 + Sq, 1, H, d, Sq, lens, "bf16", masked_keys=masked))
+    inp = W.make_attention_inputs(W.Workload("brief", 40 + Sq, B, H, d, Sq, lens, "bf16", masked_keys=masked))
     ro, rl = _oracle(inp)
-    o, l = _run(inp)
+    o, l = _run(inp, flags=64)
     _assert_parity(o, l, ro, rl)
-    for flags, side in ((1, torch.cuda.Stream()), (16, None)):
+    for flags, side in ((0, None), (1, torch.cuda.Stream()), (16, None), (16 | 64, None)):
         om, lm = _run(inp, flags=flags, copy_stream=side)
         np.testing.assert_array_equal(om, o)
         np.testing.assert_array_equal(lm, l)
-    q = dev_bf16(inp.q); ks = [dev_bf16(k) for k in inp.k]; vs = [dev_bf16(v) for v in inp.v]
-    out = torch.empty_like(q)
-    km = None if inp.key_mask is None else [torch.from_numpy(m).to(DEV) for m in inp.key_mask]
-    less = P.usp_ring_attn_workspace_bytes(P.make_attn_desc(q, ks, out, flags=64))
-    o64, l64 = _run(inp, flags=64)
-    P.usp_ring_attn_fwd(q, ks, vs, softmax_scale=float(inp.softmax_scale), key_mask=km, out=out,
-                        workspace=torch.empty(less, dtype=torch.uint8, device=DEV))
-    torch.cuda.synchronize()
-    if less < P.usp_ring_attn_workspace_bytes(P.make_attn_desc(q, ks, out)):
-        np.testing.assert_array_equal(host_f64(out), o64)
-    _assert_parity(o64, l64, ro, rl)
+    q = dev_bf16(inp.q); ks = [dev_bf16(k) for k in inp.k]
+    need = [P.usp_ring_attn_workspace_bytes(P.make_attn_desc(q, ks, torch.empty_like(q), flags=f)) for f in (0, 64, 1, 1 | 64, 16, 16 | 64)]
+    assert need[0::2] == need[1::2]
 
 
 @pytest.mark.parametrize("H,d,Sq,keys,masked,split", [
