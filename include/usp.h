@@ -80,7 +80,7 @@ typedef enum {
                                      (bf16: of lengths that are multiples of 64 or average 320 and more; 2 to 16
                                      of them non-empty) are otherwise taken as one stream of key tiles by a
                                      single launch (when the Q shard's 256-query blocks fit one round of
-                                     work-groups on the chip, or the chunks are short, or the
+                                     work-groups on the chip, or the chunks are bf16 and short, or the
                                      transfers are asked to ride inside the launch), the running
                                      softmax state staying in registers from the first chunk to the last
                                      (no carried state in the workspace); FP8 chunks are decoded by

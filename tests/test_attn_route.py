@@ -100,17 +100,14 @@ def test_the_mixed_form_is_ignored_where_it_always_was():
     assert _route(1, 6, 64, 300, (513, 640), flags=b.USP_ATTN_KERNEL_MIXED).one_launch      # (d = 64 has no such form)
 
 
-# B, H, d, Sq, chunks: FP8 rings above one round of 256-query blocks, all chunks at hand
-@pytest.mark.parametrize("B,H,d,Sq,lens,one", [
-    (1, 64, 128, 1025, (2048, 2048), True), (1, 64, 128, 1025, (2048, 2049), False),
-    (2, 129, 128, 20, (2048, 2048), False),               # 541 MB of decoded chunks
-    (1, 64, 64, 1025, (2048, 0, 2048), True), (1, 64, 64, 1025, (1408, 1407), True), (1, 64, 64, 1025, (1408, 1409), False),
-    (1, 24, 128, 4096, (4096, 4096), False)])
-def test_fp8_rings_above_one_round_go_by_keys_per_chunk(B, H, d, Sq, lens, one):
-    assert _route(B, H, d, Sq, lens, fp8=True).one_launch == one
+@pytest.mark.parametrize("B,H,d,Sq,lens", [(1, 64, 128, 1025, (64, 64)), (1, 64, 128, 1025, (2048, 2048)), (2, 129, 128, 20, (65, 1, 0, 130)),
+                                           (1, 64, 64, 1025, (1408, 1407)), (1, 64, 64, 1025, (256,) * 8), (1, 24, 128, 4096, (4096, 4096))])
+def test_fp8_rings_at_hand_above_one_round_of_query_blocks_are_a_launch_per_chunk(B, H, d, Sq, lens):
+    assert not _route(B, H, d, Sq, lens, fp8=True).one_launch
+    assert b.usp_ring_attn_workspace_bytes(_desc(B, H, d, Sq, lens, True)) == \
+        b.usp_ring_attn_workspace_bytes(_desc(B, H, d, Sq, lens, True, b.USP_ATTN_STEPWISE))
     assert _route(B, H, d, Sq, lens, fp8=True, flags=b.USP_ATTN_FUSED_PREFETCH).one_launch
-    for form in (b.USP_ATTN_KERNEL_WIDE, b.USP_ATTN_KERNEL_SPLIT, b.USP_ATTN_KERNEL_MIXED):
-        assert not _route(B, H, d, Sq, lens, fp8=True, flags=form).one_launch
+    assert _route(1, 2, d, 75, lens, fp8=True).one_launch                                # within one round
 
 
 @pytest.mark.parametrize("lens", [(38, 38), (219, 1, 0, 63, 65), (33,) * 16, (288,) * 4, (300, 318)])

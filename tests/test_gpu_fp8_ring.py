@@ -394,8 +394,8 @@ def test_fp8_step_preparation_one_launch_and_three_agree():
     (2, 129, 64, 1, (64, 64, 128, 64), (0, 64)),          # whole tiles, the first chunk all dead
 ])
 def test_fp8_rings_above_one_round_of_query_blocks(B, H, d, Sq, lens, masked):
-    """One launch; a launch per chunk on request, and with the workspace that one needs."""
-    P = _P()
+    """A launch per chunk with all chunks at hand: of the weights only those at the reference, one per query and launch, escape
+    their rounding to bf16, and one launch over short chunks is up to 1.14 times as far off.  One launch with the transfers inside."""
     wl = W.Workload("fp8_rounds", 300 + d, B, H, d, Sq, lens, "bf16", outlier_frac=0.01, outlier_mul=20.0, masked_keys=masked)
     inp, q, kq, ksc, vq, vsc, kx, vx = _fp8_ring(wl)
     scale = float(inp.softmax_scale)
@@ -404,10 +404,6 @@ def test_fp8_rings_above_one_round_of_query_blocks(B, H, d, Sq, lens, masked):
     so, sl = _call(q, kq, ksc, vq, vsc, scale, STEPWISE, **kw)
     _assert_parity(host_f64(so), host_f64(sl), ro, rl)
     o, l = _call(q, kq, ksc, vq, vsc, scale, 0, **kw)
-    _assert_parity(host_f64(o), host_f64(l), ro, rl)
+    assert torch.equal(o, so) and torch.equal(l, sl)
     fo, fl = _call(q, kq, ksc, vq, vsc, scale, FUSED, **kw)
-    assert torch.equal(o, fo) and torch.equal(l, fl)      # the same launch
-    less = P.usp_ring_attn_workspace_bytes(P.make_attn_desc(q, kq, o, flags=STEPWISE))
-    assert less < P.usp_ring_attn_workspace_bytes(P.make_attn_desc(q, kq, o))
-    so2, sl2 = _call(q, kq, ksc, vq, vsc, scale, 0, workspace=torch.empty(less, dtype=torch.uint8, device=DEV), **kw)
-    assert torch.equal(so, so2) and torch.equal(sl, sl2)
+    _assert_parity(host_f64(fo), host_f64(fl), ro, rl)
