@@ -120,8 +120,8 @@ typedef struct usp_attn_desc {
 
 /*
  * Bytes of device workspace usp_ring_attn_fwd needs for this descriptor
- * (0 is possible, e.g. one f32 chunk; bf16 with d = 128 or 64 always asks for a little, 1 KB per
- * 64 keys of a head, and more where few queries meet many keys).  Returns (size_t)-1 if the descriptor is invalid.
+ * (0 is possible, e.g. one f32 chunk under many queries; bf16 with d = 128 or 64 always asks for a little, 1 KB per
+ * 64 keys of a head, and more, as any other type and d over one chunk, where few queries meet many keys).  Returns (size_t)-1 if the descriptor is invalid.
  */
 size_t usp_ring_attn_workspace_bytes(const usp_attn_desc* desc);
 
@@ -178,12 +178,14 @@ usp_status usp_ring_attn_fwd(const usp_attn_desc* desc, const void* q,
  *   - Where usp_ring_attn_workspace_bytes() is at most USP_NOALLOC_SCRATCH_BYTES: the same kernels in
  *     the same order, bit-identical outputs.  A descriptor that asks for more, but whose ragged chunks
  *     taken by a launch each and keys not shared between work-groups would fit, runs that way: the same
- *     result up to rounding order, as usp_ring_attn_fwd gives with that much workspace.
+ *     result up to rounding order, as usp_ring_attn_fwd gives with that much workspace.  One chunk outside the bf16
+ *     d = 64 and 128 kernels needs no workspace and is run without the array: the bits of usp_ring_attn_fwd
+ *     with workspace NULL; such calls may overlap.
  *   - Any other is refused with USP_ERR_WORKSPACE and nothing is enqueued (e.g. the FLUX-1024 ring shard
  *     needs 17 MB, the Qwen-Image-like FP8 shard 0.5 GB: the latter has to bring its own workspace).
  *   - USP_ATTN_DOUBLE_BUFFER (side stream and events) is refused with USP_ERR_UNSUPPORTED; the
  *     transfers inside the launches (USP_ATTN_FUSED_PREFETCH) are available.
- *   - Every call on one GPU uses that GPU's one array: calls that overlap in time on one GPU (two
+ *   - Every other call on one GPU uses that GPU's one array: calls that overlap in time on one GPU (two
  *     streams, two host threads) race and give undefined results; calls ordered on one stream are
  *     safe.  Nothing is carried from call to call: whatever a call needs to start at zero it clears
  *     itself, on compute_stream.

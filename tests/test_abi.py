@@ -159,6 +159,24 @@ def test_noalloc_entry_point_limits_without_gpu():
     assert lib.usp_ring_attn_fwd_noalloc(ctypes.byref(d), None, None, None, None, None, None, None, None, None) == b.USP_ERR_UNSUPPORTED
 
 
+def test_noalloc_calls_of_one_chunk_on_the_general_kernel_leave_the_scratch_alone():
+    """They need no workspace, so they may overlap on one GPU and be the first call under a graph capture.  The address of the array
+    is looked up (a HIP error without a GPU) before the pointers are looked at, and only where the array is used."""
+    from paper_2602_10940_amd import binding as b
+    lib = b.load_library()
+    lens = (ctypes.c_int32 * 1)(2000)
+    for dt, kv, d, Sq in ((b.USP_F32, b.USP_F32, 128, 100), (b.USP_F32, b.USP_FP8_E4M3FN, 64, 1), (b.USP_BF16, b.USP_BF16, 72, 64),
+                          (b.USP_BF16, b.USP_FP8_E4M3FN, 160, 64), (b.USP_F32, b.USP_F32, 128, 9000)):
+        x = b.AttnDesc()
+        x.B, x.H, x.d, x.Sq, x.n_chunks, x.qo_dtype, x.kv_dtype = 1, 2, d, Sq, 1, dt, kv
+        x.chunk_len = ctypes.cast(lens, ctypes.POINTER(ctypes.c_int32))
+        for i, s in enumerate((2 * Sq * d, Sq * d, d)):
+            x.q_stride[i] = x.o_stride[i] = s
+        assert (b.usp_ring_attn_workspace_bytes(x) > 0) == (Sq < 9000)     # (keys shared where there is room)
+        assert lib.usp_ring_attn_fwd_noalloc(ctypes.byref(x), *[None] * 9) == b.USP_ERR_INVALID_ARG
+        assert b"NULL" in lib.usp_last_error()
+
+
 def test_header_is_plain_c():
     """include/usp.h is the boundary: it must compile as C99 and as C++ with nothing but the standard headers."""
     import shutil

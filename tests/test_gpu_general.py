@@ -221,7 +221,7 @@ SHARED = [
 @pytest.mark.parametrize("dtype,B,H,d,Sq,keys,masked,fp8", SHARED)
 def test_work_groups_that_share_the_keys_of_a_query_block(dtype, B, H, d, Sq, keys, masked, fp8):
     """Against the oracle (bars as above) and against the same call without the workspace, which one work-group per query block
-    serves: with room for the shares, in the library's own room, with too little, and replayed from a graph; inputs and result in [B, S, H, d] storage."""
+    serves: with room for the shares, with too little, through the entry point that uses none, and replayed from a graph; inputs and result in [B, S, H, d] storage."""
     import paper_2602_10940_amd as P
     inp = W.make_attention_inputs(W.Workload("shared", 700 + d, B, H, d, Sq, (keys,), dtype, masked_keys=masked))
     up = dev_f32 if dtype == "f32" else dev_bf16
@@ -242,7 +242,7 @@ def test_work_groups_that_share_the_keys_of_a_query_block(dtype, B, H, d, Sq, ke
     small, small_l = run(workspace=torch.empty(256, dtype=torch.uint8, device=DEV))
     go, gl = torch.empty_like(q), torch.empty((B, H, Sq), dtype=torch.float32, device=DEV)
     P.usp_ring_attn_fwd_noalloc(q, [k], [v], go, gl, **kw)
-    assert torch.equal(go, o) and torch.equal(gl, l)
+    assert torch.equal(go, small) and torch.equal(gl, small_l)
     ws = torch.empty(need, dtype=torch.uint8, device=DEV)
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph):
