@@ -88,7 +88,7 @@ typedef enum {
                                      USP_ATTN_FUSED_PREFETCH, which for them is the same launch.  Same
                                      result up to rounding order. */
 #define USP_ATTN_KERNEL_MIXED 32u /* one launch of both: 256-query work-groups, and the blocks of the
-                                     last, partly filled round as pairs of key-split work-groups
+                                     last, partly filled round, or more of them, as pairs of key-split work-groups
                                      (forced: the second half of all blocks).  d = 128 only, and not in a
                                      launch over a ring: a launch per chunk is taken for this bit where
                                      chunks are ragged, where bf16 ones come with key masks, and, without

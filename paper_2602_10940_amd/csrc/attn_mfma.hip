@@ -1263,8 +1263,8 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(const float* __restri
 }
 
 // Mixed launch: when the 256-query blocks do not fill the last round of work-groups on the 256 CUs
-// (one work-group per CU at a time), the blocks of that round are run as two key-split work-groups
-// of 128 queries each, which take about 0.55 of a wide work-group's time.  Per XCD (ids go round
+// (one work-group per CU at a time), at least the blocks of that round, and up to half of all (attn_mfma_mixed_grid), are run
+// as two key-split work-groups of 128 queries each, which take about 0.55 of a wide work-group's time.  Per XCD (ids go round
 // robin) the contiguous, head-major range of blocks is dispatched wide blocks first, then the
 // halves of its last s.mix_halves blocks.
 template <bool kExt, bool kDead>
@@ -1467,6 +1467,29 @@ RingForm attn_mfma_ring_form(int B, int H, int Sq, int d, int64_t tiles, int chu
   return {take_split, (take_split ? split : wide) < 0.97 * stepwise};
 }
 
+// The mixed launch: taken when the last round of 256-query work-groups would be at most half full, whose blocks are then run as halves.
+// Up to half of all blocks are, as long as the work-groups need no round more: the CUs that begin with halves have
+// gone on to the next ones when the wide work-groups end.  us with the last round's blocks alone, so: 264 blocks, 256 keys 22.7, 21.8; 272, 2048 82.4,
+// 79.0; 336, 2048 84.0, 83.0; FP8, 266, 2048 97.9, 94.4; 78 random shapes of 260 to 1100 blocks, one chunk, 0.96 to 1.00 of the time; 60 rings
+// of two to four chunks, a launch per chunk with carried state, 0.91 to 0.99 (mean 0.957; one of 36 us 1.06, 0.99 when repeated).  From 96 blocks in the last round on there is nothing in it (0.97 to 1.03).
+// Copy work-groups, at the end of the same grid, are left their CUs (kMostCopyWGs) in the last round: in a round of their own they
+// would have nothing to run beside, and the fewer there are, the longer they take.  us a call with the last round's blocks alone, with halves up to the end of the
+// round, so, three chunks from HBM and from pinned host memory: 264 blocks, 640 keys 123.8, 117.0, 115.9 and 495, 488, 487; 520, 128 keys 114.4, 111.5, 109.9
+// and 162.4, 165.5, 159.6; 600, 640 keys 233.6, 238.3, 231.0 and 1347, 1349, 1344; 26 such, merged in the launch or not: 0.90 to 1.01 of the time.
+MixedGrid attn_mfma_mixed_grid(int items, bool forced, bool copies) {
+  const int rem = items % 256, blocks = forced ? (items + 1) / 2 : rem <= 128 ? rem : 0;   // forced: the second half of the blocks
+  if (blocks == 0) return {0, 0, 0};
+  const int per = (items + kXcds - 1) / kXcds;
+  int halves = (blocks + kXcds - 1) / kXcds;
+  if (!forced && rem < 96) {
+    const int rounds = (per + 256 / kXcds - 1) / (256 / kXcds), room = rounds * (256 / kXcds) - per - (copies ? kMostCopyWGs / kXcds : 0);
+    const int more = (per + 1) / 2 < room ? (per + 1) / 2 : room;
+    if (more > halves) halves = more;
+  }
+  const int wgs = kXcds * (per + halves);
+  return {wgs, halves, copies ? copy_wgs_beside(wgs) : 0};
+}
+
 usp_status launch_attn_mfma(const AttnStep& step, hipStream_t st) {
   AttnStep s = step;
   if (s.parts < 1) s.parts = 1;
@@ -1537,28 +1560,15 @@ usp_status launch_attn_mfma(const AttnStep& step, hipStream_t st) {
     set_error("the bf16 matrix-core kernels take V already multiplied by its scales");
     return USP_ERR_INVALID_ARG;
   }
-  // Mixed launch when the last round of 256-query work-groups would be at most half full
+  // (the mixed kernel has no half-head-dimension form, and shares no keys; variant 4 asks for it)
   const int items = (int)((s.Sq + kQPerWG - 1) / kQPerWG) * s.B * s.H;
-  const int rem = items % 256;
-  int mix_blocks = 0;
-  if (s.half_d || s.parts > 1) mix_blocks = 0;                                           // (the mixed kernel has no half-head-dimension form)
-  else if (s.variant == 4) mix_blocks = (items + 1) / 2;                  // forced: the second half of the blocks
-  else if (s.variant == 0 && !split && rem > 0 && rem <= 128) mix_blocks = rem;
-  if (mix_blocks > 0) {
-    s.mix_halves = (mix_blocks + kXcds - 1) / kXcds;
-    const int per = (items + kXcds - 1) / kXcds;
-    // Up to half of all blocks are run as halves, as long as the work-groups need no round more: the CUs that begin with halves have
-    // gone on to the next ones when the wide work-groups end.  us with the last round's blocks alone, so: 264 blocks, 256 keys 22.7, 21.8; 272, 2048 82.4,
-    // 79.0; 336, 2048 84.0, 83.0; FP8, 266, 2048 97.9, 94.4; 78 random shapes of 260 to 1100 blocks 0.96 to 1.00 of the time.  From 96 blocks in
-    // the last round on there is nothing in it (0.97 to 1.03).
-    if (s.variant == 0 && rem < 96) {
-      const int rounds = (per + 256 / kXcds - 1) / (256 / kXcds), room = rounds * (256 / kXcds) - per;
-      const int more = (per + 1) / 2 < room ? (per + 1) / 2 : room;
-      if (more > s.mix_halves) s.mix_halves = more;
-    }
-    const unsigned wgs_mixed = (unsigned)(kXcds * (per + s.mix_halves));
-    s.grid_wgs = (int)wgs_mixed;
-    s.copy_wgs = prefetch_wg_count(s, (int)wgs_mixed);
+  const MixedGrid mixed = s.half_d || s.parts > 1 || !(s.variant == 4 || (s.variant == 0 && !split))
+                              ? MixedGrid{0, 0, 0} : attn_mfma_mixed_grid(items, s.variant == 4, s.n_copy > 0);
+  if (mixed.wgs > 0) {
+    const unsigned wgs_mixed = (unsigned)mixed.wgs;
+    s.mix_halves = mixed.halves;
+    s.grid_wgs = mixed.wgs;
+    s.copy_wgs = mixed.copy_wgs;
     if (ext) return dead ? launch_mixed<true, true>(s, wgs_mixed, st) : launch_mixed<true, false>(s, wgs_mixed, st);
     return dead ? launch_mixed<false, true>(s, wgs_mixed, st) : launch_mixed<false, false>(s, wgs_mixed, st);
   }

@@ -85,6 +85,12 @@ usp_status usp_diag_ring_attn_fwd_wait(const usp_attn_desc* desc, const void* q,
 usp_status usp_diag_attn_route(const usp_attn_desc* desc, int32_t masked, int32_t* one_launch, int32_t* split,
                                int32_t* parts);
 
+/* The mixed launch of 256-query work-groups and key-split halves over `blocks` blocks of 256 queries (d = 128); host only.
+ *   forced, copies : USP_ATTN_KERNEL_MIXED; the launch carries a transfer
+ *   wgs, halves, copy_wgs : receive the attention work-groups (0: no such launch), the blocks of each eighth of them
+ *                    that are run as two, and the copy work-groups behind them */
+usp_status usp_diag_mixed_grid(int32_t blocks, int32_t forced, int32_t copies, int32_t* wgs, int32_t* halves, int32_t* copy_wgs);
+
 #ifdef __cplusplus
 }
 #endif

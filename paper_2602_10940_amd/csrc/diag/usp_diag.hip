@@ -285,4 +285,15 @@ usp_status usp_diag_attn_route(const usp_attn_desc* desc, int32_t masked, int32_
   return USP_OK;
 }
 
+usp_status usp_diag_mixed_grid(int32_t blocks, int32_t forced, int32_t copies, int32_t* wgs, int32_t* halves, int32_t* copy_wgs) {
+  clear_error();
+  USP_CHECK_ARG(wgs && halves && copy_wgs, "an output is NULL");
+  USP_CHECK_ARG(blocks > 0 && blocks <= 1 << 24, "blocks=%d out of range", blocks);
+  const MixedGrid g = attn_mfma_mixed_grid(blocks, forced != 0, copies != 0);
+  *wgs = g.wgs;
+  *halves = g.halves;
+  *copy_wgs = g.copy_wgs;
+  return USP_OK;
+}
+
 }  // extern "C"

@@ -166,9 +166,10 @@ static_assert(offsetof(AttnStep, chunk) + sizeof(AttnStep::Chunk) <= 6 * 64, "on
 // Copy work-groups that go with attn_wgs attention work-groups, one of which fits on a CU: the CUs the
 // attention grid leaves free, as a multiple of 8 in [16, 64] (one work-group copied about 50 GB/s when this was chosen, with
 // one batch of loads in flight; it has two now).
+constexpr int kMostCopyWGs = 64;
 inline int copy_wgs_beside(int attn_wgs) {
   const int n = (256 - attn_wgs % 256) / 8 * 8;
-  return n < 16 ? 16 : (n > 64 ? 64 : n);
+  return n < 16 ? 16 : (n > kMostCopyWGs ? kMostCopyWGs : n);
 }
 // Groups into which the copy work-groups of a launch over a ring fall, each with chunks of its own: a chunk is a
 // chain of load, store, acknowledgement and count that takes 4 to 5 us however short it is, so short chunks travel
@@ -187,6 +188,10 @@ usp_status launch_attn_mfma(const AttnStep& s, hipStream_t st);
 bool attn_mfma_supported(const AttnStep& s);
 // How the matrix-core kernels run a launch that finishes its result: variant as AttnStep::variant, and parts
 struct AttnForm { int variant, parts; };
+// The mixed launch of 256-query work-groups and key-split halves over `items` query blocks: all attention work-groups, the blocks of
+// each XCD that are run as halves, and the copy work-groups behind them if the launch carries a transfer.  wgs = 0: not taken.
+struct MixedGrid { int wgs, halves, copy_wgs; };
+MixedGrid attn_mfma_mixed_grid(int items, bool forced, bool copies);
 // What a launch over a ring moves while it computes: chunks that hold keys, bytes read and written for all
 // but the first of them and for the largest of those, tiles of the last
 struct RingTransfers { int chunks; int64_t bytes, largest, last_tiles; bool fp8; };

@@ -42,6 +42,8 @@ def load_diag_library() -> ctypes.CDLL:
                                                 vp, vp, vp, sz, vp, i32, i32]
     lib.usp_diag_attn_route.restype = i32
     lib.usp_diag_attn_route.argtypes = [ctypes.POINTER(B.AttnDesc), i32] + [ctypes.POINTER(i32)] * 3
+    lib.usp_diag_mixed_grid.restype = i32
+    lib.usp_diag_mixed_grid.argtypes = [i32, i32, i32] + [ctypes.POINTER(i32)] * 3
     _diag = lib
     return lib
 
@@ -109,6 +111,19 @@ def usp_diag_attn_route(desc: B.AttnDesc, masked: bool = False) -> AttnRoute:
     B._check(lib.usp_diag_attn_route(ctypes.byref(desc), 1 if masked else 0, ctypes.byref(one), ctypes.byref(split),
                                      ctypes.byref(parts)))
     return AttnRoute(bool(one.value), bool(split.value), parts.value)
+
+
+class MixedGrid(NamedTuple):
+    wgs: int           # attention work-groups; 0: no mixed launch
+    halves: int        # blocks of each XCD run as two key-split work-groups
+    copy_wgs: int      # behind them
+
+
+def usp_diag_mixed_grid(blocks: int, forced: bool = False, copies: bool = False) -> MixedGrid:
+    lib = load_diag_library()
+    out = [ctypes.c_int32() for _ in range(3)]
+    B._check(lib.usp_diag_mixed_grid(int(blocks), 1 if forced else 0, 1 if copies else 0, *[ctypes.byref(x) for x in out]))
+    return MixedGrid(*[x.value for x in out])
 
 
 def usp_diag_ring_attn_fwd_wait(q: torch.Tensor, k_chunks: Sequence[torch.Tensor], v_chunks: Sequence[torch.Tensor],

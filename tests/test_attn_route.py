@@ -120,3 +120,27 @@ def test_short_ragged_bf16_rings_are_a_launch_per_chunk(lens, H, Sq, flags):
             b.usp_ring_attn_workspace_bytes(_desc(1, H, d, Sq, lens, flags=flags | b.USP_ATTN_STEPWISE))
     if flags != b.USP_ATTN_DOUBLE_BUFFER:
         assert _route(1, 2, 128, 75, (320, 321), flags=flags).one_launch and _route(1, 2, 128, 75, (64, 64), flags=flags).one_launch
+
+
+def test_copy_work_groups_of_a_mixed_launch_find_their_cus_free():
+    for blocks in range(1, 2600):
+        plain, g = diag.usp_diag_mixed_grid(blocks), diag.usp_diag_mixed_grid(blocks, copies=True)
+        rem, per = blocks % 256, -(-blocks // 8)
+        assert (plain.wgs > 0) == (g.wgs > 0) == (0 < rem <= 128)
+        if not g.wgs:
+            continue
+        last = -(-rem // 8)                                        # the last round's blocks alone
+        for x in (plain, g):
+            assert x.wgs == 8 * (per + x.halves) and last <= x.halves <= max(last, (per + 1) // 2)
+            assert x.halves == last or x.wgs <= 256 * -(-8 * per // 256)   # no round more
+        assert plain.copy_wgs == 0 and g.halves <= plain.halves
+        if g.halves > last:
+            assert g.copy_wgs == 64 and g.wgs + g.copy_wgs <= 256 * -(-8 * per // 256)
+        else:
+            assert g.wgs == 8 * (per + last)
+
+
+@pytest.mark.parametrize("blocks,wgs,copies_wgs,copy_wgs", [(264, 400, 400, 64), (343, 512, 448, 64), (520, 768, 704, 64), (384, 512, 512, 64)])
+def test_mixed_launches_by_number(blocks, wgs, copies_wgs, copy_wgs):
+    assert diag.usp_diag_mixed_grid(blocks).wgs == wgs and diag.usp_diag_mixed_grid(blocks, copies=True)[::2] == (copies_wgs, copy_wgs)
+    assert diag.usp_diag_mixed_grid(blocks, forced=True).halves == -(-((blocks + 1) // 2) // 8)

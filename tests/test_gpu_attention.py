@@ -796,3 +796,19 @@ def test_mixed_launch_with_halves_of_earlier_rounds(H, Sq, keys, masked):
     o, l = _run(inp)
     ro, rl = _oracle(inp)
     _assert_parity(o, l, ro, rl)
+
+
+@pytest.mark.parametrize("H,Sq,lens", [(33, 2000, (64, 70, 64)), (49, 1700, (64, 128)), (105, 1100, (100, 0, 64)), (88, 1000, (64, 64))])
+@pytest.mark.parametrize("flags", [16 | 64, 16 | 2])
+def test_mixed_launch_that_carries_a_transfer(H, Sq, lens, flags):
+    """264, 343 and 525 blocks, more of which are run as halves as far as the copy work-groups keep their CUs; 352 (the last round's alone)."""
+    P = _P()
+    inp = W.make_attention_inputs(W.Workload("mixed_pre", 79, 1, H, 128, Sq, lens, "bf16"))
+    q = dev_bf16(inp.q); ks = [dev_bf16(k) for k in inp.k]; vs = [dev_bf16(v) for v in inp.v]
+    out = torch.empty_like(q)
+    ws = torch.full((P.usp_ring_attn_workspace_bytes(P.make_attn_desc(q, ks, out, flags=flags)),), 0xFF, dtype=torch.uint8, device=DEV)
+    ro, rl = _oracle(inp)
+    for _ in range(2):
+        o, l = P.usp_ring_attn_fwd(q, ks, vs, softmax_scale=float(inp.softmax_scale), flags=flags, out=out, workspace=ws)
+        torch.cuda.synchronize()
+        _assert_parity(host_f64(o), host_f64(l), ro, rl)
