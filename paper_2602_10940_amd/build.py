@@ -5,6 +5,7 @@
 from __future__ import annotations
 
 import os
+import shutil
 import subprocess
 import sys
 import sysconfig
@@ -46,6 +47,17 @@ def hipcc() -> str:
     raise RuntimeError("hipcc not found")
 
 
+def hip_include() -> str:
+    """The include directory of the ROCm that hipcc() belongs to (a name without a path is looked up as the shell does),
+    of torch's, or the usual one: the first that holds HIP's headers."""
+    from torch.utils.cpp_extension import ROCM_HOME
+    c = shutil.which(hipcc())
+    for root in (c and os.path.dirname(os.path.dirname(os.path.realpath(c))), ROCM_HOME, "/opt/rocm"):
+        if root and os.path.exists(os.path.join(root, "include", "hip", "hip_runtime_api.h")):
+            return os.path.join(root, "include")
+    raise RuntimeError("no HIP headers beside hipcc (%s), in ROCM_HOME or under /opt/rocm" % (c or "not on PATH"))
+
+
 def _compile(src: str, extra) -> str:
     obj = os.path.join(OBJ_DIR, os.path.splitext(os.path.basename(src))[0] + ".o")
     cmd = [hipcc(), *HIPCC_FLAGS, *extra, "-c", os.path.join(CSRC, src), "-o", obj]
@@ -59,8 +71,7 @@ def _compile_calls() -> str:
     import torch
     from torch.utils.cpp_extension import include_paths
     obj = os.path.join(OBJ_DIR, "py_calls.o")
-    rocm = os.path.dirname(os.path.dirname(os.path.realpath(hipcc())))
-    incs = [sysconfig.get_path("include"), *include_paths(), os.path.join(rocm, "include"), os.path.join(ROOT, "include")]
+    incs = [sysconfig.get_path("include"), *include_paths(), hip_include(), os.path.join(ROOT, "include")]
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM", "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
            *[x for i in incs for x in ("-isystem", i)], "-c", os.path.join(CSRC, CALLS_SOURCE), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
