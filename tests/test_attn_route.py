@@ -7,12 +7,13 @@ from paper_2602_10940_amd import binding as b
 from paper_2602_10940_amd import diag
 
 
-def _desc(B, H, d, Sq, lens, fp8=False, flags=0):
+def _desc(B, H, d, Sq, lens, fp8=False, flags=0, f32=False):
     x = b.AttnDesc()
     x._lens = (ctypes.c_int32 * len(lens))(*lens)
     x.B, x.H, x.d, x.Sq, x.n_chunks, x.flags = B, H, d, Sq, len(lens), flags
     x.chunk_len = ctypes.cast(x._lens, ctypes.POINTER(ctypes.c_int32))
-    x.qo_dtype, x.kv_dtype = b.USP_BF16, b.USP_FP8_E4M3FN if fp8 else b.USP_BF16
+    x.qo_dtype = b.USP_F32 if f32 else b.USP_BF16
+    x.kv_dtype = b.USP_FP8_E4M3FN if fp8 else x.qo_dtype
     for i, s in enumerate((H * Sq * d, Sq * d, d)):
         x.q_stride[i] = x.o_stride[i] = s
     return x
@@ -144,3 +145,36 @@ def test_copy_work_groups_of_a_mixed_launch_find_their_cus_free():
 def test_mixed_launches_by_number(blocks, wgs, copies_wgs, copy_wgs):
     assert diag.usp_diag_mixed_grid(blocks).wgs == wgs and diag.usp_diag_mixed_grid(blocks, copies=True)[::2] == (copies_wgs, copy_wgs)
     assert diag.usp_diag_mixed_grid(blocks, forced=True).halves == -(-((blocks + 1) // 2) // 8)
+
+
+# B, H, d, Sq, keys, fp32, from FP8: the number of work-groups that share the keys of a query block in the general kernel
+GENERAL = [(1, 8, 32, 102, 1549, True, False, 8), (1, 8, 128, 102, 1549, True, False, 8), (1, 4, 64, 512, 512, True, False, 4),
+           (1, 4, 32, 512, 512, True, False, 1), (1, 16, 40, 153, 1793, False, False, 8), (1, 16, 160, 153, 1793, False, False, 4),
+           (1, 16, 112, 153, 1793, False, True, 4), (2, 16, 72, 1024, 1024, False, False, 1), (1, 2, 64, 128, 256, True, False, 1)]
+
+
+@pytest.mark.parametrize("B,H,d,Sq,keys,f32,fp8,parts", GENERAL)
+def test_general_calls_over_one_chunk_under_few_queries_share_their_keys(B, H, d, Sq, keys, f32, fp8, parts):
+    assert _route(B, H, d, Sq, (keys,), fp8=fp8, f32=f32) == (False, False, parts)
+    # several chunks are merged one after another and keep their keys together, also where one alone holds any
+    for lens in ((keys // 2, keys - keys // 2), (keys, 0), (0, keys)):
+        assert _route(B, H, d, Sq, lens, fp8=fp8, f32=f32).parts == 1
+
+
+@pytest.mark.parametrize("f32", [True, False])
+@pytest.mark.parametrize("d", [8, 40, 72, 96, 128, 136, 160, 168, 256])
+def test_the_shares_of_a_general_call(d, f32):
+    if not f32 and d == 128:
+        return                                                                  # (a matrix-core kernel's)
+    for heads in (1, 3, 8, 24, 60, 255, 256):
+        for Sq in (1, 17, 100, 513, 2048):
+            for keys in (1, 64, 192, 193, 256, 257, 1024, 4097, 70000):
+                parts = _route(1, heads, d, Sq, (keys,), f32=f32).parts
+                need = b.usp_ring_attn_workspace_bytes(_desc(1, heads, d, Sq, (keys,), f32=f32))
+                if heads * -(-Sq // 64) >= 256 or d > 160 or (f32 and d > 128) or keys <= 192:
+                    assert parts == 1
+                assert parts in (1, 2, 4, 8) and 2 * parts <= max(2, -(-keys // 64))      # two tiles each at least
+                assert parts == 1 or parts * heads * -(-Sq // (16 if f32 else 32)) <= 768
+                # fp32 O~ and (m, l) of every share, and nothing where the keys stay together
+                rows = heads * Sq
+                assert need == (0 if parts == 1 else sum(-(-4 * n * parts * rows // 256) * 256 for n in (d, 2)))

@@ -218,7 +218,7 @@ def test_ring4_fused_unfused_and_double_buffered_agree():
     np.testing.assert_array_equal(lf2, lu)
 
 
-@pytest.mark.parametrize("flags,lens,masked", [(0, (192, 64, 100, 128), None), (16, (192, 64, 100, 128), None),
+@pytest.mark.parametrize("flags,lens,masked", [(0, (192, 64, 100, 128), None), (16, (192, 64, 100, 128), None), (16 | 64, (192, 64, 128, 128), None),
                                                (2, (192, 64, 100, 128), None), (0, (192, 64, 128, 128), None),
                                                (16, (192, 64, 128, 128), None),
                                                (0, (192, 64, 128, 128), (200, 300)), (16, (192, 64, 128, 128), (200, 300))])
@@ -259,15 +259,15 @@ def test_ring_call_replays_from_a_hip_graph(flags, lens, masked):
         assert torch.equal(out, ref_o) and torch.equal(lse, ref_l)
 
 
-@pytest.mark.parametrize("flags", [1, 16])
+@pytest.mark.parametrize("flags", [1, 16, 1 | 64, 16 | 64])
 @pytest.mark.parametrize("lens", [(136,) * 8, (128, 0, 192, 64, 0, 7, 256, 64), (128, 0, 192, 64, 0, 64, 256, 64),
                                   (0, 64, 1152, 64), (64,) * 16])
 def test_double_buffer_poisoned_staging(flags, lens):
     """Fill the workspace with NaN bit patterns first: a chunk consumed before its copy landed
     (a missing event, a transfer into the wrong buffer) would put NaN into O.  Both transfer
     modes; equal chunks, and unequal ones with empty chunks, a ragged tail and whole-tile chunks
-    (every attention kernel variant carries a transfer at some step).  With lengths that are all
-    multiples of 64, flags 16 runs the whole ring as one launch whose first work-groups copy the
+    (plain, ragged and masked-tail launches carry a transfer at some step).  With lengths that are all
+    multiples of 64, flags 16 without STEPWISE runs the whole ring as one launch whose first work-groups copy the
     chunks and publish arrival counters; a tile loaded before its chunk's count was reached would
     be the NaN of the poisoned buffer."""
     P = _P()
@@ -277,7 +277,7 @@ def test_double_buffer_poisoned_staging(flags, lens):
     out = torch.empty_like(q)
     desc = P.make_attn_desc(q, ks, out, float(inp.softmax_scale), flags)
     ws = torch.full((P.usp_ring_attn_workspace_bytes(desc),), 0xFF, dtype=torch.uint8, device=DEV)
-    side = torch.cuda.Stream() if flags == 1 else None
+    side = torch.cuda.Stream() if flags & 1 else None
     for _ in range(3):
         o, l = P.usp_ring_attn_fwd(q, ks, vs, softmax_scale=float(inp.softmax_scale), flags=flags,
                                    out=out, workspace=ws, copy_stream=side)
