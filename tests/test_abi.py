@@ -177,6 +177,19 @@ def test_noalloc_calls_of_one_chunk_on_the_general_kernel_leave_the_scratch_alon
         assert b"NULL" in lib.usp_last_error()
 
 
+def test_mapped_calls_without_an_element_take_any_stride():
+    """A stride of 2^48 is refused where an index moves by it, but rows of no columns, no rows, and an index that is always 0 have nothing
+    to reach.  (Strides that are multiples of 8 elements, so that rows stay aligned.)"""
+    from paper_2602_10940_amd import binding as b
+    lib = b.load_library()
+    far = (1 << 48, 1 << 50, 64, 64)
+    for fn in (lib.usp_fp8_quant_mapped, lib.usp_fp8_dequant_mapped):
+        call = lambda n, cols: fn(ctypes.byref(b.make_row_map(n, far, far)), cols, b.USP_BF16, None, None, None, None)
+        assert call((2, 3, 1, 1), 0) == call((0, 3, 1, 1), 64) == call((2, 3, 0, 1), 64) == b.USP_OK
+        assert call((2, 3, 1, 1), 64) == b.USP_ERR_INVALID_ARG and b"past any memory" in lib.usp_last_error()
+        assert call((1, 1, 3, 1), 64) == b.USP_ERR_INVALID_ARG and b"NULL" in lib.usp_last_error()      # (the strides were taken)
+
+
 def test_header_is_plain_c():
     """include/usp.h is the boundary: it must compile as C99 and as C++ with nothing but the standard headers."""
     import shutil
