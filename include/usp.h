@@ -187,8 +187,8 @@ usp_status usp_ring_attn_fwd(const usp_attn_desc* desc, const void* q,
  *     transfers inside the launches (USP_ATTN_FUSED_PREFETCH) are available.
  *   - Every other call on one GPU uses that GPU's one array: calls that overlap in time on one GPU (two
  *     streams, two host threads) race and give undefined results; calls ordered on one stream are
- *     safe.  Nothing is carried from call to call: whatever a call needs to start at zero it clears
- *     itself, on compute_stream.
+ *     safe.  Nothing is carried from call to call: what an earlier call has left in the array is overwritten before it is
+ *     read, or (the arrival counters of a ring) recognised as another launch's, on compute_stream.
  *   - The first call on a device looks up the array's address for that device (no allocation); make
  *     that call outside graph capture.
  */

@@ -97,12 +97,15 @@ bool few_work_groups(bool f32, int B, int H, int Sq, int d, int64_t* wgs) {
 // steps of 32, in bf16 by d; what a tile takes longer with two work-groups on a CU, and with more than two; the second launch 2.5,
 // and the shares, written and read, at 5 TB/s.  Powers of two: a share's number then says which XCDs it runs on, so that each
 // L2 holds its part of K and V only (56 work-groups over 25 tiles, d = 128, shared by 3, 4, 6, 8, 12: 29.2, 23.7, 27.1, 23.8,
-// 30.9 us); more than 8 gains 4 % at the most.  A share has two tiles at least, 768 work-groups fit the chip at once.
+// 30.9 us); more than 8 gains 4 % at the most.  A share has two tiles at least.  768 work-groups are a fitted limit: where LDS takes three
+// to a CU they run at once, where it takes two (fp32 d = 33 to 64 and 97 to 128, bf16 d = 65 to 128) those above 512 are a second round, and the factor 2.1 stands for that.
 // Of 80 shapes, each measured with 1, 2, 4 and 8, the choice is on average 1 %, at worst 15 %, above the best and never above 1.
 // us before and after: fp32, 8 heads of 102 queries, 1549 keys, d = 32, 64, 96, 128 23.5, 34.5, 45.4, 60.3 -> 11.7, 15.6, 19.3, 23.5; 4 heads of
 // 512 queries, 512 keys 8.7, 13.0, 17.6, 22.7 -> 8.7 (as before), 11.4, 14.0, 17.1; bf16, 16 heads of 153 queries, 1793 keys, d = 40, 72, 112,
 // 160 25.5, 30.4, 35.7, 36.7 -> 13.2, 15.5, 17.3, 21.8, d = 40, 72, 112 from FP8 35.0, 41.7, 49.2 -> 14.6, 19.1, 22.9.
-// Several chunks are merged one after another, with the operations and the bits of a launch per chunk, and are not shared.
+// Against 64 bits, 21 random shapes, relative L2 over that of one work-group: fp32 0.56 to 0.98, bf16 1.00.
+// Several chunks are merged one after another, with the operations and the bits of a launch per chunk, and are not shared; a ring of which one
+// chunk alone holds keys counts as several (its workspace and its launches are those of a ring).
 int attn_generic_parts(bool f32, int B, int H, int Sq, int d, int keys) {
   int64_t wgs64;
   if (d > 160 || (f32 && d > 128) || !few_work_groups(f32, B, H, Sq, d, &wgs64)) return 1;   // (the sizes of 256 fill a CU with one work-group)

@@ -1381,7 +1381,7 @@ int64_t attn_mfma_max_dead_tiles() { return kMaxWords; }
 // (The prologue and the transfers have become shorter since these figures were taken, by 2 to 3 us and by a third: on 1660
 // random launches the choice takes 4 to 5 % more than the best number of parts on average, one chunk 1.28 times as much at most,
 // a ring 1.5 times.  The figures here and below are those of the launches the constants were fitted to.)
-// At most 240 work-groups, so that the copy work-groups of the same launch (16 at least) find a CU.
+// At most 240 work-groups, so that the copy work-groups of the same launch (16 at least) find a CU (one chunk, which has none, is held to it too).
 //
 // A ring's chunks arrive inside the launch (FP8 chunks always; bf16 ones with USP_ATTN_FUSED_PREFETCH, and the plain
 // call takes the same form, so that the two give the same bits): the last one 11 us after the start, plus 4 (FP8: 7)
@@ -1398,7 +1398,8 @@ int64_t attn_mfma_max_dead_tiles() { return kMaxWords; }
 // half the chip idle (Sq that ends in the first half of a block, 129 to 250 blocks), or, for d = 64, by the estimates of attn_mfma_ring_form (three rounds
 // of half the time instead of two).  us before, key-split: 136 blocks, 1024 keys 25.8, 18.2; 138 blocks, 4608 keys from FP8 128, 91; 132 blocks, 512
 // keys 16.1, 12.2; d = 64, 336 blocks, 4608 keys 154, 128, 2048 keys 73.5, 63.7, 522 blocks, 4143 keys 227, 209.  Of 350 random launches, bf16, FP8 and
-// masked, 30 take it, in 0.70 to 0.98 of the time; of 400 more 26, one of them (FP8, d = 64, 360 blocks, 1024 keys) in 1.02.
+// masked, 30 take it, in 0.70 to 0.98 of the time; of 400 more 26, one of them (FP8, d = 64, 360 blocks, 1024 keys) in 1.02.  Their error against 64 bits is 0.96 to
+// 1.00 of the other form's, with outliers, where the two forms' references differ, 0.86 to 1.05 (mean 1.00), lse 0.3 to 1.0.
 AttnForm attn_mfma_form(int B, int H, int Sq, int d, int64_t tiles, const RingTransfers* ring) {
   const int64_t blocks = (int64_t)B * H * ((Sq + kQPerWGSplit - 1) / kQPerWGSplit), wgs = 8 * ((blocks + 7) / 8);
   AttnForm best = {0, 1};
@@ -1442,7 +1443,7 @@ AttnForm attn_mfma_form(int B, int H, int Sq, int d, int64_t tiles, const RingTr
 // rounds * (10.8 + 1.46 * tiles), d = 64 (8.0 + 1.13 * tiles); key-split ones rounds * (9.6 + 0.73 * tiles) and 0.116
 // per tile and 256 work-groups (idle CUs let the others clock higher), d = 64 (7.1 + 0.47 * tiles) and 0.16; a launch
 // per chunk 10.5 (d = 64: 1.1) each, 5.3 (6.5) per chunk and round, 1.48 (1.12) per tile and round, the last round counting
-// 0.6 where the mixed launch can halve its blocks (d = 128), and 0.115 (0.22) per MB of the carried fp32 O, out and
+// 0.6 where the mixed launch can halve its blocks (d = 128; fitted when those of the last round alone were: with less than 96 of them it takes 4 % less now), and 0.115 (0.22) per MB of the carried fp32 O, out and
 // back between two chunks.  70 rings of 260 to 864 blocks, two to eight chunks of 64 to 4096 keys, all three timed, with the
 // prologue 2 to 3 us longer than it is now: each estimate within 12 % (d = 128: 9 %).  Per chunk, 256-query, key-split: B = 2, H = 24, Sq = 4608, two of 1536
 // 370, 331, 363 us; B = 2, H = 22, d = 64, Sq = 4416, two of 128 92, 47, 62; H = 24, Sq = 2816, four of 1024 245,
