@@ -17,8 +17,9 @@
 //     bf16 and used directly as the B operand of O^T += V^T P^T; it never touches LDS.  (The lane
 //     that holds keys 16*mb + 4*g + i of a query is the lane that must supply contraction indices
 //     8*g + j of the P.V step: the keys of a step are simply taken in that order on the V side.)
-//   * K and V tiles (64 keys) sit in LDS row-major, XOR-swizzled instead of padded; the V^T
-//     operand (8 keys of one head-dim column per lane) comes from the LDS transposing read.
+//   * K and V tiles (64 keys) sit in LDS as 64-byte pieces of rows, ordered so that an operand's address is one
+//     register of the lane's plus an immediate (TileLayout); the V^T operand (8 keys of one head-dim column per
+//     lane) comes from the LDS transposing read.
 //   * O and l are rescaled lazily: only when a row max has outgrown the exponent reference.
 //   * exp is taken in base 2 with scale * log2(e) folded into one FMA.
 #include "usp_common.h"
@@ -39,14 +40,25 @@ constexpr int kQPerWave = 32;
 constexpr int kQPerWG = kWaves * kQPerWave;   // 256
 constexpr int kQPerWGSplit = 4 * kQPerWave;     // 128: split kernel, two waves per 32 queries
 constexpr int kTile = 64;        // keys per LDS tile
-constexpr int kRowB = kD * 2;    // bytes per K / V row in LDS (256, unpadded)
-constexpr int kTileB = kTile * kRowB;          // 16 KB
 
-// K and V tiles are row-major [key][128 bf16] in LDS without padding; bank conflicts are
-// avoided by XOR-swizzling a row (SQ_LDS_BANK_CONFLICT reads 0 for both):
-//   K: the 16-byte piece c of key r sits at piece c ^ (r & 15)   (16-byte MFMA operand reads: 16 lanes, 16 rows)
-//   V: the 32-byte chunk c of key r sits at chunk c ^ (r & 7)     (transposing 8-byte reads: 32 lanes, 8 rows of 32 bytes)
-// (head dimension 64, 128-byte rows: see attn_pp_body)
+// K and V tiles in LDS.  A tile load moves 1 KB: a group of 4 rows (kHalfD, head dimension 64: 8 rows of 128 bytes).  Inside a
+// group the 64-byte quarters (halves) of its rows follow one another, first all rows' first quarter, then all rows' second, ..:
+// the quarter of an operand is then an immediate offset, as its key block is, and all reads of a tensor share one address register
+// (V with kHalfD two).  Four consecutive lanes of a load still fetch 64 consecutive bytes, which is what the address unit counts.
+// Groups lie kPitch apart, a padding that puts the rows a read touches together into different banks (64 of 4 bytes):
+//   K: 16 lanes read 16 bytes of 16 rows, 4 groups apart by 16 bytes: row i of group q at bank 4 * (4 i + q) and up.
+//      kHalfD: 2 groups apart by 32; rows 4 to 7 of a group would meet rows 0 to 3 and have their 16-byte pieces swapped pairwise.
+//   V: 32 lanes read 32 bytes of 8 rows by the transposing read: two groups, apart by 32; kHalfD: one group, whose rows 4 to 7
+//      have the halves of their 64 bytes swapped.
+// With rows of 256 bytes swizzled by XOR, as they were, K took 4 address registers and V 8, each a vector addition per phase, and
+// every load set m0 for itself: 24 heads of 4608 219.8 -> 217.8 us, FP8 ring of two chunks of 4096 under 24 heads 434 -> 426, ragged ring
+// of two chunks of 2215 under 12 heads 64.2 -> 62.6.
+template <bool kHalfD>
+struct TileLayout {
+  static constexpr int kGroup = kHalfD ? 8 : 4;                    // rows that one load moves
+  static constexpr int kPitchK = 1024 + (kHalfD ? 32 : 16), kPitchV = 1024 + (kHalfD ? 0 : 32);
+  static constexpr int kQuarter = kGroup * 64;                     // from a row's 64 bytes to its next
+};
 // Work-group -> (batch*head, query block) with the 8 XCDs of the chip in mind: consecutive
 // work-group ids go to consecutive XCDs (id % 8), each with its own L2.  The (head, query block)
 // items, head-major, are cut into 8 contiguous ranges of equal length, one per XCD: the query
@@ -301,23 +313,34 @@ __device__ __forceinline__ void finish_and_store(const AttnStep& s, f32x4 (&oacc
 //
 // kHalfD: head dimension 64 (see attn_pp_body).
 // =============================================================================================
-__device__ __forceinline__ void lds_dma16(const void* gbase, uint32_t lane_off, uint32_t lds_base) {
-  // 64 lanes x 16 bytes from gbase (wave-uniform) + lane_off (per lane): lane i's 16 bytes land at
-  // lds_base + 16*i.  Issued through inline asm so the compiler does not serialise later LDS reads
-  // behind it; completion is awaited with an explicit vmcnt wait before the barrier that
-  // publishes the tile.
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-               :: "s"(lds_base), "v"(lane_off), "s"(gbase) : "memory", "m0");
-}
-// The same from an address per lane.
+// 64 lanes x 16 bytes from an address per lane: lane i's 16 bytes land at lds_base + 16*i.  Issued through inline asm so
+// the compiler does not serialise later LDS reads behind it; completion is awaited with an explicit vmcnt wait before the
+// barrier that publishes the tile.
 __device__ __forceinline__ void lds_dma16_lanes(const void* p, uint32_t lds_base) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(lds_base), "v"(p) : "memory", "m0");
 }
-// The same through a buffer descriptor (base, 0, bytes, flags) with a uniform offset on top of the lanes':
-// lanes that fall outside the descriptor's bytes load zeros.
-__device__ __forceinline__ void lds_dma16_bounded(u32x4 desc, uint32_t lane_off, uint32_t offset, uint32_t lds_base) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-               :: "s"(lds_base), "v"(lane_off), "s"(desc), "s"(offset) : "memory", "m0");
+// Two (kPair = 0: one) such loads, numbers j and j + 1 (j = 0 or 2) of a wave's share of a tile: load i's bytes land at lds_base + i * kPitch,
+// and come from gbase + off + i * kPitch (an immediate offset counts on both sides).
+template <int kPitch, int kPair>
+__device__ __forceinline__ void lds_dma16_pair(const void* gbase, uint32_t off0, uint32_t off1, uint32_t lds_base, int j) {
+  if (!kPair) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "s"(lds_base), "v"(off0), "s"(gbase) : "memory", "m0");
+  else if (j == 0)
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %3\n\tglobal_load_lds_dwordx4 %2, %3 offset:%4"
+                 :: "s"(lds_base), "v"(off0), "v"(off1), "s"(gbase), "n"(kPitch) : "memory", "m0");
+  else
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %3 offset:%4\n\tglobal_load_lds_dwordx4 %2, %3 offset:%5"
+                 :: "s"(lds_base), "v"(off0), "v"(off1), "s"(gbase), "n"(2 * kPitch), "n"(3 * kPitch) : "memory", "m0");
+}
+// The same through a buffer descriptor (base, 0, bytes, flags): lanes that fall outside the descriptor's bytes load zeros.
+template <int kPitch, int kPair>
+__device__ __forceinline__ void lds_dma16_pair_bounded(u32x4 desc, uint32_t off0, uint32_t off1, uint32_t lds_base, int j) {
+  if (!kPair) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" :: "s"(lds_base), "v"(off0), "s"(desc) : "memory", "m0");
+  else if (j == 0)
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %3, 0 offen lds\n\tbuffer_load_dwordx4 %2, %3, 0 offen offset:%4 lds"
+                 :: "s"(lds_base), "v"(off0), "v"(off1), "s"(desc), "n"(kPitch) : "memory", "m0");
+  else
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %3, 0 offen offset:%4 lds\n\tbuffer_load_dwordx4 %2, %3, 0 offen offset:%5 lds"
+                 :: "s"(lds_base), "v"(off0), "v"(off1), "s"(desc), "n"(2 * kPitch), "n"(3 * kPitch) : "memory", "m0");
 }
 __device__ __forceinline__ void lds_dma4(const void* gbase, uint32_t lane_off, uint32_t lds_base) {
   // the same with 4 bytes per lane: lane i's dword lands at lds_base + 4*i
@@ -332,11 +355,13 @@ __device__ __forceinline__ void wait_loads() {
 }
 constexpr int kStages = 3, kStagesSplitK = 4;   // LDS tile buffers per tensor; of K in the key-split form
 constexpr int kExtTileB = kTile * 4;   // bytes of one tile's record: the factors of its 64 keys
+constexpr int kStageB = 16 * TileLayout<false>::kPitchV + kExtTileB;   // a stage of either tensor, with room for a record
+constexpr int kQRowsB = 8 * TileLayout<false>::kPitchK;                // 32 rows of Q, laid out as K is
 
 // LDS of a work-group: K stages | V stages | four records | the words of kDead launches (188 000 keys).  The
 // wide work-groups' epilogue stages each wave's O tile (eight regions from offset 0, over everything else,
 // which is dead by then).
-constexpr int kExtOff = (kStagesSplitK + kStages) * kTileB;
+constexpr int kExtOff = (kStagesSplitK + kStages) * kStageB;
 constexpr int kWordsOff = kExtOff + 4 * kExtTileB;
 constexpr int kLdsBytes = 8 * kEpiWaveB;
 constexpr int kMaxWords = 2944;
@@ -427,26 +452,28 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
   const int q0 = q_base + (kSplit ? (wave & 3) : wave) * kQPerWave;
   const bool grpA = wave < 4;
 
-  constexpr int RB = kHalfD ? 128 : kRowB;   // bytes per row of Q, K and V, in LDS too
+  typedef TileLayout<kHalfD> Layout;
+  constexpr int RB = kHalfD ? 128 : 256;     // bytes per row of Q, K and V
   const uint32_t lds_base = (uint32_t)(uintptr_t)smem_raw;
+  // this lane's row of a group that a load moves, and its byte in that row (K and Q, V)
+  const int dma_i = (lane >> 2) & (Layout::kGroup - 1), dma_q = kHalfD ? lane >> 5 : lane >> 4;
+  const uint32_t dma_k = (uint32_t)(64 * dma_q + 16 * ((lane & 3) ^ (kHalfD ? dma_i >> 2 : 0)));
+  const uint32_t dma_v = (uint32_t)(64 * dma_q + 16 * ((lane & 3) ^ (kHalfD ? dma_i >> 2 << 1 : 0)));
   // ---- Q first, the longest way to the first score.  Its operand layout (16 rows x 64 bytes an instruction) would take the
-  // CU's one address unit 64 cycles a load, 4000 for a work-group, so whole rows are moved to LDS, swizzled as K's are, and
-  // the operands read from there.  It lands in tile buffers that no load in front of the second barrier uses: split, the
-  // 32 rows of a pair of waves, half by each, in V stages 1 and 2; wide, a wave's own 32 rows in K stage 2, V stages 1
+  // CU's one address unit 64 cycles a load, 4000 for a work-group, so it is moved to LDS as K is and the operands are
+  // read from there.  It lands in stages that no load in front of the second barrier uses, 32 rows for each half stage: split, the
+  // rows of a pair of waves, half by each, in V stages 1 and 2; wide, a wave's own 32 rows in K stage 2, V stages 1
   // and 2 and the room behind them.
-  const uint32_t q_lds = lds_base + (kSplit ? (kStagesK + 1) * kTileB + (wave & 3) * kQPerWave * RB
-                                            : wave < 2 ? 2 * kTileB + wave * kQPerWave * RB : 4 * kTileB + (wave - 2) * kQPerWave * RB);
+  const int q_slot = kSplit ? 2 * (kStagesK + 1) + (wave & 3) : wave < 2 ? 4 + wave : 6 + wave;
+  const uint32_t q_lds = lds_base + (q_slot >> 1) * kStageB + (q_slot & 1) * kQRowsB;
   {
     const bf16_t* qb = (const bf16_t*)s.q + b * s.qs[0] + h * s.qs[1];
-    constexpr int kRPI = kHalfD ? 8 : 4, kLPR = 64 / kRPI;   // rows per instruction, lanes per row
-    const int first = kSplit && !grpA ? kQPerWave / 2 : 0;
+    constexpr int kGroups = (kSplit ? kQPerWave / 2 : kQPerWave) / Layout::kGroup;
+    const int first = kSplit && !grpA ? kGroups : 0;
 #pragma unroll
-    for (int t = 0; t < (kSplit ? kQPerWave / 2 : kQPerWave) / kRPI; ++t) {
-      const int row = first + t * kRPI + lane / kLPR;
-      const int piece = kHalfD ? (lane % kLPR) ^ ((row >> 1) & 7) : (lane % kLPR) ^ (row & 15);
-      lds_dma16_lanes(qb + (int64_t)min(q0 + row, s.Sq - 1) * s.qs[2] + 8 * piece,
-                      __builtin_amdgcn_readfirstlane(q_lds + (first + t * kRPI) * RB));
-    }
+    for (int t = 0; t < kGroups; ++t)
+      lds_dma16_lanes((const unsigned char*)(qb + (int64_t)min(q0 + (first + t) * Layout::kGroup + dma_i, s.Sq - 1) * s.qs[2]) + dma_k,
+                      __builtin_amdgcn_readfirstlane(q_lds + (first + t) * Layout::kPitchK));
   }
   const unsigned char* kb = (const unsigned char*)((const bf16_t*)s.k + b * s.ks[0] + h * s.ks[1]);
   const unsigned char* vb = (const unsigned char*)((const bf16_t*)s.v + b * s.ks[0] + h * s.ks[1]);
@@ -542,48 +569,44 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
   constexpr int kProbeAheadTiles = 4;
 
   if (!kDead || nt > 0) {   // (uniform over the work-group)
-  // ---- direct global->LDS tile loads, 4 rows (16 lanes each) per instruction.  wide: wave w moves
-  // rows 8w..8w+7 of every tile.  split: only the group in its softmax phase loads, wave w its own
-  // rows 8w..8w+7 and those of its partner w^4, 32 rows away (same swizzle: 32 is a multiple of
-  // 16).  Per-lane byte offsets inside a tile are fixed; the tile base pointers advance as scalars.
-  // kHalfD (head dimension 64): rows are 128 bytes in global memory and in LDS, so one instruction moves
-  // 8 rows (8 lanes each) and a wave's share of a tile is a single load per tensor; the swizzles are
-  //   K: piece c (of 8) of key r sits at piece c ^ ((r >> 1) & 7)   (two rows share a sweep of the banks)
-  //   V: the 64-byte half h of key r sits at half h ^ ((r >> 1) & 1)
-  const int dma_r0 = 8 * wave + (kHalfD ? (lane >> 3) : (lane >> 4)), dma_r1 = dma_r0 + 4;
-  const int dma_p = kHalfD ? (lane & 7) : (lane & 15);
+  // ---- direct global->LDS tile loads, a group of rows per instruction.  wide: wave w moves rows 8w..8w+7 of every
+  // tile.  split: only the group in its softmax phase loads, its wave w & 3 the rows 16 * (w & 3) .. + 15.  The loads of a wave and
+  // tensor are kPitch apart in LDS, and as far by their immediate offset, which counts in global memory too and is
+  // taken off the lanes' offsets again (kBias keeps those positive).
+  // kDead: a tile is loaded through a descriptor that ends with its chunk, so that the rows past the end of a
+  // ragged one arrive as zeros (finite data; their P is 0).
+  constexpr int kLoads = (kSplit ? 16 : 8) / Layout::kGroup;   // a wave's, per tile and tensor
+  constexpr uint32_t kBias = 4096;
+  const int dma_row = kSplit ? 16 * (wave & 3) : 8 * wave;
   const uint32_t rowB = (uint32_t)(s.ks[2] * 2);   // bytes between keys in global memory
   const int64_t tileB = (int64_t)kTile * rowB;
-  const uint32_t ksw0 = kHalfD ? (uint32_t)((dma_p ^ ((dma_r0 >> 1) & 7)) << 4) : (uint32_t)((dma_p ^ (dma_r0 & 15)) << 4);
-  const uint32_t ksw1 = (dma_p ^ (dma_r1 & 15)) << 4;
-  // V: the 32-byte chunk c of key r sits at chunk c ^ (r & 7) (kHalfD: c ^ ((r >> 1) & 3)): in 16-byte pieces
-  const uint32_t vsw0 = kHalfD ? (uint32_t)((dma_p ^ (((dma_r0 >> 1) & 3) << 1)) << 4) : (uint32_t)((dma_p ^ ((dma_r0 & 7) << 1)) << 4);
-  const uint32_t vsw1 = (dma_p ^ ((dma_r1 & 7) << 1)) << 4;
-  // kDead: a tile is loaded through a descriptor that ends with its chunk, so that the rows past the end of a
-  // ragged one arrive as zeros (finite data; their P is 0); a wave's rows of the tile's lower or upper half
-  // (split) are then told apart by the uniform offset
-  const int pair_rows = kSplit ? (grpA ? 32 : -32) : 0;
-  const int own_half = kDead && kSplit && !grpA ? 32 : 0;
-  const uint32_t kg0 = (dma_r0 - own_half) * rowB + ksw0, kg1 = (dma_r1 - own_half) * rowB + ksw1;
-  const uint32_t vg0 = (dma_r0 - own_half) * rowB + vsw0, vg1 = (dma_r1 - own_half) * rowB + vsw1;
-  const uint32_t lds_k = __builtin_amdgcn_readfirstlane(lds_base + 8 * wave * RB);
-  const uint32_t lds_v = __builtin_amdgcn_readfirstlane(lds_base + kStagesK * kTileB + 8 * wave * RB);
+  uint32_t k_off[kLoads], v_off[kLoads];
+#pragma unroll
+  for (int j = 0; j < kLoads; ++j) {
+    const uint32_t row = (uint32_t)(dma_row + j * Layout::kGroup + dma_i) * rowB + kBias;
+    k_off[j] = row + dma_k - j * Layout::kPitchK;
+    v_off[j] = row + dma_v - j * Layout::kPitchV;
+  }
+  const uint32_t lds_k = __builtin_amdgcn_readfirstlane(lds_base + dma_row / Layout::kGroup * Layout::kPitchK);
+  const uint32_t lds_v = __builtin_amdgcn_readfirstlane(lds_base + kStagesK * kStageB + dma_row / Layout::kGroup * Layout::kPitchV);
   // a tile of K or V: where it starts, and how many rows its chunk has from there on
   struct TileRef { const unsigned char* p; int left; };
   // (the descriptor ends with the last row, not with the step to the one after it: 64 steps of 64 MB are 2^32)
-  auto tile_desc = [&](TileRef t) -> u32x4 {
-    const uint64_t p = (uint64_t)(uintptr_t)t.p;
-    return u32x4{(uint32_t)p, (uint32_t)(p >> 32) & 0xffffu, (uint32_t)min(t.left, kTile) * rowB - (rowB - RB), 0x00020000u};
+  auto tile_desc = [&](const TileRef& t) -> u32x4 {
+    const uint64_t p = (uint64_t)(uintptr_t)t.p - kBias;
+    return u32x4{(uint32_t)p, (uint32_t)(p >> 32) & 0xffffu, (uint32_t)min(t.left, kTile) * rowB - (rowB - RB) + kBias, 0x00020000u};
   };
-  auto issue_half = [&](const TileRef& t, uint32_t off, uint32_t lds, int half, bool pair) {
-    if (kHalfD && half) return;               // one load covers the wave's 8 rows
-    const int dr = pair ? pair_rows : 0;
-    lds += dr * RB + half * 4 * RB;
-    if (kDead) lds_dma16_bounded(tile_desc(t), off, (uint32_t)(own_half + dr) * rowB, lds);
-    else lds_dma16(t.p + (int64_t)dr * rowB, off, lds);
+  // two loads (kHalfD, wide: the one) of a wave's, j and j + 1
+  auto issue_k = [&](const TileRef& t, int stage, int j) {
+    constexpr int kPair = kLoads < 2 ? 0 : 1;
+    if (kDead) lds_dma16_pair_bounded<Layout::kPitchK, kPair>(tile_desc(t), k_off[j], k_off[j + kPair], lds_k + stage * kStageB, j);
+    else lds_dma16_pair<Layout::kPitchK, kPair>(t.p - kBias, k_off[j], k_off[j + kPair], lds_k + stage * kStageB, j);
   };
-  auto issue_k_half = [&](const TileRef& t, int stage, int half, bool pair) { issue_half(t, half ? kg1 : kg0, lds_k + stage * kTileB, half, pair); };
-  auto issue_v_half = [&](const TileRef& t, int stage, int half, bool pair) { issue_half(t, half ? vg1 : vg0, lds_v + stage * kTileB, half, pair); };
+  auto issue_v = [&](const TileRef& t, int stage, int j) {
+    constexpr int kPair = kLoads < 2 ? 0 : 1;
+    if (kDead) lds_dma16_pair_bounded<Layout::kPitchV, kPair>(tile_desc(t), v_off[j], v_off[j + kPair], lds_v + stage * kStageB, j);
+    else lds_dma16_pair<Layout::kPitchV, kPair>(t.p - kBias, v_off[j], v_off[j + kPair], lds_v + stage * kStageB, j);
+  };
   // kExt: the record of a tile, one load by the first wave of the loading group
   const unsigned char* extb = kExt ? (const unsigned char*)s.ext + (int64_t)bh_ * nt_all * kExtTileB : nullptr;
   const uint32_t lds_ext = lds_base + kExtOff;
@@ -604,13 +627,13 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
     if (kMulti) await_record(t_beg + tile_idx);
     lds_dma4(extb + (int64_t)(t_beg + tile_idx) * kExtTileB, lane * 4, lds_ext + stage * kExtTileB);
   };
-  auto issue_k_tile = [&](TileRef t, int stage) {   // this wave's share
-    issue_k_half(t, stage, 0, false); issue_k_half(t, stage, 1, false);
-    if (kSplit) { issue_k_half(t, stage, 0, true); issue_k_half(t, stage, 1, true); }
+  auto issue_k_tile = [&](const TileRef& t, int stage) {   // this wave's share
+#pragma unroll
+    for (int j = 0; j < kLoads; j += 2) issue_k(t, stage, j);
   };
-  auto issue_v_tile = [&](TileRef t, int stage) {
-    issue_v_half(t, stage, 0, false); issue_v_half(t, stage, 1, false);
-    if (kSplit) { issue_v_half(t, stage, 0, true); issue_v_half(t, stage, 1, true); }
+  auto issue_v_tile = [&](const TileRef& t, int stage) {
+#pragma unroll
+    for (int j = 0; j < kLoads; j += 2) issue_v(t, stage, j);
   };
 
   // A place in the K or V stream, moved on by whole tiles.  kMulti: the chunks follow one another; a place
@@ -686,28 +709,16 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
   f32x4 sacc[4][2];   // scores: [16-key block mb][16-query block nb]: keys 16*mb + 4*g + i of query 16*nb + r
   u32x4 pk[2][2];     // bf16 P as the B operand of P.V: [32-key step kk][nb]: keys 32*kk + 16*(j >> 2) + 4*g + (j & 3), j = 0..7
 
-  // per-lane LDS read addresses (see the layout notes at the top): 4 for the K operand (one per 32-wide
-  // slice of the head dimension), 8 for the V^T operand (one per 16-wide slice); stage, key block
-  // and row offsets are compile-time immediates on top of these
+  // per-lane LDS read addresses (see TileLayout): stage, head-dim slice and key block are added to these, the latter two as immediates
   typedef const __attribute__((address_space(3))) unsigned char* lds_cptr;
-  lds_cptr k_rd[4], v_rd[8];
+  lds_cptr k_rd, v_rd[2];                       // K: row r, dims 8*g .. +7; V: by db & 1
   {
-    const int vrow = 4 * g + (r >> 2);          // the key this lane names in a transposing read (plus 32*kk, plus 16)
-    if (!kHalfD) {
-#pragma unroll
-      for (int ks = 0; ks < 4; ++ks)
-        k_rd[ks] = (lds_cptr)(uintptr_t)(lds_base + r * RB + (((4 * ks + g) ^ r) << 4));
-#pragma unroll
-      for (int db = 0; db < 8; ++db)
-        v_rd[db] = (lds_cptr)(uintptr_t)(lds_base + kStagesK * kTileB + vrow * RB + ((db ^ (vrow & 7)) << 5) + 8 * (r & 3));
-    } else {
-#pragma unroll
-      for (int ks = 0; ks < 4; ++ks)
-        k_rd[ks] = (lds_cptr)(uintptr_t)(lds_base + r * RB + ((((4 * ks + g) & 7) ^ ((r >> 1) & 7)) << 4));
-#pragma unroll
-      for (int db = 0; db < 8; ++db)
-        v_rd[db] = (lds_cptr)(uintptr_t)(lds_base + kStagesK * kTileB + vrow * RB + (((db & 3) ^ ((vrow >> 1) & 3)) << 5) + 8 * (r & 3));
-    }
+    const int kr = r & (Layout::kGroup - 1);
+    k_rd = (lds_cptr)(uintptr_t)(lds_base + r / Layout::kGroup * Layout::kPitchK + kr * 64 + ((g ^ (kHalfD ? kr >> 2 : 0)) << 4));
+    const int vrow = 4 * g + (r >> 2), vr = vrow & (Layout::kGroup - 1);   // the key this lane names in a transposing read (plus 32*kk, plus 16)
+    const uint32_t v0 = lds_base + kStagesK * kStageB + vrow / Layout::kGroup * Layout::kPitchV + vr * 64 + 8 * (r & 3);
+    v_rd[0] = (lds_cptr)(uintptr_t)(v0 + (kHalfD ? (vr >> 2) * 32 : 0));
+    v_rd[1] = (lds_cptr)(uintptr_t)(v0 + (kHalfD ? (1 - (vr >> 2)) * 32 : 32));
   }
   // kExt: this lane's keys of a tile are rows 16*mb + 4*g + (0..3), mb = 0..3
   const lds_cptr x_rd = (lds_cptr)(uintptr_t)(lds_ext + 16 * g);
@@ -716,11 +727,12 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
   // V^T: head dims 16*db .. +15 (MFMA rows), keys of step kk in the order of pk: two transposing reads of
   // four keys each (rows 32*kk + 4*g + i and 32*kk + 16 + 4*g + i).
   auto k_operand = [&](int stage, int mb, int ks) -> bf16x8 {
-    return *reinterpret_cast<const __attribute__((address_space(3))) bf16x8*>(k_rd[ks] + stage * kTileB + 16 * mb * RB);
+    return *reinterpret_cast<const __attribute__((address_space(3))) bf16x8*>(k_rd + stage * kStageB + 16 / Layout::kGroup * mb * Layout::kPitchK + ks * Layout::kQuarter);
   };
   auto v_operand = [&](int stage, int kk, int db) -> bf16x8 {
-    const u32x2 lo = lds_read_tr3(v_rd[db] + stage * kTileB + 32 * kk * RB);
-    const u32x2 hi = lds_read_tr3(v_rd[db] + stage * kTileB + (32 * kk + 16) * RB);
+    const lds_cptr p = (kHalfD ? v_rd[db & 1] : v_rd[0] + 32 * (db & 1)) + stage * kStageB + (db >> 1) * Layout::kQuarter;
+    const u32x2 lo = lds_read_tr3(p + 32 / Layout::kGroup * kk * Layout::kPitchV);
+    const u32x2 hi = lds_read_tr3(p + (32 * kk + 16) / Layout::kGroup * Layout::kPitchV);
     return __builtin_bit_cast(bf16x8, u32x4{lo[0], lo[1], hi[0], hi[1]});
   };
   const f32x4 zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -921,35 +933,19 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
     if (do_v) settle(vpre, true);
     // sched_barrier: keep each load between two blocks of arithmetic (the scheduler would
     // otherwise hoist all of them to the top, where they queue behind one another)
-    if (!kSplit) {
-      if (do_k) issue_k_half(kpre.t, sk, 0, false);
-      exp_block(0, 0, psum[0], xs, true);
-      __builtin_amdgcn_sched_barrier(0);
-      if (do_k) issue_k_half(kpre.t, sk, 1, false);
-      exp_block(0, 1, psum[1], xs, true);
-      __builtin_amdgcn_sched_barrier(0);
-      if (do_v) issue_v_half(vpre.t, sv, 0, false);
-      exp_block(1, 0, psum[0], xs, true);
-      __builtin_amdgcn_sched_barrier(0);
-      if (do_v) issue_v_half(vpre.t, sv, 1, false);
-      if (kExt && do_x) issue_ext(xpre_idx, xst);
-      exp_block(1, 1, psum[1], xs, true);
-      __builtin_amdgcn_sched_barrier(0);
-    } else {
-      if (do_v) { issue_v_half(vpre.t, sv, 0, false); issue_v_half(vpre.t, sv, 0, true); }
-      exp_block(0, 0, psum[0], xs, true);
-      __builtin_amdgcn_sched_barrier(0);
-      if (do_v) { issue_v_half(vpre.t, sv, 1, false); issue_v_half(vpre.t, sv, 1, true); }
-      exp_block(0, 1, psum[1], xs, true);
-      __builtin_amdgcn_sched_barrier(0);
-      if (do_k) { issue_k_half(kpre.t, sk, 0, false); issue_k_half(kpre.t, sk, 0, true); }
-      exp_block(1, 0, psum[0], xs, true);
-      __builtin_amdgcn_sched_barrier(0);
-      if (do_k) { issue_k_half(kpre.t, sk, 1, false); issue_k_half(kpre.t, sk, 1, true); }
-      if (kExt && do_x) issue_ext(xpre_idx, xst);
-      exp_block(1, 1, psum[1], xs, true);
-      __builtin_amdgcn_sched_barrier(0);
-    }
+    if (do_v) issue_v(vpre.t, sv, 0);
+    exp_block(0, 0, psum[0], xs, true);
+    __builtin_amdgcn_sched_barrier(0);
+    if (do_v && kLoads > 2) issue_v(vpre.t, sv, 2);
+    exp_block(0, 1, psum[1], xs, true);
+    __builtin_amdgcn_sched_barrier(0);
+    if (do_k) issue_k(kpre.t, sk, 0);
+    exp_block(1, 0, psum[0], xs, true);
+    __builtin_amdgcn_sched_barrier(0);
+    if (do_k && kLoads > 2) issue_k(kpre.t, sk, 2);
+    if (kExt && do_x) issue_ext(xpre_idx, xst);
+    exp_block(1, 1, psum[1], xs, true);
+    __builtin_amdgcn_sched_barrier(0);
     kpre.t.p += kPreStep * tileB; kpre.t.left -= kPreStep * kTile;
     vpre.t.p += kPreStep * tileB; vpre.t.left -= kPreStep * kTile;
     // (per query block: a block all of whose lanes passed keeps its exponentials and its reference)
@@ -1023,7 +1019,7 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
 
   // prologue: Q has landed and is read, then the tiles of the first scores
   {
-    constexpr int kTL = (kSplit ? 2 : 1) * (kHalfD ? 1 : 2);   // a wave's loads per tile
+    constexpr int kTL = kLoads;   // a wave's loads per tile
     if (kSplit) {
       if (grpA || nt > 2) wait_loads<2 * kTL>();
       else wait_loads<0>();
@@ -1035,7 +1031,7 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
     for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
       for (int ks = 0; ks < kKS; ++ks)
-        qreg[nb][ks] = *reinterpret_cast<const __attribute__((address_space(3))) bf16x8*>(k_rd[ks] + (q_lds - lds_base) + 16 * nb * RB);
+        qreg[nb][ks] = *reinterpret_cast<const __attribute__((address_space(3))) bf16x8*>(k_rd + (q_lds - lds_base) + 16 / Layout::kGroup * nb * Layout::kPitchK + ks * Layout::kQuarter);
     if (kSplit) {
       if (grpA || nt > 2) wait_loads<kTL, true>();
       else wait_loads<0, true>();
