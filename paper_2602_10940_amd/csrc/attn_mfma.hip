@@ -572,11 +572,12 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
   // ---- direct global->LDS tile loads, a group of rows per instruction.  wide: wave w moves rows 8w..8w+7 of every
   // tile.  split: only the group in its softmax phase loads, its wave w & 3 the rows 16 * (w & 3) .. + 15.  The loads of a wave and
   // tensor are kPitch apart in LDS, and as far by their immediate offset, which counts in global memory too and is
-  // taken off the lanes' offsets again (kBias keeps those positive).
+  // taken off the lanes' offsets again (kBias keeps those positive, for rows of RB bytes and more).
   // kDead: a tile is loaded through a descriptor that ends with its chunk, so that the rows past the end of a
   // ragged one arrive as zeros (finite data; their P is 0).
   constexpr int kLoads = (kSplit ? 16 : 8) / Layout::kGroup;   // a wave's, per tile and tensor
-  constexpr uint32_t kBias = 4096;
+  constexpr uint32_t kBias = 128;
+  static_assert(kBias >= 3 * (uint32_t)(Layout::kPitchV - 1024) && kBias >= 3 * (uint32_t)(Layout::kPitchK - 1024), "lane offsets");
   const int dma_row = kSplit ? 16 * (wave & 3) : 8 * wave;
   const uint32_t rowB = (uint32_t)(s.ks[2] * 2);   // bytes between keys in global memory
   const int64_t tileB = (int64_t)kTile * rowB;
@@ -589,92 +590,77 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
   }
   const uint32_t lds_k = __builtin_amdgcn_readfirstlane(lds_base + dma_row / Layout::kGroup * Layout::kPitchK);
   const uint32_t lds_v = __builtin_amdgcn_readfirstlane(lds_base + kStagesK * kStageB + dma_row / Layout::kGroup * Layout::kPitchV);
-  // a tile of K or V: where it starts, and how many rows its chunk has from there on
-  struct TileRef { const unsigned char* p; int left; };
-  // (the descriptor ends with the last row, not with the step to the one after it: 64 steps of 64 MB are 2^32)
-  auto tile_desc = [&](const TileRef& t) -> u32x4 {
-    const uint64_t p = (uint64_t)(uintptr_t)t.p - kBias;
-    return u32x4{(uint32_t)p, (uint32_t)(p >> 32) & 0xffffu, (uint32_t)min(t.left, kTile) * rowB - (rowB - RB) + kBias, 0x00020000u};
-  };
-  // two loads (kHalfD, wide: the one) of a wave's, j and j + 1
-  auto issue_k = [&](const TileRef& t, int stage, int j) {
-    constexpr int kPair = kLoads < 2 ? 0 : 1;
-    if (kDead) lds_dma16_pair_bounded<Layout::kPitchK, kPair>(tile_desc(t), k_off[j], k_off[j + kPair], lds_k + stage * kStageB, j);
-    else lds_dma16_pair<Layout::kPitchK, kPair>(t.p - kBias, k_off[j], k_off[j + kPair], lds_k + stage * kStageB, j);
-  };
-  auto issue_v = [&](const TileRef& t, int stage, int j) {
-    constexpr int kPair = kLoads < 2 ? 0 : 1;
-    if (kDead) lds_dma16_pair_bounded<Layout::kPitchV, kPair>(tile_desc(t), v_off[j], v_off[j + kPair], lds_v + stage * kStageB, j);
-    else lds_dma16_pair<Layout::kPitchV, kPair>(t.p - kBias, v_off[j], v_off[j + kPair], lds_v + stage * kStageB, j);
-  };
-  // kExt: the record of a tile, one load by the first wave of the loading group
-  const unsigned char* extb = kExt ? (const unsigned char*)s.ext + (int64_t)bh_ * nt_all * kExtTileB : nullptr;
-  const uint32_t lds_ext = lds_base + kExtOff;
-  // kMulti: the record of a tile is written by the copy work-groups together with its chunk
-  int xcur_c = 0, xcur_end = kMulti ? tiles_of(s.chunk[0].Sc) : 0;
-  auto await_record = [&](int idx) {
-    while (idx >= xcur_end) {
-      ++xcur_c;
-      xcur_end += tiles_of(s.chunk[xcur_c].Sc);
-      if (xcur_c > arrived_upto) {
-        if (!wait_arrival<!kExt>(s, xcur_c)) late = true;
-        arrived_upto = xcur_c;
-      }
-    }
-  };
-  auto issue_ext = [&](int tile_idx, int stage) {
-    if ((wave & 3) != 0) return;
-    if (kMulti) await_record(t_beg + tile_idx);
-    lds_dma4(extb + (int64_t)(t_beg + tile_idx) * kExtTileB, lane * 4, lds_ext + stage * kExtTileB);
-  };
-  auto issue_k_tile = [&](const TileRef& t, int stage) {   // this wave's share
-#pragma unroll
-    for (int j = 0; j < kLoads; j += 2) issue_k(t, stage, j);
-  };
-  auto issue_v_tile = [&](const TileRef& t, int stage) {
-#pragma unroll
-    for (int j = 0; j < kLoads; j += 2) issue_v(t, stage, j);
-  };
-
-  // A place in the K or V stream, moved on by whole tiles.  kMulti: the chunks follow one another; a place
-  // that has run past its chunk (left <= 0) is carried into the next one when its tile is asked for.  Kept
-  // in scalar registers: a lone wave issues one instruction of any kind per 5 cycles or so, and looking the chunk up
-  // for every tile cost the softmax phase some hundred scalar instructions and the latency of their loads.
-  struct TileCursor { TileRef t; int c; };
-  auto chunk_base = [&](int c, bool is_v) -> const unsigned char* {
-    if (!kMulti) return is_v ? vb : kb;
+  // The tiles are a stream, of one chunk or (kMulti) of chunks that follow one another, and a place in it is kept in scalar
+  // registers: where K's and V's tile begin (less kBias), the rows their chunk has from there on, and the chunk.  A place that
+  // has run past its chunk (left <= 0) is carried into the next one by enter().
+  struct Place { uint64_t k, v; int left, c; };
+  auto chunk_base = [&](int c, bool is_v) -> uint64_t {
+    if (!kMulti) return (uint64_t)(uintptr_t)(is_v ? vb : kb) - kBias;
     const AttnStep::Chunk& ch = s.chunk[c];
-    return (const unsigned char*)((const bf16_t*)(is_v ? ch.v : ch.k) + b * ch.ks0 + h * ch.ks1);
+    return (uint64_t)(uintptr_t)((const bf16_t*)(is_v ? ch.v : ch.k) + b * ch.ks0 + h * ch.ks1) - kBias;
   };
-  auto place = [&](int idx, bool is_v) -> TileCursor {   // idx tiles behind this work-group's first one
-    idx += t_beg;
-    return TileCursor{TileRef{chunk_base(0, is_v) + idx * tileB, (kMulti ? s.chunk[0].Sc : s.Sc) - idx * kTile}, 0};
-  };
-  auto settle = [&](TileCursor& cur, bool is_v) {
+  auto enter = [&](Place& p) {
     if (!kMulti) return;
-    while (cur.t.left <= 0) {
-      const int over = (-cur.t.left) / kTile;   // whole tiles of the next chunk
-      ++cur.c;
-      cur.t.p = chunk_base(cur.c, is_v) + over * tileB;
-      cur.t.left = s.chunk[cur.c].Sc - over * kTile;
-      if (cur.c > arrived_upto) {
+    while (p.left <= 0) {
+      const int over = (-p.left) / kTile;   // whole tiles of the next chunk
+      ++p.c;
+      p.k = chunk_base(p.c, false) + over * tileB;
+      p.v = chunk_base(p.c, true) + over * tileB;
+      p.left = s.chunk[p.c].Sc - over * kTile;
+      if (p.c > arrived_upto) {
         // the count read a few tiles ago usually settles it; otherwise poll
-        const bool seen = probe_c == cur.c && has_arrived<!kExt>(s, probe_val);
-        if (!seen && !wait_arrival<!kExt>(s, cur.c)) late = true;
-        arrived_upto = cur.c;
+        const bool seen = probe_c == p.c && has_arrived<!kExt>(s, probe_val);
+        if (!seen && !wait_arrival<!kExt>(s, p.c)) late = true;
+        arrived_upto = p.c;
       }
     }
-    // a few tiles before the K stream leaves a chunk, read the next chunk's count without waiting
-    // for the answer: a blocking poll at the boundary costs a round trip to memory on the critical path
-    if (!is_v && cur.t.left <= kProbeAheadTiles * kTile && cur.c + 1 < s.n_multi && cur.c + 1 > arrived_upto && probe_c <= cur.c) {
-      probe_c = cur.c + 1;
-      probe_val = read_count<!kExt>(s.arrive + probe_c);
+  };
+  auto raw_place = [&](int idx) -> Place {   // idx tiles behind this work-group's first one
+    idx += t_beg;
+    return Place{chunk_base(0, false) + idx * tileB, chunk_base(0, true) + idx * tileB, (kMulti ? s.chunk[0].Sc : s.Sc) - idx * kTile, 0};
+  };
+  auto place = [&](int idx) -> Place {
+    Place p = raw_place(idx);
+    enter(p);
+    return p;
+  };
+  // kDead: bytes of a tile's descriptor, which ends with the last row, not with the step to the one after it: 64 steps of 64 MB are 2^32
+  auto tile_bytes = [&](int left) -> uint32_t { return (uint32_t)min(left, kTile) * rowB - (rowB - RB) + kBias; };
+  // loads j and j + 1 (kHalfD, wide: the one) of a wave's share of a tile, to the stage that begins `stage` bytes behind the first
+  constexpr int kPair = kLoads < 2 ? 0 : 1;
+  auto issue_k = [&](uint64_t p, uint32_t bytes, int stage, int j) {
+    if (kDead) lds_dma16_pair_bounded<Layout::kPitchK, kPair>(u32x4{(uint32_t)p, (uint32_t)(p >> 32) & 0xffffu, bytes, 0x00020000u}, k_off[j], k_off[j + kPair], lds_k + stage, j);
+    else lds_dma16_pair<Layout::kPitchK, kPair>((const void*)(uintptr_t)p, k_off[j], k_off[j + kPair], lds_k + stage, j);
+  };
+  auto issue_v = [&](uint64_t p, uint32_t bytes, int stage, int j) {
+    if (kDead) lds_dma16_pair_bounded<Layout::kPitchV, kPair>(u32x4{(uint32_t)p, (uint32_t)(p >> 32) & 0xffffu, bytes, 0x00020000u}, v_off[j], v_off[j + kPair], lds_v + stage, j);
+    else lds_dma16_pair<Layout::kPitchV, kPair>((const void*)(uintptr_t)p, v_off[j], v_off[j + kPair], lds_v + stage, j);
+  };
+  auto issue_k_tile = [&](const Place& p, int stage) {   // this wave's share
+#pragma unroll
+    for (int j = 0; j < kLoads; j += 2) issue_k(p.k, tile_bytes(p.left), stage * kStageB, j);
+  };
+  auto issue_v_tile = [&](const Place& p, int stage) {
+#pragma unroll
+    for (int j = 0; j < kLoads; j += 2) issue_v(p.v, tile_bytes(p.left), stage * kStageB, j);
+  };
+  // kExt: the record of a tile, one load by the first wave of the loading group.  kMulti: it is written by the copy work-groups
+  // together with its chunk, which await_record waits for where the K stream has not.  Records lie behind the V tiles (split) or,
+  // four of them, behind all stages.
+  const uint32_t lds_ext = lds_base + (kSplit ? kStagesK * kStageB + kStageB - kExtTileB : kExtOff);
+  uint64_t xpre = kExt ? (uint64_t)(uintptr_t)s.ext + ((int64_t)bh_ * nt_all + t_beg) * kExtTileB : 0;   // the record loaded next
+  auto await_record = [&](int idx) {
+    int c = 0;
+    for (int end = tiles_of(s.chunk[0].Sc); t_beg + idx >= end;) {
+      end += tiles_of(s.chunk[++c].Sc);
+      if (c > arrived_upto) {
+        if (!wait_arrival<!kExt>(s, c)) late = true;
+        arrived_upto = c;
+      }
     }
   };
-  auto tile_at = [&](int idx, bool is_v) -> TileRef {
-    TileCursor cur = place(idx, is_v);
-    settle(cur, is_v);
-    return cur.t;
+  auto issue_ext = [&](int stage) {
+    if ((wave & 3) == 0) lds_dma4((const void*)(uintptr_t)xpre, lane * 4, lds_ext + stage);
   };
 
   // Tiles needed before the first loads of the softmax phases land are fetched here.
@@ -684,26 +670,63 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
   // next K / V tile this wave prefetches; split: K(p+3) / V(p+1) of its group's first softmax phase, p = 0 (A) or 1 (B)
   const int kpre_idx = (kSplit ? 3 : 2) + (wave >> 2), vpre_idx = 1 + (wave >> 2);
   if (kMulti) touch_chunks();
+  constexpr int kExtStep = kSplit ? kStageB : kExtTileB;   // from one stage of the records to the next
   if (kExt && grpA) {
-    issue_ext(0, 0);
-    if (nt > 1) issue_ext(1, 1);
+    if (kMulti) await_record(nt > 1 ? 1 : 0);
+    issue_ext(0);
+    xpre += kExtTileB;
+    if (nt > 1) issue_ext(kExtStep);
+    xpre += kExtTileB;
   }
   if (!kSplit) {
-    issue_k_tile(tile_at(0, false), 0);
-    issue_v_tile(tile_at(0, true), 0);
-    if (nt > 1) issue_k_tile(tile_at(1, false), 1);   // (V(1) and K(2): group B, once Q has left their place)
+    const Place first = place(0);
+    issue_k_tile(first, 0);
+    issue_v_tile(first, 0);
+    if (nt > 1) issue_k_tile(place(1), 1);   // (V(1) and K(2): group B, once Q has left their place)
   } else {
-    // a group moves whole tiles, its own rows and its partner waves': each group two of them
+    // a group moves whole tiles: each group two of them
     if (grpA) {
-      issue_k_tile(tile_at(0, false), 0);
-      issue_v_tile(tile_at(0, true), 0);
+      const Place first = place(0);
+      issue_k_tile(first, 0);
+      issue_v_tile(first, 0);
     } else {
-      if (nt > 1) issue_k_tile(tile_at(1, false), 1);
-      if (nt > 2) issue_k_tile(tile_at(2, false), 2);
+      if (nt > 1) issue_k_tile(place(1), 1);
+      if (nt > 2) issue_k_tile(place(2), 2);
     }
   }
-  TileCursor kpre = place(kpre_idx, false), vpre = place(vpre_idx, true);
+  // The K tile that this wave loads next and, for the same softmax phase, the V tile: its way through the chunks is the K
+  // tile's one phase later, so that only K's is looked after (look_up).  left_look: what is left of K's chunk when there is
+  // something to do: at its end, or a few tiles in front of it, where the next chunk's count is read ahead.  (A lone wave issues
+  // one instruction of any kind per 5 cycles or so.  With a place for each tensor, moved on and looked at by itself, stages as
+  // numbers and a place looked up per record: 24 heads of 4608 3 % more, ring of eight chunks of 2112 under 12 heads 3.4 %, ragged ring
+  // of two of 2215 5 %, on a box where the first took 235 us.)
+  if (kExt && kSplit && !grpA) xpre += 3 * kExtTileB;
+  Place pre = raw_place(kpre_idx);
+  uint64_t vpre = 0;
+  uint32_t vpre_bytes = 0;
+  auto first_v = [&]() {
+    if (vpre_idx >= nt) return;
+    const Place p = place(vpre_idx);
+    vpre = p.v;
+    vpre_bytes = tile_bytes(p.left);
+  };
   constexpr int kPreStep = kSplit ? 2 : 1;   // tiles between two softmax phases of a wave
+  const int64_t pre_step = kPreStep * tileB;
+  int left_look = kMulti && s.arrive != nullptr ? kProbeAheadTiles * kTile : 0;
+  auto look_up = [&]() {
+    if (pre.left <= 0) {
+      enter(pre);
+      vpre = pre.v - pre_step;
+    }
+    // a blocking poll at the boundary would cost a round trip to memory on the critical path
+    const bool ahead = pre.c + 1 < s.n_multi && pre.c + 1 > arrived_upto && probe_c <= pre.c;
+    left_look = ahead ? kProbeAheadTiles * kTile : 0;
+    if (ahead && pre.left <= kProbeAheadTiles * kTile) {
+      probe_c = pre.c + 1;
+      probe_val = read_count<!kExt>(s.arrive + probe_c);
+      left_look = 0;
+    }
+  };
 
   bf16x8 qreg[2][4];   // Q^T operand (B of S^T = K Q^T): lane (r, g) holds Q[q0 + 16*nb + r][32*ks + 8*g .. +7]
   f32x4 sacc[4][2];   // scores: [16-key block mb][16-query block nb]: keys 16*mb + 4*g + i of query 16*nb + r
@@ -722,15 +745,16 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
   }
   // kExt: this lane's keys of a tile are rows 16*mb + 4*g + (0..3), mb = 0..3
   const lds_cptr x_rd = (lds_cptr)(uintptr_t)(lds_ext + 16 * g);
+  // (stages below are bytes behind the first stage: of K, of V, of the records)
 
   // LDS operands.  K: keys 16*mb .. +15 (MFMA rows), head dims 32*ks + 8*g .. +7: one 16-byte read.
   // V^T: head dims 16*db .. +15 (MFMA rows), keys of step kk in the order of pk: two transposing reads of
   // four keys each (rows 32*kk + 4*g + i and 32*kk + 16 + 4*g + i).
   auto k_operand = [&](int stage, int mb, int ks) -> bf16x8 {
-    return *reinterpret_cast<const __attribute__((address_space(3))) bf16x8*>(k_rd + stage * kStageB + 16 / Layout::kGroup * mb * Layout::kPitchK + ks * Layout::kQuarter);
+    return *reinterpret_cast<const __attribute__((address_space(3))) bf16x8*>(k_rd + stage + 16 / Layout::kGroup * mb * Layout::kPitchK + ks * Layout::kQuarter);
   };
   auto v_operand = [&](int stage, int kk, int db) -> bf16x8 {
-    const lds_cptr p = (kHalfD ? v_rd[db & 1] : v_rd[0] + 32 * (db & 1)) + stage * kStageB + (db >> 1) * Layout::kQuarter;
+    const lds_cptr p = (kHalfD ? v_rd[db & 1] : v_rd[0] + 32 * (db & 1)) + stage + (db >> 1) * Layout::kQuarter;
     const u32x2 lo = lds_read_tr3(p + 32 / Layout::kGroup * kk * Layout::kPitchV);
     const u32x2 hi = lds_read_tr3(p + (32 * kk + 16) / Layout::kGroup * Layout::kPitchV);
     return __builtin_bit_cast(bf16x8, u32x4{lo[0], lo[1], hi[0], hi[1]});
@@ -818,7 +842,7 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
   // that the waves do not hit the load path at once.
   // kExt: the per-key factor c replaces the uniform scale.
   auto x_vec = [&](int stage, int mb) -> f32x4 {   // c of keys 16*mb + 4*g + (0..3)
-    return *reinterpret_cast<const __attribute__((address_space(3))) f32x4*>(x_rd + stage * kExtTileB + 64 * mb);
+    return *reinterpret_cast<const __attribute__((address_space(3))) f32x4*>(x_rd + stage + 64 * mb);
   };
   // c of the second key step is fetched while the first is computed
   f32x4 xc[2][2];
@@ -827,7 +851,7 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
     for (int a = 0; a < 2; ++a) xc[kk][a] = x_vec(xs, 2 * kk + a);
   };
   // one block: the 8 scores of query block nb over key step kk -> pk[kk][nb]
-  auto exp_block = [&](int kk, int nb, float& psum, int xs, bool fetch_ahead) {
+  auto exp_block = [&](int kk, int nb, float& psum, int xs, bool fetch_ahead) {   // (key step 0 begins the sum)
     float p[8];
     if (!kExt) {
 #pragma unroll
@@ -835,7 +859,7 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           p[4 * a + e] = __builtin_amdgcn_exp2f(fmaf(sacc[2 * kk + a][nb][e], scale2, -m[nb]));
-          psum += p[4 * a + e];
+          psum = kk == 0 && a == 0 && e == 0 ? p[0] : psum + p[4 * a + e];
         }
     } else {
       if (fetch_ahead && kk == 0 && nb == 1) x_load(1, xs);   // blocks run in the order (0,0) (0,1) (1,0) (1,1)
@@ -844,7 +868,7 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           p[4 * a + e] = __builtin_amdgcn_exp2f(fmaf(sacc[2 * kk + a][nb][e], xc[kk][a][e], -m[nb]));
-          psum += p[4 * a + e];
+          psum = kk == 0 && a == 0 && e == 0 ? p[0] : psum + p[4 * a + e];
         }
       }
     }
@@ -904,58 +928,67 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
   int sm_tile = t_beg + (kSplit && !grpA ? 1 : 0);   // kDead: tile of this wave's next softmax phase
   int next_dead = 0;                         // kDead: the next tile with a dead key, as far as it has been looked up
   typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-  // SM of the tile whose record sits in stage xs; loads K tile kpre_idx into stage sk (if do_k, with
-  // the record of tile xpre_idx into stage xst if do_x) and V tile vpre_idx into stage sv (if do_v)
-  auto SM = [&](int xs, int sk, int sv, bool do_k, bool do_v, bool do_x, int xpre_idx, int xst) {
+  // SM of the tile whose record sits in stage xs; loads the next K tile into stage sk (if do_k), its record, or with idx >= 0 that of
+  // tile idx alone, into stage xst (if do_x), and the next V tile into stage sv (if do_v)
+  auto SM = [&](int xs, int sk, int sv, bool do_k, bool do_v, bool do_x, int xst, int idx) {
     float psum[2] = {0.0f, 0.0f};
     if (kExt) x_load(0, xs);
     if (kDead) {
-      if (next_dead < sm_tile) next_dead = find_dead(sm_tile);
-      if (next_dead == sm_tile) {
-        // (any positive finite factor keeps -inf, and exp2 makes it 0)
-        const uint64_t live = dead_word(sm_tile) >> (4 * g);
+      if (sm_tile >= next_dead) {
+        if (next_dead < sm_tile) next_dead = find_dead(sm_tile);
+        if (next_dead == sm_tile) {
+          // (any positive finite factor keeps -inf, and exp2 makes it 0)
+          const uint64_t live = dead_word(sm_tile) >> (4 * g);
 #pragma unroll
-        for (int mb = 0; mb < 4; ++mb) {
-          const uint32_t bits = (uint32_t)(live >> (16 * mb));   // bit e: key 16*mb + 4*g + e
+          for (int mb = 0; mb < 4; ++mb) {
+            const uint32_t bits = (uint32_t)(live >> (16 * mb));   // bit e: key 16*mb + 4*g + e
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const bool keep = (bits & (1u << e)) != 0u;
-            sacc[mb][0][e] = keep ? sacc[mb][0][e] : -INFINITY;
-            sacc[mb][1][e] = keep ? sacc[mb][1][e] : -INFINITY;
+            for (int e = 0; e < 4; ++e) {
+              const bool keep = (bits & (1u << e)) != 0u;
+              sacc[mb][0][e] = keep ? sacc[mb][0][e] : -INFINITY;
+              sacc[mb][1][e] = keep ? sacc[mb][1][e] : -INFINITY;
+            }
+            __builtin_amdgcn_sched_barrier(0);   // one block's lane masks at a time: sixteen pairs of scalar registers are not to be had
           }
-          __builtin_amdgcn_sched_barrier(0);   // one block's lane masks at a time: sixteen pairs of scalar registers are not to be had
+          next_dead = find_dead(sm_tile + 1);
         }
-        next_dead = find_dead(sm_tile + 1);
       }
       sm_tile += kPreStep;
     }
-    if (do_k) settle(kpre, false);
-    if (do_v) settle(vpre, true);
     // sched_barrier: keep each load between two blocks of arithmetic (the scheduler would
     // otherwise hoist all of them to the top, where they queue behind one another)
-    if (do_v) issue_v(vpre.t, sv, 0);
+    if (do_v) issue_v(vpre, vpre_bytes, sv, 0);
     exp_block(0, 0, psum[0], xs, true);
     __builtin_amdgcn_sched_barrier(0);
-    if (do_v && kLoads > 2) issue_v(vpre.t, sv, 2);
+    if (do_v && kLoads > 2) issue_v(vpre, vpre_bytes, sv, 2);
     exp_block(0, 1, psum[1], xs, true);
     __builtin_amdgcn_sched_barrier(0);
-    if (do_k) issue_k(kpre.t, sk, 0);
+    if (do_k) {
+      if (kMulti && pre.left <= left_look) look_up();
+      if (kDead) vpre_bytes = tile_bytes(pre.left);
+      issue_k(pre.k, vpre_bytes, sk, 0);
+    }
     exp_block(1, 0, psum[0], xs, true);
     __builtin_amdgcn_sched_barrier(0);
-    if (do_k && kLoads > 2) issue_k(kpre.t, sk, 2);
-    if (kExt && do_x) issue_ext(xpre_idx, xst);
+    if (do_k && kLoads > 2) issue_k(pre.k, vpre_bytes, sk, 2);
+    if (kExt && do_x) {
+      if (kMulti && idx >= 0) await_record(idx);
+      issue_ext(xst);
+    }
     exp_block(1, 1, psum[1], xs, true);
     __builtin_amdgcn_sched_barrier(0);
-    kpre.t.p += kPreStep * tileB; kpre.t.left -= kPreStep * kTile;
-    vpre.t.p += kPreStep * tileB; vpre.t.left -= kPreStep * kTile;
+    pre.k += pre_step;
+    if (kMulti || kDead) pre.left -= kPreStep * kTile;
+    vpre += pre_step;
+    if (kExt) xpre += kPreStep * kExtTileB;
     // (per query block: a block all of whose lanes passed keeps its exponentials and its reference)
-    const bool redo0 = __builtin_amdgcn_ballot_w64(!(psum[0] <= kCertifiedSum)) != 0ull;
-    const bool redo1 = __builtin_amdgcn_ballot_w64(!(psum[1] <= kCertifiedSum)) != 0ull;
+    const uint64_t redo0 = __builtin_amdgcn_ballot_w64(!(psum[0] <= kCertifiedSum));
+    const uint64_t redo1 = __builtin_amdgcn_ballot_w64(!(psum[1] <= kCertifiedSum));
     // (kFarOff: what ordinary scores never reach lies outside the loop over the tiles.  FP8 ring of three chunks of 1152 keys,
     // 12 heads, d = 64, 45.8 -> 43.8 us; in the 256-query form, which has no register to spare, that spills, and the mixed
     // launch, which holds both, takes 447 us instead of 435 on 24 heads of 4096 queries, FP8 ring of two with outliers.)
     constexpr bool kFarOff = kSplit && kMulti;
-    if (kFarOff ? __builtin_expect(redo0 || redo1, 0) : (redo0 || redo1)) {
+    if (kFarOff ? __builtin_expect((redo0 | redo1) != 0ull, 0) : (redo0 | redo1) != 0ull) {
       if (!heavy && __builtin_amdgcn_ballot_w64(m[0] != -INFINITY || m[1] != -INFINITY) != 0ull) {
         heavy = true;
         lhat[0] = lsum[0];
@@ -966,7 +999,7 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
       if (kExt) { x_load(0, xs); x_load(1, xs); }
 #pragma unroll
       for (int nb = 0; nb < 2; ++nb) {
-        if (!(nb ? redo1 : redo0)) continue;
+        if ((nb ? redo1 : redo0) == 0ull) continue;
         const float m_new = tmax[nb] > m[nb] ? tmax[nb] + kRefMargin : m[nb];
         // m = -inf (first live tile) gives the factor 0; no live key so far: nothing to rescale, P = 0
         rescale(nb, m_new == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f(m[nb] - m_new));
@@ -1002,8 +1035,8 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
       for (int nb = 0; nb < 2; ++nb) asm volatile("" : "+v"(pk[kk][nb]));
     asm volatile("" : "+v"(lsum[0]), "+v"(lsum[1]), "+v"(lhat[0]), "+v"(lhat[1]));
   };
-  auto nxt = [](int x) { return x == 2 ? 0 : x + 1; };
-  auto first_scores = [&](int stage) {
+  auto first_scores = [&](int stage) {   // (of tile `stage`)
+    stage *= kStageB;
 #pragma unroll
     for (int mb = 0; mb < 4; ++mb) {
       sacc[mb][0] = zero4;
@@ -1065,9 +1098,10 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
     first_reference(0);
     wait_loads<0>();   // V(0), K(1): published by the barrier in front of A's matrix phase
     if (!grpA) {
-      if (nt > 1) issue_v_tile(tile_at(1, true), 1);
-      if (nt > 2) issue_k_tile(tile_at(2, false), 2);
+      if (nt > 1) issue_v_tile(place(1), 1);
+      if (nt > 2) issue_k_tile(place(2), 2);
     }
+    first_v();
     // Both groups execute the same barrier sequence (two per tile index j = 0..nt); the steady-state
     // bodies are straight-line code so the accumulators stay in place.
     // sched_barrier(0): nothing may be moved across a phase boundary (the compiler would otherwise
@@ -1093,19 +1127,24 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
       if (needed) __builtin_amdgcn_s_barrier();
       __builtin_amdgcn_sched_barrier(0);
     };
-    int st = 0;                            // LDS stage of tile j, j % 3
+    // LDS stages of tiles j, j + 1 and j + 2 (mod 3), and the record's of tile j (mod 4)
+    int st = 0, s1 = kStageB, s2 = 2 * kStageB, xs = 0;
+    auto next_tile = [&]() {
+      const int sp = st;
+      st = s1; s1 = s2; s2 = sp;
+      xs = (xs + kExtTileB) & (3 * kExtTileB);
+    };
     if (grpA) {
       // tile j: phase 2j = SM(j), prefetching K(j+2) and its record -> stage st+2, V(j+1) -> stage st+1;
       //         phase 2j+1 = MM(j) with V(j) in stage st, K(j+1) in stage st+1
       for (int j = 0; j < nt - 1; ++j) {
-        const int s1 = nxt(st), s2 = nxt(s1);
-        SM(j & 3, s2, s1, j + 2 < nt, true, j + 2 < nt, j + 2, (j + 2) & 3);
+        SM(xs, s2, s1, j + 2 < nt, true, j + 2 < nt, xs ^ (2 * kExtTileB), -1);
         phase_barrier(j + 2 < nt ? 1 : 2);
         MM_full(st, s1);
         phase_barrier(0, false);
-        st = s1;
+        next_tile();
       }
-      SM((nt - 1) & 3, 0, 0, false, false, false, 0, 0);
+      SM(xs, 0, 0, false, false, false, 0, -1);
       phase_barrier(2);
       MM_last(st);
       phase_barrier(0, false);
@@ -1115,14 +1154,13 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
       // tile j: phase 2j = MM(j-1) with V(j-1) in stage st-1, K(j) in stage st;
       //         phase 2j+1 = SM(j), prefetching K(j+3) -> stage st, V(j+2) -> stage st+2
       phase_barrier(0);                                 // phase 0: nothing to do yet
-      SM(0, 0, 2, 3 < nt, 2 < nt, false, 0, 0);         // phase 1 (tile 0)
+      SM(0, 0, 2 * kStageB, 3 < nt, 2 < nt, false, 0, -1);         // phase 1 (tile 0)
       phase_barrier(3 < nt ? 1 : 2, false);
       for (int j = 1; j < nt; ++j) {
-        const int sp = st;                              // stage of tile j-1
-        st = nxt(st);
-        MM_full(sp, st);
+        MM_full(st, s1);
         phase_barrier(0);
-        SM(j & 3, st, sp, j + 3 < nt, j + 2 < nt, false, 0, 0);   // st+2 == sp (mod 3)
+        next_tile();
+        SM(xs, st, s2, j + 3 < nt, j + 2 < nt, false, 0, -1);
         phase_barrier(j + 3 < nt ? 1 : 2, false);
       }
       MM_last(st);
@@ -1133,9 +1171,10 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
     // scores of tile 0 (group A) / tile 1 (group B)
     if (grpA || nt > 1) {
       first_scores(grpA ? 0 : 1);
-      first_reference(grpA ? 0 : 1);
+      first_reference(grpA ? 0 : kStageB);
     }
     wait_loads<0>();   // V(0), K(2): published by the barrier that ends phase 0
+    first_v();
     // Phases p = 0..nt, one work-group barrier each; both groups execute nt + 1 of them.
     //   reads in phase p : V(p-1) from stage (p-1)%3, K(p+1) from stage (p+1)%4, record p from p%3
     //   batch of phase p : K(p+3) -> stage (p+3)%4 (last read, as K(p-1), in phase p-2; a stage less, and the
@@ -1155,19 +1194,26 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
       __builtin_amdgcn_sched_barrier(0);
     };
     int t = grpA ? 0 : 1;                  // this group's current tile; SM(t) runs in phase t
-    int st = t;                            // t % 3
+    // stages of V and the records of tiles t, t + 1 and t + 2 (mod 3); of K, of tiles t + 2 (read) and t + 3 (loaded), mod 4: from
+    // one to the next but one and back
+    int st = t * kStageB, s1 = st + kStageB, s2 = grpA ? 2 * kStageB : 0;
+    int k_rdst = (t + 2) * kStageB, k_ldst = grpA ? 3 * kStageB : 0;
+    constexpr int kFlipEven = 2 * kStageB, kFlipOdd = kStageB ^ (3 * kStageB);
+    const int flip_rd = grpA ? kFlipEven : kFlipOdd, flip_ld = grpA ? kFlipOdd : kFlipEven;
     if (!grpA) end_phase(false);           // phase 0: group B has no scores yet
     while (t + 2 < nt) {
-      const int s1 = nxt(st), s2 = nxt(s1);                // (t + 1) % 3, (t + 2) % 3
-      SM(st, (t + 3) & 3, s1, t + 3 < nt, true, true, t + 2, s2);   // phase t (t + 1 < nt holds here)
+      SM(st, k_ldst, s1, t + 3 < nt, true, true, s2, t + 3 < nt ? -1 : t + 2);   // phase t (t + 1 < nt holds here)
       end_phase(false);
-      MM_full(st, (t + 2) & 3);                            // phase t + 1
+      MM_full(st, k_rdst);                                 // phase t + 1
       end_phase(true);
       t += 2;
-      st = s2;
+      const int sp = st;
+      st = s2; s2 = s1; s1 = sp;
+      k_rdst ^= flip_rd;
+      k_ldst ^= flip_ld;
     }
     if (t < nt) {                                          // this group's last tile
-      SM(st, 0, nxt(st), false, t + 1 < nt, false, 0, 0);
+      SM(st, 0, s1, false, t + 1 < nt, false, 0, -1);
       end_phase(false);
       MM_last(st);
       end_phase(true);
