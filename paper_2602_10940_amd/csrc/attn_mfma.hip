@@ -45,18 +45,19 @@ constexpr int kTile = 64;        // keys per LDS tile
 // group the 64-byte quarters (halves) of its rows follow one another, first all rows' first quarter, then all rows' second, ..:
 // the quarter of an operand is then an immediate offset, as its key block is, and all reads of a tensor share one address register
 // (V with kHalfD two).  Four consecutive lanes of a load still fetch 64 consecutive bytes, which is what the address unit counts.
-// Groups lie kPitch apart, a padding that puts the rows a read touches together into different banks (64 of 4 bytes):
-//   K: 16 lanes read 16 bytes of 16 rows, 4 groups apart by 16 bytes: row i of group q at bank 4 * (4 i + q) and up.
-//      kHalfD: 2 groups apart by 32; rows 4 to 7 of a group would meet rows 0 to 3 and have their 16-byte pieces swapped pairwise.
-//   V: 32 lanes read 32 bytes of 8 rows by the transposing read: two groups, apart by 32; kHalfD: one group, whose rows 4 to 7
-//      have the halves of their 64 bytes swapped.
+// What is left is that the rows a read touches together lie in different banks (64 of 4 bytes):
+//   K: a 16-byte read takes the lanes 0-3, 12-15, 20-27, then 4-11, 16-19, 28-31, then the same of the upper half (measured, lane
+//      against lane).  Rows r to r + 3 (r a multiple of 4) differ by 64 bytes; the 16-byte pieces of their 64 bytes are swapped by
+//      XOR with swap_k(r / 4), which gives each of those sets of (rows, piece) a place of its own.
+//   V: 32 lanes read 32 bytes of 8 rows by the transposing read: two groups, which lie 32 bytes more than 1 KB apart; kHalfD: one group,
+//      whose rows 4 to 7 have the halves of their 64 bytes swapped.
 // With rows of 256 bytes swizzled by XOR, as they were, K took 4 address registers and V 8, each a vector addition per phase, and
-// every load set m0 for itself: 24 heads of 4608 219.8 -> 217.8 us, FP8 ring of two chunks of 4096 under 24 heads 434 -> 426, ragged ring
-// of two chunks of 2215 under 12 heads 64.2 -> 62.6.
+// every load set m0 for itself.
 template <bool kHalfD>
 struct TileLayout {
   static constexpr int kGroup = kHalfD ? 8 : 4;                    // rows that one load moves
-  static constexpr int kPitchK = 1024 + (kHalfD ? 32 : 16), kPitchV = 1024 + (kHalfD ? 0 : 32);
+  static constexpr int kPitchK = 1024, kPitchV = 1024 + (kHalfD ? 0 : 32);   // from a group to the next
+  static __device__ __forceinline__ int swap_k(int four) { return ((four ^ (four >> 1)) & 1) << 1 | ((four >> 1) & 1); }   // 0 2 3 1
   static constexpr int kQuarter = kGroup * 64;                     // from a row's 64 bytes to its next
 };
 // Work-group -> (batch*head, query block) with the 8 XCDs of the chip in mind: consecutive
@@ -132,9 +133,12 @@ __device__ __forceinline__ RowFinish finish_row(const AttnStep& s, float m, floa
 //   split: waves w and w + 4 hold the same 32 queries over different keys.  Both stage, and behind a barrier wave w puts the
 //          two together for the first 16 queries, wave w + 4 for the others.
 // kHalfD: head dimension 64: only the first four 16-wide blocks exist, rows are 64 wide everywhere.
-constexpr int kEpiPitch = kD * 4 + 16;                    // bytes per staged row
 constexpr int kEpiInfoB = kQPerWave * 32 + 16 * 16;       // per row: m, four partial sums l, factor of O~ (split) or the row's weights (wide); split: the 16 rows' weights
-constexpr int kEpiWaveB = kQPerWave * kEpiPitch + kEpiInfoB;
+template <bool kHalfD>
+struct EpiLayout {
+  static constexpr int kPitch = (kHalfD ? 64 : kD) * 4 + 16;       // bytes per staged row
+  static constexpr int kWaveB = kQPerWave * kPitch + kEpiInfoB;
+};
 
 // Rows 0 .. rows - 1 of the wave's share, of them `valid` (may be <= 0) exist.  a, b: the staged rows (b of the other half of
 // the keys, split only); info: per row {weight of a, weight of b, scale, weight of the carry}.  kCarry: fold the carried O
@@ -143,7 +147,7 @@ template <bool kSplit, bool kHalfD, bool kCarry, bool kF32>
 __device__ __forceinline__ void store_rows(const unsigned char* a, const unsigned char* b, const f32x4* info, int lane, int valid,
                                            const float* carry, float* dst32, bf16_t* dst16, int64_t stride16) {
   constexpr int kLPR = kHalfD ? 8 : 16, kRPI = 64 / kLPR;           // lanes per row, rows per instruction
-  constexpr int kRows = kSplit ? 16 : kQPerWave, kRowF = kHalfD ? 64 : kD;
+  constexpr int kRows = kSplit ? 16 : kQPerWave, kRowF = kHalfD ? 64 : kD, kEpiPitch = EpiLayout<kHalfD>::kPitch;
   const int sub = lane / kLPR, c = lane % kLPR;
 #pragma unroll
   for (int it = 0; it < kRows / kRPI; ++it) {
@@ -184,7 +188,7 @@ __device__ __forceinline__ void store_rows(const unsigned char* a, const unsigne
 template <bool kSplit, bool kHalfD>
 __device__ __forceinline__ void finish_and_store(const AttnStep& s, f32x4 (&oacc)[8][2], const float (&m)[2], const float (&lsum)[2], const float (&lratio)[2],
                                                  int b, int h, int q0, int wave, int lane, unsigned char* smem, bool invalid, int part) {
-  constexpr int kDB = kHalfD ? 4 : 8, kRowF = kHalfD ? 64 : kD;
+  constexpr int kDB = kHalfD ? 4 : 8, kRowF = kHalfD ? 64 : kD, kEpiPitch = EpiLayout<kHalfD>::kPitch, kEpiWaveB = EpiLayout<kHalfD>::kWaveB;
   const int r = lane & 15, g = lane >> 4;
   const int64_t row0 = ((int64_t)b * s.H + h) * s.Sq;     // first row of this (batch, head) in lse / acc
   unsigned char* epi = smem + wave * kEpiWaveB;
@@ -355,17 +359,22 @@ __device__ __forceinline__ void wait_loads() {
 }
 constexpr int kStages = 3, kStagesSplitK = 4;   // LDS tile buffers per tensor; of K in the key-split form
 constexpr int kExtTileB = kTile * 4;   // bytes of one tile's record: the factors of its 64 keys
-constexpr int kStageB = 16 * TileLayout<false>::kPitchV + kExtTileB;   // a stage of either tensor, with room for a record
-constexpr int kQRowsB = 8 * TileLayout<false>::kPitchK;                // 32 rows of Q, laid out as K is
 
-// LDS of a work-group: K stages | V stages | four records | the words of kDead launches (188 000 keys).  The
-// wide work-groups' epilogue stages each wave's O tile (eight regions from offset 0, over everything else,
-// which is dead by then).
-constexpr int kExtOff = (kStagesSplitK + kStages) * kStageB;
-constexpr int kWordsOff = kExtOff + 4 * kExtTileB;
-constexpr int kLdsBytes = 8 * kEpiWaveB;
+// LDS of a work-group: K stages | V stages (each with room for a record) | four records | the words of kDead launches (188 000 keys).
+// The epilogue stages each wave's O tile (eight regions from offset 0, over everything else, which is dead by then).
 constexpr int kMaxWords = 2944;
-static_assert(kWordsOff % 8 == 0 && kWordsOff + kMaxWords * 8 <= kLdsBytes && kLdsBytes <= 159 * 1024, "LDS plan");   // (some is left to __syncthreads_or)
+template <bool kHalfD>
+struct LdsPlan {
+  typedef TileLayout<kHalfD> L;
+  static constexpr int kTileB = kTile / L::kGroup * (L::kPitchK > L::kPitchV ? L::kPitchK : L::kPitchV);
+  static constexpr int kStageB = kTileB + kExtTileB;
+  static constexpr int kQRowsB = kQPerWave / L::kGroup * L::kPitchK;     // 32 rows of Q, laid out as K is
+  static constexpr int kExtOff = (kStagesSplitK + kStages) * kStageB;
+  static constexpr int kWordsOff = kExtOff + 4 * kExtTileB;
+  static constexpr int kEpilogueB = 8 * EpiLayout<kHalfD>::kWaveB;
+  static constexpr int bytes(int words) { return kEpilogueB > kWordsOff + 8 * words ? kEpilogueB : kWordsOff + 8 * words; }
+  static_assert(2 * kQRowsB <= kTileB && kWordsOff % 8 == 0 && bytes(kMaxWords) <= 159 * 1024, "LDS plan");   // (some is left to __syncthreads_or)
+};
 
 // LDS transposing read: the 16 lanes of a group each name 8 bytes; seen as a 4 x 16 matrix of
 // bf16 (row i = the data of lanes 4i..4i+3), lane j of the group receives column j.
@@ -433,6 +442,11 @@ __device__ __forceinline__ uint64_t live_keys(const uint8_t* mask, int Sc, int t
   return __builtin_amdgcn_ballot_w64(live);
 }
 
+// The key-split forms of head dimension 64 fit 128 vector registers and half of the LDS: two work-groups to a CU, four waves
+// to a SIMD, where the softmax phases, the longer ones there, overlap with one another.  (24 heads of 4608: 166.8 us with one
+// work-group a CU, 141.5 with two; 256-query work-groups 157.)  Not FP8 chunks with dead keys or in one launch over a ring, whose factors
+// would have to be read from LDS when they are needed (ring of eight of 2112 under 12 heads 170 -> 190 us).
+constexpr bool four_waves(bool split, bool ext, bool multi, bool dead, bool half_d) { return split && half_d && !(ext && (multi || dead)); }
 // One work-group's share: the queries q_base .. q_base + 255 (wide) or + 127 (split) of (batch, head) bh_.
 // kHalfD: head dimension 64: rows of Q, K, V and O are 128 bytes (K and V are read in place, their LDS
 // tiles have 128-byte rows with swizzles of their own), the scores contract over two 32-wide slices
@@ -452,12 +466,17 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
   const int q0 = q_base + (kSplit ? (wave & 3) : wave) * kQPerWave;
   const bool grpA = wave < 4;
 
+  constexpr bool kFour = four_waves(kSplit, kExt, kMulti, kDead, kHalfD);
   typedef TileLayout<kHalfD> Layout;
+  typedef LdsPlan<kHalfD> Lds;
+  constexpr int kStageB = Lds::kStageB, kQRowsB = Lds::kQRowsB;
   constexpr int RB = kHalfD ? 128 : 256;     // bytes per row of Q, K and V
   const uint32_t lds_base = (uint32_t)(uintptr_t)smem_raw;
   // this lane's row of a group that a load moves, and its byte in that row (K and Q, V)
   const int dma_i = (lane >> 2) & (Layout::kGroup - 1), dma_q = kHalfD ? lane >> 5 : lane >> 4;
-  const uint32_t dma_k = (uint32_t)(64 * dma_q + 16 * ((lane & 3) ^ (kHalfD ? dma_i >> 2 : 0)));
+  auto dma_k = [&](int group) -> uint32_t {   // (of the tile)
+    return (uint32_t)(64 * dma_q + 16 * ((lane & 3) ^ Layout::swap_k(kHalfD ? 2 * group + (dma_i >> 2) : group)));
+  };
   const uint32_t dma_v = (uint32_t)(64 * dma_q + 16 * ((lane & 3) ^ (kHalfD ? dma_i >> 2 << 1 : 0)));
   // ---- Q first, the longest way to the first score.  Its operand layout (16 rows x 64 bytes an instruction) would take the
   // CU's one address unit 64 cycles a load, 4000 for a work-group, so it is moved to LDS as K is and the operands are
@@ -472,7 +491,7 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
     const int first = kSplit && !grpA ? kGroups : 0;
 #pragma unroll
     for (int t = 0; t < kGroups; ++t)
-      lds_dma16_lanes((const unsigned char*)(qb + (int64_t)min(q0 + (first + t) * Layout::kGroup + dma_i, s.Sq - 1) * s.qs[2]) + dma_k,
+      lds_dma16_lanes((const unsigned char*)(qb + (int64_t)min(q0 + (first + t) * Layout::kGroup + dma_i, s.Sq - 1) * s.qs[2]) + dma_k(first + t),
                       __builtin_amdgcn_readfirstlane(q_lds + (first + t) * Layout::kPitchK));
   }
   const unsigned char* kb = (const unsigned char*)((const bf16_t*)s.k + b * s.ks[0] + h * s.ks[1]);
@@ -485,7 +504,7 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
   const bool masked = s.any_mask != 0;
   int nt = nt_all;
   typedef const __attribute__((address_space(3))) uint64_t* lds_words;
-  const lds_words words = (lds_words)(uintptr_t)((uint32_t)(uintptr_t)smem_raw + kWordsOff);
+  const lds_words words = (lds_words)(uintptr_t)((uint32_t)(uintptr_t)smem_raw + Lds::kWordsOff);
   const bool in_lds = kMulti || nt_all <= kMaxWords;   // (the host keeps several chunks below that)
   // the word of tile t where the words have no room in LDS
   auto word_from_memory = [&](int t) -> uint64_t {
@@ -585,7 +604,7 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
 #pragma unroll
   for (int j = 0; j < kLoads; ++j) {
     const uint32_t row = (uint32_t)(dma_row + j * Layout::kGroup + dma_i) * rowB + kBias;
-    k_off[j] = row + dma_k - j * Layout::kPitchK;
+    k_off[j] = row + dma_k(dma_row / Layout::kGroup + j) - j * Layout::kPitchK;
     v_off[j] = row + dma_v - j * Layout::kPitchV;
   }
   const uint32_t lds_k = __builtin_amdgcn_readfirstlane(lds_base + dma_row / Layout::kGroup * Layout::kPitchK);
@@ -647,7 +666,7 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
   // kExt: the record of a tile, one load by the first wave of the loading group.  kMulti: it is written by the copy work-groups
   // together with its chunk, which await_record waits for where the K stream has not.  Records lie behind the V tiles (split) or,
   // four of them, behind all stages.
-  const uint32_t lds_ext = lds_base + (kSplit ? kStagesK * kStageB + kStageB - kExtTileB : kExtOff);
+  const uint32_t lds_ext = lds_base + (kSplit ? kStagesK * kStageB + Lds::kTileB : Lds::kExtOff);
   uint64_t xpre = kExt ? (uint64_t)(uintptr_t)s.ext + ((int64_t)bh_ * nt_all + t_beg) * kExtTileB : 0;   // the record loaded next
   auto await_record = [&](int idx) {
     int c = 0;
@@ -660,7 +679,10 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
     }
   };
   auto issue_ext = [&](int stage) {
-    if ((wave & 3) == 0) lds_dma4((const void*)(uintptr_t)xpre, lane * 4, lds_ext + stage);
+    if ((wave & 3) != 0) return;
+    uint32_t l4 = lane * 4;
+    if (kFour) asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0\n\tv_lshlrev_b32 %0, 2, %0" : "=v"(l4));   // (counted here, not kept)
+    lds_dma4((const void*)(uintptr_t)xpre, l4, lds_ext + stage);
   };
 
   // Tiles needed before the first loads of the softmax phases land are fetched here.
@@ -734,14 +756,13 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
 
   // per-lane LDS read addresses (see TileLayout): stage, head-dim slice and key block are added to these, the latter two as immediates
   typedef const __attribute__((address_space(3))) unsigned char* lds_cptr;
-  lds_cptr k_rd, v_rd[2];                       // K: row r, dims 8*g .. +7; V: by db & 1
+  lds_cptr k_rd, v_rd;                          // K: row r, dims 8*g .. +7; V
   {
     const int kr = r & (Layout::kGroup - 1);
-    k_rd = (lds_cptr)(uintptr_t)(lds_base + r / Layout::kGroup * Layout::kPitchK + kr * 64 + ((g ^ (kHalfD ? kr >> 2 : 0)) << 4));
+    k_rd = (lds_cptr)(uintptr_t)(lds_base + r / Layout::kGroup * Layout::kPitchK + kr * 64 + ((g ^ Layout::swap_k(r >> 2)) << 4));
     const int vrow = 4 * g + (r >> 2), vr = vrow & (Layout::kGroup - 1);   // the key this lane names in a transposing read (plus 32*kk, plus 16)
     const uint32_t v0 = lds_base + kStagesK * kStageB + vrow / Layout::kGroup * Layout::kPitchV + vr * 64 + 8 * (r & 3);
-    v_rd[0] = (lds_cptr)(uintptr_t)(v0 + (kHalfD ? (vr >> 2) * 32 : 0));
-    v_rd[1] = (lds_cptr)(uintptr_t)(v0 + (kHalfD ? (1 - (vr >> 2)) * 32 : 32));
+    v_rd = (lds_cptr)(uintptr_t)(v0 + (kHalfD ? (vr >> 2) * 32 : 0));
   }
   // kExt: this lane's keys of a tile are rows 16*mb + 4*g + (0..3), mb = 0..3
   const lds_cptr x_rd = (lds_cptr)(uintptr_t)(lds_ext + 16 * g);
@@ -754,7 +775,8 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
     return *reinterpret_cast<const __attribute__((address_space(3))) bf16x8*>(k_rd + stage + 16 / Layout::kGroup * mb * Layout::kPitchK + ks * Layout::kQuarter);
   };
   auto v_operand = [&](int stage, int kk, int db) -> bf16x8 {
-    const lds_cptr p = (kHalfD ? v_rd[db & 1] : v_rd[0] + 32 * (db & 1)) + stage + (db >> 1) * Layout::kQuarter;
+    // (kHalfD: the other 32 bytes of the lane's 64, whichever they are)
+    const lds_cptr q = v_rd + stage, p = (kHalfD && (db & 1) ? (lds_cptr)(uintptr_t)((uint32_t)(uintptr_t)q ^ 32) : q + (kHalfD ? 0 : 32 * (db & 1))) + (db >> 1) * Layout::kQuarter;
     const u32x2 lo = lds_read_tr3(p + 32 / Layout::kGroup * kk * Layout::kPitchV);
     const u32x2 hi = lds_read_tr3(p + (32 * kk + 16) / Layout::kGroup * Layout::kPitchV);
     return __builtin_bit_cast(bf16x8, u32x4{lo[0], lo[1], hi[0], hi[1]});
@@ -862,7 +884,8 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
           psum = kk == 0 && a == 0 && e == 0 ? p[0] : psum + p[4 * a + e];
         }
     } else {
-      if (fetch_ahead && kk == 0 && nb == 1) x_load(1, xs);   // blocks run in the order (0,0) (0,1) (1,0) (1,1)
+      // blocks run in the order (0,0) (0,1) (1,0) (1,1)
+      if (fetch_ahead && kk == 0 && nb == (kFour ? 0 : 1)) x_load(1, xs);
 #pragma unroll
       for (int a = 0; a < 2; ++a) {
 #pragma unroll
@@ -875,10 +898,11 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
 #pragma unroll
     for (int j = 0; j < 4; ++j) pk[kk][nb][j] = pack_bf16x2(p[2 * j], p[2 * j + 1]);
     // anchor the block here, between the tile loads that surround it in program order
-    asm volatile("" : "+v"(pk[kk][nb]));
+    if (kFour) asm volatile("" : "+v"(pk[kk][nb]), "+v"(psum));   // (with its sum: summed later, all of the block's terms would stay in registers)
+    else asm volatile("" : "+v"(pk[kk][nb]));
   };
   // largest exponent argument (before the reference is subtracted) of each of this lane's two queries over the tile
-  auto tile_max = [&](int xs, float (&tmax)[2]) {
+  auto tile_max = [&](int xs, float (&tmax)[2], bool do0 = true, bool do1 = true) {
     tmax[0] = tmax[1] = -INFINITY;
     if (!kExt) {
 #pragma unroll
@@ -897,10 +921,11 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
 #pragma unroll
       for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) tmax[nb] = fmaxf(tmax[nb], sacc[mb][nb][e] * c[e]);
+        for (int e = 0; e < 4; ++e)
+          if (nb ? do1 : do0) tmax[nb] = fmaxf(tmax[nb], sacc[mb][nb][e] * c[e]);
     }
-    tmax[0] = xgroup_max(tmax[0]);
-    tmax[1] = xgroup_max(tmax[1]);
+    if (do0) tmax[0] = xgroup_max(tmax[0]);
+    if (do1) tmax[1] = xgroup_max(tmax[1]);
   };
   // O~ and l of query block nb, for a reference that moves on.  (2^-126, the least factor that is not 0, takes what was summed
   // under a reference that lagged by 2^60 to 2^-34 of the 2^-32 that the new largest weight has.)
@@ -928,6 +953,40 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
   int sm_tile = t_beg + (kSplit && !grpA ? 1 : 0);   // kDead: tile of this wave's next softmax phase
   int next_dead = 0;                         // kDead: the next tile with a dead key, as far as it has been looked up
   typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  // (kFarOff: what ordinary scores never reach lies outside the loop over the tiles.  FP8 ring of three chunks of 1152 keys,
+  // 12 heads, d = 64, 45.8 -> 43.8 us; in the 256-query form, which has no register to spare, that spills, and the mixed
+  // launch, which holds both, takes 447 us instead of 435 on 24 heads of 4096 queries, FP8 ring of two with outliers.)
+  constexpr bool kFarOff = kSplit && kMulti;
+  // The exponentials of the query blocks do0, do1 (constants) again if one of their lanes failed (fail0, fail1).
+  // had: some lane has had a reference before this tile
+  auto redo = [&](bool do0, bool do1, uint64_t fail0, uint64_t fail1, uint64_t had, int xs, float (&psum)[2]) {
+    if (!heavy && had != 0ull) {
+      heavy = true;
+      lhat[0] = lsum[0];
+      lhat[1] = lsum[1];
+    }
+    float tmax[2];
+    tile_max(xs, tmax, do0, do1);
+    if (kExt) { x_load(0, xs); x_load(1, xs); }
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb) {
+      if (!(nb ? do1 : do0) || (nb ? fail1 : fail0) == 0ull) continue;
+      const float m_new = tmax[nb] > m[nb] ? tmax[nb] + kRefMargin : m[nb];
+      // m = -inf (first live tile) gives the factor 0; no live key so far: nothing to rescale, P = 0
+      rescale(nb, m_new == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f(m[nb] - m_new));
+      m[nb] = m_new;
+      psum[nb] = 0.0f;
+      if ((kExt || kDead) && m_new == -INFINITY) {
+        pk[0][nb] = u32x4{0u, 0u, 0u, 0u};
+        pk[1][nb] = u32x4{0u, 0u, 0u, 0u};
+      } else {
+        exp_block(0, nb, psum[nb], xs, false);
+        exp_block(1, nb, psum[nb], xs, false);
+      }
+    }
+  };
+  auto failed = [&](float sum) -> uint64_t { return __builtin_amdgcn_ballot_w64(!(sum <= kCertifiedSum)); };
+  auto has_reference = [&]() -> uint64_t { return __builtin_amdgcn_ballot_w64(m[0] != -INFINITY || m[1] != -INFINITY); };
   // SM of the tile whose record sits in stage xs; loads the next K tile into stage sk (if do_k), its record, or with idx >= 0 that of
   // tile idx alone, into stage xst (if do_x), and the next V tile into stage sv (if do_v)
   auto SM = [&](int xs, int sk, int sv, bool do_k, bool do_v, bool do_x, int xst, int idx) {
@@ -957,62 +1016,61 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
     }
     // sched_barrier: keep each load between two blocks of arithmetic (the scheduler would
     // otherwise hoist all of them to the top, where they queue behind one another)
-    if (do_v) issue_v(vpre, vpre_bytes, sv, 0);
-    exp_block(0, 0, psum[0], xs, true);
-    __builtin_amdgcn_sched_barrier(0);
-    if (do_v && kLoads > 2) issue_v(vpre, vpre_bytes, sv, 2);
-    exp_block(0, 1, psum[1], xs, true);
-    __builtin_amdgcn_sched_barrier(0);
-    if (do_k) {
+    auto load_k = [&]() {
+      if (!do_k) return;
       if (kMulti && pre.left <= left_look) look_up();
       if (kDead) vpre_bytes = tile_bytes(pre.left);
       issue_k(pre.k, vpre_bytes, sk, 0);
-    }
-    exp_block(1, 0, psum[0], xs, true);
-    __builtin_amdgcn_sched_barrier(0);
-    if (do_k && kLoads > 2) issue_k(pre.k, vpre_bytes, sk, 2);
-    if (kExt && do_x) {
+    };
+    auto load_record = [&]() {
+      if (!kExt || !do_x) return;
       if (kMulti && idx >= 0) await_record(idx);
       issue_ext(xst);
+    };
+    if (do_v) issue_v(vpre, vpre_bytes, sv, 0);
+    if (kFour && kExt) {
+      // one query block after the other: the first one's scores are done with when the second one's exponentials begin
+      exp_block(0, 0, psum[0], xs, true);
+      __builtin_amdgcn_sched_barrier(0);
+      load_k();
+      exp_block(1, 0, psum[0], xs, false);
+      __builtin_amdgcn_sched_barrier(0);
+      const uint64_t fail0 = failed(psum[0]);
+      uint64_t had = 0ull;
+      if (__builtin_expect(fail0 != 0ull, 0)) {
+        had = has_reference();
+        redo(true, false, fail0, 0ull, had, xs, psum);
+      }
+      load_record();
+      exp_block(0, 1, psum[1], xs, false);
+      __builtin_amdgcn_sched_barrier(0);
+      exp_block(1, 1, psum[1], xs, false);
+      __builtin_amdgcn_sched_barrier(0);
+      const uint64_t fail1 = failed(psum[1]);
+      if (__builtin_expect(fail1 != 0ull, 0)) redo(false, true, 0ull, fail1, fail0 != 0ull ? had : has_reference(), xs, psum);
+    } else {
+      exp_block(0, 0, psum[0], xs, true);
+      __builtin_amdgcn_sched_barrier(0);
+      if (do_v && kLoads > 2) issue_v(vpre, vpre_bytes, sv, 2);
+      exp_block(0, 1, psum[1], xs, true);
+      __builtin_amdgcn_sched_barrier(0);
+      load_k();
+      exp_block(1, 0, psum[0], xs, true);
+      __builtin_amdgcn_sched_barrier(0);
+      if (do_k && kLoads > 2) issue_k(pre.k, vpre_bytes, sk, 2);
+      load_record();
+      exp_block(1, 1, psum[1], xs, true);
+      __builtin_amdgcn_sched_barrier(0);
     }
-    exp_block(1, 1, psum[1], xs, true);
-    __builtin_amdgcn_sched_barrier(0);
     pre.k += pre_step;
     if (kMulti || kDead) pre.left -= kPreStep * kTile;
     vpre += pre_step;
     if (kExt) xpre += kPreStep * kExtTileB;
     // (per query block: a block all of whose lanes passed keeps its exponentials and its reference)
-    const uint64_t redo0 = __builtin_amdgcn_ballot_w64(!(psum[0] <= kCertifiedSum));
-    const uint64_t redo1 = __builtin_amdgcn_ballot_w64(!(psum[1] <= kCertifiedSum));
-    // (kFarOff: what ordinary scores never reach lies outside the loop over the tiles.  FP8 ring of three chunks of 1152 keys,
-    // 12 heads, d = 64, 45.8 -> 43.8 us; in the 256-query form, which has no register to spare, that spills, and the mixed
-    // launch, which holds both, takes 447 us instead of 435 on 24 heads of 4096 queries, FP8 ring of two with outliers.)
-    constexpr bool kFarOff = kSplit && kMulti;
-    if (kFarOff ? __builtin_expect((redo0 | redo1) != 0ull, 0) : (redo0 | redo1) != 0ull) {
-      if (!heavy && __builtin_amdgcn_ballot_w64(m[0] != -INFINITY || m[1] != -INFINITY) != 0ull) {
-        heavy = true;
-        lhat[0] = lsum[0];
-        lhat[1] = lsum[1];
-      }
-      float tmax[2];
-      tile_max(xs, tmax);
-      if (kExt) { x_load(0, xs); x_load(1, xs); }
-#pragma unroll
-      for (int nb = 0; nb < 2; ++nb) {
-        if ((nb ? redo1 : redo0) == 0ull) continue;
-        const float m_new = tmax[nb] > m[nb] ? tmax[nb] + kRefMargin : m[nb];
-        // m = -inf (first live tile) gives the factor 0; no live key so far: nothing to rescale, P = 0
-        rescale(nb, m_new == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f(m[nb] - m_new));
-        m[nb] = m_new;
-        psum[nb] = 0.0f;
-        if ((kExt || kDead) && m_new == -INFINITY) {
-          pk[0][nb] = u32x4{0u, 0u, 0u, 0u};
-          pk[1][nb] = u32x4{0u, 0u, 0u, 0u};
-        } else {
-          exp_block(0, nb, psum[nb], xs, false);
-          exp_block(1, nb, psum[nb], xs, false);
-        }
-      }
+    if (!(kFour && kExt)) {
+      const uint64_t fail0 = failed(psum[0]), fail1 = failed(psum[1]);
+      if (kFarOff ? __builtin_expect((fail0 | fail1) != 0ull, 0) : (fail0 | fail1) != 0ull)
+        redo(true, true, fail0, fail1, heavy ? 0ull : has_reference(), xs, psum);
     }
     lsum[0] += psum[0];
     lsum[1] += psum[1];
@@ -1245,7 +1303,7 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
 }
 
 template <bool kSplit, bool kExt, bool kMulti, bool kDead, bool kHalfD>
-__global__ __launch_bounds__(kThreads, 2) void attn_pp_kernel(AttnStep s) {
+__global__ __launch_bounds__(kThreads, four_waves(kSplit, kExt, kMulti, kDead, kHalfD) ? 4 : 2) void attn_pp_kernel(AttnStep s) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   touch_step();
   if (!kMulti && (int)blockIdx.x >= s.grid_wgs) {   // prefetch work-group: copy and leave
@@ -1373,8 +1431,9 @@ usp_status launch_attn_arrive_set(uint64_t* arrive, uint64_t tag, hipStream_t st
 namespace {
 template <bool kSplit, bool kExt, bool kMulti, bool kDead, bool kHalfD>
 usp_status launch_pp(const AttnStep& s, unsigned wgs, hipStream_t st) {
-  constexpr int lds = kLdsBytes;
-  USP_CHECK_HIP((allow_large_lds<attn_pp_kernel<kSplit, kExt, kMulti, kDead, kHalfD>>(lds)));
+  typedef LdsPlan<kHalfD> Lds;
+  const int lds = Lds::bytes(kDead && s.tiles <= kMaxWords ? s.tiles : 0);
+  USP_CHECK_HIP((allow_large_lds<attn_pp_kernel<kSplit, kExt, kMulti, kDead, kHalfD>>(Lds::bytes(kMaxWords))));
   hipLaunchKernelGGL((attn_pp_kernel<kSplit, kExt, kMulti, kDead, kHalfD>), dim3(wgs + s.copy_wgs), dim3(kThreads), lds, st, s);
   USP_CHECK_HIP(hipGetLastError());
   return USP_OK;
@@ -1388,6 +1447,19 @@ template <bool kMulti>
 usp_status launch_pp_any(const AttnStep& s, bool ext, bool dead, bool split, unsigned wgs, hipStream_t st) {
   if (ext) return dead ? launch_pp_form<true, kMulti, true>(s, split, wgs, st) : launch_pp_form<true, kMulti, false>(s, split, wgs, st);
   return dead ? launch_pp_form<false, kMulti, true>(s, split, wgs, st) : launch_pp_form<false, kMulti, false>(s, split, wgs, st);
+}
+// A launch over one chunk (or step) of head dimension 64, four waves to a SIMD (four_waves): key-split or 256-query work-groups.  In
+// microseconds, over `tiles` of keys: 256-query work-groups, one to a CU, 6.1 + 1.04 each round; key-split ones 7.8 + 0.88 for two
+// on a CU, 5.6 + 0.53 for one; from FP8 6.5 + 1.06, 9.5 + 0.96 and 6.6 + 0.6.  256-query, key-split: 308 blocks of 128, 128 keys 8.3, 10.1;
+// 380, 448 keys 12.1, 12.6; 270, 1408 keys 27.5, 25.2; 540, 1728 keys 62.9, 44.1; 864, 4608 keys 157, 141; from FP8 270, 1408 keys 32.0,
+// 31.6; 540, 1728 keys 67.3, 53.0.
+bool narrow_takes_split(int64_t blocks, int64_t halves, int tiles, bool ext) {
+  const int64_t rounds = (blocks + 255) / 256, per_cu = (halves + 255) / 256;
+  if (per_cu <= 1) return true;
+  const double n = tiles;
+  const double wide = (double)rounds * (ext ? 6.5 + 1.06 * n : 6.1 + 1.04 * n);
+  const double pair = ext ? 9.5 + 0.96 * n : 7.8 + 0.88 * n, one = ext ? 6.6 + 0.6 * n : 5.6 + 0.53 * n;
+  return (double)(per_cu / 2) * pair + (per_cu % 2 ? one : 0.0) < wide;
 }
 usp_status launch_combine(const AttnStep& s, hipStream_t st) {
   const uint32_t rows = (uint32_t)((int64_t)s.B * s.H * s.Sq), per = 1024 / (uint32_t)s.d;
@@ -1404,7 +1476,7 @@ usp_status launch_combine(const AttnStep& s, hipStream_t st) {
 }
 template <bool kExt, bool kDead>
 usp_status launch_mixed(const AttnStep& s, unsigned wgs, hipStream_t st) {
-  constexpr int lds = kLdsBytes;
+  constexpr int lds = LdsPlan<false>::bytes(kMaxWords);
   USP_CHECK_HIP((allow_large_lds<attn_pp_mixed_kernel<kExt, kDead>>(lds)));
   hipLaunchKernelGGL((attn_pp_mixed_kernel<kExt, kDead>), dim3(wgs + s.copy_wgs), dim3(kThreads), lds, st, s);
   USP_CHECK_HIP(hipGetLastError());
@@ -1594,7 +1666,9 @@ usp_status launch_attn_mfma(const AttnStep& step, hipStream_t st) {
   // Few query blocks (a small Q shard of a ring step): 256-query work-groups would leave CUs idle;
   // 128-query work-groups whose two wave groups split the keys fill twice as many.
   const unsigned wgs256 = wg_grid_size((s.Sq + kQPerWG - 1) / kQPerWG, s.B * s.H);
-  const bool split = s.variant == 2 || (s.variant == 0 && (int)wgs256 <= kSplitBelowWGs);
+  const bool narrow_split = s.half_d && four_waves(true, ext, false, dead, true) &&
+                            narrow_takes_split((int64_t)s.B * s.H * ((s.Sq + kQPerWG - 1) / kQPerWG), (int64_t)s.B * s.H * ((s.Sq + kQPerWGSplit - 1) / kQPerWGSplit), s.tiles, ext);
+  const bool split = s.variant == 2 || (s.variant == 0 && ((int)wgs256 <= kSplitBelowWGs || narrow_split));
   if (ext && s.ext == nullptr) {
     set_error("attention step with FP8 scales needs its per-tile records");
     return USP_ERR_INVALID_ARG;

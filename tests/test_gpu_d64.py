@@ -97,3 +97,41 @@ def test_fp8_kv_d64_ring_against_oracle(lens, flags):
     torch.cuda.synchronize()
     ro, rl = orc.ring_attention(inp.q, kx, vx, float(inp.softmax_scale), inp.key_mask)
     _assert_parity(host_f64(o), host_f64(l), ro, rl)
+
+
+@pytest.mark.parametrize("H,Sq,keys,masked,fp8,split", [
+    (26, 1300, 640, (0, 0), False, False),     # 286 blocks of 128, two to a CU: ten tiles are too few
+    (26, 1300, 769, (0, 0), False, True),      # thirteen, the last one ragged
+    (26, 1300, 768, (100, 300), False, True),  # dead tiles in the middle
+    (64, 1024, 64, (0, 0), False, False),      # 512 blocks, one tile
+    (27, 2400, 128, (0, 0), False, True),      # 513: the third work-group of a CU has it alone
+    (26, 1300, 1024, (0, 0), True, False),     # from FP8 the line lies higher
+    (27, 2400, 448, (0, 0), True, True),
+    (27, 2400, 449, (0, 0), True, False),      # FP8 with dead keys: one work-group to a CU, the rule it had
+])
+def test_d64_two_work_groups_to_a_cu(H, Sq, keys, masked, fp8, split):
+    """The form that the rule picks over one chunk, as its flag gives it, against the oracle."""
+    import paper_2602_10940_amd as P
+    inp = W.make_attention_inputs(W.Workload("d64_two", 95, 1, H, 64, Sq, (keys,), "bf16", masked_keys=masked))
+    q, k, v = dev_bf16(inp.q), dev_bf16(inp.k[0]), dev_bf16(inp.v[0])
+    kw = {}
+    kx, vx = inp.k[0], inp.v[0]
+    if fp8:
+        (a, sa), (b, sb) = (P.usp_fp8_quant(x.reshape(H * keys, 64)) for x in (k, v))
+        kx, vx = (orc.dequant_exact_f64(c.cpu().numpy().reshape(1, H, keys, 64), s.cpu().numpy().reshape(1, H, keys)) for c, s in ((a, sa), (b, sb)))
+        k, v = a.reshape(1, H, keys, 64), b.reshape(1, H, keys, 64)
+        kw = {"k_scales": [sa.reshape(1, H, keys)], "v_scales": [sb.reshape(1, H, keys)]}
+    if masked[1]:
+        kw["key_mask"] = [torch.from_numpy(inp.key_mask[0]).to(DEV)]
+    scale = float(inp.softmax_scale)
+    o, l = P.usp_ring_attn_fwd(q, [k], [v], softmax_scale=scale, **kw)
+    os_, ls = P.usp_ring_attn_fwd(q, [k], [v], softmax_scale=scale, flags=P.USP_ATTN_KERNEL_SPLIT, **kw)
+    ow, lw = P.usp_ring_attn_fwd(q, [k], [v], softmax_scale=scale, flags=P.USP_ATTN_KERNEL_WIDE, **kw)
+    torch.cuda.synchronize()
+    same, other = ((os_, ls), ow) if split else ((ow, lw), os_)
+    assert torch.equal(o, same[0]) and torch.equal(l, same[1])
+    assert keys == 64 or not torch.equal(o, other)      # (one tile: there is nothing to divide)
+    heads = [0, H - 1]
+    ro, rl = orc.ring_attention(inp.q[:, heads], [kx[:, heads]], [vx[:, heads]], scale, inp.key_mask if masked[1] else None)
+    for x, y in ((o, l), (os_, ls), (ow, lw)):
+        _assert_parity(host_f64(x[:, heads]), host_f64(y[:, heads]), ro, rl)
