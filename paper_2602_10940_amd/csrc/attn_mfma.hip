@@ -648,36 +648,28 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
   // loads j and j + 1 (kHalfD, wide: the one) of a wave's share of a tile, to the stage that begins `stage` bytes behind the first
   constexpr int kPair = kLoads < 2 ? 0 : 1;
   auto issue_k = [&](uint64_t p, uint32_t bytes, int stage, int j) {
-    if (kDead) lds_dma16_pair_bounded<Layout::kPitchK, kPair>(u32x4{(uint32_t)p, (uint32_t)(p >> 32) & 0xffffu, bytes, 0x00020000u}, k_off[j], k_off[j + kPair], lds_k + stage, j);
+    if (kDead)
+      lds_dma16_pair_bounded<Layout::kPitchK, kPair>(u32x4{(uint32_t)p, (uint32_t)(p >> 32) & 0xffffu, bytes, 0x00020000u}, k_off[j], k_off[j + kPair], lds_k + stage, j);
     else lds_dma16_pair<Layout::kPitchK, kPair>((const void*)(uintptr_t)p, k_off[j], k_off[j + kPair], lds_k + stage, j);
   };
   auto issue_v = [&](uint64_t p, uint32_t bytes, int stage, int j) {
-    if (kDead) lds_dma16_pair_bounded<Layout::kPitchV, kPair>(u32x4{(uint32_t)p, (uint32_t)(p >> 32) & 0xffffu, bytes, 0x00020000u}, v_off[j], v_off[j + kPair], lds_v + stage, j);
+    if (kDead)
+      lds_dma16_pair_bounded<Layout::kPitchV, kPair>(u32x4{(uint32_t)p, (uint32_t)(p >> 32) & 0xffffu, bytes, 0x00020000u}, v_off[j], v_off[j + kPair], lds_v + stage, j);
     else lds_dma16_pair<Layout::kPitchV, kPair>((const void*)(uintptr_t)p, v_off[j], v_off[j + kPair], lds_v + stage, j);
   };
   auto issue_k_tile = [&](const Place& p, int stage) {   // this wave's share
 #pragma unroll
-    for (int j = 0; j < kLoads; j += 2) issue_k(p.k, tile_bytes(p.left), stage * kStageB, j);
+    for (int j = 0; j < kLoads; j += 2) issue_k(p.k, kDead ? tile_bytes(p.left) : 0, stage * kStageB, j);
   };
   auto issue_v_tile = [&](const Place& p, int stage) {
 #pragma unroll
-    for (int j = 0; j < kLoads; j += 2) issue_v(p.v, tile_bytes(p.left), stage * kStageB, j);
+    for (int j = 0; j < kLoads; j += 2) issue_v(p.v, kDead ? tile_bytes(p.left) : 0, stage * kStageB, j);
   };
-  // kExt: the record of a tile, one load by the first wave of the loading group.  kMulti: it is written by the copy work-groups
-  // together with its chunk, which await_record waits for where the K stream has not.  Records lie behind the V tiles (split) or,
-  // four of them, behind all stages.
-  const uint32_t lds_ext = lds_base + (kSplit ? kStagesK * kStageB + Lds::kTileB : Lds::kExtOff);
+  // kExt: the record of a tile, one load by the first wave of the loading group, together with its K tile (kMulti: whose place says
+  // that the chunk has arrived, which the copy work-groups write it with).  Records lie behind the K tiles (split) or, four of
+  // them, behind all stages.
+  const uint32_t lds_ext = lds_base + (kSplit ? Lds::kTileB : Lds::kExtOff);
   uint64_t xpre = kExt ? (uint64_t)(uintptr_t)s.ext + ((int64_t)bh_ * nt_all + t_beg) * kExtTileB : 0;   // the record loaded next
-  auto await_record = [&](int idx) {
-    int c = 0;
-    for (int end = tiles_of(s.chunk[0].Sc); t_beg + idx >= end;) {
-      end += tiles_of(s.chunk[++c].Sc);
-      if (c > arrived_upto) {
-        if (!wait_arrival<!kExt>(s, c)) late = true;
-        arrived_upto = c;
-      }
-    }
-  };
   auto issue_ext = [&](int stage) {
     if ((wave & 3) != 0) return;
     uint32_t l4 = lane * 4;
@@ -688,33 +680,44 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
   // Tiles needed before the first loads of the softmax phases land are fetched here.
   //   wide : A's SM(j) prefetches K(j+2) (with its record) and V(j+1); B's SM(j), one phase later,
   //          K(j+3) and V(j+2).
-  //   split: the softmax phase p prefetches K(p+3), V(p+1) and the record of tile p+2.
+  //   split: the softmax phase p prefetches K(p+3) with its record and V(p+1).
   // next K / V tile this wave prefetches; split: K(p+3) / V(p+1) of its group's first softmax phase, p = 0 (A) or 1 (B)
   const int kpre_idx = (kSplit ? 3 : 2) + (wave >> 2), vpre_idx = 1 + (wave >> 2);
   if (kMulti) touch_chunks();
-  constexpr int kExtStep = kSplit ? kStageB : kExtTileB;   // from one stage of the records to the next
-  if (kExt && grpA) {
-    if (kMulti) await_record(nt > 1 ? 1 : 0);
-    issue_ext(0);
+  auto first_record = [&](int stage) {
+    if (!kExt) return;
+    issue_ext(stage);
     xpre += kExtTileB;
-    if (nt > 1) issue_ext(kExtStep);
-    xpre += kExtTileB;
-  }
+  };
   if (!kSplit) {
     const Place first = place(0);
+    if (grpA) first_record(0);
     issue_k_tile(first, 0);
     issue_v_tile(first, 0);
-    if (nt > 1) issue_k_tile(place(1), 1);   // (V(1) and K(2): group B, once Q has left their place)
-  } else {
-    // a group moves whole tiles: each group two of them
-    if (grpA) {
-      const Place first = place(0);
-      issue_k_tile(first, 0);
-      issue_v_tile(first, 0);
-    } else {
-      if (nt > 1) issue_k_tile(place(1), 1);
-      if (nt > 2) issue_k_tile(place(2), 2);
+    if (nt > 1) {                          // (V(1) and K(2): group B, once Q has left their place)
+      const Place second = place(1);
+      if (grpA) first_record(kExtTileB);
+      issue_k_tile(second, 1);
     }
+  } else if (grpA) {                       // a group moves whole tiles: each group two of them
+    const Place first = place(0);
+    first_record(0);
+    issue_k_tile(first, 0);
+    issue_v_tile(first, 0);
+    xpre += 2 * kExtTileB;                 // (its first softmax phase loads record 3, the other group's record 4)
+  } else {
+    xpre += kExtTileB;
+    if (nt > 1) {
+      const Place second = place(1);
+      first_record(kStageB);
+      issue_k_tile(second, 1);
+    }
+    if (nt > 2) {
+      const Place third = place(2);
+      first_record(2 * kStageB);
+      issue_k_tile(third, 2);
+    }
+    xpre += kExtTileB;
   }
   // The K tile that this wave loads next and, for the same softmax phase, the V tile: its way through the chunks is the K
   // tile's one phase later, so that only K's is looked after (look_up).  left_look: what is left of K's chunk when there is
@@ -722,7 +725,6 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
   // one instruction of any kind per 5 cycles or so.  With a place for each tensor, moved on and looked at by itself, stages as
   // numbers and a place looked up per record: 24 heads of 4608 3 % more, ring of eight chunks of 2112 under 12 heads 3.4 %, ragged ring
   // of two of 2215 5 %, on a box where the first took 235 us.)
-  if (kExt && kSplit && !grpA) xpre += 3 * kExtTileB;
   Place pre = raw_place(kpre_idx);
   uint64_t vpre = 0;
   uint32_t vpre_bytes = 0;
@@ -782,6 +784,19 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
     return __builtin_bit_cast(bf16x8, u32x4{lo[0], lo[1], hi[0], hi[1]});
   };
   const f32x4 zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
+  // kExt: the per-key factor c replaces the uniform scale of the softmax phase.  c of the second key step is fetched while the first is computed,
+  // of the first (kAhead) in the matrix phase before, so that the softmax phase, the longer one here, does not begin with a wait: FP8
+  // ring of four chunks of 1152 under 24 heads 70.0 -> 67.9 us, of eight of 2112 under 12 heads, d = 64 164 -> 157.  Not where a SIMD holds four
+  // waves, and not in 256-query work-groups of d = 64 (24 heads of 4608 165 -> 168).
+  constexpr bool kAhead = kExt && !kFour && (kSplit || !kHalfD);
+  auto x_vec = [&](int stage, int mb) -> f32x4 {   // c of keys 16*mb + 4*g + (0..3)
+    return *reinterpret_cast<const __attribute__((address_space(3))) f32x4*>(x_rd + stage + 64 * mb);
+  };
+  f32x4 xc[2][2];
+  auto x_load = [&](int kk, int xs) {
+#pragma unroll
+    for (int a = 0; a < 2; ++a) xc[kk][a] = x_vec(xs, 2 * kk + a);
+  };
   // matrix phase: O += P V (V tile in stage sv) interleaved with the scores of the next tile (K in
   // stage sk), in four blocks of sixteen MFMAs: block b takes kNV V^T operands (key step b >> 1, head-dim
   // blocks kNV * (b & 1) ..) and kNV K operands (head-dim slice b, all key blocks; kHalfD: key block b, both slices), each
@@ -793,7 +808,8 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
   // MFMAs and the reads issued behind them) rather than left to the instruction scheduler.
   // (The softmax phase is the one with the raised priority: what it loses to the matrix phase's issue beside it, it
   // loses in full, while the matrix core has work queued.  24 heads of 4608 queries and keys 225 -> 218 us against the other way round.)
-  auto MM_full = [&](int sv, int sk) {
+  // (kAhead: the first factors of that tile, whose record lies in stage xs, are read while the last operands are used.)
+  auto MM_full = [&](int sv, int sk, int xs) {
     __builtin_amdgcn_s_setprio(0);
     bf16x8 va[2][kNV], ka[2][kNV];
 #pragma unroll
@@ -817,6 +833,7 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
       }
 #pragma unroll
       for (int j = 0; j < kNV; ++j) {             // (kNV is both the key blocks and, or for kHalfD, the head-dim slices)
+        if (kAhead && blk == 3 && j == 0) x_load(0, xs);
         const int mb = kHalfD ? blk : j, ks = kHalfD ? j : blk;
         if (!kHalfD && (j & 1)) sacc[mb][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[c][j], qreg[1][ks], ks == 0 ? zero4 : sacc[mb][1], 0, 0, 0);
         sacc[mb][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[c][j], qreg[0][ks], ks == 0 ? zero4 : sacc[mb][0], 0, 0, 0);
@@ -862,16 +879,6 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
   // does the wave find the true maximum, move m, rescale O and l, and redo the exponentials.
   // While it runs, the wave also issues its tile loads, spread between the exponential blocks so
   // that the waves do not hit the load path at once.
-  // kExt: the per-key factor c replaces the uniform scale.
-  auto x_vec = [&](int stage, int mb) -> f32x4 {   // c of keys 16*mb + 4*g + (0..3)
-    return *reinterpret_cast<const __attribute__((address_space(3))) f32x4*>(x_rd + stage + 64 * mb);
-  };
-  // c of the second key step is fetched while the first is computed
-  f32x4 xc[2][2];
-  auto x_load = [&](int kk, int xs) {
-#pragma unroll
-    for (int a = 0; a < 2; ++a) xc[kk][a] = x_vec(xs, 2 * kk + a);
-  };
   // one block: the 8 scores of query block nb over key step kk -> pk[kk][nb]
   auto exp_block = [&](int kk, int nb, float& psum, int xs, bool fetch_ahead) {   // (key step 0 begins the sum)
     float p[8];
@@ -987,11 +994,11 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
   };
   auto failed = [&](float sum) -> uint64_t { return __builtin_amdgcn_ballot_w64(!(sum <= kCertifiedSum)); };
   auto has_reference = [&]() -> uint64_t { return __builtin_amdgcn_ballot_w64(m[0] != -INFINITY || m[1] != -INFINITY); };
-  // SM of the tile whose record sits in stage xs; loads the next K tile into stage sk (if do_k), its record, or with idx >= 0 that of
-  // tile idx alone, into stage xst (if do_x), and the next V tile into stage sv (if do_v)
-  auto SM = [&](int xs, int sk, int sv, bool do_k, bool do_v, bool do_x, int xst, int idx) {
+  // SM of the tile whose record sits in stage xs; loads the next K tile into stage sk and, if do_x, its record into stage xst (if do_k), and the
+  // next V tile into stage sv (if do_v)
+  auto SM = [&](int xs, int sk, int sv, bool do_k, bool do_v, bool do_x, int xst) {
     float psum[2] = {0.0f, 0.0f};
-    if (kExt) x_load(0, xs);
+    if (kExt && !kAhead) x_load(0, xs);
     if (kDead) {
       if (sm_tile >= next_dead) {
         if (next_dead < sm_tile) next_dead = find_dead(sm_tile);
@@ -1023,9 +1030,7 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
       issue_k(pre.k, vpre_bytes, sk, 0);
     };
     auto load_record = [&]() {
-      if (!kExt || !do_x) return;
-      if (kMulti && idx >= 0) await_record(idx);
-      issue_ext(xst);
+      if (kExt && do_k && do_x) issue_ext(xst);
     };
     if (do_v) issue_v(vpre, vpre_bytes, sv, 0);
     if (kFour && kExt) {
@@ -1192,17 +1197,18 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
       st = s1; s1 = s2; s2 = sp;
       xs = (xs + kExtTileB) & (3 * kExtTileB);
     };
+    if (kAhead) x_load(0, 0);
     if (grpA) {
       // tile j: phase 2j = SM(j), prefetching K(j+2) and its record -> stage st+2, V(j+1) -> stage st+1;
       //         phase 2j+1 = MM(j) with V(j) in stage st, K(j+1) in stage st+1
       for (int j = 0; j < nt - 1; ++j) {
-        SM(xs, s2, s1, j + 2 < nt, true, j + 2 < nt, xs ^ (2 * kExtTileB), -1);
+        SM(xs, s2, s1, j + 2 < nt, true, true, xs ^ (2 * kExtTileB));
         phase_barrier(j + 2 < nt ? 1 : 2);
-        MM_full(st, s1);
+        MM_full(st, s1, (xs + kExtTileB) & (3 * kExtTileB));
         phase_barrier(0, false);
         next_tile();
       }
-      SM(xs, 0, 0, false, false, false, 0, -1);
+      SM(xs, 0, 0, false, false, false, 0);
       phase_barrier(2);
       MM_last(st);
       phase_barrier(0, false);
@@ -1212,13 +1218,13 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
       // tile j: phase 2j = MM(j-1) with V(j-1) in stage st-1, K(j) in stage st;
       //         phase 2j+1 = SM(j), prefetching K(j+3) -> stage st, V(j+2) -> stage st+2
       phase_barrier(0);                                 // phase 0: nothing to do yet
-      SM(0, 0, 2 * kStageB, 3 < nt, 2 < nt, false, 0, -1);         // phase 1 (tile 0)
+      SM(0, 0, 2 * kStageB, 3 < nt, 2 < nt, false, 0);         // phase 1 (tile 0)
       phase_barrier(3 < nt ? 1 : 2, false);
       for (int j = 1; j < nt; ++j) {
-        MM_full(st, s1);
+        MM_full(st, s1, (xs + kExtTileB) & (3 * kExtTileB));
         phase_barrier(0);
         next_tile();
-        SM(xs, st, s2, j + 3 < nt, j + 2 < nt, false, 0, -1);
+        SM(xs, st, s2, j + 3 < nt, j + 2 < nt, false, 0);
         phase_barrier(j + 3 < nt ? 1 : 2, false);
       }
       MM_last(st);
@@ -1234,12 +1240,12 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
     wait_loads<0>();   // V(0), K(2): published by the barrier that ends phase 0
     first_v();
     // Phases p = 0..nt, one work-group barrier each; both groups execute nt + 1 of them.
-    //   reads in phase p : V(p-1) from stage (p-1)%3, K(p+1) from stage (p+1)%4, record p from p%3
+    //   reads in phase p : V(p-1) from stage (p-1)%3, K(p+1) and the first factors of record p+1 from stage (p+1)%4, the others of record p
     //   batch of phase p : K(p+3) -> stage (p+3)%4 (last read, as K(p-1), in phase p-2; a stage less, and the
     //                      batch of phase 0 would land on K(0), which the first scores read without a
     //                      barrier in between),
     //                      V(p+1) -> stage (p+1)%3 (last read, as V(p-2), in phase p-1),
-    //                      record p+2 -> stage (p+2)%3 (last read, as record p-1, in phase p-1)
+    //                      record p+3 with K(p+3) (last read, as record p-1, in phase p-1)
     //   end of phase p   : the batch of phase p-1 must have landed (first read in phase p+1); its
     //                      issuers are the group now ending a matrix phase, which waits for all of
     //                      its loads; the other group has only this phase's batch in flight
@@ -1252,26 +1258,28 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
       __builtin_amdgcn_sched_barrier(0);
     };
     int t = grpA ? 0 : 1;                  // this group's current tile; SM(t) runs in phase t
-    // stages of V and the records of tiles t, t + 1 and t + 2 (mod 3); of K, of tiles t + 2 (read) and t + 3 (loaded), mod 4: from
-    // one to the next but one and back
+    // stages of V, of tiles t, t + 1 and t + 2 (mod 3); of K and the records, of tiles t (the record), t + 2 (read) and t + 3 (loaded), mod
+    // 4: from one to the next but one and back
     int st = t * kStageB, s1 = st + kStageB, s2 = grpA ? 2 * kStageB : 0;
-    int k_rdst = (t + 2) * kStageB, k_ldst = grpA ? 3 * kStageB : 0;
+    int xs = t * kStageB, k_rdst = (t + 2) * kStageB, k_ldst = grpA ? 3 * kStageB : 0;
     constexpr int kFlipEven = 2 * kStageB, kFlipOdd = kStageB ^ (3 * kStageB);
     const int flip_rd = grpA ? kFlipEven : kFlipOdd, flip_ld = grpA ? kFlipOdd : kFlipEven;
+    if (kAhead) x_load(0, xs);
     if (!grpA) end_phase(false);           // phase 0: group B has no scores yet
     while (t + 2 < nt) {
-      SM(st, k_ldst, s1, t + 3 < nt, true, true, s2, t + 3 < nt ? -1 : t + 2);   // phase t (t + 1 < nt holds here)
+      SM(xs, k_ldst, s1, t + 3 < nt, true, true, k_ldst);   // phase t (t + 1 < nt holds here)
       end_phase(false);
-      MM_full(st, k_rdst);                                 // phase t + 1
+      MM_full(st, k_rdst, k_rdst);                          // phase t + 1
       end_phase(true);
       t += 2;
       const int sp = st;
       st = s2; s2 = s1; s1 = sp;
+      xs = k_rdst;
       k_rdst ^= flip_rd;
       k_ldst ^= flip_ld;
     }
     if (t < nt) {                                          // this group's last tile
-      SM(st, 0, s1, false, t + 1 < nt, false, 0, -1);
+      SM(xs, 0, s1, false, t + 1 < nt, false, 0);
       end_phase(false);
       MM_last(st);
       end_phase(true);
