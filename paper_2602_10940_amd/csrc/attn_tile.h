@@ -14,8 +14,8 @@
 //     infinity is NaN).  fp32 Q (engine F32Q): v_mfma_f32_16x16x4_f32.
 //   * Per-key factors: FP8 scales of K multiply the fp32 scores, those of V multiply P.
 //   * 64-key tiles come to LDS while the one before is computed on: bf16 ones of d <= 128 directly (work-groups being few: by
-//     width and mask, see attn_generic.hip), the others through registers (see Plan).  Pitches are odd multiples of 16 bytes (K) and of 32 bytes (V of Bf16Q, read transposed), or
-//     d + 4 words (F32Q): no bank conflicts in the operand reads.
+//     width and mask, see attn_generic.hip), the others through registers (see Plan).  Pitches are odd multiples of 32 bytes (Bf16Q, V read transposed: no bank conflicts in the operand
+//     reads), or d + 4 words (F32Q; K's reads conflict, which d + 8 words cure for nothing: fp32 is bound by its MFMAs).
 //   * kKW waves share the 16 queries and take 64 / kKW keys of every tile each, their partial results
 //     being combined through LDS at the end of a chunk: for calls with few query blocks, and to have eight waves on 64 queries.
 //   * Where the work-groups are still few and there is one chunk, each query block's tiles are cut into ranges with a work-group
@@ -150,7 +150,10 @@ template <int kD, int kDB, int kMB>
 struct Bf16Q {
   typedef bf16_t qo_elt;
   static constexpr int kSK = kD / 32, kBlocks = kDB;
-  static constexpr int kPitchK = kD * 2 + 16, kPitchV = (kDB | 1) * 32;   // bytes
+  // bytes.  K: an odd multiple of 32: a 16-byte read takes the lanes 0-3, 12-15, 20-27 together (then 4-11, 16-19, 28-31, then the upper
+  // half likewise), so that 8 rows of one piece must lie in the even 16-byte places of the banks and 8 of the next piece
+  // in the odd ones.  (An odd multiple of 16 put two into one: d = 72, 32 heads of 1024 29.65 -> 29.1 us, from FP8 37.7 -> 36.3, d = 112 37.3 -> 36.3.)
+  static constexpr int kPitchK = kD * 2 + 32, kPitchV = (kDB | 1) * 32;
   static_assert(kD % 32 == 0 && kMB % 2 == 0, "32-wide contraction steps");
   bf16x8 q[kSK];
   __device__ __forceinline__ void load_q(const bf16_t* row, int d, int g) {
