@@ -165,6 +165,16 @@ struct Bf16Q {
       q[ks] = __builtin_bit_cast(bf16x8, w);
     }
   }
+  // Q is waited for here, in front of the tiles.  Left to its first use, the wait stands at the head of the loop over them, and there
+  // it waits in every tile for the next one, just asked for, too.  With tiles going to LDS directly: two chunks of 800 keys under 16 heads of
+  // 800, d = 80 31.7 -> 28.8 us, 10 heads of 512, 900 keys, d = 112 19.8 -> 17.0, 22 heads of 700, d = 72 15.7 -> 14.7; fp32 ring of two of 128 under two
+  // heads 9.85 -> 9.53.  Not from FP8, where the tile is converted on its way to LDS and the wait for it comes better early (d = 72, 32 heads
+  // of 1024 36.4 us with that wait, 38.4 without), nor in fp32 where one wave has 16 queries for itself or d is above 64 (16 heads of 700, d = 128
+  // 64.4, 65.0: kQFirst).
+  __device__ __forceinline__ void landed() {
+#pragma unroll
+    for (int ks = 0; ks < kSK; ++ks) asm volatile("" : "+v"(q[ks]));
+  }
   template <class U> static __device__ __forceinline__ void put(unsigned char* kv, int pitch, int row, int unit, const U& u) {
     *reinterpret_cast<u32x4*>(kv + row * pitch + unit * 16) = u.as_bf16();
   }
@@ -239,6 +249,10 @@ struct F32Q {
       q[s] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
       if (c < d) q[s] = *reinterpret_cast<const f32x4*>(row + c);
     }
+  }
+  __device__ __forceinline__ void landed() {
+#pragma unroll
+    for (int s = 0; s < kSK; ++s) asm volatile("" : "+v"(q[s]));
   }
   template <class U> static __device__ __forceinline__ void put(unsigned char* kv, int pitch, int row, int unit, const U& u) {
     f32x4 a, b;
@@ -325,6 +339,7 @@ void attn_tile_kernel(AttnStep s) {
   typedef typename Unit::elt KT;
   typedef typename E::qo_elt QT;
   constexpr bool fp8 = std::is_same<Unit, UnitF8>::value;
+  constexpr bool kQFirst = !fp8 && (std::is_same<QT, float>::value ? kD <= 64 && kKW > 1 : kD <= 128);   // (see landed)
   extern __shared__ __align__(16) unsigned char smem[];
   touch_step();
   if (s.copy_wgs > 0 && blockIdx.x >= gridDim.x - s.copy_wgs) {   // prefetch work-groups end the x axis
@@ -491,15 +506,20 @@ void attn_tile_kernel(AttnStep s) {
   auto lds_of = [&](const unsigned char* p) -> uint32_t { return __builtin_amdgcn_readfirstlane(lds0 + (uint32_t)(p - smem)); };
   fetch_next(lds0);
   if (kDma) {
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0x0F70);                         // vmcnt(0)
+    e.landed();
     live = live_word();
     __syncthreads();
     fetch_next(lds_of(oth));
   } else if (kBuffers == 2 && fetched) {
     stage(cur);
+    if (kQFirst) e.landed();
     live = live_word();
     fetch_next(0);
     __syncthreads();
+  } else if (kQFirst) {
+    e.landed();
   }
 
   for (int c = 0; c < s.n_multi; ++c) {
@@ -573,7 +593,8 @@ void attn_tile_kernel(AttnStep s) {
       e.pv(cur + kTile * E::kPitchK + k0 * E::kPitchV, r, g, p, o);
       if (kBuffers == 2) {
         if (kDma) {
-          asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // the next tile, asked for a tile ago
+          asm volatile("" ::: "memory");
+          __builtin_amdgcn_s_waitcnt(0x0F70);                    // the next tile, asked for a tile ago
           live_next = live_word();
           __syncthreads();
           fetch_next(lds_of(cur));
