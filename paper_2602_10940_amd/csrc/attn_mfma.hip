@@ -68,6 +68,7 @@ struct TileLayout {
 // of work-groups whatever the head count.  The grid holds 8 * ceil(items / 8) ids; ids past the
 // last item return false.
 constexpr int kXcds = 8;
+constexpr int kMostParts = 16;
 constexpr int kSplitBelowWGs = 128;   // use the key-split kernel when 256-query work-groups number at most this
 __device__ __forceinline__ bool wg_to_tile(int attn_wgs, int nqb, int bh_total, int& bh, int& qb, int lead = 0) {
   const int id = blockIdx.x - lead;                   // the copy work-groups are the last ids of the grid, or the first `lead` (a multiple of 8)
@@ -1341,32 +1342,54 @@ __global__ __launch_bounds__(kThreads, four_waves(kSplit, kExt, kMulti, kDead, k
 
 // The parts of a launch whose work-groups shared the keys of a query block (AttnStep::parts): per query,
 // O = sum_i 2^(m_i - m) O~_i / l, l = sum_i 2^(m_i - m) l_i, m = max_i m_i, and lse = (m + log2 l) ln 2.
-// One thread per four head dims; bound by the reading of the parts, which lie in the caches.
-template <int kRowD>
+// One thread per eight head dims; the parts lie in the caches, so what bounds it is the launch and one trip to them: all of up to
+// kParts parts' loads are issued together (four parts 0.3 to 0.5 us less than one after the other).
+template <int kRowD, int kParts>
 __global__ __launch_bounds__(256) void attn_combine_kernel(const float* __restrict__ part_o, const float* __restrict__ part_ml,
                                                            bf16_t* __restrict__ out, float* __restrict__ lse, int parts,
                                                            uint32_t rows, uint32_t Sq, uint32_t H, int64_t os0, int64_t os1, int64_t os2) {
-  constexpr uint32_t kLanes = kRowD / 4;
+  constexpr uint32_t kLanes = kRowD / 8;
   const uint32_t row = blockIdx.x * (256 / kLanes) + threadIdx.x / kLanes, c = threadIdx.x % kLanes;
   if (row >= rows) return;
+  constexpr int kBatch = kParts < 8 ? kParts : 8;   // parts whose O~ is on the way at a time
+  float2 ml[kParts];
+  f32x4 x[kBatch][2];
+  auto load = [&](int first) {
+#pragma unroll
+    for (int i = 0; i < kBatch; ++i)
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+        x[i][u] = *reinterpret_cast<const f32x4*>(part_o + ((int64_t)(first + i < parts ? first + i : 0) * rows + row) * kRowD + 8 * c + 4 * u);
+  };
+#pragma unroll
+  for (int i = 0; i < kParts; ++i) ml[i] = *reinterpret_cast<const float2*>(part_ml + 2 * ((int64_t)(i < parts ? i : 0) * rows + row));
+  load(0);
   float m = -INFINITY;
-  for (int i = 0; i < parts; ++i) m = fmaxf(m, part_ml[2 * ((int64_t)i * rows + row)]);
+#pragma unroll
+  for (int i = 0; i < kParts; ++i) m = fmaxf(m, ml[i].x);   // (those past the last repeat the first)
   const float ref = m == -INFINITY ? 0.0f : m;   // (no live key: every weight and every l is 0)
   float l = 0.0f;
-  f32x4 o = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll 4
-  for (int i = 0; i < parts; ++i) {
-    const float2 ml = *reinterpret_cast<const float2*>(part_ml + 2 * ((int64_t)i * rows + row));
-    const f32x4 x = *reinterpret_cast<const f32x4*>(part_o + ((int64_t)i * rows + row) * kRowD + 4 * c);
-    const float w = __builtin_amdgcn_exp2f(ml.x - ref);
-    l = fmaf(w, ml.y, l);
+  f32x4 o[2] = {{0.0f, 0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f, 0.0f}};
 #pragma unroll
-    for (int e = 0; e < 4; ++e) o[e] = fmaf(w, x[e], o[e]);
+  for (int first = 0; first < kParts; first += kBatch) {
+    if (first > 0) load(first);
+#pragma unroll
+    for (int i = 0; i < kBatch; ++i) {
+      if (first + i < parts) {
+        const float w = __builtin_amdgcn_exp2f(ml[first + i].x - ref);
+        l = fmaf(w, ml[first + i].y, l);
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) o[u][e] = fmaf(w, x[i][u][e], o[u][e]);
+      }
+    }
   }
   const float inv = l == 0.0f ? 0.0f : 1.0f / l;   // (a part that gave up left NaN in l and O~)
   const uint32_t bh = row / Sq, qi = row - bh * Sq, b = bh / H, h = bh - b * H;
-  const u32x2 v = {pack_bf16x2(o[0] * inv, o[1] * inv), pack_bf16x2(o[2] * inv, o[3] * inv)};
-  __builtin_nontemporal_store(v, reinterpret_cast<u32x2*>(out + b * os0 + h * os1 + (int64_t)qi * os2 + 4 * c));
+  const u32x4 v = {pack_bf16x2(o[0][0] * inv, o[0][1] * inv), pack_bf16x2(o[0][2] * inv, o[0][3] * inv),
+                   pack_bf16x2(o[1][0] * inv, o[1][1] * inv), pack_bf16x2(o[1][2] * inv, o[1][3] * inv)};
+  __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(out + b * os0 + h * os1 + (int64_t)qi * os2 + 8 * c));
   if (c == 0) lse[row] = l == 0.0f ? -INFINITY : (m + log2f(l)) * 0.69314718055994530942f;
 }
 
@@ -1469,19 +1492,22 @@ bool narrow_takes_split(int64_t blocks, int64_t halves, int tiles, bool ext) {
   const double pair = ext ? 9.5 + 0.96 * n : 7.8 + 0.88 * n, one = ext ? 6.6 + 0.6 * n : 5.6 + 0.53 * n;
   return (double)(per_cu / 2) * pair + (per_cu % 2 ? one : 0.0) < wide;
 }
-usp_status launch_combine(const AttnStep& s, hipStream_t st) {
-  const uint32_t rows = (uint32_t)((int64_t)s.B * s.H * s.Sq), per = 1024 / (uint32_t)s.d;
-  const dim3 grid((rows + per - 1) / per);
-  bf16_t* out = (bf16_t*)s.out;
-  if (s.half_d)
-    hipLaunchKernelGGL((attn_combine_kernel<64>), grid, dim3(256), 0, st, s.part_o, s.part_ml, out, s.lse, s.parts, rows,
-                       (uint32_t)s.Sq, (uint32_t)s.H, s.os[0], s.os[1], s.os[2]);
-  else
-    hipLaunchKernelGGL((attn_combine_kernel<128>), grid, dim3(256), 0, st, s.part_o, s.part_ml, out, s.lse, s.parts, rows,
-                       (uint32_t)s.Sq, (uint32_t)s.H, s.os[0], s.os[1], s.os[2]);
+template <int kRowD, int kParts>
+void launch_combine_as(const AttnStep& s, hipStream_t st) {
+  const uint32_t rows = (uint32_t)((int64_t)s.B * s.H * s.Sq), per = 256 * 8 / kRowD;
+  hipLaunchKernelGGL((attn_combine_kernel<kRowD, kParts>), dim3((rows + per - 1) / per), dim3(256), 0, st, s.part_o, s.part_ml, (bf16_t*)s.out, s.lse,
+                     s.parts, rows, (uint32_t)s.Sq, (uint32_t)s.H, s.os[0], s.os[1], s.os[2]);
+}
+template <int kRowD>
+usp_status launch_combine_d(const AttnStep& s, hipStream_t st) {
+  if (s.parts <= 2) launch_combine_as<kRowD, 2>(s, st);
+  else if (s.parts <= 4) launch_combine_as<kRowD, 4>(s, st);
+  else if (s.parts <= 8) launch_combine_as<kRowD, 8>(s, st);
+  else launch_combine_as<kRowD, kMostParts>(s, st);
   USP_CHECK_HIP(hipGetLastError());
   return USP_OK;
 }
+usp_status launch_combine(const AttnStep& s, hipStream_t st) { return s.half_d ? launch_combine_d<64>(s, st) : launch_combine_d<kD>(s, st); }
 template <bool kExt, bool kDead>
 usp_status launch_mixed(const AttnStep& s, unsigned wgs, hipStream_t st) {
   constexpr int lds = LdsPlan<false>::bytes(kMaxWords);
@@ -1495,16 +1521,17 @@ usp_status launch_mixed(const AttnStep& s, unsigned wgs, hipStream_t st) {
 int64_t attn_mfma_max_dead_tiles() { return kMaxWords; }
 
 // Keys shared between work-groups: for Q shards whose key-split work-groups leave most of the chip idle.  In
-// microseconds, a launch takes about 7.5 + tiles * t, t = 0.75 up to 128 work-groups and 0.92 at 216 and
-// more; parts add 6 for the second launch and what the parts' bytes, written and read, take at 5.5 TB/s.
-// Taken when that comes out at least 3 us lower.  Measured, 1 against the chosen number of parts: H = 3, Sq = 4608,
-// 4608 keys 57 -> 43 us; H = 1, Sq = 256, 4608 keys 57 -> 21 us; H = 4, Sq = 1024, 1024 keys 20.6 us with 1, 2 or 4.
+// microseconds, a launch over one chunk takes 5.5 + tiles * 0.66 (d = 64: 5.6 and 0.46), a tile up to 19 % (10 %) longer from 128 to 216
+// work-groups and, d = 64, where two share a CU, up to 1.85 times as long from 256 to 384; parts add 2.3 + 0.35 each (1.7 + 0.25)
+// and what their bytes, written and read, take at 4.1 (3.4) TB/s.  46 random launches of 4 to 260 work-groups, each with 1, 2, 3, 4, 6 and 8 parts:
+// 4 % rms; the choice is 0.2 % above the best on average, 2.3 % at most; of 64 more, up to 14 000 keys and 16 parts, 7 % at most.  us with 1 part and with the chosen number: H = 1, Sq = 936, 985 keys, d = 64
+// 14.2, 11.9 (by the constants before, with 13 parts, 15.1); B = 2, H = 2, Sq = 3861, 3456 keys, d = 64 31.0, 25.9; B = 2, H = 2, Sq = 241, 1568 keys,
+// d = 128 22.8, 15.1 (17.6).  H = 3, Sq = 4608, 4608 keys 57 -> 39.
 // One chunk of 500 to 2600 keys, d = 64 or 128, bf16 or FP8, 35 random shapes that take parts: 0.54 to 0.97 of the time.
-// (The prologue and the transfers have become shorter since these figures were taken, by 2 to 3 us and by a third: on 1660
-// random launches the choice takes 4 to 5 % more than the best number of parts on average, one chunk 1.28 times as much at most,
-// a ring 1.5 times.  The figures here and below are those of the launches the constants were fitted to.)
-// At most 240 work-groups, so that the copy work-groups of the same launch (16 at least) find a CU (one chunk, which has none, is held to it too).
+// At most 240 work-groups (d = 64, one chunk: 480, two to a CU), so that the copy work-groups of the same launch (16 at least) find a CU (one chunk, which has none, is held to it too).
 //
+// (The constants of a ring are older: the prologue and the transfers have become shorter since, by 2 to 3 us and by a third.  On random launches the
+// choice takes 4 to 5 % more than the best number of parts on average, 1.5 times as much at most.)
 // A ring's chunks arrive inside the launch (FP8 chunks always; bf16 ones with USP_ATTN_FUSED_PREFETCH, and the plain
 // call takes the same form, so that the two give the same bits): the last one 11 us after the start, plus 4 (FP8: 7)
 // for each that its group of copy work-groups has to bring one after another, and the bytes moved at 50 GB/s per
@@ -1525,19 +1552,25 @@ int64_t attn_mfma_max_dead_tiles() { return kMaxWords; }
 AttnForm attn_mfma_form(int B, int H, int Sq, int d, int64_t tiles, const RingTransfers* ring) {
   const int64_t blocks = (int64_t)B * H * ((Sq + kQPerWGSplit - 1) / kQPerWGSplit), wgs = 8 * ((blocks + 7) / 8);
   AttnForm best = {0, 1};
+  const bool pairs = !ring && d != kD;   // two work-groups to a CU
   if (wgs > 120) {
     const int64_t wide = (int64_t)B * H * ((Sq + kQPerWG - 1) / kQPerWG);
     if (!ring && (wide <= 256 ? wgs <= 256 : d != kD)) best.variant = attn_mfma_ring_form(B, H, Sq, d, tiles, 1, 0).split ? 2 : 0;
-    return best;
+    if (!pairs || wgs > 240) return best;
   }
-  const double tile = !ring ? 0.75 : d == kD ? (ring->fp8 ? 0.82 : 0.75) : (ring->fp8 ? 0.65 : 0.58);
+  auto crowd = [](double n) { return n <= 128 ? 0.0 : n >= 216 ? 1.0 : (n - 128) / 88; };   // how far work-groups take each other's time
   auto cost = [&](int parts) {
-    const double n = (double)wgs * parts;
-    const double t = tile * (1.0 + 0.17 / 0.75 * (n <= 128 ? 0.0 : n >= 216 ? 1.0 : (n - 128) / 88));
-    const double combine = parts > 1 ? 6.0 + 2.0 * 4 * d * parts * B * H * Sq / 5.5e6 : 0.0;
+    const double n = (double)wgs * parts, bytes = 2.0 * 4 * d * parts * B * H * Sq;
     const int64_t mine = (tiles + parts - 1) / parts;
+    if (!ring) {
+      const double shared = n <= 256 ? 0.0 : n >= 384 ? 0.75 : 0.75 * (n - 256) / 128;
+      if (d == kD) return 5.5 + (double)mine * 0.66 * (1.0 + 0.19 * crowd(n)) + (parts > 1 ? 2.3 + 0.35 * parts + bytes / 4.1e6 : 0.0);
+      return 5.6 + (double)mine * 0.46 * (1.0 + 0.1 * crowd(n) + shared) + (parts > 1 ? 1.7 + 0.25 * parts + bytes / 3.4e6 : 0.0);
+    }
+    const double tile = d == kD ? (ring->fp8 ? 0.82 : 0.75) : (ring->fp8 ? 0.65 : 0.58);
+    const double t = tile * (1.0 + 0.17 / 0.75 * crowd(n));
+    const double combine = parts > 1 ? 6.0 + bytes / 5.5e6 : 0.0;
     const double work = (double)mine * t;
-    if (!ring) return 7.5 + work + combine;
     const int copy_wgs = copy_wgs_beside((int)(8 * ((blocks * parts + 7) / 8)));
     const int later = ring->chunks - 1, groups = copy_groups_of(copy_wgs, later, ring->largest);
     const double chain = (later + groups - 1) / groups * (ring->fp8 ? 7.0 : 4.0) + (double)ring->bytes / (copy_wgs * 50e3);
@@ -1549,8 +1582,8 @@ AttnForm attn_mfma_form(int B, int H, int Sq, int d, int64_t tiles, const RingTr
     return (busy > waited ? busy : waited) + (parts > 1 ? combine + 1.0 : 0.0);
   };
   const double one = cost(1);
-  double least = !ring ? one - 3.0 : 0.96 * one;
-  for (int parts = 2; parts <= 16 && parts * wgs <= 240 && parts <= tiles; ++parts) {
+  double least = !ring ? 0.97 * one : 0.96 * one;
+  for (int parts = 2; parts <= kMostParts && parts * wgs <= (pairs ? 480 : 240) && parts <= tiles; ++parts) {
     const double c = cost(parts);
     if (c < least) { least = c; best = {2, parts}; }
   }

@@ -47,6 +47,31 @@ def test_transfers_inside_the_launch_do_not_change_the_form(d, lens):
         assert _route(1, H, d, Sq, lens) == _route(1, H, d, Sq, lens, flags=b.USP_ATTN_FUSED_PREFETCH)
 
 
+# B, H, d, Sq, keys and the parts that were fastest of 1, 2, 3, 4, 6 and 8 (or within 2 % of it)
+SHARED = [(1, 5, 64, 112, 3648, (6, 7, 8, 10)), (1, 1, 64, 936, 985, (4, 5)), (2, 2, 64, 3861, 3456, (2,)), (1, 12, 64, 416, 576, (1,)),
+          (2, 13, 64, 2049, 640, (1,)), (2, 2, 128, 241, 1568, (4, 5, 6, 7)), (1, 3, 128, 4608, 4608, (2, 3)), (1, 2, 128, 212, 3926, (8, 9, 10)),
+          (2, 2, 128, 1937, 384, (1,)), (2, 14, 128, 737, 960, (1,)), (1, 2, 128, 300, 16384, (12, 13, 14, 15, 16))]
+
+
+@pytest.mark.parametrize("B,H,d,Sq,keys,parts", SHARED)
+def test_parts_of_one_chunk(B, H, d, Sq, keys, parts):
+    got = _route(B, H, d, Sq, (keys,)).parts
+    assert got in parts
+    need = b.usp_ring_attn_workspace_bytes(_desc(B, H, d, Sq, (keys,)))
+    assert got == 1 or need >= 4 * got * B * H * Sq * (d + 2)
+
+
+def test_parts_never_outnumber_what_a_second_launch_takes():
+    for d in (64, 128):
+        for heads in (1, 2, 7, 24, 60):
+            for Sq in (1, 129, 500, 4608):
+                for keys in (1, 64, 65, 513, 4097, 70000):
+                    blocks = 8 * -(-heads * -(-Sq // 128) // 8)
+                    for lens, most in (((keys,), 480 if d == 64 else 240), ((64 * -(-keys // 64),) * 2, 240)):
+                        parts = _route(1, heads, d, Sq, lens).parts
+                        assert 1 <= parts <= 16 and (parts == 1 or (parts * blocks <= most and parts <= sum(-(-n // 64) for n in lens)))
+
+
 # us of a launch per chunk, one launch of 256-query work-groups, one key-split launch (all chunks at hand)
 MEASURED = [(2, 24, 128, 4608, 2, 1536, 370, 331, 363), (2, 22, 64, 4416, 2, 128, 92, 47, 62), (2, 19, 64, 3621, 2, 128, 71, 37, 46),
             (1, 22, 128, 3112, 2, 128, 57, 32, 39), (1, 24, 128, 2816, 4, 1024, 245, 208, 184), (1, 20, 128, 3500, 3, 2048, 302, 302, 261),

@@ -135,3 +135,18 @@ def test_d64_two_work_groups_to_a_cu(H, Sq, keys, masked, fp8, split):
     ro, rl = orc.ring_attention(inp.q[:, heads], [kx[:, heads]], [vx[:, heads]], scale, inp.key_mask if masked[1] else None)
     for x, y in ((o, l), (os_, ls), (ow, lw)):
         _assert_parity(host_f64(x[:, heads]), host_f64(y[:, heads]), ro, rl)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("H,Sq,keys,masked", [(1, 100, 1024, (0, 0)),         # (100 rows: the last work-group of the second launch half full)
+                                              (1, 257, 4000, (0, 0)), (2, 33, 4096, (64, 2100)), (3, 130, 960, (959, 960)), (1, 7, 16384, (0, 0))])
+def test_parts_put_together_against_oracle(d, H, Sq, keys, masked):
+    """Two to sixteen parts, the second launch with fewer parts than it has room for, and parts without a live key."""
+    from paper_2602_10940_amd import diag
+    import paper_2602_10940_amd as P
+    inp = W.make_attention_inputs(W.Workload("parts", 96, 1, H, d, Sq, (keys,), "bf16", masked_keys=masked))
+    q, k = dev_bf16(inp.q), dev_bf16(inp.k[0])
+    assert diag.usp_diag_attn_route(P.make_attn_desc(q, [k], torch.empty_like(q)), bool(masked[1])).parts > 1
+    o, l = _run(inp)
+    ro, rl = _oracle(inp)
+    _assert_parity(o, l, ro, rl)
