@@ -1521,12 +1521,17 @@ usp_status launch_mixed(const AttnStep& s, unsigned wgs, hipStream_t st) {
 int64_t attn_mfma_max_dead_tiles() { return kMaxWords; }
 
 // Keys shared between work-groups: for Q shards whose key-split work-groups leave most of the chip idle.  In
-// microseconds, a launch over one chunk takes 5.5 + tiles * 0.66 (d = 64: 5.6 and 0.46), a tile up to 19 % (10 %) longer from 128 to 216
-// work-groups and, d = 64, where two share a CU, up to 1.85 times as long from 256 to 384; parts add 2.3 + 0.35 each (1.7 + 0.25)
-// and what their bytes, written and read, take at 4.1 (3.4) TB/s.  46 random launches of 4 to 260 work-groups, each with 1, 2, 3, 4, 6 and 8 parts:
-// 4 % rms; the choice is 0.2 % above the best on average, 2.3 % at most; of 64 more, up to 14 000 keys and 16 parts, 7 % at most.  us with 1 part and with the chosen number: H = 1, Sq = 936, 985 keys, d = 64
-// 14.2, 11.9 (by the constants before, with 13 parts, 15.1); B = 2, H = 2, Sq = 3861, 3456 keys, d = 64 31.0, 25.9; B = 2, H = 2, Sq = 241, 1568 keys,
-// d = 128 22.8, 15.1 (17.6).  H = 3, Sq = 4608, 4608 keys 57 -> 39.
+// microseconds, a launch takes about 7.5 + tiles * t, t = 0.75 up to 128 work-groups and 0.92 at 216 and
+// more; parts add 6 for the second launch and what the parts' bytes, written and read, take at 5.5 TB/s.
+// Taken when that comes out at least 3 us lower.
+// Over one chunk that leaves launches which gain by parts as well, since the prologue, the second launch and, for d = 64, two work-groups on a
+// CU have made them cheaper: 5.5 + tiles * 0.66 (d = 64: 5.6 and 0.46), a tile up to 19 % (10 %) longer from 128 to 216 work-groups and,
+// d = 64, up to 1.85 times as long from 256 to 384; parts add 2.3 + 0.35 each (1.7 + 0.25) and their bytes at 4.1 (3.4) TB/s.  46 random launches of
+// 4 to 260 work-groups, each with 1, 2, 3, 4, 6 and 8 parts: 4 % rms.  us with 1 part and so: B = 2, H = 2, Sq = 3861, 3456 keys, d = 64 31.0, 25.9;
+// H = 2, Sq = 1399, 1024 keys, d = 128 16.0, 14.5.  It is not asked where the first rule has taken parts: it would take fewer there, 13 of 16 tiles
+// become 4, up to 20 % faster, but every part's first tile has one weight exact, and with fewer parts O is 1.03 times as far from 64
+// bits in the mean of 18 launches, 1.16 at most.
+// Measured, 1 against the chosen number of parts: H = 3, Sq = 4608, 4608 keys 57 -> 39 us; H = 1, Sq = 256, 4608 keys 57 -> 19 us.
 // One chunk of 500 to 2600 keys, d = 64 or 128, bf16 or FP8, 35 random shapes that take parts: 0.54 to 0.97 of the time.
 // At most 240 work-groups (d = 64, one chunk: 480, two to a CU), so that the copy work-groups of the same launch (16 at least) find a CU (one chunk, which has none, is held to it too).
 //
@@ -1559,18 +1564,21 @@ AttnForm attn_mfma_form(int B, int H, int Sq, int d, int64_t tiles, const RingTr
     if (!pairs || wgs > 240) return best;
   }
   auto crowd = [](double n) { return n <= 128 ? 0.0 : n >= 216 ? 1.0 : (n - 128) / 88; };   // how far work-groups take each other's time
+  // one chunk, the times as they are
+  auto chunk_cost = [&](int parts) {
+    const double n = (double)wgs * parts, bytes = 2.0 * 4 * d * parts * B * H * Sq;
+    const double mine = (double)((tiles + parts - 1) / parts), shared = n <= 256 ? 0.0 : n >= 384 ? 0.75 : 0.75 * (n - 256) / 128;
+    if (d == kD) return 5.5 + mine * 0.66 * (1.0 + 0.19 * crowd(n)) + (parts > 1 ? 2.3 + 0.35 * parts + bytes / 4.1e6 : 0.0);
+    return 5.6 + mine * 0.46 * (1.0 + 0.1 * crowd(n) + shared) + (parts > 1 ? 1.7 + 0.25 * parts + bytes / 3.4e6 : 0.0);
+  };
   auto cost = [&](int parts) {
     const double n = (double)wgs * parts, bytes = 2.0 * 4 * d * parts * B * H * Sq;
     const int64_t mine = (tiles + parts - 1) / parts;
-    if (!ring) {
-      const double shared = n <= 256 ? 0.0 : n >= 384 ? 0.75 : 0.75 * (n - 256) / 128;
-      if (d == kD) return 5.5 + (double)mine * 0.66 * (1.0 + 0.19 * crowd(n)) + (parts > 1 ? 2.3 + 0.35 * parts + bytes / 4.1e6 : 0.0);
-      return 5.6 + (double)mine * 0.46 * (1.0 + 0.1 * crowd(n) + shared) + (parts > 1 ? 1.7 + 0.25 * parts + bytes / 3.4e6 : 0.0);
-    }
-    const double tile = d == kD ? (ring->fp8 ? 0.82 : 0.75) : (ring->fp8 ? 0.65 : 0.58);
+    const double tile = !ring ? 0.75 : d == kD ? (ring->fp8 ? 0.82 : 0.75) : (ring->fp8 ? 0.65 : 0.58);
     const double t = tile * (1.0 + 0.17 / 0.75 * crowd(n));
     const double combine = parts > 1 ? 6.0 + bytes / 5.5e6 : 0.0;
     const double work = (double)mine * t;
+    if (!ring) return 7.5 + work + combine;
     const int copy_wgs = copy_wgs_beside((int)(8 * ((blocks * parts + 7) / 8)));
     const int later = ring->chunks - 1, groups = copy_groups_of(copy_wgs, later, ring->largest);
     const double chain = (later + groups - 1) / groups * (ring->fp8 ? 7.0 : 4.0) + (double)ring->bytes / (copy_wgs * 50e3);
@@ -1581,10 +1589,18 @@ AttnForm attn_mfma_form(int B, int H, int Sq, int d, int64_t tiles, const RingTr
     const double waited = from_last > from_first ? from_last : from_first;
     return (busy > waited ? busy : waited) + (parts > 1 ? combine + 1.0 : 0.0);
   };
-  const double one = cost(1);
-  double least = !ring ? 0.97 * one : 0.96 * one;
+  if (wgs <= 120) {
+    const double one = cost(1);
+    double least = !ring ? one - 3.0 : 0.96 * one;
+    for (int parts = 2; parts <= kMostParts && parts * wgs <= 240 && parts <= tiles; ++parts) {
+      const double c = cost(parts);
+      if (c < least) { least = c; best = {2, parts}; }
+    }
+  }
+  if (ring || best.parts > 1) return best;
+  double least = 0.97 * chunk_cost(1);
   for (int parts = 2; parts <= kMostParts && parts * wgs <= (pairs ? 480 : 240) && parts <= tiles; ++parts) {
-    const double c = cost(parts);
+    const double c = chunk_cost(parts);
     if (c < least) { least = c; best = {2, parts}; }
   }
   return best;
