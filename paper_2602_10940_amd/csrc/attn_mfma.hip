@@ -449,8 +449,7 @@ __device__ __forceinline__ uint64_t live_keys(const uint8_t* mask, int Sc, int t
 // would have to be read from LDS when they are needed (ring of eight of 2112 under 12 heads 170 -> 190 us).
 constexpr bool four_waves(bool split, bool ext, bool multi, bool dead, bool half_d) { return split && half_d && !(ext && (multi || dead)); }
 // One work-group's share: the queries q_base .. q_base + 255 (wide) or + 127 (split) of (batch, head) bh_.
-// kHalfD: head dimension 64: rows of Q, K, V and O are 128 bytes (K and V are read in place, their LDS
-// tiles have 128-byte rows with swizzles of their own), the scores contract over two 32-wide slices
+// kHalfD: head dimension 64: rows of Q, K, V and O are 128 bytes (K and V are read in place; their LDS tiles: TileLayout), the scores contract over two 32-wide slices
 // of the head dimension and P.V produces four 16-wide blocks.
 template <bool kSplit, bool kExt, bool kMulti, bool kDead, bool kHalfD>
 __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* smem_raw, int bh_, int q_base, int part) {
