@@ -68,7 +68,6 @@ struct TileLayout {
 // of work-groups whatever the head count.  The grid holds 8 * ceil(items / 8) ids; ids past the
 // last item return false.
 constexpr int kXcds = 8;
-constexpr int kMostParts = 16;
 constexpr int kSplitBelowWGs = 128;   // use the key-split kernel when 256-query work-groups number at most this
 __device__ __forceinline__ bool wg_to_tile(int attn_wgs, int nqb, int bh_total, int& bh, int& qb, int lead = 0) {
   const int id = blockIdx.x - lead;                   // the copy work-groups are the last ids of the grid, or the first `lead` (a multiple of 8)
@@ -1532,7 +1531,10 @@ int64_t attn_mfma_max_dead_tiles() { return kMaxWords; }
 // bits in the mean of 18 launches, 1.16 at most.
 // Measured, 1 against the chosen number of parts: H = 3, Sq = 4608, 4608 keys 57 -> 39 us; H = 1, Sq = 256, 4608 keys 57 -> 19 us.
 // One chunk of 500 to 2600 keys, d = 64 or 128, bf16 or FP8, 35 random shapes that take parts: 0.54 to 0.97 of the time.
-// At most 240 work-groups (d = 64, one chunk: 480, two to a CU), so that the copy work-groups of the same launch (16 at least) find a CU (one chunk, which has none, is held to it too).
+// At most 240 work-groups, so that the copy work-groups of the same launch (16 at least) find a CU (one chunk, which has none, is held to it too); 480 where
+// two fit a CU (one chunk of d = 64, four_waves).  FP8 with dead keys has one to a CU, and beyond 240 parts would be a second round.  (From FP8, d = 64, us undivided
+// and in two parts: 11 heads of 1500, 4500 keys 55.6, 64.6; 17 of 1000, 4608 keys of which 300 masked 61.4, 70.1; 8 of 2100, 3500 keys 40.9, 52.1.  Three parts
+// for two rounds gain above 4000 keys, 13 of 1500, 4500 keys 56.3, 52.6, and lose below: 8 of 2100, 3500 keys 44.7; they are not taken.)
 //
 // (The constants of a ring are older: the prologue and the transfers have become shorter since, by 2 to 3 us and by a third.  On random launches the
 // choice takes 4 to 5 % more than the best number of parts on average, 1.5 times as much at most.)
@@ -1553,13 +1555,13 @@ int64_t attn_mfma_max_dead_tiles() { return kMaxWords; }
 // keys 16.1, 12.2; d = 64, 336 blocks, 4608 keys 154, 128, 2048 keys 73.5, 63.7, 522 blocks, 4143 keys 227, 209.  Of 350 random launches, bf16, FP8 and
 // masked, 30 take it, in 0.70 to 0.98 of the time; of 400 more 26, one of them (FP8, d = 64, 360 blocks, 1024 keys) in 1.02.  Their error against 64 bits is 0.96 to
 // 1.00 of the other form's, with outliers, where the two forms' references differ, 0.86 to 1.05 (mean 1.00), lse 0.3 to 1.0.
-AttnForm attn_mfma_form(int B, int H, int Sq, int d, int64_t tiles, const RingTransfers* ring) {
+AttnForm attn_mfma_form(int B, int H, int Sq, int d, int64_t tiles, const RingTransfers* ring, bool fp8, bool dead, int most) {
   const int64_t blocks = (int64_t)B * H * ((Sq + kQPerWGSplit - 1) / kQPerWGSplit), wgs = 8 * ((blocks + 7) / 8);
   AttnForm best = {0, 1};
-  const bool pairs = !ring && d != kD;   // two work-groups to a CU
+  const bool pairs = !ring && four_waves(true, fp8, false, dead, d != kD);   // two work-groups to a CU (whose launch has a rule of its own, narrow_takes_split)
   if (wgs > 120) {
     const int64_t wide = (int64_t)B * H * ((Sq + kQPerWG - 1) / kQPerWG);
-    if (!ring && (wide <= 256 ? wgs <= 256 : d != kD)) best.variant = attn_mfma_ring_form(B, H, Sq, d, tiles, 1, 0).split ? 2 : 0;
+    if (!ring && !pairs && (wide <= 256 ? wgs <= 256 : d != kD)) best.variant = attn_mfma_ring_form(B, H, Sq, d, tiles, 1, 0).split ? 2 : 0;
     if (!pairs || wgs > 240) return best;
   }
   auto crowd = [](double n) { return n <= 128 ? 0.0 : n >= 216 ? 1.0 : (n - 128) / 88; };   // how far work-groups take each other's time
@@ -1591,14 +1593,14 @@ AttnForm attn_mfma_form(int B, int H, int Sq, int d, int64_t tiles, const RingTr
   if (wgs <= 120) {
     const double one = cost(1);
     double least = !ring ? one - 3.0 : 0.96 * one;
-    for (int parts = 2; parts <= kMostParts && parts * wgs <= 240 && parts <= tiles; ++parts) {
+    for (int parts = 2; parts <= most && parts * wgs <= 240 && parts <= tiles; ++parts) {
       const double c = cost(parts);
       if (c < least) { least = c; best = {2, parts}; }
     }
   }
   if (ring || best.parts > 1) return best;
   double least = 0.97 * chunk_cost(1);
-  for (int parts = 2; parts <= kMostParts && parts * wgs <= (pairs ? 480 : 240) && parts <= tiles; ++parts) {
+  for (int parts = 2; parts <= most && parts * wgs <= (pairs ? 480 : 240) && parts <= tiles; ++parts) {
     const double c = chunk_cost(parts);
     if (c < least) { least = c; best = {2, parts}; }
   }

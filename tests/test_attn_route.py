@@ -62,6 +62,32 @@ def test_parts_of_one_chunk(B, H, d, Sq, keys, parts):
     assert got == 1 or need >= 4 * got * B * H * Sq * (d + 2)
 
 
+# B, H, Sq, keys, masked: FP8, d = 64.  Dead keys (a mask, a ragged end) leave one work-group to a CU, whole unmasked tiles two
+CROWDED = [(1, 11, 1500, 4500, False), (1, 9, 2048, 4600, False), (1, 13, 1500, 4500, False), (1, 17, 1000, 4608, True), (1, 17, 1000, 4600, False),
+           (1, 17, 1000, 4600, True), (1, 8, 2100, 3500, False), (2, 5, 2048, 4608, True), (1, 30, 1024, 16384, True)]
+
+
+@pytest.mark.parametrize("B,H,Sq,keys,masked", CROWDED)
+def test_parts_of_a_form_with_one_work_group_to_a_cu_take_one_round(B, H, Sq, keys, masked):
+    """More than 120 work-groups undivided: two parts would be a second round of work-groups."""
+    assert 120 < 8 * -(-B * H * -(-Sq // 128) // 8) <= 240
+    assert _route(B, H, 64, Sq, (keys,), fp8=True, masked=masked).parts == 1
+
+
+def test_a_mask_takes_parts_only_from_the_form_that_it_changes():
+    assert _route(1, 17, 64, 1000, (4608,), fp8=True).parts > 1
+    for B, H, d, Sq, keys, parts in SHARED:      # bf16: the same with a mask
+        assert _route(B, H, d, Sq, (keys,), masked=True) == _route(B, H, d, Sq, (keys,))
+    for H, Sq, keys in ((2, 300, 4096), (6, 1500, 3000), (1, 64, 960)):      # FP8, few query blocks: parts within one round, mask or not
+        for k in (keys // 64 * 64, keys // 64 * 64 - 1):
+            for masked in (False, True):
+                parts = _route(1, H, 64, Sq, (k,), fp8=True, masked=masked).parts
+                assert parts > 1 and (parts * 8 * -(-H * -(-Sq // 128) // 8) <= 240 or not (masked or k % 64))
+        whole = (keys // 64 * 64,)               # the workspace has room for either
+        most = max(_route(1, H, 64, Sq, whole, fp8=True, masked=m).parts for m in (False, True))
+        assert b.usp_ring_attn_workspace_bytes(_desc(1, H, 64, Sq, whole, fp8=True)) >= 4 * H * Sq * 66 * most
+
+
 def test_parts_never_outnumber_what_a_second_launch_takes():
     for d in (64, 128):
         for heads in (1, 2, 7, 24, 60):
