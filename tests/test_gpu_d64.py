@@ -137,6 +137,26 @@ def test_d64_two_work_groups_to_a_cu(H, Sq, keys, masked, fp8, split):
         _assert_parity(host_f64(x[:, heads]), host_f64(y[:, heads]), ro, rl)
 
 
+@pytest.mark.parametrize("fp8", [False, True])
+@pytest.mark.parametrize("lens", [(64,), (128,), (1088,), (64, 192), (320, 64, 576)])
+def test_d64_256_query_form_with_a_mask_that_masks_nothing(lens, fp8):
+    """The form for dead keys, whose tiles lie otherwise in LDS (V's rows whole, from FP8), gives the bits of the one for none."""
+    import paper_2602_10940_amd as P
+    B, H, Sq = 2, 3, 530
+    g = torch.Generator(device=DEV)
+    g.manual_seed(sum(lens))
+    q, *kv = (torch.randn((B, H, s, 64), generator=g, device=DEV).bfloat16() for s in (Sq,) + lens + lens)
+    k, v, kw = kv[:len(lens)], kv[len(lens):], {}
+    if fp8:
+        ks, vs = ([P.usp_fp8_quant(x.reshape(-1, 64)) for x in y] for y in (k, v))
+        k, v = ([c.reshape(B, H, -1, 64) for c, _ in y] for y in (ks, vs))
+        kw = {"k_scales": [s.reshape(B, H, -1) for _, s in ks], "v_scales": [s.reshape(B, H, -1) for _, s in vs]}
+    flags = P.USP_ATTN_KERNEL_WIDE
+    o, l = P.usp_ring_attn_fwd(q, k, v, flags=flags, **kw)
+    om, lm = P.usp_ring_attn_fwd(q, k, v, flags=flags, key_mask=[torch.ones((B, n), dtype=torch.uint8, device=DEV) for n in lens], **kw)
+    assert torch.isfinite(o.float()).all() and torch.equal(o, om) and torch.equal(l, lm)
+
+
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("H,Sq,keys,masked", [(1, 100, 1024, (0, 0)),         # (100 rows: the last work-group of the second launch half full)
                                               (1, 257, 4000, (0, 0)), (2, 33, 4096, (64, 2100)), (3, 130, 960, (959, 960)), (1, 7, 16384, (0, 0))])
