@@ -610,9 +610,9 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
   uint32_t k_off[kLoads], v_off[kLoads];
 #pragma unroll
   for (int j = 0; j < kLoads; ++j) {
-    const uint32_t row = dma_row + j * Layout::kGroup;
-    k_off[j] = (row + dma_i) * rowB + kBias + dma_k(dma_row / Layout::kGroup + j) - j * Layout::kPitchK;
-    v_off[j] = (row + dma_iv) * rowB + kBias + dma_v - j * Layout::kPitchV;
+    const uint32_t row = (uint32_t)(dma_row + j * Layout::kGroup + dma_i) * rowB + kBias;
+    k_off[j] = row + dma_k(dma_row / Layout::kGroup + j) - j * Layout::kPitchK;
+    v_off[j] = (kRowsV ? (uint32_t)(dma_row + j * Layout::kGroup + dma_iv) * rowB + kBias : row) + dma_v - j * Layout::kPitchV;
   }
   const uint32_t lds_k = __builtin_amdgcn_readfirstlane(lds_base + dma_row / Layout::kGroup * Layout::kPitchK);
   const uint32_t lds_v = __builtin_amdgcn_readfirstlane(lds_base + kStagesK * kStageB + dma_row / Layout::kGroup * Layout::kPitchV);
@@ -770,11 +770,10 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
     const int kr = r & (Layout::kGroup - 1);
     k_rd = (lds_cptr)(uintptr_t)(lds_base + r / Layout::kGroup * Layout::kPitchK + kr * 64 + ((g ^ Layout::swap_k(r >> 2)) << 4));
     const int vrow = 4 * g + (r >> 2), vr = vrow & (Layout::kGroup - 1);   // the key this lane names in a transposing read (plus 32*kk, plus 16)
-    const uint32_t v0 = lds_base + kStagesK * kStageB + vrow / Layout::kGroup * Layout::kPitchV + 8 * (r & 3);
-    if (kRowsV)
+    const uint32_t v0 = lds_base + kStagesK * kStageB + vrow / Layout::kGroup * Layout::kPitchV + vr * (kRowsV ? RB : 64) + 8 * (r & 3);
+    v_rd[0] = (lds_cptr)(uintptr_t)(v0 + (kHalfD && !kRowsV ? (vr >> 2) * 32 : 0));
 #pragma unroll
-      for (int db = 0; db < (kRowsV ? 4 : 1); ++db) v_rd[db] = (lds_cptr)(uintptr_t)(v0 + vr * RB + ((db ^ (vr >> 1 & 3)) << 5));
-    else v_rd[0] = (lds_cptr)(uintptr_t)(v0 + vr * 64 + (kHalfD ? (vr >> 2) * 32 : 0));
+    for (int db = 0; db < (kRowsV ? 4 : 0); ++db) v_rd[db] = (lds_cptr)(uintptr_t)(v0 + ((db ^ (vr >> 1 & 3)) << 5));
   }
   // kExt: this lane's keys of a tile are rows 16*mb + 4*g + (0..3), mb = 0..3
   const lds_cptr x_rd = (lds_cptr)(uintptr_t)(lds_ext + 16 * g);
