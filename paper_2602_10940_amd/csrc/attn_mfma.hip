@@ -1575,7 +1575,7 @@ AttnForm attn_mfma_form(int B, int H, int Sq, int d, int64_t tiles, const RingTr
   const bool pairs = !ring && four_waves(true, fp8, false, dead, d != kD);   // two work-groups to a CU (whose launch has a rule of its own, narrow_takes_split)
   if (wgs > 120) {
     const int64_t wide = (int64_t)B * H * ((Sq + kQPerWG - 1) / kQPerWG);
-    if (!ring && !pairs && (wide <= 256 ? wgs <= 256 : d != kD)) best.variant = attn_mfma_ring_form(B, H, Sq, d, tiles, 1, 0).split ? 2 : 0;
+    if (!ring && !pairs && (wide <= 256 ? wgs <= 256 : d != kD)) best.variant = attn_mfma_ring_form(B, H, Sq, d, tiles, 1, 0, fp8).split ? 2 : 0;
     if (!pairs || wgs > 240) return best;
   }
   auto crowd = [](double n) { return n <= 128 ? 0.0 : n >= 216 ? 1.0 : (n - 128) / 88; };   // how far work-groups take each other's time
@@ -1622,34 +1622,53 @@ AttnForm attn_mfma_form(int B, int H, int Sq, int d, int64_t tiles, const RingTr
 }
 
 // How one launch over a ring is decomposed, and whether it is expected to beat a launch per chunk (bf16 chunks,
-// all of them at hand).  variant: as AttnStep::variant, 1 and 2 force a form and are judged by that one.
+// all of them at hand).  variant: as AttnStep::variant, 1 and 2 force a form and are judged by that one.  fp8: chunks decoded from FP8.
 // Up to one round of 256-query blocks on the 256 CUs the one launch is always the better; key-split there where
-// the blocks number at most kSplitBelowWGs or their halves, which take about 0.55 of a block's time, fit a round.
+// the blocks number at most kSplitBelowWGs or their halves, which take about 0.55 of a block's time, fit a round.  (d = 64 from bf16, two key-split
+// work-groups to a CU, would gain up to 13 % with more halves than that where chunks are long and at hand, and lose up to 23 % with the
+// transfers inside: 210 blocks, 40 tiles, eight chunks 64.4 us 256-query, 79.5 key-split.  It is left alone.)
 // Beyond, in microseconds, with `rounds` of the work-groups over the CUs: 256-query work-groups
-// rounds * (10.8 + 1.46 * tiles), d = 64 (8.0 + 1.13 * tiles); key-split ones rounds * (9.6 + 0.73 * tiles) and 0.116
-// per tile and 256 work-groups (idle CUs let the others clock higher), d = 64 (7.1 + 0.47 * tiles) and 0.16; a launch
-// per chunk 10.5 (d = 64: 1.1) each, 5.3 (6.5) per chunk and round, 1.48 (1.12) per tile and round, the last round counting
-// 0.6 where the mixed launch can halve its blocks (d = 128; fitted when those of the last round alone were: with less than 96 of them it takes 4 % less now), and 0.115 (0.22) per MB of the carried fp32 O, out and
-// back between two chunks.  70 rings of 260 to 864 blocks, two to eight chunks of 64 to 4096 keys, all three timed, with the
+// rounds * (10.8 + 1.46 * tiles), d = 64 from FP8 (8.0 + 1.13 * tiles); key-split ones rounds * (9.6 + 0.73 * tiles) and 0.116
+// per tile and 256 work-groups (idle CUs let the others clock higher), d = 64 from FP8 (7.1 + 0.47 * tiles) and 0.16; a launch
+// per chunk 10.5 each, 5.3 per chunk and round, 1.48 per tile and round, the last round counting
+// 0.6 where the mixed launch can halve its blocks (fitted when those of the last round alone were: with less than 96 of them it takes 4 % less now), and 0.115
+// per MB of the carried fp32 O, out and back between two chunks.  70 rings of 260 to 864 blocks, two to eight chunks of 64 to 4096 keys, all three timed, with the
 // prologue 2 to 3 us longer than it is now: each estimate within 12 % (d = 128: 9 %).  Per chunk, 256-query, key-split: B = 2, H = 24, Sq = 4608, two of 1536
-// 370, 331, 363 us; B = 2, H = 22, d = 64, Sq = 4416, two of 128 92, 47, 62; H = 24, Sq = 2816, four of 1024 245,
-// 208, 184; B = 2, H = 18, Sq = 3629, two of 3008 430, 456, 432 (left per chunk).
-RingForm attn_mfma_ring_form(int B, int H, int Sq, int d, int64_t tiles, int chunks, int variant) {
+// 370, 331, 363 us; H = 24, Sq = 2816, four of 1024 245, 208, 184; B = 2, H = 18, Sq = 3629, two of 3008 430, 456, 432 (left per chunk).
+// d = 64 from bf16, where two key-split work-groups share a CU (four_waves): 256-query ones rounds * (5.8 + 1.04 * tiles), key-split ones
+// 4.5 + 1.2 * chunks + 0.944 * tiles for two on a CU and 4.0 + 0.485 * tiles for one.  380 rings of 257 to 2200 blocks, two to twelve chunks of 64 to 4608
+// keys, whole, ragged and masked, every form timed with the chunks at hand and with the transfers inside, which take the same form: 115 become key-split by
+// these figures that were not by the ones for one to a CU, which stood here, in 0.87 of the time in the mean (0.76 to 0.97), with the
+// transfers inside 0.90 (1.004 at most); of 130 rings that were not fitted to 20, in 0.91 (0.998) and 0.93 (1.02).  The error against 64 bits is 0.996 of the
+// other form's in the mean (1.003 at most, with outliers 1.08), lse's 0.47 (with outliers 1.0).  The cost per chunk is higher than the chunks at hand ask
+// for, so that many short ones stay 256-query: 408 blocks, 64 tiles, eight chunks 139.5, 132.2, with the transfers inside 148.6, 160.4.  So do less than
+// six tiles in more than one round: 340 blocks, four tiles 18.9, 16.6, with the transfers inside 22.8, 26.1; six 22.4, 19.2 and 26.3, 23.3.  24 heads of 4608,
+// two of 2304 154.6, 144.9.  A launch per chunk took 1.02 to 4 times the better one's time throughout (352 tiles in two chunks 525, 512).
+RingForm attn_mfma_ring_form(int B, int H, int Sq, int d, int64_t tiles, int chunks, int variant, bool fp8) {
   const int64_t blocks = (int64_t)B * H * ((Sq + kQPerWG - 1) / kQPerWG), halves = (int64_t)B * H * ((Sq + kQPerWGSplit - 1) / kQPerWGSplit);
   if (blocks <= 256) {
     const int64_t w256 = (blocks + 7) / 8 * 8, w128 = (halves + 7) / 8 * 8;   // (as the grid rounds them)
     return {variant == 2 || (variant != 1 && (w256 <= kSplitBelowWGs || w128 <= 256)), true};
   }
-  const bool narrow = d != kD;
   const int64_t r256 = (blocks + 255) / 256, r128 = (halves + 255) / 256, rem = blocks % 256;
   const double n = (double)tiles;
-  const double wide = (double)r256 * (narrow ? 8.0 + 1.13 * n : 10.8 + 1.46 * n);
-  const double split = narrow ? (double)r128 * (7.1 + 0.47 * n) + 0.16 * n * (double)halves / 256.0
-                              : (double)r128 * (9.6 + 0.73 * n) + 0.116 * n * (double)halves / 256.0;
-  const double rounds = (double)(blocks / 256) + (rem == 0 ? 0.0 : !narrow && rem <= 128 ? 0.6 : 1.0);
+  if (d != kD) {
+    double wide, split;
+    if (four_waves(true, fp8, true, false, true)) {
+      wide = (double)r256 * (5.8 + 1.04 * n);
+      split = (double)(r128 / 2) * (4.5 + 1.2 * chunks + 0.944 * n) + (r128 % 2 ? 4.0 + 0.485 * n : 0.0);
+      if (r128 > 2 && tiles < 6) split = wide;
+    } else {
+      wide = (double)r256 * (8.0 + 1.13 * n);
+      split = (double)r128 * (7.1 + 0.47 * n) + 0.16 * n * (double)halves / 256.0;
+    }
+    return {variant == 2 || (variant != 1 && split < wide), true};
+  }
+  const double wide = (double)r256 * (10.8 + 1.46 * n);
+  const double split = (double)r128 * (9.6 + 0.73 * n) + 0.116 * n * (double)halves / 256.0;
+  const double rounds = (double)(blocks / 256) + (rem == 0 ? 0.0 : rem <= 128 ? 0.6 : 1.0);
   const double carry = 2.0 * 4 * d * B * H * Sq / 1e6;
-  const double stepwise = chunks * (narrow ? 1.1 + 6.5 * rounds : 10.5 + 5.3 * rounds) + rounds * n * (narrow ? 1.12 : 1.48) +
-                          (chunks - 1) * carry * (narrow ? 0.22 : 0.115);
+  const double stepwise = chunks * (10.5 + 5.3 * rounds) + rounds * n * 1.48 + (chunks - 1) * carry * 0.115;
   const bool take_split = variant == 2 || (variant != 1 && split < wide);
   return {take_split, (take_split ? split : wide) < 0.97 * stepwise};
 }
@@ -1707,7 +1726,7 @@ usp_status launch_attn_mfma(const AttnStep& step, hipStream_t st) {
     // (there is no mixed form of this launch)
     int64_t tiles = 0;
     for (int c = 0; c < s.n_multi; ++c) tiles += (s.chunk[c].Sc + kTile - 1) / kTile;
-    const bool split = attn_mfma_ring_form(s.B, s.H, s.Sq, s.d, tiles, s.n_multi, s.variant).split;
+    const bool split = attn_mfma_ring_form(s.B, s.H, s.Sq, s.d, tiles, s.n_multi, s.variant, s.multi_fp8).split;
     const unsigned wgs = split ? w128 : w256;
     s.grid_wgs = (int)wgs;
     s.tiles = (int)tiles;

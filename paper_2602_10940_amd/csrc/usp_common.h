@@ -200,7 +200,7 @@ AttnForm attn_mfma_form(int B, int H, int Sq, int d, int64_t tiles, const RingTr
 constexpr int kMostParts = 16;   // of the keys of a query block, on the matrix-core path
 // One launch over a ring: key-split or 256-query work-groups, and whether it is expected to beat a launch per chunk
 struct RingForm { bool split, pays; };
-RingForm attn_mfma_ring_form(int B, int H, int Sq, int d, int64_t tiles, int chunks, int variant);
+RingForm attn_mfma_ring_form(int B, int H, int Sq, int d, int64_t tiles, int chunks, int variant, bool fp8);
 // tiles a launch over several chunks takes if some of its keys are dead (a mask, a ragged chunk)
 int64_t attn_mfma_max_dead_tiles();
 // A value that no launch of this process has had, its lower 16 bits zero.  Of other processes' only by a chance of 2^-48 and for

@@ -100,10 +100,19 @@ def test_parts_never_outnumber_what_a_second_launch_takes():
 
 
 # us of a launch per chunk, one launch of 256-query work-groups, one key-split launch (all chunks at hand)
-MEASURED = [(2, 24, 128, 4608, 2, 1536, 370, 331, 363), (2, 22, 64, 4416, 2, 128, 92, 47, 62), (2, 19, 64, 3621, 2, 128, 71, 37, 46),
-            (1, 22, 128, 3112, 2, 128, 57, 32, 39), (1, 24, 128, 2816, 4, 1024, 245, 208, 184), (1, 20, 128, 3500, 3, 2048, 302, 302, 261),
-            (2, 15, 64, 2149, 6, 384, 189, 99, 63), (2, 13, 128, 2384, 6, 256, 214, 92, 64), (2, 22, 64, 1725, 6, 3328, 810, 701, 544),
-            (2, 21, 128, 1865, 8, 1216, 563, 470, 410), (2, 18, 128, 3629, 2, 3008, 430, 456, 432), (2, 14, 64, 4544, 2, 960, 114, 84, 96)]
+MEASURED = [(2, 24, 128, 4608, 2, 1536, 370, 331, 363), (1, 22, 128, 3112, 2, 128, 57, 32, 39), (1, 24, 128, 2816, 4, 1024, 245, 208, 184),
+            (1, 20, 128, 3500, 3, 2048, 302, 302, 261), (2, 13, 128, 2384, 6, 256, 214, 92, 64), (2, 21, 128, 1865, 8, 1216, 563, 470, 410),
+            (2, 18, 128, 3629, 2, 3008, 430, 456, 432)]
+# d = 64, two key-split work-groups to a CU.  us of a launch per chunk (any form, 256-query, key-split), one launch of 256-query work-groups, one
+# key-split launch, and these two with the transfers inside
+MEASURED_64 = [(2, 22, 4416, 2, 128, (66.2, 66.5, 57.1), (36.7, 34.1), (42.8, 44.9)), (2, 19, 3621, 2, 128, (49.7, 49.5, 43.3), (27.1, 24.4), (32.3, 35.3)),
+               (2, 15, 2149, 6, 384, (86.7, 142.1, 86.1), (82.3, 44.1), (88.9, 66.6)), (2, 22, 1725, 6, 3328, (498.6, 701.5, 494.5), (633.2, 445.0), (634.8, 478.9)),
+               (2, 14, 4544, 2, 960, (79.8, 90.6, 80.1), (71.5, 68.6), (83.6, 74.0)), (1, 24, 4608, 2, 2304, (155.4, 171.1, 155.6), (154.6, 144.9), (155.6, 146.5)),
+               (1, 17, 4300, 8, 512, (173.4, 230.4, 173.3), (137.9, 100.4), (146.2, 119.7)), (1, 17, 5000, 2, 128, (29.1, 32.8, 29.1), (18.9, 16.6), (22.8, 26.1)),
+               (1, 17, 5000, 2, 192, (31.5, 37.2, 31.6), (22.4, 19.2), (26.3, 23.3)), (2, 24, 3900, 8, 832, (424.0, 498.8, 424.9), (335.8, 316.3), (377.4, 326.9)),
+               (1, 300, 100, 2, 128, (18.0, 26.3, 18.0), (18.3, 12.0), (31.4, 25.5)), (1, 24, 4096, 12, 128, (205.0, 233.7, 204.7), (60.2, 49.3), (74.4, 68.6)),
+               (1, 20, 4608, 2, 11264, (525.3, 733.9, 522.5), (721.6, 511.9), (722.7, 515.3)), (1, 17, 4096, 2, 320, (34.3, 42.9, 34.7), (30.3, 24.1), (32.8, 27.5)),
+               (2, 17, 2921, 8, 512, (249.9, 248.9, 221.6), (139.7, 130.5), (150.0, 160.8))]
 
 
 @pytest.mark.parametrize("B,H,d,Sq,n,chunk,stepwise,wide,split", MEASURED)
@@ -119,6 +128,31 @@ def test_more_than_one_round_of_query_blocks_runs_the_form_that_was_judged(B, H,
         f = _route(B, H, d, Sq, (chunk,) * n, flags=flag)
         assert (us if f.one_launch else stepwise) <= 1.05 * min(us, stepwise)
         assert not f.one_launch or f.split == (flag == b.USP_ATTN_KERNEL_SPLIT)
+
+
+@pytest.mark.parametrize("B,H,Sq,n,chunk,stepwise,at_hand,inside", MEASURED_64)
+def test_d64_rings_above_one_round_run_the_faster_form(B, H, Sq, n, chunk, stepwise, at_hand, inside):
+    """One form for both ways a ring's chunks come: the faster with the chunks at hand, unless that is the slower one with the transfers inside."""
+    lens, pre = (chunk,) * n, b.USP_ATTN_FUSED_PREFETCH
+    r, p = _route(B, H, 64, Sq, lens), _route(B, H, 64, Sq, lens, flags=pre)
+    assert B * H * -(-Sq // 256) > 256 and r.one_launch and p.one_launch and r.split == p.split
+    assert inside[r.split] <= 1.05 * min(inside)
+    assert at_hand[r.split] <= 1.05 * min(at_hand) or inside[not r.split] > inside[r.split]
+    for split, flag in ((False, b.USP_ATTN_KERNEL_WIDE), (True, b.USP_ATTN_KERNEL_SPLIT)):      # a forced form, against a launch per chunk in that form
+        f = _route(B, H, 64, Sq, lens, flags=flag)
+        assert f.one_launch and f.split == split and at_hand[split] <= 1.05 * stepwise[1 + split]
+    assert min(at_hand) <= min(stepwise)
+
+
+@pytest.mark.parametrize("B,H,Sq,lens,split", [(1, 17, 5000, (128, 64), False), (1, 17, 5000, (192, 192), True), (1, 17, 5000, (320, 321), True),
+                                               (1, 300, 100, (64, 64), True), (1, 24, 4608, (2304, 2304), True), (1, 24, 4608, (2303, 2302), True)])
+def test_d64_rings_from_fp8_are_not_taken_for_two_work_groups_to_a_cu(B, H, Sq, lens, split):
+    """FP8 chunks keep one key-split work-group to a CU; dead keys change nothing about bf16 ones."""
+    pre = b.USP_ATTN_FUSED_PREFETCH
+    assert [_route(B, H, 64, Sq, lens, flags=pre, masked=m).split for m in (False, True)] == [split, split]
+    tiles, blocks, halves = sum(-(-n // 64) for n in lens), B * H * -(-Sq // 256), B * H * -(-Sq // 128)
+    wide = -(-blocks // 256) * (8.0 + 1.13 * tiles)
+    assert _route(B, H, 64, Sq, lens, fp8=True, flags=pre).split == (-(-halves // 256) * (7.1 + 0.47 * tiles) + 0.16 * tiles * halves / 256 < wide)
 
 
 @pytest.mark.parametrize("H,n,fp8", [(12, 3, False), (12, 8, False), (8, 8, False), (20, 3, False), (12, 2, True)])

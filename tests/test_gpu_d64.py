@@ -137,6 +137,34 @@ def test_d64_two_work_groups_to_a_cu(H, Sq, keys, masked, fp8, split):
         _assert_parity(host_f64(x[:, heads]), host_f64(y[:, heads]), ro, rl)
 
 
+@pytest.mark.parametrize("H,Sq,lens,masked,split", [
+    (65, 1025, (64, 64), (0, 0), False),          # 325 blocks of 256, 585 of 128: two rounds, three work-groups to a CU
+    (65, 1025, (192, 192), (0, 0), True),
+    (65, 1025, (128, 320), (100, 300), True),     # dead tiles in the middle
+    (65, 1025, (320, 321), (0, 0), True),         # ragged
+    (26, 4096, (320, 320), (0, 0), False),        # 416 and 832: two rounds, four to a CU, few tiles
+    (26, 4096, (1024, 1024), (0, 0), True),
+    (300, 100, (64, 64), (0, 0), True),           # one round of pairs
+])
+def test_d64_rings_above_one_round(H, Sq, lens, masked, split):
+    """The form that the rule picks, as its flag gives it, the chunks at hand and with the transfers inside, against the oracle."""
+    import paper_2602_10940_amd as P
+    inp = W.make_attention_inputs(W.Workload("d64_rounds", 97, 1, H, 64, Sq, lens, "bf16", masked_keys=masked))
+    q, k, v = dev_bf16(inp.q), [dev_bf16(x) for x in inp.k], [dev_bf16(x) for x in inp.v]
+    scale = float(inp.softmax_scale)
+    kw = {"key_mask": [torch.from_numpy(x).to(DEV) for x in inp.key_mask]} if masked[1] else {}
+    forms = P.USP_ATTN_KERNEL_WIDE, P.USP_ATTN_KERNEL_SPLIT
+    got = [P.usp_ring_attn_fwd(q, k, v, softmax_scale=scale, flags=f, **kw) for f in (0, P.USP_ATTN_FUSED_PREFETCH, *forms)]
+    torch.cuda.synchronize()
+    (o, l), (op, lp), same, other = got[0], got[1], got[2 + split], got[3 - split]
+    assert torch.equal(o, same[0]) and torch.equal(l, same[1]) and not torch.equal(o, other[0])
+    assert torch.equal(o, op) and torch.equal(l, lp)
+    heads = [0, H - 1]
+    ro, rl = orc.ring_attention(inp.q[:, heads], [x[:, heads] for x in inp.k], [x[:, heads] for x in inp.v], scale, inp.key_mask if masked[1] else None)
+    for x, y in (got[0], other):
+        _assert_parity(host_f64(x[:, heads]), host_f64(y[:, heads]), ro, rl)
+
+
 @pytest.mark.parametrize("fp8", [False, True])
 @pytest.mark.parametrize("lens", [(64,), (128,), (1088,), (64, 192), (320, 64, 576)])
 def test_d64_256_query_form_with_a_mask_that_masks_nothing(lens, fp8):
