@@ -363,6 +363,7 @@ constexpr int kExtTileB = kTile * 4;   // bytes of one tile's record: the factor
 // LDS of a work-group: K stages | V stages (each with room for a record) | four records | the words of kDead launches (188 000 keys).
 // The epilogue stages each wave's O tile (eight regions from offset 0, over everything else, which is dead by then).
 constexpr int kMaxWords = 2944;
+constexpr int kLdsAlign = 64;   // of the dynamic LDS: d = 64 finds the other half of a row's 64 bytes of V by XOR of the address with 32 (v_operand)
 template <bool kHalfD>
 struct LdsPlan {
   typedef TileLayout<kHalfD> L;
@@ -373,6 +374,7 @@ struct LdsPlan {
   static constexpr int kWordsOff = kExtOff + 4 * kExtTileB;
   static constexpr int kEpilogueB = 8 * EpiLayout<kHalfD>::kWaveB;
   static constexpr int bytes(int words) { return kEpilogueB > kWordsOff + 8 * words ? kEpilogueB : kWordsOff + 8 * words; }
+  static_assert(kStageB % kLdsAlign == 0 && L::kPitchV % (kHalfD ? kLdsAlign : 16) == 0, "rows of V are told apart by address bits");
   static_assert(2 * kQRowsB <= kTileB && kWordsOff % 8 == 0 && bytes(kMaxWords) <= 159 * 1024, "LDS plan");   // (some is left to __syncthreads_or)
 };
 
@@ -1325,7 +1327,7 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
 
 template <bool kSplit, bool kExt, bool kMulti, bool kDead, bool kHalfD>
 __global__ __launch_bounds__(kThreads, four_waves(kSplit, kExt, kMulti, kDead, kHalfD) ? 4 : 2) void attn_pp_kernel(AttnStep s) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
+  extern __shared__ __align__(kLdsAlign) unsigned char smem_raw[];
   touch_step();
   if (!kMulti && (int)blockIdx.x >= s.grid_wgs) {   // prefetch work-group: copy and leave
     prefetch_copy(s, blockIdx.x - s.grid_wgs, threadIdx.x, kThreads);
@@ -1412,7 +1414,7 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(const float* __restri
 // halves of its last s.mix_halves blocks.
 template <bool kExt, bool kDead>
 __global__ __launch_bounds__(kThreads, 2) void attn_pp_mixed_kernel(AttnStep s) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
+  extern __shared__ __align__(kLdsAlign) unsigned char smem_raw[];
   touch_step();
   if ((int)blockIdx.x >= s.grid_wgs) {
     prefetch_copy(s, blockIdx.x - s.grid_wgs, threadIdx.x, kThreads);

@@ -1,6 +1,7 @@
 """Registers of the kernels as built: none keeps a vector register in scratch memory.  A scratch access is a load that the
-matrix-core kernels' counted waits do not count."""
+matrix-core kernels' counted waits do not count.  And where their LDS begins."""
 import os
+import re
 import struct
 
 import pytest
@@ -50,3 +51,12 @@ def test_no_kernel_spills_a_vector_register():
     spilled = {k[".name"]: (k[".vgpr_spill_count"], k[".private_segment_fixed_size"]) for k in kernels
                if k[".vgpr_spill_count"] or k[".private_segment_fixed_size"]}
     assert not spilled
+
+
+def test_lds_of_the_matrix_core_kernels_begins_at_a_multiple_of_64():
+    """d = 64 finds half of V's rows by XOR of a whole LDS address with 32.  What the compiler puts in front of the array (256 bytes for
+    __syncthreads_or today) is not for the source to say, so the array has to ask for it."""
+    text = open(os.path.join(os.path.dirname(B.LIB_PATH), "csrc", "attn_mfma.hip")).read()
+    asked = re.findall(r"extern __shared__ __align__\((\w+)\)", text)
+    values = [int(x) if x.isdigit() else int(re.search(r"constexpr int %s = (\d+);" % x, text).group(1)) for x in asked]
+    assert len(values) == text.count("extern __shared__") == 2 and all(v % 64 == 0 for v in values)
