@@ -95,11 +95,7 @@ usp_status launch_tile_combine(const AttnStep& s, hipStream_t st) {
   };
   if (s.parts <= 2) launch(attn_tile_combine_kernel<T, 2>);
   else if (s.parts <= 4) launch(attn_tile_combine_kernel<T, 4>);
-  else if (s.parts <= 8) launch(attn_tile_combine_kernel<T, 8>);
-  else {
-    set_error("the keys of a query block are shared by at most 8 work-groups (got %d)", s.parts);
-    return USP_ERR_INVALID_ARG;
-  }
+  else launch(attn_tile_combine_kernel<T, kMostShares>);
   USP_CHECK_HIP(hipGetLastError());
   return USP_OK;
 }
@@ -138,7 +134,7 @@ int attn_generic_parts(bool f32, int B, int H, int Sq, int d, int keys) {
   };
   int best = 1;
   double least = 0.93 * cost(1);
-  for (int p = 2; p <= 8 && 2 * p <= tiles && wgs * p <= 768; p *= 2) {
+  for (int p = 2; p <= kMostShares && 2 * p <= tiles && wgs * p <= 768; p *= 2) {
     const double c = cost(p);
     if (c < least) { least = c; best = p; }
   }
@@ -160,6 +156,10 @@ usp_status launch_attn_generic(const AttnStep& step, hipStream_t st) {
   s.copy_wgs = s.n_copy > 0 ? 32 : 0;
   if (s.parts > 1 && (s.mode != 0 || s.n_multi != 1 || s.copy_wgs != 0 || !s.part_o || !s.part_ml)) {
     set_error("a launch that shares keys between work-groups has one chunk, finishes the result and needs room for the shares");
+    return USP_ERR_INVALID_ARG;
+  }
+  if (s.parts > kMostShares) {
+    set_error("the keys of a query block are shared by at most %d work-groups (got %d)", kMostShares, s.parts);
     return USP_ERR_INVALID_ARG;
   }
   int64_t wgs;

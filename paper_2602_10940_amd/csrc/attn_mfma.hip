@@ -1705,6 +1705,10 @@ usp_status launch_attn_mfma(const AttnStep& step, hipStream_t st) {
     set_error("a launch that shares keys between work-groups finishes the result and needs room for the parts (key-split form)");
     return USP_ERR_INVALID_ARG;
   }
+  if (s.parts > kMostParts) {
+    set_error("the keys of a query block are shared by at most %d work-groups (got %d)", kMostParts, s.parts);
+    return USP_ERR_INVALID_ARG;
+  }
   if (s.n_multi > 0) {
     if (s.n_multi > AttnStep::kMaxMulti || s.mode != 0 || s.n_copy != 0 || s.key_mask || s.k_scale || s.v_scale) {   // (n_copy: the per-step form of the transfers)
       set_error("a launch over several chunks takes at most %d chunks and finishes the result", AttnStep::kMaxMulti);

@@ -91,6 +91,11 @@ usp_status usp_diag_attn_route(const usp_attn_desc* desc, int32_t masked, int32_
  *                    that are run as two, and the copy work-groups behind them */
 usp_status usp_diag_mixed_grid(int32_t blocks, int32_t forced, int32_t copies, int32_t* wgs, int32_t* halves, int32_t* copy_wgs);
 
+/* The answer of an attention launch that is asked to share the keys of a query block between `parts` work-groups, more than its second
+ * launch holds.  The launch has no queries, so that nothing runs whatever the answer.
+ *   kind : 0 the matrix-core kernels, 1 and 2 the general kernel on bf16 and on fp32 */
+usp_status usp_diag_too_many_parts(int32_t kind, int32_t parts);
+
 #ifdef __cplusplus
 }
 #endif

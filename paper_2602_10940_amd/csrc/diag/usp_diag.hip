@@ -296,4 +296,22 @@ usp_status usp_diag_mixed_grid(int32_t blocks, int32_t forced, int32_t copies, i
   return USP_OK;
 }
 
+usp_status usp_diag_too_many_parts(int32_t kind, int32_t parts) {
+  clear_error();
+  USP_CHECK_ARG(kind >= 0 && kind <= 2, "kind=%d out of range", kind);
+  USP_CHECK_ARG(parts > (kind == 0 ? kMostParts : kMostShares), "parts=%d are not too many", parts);
+  float room[2] = {0.0f, 0.0f};
+  AttnStep s = {};
+  s.B = s.H = 1;
+  s.Sq = 0;
+  s.Sc = 64;
+  s.d = 64;
+  s.half_d = kind == 0 ? 1 : 0;
+  s.variant = 2;
+  s.parts = parts;
+  s.part_o = s.part_ml = room;
+  s.qo_dtype = s.kv_dtype = kind == 2 ? USP_F32 : USP_BF16;
+  return kind == 0 ? launch_attn_mfma(s, nullptr) : launch_attn_generic(s, nullptr);
+}
+
 }  // extern "C"

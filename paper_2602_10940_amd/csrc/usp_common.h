@@ -197,7 +197,8 @@ MixedGrid attn_mfma_mixed_grid(int items, bool forced, bool copies);
 struct RingTransfers { int chunks; int64_t bytes, largest, last_tiles; bool fp8; };
 // ring: null for a launch over one chunk, and of that: decoded from FP8; some of its keys are dead (a mask, a ragged end); most: parts at most
 AttnForm attn_mfma_form(int B, int H, int Sq, int d, int64_t tiles, const RingTransfers* ring, bool fp8, bool dead, int most);
-constexpr int kMostParts = 16;   // of the keys of a query block, on the matrix-core path
+// parts of the keys of a query block at most, of which a second launch holds all at once: matrix-core kernels, general kernel
+constexpr int kMostParts = 16, kMostShares = 8;
 // One launch over a ring: key-split or 256-query work-groups, and whether it is expected to beat a launch per chunk
 struct RingForm { bool split, pays; };
 RingForm attn_mfma_ring_form(int B, int H, int Sq, int d, int64_t tiles, int chunks, int variant, bool fp8);

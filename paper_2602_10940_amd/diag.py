@@ -44,6 +44,8 @@ def load_diag_library() -> ctypes.CDLL:
     lib.usp_diag_attn_route.argtypes = [ctypes.POINTER(B.AttnDesc), i32] + [ctypes.POINTER(i32)] * 3
     lib.usp_diag_mixed_grid.restype = i32
     lib.usp_diag_mixed_grid.argtypes = [i32, i32, i32] + [ctypes.POINTER(i32)] * 3
+    lib.usp_diag_too_many_parts.restype = i32
+    lib.usp_diag_too_many_parts.argtypes = [i32, i32]
     _diag = lib
     return lib
 
@@ -124,6 +126,11 @@ def usp_diag_mixed_grid(blocks: int, forced: bool = False, copies: bool = False)
     out = [ctypes.c_int32() for _ in range(3)]
     B._check(lib.usp_diag_mixed_grid(int(blocks), 1 if forced else 0, 1 if copies else 0, *[ctypes.byref(x) for x in out]))
     return MixedGrid(*[x.value for x in out])
+
+
+def usp_diag_too_many_parts(kind: int, parts: int) -> None:
+    """Raises what an attention launch (0 matrix-core, 1 general bf16, 2 general fp32) says to more parts than its second launch holds."""
+    B._check(load_diag_library().usp_diag_too_many_parts(int(kind), int(parts)))
 
 
 def usp_diag_ring_attn_fwd_wait(q: torch.Tensor, k_chunks: Sequence[torch.Tensor], v_chunks: Sequence[torch.Tensor],

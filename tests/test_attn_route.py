@@ -264,3 +264,11 @@ def test_the_shares_of_a_general_call(d, f32):
                 # fp32 O~ and (m, l) of every share, and nothing where the keys stay together
                 rows = heads * Sq
                 assert need == (0 if parts == 1 else sum(-(-4 * n * parts * rows // 256) * 256 for n in (d, 2)))
+
+
+@pytest.mark.parametrize("kind,most", [(0, 16), (1, 8), (2, 8)])
+def test_more_parts_than_the_second_launch_holds_are_refused_in_front_of_the_first(kind, most):
+    for parts in (most + 1, 2 * most, 1 << 20):
+        with pytest.raises(b.UspError, match="at most %d work-groups \\(got %d\\)" % (most, parts)) as e:
+            diag.usp_diag_too_many_parts(kind, parts)
+        assert e.value.status == b.USP_ERR_INVALID_ARG
