@@ -126,6 +126,74 @@ def test_one_key_is_the_row(at, flags, d):
     _assert_parity(host_f64(out), host_f64(lse), *orc.ring_attention(q, [k], [v], 1.0, None))
 
 
+def _rows_of(which):
+    """Of 40 queries, those of the first, the second or both blocks of sixteen that a wave holds."""
+    block = np.arange(40) // 16 % 2
+    return np.ones(40, bool) if which == "both" else block == (which == "second")
+
+
+def _from_fp8(x):
+    """Codes and scales on the GPU, and the values they stand for, float64."""
+    import paper_2602_10940_amd as P
+    c, s = P.usp_fp8_quant(dev_bf16(x).reshape(-1, x.shape[-1]))
+    return c.reshape(x.shape), s.reshape(x.shape[:3]), orc.dequant_exact_f64(c.cpu().numpy().reshape(x.shape), s.cpu().numpy().reshape(x.shape[:3]))
+
+
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("flags", [WIDE, SPLIT])
+@pytest.mark.parametrize("which", ["first", "second", "both"])
+@pytest.mark.parametrize("levels", [(0, 62, 64, 66), (0, 62, 66, 66, 120, 62, 130, 131, 100), (0, 100, 62, 100, 0, 101, 62, 0)])
+def test_references_that_lag_from_fp8(levels, which, flags, d):
+    """Whole unmasked tiles from FP8, where the key-split form of d = 64 certifies one block of sixteen queries after the other: the scores of
+    one block, of the other or of both climb, those of the rest stay 0."""
+    import paper_2602_10940_amd as P
+    rng = np.random.default_rng(7)
+    n = 64 * len(levels)
+    q = np.zeros((1, 2, 40, d), np.float32)
+    q[..., 0] = rng.choice([1.0, 0.75, 0.5], size=(1, 2, 40)) * _rows_of(which)
+    k = np.zeros((1, 2, n, d), np.float32)
+    k[..., 0] = np.repeat(np.asarray(levels, np.float32), 64) - rng.integers(0, 8, size=(1, 2, n)) * 0.5
+    kc, ks, kx = _from_fp8(k)
+    vc, vs, vx = _from_fp8(_bf16(rng.standard_normal((1, 2, n, d))))
+    out, lse = P.usp_ring_attn_fwd(dev_bf16(q), [kc], [vc], k_scales=[ks], v_scales=[vs], softmax_scale=1.0, flags=flags)
+    torch.cuda.synchronize()
+    _assert_parity(host_f64(out), host_f64(lse), *orc.ring_attention(q, [kx], [vx], 1.0, None))
+
+
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("flags", [WIDE, SPLIT])
+@pytest.mark.parametrize("which", ["first", "second", "both"])
+@pytest.mark.parametrize("at", [320, 447])
+def test_one_key_is_the_row_from_fp8(at, which, flags, d):
+    """As test_one_key_is_the_row, for the queries of one block or of both."""
+    import paper_2602_10940_amd as P
+    rng = np.random.default_rng(at)
+    n = 64 * 7
+    rows = _rows_of(which)
+    k = np.zeros((1, 2, n, d), np.float32)
+    k[:, :, 192:, 0] = 100.0
+    k[:, :, at, 0] = 140.0
+    k[:, :, at, 1:3] = 1.0
+    kc, ks, kx = _from_fp8(k)
+    k0, k1, rest = kx[0, 0, at, 0], kx[0, 0, at, 1], kx[0, 0, -1 if at != n - 1 else -2, 0]
+    assert k0 == 140.0 and 0.9 < k1 < 1.1 and abs(rest - 100.0) < 1e-4
+    q = np.zeros((1, 2, 40, d), np.float32)
+    q[..., 0] = rng.choice([1.0, 0.984375, 0.96875, 0.953125], size=(1, 2, 40)) * rows
+    mantissa = rng.choice([1.0033, 1.0045], size=(1, 2, 40))
+    up = q[..., 0].astype(np.float64) * 40 * np.log2(np.e)
+    left = (np.floor(up) + 1 + np.log2(mantissa) - up) / np.log2(np.e) / k1 * rows
+    q[..., 1] = _bf16(left)
+    q[..., 2] = _bf16(left - q[..., 1])
+    vc, vs, vx = _from_fp8(_bf16(rng.standard_normal((1, 2, n, d))))
+    row = _bf16((vc[:, :, at:at + 1].view(torch.float8_e4m3fn).float() * vs[:, :, at:at + 1, None]).cpu().numpy()).astype(np.float64)
+    p = np.exp2(((q[..., 0].astype(np.float64) * 40 + k1 * (q[..., 1].astype(np.float64) + q[..., 2])) * np.log2(np.e)) % 1.0)[..., None]
+    assert np.abs(p[:, :, rows, 0] - mantissa[:, :, rows]).max() < 1e-4 and np.mean((_bf16(_bf16(p) * row / p) != row)[:, :, rows]) > 0.5
+    out, lse = P.usp_ring_attn_fwd(dev_bf16(q), [kc], [vc], k_scales=[ks], v_scales=[vs], softmax_scale=1.0, flags=flags)
+    torch.cuda.synchronize()
+    assert np.array_equal(host_f64(out)[:, :, rows], np.broadcast_to(row, q.shape)[:, :, rows])
+    _assert_parity(host_f64(out), host_f64(lse), *orc.ring_attention(q, [kx], [vx], 1.0, None))
+
+
 @pytest.mark.parametrize("d", [128, 64])
 @pytest.mark.parametrize("fp8", [False, True])
 @pytest.mark.parametrize("H,lens", [(1, (64, 64)), (1, (640, 1)), (3, (321, 319, 322)), (5, (128, 192, 64, 640)), (2, (2048, 2111))])
