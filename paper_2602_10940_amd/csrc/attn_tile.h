@@ -23,18 +23,18 @@
 //
 // What bounds it (bf16, d = 72): the issue of instructions and the bytes that the operand reads return.  Per wave, 16 queries
 // and 32 keys: 80 VALU instructions, 21 MFMAs of 16 cycles, 16 operand reads of 11 KB; with what stands before and behind the tiles
-// the VALU issues for 58 % of the launch's cycles and the matrix cores work for 33 %, mostly one after the other.
+// the VALU issues for 63 % of the launch's cycles and the matrix cores work for 36 %, mostly one after the other.
 // So: one barrier per tile, tiles fetched through descriptors at places fixed per lane (directly to LDS they cost
 // neither registers nor LDS writes), no test of a key outside masked and ragged tiles, no work for 16-wide blocks past the
 // head dimension, O rescaled only when a maximum has outgrown a reference that was set 2^8 above it.  B=2 H=16 S=1024 d=72
-// bf16, a call among others: 29.0 us (32.5 with tiles through registers and four waves; one wave per query row
+// bf16, a call among others: 28.0 us (32.5 with tiles through registers and four waves; one wave per query row
 // with scalar products, the first form, 857); 22 heads of 700 queries and keys 17.8 -> 15.8.
 // (The exponentials against the old reference first, the maximum only where their sum does not show that none exceeds it, and
 // the remainders of the split of P as dot products with -1 were no gain up to d = 128: one work-group on a CU waits for the longer chain
 // of every tile.  16 heads of 1024, FP8, d = 40 29.0 us against 25.5, d = 72 34.2 against 30.7, d = 96 31.5 against 32.7; bf16,
 // d = 40 20.4 against 19.7, d = 56 22.5 against 21.6, 24 heads 26.3 against 25.2.)  fp32 is bound by the fp32 matrix
 // rate from about 256 work-groups on (d = 64, 32 heads: 80 us, 107 TFLOP/s).  Two chunks of 128 keys, H=2 Sq=128 d=64
-// fp32: one launch, 9.9 us a call.
+// fp32: one launch, 9.6 us a call.
 #pragma once
 #include <type_traits>
 
