@@ -1495,16 +1495,17 @@ usp_status launch_pp_any(const AttnStep& s, bool ext, bool dead, bool split, uns
 }
 // A launch over one chunk (or step) of head dimension 64, four waves to a SIMD (four_waves): key-split or 256-query work-groups.  In
 // microseconds, over `tiles` of keys: 256-query work-groups, one to a CU, 6.1 + 1.04 each round; key-split ones 7.8 + 0.88 for two
-// on a CU, 5.6 + 0.53 for one; from FP8 6.5 + 1.06, 9.5 + 0.96 and 6.6 + 0.6.  256-query, key-split: 308 blocks of 128, 128 keys 8.3, 10.1;
-// 380, 448 keys 12.1, 12.6; 270, 1408 keys 27.5, 25.2; 540, 1728 keys 62.9, 44.1; 864, 4608 keys 157, 141; from FP8 270, 1408 keys 32.0,
-// 31.6; 540, 1728 keys 67.3, 53.0.
+// on a CU, 5.6 + 0.53 for one; from FP8 6.5 + 1.0, 5.0 + 0.98 and 4.0 once, and 4.6 + 0.6.  256-query, key-split: 308 blocks of 128, 128 keys 8.3, 10.1;
+// 378, 448 keys 12.6, 13.2; 270, 1408 keys 27.5, 25.2; 540, 1728 keys 62.9, 44.1; 864, 4608 keys 158, 144; from FP8 375, 3136 keys 60.3, 62.4;
+// 513, 192 keys 18.2, 16.9; 540, 1728 keys 67.3, 53.0; 1190, 448 keys 39.1, 35.3.  363 random launches from bf16 take 1.001 of the better one's time in the mean, 1.04 at most,
+// 171 from FP8 1.001 and 1.03 (with 6.5 + 1.06, 9.5 + 0.96 and 6.6 + 0.6, fitted to 256-query work-groups as they were, 1.014 and 1.16: key-split from 30 tiles on).
 bool narrow_takes_split(int64_t blocks, int64_t halves, int tiles, bool ext) {
   const int64_t rounds = (blocks + 255) / 256, per_cu = (halves + 255) / 256;
   if (per_cu <= 1) return true;
   const double n = tiles;
-  const double wide = (double)rounds * (ext ? 6.5 + 1.06 * n : 6.1 + 1.04 * n);
-  const double pair = ext ? 9.5 + 0.96 * n : 7.8 + 0.88 * n, one = ext ? 6.6 + 0.6 * n : 5.6 + 0.53 * n;
-  return (double)(per_cu / 2) * pair + (per_cu % 2 ? one : 0.0) < wide;
+  const double wide = (double)rounds * (ext ? 6.5 + 1.0 * n : 6.1 + 1.04 * n);
+  const double pair = ext ? 5.0 + 0.98 * n : 7.8 + 0.88 * n, one = ext ? 4.6 + 0.6 * n : 5.6 + 0.53 * n;
+  return (double)(per_cu / 2) * pair + (ext ? 4.0 : 0.0) + (per_cu % 2 ? one : 0.0) < wide;
 }
 template <int kRowD, int kParts>
 void launch_combine_as(const AttnStep& s, hipStream_t st) {

@@ -108,6 +108,8 @@ def test_fp8_kv_d64_ring_against_oracle(lens, flags):
     (26, 1300, 1024, (0, 0), True, False),     # from FP8 the line lies higher
     (27, 2400, 448, (0, 0), True, True),
     (27, 2400, 449, (0, 0), True, False),      # FP8 with dead keys: one work-group to a CU, the rule it had
+    (26, 1300, 3136, (0, 0), True, False),     # and above what a call over whole tiles reaches while the chip takes all work-groups at once
+    (27, 2400, 192, (0, 0), True, True),       # a round less: few tiles are enough
 ])
 def test_d64_two_work_groups_to_a_cu(H, Sq, keys, masked, fp8, split):
     """The form that the rule picks over one chunk, as its flag gives it, against the oracle."""
