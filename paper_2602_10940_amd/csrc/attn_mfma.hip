@@ -1607,7 +1607,9 @@ AttnForm attn_mfma_form(int B, int H, int Sq, int d, int64_t tiles, const RingTr
     const double waited = from_last > from_first ? from_last : from_first;
     return (busy > waited ? busy : waited) + (parts > 1 ? combine + 1.0 : 0.0);
   };
-  if (wgs <= 120) {
+  // (Either rule is asked only where the tiles could pay for its second launch: up to 12 tiles of 0.75 are less than 6 + 3, up to 4 of 0.66 * 1.19
+  // or 0.46 * 1.1 less than 2.3 + 0.35 * 2 or 1.7 + 0.25 * 2.  Calls so short are as fast as the host issues them.)
+  if (wgs <= 120 && (ring || tiles > 12)) {
     const double one = cost(1);
     double least = !ring ? one - 3.0 : 0.96 * one;
     for (int parts = 2; parts <= most && parts * wgs <= 240 && parts <= tiles; ++parts) {
@@ -1615,7 +1617,7 @@ AttnForm attn_mfma_form(int B, int H, int Sq, int d, int64_t tiles, const RingTr
       if (c < least) { least = c; best = {2, parts}; }
     }
   }
-  if (ring || best.parts > 1) return best;
+  if (ring || best.parts > 1 || tiles <= 4) return best;
   double least = 0.97 * chunk_cost(1);
   for (int parts = 2; parts <= most && parts * wgs <= (pairs ? 480 : 240) && parts <= tiles; ++parts) {
     const double c = chunk_cost(parts);
