@@ -745,7 +745,11 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
   };
   constexpr int kPreStep = kSplit ? 2 : 1;   // tiles between two softmax phases of a wave
   const int64_t pre_step = kPreStep * tileB;
-  int left_look = kMulti && s.arrive != nullptr ? kProbeAheadTiles * kTile : 0;
+  // Not where the first chunk (from FP8, a part's first chunk: the other way costs whole rings of either 1 to 2 %, by the code that the compiler makes of it) has six tiles or
+  // less: looked at in the first phases, the count is rarely there yet, and the wait for the loads behind it waits for its way to memory.  us a call, transfers inside,
+  // looked at and not: key-split, 24 heads, 512 queries, two of 384 19.3, 16.8; 384 queries, FP8, two of 320 22.1, 19.3; 256-query, B = 2, 14 heads of 1308, two of 256
+  // 22.5, 17.9, 12 of 1660, d = 64, FP8, two of 192 21.0, 16.9.  Where the count is there early it costs up to 4 %; seven and eight tiles the other way round 0.6 % more.
+  int left_look = kMulti && s.arrive != nullptr && s.chunk[0].Sc - (kExt ? t_beg * kTile : 0) > 6 * kTile ? kProbeAheadTiles * kTile : 0;
   auto look_up = [&]() {
     if (pre.left <= 0) {
       enter(pre);
