@@ -750,6 +750,8 @@ __device__ __forceinline__ void attn_pp_body(const AttnStep& s, unsigned char* s
   // looked at and not: key-split, 24 heads, 512 queries, two of 384 19.3, 16.8; 384 queries, FP8, two of 320 22.1, 19.3; 256-query, B = 2, 14 heads of 1308, two of 256
   // 22.5, 17.9, 12 of 1660, d = 64, FP8, two of 192 21.0, 16.9.  Where the count is there early it costs up to 4 %; seven and eight tiles the other way round 0.6 % more.
   int left_look = kMulti && s.arrive != nullptr && s.chunk[0].Sc - (kExt ? t_beg * kTile : 0) > 6 * kTile ? kProbeAheadTiles * kTile : 0;
+  // (A number from here on, not a condition worked out anew in the loop: the 256-query form of d = 64 from FP8 took 1 to 5 % longer, B = 2, 22 heads of 832, six of 832 87.9, 91.9.)
+  if (kMulti) asm volatile("" : "+s"(left_look));
   auto look_up = [&]() {
     if (pre.left <= 0) {
       enter(pre);
