@@ -1653,7 +1653,7 @@ AttnForm attn_mfma_form(int B, int H, int Sq, int d, int64_t tiles, const RingTr
 // transfers inside 0.90 (1.004 at most); of 130 rings that were not fitted to 20, in 0.91 (0.998) and 0.93 (1.02).  The error against 64 bits is 0.996 of the
 // other form's in the mean (1.003 at most, with outliers 1.08), lse's 0.47 (with outliers 1.0).  The cost per chunk is higher than the chunks at hand ask
 // for, so that many short ones stay 256-query: 408 blocks, 64 tiles, eight chunks 139.5, 132.2, with the transfers inside 148.6, 160.4.  So do less than
-// six tiles in more than one round: 340 blocks, four tiles 18.9, 16.6, with the transfers inside 22.8, 26.1; six 22.4, 19.2 and 26.3, 23.3.  24 heads of 4608,
+// six tiles in more than one round: 340 blocks, four tiles 18.9, 16.6, with the transfers inside 23.0, 26.2; six 22.5, 19.2 and 24.9, 23.3.  24 heads of 4608,
 // two of 2304 154.6, 144.9.  A launch per chunk took 1.02 to 4 times the better one's time throughout (352 tiles in two chunks 525, 512).
 RingForm attn_mfma_ring_form(int B, int H, int Sq, int d, int64_t tiles, int chunks, int variant, bool fp8) {
   const int64_t blocks = (int64_t)B * H * ((Sq + kQPerWG - 1) / kQPerWG), halves = (int64_t)B * H * ((Sq + kQPerWGSplit - 1) / kQPerWGSplit);

@@ -109,7 +109,7 @@ MEASURED_64 = [(2, 22, 4416, 2, 128, (66.2, 66.5, 57.1), (36.7, 34.1), (42.8, 44
                (2, 15, 2149, 6, 384, (86.7, 142.1, 86.1), (82.3, 44.1), (88.9, 66.6)), (2, 22, 1725, 6, 3328, (498.6, 701.5, 494.5), (633.2, 445.0), (634.8, 478.9)),
                (2, 14, 4544, 2, 960, (79.8, 90.6, 80.1), (71.5, 68.6), (83.6, 74.0)), (1, 24, 4608, 2, 2304, (155.4, 171.1, 155.6), (154.6, 144.9), (155.6, 146.5)),
                (1, 17, 4300, 8, 512, (173.4, 230.4, 173.3), (137.9, 100.4), (146.2, 119.7)), (1, 17, 5000, 2, 128, (29.1, 32.8, 29.1), (18.9, 16.6), (22.8, 26.1)),
-               (1, 17, 5000, 2, 192, (31.5, 37.2, 31.6), (22.4, 19.2), (26.3, 23.3)), (2, 24, 3900, 8, 832, (424.0, 498.8, 424.9), (335.8, 316.3), (377.4, 326.9)),
+               (1, 17, 5000, 2, 192, (31.5, 37.1, 31.5), (22.5, 19.2), (24.9, 23.3)), (2, 24, 3900, 8, 832, (424.0, 498.8, 424.9), (335.8, 316.3), (377.4, 326.9)),
                (1, 300, 100, 2, 128, (18.0, 26.3, 18.0), (18.3, 12.0), (31.4, 25.5)), (1, 24, 4096, 12, 128, (205.0, 233.7, 204.7), (60.2, 49.3), (74.4, 68.6)),
                (1, 20, 4608, 2, 11264, (525.3, 733.9, 522.5), (721.6, 511.9), (722.7, 515.3)), (1, 17, 4096, 2, 320, (34.3, 42.9, 34.7), (30.3, 24.1), (32.8, 27.5)),
                (2, 17, 2921, 8, 512, (249.9, 248.9, 221.6), (139.7, 130.5), (150.0, 160.8))]
